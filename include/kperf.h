@@ -332,10 +332,8 @@ kp_status kp_stages_critical(const void* stages, int n_wg, int n_regions, int ma
  * stream's wave leaves the low 12 bits of its hardware id register in kp_wg_hdr.wave_hw_id[]
  * (KP_FLAG_HW_IDS).  The records themselves are the same either way.
  * Bit 27 and the flush strategy go through the generic record sites (a site writes the records of the
- * site before it to LDS); in the 256x256x64 GEMM and the attention kernel every other combination keeps
- * the cheaper chained sites (the loop stores only the clocks of its sites, a fixed sequence, and the
- * records are made from them when the trace is copied out: the same records in the same slots), in the
- * small GEMM bits 28 and 30 and a partial region mask take the generic sites too.
+ * site before it to LDS); every other combination keeps the cheaper chained sites (the loop stores only the clocks of its sites, a fixed sequence, and the
+ * records are made from them when the trace is copied out: the same records in the same slots).
  *
  * trace_buf: device, kp_trace_bytes(n_wg, streams, trace_cap) bytes, 16-byte aligned; headers and
  * records are fully written by the kernel (no pre-zeroing needed; slots beyond total_written
@@ -376,8 +374,10 @@ kp_status kp_gemm_launch_shape(int M, int N, int K, int* n_wg, int* waves_per_wg
  *       this one has a bare scheduling fence and the stages stay apart; with bit 26 (KP_MASK_UNFENCED)
  *       as well the fences are left out and the compiler threads the stages as it likes (for the
  *       comparison of the two; KP_ERR_INVALID_ARG with any region bit or without KP_MASK_PHASES).
- *   otherwise M, N multiples of 64 and K of 32: tile 64x64x32, 4 waves,
- *       0 global load, 1 LDS store, 2 MFMA (each once per K-step)
+ *   otherwise M, N multiples of 64 and K of 32: tile 64x64x32, 4 waves, each once per K-step:
+ *       0 global load (issued here for a K-step up to five further on), 1 LDS store (the tiles of a later K-step
+ *       are stored, behind the operand reads of this one), 2 MFMA (behind every second K-step with the workgroup
+ *       barrier)
  * Other shapes: KP_ERR_UNSUPPORTED_SHAPE.
  */
 kp_status kp_gemm_instrumented(const void* A, const void* B, void* C, int M, int N, int K,
@@ -422,8 +422,8 @@ kp_status kp_attn_instrumented(const void* Q, const void* K, const void* V, void
  * mode bits 4 and 5 select the form of the record sites, which the instrumented kernels also choose
  * among and which decides the constant a region is measured too long by: neither bit the generic sites
  * (region mask, either strategy, either clock, either store), bit 4 the lean sites (all regions, circular
- * strategy: the small GEMM), bit 5 the chained sites of the 256x256x64 GEMM and the attention kernel (the
- * loop keeps only the clocks of the sites, the records are made when the trace is copied out); with
+ * strategy, records written to LDS at the next site), bit 5 the chained sites of the GEMMs and the attention kernel
+ * (the loop keeps only the clocks of the sites, the records are made when the trace is copied out); with
  * either bit, bits 1..3 and 6 must be 0 (KP_ERR_INVALID_ARG otherwise).  mode bit6 selects the
  * store of KP_MASK_COLLAB (all lanes write the record; hardware ids in the workgroup header).
  *   cycles     HOST pointer to n_regions values (n_regions <= 32)

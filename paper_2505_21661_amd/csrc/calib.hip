@@ -46,7 +46,7 @@ __device__ __forceinline__ void busy(uint32_t mode, uint32_t len, float& x) {
 
 // SITE: the form of the record sites (kp_record.h): 1 generic, 2 lean (records written to LDS at the
 // next site), 4 chained (clock reads parked in scalar registers, their clocks stored after the region, the
-// records made when the trace is copied out).  The instrumented kernels use all three; a region costs a
+// records made when the trace is copied out).  The instrumented kernels use the first and the last; a region costs a
 // different constant with each.
 struct CalibChain {  // site 2 r opens region r, site 2 r + 1 closes it (every region enabled)
   static constexpr bool kDense = false;

@@ -8,7 +8,8 @@
 // record into the LDS ring.  Record sites contain no floating point, so all variants produce
 // bit-identical C.
 //
-//   tile 64x64x32, 4 waves  : regions 0 global load, 1 LDS store, 2 MFMA        (per K step)
+//   tile 64x64x32, 4 waves  : per K step regions 0 global load (issue), 1 LDS store (of a later K step, behind
+//                              the operand reads of this one), 2 MFMA
 //   tile 256x256x64, 8 waves: regions 0 / 1 first / second half of a K step's MFMAs with the
 //                              staging of the next K step threaded in, 2 barrier wait, 3 epilogue (once);
 //                              or (KP_MASK_PHASES) a K step whose stages follow one another, each its own
@@ -39,11 +40,6 @@ struct GemmArgs {
   uint32_t flags;       // kp_trace_hdr.flags of the trace
 };
 
-// fp32 -> bf16, round to nearest even (v_cvt_pk_bf16_f32 on gfx950)
-__device__ __forceinline__ uint32_t f32_to_bf16_rne(float f) {
-  const __bf16 h = (__bf16)f;
-  return (uint32_t)__builtin_bit_cast(uint16_t, h);
-}
 // two fp32 -> packed bf16 pair (lo in bits 15:0), round to nearest even: one v_cvt_pk_bf16_f32
 typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 typedef float f32x2 __attribute__((ext_vector_type(2)));
@@ -52,17 +48,14 @@ __device__ __forceinline__ uint32_t bf16_pack_rne(float lo, float hi) {
   return __builtin_bit_cast(uint32_t, __builtin_convertvector(v, bf16x2));
 }
 
-// LDS tiles hold rows of BK bf16 (K contiguous) in 16-byte chunks; chunk c of row r lives at chunk
-// position c ^ swz(r) so that the 16-byte reads of 32 different rows spread over all banks.
+// LDS tiles hold rows of 64 bf16 (K contiguous) in 16-byte chunks; chunk c of row r lives at chunk position
+// c ^ (r / 2) % 8, so that the 16-byte reads of 16 neighbouring rows spread over all banks: two neighbouring rows
+// already differ in the upper half of the 16 chunk positions of a 256-byte bank line, the XOR takes the next three
+// row bits (with row bits 0..2, rows r and r + 8 shared a position, and every operand read took twice as long).
 template <int BK>
 __device__ __forceinline__ uint32_t tile_off(uint32_t row, uint32_t chunk) {
-  constexpr uint32_t CPR = BK / 8;           // chunks per row
-  constexpr uint32_t RPL = 128 / (BK * 2);   // rows per 128-byte bank line (BK <= 64)
-  // With 128-byte rows (BK = 64) two neighbouring rows already differ in the upper half of the 16 chunk
-  // positions of a 256-byte bank line, so the XOR takes row bits 1..3: 16 consecutive rows then cover all
-  // 16 positions (with row bits 0..2, rows r and r + 8 shared one, and every operand read took twice as long).
-  const uint32_t s = BK == 64 ? (row >> 1) % CPR : (row / RPL) % CPR;
-  return row * (BK * 2) + ((chunk ^ s) * 16);  // byte offset
+  static_assert(BK == 64, "128-byte rows");
+  return row * 128u + ((chunk ^ ((row >> 1) & 7u)) << 4);  // byte offset
 }
 
 // Same, for the transposed B tile of the large kernel (BK = 64): its 16-byte writes come from lanes
@@ -73,13 +66,11 @@ __device__ __forceinline__ uint32_t tile_off_bt(uint32_t row, uint32_t chunk) {
 
 // END of one region and START of the next with a single clock sample.  INSTR: 0 no record sites,
 // 1 generic sites (region mask, either buffer strategy, either store), 3 the same on the constant-rate
-// clock, 2 lean sites (small kernel: all regions, circular) or chained sites (large kernel: circular, one
-// lane stores; the region mask and wave-group records included), 5 chained sites on the constant-rate clock.
-// SITE is the form of the sites a kernel uses for INSTR (kp::site<>; 6: chained).
-#define KP_BOUNDARY(ring, end_r, start_r) do { if constexpr (INSTR != 0) kp::site<SITE>(ring, end_r, start_r); } while (0)
-// The same for the large kernel, whose sites are a fixed sequence: chained, the loop keeps only the clock
-// of site K of the batch (kp::site_chain) and KP_COMMIT, which stands right after a wait for all LDS
-// traffic, stores the batch's clocks; the records are made when the trace is copied out.
+// clock, 2 chained sites (circular, one lane stores; the region mask and wave-group records included), 5 chained
+// sites on the constant-rate clock.  SITE is the form of the sites a kernel uses for INSTR (kp::site<>; 6: chained).
+// Chained, the loop keeps only the clock of site K of the batch (kp::site_chain) and KP_COMMIT, which stands
+// right after a wait for all LDS traffic, stores the batch's clocks; the records are made when the trace is
+// copied out (the sites of both kernels are a fixed sequence).
 #define KP_SITE_K(ring, K, end_r, start_r) do { if constexpr (INSTR != 0) { \
     if constexpr (SITE == 6) kp::site_chain<K, (INSTR == 5), kMayCross>(ring); else kp::site<SITE>(ring, end_r, start_r); } } while (0)
 #define KP_COMMIT(ring, N) do { if constexpr (INSTR != 0 && SITE == 6) kp::chain_commit<N>(ring); } while (0)
@@ -115,88 +106,184 @@ struct GemmChain {
 
 // ------------------------------------------------------------------------------------------
 // 64x64x32 tile, 4 waves as 2x2, each wave one 32x32 accumulator tile.
+//
+// What bounds it: with few workgroups the latency of a K step, with many the L1 and LDS traffic of so small a tile
+// (8 KiB through either per workgroup and K step against 64 cycles of MFMAs).  So the global loads run two pairs
+// of K steps ahead in registers, the two LDS stages hold a pair each (one barrier per pair), B is stored as it
+// comes and transposed by the operand read, and up to five workgroups share a CU.  Measured (median of passes in
+// a row), against one stage, loads waited for where they are issued, two barriers per K step: 2112x1984x2080
+// 57 -> 34 us (512 TFLOP/s), 4032x3968x4000 318 -> 233 us, 128x128x3776 (4 workgroups) 53 -> 18 us; with all
+// regions recorded 429 -> 266 us and 73 -> 29 us.  Three pairs ahead: 3 % slower where many workgroups share a CU
+// (registers), nothing gained with few.  Plain order of the tiles instead of bands per XCD: 39 us.
+//
+// The sequence of its record sites (n in all): the first opens region 0, then three per K step close regions
+// 0, 1 and 2 and open the next, the last only closes.
+struct SmallGemmChain {
+  static constexpr uint32_t kRegions = 3u, kLead = 0u;
+  static constexpr bool kDense = true;
+  __device__ uint32_t total(uint32_t n, uint32_t mask) const { return 2u * ((n - 1u) / 3u) * (uint32_t)__builtin_popcount(mask & 7u); }
+  __device__ uint32_t end_region(uint32_t site, uint32_t) const { return site == 0u ? kp::kNoRegion : (site - 1u) % 3u; }
+  __device__ uint32_t start_region(uint32_t site, uint32_t n) const { return site + 1u == n ? kp::kNoRegion : site % 3u; }
+};
+
 template <int INSTR>
 __global__ __launch_bounds__(256) void kp_gemm_small(GemmArgs g) {
-  constexpr int SITE = INSTR;
+  constexpr int SITE = (INSTR == 2 || INSTR == 5) ? 6 : INSTR;
+  constexpr bool REALTIME = INSTR == 3 || INSTR == 5;
+  constexpr int kMayCross = 0;
   constexpr int BM = 64, BN = 64, BK = 32;
-  __shared__ __align__(16) unsigned char sA[BM * BK * 2];
-  __shared__ __align__(16) unsigned char sB[BN * BK * 2];
+  constexpr uint32_t A_BYTES = BM * 2 * BK * 2, STAGE = A_BYTES + BN * 2 * BK * 2;
+  constexpr int AHEAD = 2;  // pairs of K steps between the request of a tile and its use
+  __shared__ __align__(16) unsigned char tiles[2 * STAGE];  // [stage][A rows of 64 k | B rows of 64 n], two K steps each
   extern __shared__ __align__(16) uint32_t ring_lds[];
-  __shared__ uint64_t t_begin[2];
 
   const uint32_t tid = threadIdx.x, lane = tid & 63u, wave = tid >> 6;
-  const uint32_t tiles_n = g.N / BN;
-  const uint32_t wg = blockIdx.x;
-  const uint32_t m0 = (wg / tiles_n) * BM, n0 = (wg % tiles_n) * BN;
+  const uint32_t tiles_m = g.M / BM, tiles_n = g.N / BN;
+  // Workgroups are dealt round-robin to the 8 XCDs: every XCD gets a run of consecutive tiles in an order that
+  // goes down bands of eight tile rows, so that the panels it streams stay in its own L2.
+  uint32_t tile_r, tile_c;
+  {
+    const uint32_t n = tiles_m * tiles_n, xcd = blockIdx.x & 7u, rest = n & 7u;
+    const uint32_t t = xcd * (n >> 3) + (xcd < rest ? xcd : rest) + (blockIdx.x >> 3);
+    const uint32_t band = t / (8u * tiles_n), first = band * 8u, in = t - band * (8u * tiles_n);
+    const uint32_t rows = tiles_m - first < 8u ? tiles_m - first : 8u;
+    tile_c = in / rows;
+    tile_r = first + in - tile_c * rows;
+  }
+  const uint32_t wg = tile_r * tiles_n + tile_c;  // recorded workgroup id = tile index
+  const uint32_t m0 = tile_r * BM, n0 = tile_c * BN;
+
+  // Global -> registers -> LDS, two K steps at a time, so that a row of the A tile is a whole 128-byte line (one
+  // K step of it is half a line, and every line went through the L1 twice): A in the even step of a pair, B in the
+  // odd one, two 16-byte chunks per thread each.  Chunk c of A row r sits at position c ^ (r / 2) % 8 (16 rows of
+  // an operand read cover all banks).  B stays as it lies in memory and is transposed by the operand read (see the
+  // large kernel); chunk c of row k at position c ^ 4 (k / 2 % 2), which spreads the four rows of a read.
+  const uint32_t KT = g.K / BK;
+  const uint32_t row = tid >> 3, chunk = tid & 7u;
+  const uint32_t a_dst = row * 128u + ((chunk ^ ((row >> 1) & 7u)) << 4);              // (row + 32: + 4096)
+  const uint32_t b_dst = A_BYTES + row * 128u + ((chunk ^ (((row >> 1) & 1u) << 2)) << 4);
+  const uint16_t* a_src = g.A + (size_t)(m0 + row) * g.K;
+  const uint16_t* b_src = g.B + n0 + chunk * 8u;
+  u32x4 ra[AHEAD][2], rb[AHEAD][2];
+  // (what lies past the last K step is asked for as the last chunk or row of the matrix and never used)
+  auto request_a = [&](uint32_t pair, int set) __attribute__((always_inline)) {
+    const uint32_t k = pair * (2 * BK) + chunk * 8u, kc = k < g.K ? k : g.K - 8u;
+    ra[set][0] = *reinterpret_cast<const u32x4*>(a_src + kc);
+    ra[set][1] = *reinterpret_cast<const u32x4*>(a_src + (size_t)32u * g.K + kc);
+  };
+  auto request_b = [&](uint32_t pair, int set) __attribute__((always_inline)) {
+    const uint32_t k0 = pair * (2 * BK) + row, k1 = k0 + 32u;
+    rb[set][0] = *reinterpret_cast<const u32x4*>(b_src + (size_t)(k0 < g.K ? k0 : g.K - 1u) * g.N);
+    rb[set][1] = *reinterpret_cast<const u32x4*>(b_src + (size_t)(k1 < g.K ? k1 : g.K - 1u) * g.N);
+  };
+  auto store_a = [&](uint32_t stage, int set) __attribute__((always_inline)) {
+    *reinterpret_cast<u32x4*>(tiles + stage * STAGE + a_dst) = ra[set][0];
+    *reinterpret_cast<u32x4*>(tiles + stage * STAGE + a_dst + 4096u) = ra[set][1];
+  };
+  auto store_b = [&](uint32_t stage, int set) __attribute__((always_inline)) {
+    *reinterpret_cast<u32x4*>(tiles + stage * STAGE + b_dst) = rb[set][0];
+    *reinterpret_cast<u32x4*>(tiles + stage * STAGE + b_dst + 4096u) = rb[set][1];
+  };
+#pragma unroll
+  for (int i = 0; i < AHEAD; ++i) { request_a((uint32_t)i, i); request_b((uint32_t)i, i); }
+
   kp::Ring ring{};
   if constexpr (INSTR != 0)
-    ring = kp::ring_init<true>(ring_lds, t_begin, g.cap_lds, g.region_mask, g.flush, g.cap_hbm, g.trace, g.n_wg, 4u >> g.group_log2, wg,
-                         g.group_log2);
+    ring = kp::ring_init<true>(ring_lds, reinterpret_cast<uint64_t*>(tiles), g.cap_lds, g.region_mask, g.flush, g.cap_hbm, g.trace,
+                         g.n_wg, 4u >> g.group_log2, wg, g.group_log2);
   ring.collab = g.collab;
-  if constexpr (INSTR == 3) kp::ring_use_realtime(ring);
-  kp::sites_begin<SITE>(ring);
-
-  // global -> register mapping
-  // A: 64 rows x 4 chunks = 256 chunks, one per thread
-  const uint32_t a_row = tid >> 2, a_chunk = tid & 3u;
-  const uint16_t* a_src = g.A + (size_t)(m0 + a_row) * g.K + a_chunk * 8;
-  // B: 4 k-groups x 32 column pairs = 128 tasks; threads 128..255 idle for B
-  const uint32_t b_kg = (tid >> 5) & 3u, b_np = tid & 31u;
-  const bool b_on = tid < 128;
-  const uint16_t* b_src = g.B + (size_t)(b_kg * 8) * g.N + n0 + b_np * 2;
+  if constexpr (REALTIME) kp::ring_use_realtime(ring);
+  // (with wave groups the host adds 16 bytes behind the ring for the waves that do not record)
+  if constexpr (SITE == 6) kp::chain_begin(ring, (uint32_t)(uintptr_t)ring_lds + (4u >> g.group_log2) * g.cap_lds * 8u);
+  else kp::sites_begin<SITE>(ring);
 
   const uint32_t wr = wave >> 1, wc = wave & 1u;  // wave position in the 2x2 grid
-  f32x16 acc = {0};
-
-  for (uint32_t kt = 0; kt < g.K / BK; ++kt) {
-    // ---- region 0: global load ---------------------------------------------------------------
-    if (kt == 0) KP_BOUNDARY(ring, kp::kNoRegion, 0); else KP_BOUNDARY(ring, 2, 0);
-    const u32x4 av = *reinterpret_cast<const u32x4*>(a_src + (size_t)kt * BK);
-    uint32_t bv[8];
+  // operand layout of v_mfma_f32_32x32x16_bf16: lane l supplies row/column l%32, k = 8*(l/32)..+7
+  uint32_t a_rd[4], b_rd;
 #pragma unroll
-    for (int i = 0; i < 8; ++i)
-      bv[i] = b_on ? *reinterpret_cast<const uint32_t*>(b_src + ((size_t)kt * BK + i) * g.N) : 0u;
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-    KP_BOUNDARY(ring, 0, 1);
-    // ---- region 1: LDS store -----------------------------------------------------------------
-    __syncthreads();  // previous step's MFMA reads are done
-    *reinterpret_cast<u32x4*>(sA + tile_off<BK>(a_row, a_chunk)) = av;
-    if (b_on) {
-      u32x4 lo, hi;  // column 2*b_np and 2*b_np+1, eight consecutive k each
-      lo.x = __builtin_amdgcn_perm(bv[1], bv[0], 0x05040100u); hi.x = __builtin_amdgcn_perm(bv[1], bv[0], 0x07060302u);
-      lo.y = __builtin_amdgcn_perm(bv[3], bv[2], 0x05040100u); hi.y = __builtin_amdgcn_perm(bv[3], bv[2], 0x07060302u);
-      lo.z = __builtin_amdgcn_perm(bv[5], bv[4], 0x05040100u); hi.z = __builtin_amdgcn_perm(bv[5], bv[4], 0x07060302u);
-      lo.w = __builtin_amdgcn_perm(bv[7], bv[6], 0x05040100u); hi.w = __builtin_amdgcn_perm(bv[7], bv[6], 0x07060302u);
-      *reinterpret_cast<u32x4*>(sB + tile_off<BK>(b_np * 2, b_kg)) = lo;
-      *reinterpret_cast<u32x4*>(sB + tile_off<BK>(b_np * 2 + 1, b_kg)) = hi;
-    }
-    __syncthreads();
-    KP_BOUNDARY(ring, 1, 2);
-    // ---- region 2: MFMA ------------------------------------------------------------------------
-#pragma unroll
-    for (int ks = 0; ks < BK / 16; ++ks) {
-      // operand layout of v_mfma_f32_32x32x16_bf16: lane l supplies row/column l%32, k = 8*(l/32)..+7
-      const uint32_t chunk = ks * 2 + (lane >> 5);
-      const bf16x8 af = *reinterpret_cast<const bf16x8*>(sA + tile_off<BK>(wr * 32 + (lane & 31u), chunk));
-      const bf16x8 bf = *reinterpret_cast<const bf16x8*>(sB + tile_off<BK>(wc * 32 + (lane & 31u), chunk));
-      acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(af, bf, acc, 0, 0, 0);
-    }
-    asm volatile("s_nop 0" ::: "memory");
+  for (int ks = 0; ks < 4; ++ks) {
+    const uint32_t r = wr * 32u + (lane & 31u), c = 2u * (uint32_t)ks + (lane >> 5);
+    a_rd[ks] = r * 128u + ((c ^ ((r >> 1) & 7u)) << 4);
   }
-  KP_BOUNDARY(ring, 2, kp::kNoRegion);
-
-  // epilogue: accumulator register v of lane l is C[row, col] with col = l%32,
-  // row = 8*(v/4) + 4*(l/32) + v%4 inside the wave's 32x32 tile
-  const uint32_t col = n0 + wc * 32 + (lane & 31u);
+  {
+    const uint32_t bi = lane & 15u, bg = lane >> 4;
+    const uint32_t k = 8u * (bg >> 1) + (bi >> 2), n = wc * 32u + 16u * (bg & 1u) + 4u * (bi & 3u);
+    b_rd = A_BYTES + k * 128u + (((n >> 3) ^ (((k >> 1) & 1u) << 2)) << 4) + 8u * ((n >> 2) & 1u);
+  }
+  auto read_b = [&](const unsigned char* stage, int ks) -> bf16x8 {
+    typedef short s16x4 __attribute__((ext_vector_type(4)));
+    typedef short s16x8 __attribute__((ext_vector_type(8)));
+    typedef __attribute__((address_space(3))) s16x4* lds_s16x4;
+    const unsigned char* at = stage + b_rd + (uint32_t)(16 * ks) * 128u;
+    const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4)(at));
+    const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4)(at + 4u * 128u));
+    const s16x8 v = {lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
+    return __builtin_bit_cast(bf16x8, v);
+  };
+  f32x16 acc = {0};  // transposed tile (B^T as the first operand): a lane holds four consecutive columns of a C row
+  store_a(0, 0);
+  store_b(0, 0);
+  asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+  KP_SITE_K(ring, 0, kp::kNoRegion, 0);
+  // K step 2 pair + HALF; the registers of pair p are set p % AHEAD
+  auto step = [&](uint32_t pair, auto half_c, int set, int next) __attribute__((always_inline)) {
+    constexpr int HALF = decltype(half_c)::value;
+    const uint32_t s = pair & 1u;
+    // ---- region 0: the global loads of pair + AHEAD are issued -----------------------------------
+    if (HALF == 0) request_a(pair + AHEAD, set); else request_b(pair + AHEAD, set);
+    KP_SITE_K(ring, 1, 0, 1);
+    // ---- region 1: the operands of this K step are requested from LDS, pair + 1 goes to the other stage
+    // (behind the last pair: nobody reads it).  The requests come first and stay on this side of the site: behind
+    // it they would be waited for together with its clock (29 against 33 us with four workgroups, recorded).
+    const unsigned char* stage = tiles + s * STAGE;
+    bf16x8 af[2], bf[2];
 #pragma unroll
-  for (int v = 0; v < 16; ++v) {
-    const uint32_t row = m0 + wr * 32 + 8 * (v / 4) + 4 * (lane >> 5) + (v % 4);
-    g.C[(size_t)row * g.N + col] = (uint16_t)f32_to_bf16_rne(acc[v]);
+    for (int i = 0; i < 2; ++i) {
+      af[i] = *reinterpret_cast<const bf16x8*>(stage + a_rd[2 * HALF + i]);
+      bf[i] = read_b(stage, 2 * HALF + i);
+    }
+    if (HALF == 0) store_a(s ^ 1u, next); else store_b(s ^ 1u, next);
+    KP_SITE_K(ring, 2, 1, 2);
+    // ---- region 2: MFMA, and behind a pair the barrier after which the other stage may be read and this one
+    // written
+#pragma unroll
+    for (int i = 0; i < 2; ++i) acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(bf[i], af[i], acc, 0, 0, 0);
+    KP_COMMIT(ring, 3);
+    if (HALF == 1) asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+    if (2u * pair + HALF + 1u < KT) KP_SITE_K(ring, 0, 2, 0); else KP_SITE_K(ring, 0, 2, kp::kNoRegion);
+  };
+  constexpr std::integral_constant<int, 0> even{};
+  constexpr std::integral_constant<int, 1> odd{};
+  static_assert(AHEAD == 2, "the K loop is unrolled by two pairs");
+  for (uint32_t pair = 0;; pair += 2u) {
+    step(pair, even, 0, 1);
+    if (2u * pair + 1u >= KT) break;
+    step(pair, odd, 0, 1);
+    if (2u * pair + 2u >= KT) break;
+    step(pair + 1u, even, 1, 0);
+    if (2u * pair + 3u >= KT) break;
+    step(pair + 1u, odd, 1, 0);
+    if (2u * pair + 4u >= KT) break;
+  }
+
+  // epilogue, transposed tile: register v of lane l is C[m, n] with m = l%32 and n = 8*(v/4) + 4*(l/32) + v%4
+  uint16_t* c_row = g.C + (size_t)(m0 + wr * 32u + (lane & 31u)) * g.N + n0 + wc * 32u + 4u * (lane >> 5);
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    u32x2 pk;
+    pk.x = bf16_pack_rne(acc[4 * q + 0], acc[4 * q + 1]);
+    pk.y = bf16_pack_rne(acc[4 * q + 2], acc[4 * q + 3]);
+    *reinterpret_cast<u32x2*>(c_row + 8 * q) = pk;
   }
   if constexpr (INSTR != 0) {
     kp::TraceGeom tg{g.n_wg, 4u >> g.group_log2, 3, g.cap_hbm, g.flags};
-    kp::sites_end<SITE>(ring);
-    kp::ring_finish<INSTR == 3>(ring, g.cap_lds, g.trace, tg, wg, g.rec_cost);
+    if constexpr (SITE == 6) {
+      kp::chain_commit<1>(ring);  // the site that closed the last K step
+      kp::ring_finish<REALTIME>(ring, g.cap_lds, g.trace, tg, wg, g.rec_cost, SmallGemmChain{});
+    } else {
+      kp::sites_end<SITE>(ring);
+      kp::ring_finish<REALTIME>(ring, g.cap_lds, g.trace, tg, wg, g.rec_cost);
+    }
   }
 }
 
@@ -714,16 +801,15 @@ extern "C" kp_status kp_gemm_instrumented(const void* A, const void* B, void* C,
   const size_t ring_bytes = (size_t)cap_lds * 8 * streams + (group_log2 ? 16 : 0);  // (16: see chain_begin)
   if (ring_bytes > 32 * 1024) return kp::fail(KP_ERR_UNSUPPORTED_SHAPE, "LDS ring of %zu bytes exceeds the 32 KiB budget", ring_bytes);
   g.cap_lds = cap_lds; g.cap_hbm = (uint32_t)cap_wave; g.rec_cost = kp::rec_cost();
-  // small kernel: every region, circular, and fewer than 2^20 records per wave (6 per K step): lean record sites
-  const bool lean = !flush && !group_log2 && !realtime && !collab && regions == (1u << s.regions) - 1u && K <= (1 << 22);
-  // The large kernel chains its sites whenever the strategy is circular and one lane stores: the region mask,
+  // Both kernels chain their sites whenever the strategy is circular and one lane stores: the region mask,
   // wave-group records and the constant-rate clock all keep that form.
   const bool chained = !flush && !collab;
   if (big) return chained ? (realtime ? launch_big_w<5>(phased, g, n_wg, ring_bytes, st) : launch_big_w<2>(phased, g, n_wg, ring_bytes, st))
                           : (realtime ? launch_big_w<3>(phased, g, n_wg, ring_bytes, st) : launch_big_w<1>(phased, g, n_wg, ring_bytes, st));
-  if (lean) hipLaunchKernelGGL(kp_gemm_small<2>, dim3(n_wg), dim3(256), ring_bytes, st, g);
+  if (chained && realtime) hipLaunchKernelGGL(kp_gemm_small<5>, dim3(n_wg), dim3(256), ring_bytes, st, g);
+  else if (chained) hipLaunchKernelGGL(kp_gemm_small<2>, dim3(n_wg), dim3(256), ring_bytes, st, g);
   else if (realtime) hipLaunchKernelGGL(kp_gemm_small<3>, dim3(n_wg), dim3(256), ring_bytes, st, g);
-  else      hipLaunchKernelGGL(kp_gemm_small<1>, dim3(n_wg), dim3(256), ring_bytes, st, g);
+  else hipLaunchKernelGGL(kp_gemm_small<1>, dim3(n_wg), dim3(256), ring_bytes, st, g);
   KP_HIP_TRY(hipGetLastError());
   return KP_OK;
 }

@@ -225,7 +225,8 @@ __device__ __forceinline__ void boundary(Ring& r, uint32_t end_region, uint32_t 
   __builtin_amdgcn_sched_barrier(0);
 }
 
-// The same site for the common case "every region enabled, circular strategy", without a branch.
+// The same site for the case "every region enabled, circular strategy", without a branch (the calibration kernel
+// measures it next to the other two forms).
 // Every instruction here is paid once per wave and site (a wave issues roughly one instruction
 // every four to five cycles and all waves of a workgroup reach their sites together), so the site
 // is kept to about twenty instructions:

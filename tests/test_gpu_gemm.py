@@ -278,6 +278,40 @@ def test_big_tile_chained_sites_write_the_generic_sites_records(kp, phased, regi
     assert (ts.reshape(n_wg, -1).max(axis=1) < span[:, 0]).all()
 
 
+@pytest.mark.parametrize("K,regions,opts", [(32, 0b111, "0"), (64, 0b111, "0"), (96, 0b101, "0"), (128, 0b010, "group"),
+                                            (160, 0b111, "realtime"), (224, 0b110, "group"), (1056, 0b111, "0"), (2080, 0b100, "realtime")])
+def test_small_tile_k_pairs_and_chained_sites(kp, K, regions, opts):
+    """The 64x64x32 tile handles its K steps in pairs, two pairs ahead: K of one step, of whole pairs and of an odd
+    number of steps, on a tile grid whose bands (eight tile rows) and shares per XCD are not even.  C against the
+    fp64 oracle and bit-identical with and without sites; the records its chained sites leave against those of the
+    generic ones (KP_MASK_COLLAB), in a ring that holds everything or wraps."""
+    M, N, cap_stream = 64 * 9, 64 * 5, 64
+    a, b = inputs.gemm_inputs(M, N, K, seed=K)
+    c0, _, (n_wg, waves, _) = run_gemm(kp, a, b, 0)
+    assert (n_wg, waves) == (45, 4)
+    assert_close_to_oracle(c0, a, b)
+    A, B = a.cuda(), b.cuda()
+    streams = 1 if opts == "group" else 4
+    mask = regions | {"0": 0, "group": kp.KP_MASK_WAVE_GROUP, "realtime": kp.KP_MASK_REALTIME}[opts]
+    raws = []
+    for extra in (0, kp.KP_MASK_COLLAB):
+        C = torch.empty(M, N, dtype=torch.bfloat16, device="cuda")
+        trace = torch.full((kp.kp_trace_bytes(n_wg, streams, cap_stream * streams),), 0x77, dtype=torch.uint8, device="cuda")
+        kp.kp_gemm_instrumented(A, B, C, M, N, K, mask | extra, trace, cap_stream * streams)
+        torch.cuda.synchronize()
+        assert torch.equal(C.view(torch.int16), c0.view(torch.int16))
+        raws.append(trace.cpu().numpy().view(np.uint32).copy())
+    (hx, rx), (hy, ry) = (_streams_of(r, n_wg, streams, cap_stream) for r in raws)
+    total = 2 * (K // 32) * bin(regions).count("1")
+    n = min(total, cap_stream)
+    assert (hx[:, 0] == np.arange(n_wg)).all()
+    assert (hx[:, 8:8 + streams] == total).all() and (hx[:, 8:24] == hy[:, 8:24]).all()
+    assert (rx[:, :, :n, 0] == ry[:, :, :n, 0]).all() and (rx[:, :, n:] == 0).all()
+    order = np.argsort(rx[:, :, :n, 0] & 0xFFFFF, axis=2)
+    ts = np.take_along_axis(rx[:, :, :n, 1], order, 2).astype(np.int64)
+    assert (np.diff(ts, axis=2) >= 0).all() and (ts > 0).all()
+
+
 def _streams_of(raw, n_wg, streams, cap):
     hdr = raw[16:16 + 32 * n_wg].reshape(n_wg, 32)
     return hdr, raw[16 + 32 * n_wg:].reshape(n_wg, streams, cap, 2)
