@@ -24,6 +24,68 @@ __host__ __device__ inline StatsLayout stats_layout(uint32_t n_wg, uint32_t W, u
   return l;
 }
 
+// Lane l receives the value of lane l-1; lane 0 receives `lane0` (DPP wave shift right by one).
+__device__ __forceinline__ uint32_t wave_shr1(uint32_t v, uint32_t lane0) {
+  return (uint32_t)__builtin_amdgcn_update_dpp((int)lane0, (int)v, 0x138, 0xF, 0xF, false);
+}
+
+// The DPP steps of an inclusive scan over the 64 lanes: four shifts inside each row of 16, then the
+// last lane of row 0/2 into row 1/3 and the last lane of the lower half into the upper half.  Lanes
+// without a source read 0.
+template <int STEP> __device__ __forceinline__ uint32_t scan_src(uint32_t v) {
+  if (STEP == 0) return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x111, 0xF, 0xF, false);  // row_shr:1
+  if (STEP == 1) return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x112, 0xF, 0xF, false);  // row_shr:2
+  if (STEP == 2) return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x114, 0xF, 0xF, false);  // row_shr:4
+  if (STEP == 3) return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x118, 0xF, 0xF, false);  // row_shr:8
+  if (STEP == 4) return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x142, 0xA, 0xF, false);  // row_bcast:15
+  return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x143, 0xC, 0xF, false);                 // row_bcast:31
+}
+
+__device__ __forceinline__ uint32_t wave_scan_add(uint32_t v) {
+  v += scan_src<0>(v); v += scan_src<1>(v); v += scan_src<2>(v);
+  v += scan_src<3>(v); v += scan_src<4>(v); v += scan_src<5>(v);
+  return v;
+}
+
+// Batcher's odd-even merge sort of N registers: a fixed network (63 exchanges for 16 words, 384 for 48),
+// every index known at compile time.
+template <int N, typename T>
+__device__ __forceinline__ void network_sort(T (&key)[N]) {
+#pragma unroll
+  for (int pp = 1; pp < N; pp <<= 1) {
+#pragma unroll
+    for (int k = pp; k >= 1; k >>= 1) {
+#pragma unroll
+      for (int j = k % pp; j + k < N; j += 2 * k) {
+#pragma unroll
+        for (int i = 0; i < (k < N - j - k ? k : N - j - k); ++i) {
+          if ((i + j) / (2 * pp) == (i + j + k) / (2 * pp)) {
+            const T x = key[i + j], y = key[i + j + k];
+            key[i + j] = x < y ? x : y;
+            key[i + j + k] = x < y ? y : x;
+          }
+        }
+      }
+    }
+  }
+}
+
+// Ascending order of N (a power of two) registers that first rise and then fall, or the reverse.
+template <int N, typename T>
+__device__ __forceinline__ void bitonic_merge(T (&v)[N]) {
+#pragma unroll
+  for (int k = N / 2; k >= 1; k >>= 1) {
+#pragma unroll
+    for (int i = 0; i < N; ++i) {
+      if ((i & k) == 0) {
+        const T x = v[i], y = v[i + k];
+        v[i] = x < y ? x : y;
+        v[i + k] = x < y ? y : x;
+      }
+    }
+  }
+}
+
 // The main kernel of the decoder for geometries the LDS-resident one does not take (more than 32
 // regions, more than 16384 record slots per workgroup).  Between the init and finalize kernels, on the
 // same stream; accumulates into the block exactly as the LDS-resident kernel does (histogram, sums,

@@ -102,29 +102,6 @@ struct Lds {
 // 64 lanes of a wave reading 16 consecutive words each (64 bytes apart) spread over all banks.
 __device__ __forceinline__ uint32_t clk_word(uint32_t i) { return i + ((i >> 6) << 2); }
 
-// Lane l receives the value of lane l-1; lane 0 receives `lane0` (DPP wave shift right by one).
-__device__ __forceinline__ uint32_t wave_shr1(uint32_t v, uint32_t lane0) {
-  return (uint32_t)__builtin_amdgcn_update_dpp((int)lane0, (int)v, 0x138, 0xF, 0xF, false);
-}
-
-// The DPP steps of an inclusive scan over the 64 lanes: four shifts inside each row of 16, then the
-// last lane of row 0/2 into row 1/3 and the last lane of the lower half into the upper half.  Lanes
-// without a source read 0.
-template <int STEP> __device__ __forceinline__ uint32_t scan_src(uint32_t v) {
-  if (STEP == 0) return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x111, 0xF, 0xF, false);  // row_shr:1
-  if (STEP == 1) return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x112, 0xF, 0xF, false);  // row_shr:2
-  if (STEP == 2) return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x114, 0xF, 0xF, false);  // row_shr:4
-  if (STEP == 3) return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x118, 0xF, 0xF, false);  // row_shr:8
-  if (STEP == 4) return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x142, 0xA, 0xF, false);  // row_bcast:15
-  return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x143, 0xC, 0xF, false);                 // row_bcast:31
-}
-
-__device__ __forceinline__ uint32_t wave_scan_add(uint32_t v) {
-  v += scan_src<0>(v); v += scan_src<1>(v); v += scan_src<2>(v);
-  v += scan_src<3>(v); v += scan_src<4>(v); v += scan_src<5>(v);
-  return v;
-}
-
 // Sum over the wave, added to tmp[which] by the last lane.
 __device__ __forceinline__ void add_tmp(uint32_t* tmp, int which, uint32_t v) {
   v = wave_scan_add(v);
@@ -150,44 +127,6 @@ __device__ __forceinline__ void planes_step(uint32_t (&pl)[PLANES], uint32_t x, 
   uint32_t carry = x;
 #pragma unroll
   for (int k = 0; k < PLANES; ++k) { const uint32_t o = pl[k]; pl[k] = o ^ carry; carry &= o ^ dm; }
-}
-
-// Batcher's odd-even merge sort of N registers: a fixed network (63 exchanges for 16 words, 384 for 48),
-// every index known at compile time.
-template <int N>
-__device__ __forceinline__ void network_sort(uint32_t (&key)[N]) {
-#pragma unroll
-  for (int pp = 1; pp < N; pp <<= 1) {
-#pragma unroll
-    for (int k = pp; k >= 1; k >>= 1) {
-#pragma unroll
-      for (int j = k % pp; j + k < N; j += 2 * k) {
-#pragma unroll
-        for (int i = 0; i < (k < N - j - k ? k : N - j - k); ++i) {
-          if ((i + j) / (2 * pp) == (i + j + k) / (2 * pp)) {
-            const uint32_t x = key[i + j], y = key[i + j + k];
-            key[i + j] = x < y ? x : y;
-            key[i + j + k] = x < y ? y : x;
-          }
-        }
-      }
-    }
-  }
-}
-
-// Ascending order of 8 registers that first rise and then fall (or the reverse): 12 exchanges.
-__device__ __forceinline__ void bitonic_merge8(uint32_t (&v)[8]) {
-#pragma unroll
-  for (int k = 4; k >= 1; k >>= 1) {
-#pragma unroll
-    for (int i = 0; i < 8; ++i) {
-      if ((i & k) == 0) {
-        const uint32_t x = v[i], y = v[i + k];
-        v[i] = x < y ? x : y;
-        v[i + k] = x < y ? y : x;
-      }
-    }
-  }
 }
 
 // The sweep works on one word per record of the sequence: clock << 6 | region << 1 | END; records with
@@ -245,25 +184,10 @@ __device__ __forceinline__ void sorted_own(uint32_t* clk, uint32_t tid, uint32_t
       lo[i] = key[7 - i] > bw[i] ? key[7 - i] : bw[i];         // upper 8 of (upper half below, own lower half)
       hi[i] = key[8 + i] < aw[7 - i] ? key[8 + i] : aw[7 - i];  // lower 8 of (own upper half, lower half above)
     }
-    bitonic_merge8(lo);
-    bitonic_merge8(hi);
+    bitonic_merge<8>(lo);
+    bitonic_merge<8>(hi);
 #pragma unroll
     for (int i = 0; i < 8; ++i) { key[i] = lo[i]; key[8 + i] = hi[i]; }
-  }
-}
-
-// Ascending order of 16 registers that first rise and then fall (or the reverse): 32 exchanges.
-__device__ __forceinline__ void bitonic_merge16(uint32_t (&v)[kNR]) {
-#pragma unroll
-  for (int k = 8; k >= 1; k >>= 1) {
-#pragma unroll
-    for (int i = 0; i < kNR; ++i) {
-      if ((i & k) == 0) {
-        const uint32_t x = v[i], y = v[i + k];
-        v[i] = x < y ? x : y;
-        v[i + k] = x < y ? y : x;
-      }
-    }
   }
 }
 
@@ -309,7 +233,7 @@ __device__ __forceinline__ void sorted_pairs(uint32_t* clk, uint32_t tid, uint32
       const uint32_t lo = x < y ? x : y, hi = x < y ? y : x;
       key[i] = upper ? hi : lo;
     }
-    bitonic_merge16(key);
+    bitonic_merge<kNR>(key);
     if (round == 0) __syncthreads();  // every lane has read its partner's run before it is overwritten
   }
 }

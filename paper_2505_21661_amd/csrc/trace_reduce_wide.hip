@@ -10,23 +10,34 @@
 //      later slot wins: atomic max into a rank -> slot table); a workgroup with more such records
 //      than the list holds scans all its slots for every range instead;
 //   1  pairing (an END is paired iff the nearest earlier record of its wave and region is a START):
-//      hardware wave w walks recorded wave w, 64 ranks at a time, one per lane; the lanes that hold a
-//      lane's region come from one ballot per bit of the region number, the last record of every region
-//      in the ranks before from a table in LDS.  Durations go to the histogram and the region's extrema
-//      in LDS and to the (workgroup, wave, region) row in HBM with atomics; a paired START and END each
-//      set their bit in a bitmap of the workgroup's ranks;
+//      the hardware waves share out the recorded waves in runs of consecutive ranks and walk them 64
+//      ranks at a time, one per lane; the lanes that hold a lane's region come from one ballot per bit
+//      of the region number, the last record of every region in the ranks before from a table in LDS
+//      (only where some END does not have its START right below it).  A run does not know what came before
+//      it, so it also keeps the ENDs that found no earlier record of their region, and one thread per
+//      (wave, region) joins the runs afterwards.  Durations go to the histogram and to
+//      the (wave, region) rows with atomics; a paired START and END each set their bit in a bitmap of the
+//      workgroup's ranks;
 //   2  overlap, a window of time at a time: every wave offers its next range of ranks, the window
-//      ends at the earliest last clock among the waves that have more to offer, the marked records
-//      inside the window are sorted by clock (bitonic, in LDS) and swept.  Each hardware wave sweeps a
-//      slab of the sorted events, two events per lane: LDS atomics give the slab's net change of the
-//      number of waves that have each region open, a prefix over the slabs the numbers at the slab's
-//      start, ballots over the events of a region the number right before each event.  The time two
-//      regions are both open is the sum over the ends of their common stretches minus the sum over the
-//      beginnings; a common stretch of a and b begins when one of them opens while the other is open
-//      and ends when one closes while the other is open, so every event that opens or closes a region
-//      adds its clock, signed, to the sums of that region with every open region (modulo 2^64: the
-//      total is exact).
+//      ends at the earliest last clock among the waves that have more to offer, and the marked records
+//      inside the window are sorted by clock: a counting sort into as many cells of time as the window
+//      has places, then lanes take consecutive records and finish the order in registers (with fuller
+//      cells: every record counts the records of its cell that come before it).  The number of waves that
+//      have each region open is kept bit-sliced (plane k = bit k of every region's count): each lane's net
+//      change, a scan over lanes and hardware waves, the state before each lane's records.  The total time two regions are both open is the sum over the ends of
+//      their common stretches minus the sum over the beginnings; a common stretch of a and b begins
+//      when one of them opens while the other is open and ends when one closes while the other is
+//      open, so every event that opens or closes a region adds its clock, signed, to the sums of that
+//      region with every open region (modulo 2^64: the total is exact).
 // Nothing but the inputs and the statistics block is touched in HBM.
+//
+// What bounds it: the latency of its steps (16 hardware waves in lockstep between some ten barriers per window),
+// then LDS and instruction issue in about equal parts.  So a window is as large as LDS allows (8192 records: a
+// third of a workgroup's usual ring), the order is finished in registers, and nothing is done per region.  Measured
+// on 1024 workgroups of 8 waves x 4096 records with 48 regions (268 MB), merging 2048 records at a time in LDS and
+// walking the regions one by one in the sweep before: 2594 -> 685 us (passes 0 and 1: 640 -> 187 us, of which 220 us
+// were a device-wide fence per workgroup; the sweep: 220 us, half of it the sums of the region pairs).  Keys of 64
+// bits in the register sort: 698 us.  Requesting a window's records under the sweep before it: 743 us (registers).
 #include "kp_reduce.h"
 #include "kp_stage.h"
 
@@ -36,53 +47,80 @@ using namespace kp_reduce;
 
 constexpr int kBlock = 1024;
 constexpr uint32_t kWavesHw = kBlock / 64;
-constexpr uint32_t kK = 2048;               // records in LDS at a time: 2 per thread
+constexpr uint32_t kTable = 2048;           // ranks whose winning slots pass 1 looks up at a time
+constexpr uint32_t kMinWindow = 2048, kAreaMin = 32768;  // smallest window of pass 2, and the LDS that it and pass 1 share at least
 constexpr uint32_t kListMin = 512, kListMax = 8192;  // records outside the slot of their seq that a workgroup can list: what LDS has room for
-constexpr uint32_t kSlab = kK / kWavesHw;   // sorted events per hardware wave
+constexpr uint32_t kMaxCell = 64;           // fullest time cell in which records are ranked by comparing each with each
 constexpr uint32_t kSeqMask = 0xFFFFFu;
 constexpr uint32_t kHistStride = 65;        // histogram rows 65 words apart: equal bins of different regions, different banks
-constexpr uint32_t kRegStride = 128;        // per-slab tables: one entry per region the tag can name
+constexpr uint32_t kMaxPlanes = 4 * 5;      // words of a bit-sliced count of every region the tag can name
 constexpr uint64_t kNoKey = ~0ull;
+constexpr uint32_t kNoId = 0xFFFFu;          // END << 7 | region of no record
 constexpr uint32_t kMaxLds = 160 * 1024;
 
 // per-workgroup temporaries (u32 words in LDS)
-enum { T_FIELDVALID = 0, T_DISORDER, T_OCCUPIED, T_WINNER_DISORDER, T_NONMONO, T_PAIRS, T_ORPHAN_START, T_ORPHAN_END, T_WINDOW_END,
-       T_ADVANCED, T_LISTED, T_COUNT };
+enum { T_FIELDVALID = 0, T_DISORDER, T_OCCUPIED, T_WINNER_DISORDER, T_NONMONO, T_PAIRS, T_ENDS, T_WINDOW_BEGIN,
+       T_WINDOW_END, T_WINDOW_LAST, T_MAXCELL, T_EVENTS, T_LISTED, T_COUNT };
 
 struct WideLds {  // byte offsets
-  uint32_t keys, table, bitmap, otri, hist, reg_sum, reg_max, reg_min, n_open, slab_delta, ctr, tmp, vf, pos, adv, seen, rows, list, total;
-  uint32_t rows_in_lds, list_cap;
+  uint32_t last, head, rows, row_min, table;  // pass 1
+  uint32_t cells, totals;                     // pass 2, behind the keys, which start at 0
+  uint32_t bitmap, otri, hist, reg_sum, reg_max, reg_min, ctr, tmp, vf, pos, adv, edge, list, total;
+  uint32_t per_lane, split_log2, rows_in_lds, list_cap;
 };
 inline uint32_t up16(uint32_t x) { return (x + 15u) & ~15u; }
-WideLds wide_lds(uint32_t W, uint32_t R, uint32_t nrec) {
+// LDS byte address of a place of the sorted sequence: 16 bytes of padding after every 256, so that lanes that
+// read 8 consecutive places each, 64 bytes apart, spread over all banks.
+__host__ __device__ constexpr uint32_t key_at(uint32_t place) { return place * 8u + ((place >> 5) << 4); }
+
+// per_lane: records of a window per lane; split_log2: runs per recorded wave in pass 1
+WideLds lay_out(uint32_t W, uint32_t R, uint32_t nrec, uint32_t per_lane, uint32_t split_log2, bool rows_in_lds) {
   WideLds l;
-  l.keys = 0;
-  l.table = l.keys + kK * 8;
-  l.bitmap = l.table + kK * 4;
+  l.per_lane = per_lane; l.split_log2 = split_log2; l.rows_in_lds = rows_in_lds ? 1u : 0u;
+  const uint32_t runs_bytes = (W << split_log2) * R * 8u;
+  l.last = 0;
+  l.head = l.last + runs_bytes;
+  l.rows = up16(l.head + (split_log2 ? runs_bytes : 0u));
+  l.row_min = l.rows + (rows_in_lds ? W * R * 16u : 0u);
+  l.table = up16(l.row_min + (rows_in_lds ? W * R * 4u : 0u));
+  const uint32_t pass1 = l.table + kTable * 4u;
+  l.cells = key_at(kBlock * per_lane);
+  l.totals = l.cells + kBlock * per_lane * 2u;
+  const uint32_t pass2 = l.totals + kWavesHw * kMaxPlanes * 4u;
+  uint32_t area = pass1 > pass2 ? pass1 : pass2;
+  area = area > kAreaMin ? area : kAreaMin;
+  l.bitmap = up16(area);
   l.otri = up16(l.bitmap + ((nrec + 31) / 32) * 4);
   l.hist = l.otri + R * (R + 1) / 2 * 8;
   l.reg_sum = up16(l.hist + R * kHistStride * 4);
   l.reg_max = l.reg_sum + R * 8;
   l.reg_min = l.reg_max + R * 4;
-  l.n_open = up16(l.reg_min + R * 4);
-  l.slab_delta = l.n_open + kRegStride * 4;
-  l.ctr = l.slab_delta + kWavesHw * kRegStride * 4;
+  l.ctr = up16(l.reg_min + R * 4);
   l.tmp = l.ctr + 16 * 8;
   l.vf = l.tmp + 16 * 4;
   static_assert(T_COUNT <= 16, "temporaries");
   l.pos = l.vf + 32 * 8;
   l.adv = l.pos + 16 * 4;
-  l.seen = l.adv + 16 * 4;
-  l.rows = l.seen + kWavesHw * 16;
-  // what is left goes to the (wave, region) rows of the workgroup in flight, if they fit next to the
-  // smallest list, and then to the list
-  const uint32_t rows_bytes = W * R * 16;
-  l.rows_in_lds = l.rows + rows_bytes + kListMin * 8 <= kMaxLds ? 1u : 0u;
-  l.list = l.rows + (l.rows_in_lds ? rows_bytes : 0u);
+  l.edge = l.adv + 16 * 4;
+  l.list = l.edge + kWavesHw * 16;
   l.list_cap = kListMin;
-  while (l.list_cap < kListMax && l.list + l.list_cap * 2 * 8 <= kMaxLds) l.list_cap *= 2;
+  while (l.list_cap < kListMax && l.list + l.list_cap * 2 * 8 <= kMaxLds) l.list_cap *= 2;  // what is left
   l.total = l.list + l.list_cap * 8;
   return l;
+}
+// The largest window that LDS has room for (beside a list of twice the smallest size), with the rows of the
+// (wave, region) sums in LDS and the recorded waves cut into as many runs as there are hardware waves for;
+// failing that with fewer runs; the smallest window also with the rows in HBM.
+WideLds wide_lds(uint32_t W, uint32_t R, uint32_t cap) {
+  uint32_t most = 0;
+  while ((W << (most + 1)) <= kWavesHw && (cap >> (most + 1)) >= 256u) ++most;
+  for (uint32_t per_lane = 8; per_lane >= 2; per_lane >>= 1) {
+    for (uint32_t split = most + 1; split-- > 0;) {
+      const WideLds l = lay_out(W, R, W * cap, per_lane, split, true);
+      if (l.total <= kMaxLds && (per_lane == 2 || l.list_cap > kListMin)) return l;
+    }
+  }
+  return lay_out(W, R, W * cap, 2, 0, false);
 }
 
 struct WideParams {
@@ -90,7 +128,7 @@ struct WideParams {
   const uint2* records;     // {tag, payload}
   uint64_t* out;
   uint32_t n_wg, W, R, cap, cap_log2, rec_cost, flush, nrec;
-  uint32_t range_log2;      // ranks of one wave in LDS at a time: kK >> ceil(log2 W)
+  uint32_t waves_log2;      // ceil(log2 W): a window offers (window places >> this) ranks of every wave
   WideLds lds;
 };
 
@@ -99,31 +137,88 @@ __device__ __forceinline__ uint32_t wave_sum(uint32_t v) {
   return v;
 }
 
+// Bit-sliced counters of up to 32 NW regions: plane k of word w holds bit k of the counts of regions 32 w ..
+template <int NW, int P> struct Planes { uint32_t at[NW][P]; };
+template <int NW, int P>
+__device__ __forceinline__ void planes_add(Planes<NW, P>& a, const Planes<NW, P>& b) {
+#pragma unroll
+  for (int w = 0; w < NW; ++w) {
+    uint32_t c = 0;
+#pragma unroll
+    for (int k = 0; k < P; ++k) {
+      const uint32_t s = a.at[w][k] ^ b.at[w][k], g = a.at[w][k] & b.at[w][k];
+      a.at[w][k] = s ^ c;
+      c = g | (s & c);
+    }
+  }
+}
+// count of `region` += 1, or -= 1 where down is all ones; nothing where on is zero
+template <int NW, int P>
+__device__ __forceinline__ void planes_step(Planes<NW, P>& p, uint32_t region, uint32_t on, uint32_t down) {
+  const uint32_t bit = on << (region & 31u);
+#pragma unroll
+  for (int w = 0; w < NW; ++w) {
+    uint32_t carry = (NW == 1 || (region >> 5) == (uint32_t)w) ? bit : 0u;
+#pragma unroll
+    for (int k = 0; k < P; ++k) { const uint32_t o = p.at[w][k]; p.at[w][k] = o ^ carry; carry &= o ^ down; }
+  }
+}
+template <int NW, int P>
+__device__ __forceinline__ uint32_t planes_any(const Planes<NW, P>& p, int w) {  // regions of word w with a count above zero
+  uint32_t v = p.at[w][0];
+#pragma unroll
+  for (int k = 1; k < P; ++k) v |= p.at[w][k];
+  return v;
+}
+template <int STEP, int NW, int P>
+__device__ __forceinline__ void planes_scan_step(Planes<NW, P>& p) {
+  Planes<NW, P> o;
+#pragma unroll
+  for (int w = 0; w < NW; ++w)
+#pragma unroll
+    for (int k = 0; k < P; ++k) o.at[w][k] = scan_src<STEP>(p.at[w][k]);
+  planes_add<NW, P>(p, o);
+}
+
+// E: records of a window per lane; NW: 32-bit words that hold one bit per region; P: bits of a count of waves.
+template <int E, int NW, int P>
 __global__ __launch_bounds__(kBlock) void kp_reduce_wide(WideParams p) {
   extern __shared__ __align__(16) unsigned char smem[];
-  unsigned long long* keys = reinterpret_cast<unsigned long long*>(smem + p.lds.keys);
-  uint32_t* table = reinterpret_cast<uint32_t*>(smem + p.lds.table);    // rank -> winning slot + 1, for the ranks in LDS
+  constexpr uint32_t K = kBlock * E;  // places of a window
+  // [run][region] its last record: (rank + 1) << 33 | END << 32 | clock, 0 for none; so the latest is the largest
+  unsigned long long* last_all = reinterpret_cast<unsigned long long*>(smem + p.lds.last);
+  uint2* head_all = reinterpret_cast<uint2*>(smem + p.lds.head);        // {clock, 1 << 31 | rank} of its first record if that is an END (waves cut into runs)
+  uint32_t* table1 = reinterpret_cast<uint32_t*>(smem + p.lds.table);   // rank -> winning slot + 1, kTable ranks at a time (pass 1)
+  uint32_t* table2 = reinterpret_cast<uint32_t*>(smem);                 // the same for the ranks a window looks at (before its keys are written)
+  uint32_t* cells = reinterpret_cast<uint32_t*>(smem + p.lds.cells);    // cell c: half (c & 1) of word c >> 1
   // the records outside the slot of their seq: (wave << 20 | rank) << 20 | slot, sorted
   unsigned long long* list = reinterpret_cast<unsigned long long*>(smem + p.lds.list);
   uint32_t* rows_lds = reinterpret_cast<uint32_t*>(smem + p.lds.rows);  // {u64 sum; u32 n; u32 max} per (wave, region), if p.lds.rows_in_lds
+  uint32_t* row_min = reinterpret_cast<uint32_t*>(smem + p.lds.row_min);
   uint32_t* bitmap = reinterpret_cast<uint32_t*>(smem + p.lds.bitmap);  // bit wave * cap + rank: the record is a paired START or END
   unsigned long long* otri = reinterpret_cast<unsigned long long*>(smem + p.lds.otri);  // pair (a <= b) at b (b + 1) / 2 + a
   uint32_t* hist = reinterpret_cast<uint32_t*>(smem + p.lds.hist);
   unsigned long long* reg_sum = reinterpret_cast<unsigned long long*>(smem + p.lds.reg_sum);
   uint32_t* reg_max = reinterpret_cast<uint32_t*>(smem + p.lds.reg_max);
   uint32_t* reg_min = reinterpret_cast<uint32_t*>(smem + p.lds.reg_min);
-  int32_t* n_open = reinterpret_cast<int32_t*>(smem + p.lds.n_open);          // waves that have the region open, at the window's start
-  int32_t* slab_delta = reinterpret_cast<int32_t*>(smem + p.lds.slab_delta);  // [hardware wave][region]: net change over its slab
+  uint32_t* totals = reinterpret_cast<uint32_t*>(smem + p.lds.totals);  // [hardware wave][plane]: net change over its records of the window
   unsigned long long* ctr = reinterpret_cast<unsigned long long*>(smem + p.lds.ctr);
   uint32_t* tmp = reinterpret_cast<uint32_t*>(smem + p.lds.tmp);
   uint2* sVF = reinterpret_cast<uint2*>(smem + p.lds.vf);               // per wave: records held, first surviving seq
   uint32_t* pos = reinterpret_cast<uint32_t*>(smem + p.lds.pos);        // per wave: first rank of the range in LDS
   uint32_t* adv = reinterpret_cast<uint32_t*>(smem + p.lds.adv);        // per wave: ranks the window took
-  uint32_t* seen_all = reinterpret_cast<uint32_t*>(smem + p.lds.seen);  // per hardware wave: the regions in its slab, one bit each
+  uint32_t* edge = reinterpret_cast<uint32_t*>(smem + p.lds.edge);      // pass 1, per run: 1 if it holds a record, first clock, last clock; pass 2: records in the cells of each hardware wave
+  auto key = [&](uint32_t place) -> unsigned long long& { return *reinterpret_cast<unsigned long long*>(smem + key_at(place)); };
 
-  const uint32_t tid = threadIdx.x, lane = tid & 63u, hw = tid >> 6;
+  const uint32_t tid_k = threadIdx.x;
+  uint32_t tid = tid_k, lane = tid & 63u, hw = (uint32_t)__builtin_amdgcn_readfirstlane((int)(tid >> 6));
+  // A copy of the thread index that the optimiser cannot see through: without it address arithmetic of all
+  // passes is done ahead of the loops and held in registers through them.
+  auto fresh_tid = [&]() { tid = tid_k; asm volatile("" : "+v"(tid)); lane = tid & 63u; };
   const uint32_t W = p.W, R = p.R, cap = p.cap, capm = cap - 1u, cl2 = p.cap_log2, nrec = p.nrec;
-  const uint32_t rsh = p.range_log2, C = 1u << rsh;
+  const uint32_t rsh = (E == 8 ? 13u : (E == 4 ? 12u : 11u)) - p.waves_log2, C = 1u << rsh;  // a window looks at C ranks of every wave
+  const uint32_t tsh = 11u - p.waves_log2, Ct = 1u << tsh;                                        // table1: Ct ranks of every wave
+  uint32_t region_bits = 0; while ((1u << region_bits) < R) ++region_bits;
   const StatsLayout SL = stats_layout(p.n_wg, W, R);
   if (p.out[H_STATUS] != 0) return;  // device header did not match the launch geometry
 
@@ -137,6 +232,7 @@ __global__ __launch_bounds__(kBlock) void kp_reduce_wide(WideParams p) {
     const uint32_t* wh = p.wg_hdrs + (size_t)32 * wg;
     const uint2* recs = p.records + (size_t)wg * nrec;
     __syncthreads();  // every wave is done with the workgroup before
+    fresh_tid();
 
     // ---- workgroup header ------------------------------------------------------------------------
     if (tid <= KP_MAX_WAVES) {  // (entries from W up: no records)
@@ -149,19 +245,23 @@ __global__ __launch_bounds__(kBlock) void kp_reduce_wide(WideParams p) {
       }
     }
     if (tid < T_COUNT) tmp[tid] = 0;
-    if (tid < kRegStride) n_open[tid] = 0;
     for (uint32_t i = tid; i < (nrec + 31u) / 32u; i += kBlock) bitmap[i] = 0;
+    for (uint32_t e = tid; e < (W << p.lds.split_log2) * R; e += kBlock) {  // no last record of (run, region) yet, and no first
+      last_all[e] = 0ull;
+      if (p.lds.split_log2) head_all[e] = make_uint2(0u, 0u);
+    }
     for (uint32_t e = tid; e < W * R; e += kBlock) {
-      keys[e] = 0ull;  // no last record of (wave, region) yet
       // pass 1 adds every pair to its row with atomics: in LDS, or in the statistics block itself
       if (p.lds.rows_in_lds) {
         reinterpret_cast<uint4*>(rows_lds)[e] = make_uint4(0u, 0u, 0u, 0u);
+        row_min[e] = 0xFFFFFFFFu;
       } else {
         uint64_t* row = p.out + SL.per + ((size_t)wg * W * R + e) * 2;
         row[0] = 0ull; row[1] = 0ull;
       }
     }
-    __threadfence();
+    if (tid < kWavesHw) edge[4u * tid] = 0u;
+    // (the barrier waits for a wave's stores, and the rows and the atomics on them meet in one L2: no fence)
     __syncthreads();
     uint32_t held = 0, max_v = 0;
     for (uint32_t w = 0; w < W; ++w) {
@@ -182,15 +282,27 @@ __global__ __launch_bounds__(kBlock) void kp_reduce_wide(WideParams p) {
     // ---- pass 0: every slot once -------------------------------------------------------------------
     {
       uint32_t c_field = 0, c_dis = 0;
-      for (uint32_t i = tid; i < nrec; i += kBlock) {
-        const uint2 rec = recs[i];
-        const uint32_t s = i & capm;
-        const bool good = rank_of(rec, i >> cl2, s) != 0xFFFFFFFFu;
-        c_field += good ? 1u : 0u;
-        if (good && ((rec.x ^ s) & capm) != 0u) {
-          ++c_dis;
-          const uint32_t at = atomicAdd(&tmp[T_LISTED], 1u);
-          if (at < p.lds.list_cap) list[at] = ((unsigned long long)(((i >> cl2) << 20) | rank_of(rec, i >> cl2, s)) << 20) | s;
+      const uint4* units = reinterpret_cast<const uint4*>(recs);  // two records each
+      for (uint32_t i0 = tid; i0 < nrec / 2u; i0 += 4u * kBlock) {
+        uint4 v[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) v[u] = units[i0 + u * kBlock < nrec / 2u ? i0 + u * kBlock : i0];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+          if (i0 + u * kBlock >= nrec / 2u) continue;
+#pragma unroll
+          for (uint32_t h = 0; h < 2u; ++h) {
+            const uint32_t i = 2u * (i0 + u * kBlock) + h, w = i >> cl2, s = i & capm;
+            const uint2 rec = h ? make_uint2(v[u].z, v[u].w) : make_uint2(v[u].x, v[u].y);
+            const uint32_t k = rank_of(rec, w, s);
+            const bool good = k != 0xFFFFFFFFu;
+            c_field += good ? 1u : 0u;
+            if (good && ((rec.x ^ s) & capm) != 0u) {
+              ++c_dis;
+              const uint32_t at = atomicAdd(&tmp[T_LISTED], 1u);
+              if (at < p.lds.list_cap) list[at] = ((unsigned long long)((w << 20) | k) << 20) | s;
+            }
+          }
         }
       }
       c_field = wave_sum(c_field);
@@ -239,57 +351,33 @@ __global__ __launch_bounds__(kBlock) void kp_reduce_wide(WideParams p) {
       return lo;
     };
 
-    // The ranks pos[w] .. pos[w] + C of every wave: which slot holds each (the later slot wins).
-    auto build_table = [&]() {
+    // The ranks pos[w] .. pos[w] + (1 << sh) of every wave: which slot holds each (the later slot wins).
+    auto build_table = [&](uint32_t* table, uint32_t places, uint32_t sh) {
       __syncthreads();  // pos[] is written, the table's last readers are done
-      table[tid] = 0; table[tid + kBlock] = 0;
+      for (uint32_t i = tid; i < places; i += kBlock) table[i] = 0;
       __syncthreads();
       for (uint32_t i = tid; i < nrec; i += kBlock) {
         const uint32_t w = i >> cl2, s = i & capm;
         const uint32_t k = rank_of(recs[i], w, s);
         if (k == 0xFFFFFFFFu) continue;
         const uint32_t d = k - pos[w];
-        if (d < C) atomicMax(&table[(w << rsh) + d], s + 1u);
+        if (d < (1u << sh)) atomicMax(&table[(w << sh) + d], s + 1u);
       }
       __syncthreads();
-    };
-    // The record at place idx of the ranks in LDS, (wave idx >> rsh, rank pos + (idx & (C - 1))); false: none.
-    // (With a list: for workgroups in which no two records have the same rank, as pass 2 requires.)
-    auto fetch = [&](uint32_t idx, uint2& rec) -> bool {
-      const uint32_t w = idx >> rsh, j = idx & (C - 1u);
-      if (w >= W) return false;
-      const uint2 vf = sVF[w];
-      const uint32_t k = pos[w] + j;
-      if (k >= vf.x) return false;
-      if (tabled) {
-        const uint32_t t = table[idx];
-        if (t == 0u) return false;
-        rec = recs[(size_t)w * cap + (t - 1u)];
-        return true;
-      }
-      const uint32_t s = (vf.y + k) & capm;
-      rec = recs[(size_t)w * cap + s];
-      if (rank_of(rec, w, s) == k) return true;
-      if (!listed) return false;
-      const uint32_t at = list_lower_bound((w << 20) | k);
-      if (at >= n_listed || (uint32_t)(list[at] >> 20) != ((w << 20) | k)) return false;
-      rec = recs[(size_t)w * cap + ((uint32_t)list[at] & 0xFFFFFu)];
-      return true;
     };
 
     uint32_t n_occupied = 0, n_disorder = 0;
     if (tabled) {
       uint32_t occ = 0, dis = 0;
-      for (uint32_t k0 = 0; k0 < max_v; k0 += C) {
+      for (uint32_t k0 = 0; k0 < max_v; k0 += Ct) {
         if (tid < 16) pos[tid] = k0;
-        build_table();
-#pragma unroll
-        for (int x = 0; x < 2; ++x) {
-          const uint32_t idx = tid + x * kBlock, t = table[idx];
+        build_table(table1, kTable, tsh);
+        for (uint32_t idx = tid; idx < kTable; idx += kBlock) {
+          const uint32_t t = table1[idx];
           if (t) {
             const uint32_t s = t - 1u;
             ++occ;
-            dis += (s != (recs[(size_t)(idx >> rsh) * cap + s].x & capm)) ? 1u : 0u;
+            dis += (s != (recs[(size_t)(idx >> tsh) * cap + s].x & capm)) ? 1u : 0u;
           }
         }
       }
@@ -299,154 +387,210 @@ __global__ __launch_bounds__(kBlock) void kp_reduce_wide(WideParams p) {
     }
 
     // ---- pass 1: pairing, durations, per-(wave, region) statistics, monotonicity ---------------------
-    // Hardware wave w takes recorded wave w, 64 consecutive ranks at a time, one per lane.  The nearest
-    // earlier record of a lane's (wave, region) is the highest lower lane with the same region (the lanes
-    // with a lane's region: one ballot per bit of the region number) or, when there is none, the last
-    // record of that region in the ranks before, which the wave keeps in a table of its own.
+    // Hardware wave (w << split) + i takes run i of recorded wave w, 64 consecutive ranks at a time, one per
+    // lane.  The nearest earlier record of a lane's (wave, region) is the highest lower lane with the same
+    // region (the lanes with a lane's region: one ballot per bit of the region number) or, when there is none,
+    // the last record of that region in the ranks before, which the run keeps in a table of its own.
+    // (a workgroup that looks its winning slots up in a table does not cut its waves into runs)
     {
-      uint2* last = reinterpret_cast<uint2*>(keys) + hw * R;  // per region: {clock, 1 << 31 | END << 30 | rank} of its last record
-      uint32_t n_pairs = 0, orphan_s = 0, orphan_e = 0, nonmono = 0, occupied = 0, moved = 0;  // (the same in all lanes)
+      const uint32_t split = tabled ? 0u : p.lds.split_log2;
+      const uint32_t w_here = hw >> split, run = hw & ((1u << split) - 1u);
+      unsigned long long* last = last_all + hw * R;
+      uint2* head = head_all + hw * R;
+      uint32_t n_pairs = 0, n_ends = 0, nonmono = 0, occupied = 0, moved = 0;  // (the same in all lanes)
       bool carry_has = false;
-      uint32_t carry_ts = 0;  // clock of the wave's last record so far
+      uint32_t carry_ts = 0, first_ts = 0, carry_id = kNoId;  // the run's last record so far: clock, END << 7 | region; clock of its first
       const uint64_t below = (1ull << lane) - 1ull;
-      uint64_t* rows = p.out + SL.per + ((size_t)wg * W + hw) * R * 2;
-      uint32_t* rows_here = rows_lds + hw * R * 4u;
-      auto group = [&](uint32_t k, bool ok, uint2 rec) {  // this lane: rank k, its record if ok
-        const uint32_t r = (rec.x >> 24) & 0x7Fu, ts = rec.y;
-        const bool is_end = (rec.x >> 31) != 0u;
-        const uint64_t there = __builtin_amdgcn_ballot_w64(ok);
-        if (there == 0ull) return;
-        {  // clocks must not decrease from one record of the wave to the next
-          const uint64_t lower = there & below;
-          const uint32_t before = (uint32_t)__shfl((int)ts, lower ? 63 - (int)__builtin_clzll(lower) : 0, 64);
-          const bool has = lower != 0ull || carry_has;
-          nonmono += (uint32_t)__popcll(__builtin_amdgcn_ballot_w64(ok && has && ts < (lower ? before : carry_ts)));
-          carry_ts = (uint32_t)__builtin_amdgcn_readlane((int)ts, 63 - (int)__builtin_clzll(there));
-          carry_has = true;
-        }
-        uint64_t same = there;
-#pragma unroll
-        for (uint32_t b = 0; b < 7u; ++b) {
-          const uint64_t set = __builtin_amdgcn_ballot_w64(ok && ((r >> b) & 1u));
-          same &= ((r >> b) & 1u) ? set : ~set;
-        }
-        const uint64_t lower = same & below;
-        const int src = lower ? 63 - (int)__builtin_clzll(lower) : 0;
-        uint32_t pred_ts = (uint32_t)__shfl((int)ts, src, 64);
-        uint32_t pred_info = (uint32_t)__shfl((int)(0x80000000u | ((uint32_t)is_end << 30) | k), src, 64);
-        if (ok && lower == 0ull) { const uint2 c = last[r]; pred_ts = c.x; pred_info = c.y; }
-        if (ok && (same >> lane) >> 1 == 0ull) last[r] = make_uint2(ts, 0x80000000u | ((uint32_t)is_end << 30) | k);  // the region's last record here
-        const bool pred_start = ok && (pred_info >> 30) == 2u;  // there is one and it is a START
-        const bool pair = pred_start && is_end;
-        orphan_s += (uint32_t)__popcll(__builtin_amdgcn_ballot_w64(pred_start && !is_end));  // START START
-        orphan_e += (uint32_t)__popcll(__builtin_amdgcn_ballot_w64(ok && is_end && !pred_start));
-        const uint64_t pairs = __builtin_amdgcn_ballot_w64(pair);
-        n_pairs += (uint32_t)__popcll(pairs);
-        if (pair) {
-          const uint32_t d_raw = ts - pred_ts;
-          const uint32_t d = d_raw > p.rec_cost ? d_raw - p.rec_cost : 0u;
-          atomicAdd(&hist[r * kHistStride + (31 - __clz(d | 1u))], 1u);
+      // the duration of a pair into the histogram and its row
+      auto account = [&](uint32_t w, uint32_t r, uint32_t d_raw) {
+        const uint32_t d = d_raw > p.rec_cost ? d_raw - p.rec_cost : 0u;
+        atomicAdd(&hist[r * kHistStride + (31 - __clz(d | 1u))], 1u);
+        // row {u64 sum; u32 n; u32 max}, cleared above
+        if (p.lds.rows_in_lds) {
+          uint32_t* row = rows_lds + (w * R + r) * 4u;
+          atomicAdd(reinterpret_cast<unsigned long long*>(row), (unsigned long long)d);
+          atomicAdd(row + 2, 1u);
+          atomicMax(row + 3, d);
+          atomicMin(&row_min[w * R + r], d);
+        } else {
+          uint64_t* row = p.out + SL.per + (((size_t)wg * W + w) * R + r) * 2u;
+          atomicAdd(reinterpret_cast<unsigned long long*>(row), (unsigned long long)d);
+          atomicAdd(reinterpret_cast<uint32_t*>(row) + 2, 1u);
+          atomicMax(reinterpret_cast<uint32_t*>(row) + 3, d);
           atomicAdd(&reg_sum[r], (unsigned long long)d);
           atomicMax(&reg_max[r], d);
           atomicMin(&reg_min[r], d);
-          const uint32_t b0 = hw * cap + (pred_info & kSeqMask), b1 = hw * cap + k;
-          atomicOr(&bitmap[b0 >> 5], 1u << (b0 & 31u));
-          atomicOr(&bitmap[b1 >> 5], 1u << (b1 & 31u));
-          // row {u64 sum; u32 n; u32 max}, cleared above
-          if (p.lds.rows_in_lds) {
-            uint32_t* row = rows_here + 4u * r;
-            atomicAdd(reinterpret_cast<unsigned long long*>(row), (unsigned long long)d);
-            atomicAdd(row + 2, 1u);
-            atomicMax(row + 3, d);
-          } else {
-            uint64_t* row = rows + 2u * r;
-            atomicAdd(reinterpret_cast<unsigned long long*>(row), (unsigned long long)d);
-            atomicAdd(reinterpret_cast<uint32_t*>(row) + 2, 1u);
-            atomicMax(reinterpret_cast<uint32_t*>(row) + 3, d);
-          }
         }
       };
-      const uint32_t V = hw < W ? sVF[hw < W ? hw : 0u].x : 0u;
+      auto mark = [&](uint32_t bit) { atomicOr(&bitmap[bit >> 5], 1u << (bit & 31u)); };
+      auto group = [&](uint32_t k0, bool ok, uint2 rec) {  // this lane: rank k0 + lane, its record if ok
+        const uint32_t k = k0 + lane, id = rec.x >> 24, r = id & 0x7Fu, ts = rec.y;
+        const bool is_end = ok && id >= 0x80u;
+        const uint64_t there = __builtin_amdgcn_ballot_w64(ok), ends = __builtin_amdgcn_ballot_w64(is_end);
+        if (there == 0ull) return;
+        occupied += (uint32_t)__popcll(there);
+        n_ends += (uint32_t)__popcll(ends);
+        // the record before each (clocks must not decrease from one to the next), by far the most often also
+        // the nearest one of an END's region
+        uint32_t start_ts = wave_shr1(ts, carry_ts), before_id = wave_shr1(id, carry_id);
+        const bool gaps = (there & (there + 1ull)) != 0ull;  // (uniform) a rank without a record
+        if (gaps) {
+          const uint64_t lower = there & below;
+          const uint32_t from_ts = (uint32_t)__shfl((int)ts, lower ? 63 - (int)__builtin_clzll(lower) : 0, 64);
+          start_ts = lower ? from_ts : carry_ts;
+          before_id = kNoId;
+        }
+        nonmono += (uint32_t)__popcll(__builtin_amdgcn_ballot_w64(ok && ts < start_ts));  // (0 before the run's first record)
+        if (!carry_has) first_ts = (uint32_t)__builtin_amdgcn_readlane((int)ts, (int)__builtin_ctzll(there));
+        const int top = 63 - (int)__builtin_clzll(there);
+        carry_ts = (uint32_t)__builtin_amdgcn_readlane((int)ts, top);
+        carry_id = (uint32_t)__builtin_amdgcn_readlane((int)id, top);
+        carry_has = true;
+        bool pair = is_end && before_id == r;
+        const uint64_t near = __builtin_amdgcn_ballot_w64(pair);
+        const uint32_t b0 = w_here * cap + k0;
+        if (ends & ~near) {
+          uint64_t same = there;
+          for (uint32_t b = 0; b < region_bits; ++b) {
+            const uint64_t set = __builtin_amdgcn_ballot_w64(ok && ((r >> b) & 1u));
+            same &= ((r >> b) & 1u) ? set : ~set;
+          }
+          const uint64_t lower = same & below;
+          const int src = lower ? 63 - (int)__builtin_clzll(lower) : 0;
+          const uint32_t far_ts = (uint32_t)__shfl((int)ts, src, 64);
+          if (is_end && !pair) {
+            bool start = lower != 0ull && !((ends >> src) & 1ull);
+            uint32_t at = k0 + (uint32_t)src;
+            start_ts = far_ts;
+            if (lower == 0ull) {
+              const unsigned long long c = last[r];
+              start = c != 0ull && !((c >> 32) & 1ull);
+              at = (uint32_t)(c >> 33) - 1u;
+              start_ts = (uint32_t)c;
+              if (c == 0ull && run) head[r] = make_uint2(ts, 0x80000000u | k);  // the run's first record of the region: decided when the runs are joined
+            }
+            if (start) mark(w_here * cap + at);
+            pair = start;
+          }
+        }
+        if (ok) atomicMax(&last[r], ((unsigned long long)(((k + 1u) << 1) | (is_end ? 1u : 0u)) << 32) | ts);
+        const uint64_t pairs = __builtin_amdgcn_ballot_w64(pair);
+        n_pairs += (uint32_t)__popcll(pairs);
+        if (pair) account(w_here, r, ts - start_ts);
+        // both records of a pair are marked (those found further back: above)
+        if (cap >= 64u) {  // (the ranks then start at a word of the bitmap)
+          const uint64_t marks = pairs | (near >> 1);
+          if (lane < 2u) atomicOr(&bitmap[(b0 >> 5) + lane], lane ? (uint32_t)(marks >> 32) : (uint32_t)marks);
+          if (lane == 2u && (near & 1ull)) mark(b0 - 1u);
+        } else if (pair) {
+          mark(b0 + lane);
+          if ((near >> lane) & 1ull) mark(b0 + lane - 1u);
+        }
+      };
+      const uint32_t V = w_here < W ? sVF[w_here].x : 0u;
       if (!tabled) {
-        // rank k belongs in slot (first + k) mod cap; nothing is shared with the other waves
-        const uint32_t first = sVF[hw < W ? hw : 0u].y;
-        uint32_t cursor = 0, cursor_end = 0;  // this wave's stretch of the sorted list
-        if (listed && hw < W) { cursor = list_lower_bound(hw << 20); cursor_end = list_lower_bound((hw + 1u) << 20); }
-        for (uint32_t k0 = 0; k0 < V; k0 += 256u) {
-          uint2 rec[4];
-          bool ok[4];
-          uint32_t slot[4];
+        // rank k belongs in slot (first + k) mod cap; nothing is shared with the other runs
+        const uint32_t first = sVF[w_here < W ? w_here : 0u].y;
+        const uint32_t k_begin = run * (cap >> split), k_end = V < k_begin + (cap >> split) ? V : k_begin + (cap >> split);
+        uint32_t cursor = 0, cursor_end = 0;  // this run's stretch of the sorted list
+        if (listed && w_here < W) {
+          cursor = list_lower_bound((w_here << 20) | k_begin);
+          cursor_end = list_lower_bound(k_begin + (cap >> split) < (1u << 20) ? (w_here << 20) | (k_begin + (cap >> split)) : (w_here + 1u) << 20);
+        }
+        const uint2* seg = recs + (size_t)(w_here < W ? w_here : 0u) * cap;
+        uint2 ahead[4];  // the records of the next 256 ranks are on their way while 64 are walked
+        auto request = [&](uint32_t k0) -> uint2 { const uint32_t k = k0 + lane; return seg[k < k_end ? (first + k) & capm : 0u]; };
 #pragma unroll
-          for (int g = 0; g < 4; ++g) {  // (the loads are in flight together)
-            const uint32_t k = k0 + 64u * g + lane;
-            slot[g] = (first + k) & capm;
-            rec[g] = recs[(size_t)hw * cap + (k < V ? slot[g] : 0u)];
-            ok[g] = k < V && rank_of(rec[g], hw, slot[g]) == k;
-          }
-          if (cursor < cursor_end && ((uint32_t)(list[cursor] >> 20) & kSeqMask) < k0 + 256u) {
+        for (int g = 0; g < 4; ++g) ahead[g] = k_begin < k_end ? request(k_begin + 64u * g) : make_uint2(0u, 0u);
+#pragma unroll 1
+        for (uint32_t k0 = k_begin; k0 < k_end; k0 += 64u) {
+          const uint32_t k = k0 + lane;
+          uint32_t slot = (first + k) & capm;
+          uint2 rec = ahead[0];
+          ahead[0] = ahead[1]; ahead[1] = ahead[2]; ahead[2] = ahead[3];
+          ahead[3] = request(k0 + 256u);
+          bool ok = k < k_end && rank_of(rec, w_here, slot) == k;
+          if (cursor < cursor_end && ((uint32_t)(list[cursor] >> 20) & kSeqMask) < k0 + 64u) {
             // listed records whose rank is among these: a later slot displaces an earlier one
-            bool moved_here[4] = {false, false, false, false};
+            bool moved_here = false;
             while (cursor < cursor_end) {
-              const unsigned long long key = list[cursor];
-              const uint32_t rank = (uint32_t)(key >> 20) & kSeqMask, s = (uint32_t)key & 0xFFFFFu;
-              if (rank >= k0 + 256u) break;
+              const unsigned long long entry = list[cursor];
+              const uint32_t rank = (uint32_t)(entry >> 20) & kSeqMask, s = (uint32_t)entry & 0xFFFFFu;
+              if (rank >= k0 + 64u) break;
               ++cursor;
-#pragma unroll
-              for (int g = 0; g < 4; ++g) {
-                if (rank == k0 + 64u * g + lane && (!ok[g] || s > slot[g])) { slot[g] = s; ok[g] = true; moved_here[g] = true; }
-              }
+              if (rank == k && (!ok || s > slot)) { slot = s; ok = true; moved_here = true; }
             }
-#pragma unroll
-            for (int g = 0; g < 4; ++g) {
-              if (moved_here[g]) rec[g] = recs[(size_t)hw * cap + slot[g]];
-            }
+            if (moved_here) rec = seg[slot];
           }
-#pragma unroll
-          for (int g = 0; g < 4; ++g) {
-            occupied += (uint32_t)__popcll(__builtin_amdgcn_ballot_w64(ok[g]));
-            moved += (uint32_t)__popcll(__builtin_amdgcn_ballot_w64(ok[g] && ((rec[g].x ^ slot[g]) & capm) != 0u));
-            group(k0 + 64u * g + lane, ok[g], rec[g]);
-          }
+          if (displaced) moved += (uint32_t)__popcll(__builtin_amdgcn_ballot_w64(ok && ((rec.x ^ slot) & capm) != 0u));
+          group(k0, ok, rec);
         }
       } else {
-        for (uint32_t k0 = 0; k0 < max_v; k0 += C) {
+        for (uint32_t k0 = 0; k0 < max_v; k0 += Ct) {
           if (tid < 16) pos[tid] = k0;
-          build_table();
-          for (uint32_t j0 = 0; j0 < C && k0 + j0 < V; j0 += 128u) {
-            uint2 rec[2];
-            bool ok[2];
-#pragma unroll
-            for (int g = 0; g < 2; ++g) {
-              const uint32_t j = j0 + 64u * g + lane, t = table[(hw << rsh) + j];
-              ok[g] = t != 0u;
-              rec[g] = recs[(size_t)hw * cap + (ok[g] ? t - 1u : 0u)];
-            }
-#pragma unroll
-            for (int g = 0; g < 2; ++g) group(k0 + j0 + 64u * g + lane, ok[g], rec[g]);
+          build_table(table1, kTable, tsh);
+#pragma unroll 1
+          for (uint32_t j0 = 0; j0 < Ct && k0 + j0 < V; j0 += 64u) {
+            const uint32_t t = table1[(hw << tsh) + j0 + lane];
+            group(k0 + j0, t != 0u, recs[(size_t)hw * cap + (t ? t - 1u : 0u)]);
           }
         }
       }
-      if (lane == 0 && hw < W) {
+      if (lane == 0 && w_here < W) {
         if (n_pairs) atomicAdd(&tmp[T_PAIRS], n_pairs);
-        if (orphan_s) atomicAdd(&tmp[T_ORPHAN_START], orphan_s);
-        if (orphan_e) atomicAdd(&tmp[T_ORPHAN_END], orphan_e);
+        if (n_ends) atomicAdd(&tmp[T_ENDS], n_ends);
         if (nonmono) atomicAdd(&tmp[T_NONMONO], nonmono);
-        if (occupied) atomicAdd(&tmp[T_OCCUPIED], occupied);
+        if (occupied && !tabled) atomicAdd(&tmp[T_OCCUPIED], occupied);
         if (moved) atomicAdd(&tmp[T_WINNER_DISORDER], moved);
+        edge[4u * hw] = carry_has ? 1u : 0u;
+        edge[4u * hw + 1u] = first_ts;
+        edge[4u * hw + 2u] = carry_ts;
       }
       __syncthreads();
-      // a region whose last record is a START: that START has no END
-      uint32_t open_ended = 0;
+      // Join the runs of a wave, region by region.
+      n_pairs = 0;  // (from here on each lane's own)
       for (uint32_t e = tid; e < W * R; e += kBlock) {
-        open_ended += (reinterpret_cast<const uint2*>(keys)[e].y >> 30) == 2u ? 1u : 0u;
-        if (p.lds.rows_in_lds) {
+        const uint32_t w = e / R, r = e - w * R;
+        unsigned long long before = 0ull;
+        for (uint32_t i = 0; i + 1u < (1u << split); ++i) {
+          const unsigned long long l = last_all[((w << split) + i) * R + r];
+          if (l) before = l;
+          const uint2 h = head_all[((w << split) + i + 1u) * R + r];  // an END that found no earlier record in its own run
+          if (h.y && before && !((before >> 32) & 1ull)) {
+            ++n_pairs;
+            account(w, r, h.x - (uint32_t)before);
+            mark(w * cap + (uint32_t)(before >> 33) - 1u);
+            mark(w * cap + (h.y & kSeqMask));
+          }
+        }
+        if (p.lds.rows_in_lds) {  // (nobody else adds to this row any more)
+          const uint64_t sum = reinterpret_cast<const uint64_t*>(rows_lds)[2u * e], n_max = reinterpret_cast<const uint64_t*>(rows_lds)[2u * e + 1u];
           uint64_t* row = p.out + SL.per + ((size_t)wg * W * R + e) * 2;
-          row[0] = reinterpret_cast<const uint64_t*>(rows_lds)[2u * e];
-          row[1] = reinterpret_cast<const uint64_t*>(rows_lds)[2u * e + 1u];
+          row[0] = sum;
+          row[1] = n_max;
+          if ((uint32_t)n_max) {
+            atomicAdd(&reg_sum[r], (unsigned long long)sum);
+            atomicMax(&reg_max[r], (uint32_t)(n_max >> 32));
+            atomicMin(&reg_min[r], row_min[e]);
+          }
         }
       }
-      open_ended = wave_sum(open_ended);
-      if (lane == 0 && open_ended) atomicAdd(&tmp[T_ORPHAN_START], open_ended);
+      nonmono = 0;
+      if (tid < W) {
+        bool has = false;
+        uint32_t ts = 0;
+        for (uint32_t i = 0; i < (1u << split); ++i) {
+          const uint32_t* at = edge + 4u * ((tid << split) + i);
+          if (!at[0]) continue;
+          nonmono += has && at[1] < ts ? 1u : 0u;
+          has = true; ts = at[2];
+        }
+      }
+      n_pairs = wave_sum(n_pairs); nonmono = wave_sum(nonmono);
+      if (lane == 0) {
+        if (n_pairs) atomicAdd(&tmp[T_PAIRS], n_pairs);
+        if (nonmono) atomicAdd(&tmp[T_NONMONO], nonmono);
+      }
       n_occupied = tmp[T_OCCUPIED];
       n_disorder = tmp[T_WINNER_DISORDER];
     }
@@ -458,8 +602,8 @@ __global__ __launch_bounds__(kBlock) void kp_reduce_wide(WideParams p) {
       ctr[H_DISORDER] += n_disorder;
       ctr[H_NONMONO] += tmp[T_NONMONO];
       ctr[H_PAIRS] += tmp[T_PAIRS];
-      ctr[H_ORPHAN_START] += tmp[T_ORPHAN_START];
-      ctr[H_ORPHAN_END] += tmp[T_ORPHAN_END];
+      ctr[H_ORPHAN_START] += n_occupied - tmp[T_ENDS] - tmp[T_PAIRS];  // every START and END is paired or an orphan
+      ctr[H_ORPHAN_END] += tmp[T_ENDS] - tmp[T_PAIRS];
       ctr[H_SPAN_OVF] += span_overflow ? 1u : 0u;
       ctr[H_OVERLAP_WGS] += eligible ? 1u : 0u;
     }
@@ -468,154 +612,293 @@ __global__ __launch_bounds__(kBlock) void kp_reduce_wide(WideParams p) {
     // ---- pass 2: region-pair overlap -----------------------------------------------------------------
     // Every rank below a wave's record count holds a record here and the clocks of a wave do not decrease.
     if (tid < 16) pos[tid] = 0;
+    Planes<NW, P> open_now;  // waves that have each region open at the window's start (the same in all threads)
+#pragma unroll
+    for (int w = 0; w < NW; ++w)
+#pragma unroll
+      for (int k = 0; k < P; ++k) open_now.at[w][k] = 0u;
     for (uint32_t round = 0; round <= nrec; ++round) {  // (every window takes at least one record: the bound is never reached)
       __syncthreads();
+      fresh_tid();
       bool more = false;
       for (uint32_t w = 0; w < W; ++w) more = more || pos[w] < sVF[w].x;
       if (!more) break;
-      __syncthreads();
-      if (tid == 0) { tmp[T_WINDOW_END] = 0xFFFFFFFFu; tmp[T_ADVANCED] = 0; }
+      if (tabled) build_table(table2, K, rsh);
+      if (tid == 0) { tmp[T_WINDOW_BEGIN] = 0xFFFFFFFFu; tmp[T_WINDOW_END] = 0xFFFFFFFFu; tmp[T_WINDOW_LAST] = 0u; tmp[T_MAXCELL] = 0u; }
       if (tid < 16) adv[tid] = 0;
-      if (tabled) build_table(); else __syncthreads();
-      // clock << 9 | not marked << 8 | region << 1 | END
-      unsigned long long mine[2];
 #pragma unroll
-      for (int x = 0; x < 2; ++x) {
-        const uint32_t idx = tid + x * kBlock, w = idx >> rsh, j = idx & (C - 1u);
-        uint2 rec = make_uint2(0u, 0u);
-        const bool ok = fetch(idx, rec);
-        mine[x] = kNoKey;
-        if (ok) {
-          const uint32_t k = pos[w] + j, b = w * cap + k;
-          const uint32_t marked = (bitmap[b >> 5] >> (b & 31u)) & 1u;
-          mine[x] = ((unsigned long long)rec.y << 9) | ((marked ^ 1u) << 8) | (((rec.x >> 24) & 0x7Fu) << 1) | (rec.x >> 31);
+      for (int x = 0; x < E / 2; ++x) cells[tid + x * kBlock] = 0u;
+      __syncthreads();
+      // ---- the records this window looks at: place idx is (wave idx >> rsh, rank pos + (idx & (C - 1))) ----
+      uint2 rec[E];
+#pragma unroll
+      for (int x = 0; x < E; ++x) {
+        const uint32_t idx = tid + x * kBlock, w = idx >> rsh, k = pos[w & 15u] + (idx & (C - 1u));
+        const uint2 vf = sVF[w];  // (no records from wave W up)
+        const uint32_t s = tabled ? table2[idx] - 1u : (vf.y + k) & capm;
+        rec[x] = recs[k < vf.x ? (size_t)w * cap + s : (size_t)0];
+      }
+      bool ok[E];
+#pragma unroll
+      for (int x = 0; x < E; ++x) {
+        const uint32_t idx = tid + x * kBlock, w = idx >> rsh, j = idx & (C - 1u), k = pos[w & 15u] + j;
+        const uint2 vf = sVF[w];
+        ok[x] = k < vf.x;  // (every such rank holds a record here)
+        if (ok[x] && !tabled && rank_of(rec[x], w, (vf.y + k) & capm) != k) {  // the rank's record is on the list
+          const uint32_t at = list_lower_bound((w << 20) | k);
+          ok[x] = at < n_listed && (uint32_t)(list[at] >> 20) == ((w << 20) | k);
+          if (ok[x]) rec[x] = recs[(size_t)w * cap + ((uint32_t)list[at] & 0xFFFFFu)];
+        }
+        if (ok[x]) {
+          const uint32_t left = vf.x - k;  // records of the wave from this one on
+          if (j == 0u) atomicMin(&tmp[T_WINDOW_BEGIN], rec[x].y);
+          if (j == C - 1u || left == 1u) atomicMax(&tmp[T_WINDOW_LAST], rec[x].y);
           // a wave with records beyond this range: the window cannot reach past the range's last clock
-          if (j == C - 1u && k + 1u < sVF[w].x) atomicMin(&tmp[T_WINDOW_END], rec.y);
+          if (j == C - 1u && left > 1u) atomicMin(&tmp[T_WINDOW_END], rec[x].y);
         }
-        keys[idx] = mine[x];
       }
       __syncthreads();
-      const uint32_t window_end = tmp[T_WINDOW_END];
+      // ---- counting sort of the marked records inside the window into K cells of time ---------------------
+      const uint32_t t_begin = tmp[T_WINDOW_BEGIN];
+      const uint32_t t_end = tmp[T_WINDOW_END] < tmp[T_WINDOW_LAST] ? tmp[T_WINDOW_END] : tmp[T_WINDOW_LAST];
+      // (a product and a conversion that never decrease with the clock: the cells follow one another in time)
+      const float scale = (float)K / ((float)(t_end - t_begin) + 1.0f);
+      uint32_t ca[E];  // cell | arrival in the cell << 16; all ones: no event
 #pragma unroll
-      for (int x = 0; x < 2; ++x) {
+      for (int x = 0; x < E; ++x) {
         const uint32_t idx = tid + x * kBlock, w = idx >> rsh, j = idx & (C - 1u);
-        const unsigned long long next = j == C - 1u ? kNoKey : keys[idx + 1u];
-        const bool inside = mine[x] != kNoKey && (uint32_t)(mine[x] >> 9) <= window_end;
-        const bool next_inside = next != kNoKey && (uint32_t)(next >> 9) <= window_end;
-        if (inside && !next_inside) { adv[w] = j + 1u; tmp[T_ADVANCED] = 1u; }  // the records inside are the first ones of the range
-        mine[x] = inside ? mine[x] : kNoKey;  // (records that are no events stay: every wave's run stays in clock order)
+        const bool inside = ok[x] && rec[x].y <= t_end;  // the records inside are the first ones of the range
+        const uint64_t taken = __builtin_amdgcn_ballot_w64(inside);
+        // (a wave offers at least 128 ranks, so that the 64 places of a hardware wave are one recorded wave's)
+        if (lane == 0u && taken) atomicAdd(&adv[w], (uint32_t)__popcll(taken));
+        const uint32_t b = (w & 15u) * cap + pos[w & 15u] + j;
+        const bool event = inside && ((bitmap[inside ? b >> 5 : 0u] >> (b & 31u)) & 1u);
+        uint32_t c = (uint32_t)((float)(rec[x].y - t_begin) * scale);
+        c = c < K - 1u ? c : K - 1u;
+        const uint32_t sh = (c & 1u) << 4;
+        ca[x] = 0xFFFFFFFFu;
+        if (event) ca[x] = c | (((atomicAdd(&cells[c >> 1], 1u << sh) >> sh) & 0xFFFFu) << 16);
       }
       __syncthreads();
-      keys[tid] = mine[0]; keys[tid + kBlock] = mine[1];
-      __syncthreads();
-      if (tmp[T_ADVANCED] == 0u) break;  // (cannot happen, see above)
-      // The runs of the waves (C places each, in clock order; places without a record at the end) are merged
-      // by clock, pairs of runs of `size / 2` at a time: the first step compares place i of the lower run
-      // with place size/2 - 1 - i of the upper one, the others are the half-cleaners of a bitonic merge.
-      for (uint32_t size = 2u * C; size <= kK; size <<= 1) {
-        const uint32_t half = size >> 1;
-        {
-          const uint32_t blk = (tid / half) * size, i = tid & (half - 1u), lo = blk + i, hi = blk + size - 1u - i;
-          const unsigned long long a = keys[lo], b = keys[hi];
-          if ((a >> 9) > (b >> 9)) { keys[lo] = b; keys[hi] = a; }
-          __syncthreads();
-        }
-        for (uint32_t stride = half >> 1; stride > 0; stride >>= 1) {
-          const uint32_t lo = ((tid & ~(stride - 1u)) << 1) | (tid & (stride - 1u)), hi = lo | stride;
-          const unsigned long long a = keys[lo], b = keys[hi];
-          if ((a >> 9) > (b >> 9)) { keys[lo] = b; keys[hi] = a; }
-          __syncthreads();
-        }
-      }
-      // slab of this hardware wave, two places per lane: lane l holds places l and 64 + l
-      const unsigned long long place0 = keys[hw * kSlab + lane], place1 = keys[hw * kSlab + 64u + lane];
-      const uint32_t low0 = (uint32_t)place0, high0 = (uint32_t)(place0 >> 32), low1 = (uint32_t)place1, high1 = (uint32_t)(place1 >> 32);
-      // net change per region over the slab
-      slab_delta[hw * kRegStride + lane] = 0;
-      slab_delta[hw * kRegStride + 64u + lane] = 0;  // (LDS operations of one wave take effect in order)
-      if (place0 != kNoKey && !(low0 & 0x100u)) atomicAdd(&slab_delta[hw * kRegStride + ((low0 >> 1) & 0x7Fu)], (low0 & 1u) ? -1 : 1);
-      if (place1 != kNoKey && !(low1 & 0x100u)) atomicAdd(&slab_delta[hw * kRegStride + ((low1 >> 1) & 0x7Fu)], (low1 & 1u) ? -1 : 1);
-      __syncthreads();
-      {
-        int32_t c_lo = n_open[lane], c_hi = n_open[64u + lane];  // waves that have region lane, lane + 64 open
-        for (uint32_t h = 0; h < hw; ++h) {
-          c_lo += slab_delta[h * kRegStride + lane];
-          c_hi += slab_delta[h * kRegStride + 64u + lane];
-        }
-        // Which events open or close their region: the number of waves that have the region open right
-        // before the event is the number at the slab's start plus the STARTs minus the ENDs of the region
-        // at earlier places of the slab.  The lanes whose event has the same region come from one ballot per
-        // bit of the region number.
-        const bool ev0 = place0 != kNoKey && !(low0 & 0x100u), ev1 = place1 != kNoKey && !(low1 & 0x100u);
-        const uint32_t r0 = (low0 >> 1) & 0x7Fu, r1 = (low1 >> 1) & 0x7Fu;
-        const bool end0 = (low0 & 1u) != 0u, end1 = (low1 & 1u) != 0u;
-        uint64_t same00 = __builtin_amdgcn_ballot_w64(ev0);  // places 0..63 with the region of this lane's place there
-        uint64_t same01 = same00;                              // places 0..63 with the region of this lane's place 64 + lane
-        uint64_t same11 = __builtin_amdgcn_ballot_w64(ev1);  // places 64..127 with that region
+      {  // exclusive prefix sum over the cell counters, E cells per thread
+        uint32_t wv[E / 2], run = 0, fullest = 0;
 #pragma unroll
-        for (uint32_t b = 0; b < 7u; ++b) {
-          const uint64_t set0 = __builtin_amdgcn_ballot_w64(ev0 && ((r0 >> b) & 1u));
-          const uint64_t set1 = __builtin_amdgcn_ballot_w64(ev1 && ((r1 >> b) & 1u));
-          same00 &= ((r0 >> b) & 1u) ? set0 : ~set0;
-          same01 &= ((r1 >> b) & 1u) ? set0 : ~set0;
-          same11 &= ((r1 >> b) & 1u) ? set1 : ~set1;
+        for (int i = 0; i < E / 2; ++i) {
+          const uint32_t v = cells[tid * (E / 2) + i], lo = v & 0xFFFFu, hi = v >> 16;
+          fullest = lo > fullest ? lo : fullest;
+          fullest = hi > fullest ? hi : fullest;
+          wv[i] = run | ((run + lo) << 16);
+          run += lo + hi;
         }
-        const uint64_t ends0 = __builtin_amdgcn_ballot_w64(ev0 && end0), ends1 = __builtin_amdgcn_ballot_w64(ev1 && end1);
-        const uint64_t below = (1ull << lane) - 1ull;
-        auto net = [](uint64_t places, uint64_t ends) -> int32_t {  // STARTs minus ENDs among `places`
-          return (int32_t)__popcll(places & ~ends) - (int32_t)__popcll(places & ends);
-        };
-        // the counts at the slab's start sit in the lane of the region
-        const int32_t at0_lo = __shfl(c_lo, (int)(r0 & 63u), 64), at0_hi = __shfl(c_hi, (int)(r0 & 63u), 64);
-        const int32_t at1_lo = __shfl(c_lo, (int)(r1 & 63u), 64), at1_hi = __shfl(c_hi, (int)(r1 & 63u), 64);
-        const int32_t before0 = (r0 < 64u ? at0_lo : at0_hi) + net(same00 & below, ends0);
-        const int32_t before1 = (r1 < 64u ? at1_lo : at1_hi) + net(same01, ends0) + net(same11 & below, ends1);
-        // the region opens (no wave had it open) or closes (the last wave that had it open)
-        const uint64_t switch0 = __builtin_amdgcn_ballot_w64(ev0 && before0 == (end0 ? 1 : 0));
-        const uint64_t switch1 = __builtin_amdgcn_ballot_w64(ev1 && before1 == (end1 ? 1 : 0));
-        // Each of these events adds its clock, signed, to the sums of its region with every region that is
-        // open at that moment (and with itself: the time the region is open at all).  Region by region,
-        // over the regions that are open at the slab's start or occur in it: whether region b is open
-        // right before an event is again the count at the start plus the STARTs minus the ENDs of b at the
-        // places before it.
-        const bool sw0 = (switch0 >> lane) & 1ull, sw1 = (switch1 >> lane) & 1ull;
-        const uint32_t t0 = (low0 >> 9) | (high0 << 23), t1 = (low1 >> 9) | (high1 << 23);
-        const unsigned long long val0 = end0 ? (unsigned long long)t0 : 0ull - (unsigned long long)t0;
-        const unsigned long long val1 = end1 ? (unsigned long long)t1 : 0ull - (unsigned long long)t1;
-        uint32_t* seen = seen_all + hw * 4u;  // bit r: region r occurs in the slab
-        if (lane < 4u) seen[lane] = 0u;       // (LDS operations of one wave take effect in order)
-        if (ev0) atomicOr(&seen[r0 >> 5], 1u << (r0 & 31u));
-        if (ev1) atomicOr(&seen[r1 >> 5], 1u << (r1 & 31u));
-        const uint64_t starts0 = __builtin_amdgcn_ballot_w64(ev0 && !end0), starts1 = __builtin_amdgcn_ballot_w64(ev1 && !end1);
-        auto with_region = [&](uint32_t b) {  // (b is the same in all lanes)
-          const int32_t lo_c = __builtin_amdgcn_readlane(c_lo, (int)(b & 63u)), hi_c = __builtin_amdgcn_readlane(c_hi, (int)(b & 63u));
-          const int32_t base = b < 64u ? lo_c : hi_c;
-          const uint64_t is_b0 = __builtin_amdgcn_ballot_w64(ev0 && r0 == b), is_b1 = __builtin_amdgcn_ballot_w64(ev1 && r1 == b);
-          const uint64_t s0 = is_b0 & starts0, e0 = is_b0 & ends0, s1 = is_b1 & starts1, e1 = is_b1 & ends1;
-          const int32_t all0 = (int32_t)__popcll(s0) - (int32_t)__popcll(e0);
-          const int32_t cnt0 = base + (int32_t)__popcll(s0 & below) - (int32_t)__popcll(e0 & below);
-          const int32_t cnt1 = base + all0 + (int32_t)__popcll(s1 & below) - (int32_t)__popcll(e1 & below);
-          if (sw0 && (r0 == b || cnt0 > 0)) {
-            const uint32_t lo_r = r0 < b ? r0 : b, hi_r = r0 < b ? b : r0;
-            atomicAdd(&otri[hi_r * (hi_r + 1u) / 2u + lo_r], val0);
-          }
-          if (sw1 && (r1 == b || cnt1 > 0)) {
-            const uint32_t lo_r = r1 < b ? r1 : b, hi_r = r1 < b ? b : r1;
-            atomicAdd(&otri[hi_r * (hi_r + 1u) / 2u + lo_r], val1);
-          }
-        };
-        const uint32_t seen0 = (uint32_t)__builtin_amdgcn_readfirstlane((int)seen[0]), seen1 = (uint32_t)__builtin_amdgcn_readfirstlane((int)seen[1]);
-        const uint32_t seen2 = (uint32_t)__builtin_amdgcn_readfirstlane((int)seen[2]), seen3 = (uint32_t)__builtin_amdgcn_readfirstlane((int)seen[3]);
-        for (uint64_t todo = __builtin_amdgcn_ballot_w64(c_lo > 0) | seen0 | ((uint64_t)seen1 << 32); todo; todo &= todo - 1ull)
-          with_region((uint32_t)__builtin_ctzll(todo));
-        for (uint64_t todo = __builtin_amdgcn_ballot_w64(c_hi > 0) | seen2 | ((uint64_t)seen3 << 32); todo; todo &= todo - 1ull)
-          with_region(64u + (uint32_t)__builtin_ctzll(todo));
+        const uint32_t incl = wave_scan_add(run);
+        uint32_t* share = edge;  // records in the cells of each hardware wave
+        if (lane == 63u) share[hw] = incl;
+        if (__builtin_amdgcn_ballot_w64(fullest > 8u)) { if (fullest > 8u) atomicMax(&tmp[T_MAXCELL], fullest); }
+        __syncthreads();
+        uint32_t below = (lane & 15u) < hw ? share[lane & 15u] : 0u;  // lane h of a row takes wave h's
+        below += scan_src<0>(below); below += scan_src<1>(below); below += scan_src<2>(below); below += scan_src<3>(below);
+        const uint32_t base = incl - run + (uint32_t)__builtin_amdgcn_readlane((int)below, 15);
+#pragma unroll
+        for (int i = 0; i < E / 2; ++i) cells[tid * (E / 2) + i] = wv[i] + base * 0x00010001u;
+        if (tid == kBlock - 1u) tmp[T_EVENTS] = base + run;
       }
       __syncthreads();
-      if (tid < kRegStride) {
-        int32_t s = 0;
-        for (uint32_t h = 0; h < kWavesHw; ++h) s += slab_delta[h * kRegStride + tid];
-        n_open[tid] += s;
+      const uint32_t n_events = tmp[T_EVENTS];
+      auto cell_start = [&](uint32_t c) -> uint32_t { return c < K ? (cells[c >> 1] >> ((c & 1u) << 4)) & 0xFFFFu : n_events; };
+      // clock << 8 | region << 1 | END: records with equal keys are interchangeable
+      auto key_of = [&](int x) -> unsigned long long { return ((unsigned long long)rec[x].y << 8) | (((rec[x].x >> 24) & 0x7Fu) << 1) | (rec[x].x >> 31); };
+      const uint32_t g0 = tid * E;
+      uint32_t clock[E], info[E];  // this lane's records of the sequence; info: region << 1 | END, bit 8 set: none
+      // Windows of less than 2^24 ticks with at most 9 records per cell, with 8 records per lane: the order is
+      // finished in registers, on keys of 32 bits that start at the window.  (9: see below.)
+      const bool in_lanes = E == 8 && tmp[T_MAXCELL] <= 9u && t_end - t_begin < (1u << 24) - 1u;  // (uniform)
+      if (!in_lanes) {
+#pragma unroll
+        for (int x = 0; x < E; ++x) {
+          if (ca[x] != 0xFFFFFFFFu) key(cell_start(ca[x] & 0xFFFFu) + (ca[x] >> 16)) = key_of(x);
+        }
+      }
+      if (in_lanes) {
+        // A cell of at most 9 records lies in at most two neighbouring lanes.  The lane sorts its own places; then
+        // lanes 2m and 2m + 1 merge (the lower lane keeps the lower 8 of the 16), and after that lanes 2m + 1 and
+        // 2m + 2.  The second merge moves no record across the boundary the first one settled: what it hands down
+        // to lane 2m + 1 belongs to the cell across the boundary above, which has no record in lane 2m (it would
+        // hold 10).
+        typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+        // word of a place: 4 words of padding after every 64
+        auto word = [&](uint32_t place) -> uint32_t* { return reinterpret_cast<uint32_t*>(smem) + place + ((place >> 6) << 2); };
+        auto lane_at = [&](uint32_t t) -> u32x4* { return reinterpret_cast<u32x4*>(word(t * E)); };
+#pragma unroll
+        for (int x = 0; x < E; ++x) {
+          if (ca[x] != 0xFFFFFFFFu) *word(cell_start(ca[x] & 0xFFFFu) + (ca[x] >> 16)) = ((rec[x].y - t_begin) << 8) | (uint32_t)(key_of(x) & 0xFFu);
+        }
+        __syncthreads();
+        uint32_t own[E];
+        {
+          const u32x4* at = lane_at(tid);
+#pragma unroll
+          for (int i = 0; i < E; ++i) own[i] = g0 + i < n_events ? at[i / 4][i % 4] : 0xFFFFFFFFu;
+        }
+        network_sort<E>(own);
+#pragma unroll
+        for (uint32_t round2 = 0; round2 < 2u; ++round2) {
+#pragma unroll
+          for (int i = 0; i < E / 4; ++i) lane_at(tid)[i] = u32x4{own[4 * i], own[4 * i + 1], own[4 * i + 2], own[4 * i + 3]};
+          __syncthreads();
+          const bool upper = ((tid ^ round2) & 1u) != 0u;  // this lane keeps the upper half of the merge
+          const bool alone = round2 == 1u && (tid == 0u || tid + 1u == (uint32_t)kBlock);
+          const u32x4* partner = lane_at(alone ? tid : (upper ? tid - 1u : tid + 1u));
+          const uint32_t neutral = upper ? 0u : 0xFFFFFFFFu;
+          u32x4 other[E / 4 ? E / 4 : 1];
+#pragma unroll
+          for (int i = 0; i < E / 4; ++i) other[i] = partner[i];
+#pragma unroll
+          for (int i = 0; i < E; ++i) {
+            const uint32_t y = alone ? neutral : other[(E - 1 - i) / 4][(E - 1 - i) % 4];
+            const uint32_t lo = own[i] < y ? own[i] : y, hi = own[i] < y ? y : own[i];
+            own[i] = upper ? hi : lo;
+          }
+          bitonic_merge<E>(own);
+          if (round2 == 0u) __syncthreads();  // every lane has read its partner's records before they are overwritten
+        }
+#pragma unroll
+        for (int i = 0; i < E; ++i) {
+          clock[i] = t_begin + (own[i] >> 8);
+          info[i] = g0 + i < n_events ? own[i] & 0xFFu : 0x100u;
+        }
+      } else if (tmp[T_MAXCELL] <= kMaxCell) {
+        __syncthreads();
+        // place inside the cell: the records with a smaller key, or with the same one and an earlier arrival
+        // (all of a lane's records together, so that their reads are in flight together)
+        uint32_t nm[E];  // records in the cell (0: this one is no event) | arrival << 16
+        uint32_t most = 0;
+#pragma unroll
+        for (int x = 0; x < E; ++x) {
+          const bool event = ca[x] != 0xFFFFFFFFu;
+          const uint32_t c = event ? ca[x] & 0xFFFFu : 0u, s0 = cell_start(c), n = event ? cell_start(c + 1u) - s0 : 0u;
+          nm[x] = n | (ca[x] & 0xFFFF0000u);
+          ca[x] = s0;
+          most = n > most ? n : most;
+        }
+        uint32_t place[E];
+#pragma unroll
+        for (int x = 0; x < E; ++x) place[x] = ca[x];
+        for (uint32_t it = 0; __builtin_amdgcn_ballot_w64(it < most); ++it) {
+#pragma unroll
+          for (int x = 0; x < E; ++x) {
+            const uint32_t n = nm[x] & 0xFFFFu;
+            const unsigned long long other = key(it < n ? ca[x] + it : 0u), mine = key_of(x);
+            place[x] += (it < n && (other < mine || (other == mine && it < (nm[x] >> 16)))) ? 1u : 0u;
+          }
+        }
+        __syncthreads();
+#pragma unroll
+        for (int x = 0; x < E; ++x) {
+          if (nm[x] & 0xFFFFu) key(place[x]) = key_of(x);
+        }
+        __syncthreads();
+      } else {
+        // many records in one cell (waves in lockstep, or a few far apart from the rest): all places, bitonic
+        uint32_t n_sort = kMinWindow;
+        while (n_sort < n_events) n_sort <<= 1;
+        for (uint32_t i = n_events + tid; i < n_sort; i += kBlock) key(i) = kNoKey;
+        __syncthreads();
+        for (uint32_t size = 2; size <= n_sort; size <<= 1) {
+          for (uint32_t stride = size >> 1; stride > 0; stride >>= 1) {
+            for (uint32_t i = tid; i < n_sort / 2u; i += kBlock) {
+              const uint32_t lo = ((i & ~(stride - 1u)) << 1) | (i & (stride - 1u)), hi = lo | stride;
+              const bool up = (lo & size) == 0u;
+              const unsigned long long x = key(lo), y = key(hi);
+              if ((x > y) == up) { key(lo) = y; key(hi) = x; }
+            }
+            __syncthreads();
+          }
+        }
+      }
+      if (!in_lanes) {
+#pragma unroll
+        for (int i = 0; i < E; ++i) {
+          const unsigned long long v = key(g0 + i);
+          clock[i] = (uint32_t)(v >> 8);
+          info[i] = g0 + i < n_events ? (uint32_t)v & 0xFFu : 0x100u;
+        }
+      }
+      // ---- sweep ---------------------------------------------------------------------------------------------
+      const bool in_slab = hw * 64u * E < n_events;  // (uniform in the wave)
+      Planes<NW, P> change;
+#pragma unroll
+      for (int w = 0; w < NW; ++w)
+#pragma unroll
+        for (int k = 0; k < P; ++k) change.at[w][k] = 0u;
+      auto step = [&](Planes<NW, P>& pl, int i) { planes_step<NW, P>(pl, info[i] >> 1, info[i] < 0x100u ? 1u : 0u, 0u - (info[i] & 1u)); };
+      if (in_slab) {
+#pragma unroll
+        for (int i = 0; i < E; ++i) step(change, i);
+        planes_scan_step<0, NW, P>(change); planes_scan_step<1, NW, P>(change); planes_scan_step<2, NW, P>(change);
+        planes_scan_step<3, NW, P>(change); planes_scan_step<4, NW, P>(change); planes_scan_step<5, NW, P>(change);
+      }
+      if (lane == 63u) {
+#pragma unroll
+        for (int w = 0; w < NW; ++w)
+#pragma unroll
+          for (int k = 0; k < P; ++k) totals[hw * kMaxPlanes + w * P + k] = change.at[w][k];
+      }
+      __syncthreads();
+      Planes<NW, P> state = open_now;  // before this lane's records
+      {
+        // the net change of the hardware waves below, and of all of them: lane h of a row takes wave h's
+        Planes<NW, P> sum, below;
+#pragma unroll
+        for (int w = 0; w < NW; ++w)
+#pragma unroll
+          for (int k = 0; k < P; ++k) sum.at[w][k] = totals[(lane & 15u) * kMaxPlanes + w * P + k];
+        planes_scan_step<0, NW, P>(sum); planes_scan_step<1, NW, P>(sum); planes_scan_step<2, NW, P>(sum); planes_scan_step<3, NW, P>(sum);
+#pragma unroll
+        for (int w = 0; w < NW; ++w)
+#pragma unroll
+          for (int k = 0; k < P; ++k) {
+            below.at[w][k] = hw ? (uint32_t)__builtin_amdgcn_readlane((int)sum.at[w][k], (int)(hw - 1u)) : 0u;
+            sum.at[w][k] = (uint32_t)__builtin_amdgcn_readlane((int)sum.at[w][k], 15);
+            change.at[w][k] = wave_shr1(change.at[w][k], 0u);  // of the lanes below
+          }
+        planes_add<NW, P>(open_now, sum);
+        if (in_slab) {
+          planes_add<NW, P>(state, below);
+          planes_add<NW, P>(state, change);
+        }
+      }
+      if (in_slab) {
+#pragma unroll
+        for (int i = 0; i < E; ++i) {
+          const uint32_t r = info[i] >> 1, down = 0u - (info[i] & 1u);
+          uint32_t open[NW];  // the regions open on the side of the event where its own count is lower
+#pragma unroll
+          for (int w = 0; w < NW; ++w) open[w] = planes_any<NW, P>(state, w);
+          step(state, i);
+          bool own = false;
+#pragma unroll
+          for (int w = 0; w < NW; ++w) {
+            const uint32_t after = planes_any<NW, P>(state, w);
+            open[w] = down ? after : open[w];
+            if (NW == 1 || (r >> 5) == (uint32_t)w) own = (open[w] >> (r & 31u)) & 1u;
+          }
+          // the region opens (no wave had it open) or closes (the last wave that had it open)
+          if (info[i] < 0x100u && !own) {
+            const unsigned long long val = down ? (unsigned long long)clock[i] : 0ull - (unsigned long long)clock[i];
+            atomicAdd(&otri[r * (r + 1u) / 2u + r], val);  // the time the region is open at all
+#pragma unroll
+            for (int w = 0; w < NW; w += 2) {
+              uint64_t set = open[w];
+              if (w + 1 < NW) set |= (uint64_t)open[w + 1 < NW ? w + 1 : w] << 32;
+              while (set) {
+                const uint32_t b = 32u * w + (uint32_t)__builtin_ctzll(set);
+                set &= set - 1ull;
+                const uint32_t lo_r = r < b ? r : b, hi_r = r < b ? b : r;
+                atomicAdd(&otri[hi_r * (hi_r + 1u) / 2u + lo_r], val);
+              }
+            }
+          }
+        }
       }
       if (tid < W) pos[tid] += adv[tid];
     }
@@ -648,13 +931,36 @@ namespace kp_reduce {
 
 kp_status wide_supported(const kp_trace_hdr& h) {
   const uint32_t nrec = h.waves_per_wg * h.cap_wave;
-  const uint32_t need = wide_lds(h.waves_per_wg, h.n_regions, nrec).total;
+  const uint32_t need = wide_lds(h.waves_per_wg, h.n_regions, h.cap_wave).total;
   if (need > kMaxLds)
     return kp::fail(KP_ERR_UNSUPPORTED_SHAPE,
                     "%u record slots per workgroup with %u regions: the decoder needs %u B of LDS (limit %u)", nrec,
                     h.n_regions, need, kMaxLds);
   return KP_OK;
 }
+
+namespace {
+
+template <int E, int NW, int P>
+kp_status launch(const WideParams& p, hipStream_t s) {
+  auto kern = kp_reduce_wide<E, NW, P>;
+  static thread_local kp_stage::LaunchCache cache;
+  uint32_t grid = 0;
+  const kp_status st = kp_stage::resident_grid(kern, kBlock, p.lds.total, &cache, &grid);
+  if (st != KP_OK) return st;
+  if (grid > p.n_wg) grid = p.n_wg;
+  hipLaunchKernelGGL(kern, dim3(grid), dim3(kBlock), p.lds.total, s, p);
+  KP_HIP_TRY(hipGetLastError());
+  return KP_OK;
+}
+template <int E>
+kp_status launch_words(const WideParams& p, hipStream_t s) {
+  if (p.W == 16)  // counts up to 16
+    return p.R <= 32 ? launch<E, 1, 5>(p, s) : (p.R <= 64 ? launch<E, 2, 5>(p, s) : launch<E, 4, 5>(p, s));
+  return p.R <= 32 ? launch<E, 1, 4>(p, s) : (p.R <= 64 ? launch<E, 2, 4>(p, s) : launch<E, 4, 4>(p, s));
+}
+
+}  // namespace
 
 kp_status launch_wide(const uint32_t* wg_hdrs, const void* records, uint64_t* out, const kp_trace_hdr& h,
                       hipStream_t s) {
@@ -668,17 +974,9 @@ kp_status launch_wide(const uint32_t* wg_hdrs, const void* records, uint64_t* ou
   p.cap_log2 = 0; while ((1u << p.cap_log2) < p.cap) ++p.cap_log2;
   p.rec_cost = h.rec_cost; p.flush = h.flags & KP_FLAG_FLUSH;
   p.nrec = p.W * p.cap;
-  uint32_t wl2 = 0; while ((1u << wl2) < p.W) ++wl2;
-  p.range_log2 = 11u - wl2;  // kK = 2^11 places
-  p.lds = wide_lds(p.W, p.R, p.nrec);
-  static thread_local kp_stage::LaunchCache cache;
-  uint32_t grid = 0;
-  const kp_status st = kp_stage::resident_grid(kp_reduce_wide, kBlock, p.lds.total, &cache, &grid);
-  if (st != KP_OK) return st;
-  if (grid > p.n_wg) grid = p.n_wg;
-  hipLaunchKernelGGL(kp_reduce_wide, dim3(grid), dim3(kBlock), p.lds.total, s, p);
-  KP_HIP_TRY(hipGetLastError());
-  return KP_OK;
+  p.waves_log2 = 0; while ((1u << p.waves_log2) < p.W) ++p.waves_log2;
+  p.lds = wide_lds(p.W, p.R, p.cap);
+  return p.lds.per_lane == 8 ? launch_words<8>(p, s) : (p.lds.per_lane == 4 ? launch_words<4>(p, s) : launch_words<2>(p, s));
 }
 
 }  // namespace kp_reduce

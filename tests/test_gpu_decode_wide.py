@@ -155,3 +155,35 @@ def test_empty_trace_and_limits(kp, oracle_mod):
     with pytest.raises(kp.KperfError) as e:   # single steps exist for the LDS-resident kernel only
         kp.kp_trace_reduce_steps(dev, 16 * 64, kp.make_hdr(1, 16, 40, 64), out, 3)
     assert e.value.status == kp.KP_ERR_UNSUPPORTED_SHAPE
+
+
+@pytest.mark.parametrize("spacing", ["random", "lockstep", "equal", "far"])
+@pytest.mark.parametrize("W,R,cap", [(8, 40, 1024), (3, 70, 512), (16, 33, 256), (2, 128, 2048), (1, 33, 4096)])
+def test_sort_forms_of_the_overlap_windows(kp, oracle_mod, W, R, cap, spacing):
+    """Clocks that put few, many or all records of a window into one time cell, windows longer than 2^24 ticks,
+    and a region that stays open across the runs a wave's ranks are cut into."""
+    rng = np.random.default_rng(7 * W + R)
+    evs = []
+    for w in range(W):
+        t, wave = 3, []
+        outer = cap // 2 - 7 + w  # opens region R - 1 here, closes it a quarter of the ring later
+        while len(wave) < cap - 4:
+            step = {"random": int(rng.integers(1, 900)), "lockstep": 400, "equal": 0, "far": 1 << 16}[spacing]
+            if len(wave) == outer:
+                wave.append((S, R - 1, t))
+                continue
+            if len(wave) >= outer + cap // 4 and outer >= 0:
+                wave.append((E, R - 1, t))
+                outer = -1 << 30
+                continue
+            r = len(wave) % (R - 1)
+            wave.append((S, r, t))
+            if len(wave) == outer:
+                wave.append((S, R - 1, t))
+            wave.append((E, r, t + step))
+            t += step + (step > 0)
+        evs.append(wave[:cap])
+    wgs = [inputs.events_to_wg(evs, cap, flush=False), inputs.events_to_wg(evs[::-1], cap, flush=False)]
+    raw = inputs.encode_trace(wgs, W, R, cap, rec_cost=1)
+    stats = check(raw, oracle_mod, use_hdr=True)
+    assert stats["n_overlap_wgs"] == 2
