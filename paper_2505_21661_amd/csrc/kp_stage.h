@@ -70,25 +70,47 @@ __device__ __forceinline__ uint32_t wave_scan_add(uint32_t v) {
 __device__ __forceinline__ uint32_t live_tag_of(uint32_t iter) { return ((1u + iter % 0xFFFFu) << 16) | kMValid; }
 __device__ __forceinline__ bool is_live(uint32_t m, uint32_t live_tag) { return (m & kLiveMask) == live_tag; }
 
-// Stages recorded workgroup `wg`.  Every thread of the block calls it; it ends with a barrier, after
+// The records of a recorded workgroup on their way to LDS: a thread's share in 16-byte units of two records
+// (block_threads() makes it at most 8) and the header's record count of wave `thread`.  A persistent
+// kernel requests the next workgroup before it walks the one in LDS, so that the loads travel under the walk
+// (timeline of 4096 workgroups of 16384 records, one of them per CU at a time: 495 us with the loads waited
+// for where they were issued).
+// UNITS of them per thread, 4 where that is enough (a third more hardware waves fit a CU's registers).
+// The thread index, opaque to the optimiser: without it the addresses of all units are computed once ahead of
+// the loop over the workgroups and held in registers through the walks.
+__device__ __forceinline__ uint32_t fresh_tid() { uint32_t t = threadIdx.x; asm volatile("" : "+v"(t)); return t; }
+template <int UNITS> struct InFlight { u32x4 v[UNITS]; uint32_t total; };
+template <int BLOCK, int UNITS>
+__device__ __forceinline__ void request_workgroup(const Trace& p, uint32_t wg, InFlight<UNITS>& f) {
+  const u32x4* recs = p.records + (size_t)wg * (p.nrec / 2);
+  const uint32_t tid = fresh_tid(), n16 = p.nrec / 2;
+#pragma unroll
+  for (int u = 0; u < UNITS; ++u) {
+    if (u * BLOCK >= n16) break;  // (uniform)
+    const uint32_t i = tid + u * BLOCK;
+    f.v[u] = __builtin_nontemporal_load(recs + (i < n16 ? i : n16 - 1u));
+  }
+  f.total = p.wg_hdrs[(size_t)32 * wg + 8 + (tid & 15u)];
+}
+
+// Stages the requested workgroup `wg`.  Every thread of the block calls it; it ends with a barrier, after
 // which rec[w * cap + k] holds the record of rank k of wave w (live iff its metadata carries
 // live_tag) and sV[w] the number of ranks of wave w.  The caller must put a barrier between its last
 // read of the staging area and the next call.
-template <int BLOCK>
+template <int BLOCK, int UNITS>
 __device__ __forceinline__ void stage_workgroup(const Trace& p, unsigned char* smem, const Lds& L, uint32_t wg,
-                                                uint32_t iter) {
+                                                uint32_t iter, const InFlight<UNITS>& f) {
   uint2* rec = reinterpret_cast<uint2*>(smem + L.rec);
   uint32_t* recw = reinterpret_cast<uint32_t*>(smem + L.rec);  // word 2p = clock, 2p+1 = metadata
   uint32_t* tmp = reinterpret_cast<uint32_t*>(smem + L.tmp);
   uint32_t* sV = reinterpret_cast<uint32_t*>(smem + L.v);
   uint32_t* sFirst = reinterpret_cast<uint32_t*>(smem + L.first);
-  const uint32_t tid = threadIdx.x, lane = tid & 63u;
+  const uint32_t tid = fresh_tid(), lane = tid & 63u;
   const uint32_t W = p.W, R = p.R, cap = p.cap, nrec = p.nrec, capm = cap - 1, cl2 = p.cap_log2;
-  const uint32_t* wh = p.wg_hdrs + (size_t)32 * wg;
   const uint32_t live_tag = live_tag_of(iter);
 
-  if (tid < W) {
-    const uint32_t T = wh[8 + tid];
+  if (tid < 16u) {
+    const uint32_t T = tid < W ? f.total : 0u;
     const uint32_t V = T < cap ? T : cap;
     sV[tid] = V;
     sFirst[tid] = p.flush ? 0u : T - V;
@@ -99,40 +121,28 @@ __device__ __forceinline__ void stage_workgroup(const Trace& p, unsigned char* s
     for (uint32_t i = tid; i < nrec / 2; i += BLOCK) z[i] = u32x4{0u, 0u, 0u, 0u};
   }
   __syncthreads();
-  // ---- load and scatter by rank ---------------------------------------------------------------
+  // ---- scatter by rank --------------------------------------------------------------------------
+  uint32_t c_field = 0;  // records of this thread accepted
   {
-    const u32x4* recs = p.records + (size_t)wg * (nrec / 2);
-    const uint32_t n16 = nrec / 2;  // 16-byte units, two records each
-    uint32_t c_field = 0, c_dis = 0;
-    for (uint32_t i0 = tid; i0 < n16; i0 += 4 * BLOCK) {
-      u32x4 v[4];
+    const uint32_t n16 = nrec / 2;
+    uint32_t c_dis = 0;
 #pragma unroll
-      for (int u = 0; u < 4; ++u) {
-        const uint32_t i = i0 + u * BLOCK;
-        v[u] = __builtin_nontemporal_load(recs + (i < n16 ? i : i0));
-      }
+    for (int u = 0; u < UNITS; ++u) {
+      if (u * BLOCK >= n16) break;  // (uniform)
+      const uint32_t f0 = 2u * (tid + u * BLOCK), s0 = f0 & capm;
+      const bool live = f0 < nrec;
+      const uint32_t w = live ? f0 >> cl2 : 0u;
+      const uint32_t V = live ? sV[w] : 0u, first = sFirst[w];
 #pragma unroll
-      for (int u = 0; u < 4; ++u) {
-        const uint32_t i = i0 + u * BLOCK;
-        const bool live = i < n16;
-        const uint32_t f0 = 2 * (live ? i : i0);
-        const uint32_t w = f0 >> cl2;
-        const uint32_t V = live ? sV[w] : 0u, first = sFirst[w];
-#pragma unroll
-        for (int h = 0; h < 2; ++h) {
-          const uint32_t tag = h ? v[u].z : v[u].x, pay = h ? v[u].w : v[u].y;
-          const uint32_t s = (f0 + h) & capm;
-          const uint32_t k = ((tag & kSeqMask) - first) & kSeqMask;
-          const uint32_t region = (tag >> 24) & 0x7Fu;
-          const bool good = s < V && k < V && ((tag >> 20) & 0xFu) == w && region < R;
-          c_field += good ? 1u : 0u;
-          c_dis += (good && s != (tag & capm)) ? 1u : 0u;
-          if (good) rec[(w << cl2) + k] = make_uint2(pay, region | ((tag >> 31) ? kMEnd : 0u) | live_tag);
-        }
+      for (uint32_t h = 0; h < 2u; ++h) {
+        const uint32_t tag = h ? f.v[u].z : f.v[u].x, pay = h ? f.v[u].w : f.v[u].y;
+        const uint32_t k = (tag - first) & kSeqMask;  // the low 20 bits of tag - first are those of seq - first
+        const bool good = s0 + h < V && k < V && ((tag >> 20) & 0xFu) == w && ((tag >> 24) & 0x7Fu) < R;
+        c_field += good ? 1u : 0u;
+        c_dis |= good ? (tag ^ (s0 + h)) & capm : 0u;
+        if (good) rec[(w << cl2) + k] = make_uint2(pay, (tag >> 24) | live_tag);  // region and END flag sit in the tag as in the metadata
       }
     }
-    c_field = wave_sum(c_field);
-    if (lane == 0 && c_field) atomicAdd(&tmp[0], c_field);
     if (__builtin_amdgcn_ballot_w64(c_dis != 0u) && lane == 0) tmp[2] = 1u;
   }
   __syncthreads();
@@ -144,7 +154,8 @@ __device__ __forceinline__ void stage_workgroup(const Trace& p, unsigned char* s
     uint32_t occ = 0;
     for (uint32_t q = tid; q < nrec; q += BLOCK) occ += is_live(recw[2 * q + 1], live_tag) ? 1u : 0u;
     occ = wave_sum(occ);
-    if (lane == 0 && occ) atomicAdd(&tmp[1], occ);
+    c_field = wave_sum(c_field);
+    if (lane == 0) { atomicAdd(&tmp[0], c_field); atomicAdd(&tmp[1], occ); }
   }
   __syncthreads();
   if (tmp[1] != tmp[0]) {
@@ -160,7 +171,7 @@ __device__ __forceinline__ void stage_workgroup(const Trace& p, unsigned char* s
         const uint32_t tag = seg[2 * s];
         const uint32_t k = ((tag & kSeqMask) - first) & kSeqMask, region = (tag >> 24) & 0x7Fu;
         if (k >= V || ((tag >> 20) & 0xFu) != w || region >= R) continue;
-        rec[w * cap + k] = make_uint2(seg[2 * s + 1], region | ((tag >> 31) ? kMEnd : 0u) | live_tag);
+        rec[w * cap + k] = make_uint2(seg[2 * s + 1], (tag >> 24) | live_tag);
       }
     }
     __syncthreads();
@@ -192,7 +203,7 @@ inline kp_status trace_from_header(const void* raw, size_t n, const kp_trace_hdr
   return KP_OK;
 }
 
-// One hardware wave per recorded wave, and enough threads to stage the records quickly.
+// One hardware wave per recorded wave, and enough threads to stage the records in 8 units each.
 inline int block_threads(uint32_t W, uint32_t nrec) {
   return (W > 8 || nrec >= 8192) ? 1024 : ((W > 4 || nrec >= 2048) ? 512 : 256);
 }

@@ -9,13 +9,20 @@
 // in that wave.
 //
 // One decoder workgroup stages one recorded workgroup in LDS as (clock, metadata) pairs, ordered by
-// rank.  Then the hardware waves share out the recorded waves in runs of consecutive ranks and walk
-// them 64 ranks per round (a run above rank 0 first counts the pairs below it):
-//   - an END looks at the four ranks below through DPP wave shifts for the nearest record of its
-//     region (deeper only if needed) and is paired iff that record is a START;
+// rank.  Then the hardware waves share out the recorded waves in runs of consecutive ranks and walk them
+// 128 ranks per round, two per lane (a run above rank 0 first counts the pairs below it):
+//   - an END is paired iff the nearest earlier record of its region is a START: by far the most often the
+//     record right below it, in the same lane or the one below (a DPP wave shift).  A round in which some END
+//     has another record below it is walked 64 ranks at a time: the lanes with the END's region (one ballot per bit
+//     of the region number) say which record is the nearest, or a walk back through LDS does;
 //   - its row index is the running count of paired ENDs (ballot + popcount);
-//   - its iteration index comes from byte-wide per-region counters packed four to a 32-bit
-//     word and prefix-summed across the lanes, on top of the per-region totals of earlier rounds.
+//   - its iteration index is the number of pairs of its region in earlier rounds, a counter in LDS, plus those in
+//     lower lanes.
+// What bounds it: instruction issue (one workgroup of this size per CU at a time, 16 hardware waves), then HBM.  So
+// the next workgroup's records travel under the walk, and a lane takes two ranks: of a START and an END only one
+// makes a row.  Measured on 4096 workgroups of 8 waves x 2048 records (0.54 GB read, 0.53 GB written): 495 us with
+// the loads waited for, four ranks of look-back per record and byte-wide counters scanned over the lanes; 341 us
+// with the loads ahead and ballots in their place, one rank per lane; 281 us with two (3.8 TB/s).
 #include "kp_stage.h"
 
 namespace {
@@ -23,158 +30,190 @@ namespace {
 using namespace kp_stage;
 
 constexpr uint32_t kBelowStride = 128;  // one counter per region
+constexpr uint32_t kNoId = 0xFFFFu;     // END << 7 | region of no record
+
+// First of the rounds that part i of n emits.  A wave also counts the pairs of all rounds below its run, which
+// takes about two fifths of the time of emitting them: with c = 2/5, run i + 1 is 1 - c of run i, so that
+// all parts take the same time.
+__device__ __forceinline__ uint32_t run_start(uint32_t rounds, uint32_t i, uint32_t n) {
+  float left = 1.0f, all = 1.0f;  // (1 - c)^i, (1 - c)^n
+  for (uint32_t j = 0; j < n; ++j) { left = j < i ? left * 0.6f : left; all *= 0.6f; }
+  return i >= n ? rounds : (uint32_t)((float)rounds * (1.0f - left) / (1.0f - all) + 0.5f);
+}
 
 struct PairsOut {
   uint32_t* count;  // pairs per (workgroup, wave)
   u32x4* rows;      // cap/2 rows per (workgroup, wave)
 };
 
-template <int BLOCK>
-__global__ __launch_bounds__(BLOCK) void kp_pairs_main(Trace p, PairsOut o, uint32_t split_log2) {
+template <int BLOCK, int UNITS>
+__global__ __launch_bounds__(BLOCK) void kp_pairs_main(Trace p, PairsOut o, uint32_t parts) {
   extern __shared__ __align__(16) unsigned char smem[];
   const Lds L = lds_layout(p.nrec);
   const uint2* rec = reinterpret_cast<const uint2*>(smem + L.rec);
+  const u32x4* rec2 = reinterpret_cast<const u32x4*>(smem + L.rec);
   const uint32_t* recw = reinterpret_cast<const uint32_t*>(smem + L.rec);  // word 2p = clock, 2p+1 = metadata
   const uint32_t* sV = reinterpret_cast<const uint32_t*>(smem + L.v);
   uint32_t* below = reinterpret_cast<uint32_t*>(smem + L.end);  // per hardware wave: pairs per region below its run
 
   const uint32_t tid = threadIdx.x, lane = tid & 63u, hw = tid >> 6;
   const uint32_t W = p.W, R = p.R, cap = p.cap, cl2 = p.cap_log2;
-  const uint32_t nwords = (R + 3u) >> 2;
+  uint32_t region_bits = 0; while ((1u << region_bits) < R) ++region_bits;
   const unsigned long long lt_mask = (1ull << lane) - 1ull;
 
   // the padding entries of the count array are part of the output: zero
   if (blockIdx.x == 0 && tid < ((0u - p.n_wg * W) & 3u)) o.count[(size_t)p.n_wg * W + tid] = 0u;
-  for (uint32_t i = tid; i < (BLOCK / 64) * kBelowStride; i += BLOCK) below[i] = 0u;
-  // stage_workgroup's first barrier orders these stores before any use
 
+  InFlight<UNITS> coming;
+  request_workgroup<BLOCK, UNITS>(p, blockIdx.x, coming);
   uint32_t iter = 0;
   for (uint32_t wg = blockIdx.x; wg < p.n_wg; wg += gridDim.x, ++iter) {
-    stage_workgroup<BLOCK>(p, smem, L, wg, iter);
+    stage_workgroup<BLOCK, UNITS>(p, smem, L, wg, iter, coming);
+    request_workgroup<BLOCK, UNITS>(p, wg + gridDim.x < p.n_wg ? wg + gridDim.x : wg, coming);
     const uint32_t live_tag = live_tag_of(iter);
-    // ---- walk: 2^split_log2 hardware waves share one recorded wave -----------------------------------
+    // ---- walk: `parts` hardware waves share one recorded wave -------------------------------------------
     // Each emits the rows of a run of consecutive ranks.  A run that does not start at rank 0 first
     // counts the pairs below it (total and per region) with the same pairing rounds, so that its row
     // and iteration indices continue those of the runs below; no wave waits for another.
-    if (hw < (W << split_log2)) {
-      const uint32_t w = hw >> split_log2, part = hw & ((1u << split_log2) - 1u);
+    if (hw < W * parts) {
+      const uint32_t w = hw / parts, part = hw - w * parts;
       const uint32_t wofs = w << cl2, V = sV[w];
-      const uint32_t plen = cap >> split_log2;
-      const uint32_t k0 = part * plen, k1 = V < k0 + plen ? V : k0 + plen;  // this wave emits ranks [k0, k1)
-      const uint32_t kc = V < k0 ? V : k0;                                   // and counts ranks [0, kc)
-      uint32_t* my_below = below + hw * kBelowStride;
-      uint32_t base_lo = 0u, base_hi = 0u;  // pairs seen so far: lane r for region r / region 64 + r
+      const uint32_t rounds = (V + 127u) >> 7;
+      const uint32_t k0 = run_start(rounds, part, parts) << 7, k_next = run_start(rounds, part + 1u, parts) << 7;
+      const uint32_t k1 = V < k_next ? V : k_next;  // this wave emits ranks [k0, k1)
+      const uint32_t kc = V < k0 ? V : k0;           // and counts ranks [0, kc)
+      uint32_t* seen = below + hw * kBelowStride;    // pairs of each region so far
+      seen[lane] = 0u; seen[64u + lane] = 0u;        // (LDS operations of one wave complete in order)
       u32x4* my_rows = o.rows + ((size_t)wg * W + w) * (cap / 2);
       uint32_t n_rows = 0;
-      uint32_t cm[4] = {0u, 0u, 0u, 0u};  // metadata of the last four ranks of the previous round
-      uint2 r_next = rec[wofs + (lane < V ? lane : 0u)];  // one round ahead, to hide the LDS latency
-      uint32_t m0, t0, region, pq;
-      // One round of 64 ranks from kb, of a walk that ends at k_end: an END is paired iff the nearest
-      // earlier record of its region is a START (four ranks through DPP shifts, deeper through LDS).
-      auto pair_round = [&](uint32_t kb, uint32_t k_end) __attribute__((always_inline)) -> bool {
+      uint32_t carry_id = kNoId, carry_t = 0u;  // the rank just below the round: metadata byte (kNoId: none) and clock
+      uint32_t end_t = 0u, start_t = 0u, region = 0u;  // of this lane's pair
+      // 64 ranks from kb, one per lane, any record: is this lane's an END that is paired?
+      auto pair_64 = [&](uint32_t kb, uint32_t k_end) __attribute__((always_inline)) -> bool {
         const uint32_t k = kb + lane;
-        const bool in = k < k_end;
-        const uint32_t q0 = wofs + (in ? k : k_end - 1);
-        const uint2 r0 = r_next;
-        {
-          const uint32_t kn = k + 64;
-          r_next = rec[wofs + (kn < V ? kn : 0u)];
-        }
-        const bool valid = in && is_live(r0.y, live_tag);
-        m0 = valid ? r0.y : 0u;
-        t0 = r0.x;
-        const uint32_t m1 = wave_shr1(m0, cm[0]);
-        const uint32_t m2 = wave_shr1(m1, cm[1]);
-        const uint32_t m3 = wave_shr1(m2, cm[2]);
-        const uint32_t m4 = wave_shr1(m3, cm[3]);
-#pragma unroll
-        for (int j = 0; j < 4; ++j) cm[j] = (uint32_t)__builtin_amdgcn_readlane((int)m0, 63 - j);
-        region = m0 & kMRegion;
-        const bool is_end = (m0 & kMEnd) != 0u;  // m0 is 0 for a rank that holds no record
-        const uint32_t want = kMValid | region, sel = kMValid | kMRegion;
-        const bool h1 = (m1 & sel) == want, h2 = (m2 & sel) == want, h3 = (m3 & sel) == want, h4 = (m4 & sel) == want;
-        bool have = h1 || h2 || h3 || h4;  // nearest earlier record of the same region
-        uint32_t pm = h1 ? m1 : (h2 ? m2 : (h3 ? m3 : m4));
-        pq = q0 - (h1 ? 1u : (h2 ? 2u : (h3 ? 3u : 4u)));
-        if (is_end && !have && k > 4) {  // slow path: walk further back
-          for (uint32_t kk = k - 4; kk-- > 0;) {
-            const uint32_t mq = recw[2 * (wofs + kk) + 1];
-            if (is_live(mq, live_tag) && (mq & kMRegion) == region) { have = true; pm = mq; pq = wofs + kk; break; }
+        const uint2 r0 = rec[wofs + (k < k_end ? k : 0u)];
+        const bool valid = k < k_end && is_live(r0.y, live_tag);
+        const uint32_t id = valid ? r0.y & 0xFFu : kNoId;
+        end_t = r0.x;
+        region = id & kMRegion;
+        const uint32_t below_id = wave_shr1(id, carry_id);
+        start_t = wave_shr1(end_t, carry_t);
+        carry_id = (uint32_t)__builtin_amdgcn_readlane((int)id, 63);
+        carry_t = (uint32_t)__builtin_amdgcn_readlane((int)end_t, 63);
+        const bool is_end = valid && (id & kMEnd) != 0u;
+        bool paired = is_end && below_id == region;
+        if (__builtin_amdgcn_ballot_w64(is_end && !paired)) {
+          // nearest earlier record of the region: a lower lane, or further back in LDS
+          uint64_t same = __builtin_amdgcn_ballot_w64(valid);
+          for (uint32_t b = 0; b < region_bits; ++b) {
+            const uint64_t set = __builtin_amdgcn_ballot_w64(valid && ((region >> b) & 1u));
+            same &= ((region >> b) & 1u) ? set : ~set;
+          }
+          const uint64_t ends = __builtin_amdgcn_ballot_w64(is_end), lower = same & lt_mask;
+          const int src = lower ? 63 - (int)__builtin_clzll(lower) : 0;
+          const uint32_t far_t = (uint32_t)__shfl((int)end_t, src, 64);
+          if (is_end && !paired) {
+            if (lower) {
+              paired = !((ends >> src) & 1ull);
+              start_t = far_t;
+            } else {
+              for (uint32_t kk = kb; kk-- > 0;) {
+                const uint32_t mq = recw[2 * (wofs + kk) + 1];
+                if (!is_live(mq, live_tag) || (mq & kMRegion) != region) continue;
+                paired = !(mq & kMEnd);
+                start_t = recw[2 * (wofs + kk)];
+                break;
+              }
+            }
           }
         }
-        return is_end && have && !(pm & kMEnd);
+        return paired;
+      };
+      // 128 ranks, two neighbours per lane, if every END among them has its START right below it: then a lane
+      // holds at most one pair (an END above an END is not paired).  Else `slow`, and nothing has happened.
+      u32x4 next = rec2[(wofs + (2u * lane < V ? 2u * lane : 0u)) >> 1];  // one round ahead, to hide the LDS latency
+      auto pair_128 = [&](uint32_t kb, uint32_t k_end, bool& slow) __attribute__((always_inline)) -> bool {
+        const uint32_t k = kb + 2u * lane;
+        const u32x4 r = next;  // {clock, metadata} of the even rank and of the odd one
+        next = rec2[(wofs + (k + 128u < V ? k + 128u : 0u)) >> 1];
+        const uint32_t id0 = k < k_end && is_live(r.y, live_tag) ? r.y & 0xFFu : kNoId;
+        const uint32_t id1 = k + 1u < k_end && is_live(r.w, live_tag) ? r.w & 0xFFu : kNoId;
+        const uint32_t below_id = wave_shr1(id1, carry_id), below_t = wave_shr1(r.z, carry_t);
+        // an END carries kMEnd above its region, no record neither: x ^ y == kMEnd says "END over its START"
+        const bool near0 = (id0 ^ below_id) == kMEnd && id0 >= kMEnd, near1 = (id1 ^ id0) == kMEnd && id1 >= kMEnd;
+        const bool end0 = (id0 & ~kMRegion) == kMEnd, end1 = (id1 & ~kMRegion) == kMEnd;
+        slow = __builtin_amdgcn_ballot_w64((end0 && !near0) || (end1 && !near1)) != 0ull;
+        if (slow) return false;
+        carry_id = (uint32_t)__builtin_amdgcn_readlane((int)id1, 63);
+        carry_t = (uint32_t)__builtin_amdgcn_readlane((int)r.z, 63);
+        region = (near1 ? id1 : id0) & kMRegion;
+        end_t = near1 ? r.z : r.x;
+        start_t = near1 ? r.x : below_t;
+        return near0 || near1;
       };
       // ---- count the pairs below this run ---------------------------------------------------------------
-      for (uint32_t kb = 0; kb < kc; kb += 64) {  // kc is a multiple of 64 or the end of the wave
-        const bool paired = pair_round(kb, kc);
+      auto tally = [&](bool paired) __attribute__((always_inline)) {
         n_rows += (uint32_t)__popcll(__builtin_amdgcn_ballot_w64(paired));
-        if (paired) atomicAdd(&my_below[region], 1u);
-      }
-      if (k0 > 0) {  // uniform; LDS operations of one wave complete in order
-        base_lo = my_below[lane];
-        base_hi = my_below[64 + lane];
-        my_below[lane] = 0u;
-        my_below[64 + lane] = 0u;
+        if (paired) atomicAdd(&seen[region], 1u);
+      };
+      for (uint32_t kb = 0; kb < kc; kb += 128) {  // kc is a multiple of 128 or the end of the wave
+        bool slow;
+        const bool paired = pair_128(kb, kc, slow);
+        if (!slow) tally(paired);
+        else for (uint32_t half = 0; half < 128u; half += 64u) tally(pair_64(kb + half, kc));
       }
       // ---- emit the rows of this run ------------------------------------------------------------------------
-      for (uint32_t kb = k0; kb < k1; kb += 64) {
-        const bool paired = pair_round(kb, k1);
-        const unsigned long long pb = __builtin_amdgcn_ballot_w64(paired);
-        if (pb == 0ull) continue;
-        // iteration index: pairs of this region in earlier rounds + earlier lanes of this round.
-        // The totals of earlier rounds live in registers: lane r holds the count of region r in
-        // base_lo and of region 64 + r in base_hi.  Within the round four regions share a 32-bit
-        // word of byte-wide counters (at most 64 per round, so no byte carries into its neighbour and
-        // one 32-bit prefix sum counts four regions at once).
-        const uint32_t pt = recw[2 * (paired ? pq : wofs)];  // the START's clock, fetched early
-        const int from = (int)((region & 63u) << 2);
-        uint32_t it = (uint32_t)__builtin_amdgcn_ds_bpermute(from, (int)base_lo);
-        if (R > 64u) {  // uniform: every lane takes part in the exchange
-          const uint32_t hi = (uint32_t)__builtin_amdgcn_ds_bpermute(from, (int)base_hi);
-          if (region >= 64u) it = hi;
-        }
-        for (uint32_t wd = 0; wd < nwords; ++wd) {
-          const bool mine = paired && (region >> 2) == wd;
-          if (__builtin_amdgcn_ballot_w64(mine) == 0ull) continue;
-          const uint32_t sh = 8u * (region & 3u);
-          const uint32_t one = mine ? (1u << sh) : 0u;
-          const uint32_t incl = wave_scan_add(one);
-          if (mine) it += ((incl - one) >> sh) & 0xFFu;
-          const uint32_t tot = (uint32_t)__builtin_amdgcn_readlane((int)incl, 63);
-          // the four lanes that own this word's regions add their byte of the round's totals
-          const uint32_t add = (tot >> (8u * (lane & 3u))) & 0xFFu;
-          if (wd < 16u) base_lo += (lane >> 2) == wd ? add : 0u;
-          else          base_hi += (lane >> 2) == wd - 16u ? add : 0u;
+      auto emit = [&](bool paired) __attribute__((always_inline)) {
+        const uint64_t pb = __builtin_amdgcn_ballot_w64(paired);
+        // iteration index: pairs of this region in earlier rounds + in lower lanes of this round
+        uint64_t same = pb;
+        for (uint32_t b = 0; b < region_bits; ++b) {
+          const uint64_t set = __builtin_amdgcn_ballot_w64((region >> b) & 1u);
+          same &= ((region >> b) & 1u) ? set : ~set;
         }
         if (paired) {
-          const uint32_t d_raw = t0 - pt;
+          const uint32_t it = seen[region] + (uint32_t)__popcll(same & lt_mask);
+          const uint64_t here_up = same & ~lt_mask;
+          if ((here_up & (here_up - 1ull)) == 0ull) seen[region] = it + 1u;  // the region's last pair of the round
+          const uint32_t d_raw = end_t - start_t;
           const uint32_t d = d_raw > p.rec_cost ? d_raw - p.rec_cost : 0u;
           const uint32_t j = n_rows + (uint32_t)__popcll(pb & lt_mask);
-          my_rows[j] = u32x4{pt, d, it, region};
+          my_rows[j] = u32x4{start_t, d, it, region};
         }
         n_rows += (uint32_t)__popcll(pb);
+      };
+      for (uint32_t kb = k0; kb < k1; kb += 128) {
+        bool slow;
+        const bool paired = pair_128(kb, k1, slow);
+        if (!slow) emit(paired);
+        else for (uint32_t half = 0; half < 128u; half += 64u) emit(pair_64(kb + half, k1));
       }
       // the wave with the last run knows the total
-      if (lane == 0 && part + 1u == (1u << split_log2)) o.count[(size_t)wg * W + w] = n_rows;
+      if (lane == 0 && part + 1u == parts) o.count[(size_t)wg * W + w] = n_rows;
     }
     __syncthreads();
   }
 }
 
-template <int BLOCK>
-kp_status launch_pairs(const Trace& p, const PairsOut& o, uint32_t lds_bytes, hipStream_t s) {
-  // hardware waves per recorded wave: as many as the block has, while a run keeps at least 64 ranks
-  uint32_t split_log2 = 0;
-  while ((p.W << (split_log2 + 1)) <= (uint32_t)BLOCK / 64u && (p.cap >> (split_log2 + 1)) >= 64u) ++split_log2;
-  auto kern = kp_pairs_main<BLOCK>;
+template <int BLOCK, int UNITS>
+kp_status launch_pairs_units(const Trace& p, const PairsOut& o, uint32_t lds_bytes, hipStream_t s) {
+  // hardware waves per recorded wave: as many as the block has, while a run keeps a round of 128 ranks
+  uint32_t parts = (uint32_t)BLOCK / 64u / p.W;
+  if (parts > (p.cap + 127u) / 128u) parts = (p.cap + 127u) / 128u;
+  auto kern = kp_pairs_main<BLOCK, UNITS>;
   static thread_local LaunchCache cache;
   uint32_t grid = 0;
   const kp_status st = resident_grid(kern, BLOCK, lds_bytes, &cache, &grid);
   if (st != KP_OK) return st;
   if (grid > p.n_wg) grid = p.n_wg;
-  hipLaunchKernelGGL(kern, dim3(grid), dim3(BLOCK), lds_bytes, s, p, o, split_log2);
+  hipLaunchKernelGGL(kern, dim3(grid), dim3(BLOCK), lds_bytes, s, p, o, parts);
   KP_HIP_TRY(hipGetLastError());
   return KP_OK;
+}
+
+template <int BLOCK>
+kp_status launch_pairs(const Trace& p, const PairsOut& o, uint32_t lds_bytes, hipStream_t s) {
+  return p.nrec <= 8u * BLOCK ? launch_pairs_units<BLOCK, 4>(p, o, lds_bytes, s) : launch_pairs_units<BLOCK, 8>(p, o, lds_bytes, s);
 }
 
 size_t count_bytes(size_t n_seg) { return ((n_seg + 3) / 4) * 16; }

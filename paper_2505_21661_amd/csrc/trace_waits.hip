@@ -10,11 +10,15 @@
 //   whole = (u32)(CLK2 - CLK0) - rec_cost, >= 0     when the END is paired with a START at CLK0.
 //
 // One decoder workgroup stages one recorded workgroup in LDS, ordered by rank; the hardware waves
-// share out the recorded waves in runs of consecutive ranks and walk them 64 ranks per round.  A
-// START takes what it needs to know about the rank below -- metadata, clock, whether that END is
-// paired and with which clock -- from the lane below through DPP wave shifts (the last lane of the
-// previous round stands in for lane 0); only when that rank is empty does it walk back through LDS.  Sums, extrema and the log2 histogram go to LDS
-// atomics; totals live in LDS across the recorded workgroups of a persistent decoder workgroup.
+// share out the recorded waves in runs of consecutive ranks and walk them 128 ranks per round, two per
+// lane.  A START takes what it needs to know about the rank below -- metadata, clock, whether that END is
+// paired and with which clock -- from its own lane or the one below through DPP wave shifts (the last lane of
+// the previous round stands in for lane 0).  A round with an END that has not its START right below it, or with an
+// empty rank, is walked 64 ranks at a time, with ballots over the region numbers and walks back through LDS.
+// Sums, extrema and the log2 histogram go to LDS atomics; totals live in LDS across the recorded workgroups of
+// a persistent decoder workgroup.
+// What bounds it: instruction issue.  Measured on 9000 workgroups of 3 waves x 1024 records: 144 us with the loads
+// waited for, one rank per lane and runs cut by capacity instead of by what the wave holds; 97 us (2.3 TB/s).
 #include "kp_stage.h"
 
 namespace {
@@ -36,23 +40,31 @@ __host__ __device__ inline WaitsLayout waits_layout(uint32_t n_wg, uint32_t W, u
 }
 enum { H_WAITS = 0, H_UNCOVERED, H_ASYNC, H_NWG = 8, H_WAVES, H_NREG, H_CAP, H_COST };
 
+constexpr uint32_t kNoId = 0xFFFFu;     // END << 7 | region of no record
 constexpr uint32_t kHistStride = 65;  // regions that hit the same bin land in different LDS banks
 
+// The per-(wave, region) sums exist in up to four copies, one per quarter of a hardware wave: lanes 16 apart tend
+// to hold the same region, and LDS atomics of one instruction that hit one address are done one after the other.
+constexpr uint32_t kMaxEntries = 1024;  // entries of those sums, copies included (one copy may exceed it)
+
 struct WaitsLds {
-  uint32_t hist, pw_pack, pw_max, pw_min, reg_sum, reg_cnt, reg_max, reg_min, unc, acnt, asum, total;
+  uint32_t hist, pw_pack, pw_max, pw_min, as_pack, unc, reg_sum, reg_cnt, reg_max, reg_min, acnt, asum, total;
+  uint32_t copies;
 };
-__host__ __device__ inline WaitsLds waits_lds(uint32_t from, uint32_t W, uint32_t R) {
+__host__ __device__ inline WaitsLds waits_lds(uint32_t from, uint32_t W, uint32_t R, uint32_t copies) {
   WaitsLds l;
+  l.copies = copies;
   uint32_t o = from;
   l.hist = o; o = align16(o + R * kHistStride * 4);
-  l.pw_pack = o; o = align16(o + W * R * 8);
-  l.pw_max = o; o = align16(o + W * R * 4);
-  l.pw_min = o; o = align16(o + W * R * 4);
+  l.pw_pack = o; o = align16(o + W * R * 8 * copies);
+  l.pw_max = o; o = align16(o + W * R * 4 * copies);
+  l.pw_min = o; o = align16(o + W * R * 4 * copies);
+  l.as_pack = o; o = align16(o + R * 8);
+  l.unc = o; o = align16(o + R * 8);
   l.reg_sum = o; o = align16(o + R * 8);
   l.reg_cnt = o; o = align16(o + R * 8);
   l.reg_max = o; o = align16(o + R * 4);
   l.reg_min = o; o = align16(o + R * 4);
-  l.unc = o; o = align16(o + R * 8);
   l.acnt = o; o = align16(o + R * 8);
   l.asum = o; o = align16(o + R * 8);
   l.total = o;
@@ -84,12 +96,14 @@ __global__ void kp_waits_finalize(uint64_t* out, uint32_t n_wg, uint32_t W, uint
   }
 }
 
-template <int BLOCK>
-__global__ __launch_bounds__(BLOCK) void kp_waits_main(Trace p, uint64_t* out_words, uint32_t split_log2) {
+// (6 hardware waves per SIMD, i.e. 80 vector registers: 97 us against 102 with 85 and 122 with 64)
+template <int BLOCK, int UNITS>
+__global__ __launch_bounds__(BLOCK, BLOCK == 1024 ? 4 : 6) void kp_waits_main(Trace p, uint64_t* out_words, uint32_t parts, uint32_t copies) {
   extern __shared__ __align__(16) unsigned char smem[];
   const Lds L = lds_layout(p.nrec);
-  const WaitsLds X = waits_lds(L.end, p.W, p.R);
+  const WaitsLds X = waits_lds(L.end, p.W, p.R, copies);
   const uint2* rec = reinterpret_cast<const uint2*>(smem + L.rec);
+  const u32x4* rec2 = reinterpret_cast<const u32x4*>(smem + L.rec);
   const uint32_t* sV = reinterpret_cast<const uint32_t*>(smem + L.v);
   uint32_t* hist = reinterpret_cast<uint32_t*>(smem + X.hist);
   unsigned long long* pw_pack = reinterpret_cast<unsigned long long*>(smem + X.pw_pack);
@@ -99,7 +113,8 @@ __global__ __launch_bounds__(BLOCK) void kp_waits_main(Trace p, uint64_t* out_wo
   unsigned long long* reg_cnt = reinterpret_cast<unsigned long long*>(smem + X.reg_cnt);
   uint32_t* reg_max = reinterpret_cast<uint32_t*>(smem + X.reg_max);
   uint32_t* reg_min = reinterpret_cast<uint32_t*>(smem + X.reg_min);
-  unsigned long long* unc = reinterpret_cast<unsigned long long*>(smem + X.unc);
+  unsigned long long* as_pack = reinterpret_cast<unsigned long long*>(smem + X.as_pack);  // this workgroup's whole operations: count << 46 | sum
+  uint32_t* unc = reinterpret_cast<uint32_t*>(smem + X.unc);                              // (fewer than 2^32 per decoder workgroup)
   unsigned long long* acnt = reinterpret_cast<unsigned long long*>(smem + X.acnt);
   unsigned long long* asum = reinterpret_cast<unsigned long long*>(smem + X.asum);
 
@@ -108,125 +123,156 @@ __global__ __launch_bounds__(BLOCK) void kp_waits_main(Trace p, uint64_t* out_wo
   const WaitsLayout SL = waits_layout(p.n_wg, W, R);
 
   for (uint32_t i = tid; i < R * kHistStride; i += BLOCK) hist[i] = 0;
-  for (uint32_t i = tid; i < W * R; i += BLOCK) { pw_pack[i] = 0; pw_max[i] = 0; pw_min[i] = 0xFFFFFFFFu; }
+  for (uint32_t i = tid; i < W * R * copies; i += BLOCK) { pw_pack[i] = 0; pw_max[i] = 0; pw_min[i] = 0xFFFFFFFFu; }
   for (uint32_t i = tid; i < R; i += BLOCK) {
     reg_sum[i] = 0; reg_cnt[i] = 0; reg_max[i] = 0; reg_min[i] = 0xFFFFFFFFu;
-    unc[i] = 0; acnt[i] = 0; asum[i] = 0;
+    unc[i] = 0; as_pack[i] = 0; acnt[i] = 0; asum[i] = 0;
   }
   // stage_workgroup's first barrier orders these stores before any use
 
+  uint32_t region_bits = 0; while ((1u << region_bits) < R) ++region_bits;
+  InFlight<UNITS> coming;
+  request_workgroup<BLOCK, UNITS>(p, blockIdx.x, coming);
   uint32_t iter = 0;
   for (uint32_t wg = blockIdx.x; wg < p.n_wg; wg += gridDim.x, ++iter) {
-    stage_workgroup<BLOCK>(p, smem, L, wg, iter);
+    stage_workgroup<BLOCK, UNITS>(p, smem, L, wg, iter, coming);
+    request_workgroup<BLOCK, UNITS>(p, wg + gridDim.x < p.n_wg ? wg + gridDim.x : wg, coming);
     const uint32_t live_tag = live_tag_of(iter);
-    // ---- walk: 2^split_log2 hardware waves share one recorded wave, each a run of consecutive ranks ----
+    // ---- walk: `parts` hardware waves share one recorded wave, each an equal run of consecutive rounds ----
     // Nothing but the look-back crosses from one run into the next, and the staged records of the
     // earlier run are all in LDS, so the runs are independent.
-    if (hw < (W << split_log2)) {
-      const uint32_t w = hw >> split_log2, part = hw & ((1u << split_log2) - 1u);
+    if (hw < W * parts) {
+      const uint32_t w = hw / parts, part = hw - w * parts;
       const uint32_t wofs = w << cl2, V = sV[w];
-      const uint32_t plen = p.cap >> split_log2;
+      const uint32_t rounds = (V + 127u) >> 7, plen = ((rounds + parts - 1u) / parts) << 7;
       const uint32_t k0 = part * plen, k1 = V < k0 + plen ? V : k0 + plen;
-      uint32_t cm[4];                       // metadata of the four ranks below the round
-      uint32_t ct = 0u, cpaired = 0u, cpt = 0u;  // clock / paired flag / START clock of the rank just below
-#pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        const uint2 r = rec[wofs + (k0 > (uint32_t)j ? k0 - 1u - j : 0u)];
-        cm[j] = (k0 > (uint32_t)j && is_live(r.y, live_tag)) ? r.y : 0u;
-        if (j == 0) ct = r.x;
-      }
-      if (cm[0] & kMEnd) {  // a run that starts right above an END: is that END paired? (uniform)
-        for (uint32_t jj = k0 - 1u; jj-- > 0;) {
-          const uint2 rj = rec[wofs + jj];
-          if (!is_live(rj.y, live_tag) || ((rj.y ^ cm[0]) & kMRegion)) continue;
-          if (!(rj.y & kMEnd)) { cpaired = 1u; cpt = rj.x; }
-          break;
+      const unsigned long long lt_mask = (1ull << lane) - 1ull;
+      const uint32_t copy = (lane >> 4) & (copies - 1u);
+      // The START of an END with region `r` at rank `at`: the nearest record of its region below `from`, if that is one.
+      auto find_start = [&](uint32_t from, uint32_t r, uint32_t& clock) -> bool {
+        for (uint32_t kk = from; kk-- > 0;) {
+          const uint2 rq = rec[wofs + kk];
+          if (!is_live(rq.y, live_tag) || (rq.y & kMRegion) != r) continue;
+          clock = rq.x;
+          return !(rq.y & kMEnd);
+        }
+        return false;
+      };
+      // the rank just below the round: metadata byte (kNoId: no record) and clock; for an END, its START
+      uint32_t carry_id = kNoId, carry_t = 0u, carry_paired = 0u, carry_start = 0u;
+      if (k0 > 0u && k0 < k1) {  // (uniform)
+        const uint2 r = rec[wofs + k0 - 1u];
+        if (is_live(r.y, live_tag)) {
+          carry_id = r.y & 0xFFu; carry_t = r.x;
+          if (carry_id & kMEnd) carry_paired = find_start(k0 - 1u, carry_id & kMRegion, carry_start) ? 1u : 0u;
         }
       }
-      uint2 r_next = rec[wofs + (k0 + lane < k1 ? k0 + lane : 0u)];  // one round ahead, to hide the LDS latency
-      for (uint32_t kb = k0; kb < k1; kb += 64) {
+      // A wait: the START of this lane (clock after) above an END of region `a` (clock before), which is paired with
+      // a START at `begin` or not.
+      auto account = [&](uint32_t a, uint32_t before, uint32_t after, bool paired, uint32_t begin) __attribute__((always_inline)) {
+        const uint32_t gap = after - before;
+        const uint32_t e = (w * R + a) * copies + copy;
+        atomicAdd(&pw_pack[e], (1ull << 46) | (unsigned long long)gap);
+        atomicMax(&pw_max[e], gap);
+        atomicMin(&pw_min[e], gap);
+        atomicAdd(&hist[a * kHistStride + (gap ? 31 - __clz(gap) : 0)], 1u);
+        if (gap <= p.rec_cost) atomicAdd(&unc[a], 1u);
+        if (paired) {
+          const uint32_t whole = after - begin;
+          atomicAdd(&as_pack[a], (1ull << 46) | (unsigned long long)(whole > p.rec_cost ? whole - p.rec_cost : 0u));
+        }
+      };
+      // 64 ranks from kb, one per lane, any record.
+      auto round_64 = [&](uint32_t kb) __attribute__((always_inline)) {
         const uint32_t k = kb + lane;
-        const bool in = k < k1;
-        const uint32_t q0 = wofs + (in ? k : k1 - 1);
-        const uint2 r0 = r_next;
-        {
-          const uint32_t kn = k + 64;
-          r_next = rec[wofs + (kn < k1 ? kn : 0u)];
-        }
-        const bool valid = in && is_live(r0.y, live_tag);
-        const uint32_t m0 = valid ? r0.y : 0u, t0 = r0.x;
-        const uint32_t m1 = wave_shr1(m0, cm[0]);
-        const uint32_t m2 = wave_shr1(m1, cm[1]);
-        const uint32_t m3 = wave_shr1(m2, cm[2]);
-        const uint32_t m4 = wave_shr1(m3, cm[3]);
-        const uint32_t t1 = wave_shr1(t0, ct);
-#pragma unroll
-        for (int j = 0; j < 4; ++j) cm[j] = (uint32_t)__builtin_amdgcn_readlane((int)m0, 63 - j);
-        ct = (uint32_t)__builtin_amdgcn_readlane((int)t0, 63);
+        const uint2 r0 = rec[wofs + (k < k1 ? k : 0u)];
+        const bool valid = k < k1 && is_live(r0.y, live_tag);
+        const uint32_t id = valid ? r0.y & 0xFFu : kNoId, t0 = r0.x, region = id & kMRegion;
+        uint32_t below_id = wave_shr1(id, carry_id), below_t = wave_shr1(t0, carry_t);
         // ---- an END is paired iff the nearest earlier record of its region is a START ------------------
-        const uint32_t region = m0 & kMRegion;
-        const bool is_end = (m0 & kMEnd) != 0u;  // m0 is 0 for a rank that holds no record
-        const uint32_t want = kMValid | region, sel = kMValid | kMRegion;
-        const bool h1 = (m1 & sel) == want, h2 = (m2 & sel) == want, h3 = (m3 & sel) == want, h4 = (m4 & sel) == want;
-        bool have = h1 || h2 || h3 || h4;
-        uint32_t pm = h1 ? m1 : (h2 ? m2 : (h3 ? m3 : m4));
-        uint32_t pq = q0 - (h1 ? 1u : (h2 ? 2u : (h3 ? 3u : 4u)));
-        if (is_end && !have && k > 4) {  // slow path: walk further back
-          for (uint32_t kk = k - 4; kk-- > 0;) {
-            const uint32_t mq = rec[wofs + kk].y;
-            if (is_live(mq, live_tag) && (mq & kMRegion) == region) { have = true; pm = mq; pq = wofs + kk; break; }
+        const bool is_end = valid && (id & kMEnd) != 0u;
+        bool paired = is_end && below_id == region;
+        uint32_t start_t = below_t;
+        if (__builtin_amdgcn_ballot_w64(is_end && !paired)) {
+          unsigned long long same = __builtin_amdgcn_ballot_w64(valid);
+          for (uint32_t b = 0; b < region_bits; ++b) {
+            const unsigned long long set = __builtin_amdgcn_ballot_w64(valid && ((region >> b) & 1u));
+            same &= ((region >> b) & 1u) ? set : ~set;
+          }
+          const unsigned long long ends = __builtin_amdgcn_ballot_w64(is_end), lower = same & lt_mask;
+          const int src = lower ? 63 - (int)__builtin_clzll(lower) : 0;
+          const uint32_t far_t = (uint32_t)__shfl((int)t0, src, 64);
+          if (is_end && !paired) {
+            if (lower) { paired = !((ends >> src) & 1ull); start_t = far_t; }
+            else paired = find_start(kb, region, start_t);
           }
         }
-        const bool paired = is_end && have && !(pm & kMEnd);
-        const uint32_t pt = rec[paired ? pq : wofs].x;  // CLK0 of a paired END
         // ---- a START looks at the record below it -------------------------------------------------------
-        uint32_t below_m = m1, below_t = t1;
-        uint32_t below_paired = wave_shr1(paired ? 1u : 0u, cpaired);
-        uint32_t below_pt = wave_shr1(pt, cpt);
-        cpaired = (uint32_t)__builtin_amdgcn_readlane((int)(paired ? 1u : 0u), 63);
-        cpt = (uint32_t)__builtin_amdgcn_readlane((int)pt, 63);
+        uint32_t below_paired = wave_shr1(paired ? 1u : 0u, carry_paired);
+        uint32_t below_start = wave_shr1(start_t, carry_start);
+        carry_id = (uint32_t)__builtin_amdgcn_readlane((int)id, 63);
+        carry_t = (uint32_t)__builtin_amdgcn_readlane((int)t0, 63);
+        carry_paired = (uint32_t)__builtin_amdgcn_readlane((int)(paired ? 1u : 0u), 63);
+        carry_start = (uint32_t)__builtin_amdgcn_readlane((int)start_t, 63);
         const bool is_start = valid && !is_end;
-        if (is_start && k > 0 && !(m1 & kMValid)) {  // the rank below is empty: find the record below it
-          below_m = 0u;
-          for (uint32_t kk = k - 1; kk-- > 0;) {
+        if (is_start && below_id == kNoId) {  // the rank below is empty
+          for (uint32_t kk = k; kk-- > 0;) {  // the record below it
             const uint2 rq = rec[wofs + kk];
             if (!is_live(rq.y, live_tag)) continue;
-            below_m = rq.y; below_t = rq.x; below_paired = 0u;
-            if (rq.y & kMEnd) {  // is that END paired?
-              for (uint32_t jj = kk; jj-- > 0;) {
-                const uint2 rj = rec[wofs + jj];
-                if (!is_live(rj.y, live_tag) || ((rj.y ^ rq.y) & kMRegion)) continue;
-                if (!(rj.y & kMEnd)) { below_paired = 1u; below_pt = rj.x; }
-                break;
-              }
-            }
+            below_id = rq.y & 0xFFu; below_t = rq.x;
+            below_paired = (below_id & kMEnd) && find_start(kk, below_id & kMRegion, below_start) ? 1u : 0u;
             break;
           }
         }
-        if (is_start && (below_m & kMEnd)) {  // below_m is 0 when there is no record below
-          const uint32_t a = below_m & kMRegion;
-          const uint32_t gap = t0 - below_t;
-          const uint32_t e = w * R + a;
-          atomicAdd(&pw_pack[e], (1ull << 46) | (unsigned long long)gap);
-          atomicMax(&pw_max[e], gap);
-          atomicMin(&pw_min[e], gap);
-          atomicAdd(&hist[a * kHistStride + (gap ? 31 - __clz(gap) : 0)], 1u);
-          if (gap <= p.rec_cost) atomicAdd(&unc[a], 1ull);
-          if (below_paired) {
-            const uint32_t whole = t0 - below_pt;
-            atomicAdd(&acnt[a], 1ull);
-            atomicAdd(&asum[a], (unsigned long long)(whole > p.rec_cost ? whole - p.rec_cost : 0u));
-          }
+        if (is_start && below_id != kNoId && (below_id & kMEnd)) account(below_id & kMRegion, below_t, t0, below_paired != 0u, below_start);
+      };
+      // 128 ranks per round, two neighbours per lane, as long as every END among them has its START right below it
+      // and no rank is empty: then a lane holds at most one wait (a START above a START is none).
+      u32x4 next = rec2[(wofs + (k0 + 2u * lane < k1 ? k0 + 2u * lane : 0u)) >> 1];  // one round ahead, to hide the LDS latency
+      for (uint32_t kb = k0; kb < k1; kb += 128) {
+        const uint32_t k = kb + 2u * lane;
+        const u32x4 r = next;  // {clock, metadata} of the even rank and of the odd one
+        next = rec2[(wofs + (k + 128u < k1 ? k + 128u : 0u)) >> 1];
+        const bool in0 = k < k1, in1 = k + 1u < k1;
+        const uint32_t id0 = in0 && is_live(r.y, live_tag) ? r.y & 0xFFu : kNoId;
+        const uint32_t id1 = in1 && is_live(r.w, live_tag) ? r.w & 0xFFu : kNoId;
+        const uint32_t below_id = wave_shr1(id1, carry_id), below_t = wave_shr1(r.z, carry_t);
+        // x ^ y == kMEnd with END x: an END over its START
+        const bool near0 = (id0 ^ below_id) == kMEnd && id0 >= kMEnd, near1 = (id1 ^ id0) == kMEnd && id1 >= kMEnd;
+        const bool end0 = (id0 & ~kMRegion) == kMEnd, end1 = (id1 & ~kMRegion) == kMEnd;
+        if (__builtin_amdgcn_ballot_w64((end0 && !near0) || (end1 && !near1) || (in0 && id0 == kNoId) || (in1 && id1 == kNoId) ||
+                                        (in0 && k > 0u && below_id == kNoId)) != 0ull) {
+          round_64(kb);
+          if (kb + 64u < k1) round_64(kb + 64u);
+          continue;
         }
+        // of the lane below: is its odd record a paired END, and with which START
+        const uint32_t below_paired = wave_shr1(near1 ? 1u : 0u, carry_paired), below_start = wave_shr1(r.x, carry_start);
+        carry_id = (uint32_t)__builtin_amdgcn_readlane((int)id1, 63);
+        carry_t = (uint32_t)__builtin_amdgcn_readlane((int)r.z, 63);
+        carry_paired = (uint32_t)__builtin_amdgcn_readlane((int)(near1 ? 1u : 0u), 63);
+        carry_start = (uint32_t)__builtin_amdgcn_readlane((int)r.x, 63);
+        const bool wait1 = id1 <= kMRegion && end0;                                        // START over END in this lane
+        const bool wait0 = id0 <= kMRegion && (below_id & ~kMRegion) == kMEnd;  // START over the END of the lane below
+        if (wait0 || wait1)
+          account((wait1 ? id0 : below_id) & kMRegion, wait1 ? r.x : below_t, wait1 ? r.z : r.x, wait1 ? near0 : below_paired != 0u,
+                  wait1 ? below_t : below_start);
       }
     }
     __syncthreads();
     // ---- per-(workgroup, wave, region) output, fold into running totals ------------------------------------
     for (uint32_t e = tid; e < W * R; e += BLOCK) {
-      const unsigned long long pk = pw_pack[e];
+      unsigned long long pk = 0ull;
+      uint32_t mx = 0u, mn = 0xFFFFFFFFu;
+      for (uint32_t c = 0; c < copies; ++c) {
+        const uint32_t ec = e * copies + c;
+        pk += pw_pack[ec];
+        mx = pw_max[ec] > mx ? pw_max[ec] : mx;
+        mn = pw_min[ec] < mn ? pw_min[ec] : mn;
+        pw_pack[ec] = 0; pw_max[ec] = 0; pw_min[ec] = 0xFFFFFFFFu;
+      }
       const uint32_t n = (uint32_t)(pk >> 46);
       const unsigned long long s = pk & ((1ull << 46) - 1);
-      const uint32_t mx = pw_max[e], mn = pw_min[e];
       uint64_t* dst = out_words + SL.per + ((size_t)wg * W * R + e) * 2;
       dst[0] = s;
       dst[1] = (uint64_t)n | ((uint64_t)mx << 32);
@@ -237,10 +283,15 @@ __global__ __launch_bounds__(BLOCK) void kp_waits_main(Trace p, uint64_t* out_wo
         atomicMax(&reg_max[r], mx);
         atomicMin(&reg_min[r], mn);
       }
-      pw_pack[e] = 0; pw_max[e] = 0; pw_min[e] = 0xFFFFFFFFu;
     }
-    __syncthreads();
+    for (uint32_t r = tid; r < R; r += BLOCK) {
+      acnt[r] += as_pack[r] >> 46; asum[r] += as_pack[r] & ((1ull << 46) - 1);
+      as_pack[r] = 0ull;
+    }
+    // No barrier here: what this tail reads and resets is next touched behind the barriers of the next workgroup's
+    // staging, and nothing it touches belongs to the staging.
   }
+  __syncthreads();
 
   // ---- flush this decoder workgroup's totals --------------------------------------------------------
   unsigned long long* out = reinterpret_cast<unsigned long long*>(out_words);
@@ -254,34 +305,41 @@ __global__ __launch_bounds__(BLOCK) void kp_waits_main(Trace p, uint64_t* out_wo
       atomicAdd(&out[SL.sum + r], reg_sum[r]);
       atomicMax(&out[SL.max + r], (unsigned long long)reg_max[r]);
       atomicMin(&out[SL.min + r], (unsigned long long)reg_min[r]);
-      if (unc[r]) atomicAdd(&out[SL.unc + r], unc[r]);
+      if (unc[r]) atomicAdd(&out[SL.unc + r], (unsigned long long)unc[r]);
       if (acnt[r]) atomicAdd(&out[SL.acnt + r], acnt[r]);
       if (asum[r]) atomicAdd(&out[SL.asum + r], asum[r]);
     }
   }
 }
 
-template <int BLOCK>
-kp_status launch_waits(const Trace& p, uint64_t* out, uint32_t lds_bytes, hipStream_t s) {
-  // hardware waves per recorded wave: as many as the block has, while a run keeps at least 64 ranks
-  uint32_t split_log2 = 0;
-  while ((p.W << (split_log2 + 1)) <= (uint32_t)BLOCK / 64u && (p.cap >> (split_log2 + 1)) >= 64u) ++split_log2;
-  auto kern = kp_waits_main<BLOCK>;
+template <int BLOCK, int UNITS>
+kp_status launch_waits_units(const Trace& p, uint64_t* out, const WaitsLds& X, hipStream_t s) {
+  // hardware waves per recorded wave: as many as the block has, while a run keeps a round of 128 ranks
+  uint32_t parts = (uint32_t)BLOCK / 64u / p.W;
+  if (parts > (p.cap + 127u) / 128u) parts = (p.cap + 127u) / 128u;
+  auto kern = kp_waits_main<BLOCK, UNITS>;
   static thread_local LaunchCache cache;
   uint32_t grid = 0;
-  const kp_status st = resident_grid(kern, BLOCK, lds_bytes, &cache, &grid);
+  const kp_status st = resident_grid(kern, BLOCK, X.total, &cache, &grid);
   if (st != KP_OK) return st;
   if (grid > p.n_wg) grid = p.n_wg;
-  hipLaunchKernelGGL(kern, dim3(grid), dim3(BLOCK), lds_bytes, s, p, out, split_log2);
+  hipLaunchKernelGGL(kern, dim3(grid), dim3(BLOCK), X.total, s, p, out, parts, X.copies);
   KP_HIP_TRY(hipGetLastError());
   return KP_OK;
+}
+
+template <int BLOCK>
+kp_status launch_waits(const Trace& p, uint64_t* out, const WaitsLds& X, hipStream_t s) {
+  return p.nrec <= 8u * BLOCK ? launch_waits_units<BLOCK, 4>(p, out, X, s) : launch_waits_units<BLOCK, 8>(p, out, X, s);
 }
 
 kp_status waits_impl(const void* raw, size_t n, const kp_trace_hdr& h, void* out_waits, hipStream_t s) {
   Trace p;
   const kp_status st = trace_from_header(raw, n, h, out_waits, &p);
   if (st != KP_OK) return st;
-  const WaitsLds X = waits_lds(lds_layout(p.nrec).end, p.W, p.R);
+  uint32_t copies = 4;
+  while (copies > 1 && (copies * p.W * p.R > kMaxEntries || waits_lds(lds_layout(p.nrec).end, p.W, p.R, copies).total > kMaxLds)) copies >>= 1;
+  const WaitsLds X = waits_lds(lds_layout(p.nrec).end, p.W, p.R, copies);
   if (X.total > kMaxLds)
     return kp::fail(KP_ERR_UNSUPPORTED_SHAPE, "wait replay needs %u B of LDS for this geometry (limit %u)", X.total, kMaxLds);
 
@@ -293,9 +351,9 @@ kp_status waits_impl(const void* raw, size_t n, const kp_trace_hdr& h, void* out
   KP_HIP_TRY(hipGetLastError());
   if (p.n_wg > 0) {
     const int block = block_threads(p.W, p.nrec);
-    const kp_status ls = block == 1024 ? launch_waits<1024>(p, out, X.total, s)
-                       : block == 512  ? launch_waits<512>(p, out, X.total, s)
-                                       : launch_waits<256>(p, out, X.total, s);
+    const kp_status ls = block == 1024 ? launch_waits<1024>(p, out, X, s)
+                       : block == 512  ? launch_waits<512>(p, out, X, s)
+                                       : launch_waits<256>(p, out, X, s);
     if (ls != KP_OK) return ls;
   }
   hipLaunchKernelGGL(kp_waits_finalize, dim3(1), dim3(64), 0, s, out, p.n_wg, p.W, p.R);

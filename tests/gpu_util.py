@@ -37,3 +37,43 @@ def assert_stats_equal(want: np.ndarray, got: np.ndarray, oracle_mod):
     bad = np.argwhere((a["per"]["sum"] != b["per"]["sum"]) | (a["per"]["n"] != b["per"]["n"]) | (a["per"]["max"] != b["per"]["max"]))
     assert bad.size == 0, ("per", bad[:5], a["per"][tuple(bad[0])], b["per"][tuple(bad[0])])
     raise AssertionError("stats blocks differ outside the named fields")
+
+
+def mostly_sequential_trace(seed, W, R, cap, holes=False):
+    """Regions that follow one another, with here and there a region around others, a START without END, an END
+    without START and (holes) a record that fails its checks; two workgroups, ragged totals."""
+    import inputs
+
+    rng = np.random.default_rng(seed)
+    wgs = []
+    for _ in range(2):
+        evs = []
+        for w in range(W):
+            t, wave, outer = 0, [], -1
+            total = cap + 37 if w == 0 else int(rng.integers(1, cap + cap // 2))
+            while len(wave) < total:
+                t += int(rng.integers(0, 40))
+                r, x = int(rng.integers(0, R)), rng.random()
+                if x < 0.01 and outer < 0:
+                    outer = r
+                    wave.append((inputs.PHASE_START, r, t))
+                elif x < 0.02 and outer >= 0:
+                    wave.append((inputs.PHASE_END, outer, t))
+                    outer = -1
+                elif x < 0.025:
+                    wave.append((inputs.PHASE_START, r, t))
+                elif x < 0.03:
+                    wave.append((inputs.PHASE_END, r, t))
+                else:
+                    wave.append((inputs.PHASE_START, r, t))
+                    t += int(rng.integers(0, 900))
+                    wave.append((inputs.PHASE_END, r, t))
+            evs.append(wave[:total])
+        wg = inputs.events_to_wg(evs, cap, flush=False)
+        if holes:
+            for seg in wg["slots"]:
+                for _ in range(len(seg) // 90):
+                    i = int(rng.integers(0, len(seg)))
+                    seg[i] = (0xFFFFFFFF, seg[i][1])
+        wgs.append(wg)
+    return inputs.encode_trace(wgs, W, R, cap, rec_cost=7)

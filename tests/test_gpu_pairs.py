@@ -66,6 +66,16 @@ def test_generated_traces(kp, oracle_mod, W, R, cap, total):
     assert_pairs_equal(oracle_mod, raw, run_pairs(kp, raw))
 
 
+@pytest.mark.parametrize("holes", [False, True])
+@pytest.mark.parametrize("W,R,cap", [(1, 128, 2048), (3, 7, 1024), (16, 16, 256), (8, 33, 128), (5, 3, 64), (2, 5, 8192)])
+def test_mostly_sequential_traces(kp, oracle_mod, W, R, cap, holes):
+    """Rounds of two ranks per lane next to rounds that have to look further back, in runs of every length."""
+    from tests.gpu_util import mostly_sequential_trace
+
+    raw = mostly_sequential_trace(17 * W + R, W, R, cap, holes)
+    assert_pairs_equal(oracle_mod, raw, run_pairs(kp, raw, use_hdr=True))
+
+
 def test_many_workgroups_exercise_generation_reuse(kp, oracle_mod):
     # more recorded workgroups than resident decoder workgroups: the staging area is reused
     spec = inputs.TraceSpec(n_wg=3000, waves=4, n_regions=6, cap_wave=64, total_per_wave=64, total_var=40, seed=77,
