@@ -256,26 +256,8 @@ __global__ void kp_reduce_init(const uint32_t* trace_hdr, uint64_t* out, uint32_
   }
 }
 
-// finalize (one workgroup): cnt from the histogram, O = Otmp + Otmp^T off the diagonal, U = diag,
-// F = O/U.  Otmp is what the main kernels staged in the F area.
-__global__ void kp_reduce_finalize(uint64_t* out, uint32_t n_wg, uint32_t W, uint32_t R) {
-  const StatsLayout l = stats_layout(n_wg, W, R);
-  const uint32_t tid = threadIdx.x;
-  for (uint32_t r = tid; r < R; r += blockDim.x) {
-    uint64_t c = 0;
-    for (int b = 0; b < 64; ++b) c += out[l.hist + (size_t)r * 64 + b];
-    out[l.cnt + r] = c;
-    out[l.U + r] = out[l.F + (size_t)r * R + r];
-  }
-  for (uint32_t i = tid; i < R * R; i += blockDim.x) {
-    const uint32_t a = i / R, b = i % R;
-    out[l.O + i] = a == b ? out[l.F + i] : out[l.F + i] + out[l.F + (size_t)b * R + a];
-  }
-  __syncthreads();  // (a workgroup's own global stores are visible to it after the barrier)
-  for (uint32_t i = tid; i < R * R; i += blockDim.x) {
-    const uint64_t u = out[l.U + i / R], o = out[l.O + i];
-    reinterpret_cast<double*>(out)[l.F + i] = u ? (double)o / (double)u : 0.0;
-  }
+__global__ __launch_bounds__(1024) void kp_reduce_derive(uint64_t* out, uint32_t n_wg, uint32_t W, uint32_t R) {
+  derive_figures<1024>(out, stats_layout(n_wg, W, R), R);
 }
 
 // ------------------------------------------------------------------------------------------
@@ -1003,7 +985,9 @@ __global__ __launch_bounds__(BLOCK) void kp_reduce_main(DecodeParams p) {
       for (int l = 0; l < 3; ++l) acc[l] = i32x4{0, 0, 0, 0};
       const uint32_t j = lane & 15u;  // operand row / column: region j
       const uint32_t up = 15u - j;      // shift that takes bit j of a 16-bit set to its top
-      for (uint32_t n = 0; n < 16; ++n) {  // 64 segments: those of lanes 4n .. 4n + 3
+      // (a wave that is not full has no segments past its share of the records; with 16 waves one register is too many)
+      const uint32_t sets = BLOCK == 1024 ? 16u : (tmp[T_EVENTS] - (tid & ~63u) * kNR + 63u) >> 6;
+      for (uint32_t n = 0; n < 16 && n < sets; ++n) {  // 64 segments: those of lanes 4n .. 4n + 3
         const uint32_t src = (tid & ~63u) + 4u * n + (lane >> 4);
         const u32x4* from = reinterpret_cast<const u32x4*>(clk + clk_word(src * kNR));
         const u32x4 s0 = from[0], s1 = from[1];
@@ -1100,7 +1084,7 @@ __global__ __launch_bounds__(BLOCK) void kp_reduce_main(DecodeParams p) {
     if (h) atomicAdd(&out[SL.hist + i], (unsigned long long)h);
   }
   for (uint32_t i = tid_k; i < R * R; i += BLOCK)
-    if (oacc[i]) atomicAdd(&out[SL.F + i], oacc[i]);  // staged in the F area until finalize
+    if (oacc[i]) atomicAdd(&out[SL.F + i], oacc[i]);  // (the upper triangle)
   for (uint32_t r = tid_k; r < R; r += BLOCK) {
     if (reg_min[r] != 0xFFFFFFFFu || reg_max[r] || reg_sum[r]) {
       atomicAdd(&out[SL.sum + r], reg_sum[r]);
@@ -1109,6 +1093,7 @@ __global__ __launch_bounds__(BLOCK) void kp_reduce_main(DecodeParams p) {
     }
   }
   if (tid_k < H_STATUS && ctr[tid_k]) atomicAdd(&out[tid_k], ctr[tid_k]);
+  if (BLOCK < 1024 && gridDim.x <= kMaxCounted) finish_counted<BLOCK>(p.out, SL, R, misc);
 }
 
 // Launch shape of one kernel instantiation for one LDS size, queried once per device.
@@ -1201,7 +1186,8 @@ kp_status reduce_impl(const void* raw, size_t n, const kp_trace_hdr& h, void* ou
     if (st != KP_OK) return st;
   }
   if (main_end) KP_HIP_TRY(hipEventRecord(main_end, s));
-  hipLaunchKernelGGL(kp_reduce_finalize, dim3(1), dim3(256), 0, s, out, h.n_wg, W, R);
+  if (!wide && block < 1024 && h.n_wg <= kMaxCounted) return KP_OK;  // (at most one decoder workgroup each: derived by the last)
+  hipLaunchKernelGGL(kp_reduce_derive, dim3(1), dim3(1024), 0, s, out, h.n_wg, W, R);
   KP_HIP_TRY(hipGetLastError());
   return KP_OK;
 }

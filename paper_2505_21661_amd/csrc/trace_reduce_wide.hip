@@ -256,12 +256,13 @@ __global__ __launch_bounds__(kBlock) void kp_reduce_wide(WideParams p) {
         reinterpret_cast<uint4*>(rows_lds)[e] = make_uint4(0u, 0u, 0u, 0u);
         row_min[e] = 0xFFFFFFFFu;
       } else {
-        uint64_t* row = p.out + SL.per + ((size_t)wg * W * R + e) * 2;
-        row[0] = 0ull; row[1] = 0ull;
+        uint64_t* row = p.out + SL.per + ((size_t)wg * W * R + e) * 2;  // (stored where the atomics act)
+        __hip_atomic_store(&row[0], 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        __hip_atomic_store(&row[1], 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
       }
     }
     if (tid < kWavesHw) edge[4u * tid] = 0u;
-    // (the barrier waits for a wave's stores, and the rows and the atomics on them meet in one L2: no fence)
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // the rows are cleared before any wave adds to them
     __syncthreads();
     uint32_t held = 0, max_v = 0;
     for (uint32_t w = 0; w < W; ++w) {
@@ -911,7 +912,7 @@ __global__ __launch_bounds__(kBlock) void kp_reduce_wide(WideParams p) {
     const uint32_t h = hist[(i >> 6) * kHistStride + (i & 63u)];
     if (h) atomicAdd(&out[SL.hist + i], (unsigned long long)h);
   }
-  for (uint32_t i = tid; i < R * R; i += kBlock) {  // staged in the F area until finalize; entry (a, b) with a <= b holds the pair's sum
+  for (uint32_t i = tid; i < R * R; i += kBlock) {
     const uint32_t a = i / R, b = i - a * R;
     if (a <= b && otri[b * (b + 1u) / 2u + a]) atomicAdd(&out[SL.F + i], otri[b * (b + 1u) / 2u + a]);
   }

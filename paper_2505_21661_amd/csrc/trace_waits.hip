@@ -85,17 +85,6 @@ __global__ void kp_waits_init(uint64_t* out, uint32_t n_wg, uint32_t W, uint32_t
   }
 }
 
-// finalize: the three header counts are the sums of the per-region counts.
-__global__ void kp_waits_finalize(uint64_t* out, uint32_t n_wg, uint32_t W, uint32_t R) {
-  const WaitsLayout l = waits_layout(n_wg, W, R);
-  if (threadIdx.x < 3) {
-    const size_t from = threadIdx.x == 0 ? l.cnt : (threadIdx.x == 1 ? l.unc : l.acnt);
-    uint64_t s = 0;
-    for (uint32_t r = 0; r < R; ++r) s += out[from + r];
-    out[threadIdx.x] = s;
-  }
-}
-
 // (6 hardware waves per SIMD, i.e. 80 vector registers: 97 us against 102 with 85 and 122 with 64)
 template <int BLOCK, int UNITS>
 __global__ __launch_bounds__(BLOCK, BLOCK == 1024 ? 4 : 6) void kp_waits_main(Trace p, uint64_t* out_words, uint32_t parts, uint32_t copies) {
@@ -302,11 +291,12 @@ __global__ __launch_bounds__(BLOCK, BLOCK == 1024 ? 4 : 6) void kp_waits_main(Tr
   for (uint32_t r = tid; r < R; r += BLOCK) {
     if (reg_cnt[r]) {
       atomicAdd(&out[SL.cnt + r], reg_cnt[r]);
+      atomicAdd(&out[H_WAITS], reg_cnt[r]);  // the three header counts are the sums of the regions'
       atomicAdd(&out[SL.sum + r], reg_sum[r]);
       atomicMax(&out[SL.max + r], (unsigned long long)reg_max[r]);
       atomicMin(&out[SL.min + r], (unsigned long long)reg_min[r]);
-      if (unc[r]) atomicAdd(&out[SL.unc + r], (unsigned long long)unc[r]);
-      if (acnt[r]) atomicAdd(&out[SL.acnt + r], acnt[r]);
+      if (unc[r]) { atomicAdd(&out[SL.unc + r], (unsigned long long)unc[r]); atomicAdd(&out[H_UNCOVERED], (unsigned long long)unc[r]); }
+      if (acnt[r]) { atomicAdd(&out[SL.acnt + r], acnt[r]); atomicAdd(&out[H_ASYNC], acnt[r]); }
       if (asum[r]) atomicAdd(&out[SL.asum + r], asum[r]);
     }
   }
@@ -356,8 +346,6 @@ kp_status waits_impl(const void* raw, size_t n, const kp_trace_hdr& h, void* out
                                        : launch_waits<256>(p, out, X, s);
     if (ls != KP_OK) return ls;
   }
-  hipLaunchKernelGGL(kp_waits_finalize, dim3(1), dim3(64), 0, s, out, p.n_wg, p.W, p.R);
-  KP_HIP_TRY(hipGetLastError());
   return KP_OK;
 }
 
