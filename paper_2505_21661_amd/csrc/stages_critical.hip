@@ -8,16 +8,21 @@
 // index); the path ends in the last one; the stage before X is the latest stage of that order, earlier
 // than X, that had ended by the time X started.
 //
-// One decoder workgroup per recorded workgroup at a time (persistent, grid stride), everything in LDS:
-//   1  the entries become 64-bit keys max_end << 32 | index (no stage: all ones) and are sorted with
-//      a bitonic network;
-//   2  every stage finds the stage before it with one binary search over the sorted ends -- the stages
-//      that ended by its start are a prefix of the order -- which gives a forest of "waited for" links;
+// One decoder workgroup per recorded workgroup at a time (persistent, grid stride), everything in LDS; the
+// table entries of the next recorded workgroup are requested before this one's are worked on:
+//   1  the stages become 64-bit keys max_end << 32 | index and are sorted by a counting sort: P cells of
+//      equal length over [first end, last end], one LDS atomic with return per stage, a prefix sum over the
+//      cells, and inside a cell (one stage on average) the rank by comparison.  A table whose fullest cell
+//      holds more than kMaxCell stages is merged in a bitonic network instead;
+//   2  every stage finds the stage before it -- the stages that ended by its start are a prefix of the
+//      order -- by a search of the cell its start lies in, which gives a forest of "waited for" links;
 //   3  the path is the list that starts at the last stage: it is marked by pointer doubling (in round k
 //      every marked stage marks the stage 2^k links on and every link is replaced by two), log2(n)
 //      rounds instead of a walk of up to n steps;
 //   4  marked stages add their latency to their region's totals, and the gaps to the stage before them
 //      to the workgroup's bubbles.
+// Bound by LDS round trips between barriers.  4096 workgroups of
+// 16 regions x 64 iterations, rows and stage table included: 596 us with the network, 545 us with the cells.
 #include "kp_common.h"
 
 namespace {
@@ -27,13 +32,16 @@ typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 constexpr int kBlock = 256;
 constexpr uint32_t kMaxEntries = 4096;
 constexpr uint32_t kNone = 0xFFFFFFFFu;
+// Ranking inside a cell reads all keys of the cell for each of them; the network reads and writes every key
+// 34 times for 16 runs of 64 (55 times without runs), so that a cell of some 64 stages costs the same.
+constexpr uint32_t kMaxCell = 32;
 
 struct CriticalParams {
   const u32x4* table;          // [n_wg][R * I] of {max_dur, min_start, max_end, n_waves}
   unsigned long long* hdr;     // 8 words
   unsigned long long* region;  // [R][2]
   u32x4* rows;                 // [n_wg][2]
-  uint32_t n_wg, R, I, N, P, log2P;
+  uint32_t n_wg, R, I, N, P;
 };
 
 __global__ void kp_critical_init(unsigned long long* out, uint32_t n_wg, uint32_t R, uint32_t I) {
@@ -55,110 +63,202 @@ __device__ inline uint32_t wave_min32(uint32_t v) {
   for (int d = 32; d >= 1; d >>= 1) { const uint32_t o = __shfl_xor(v, d, 64); v = o < v ? o : v; }
   return v;
 }
+__device__ inline uint32_t wave_scan32(uint32_t v, uint32_t lane) {  // inclusive
+#pragma unroll
+  for (int d = 1; d < 64; d <<= 1) { const uint32_t o = __shfl_up(v, d, 64); v += lane >= (uint32_t)d ? o : 0u; }
+  return v;
+}
 
-// LDS: key[P] u64 | start[N] | lat[N] | jump[2][P] | mark[P] bytes | totals
-__global__ __launch_bounds__(kBlock) void kp_critical_main(CriticalParams p) {
+// LDS: key[P] u64 | start[P] | lat[P] | jump[2][P] (the first one: cells, until the links are known) | mark[P]
+// bytes | totals.  PER entries per thread: P = 256 * PER, or P <= 256 and PER = 1.
+template <int PER>
+__global__ __launch_bounds__(kBlock, PER <= 4 ? 6 : 1) void kp_critical_main(CriticalParams p) {
   extern __shared__ __align__(16) unsigned char smem[];
   const uint32_t P = p.P, N = p.N, R = p.R, I = p.I;
   unsigned long long* key = reinterpret_cast<unsigned long long*>(smem);
   uint32_t* start = reinterpret_cast<uint32_t*>(smem + 8 * (size_t)P);
   uint32_t* lat = start + P;
-  uint32_t* jump0 = lat + P;
-  uint32_t* jump1 = jump0 + P;
+  uint32_t* cells = lat + P;
+  uint32_t* jump1 = cells + P;
   uint8_t* mark = reinterpret_cast<uint8_t*>(jump1 + P);
   unsigned long long* reg_tot = reinterpret_cast<unsigned long long*>(smem + 25 * (size_t)P);  // [R][2], 8-byte aligned: P >= 64
   unsigned long long* wg_tot = reg_tot + 2 * R;   // stages, latency, bubbles
-  uint32_t* wg_small = reinterpret_cast<uint32_t*>(wg_tot + 3);  // [0] valid stages, [1] min start on the path, [2] a region's keys are out of order
-  unsigned long long* all_tot = reinterpret_cast<unsigned long long*>(wg_small + 4);  // paths, stages, latency, bubbles
+  // [0] min start on the path, [1] first end, [2] last end, [3] a cell is too full, [4] a region's keys are
+  // out of order, [8..11] stages in the cells of each hardware wave
+  uint32_t* wg_small = reinterpret_cast<uint32_t*>(wg_tot + 3);
+  unsigned long long* all_tot = reinterpret_cast<unsigned long long*>(wg_small + 12);  // paths, stages, latency, bubbles
 
-  const uint32_t tid = threadIdx.x, lane = tid & 63u;
+  const uint32_t tid = threadIdx.x, lane = tid & 63u, hw = tid >> 6;
   for (uint32_t i = tid; i < 2 * R; i += kBlock) reg_tot[i] = 0ull;
   if (tid < 4) all_tot[tid] = 0ull;
-  __syncthreads();
+
+  u32x4 entry[PER];
+  auto fetch = [&](uint32_t wg) {
+    const u32x4* tab = p.table + (size_t)wg * N;
+#pragma unroll
+    for (int u = 0; u < PER; ++u) {
+      const uint32_t i = tid + kBlock * u;
+      entry[u] = i < N ? tab[i] : u32x4{0u, 0u, 0u, 0u};
+    }
+  };
+  fetch(blockIdx.x);
 
   for (uint32_t wg = blockIdx.x; wg < p.n_wg; wg += gridDim.x) {
-    const u32x4* tab = p.table + (size_t)wg * N;
     if (tid < 3) wg_tot[tid] = 0ull;
-    if (tid == 0) { wg_small[0] = 0u; wg_small[1] = 0xFFFFFFFFu; wg_small[2] = 0u; }
-    __syncthreads();
-    // ---- 1: keys ----------------------------------------------------------------------------------
-    // The iterations of a region usually end one after the other, so that the keys of a region (a run of I
-    // consecutive entries) are in order as they come; that is checked while the keys are made (an entry that
-    // is no stage has the largest key: it must be behind the stages of its run).
-    uint32_t n_mine = 0;
-    const bool runs = I >= 2u && (I & (I - 1u)) == 0u;  // runs that the merge steps below can start from
-    bool disorder = false;
-    for (uint32_t i = tid; i < P; i += kBlock) {
-      unsigned long long k = ~0ull;
-      if (i < N) {
-        const u32x4 e = tab[i];
-        start[i] = e.y; lat[i] = e.x;
-        if (e.w != 0u) { k = ((unsigned long long)e.z << 32) | i; ++n_mine; }
-        if (runs && (i & (I - 1u)) != 0u) {
-          const u32x4 before = tab[i - 1u];
-          const unsigned long long kb = before.w != 0u ? ((unsigned long long)before.z << 32) | (i - 1u) : ~0ull;
-          disorder = disorder || kb > k;
-        }
+    if (tid < 8) wg_small[tid] = tid < 2u ? 0xFFFFFFFFu : 0u;
+    uint32_t end[PER];
+    uint32_t live = 0;  // bit u: entry u is a stage
+    uint32_t first_end = 0xFFFFFFFFu, last_end = 0;
+#pragma unroll
+    for (int u = 0; u < PER; ++u) {
+      const uint32_t i = tid + kBlock * u;
+      end[u] = entry[u].z;
+      if (entry[u].w != 0u) {
+        live |= 1u << u;
+        first_end = end[u] < first_end ? end[u] : first_end;
+        last_end = end[u] > last_end ? end[u] : last_end;
       }
-      key[i] = k;
-      mark[i] = 0;
+      if (i < P) { start[i] = entry[u].y; lat[i] = entry[u].x; cells[i] = 0u; mark[i] = 0; }
     }
-    n_mine = wave_sum32(n_mine);
-    if (lane == 0 && n_mine) atomicAdd(&wg_small[0], n_mine);
-    if (__builtin_amdgcn_ballot_w64(disorder) != 0ull && lane == 0) wg_small[2] = 1u;
+    if (wg + gridDim.x < p.n_wg) fetch(wg + gridDim.x);
+    first_end = wave_min32(first_end);
+    last_end = ~wave_min32(~last_end);
     __syncthreads();
-    // Ascending sort by merging: blocks of k/2 keys in order become blocks of k.  The first step of a merge
-    // compares key i of the lower block with key k/2 - 1 - i of the upper one (the smaller k/2 keys of the
-    // two end up below, the larger above, each a rising-then-falling sequence), the steps after it are the
-    // half-cleaners of a bitonic merge.  With every region's run in order the merging starts at blocks of I.
-    // A thread takes the pairs t = tid, tid + 256, ..., so the 64 pairs of a hardware wave lie in one block of
-    // 128 consecutive keys whenever the two keys of a pair are at most 64 apart (and, in a first step, the
-    // blocks hold at most 128 keys): such steps touch no key of another wave, and since the LDS operations
-    // of one wave take effect in order, two of them in a row need no workgroup barrier between them.
-    auto between = [&](bool local_before, bool local_after) {
-      if (local_before && local_after) { __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront"); __builtin_amdgcn_wave_barrier(); }
-      else __syncthreads();
+    if (lane == 0 && first_end <= last_end) {  // the wave has a stage
+      atomicMin(&wg_small[1], first_end);
+      atomicMax(&wg_small[2], last_end);
+    }
+    __syncthreads();
+    // ---- 1: order ---------------------------------------------------------------------------------
+    // (a clock's cell never falls as the clock rises: rounding, product and conversion are monotonic)
+    first_end = wg_small[1];
+    last_end = wg_small[2];
+    const float per_tick = (float)P / ((float)(last_end - first_end) + 1.0f);
+    auto cell_of = [&](uint32_t t) {
+      const uint32_t c = (uint32_t)((float)(t - first_end) * per_tick);
+      return c < P ? c : P - 1u;
     };
-    for (uint32_t k = (runs && wg_small[2] == 0u) ? 2u * I : 2u; k <= P; k <<= 1) {
-      const uint32_t half = k >> 1;
-      for (uint32_t t = tid; t < P / 2; t += kBlock) {
-        const uint32_t blk = (t / half) * k, i = t & (half - 1u), lo = blk + i, hi = blk + k - 1u - i;
-        const unsigned long long a = key[lo], b = key[hi];
-        if (a > b) { key[lo] = b; key[hi] = a; }
+    auto key_of = [&](int u) { return ((unsigned long long)end[u] << 32) | (tid + kBlock * u); };
+    uint32_t at[PER];  // arrival number in the cell, then the place in the order
+    bool full = false;
+#pragma unroll
+    for (int u = 0; u < PER; ++u) {
+      at[u] = 0;
+      if (live >> u & 1u) { at[u] = atomicAdd(&cells[cell_of(end[u])], 1u); full = full || at[u] >= kMaxCell; }
+    }
+    if (__builtin_amdgcn_ballot_w64(full) != 0ull && lane == 0) wg_small[3] = 1u;
+    __syncthreads();
+    uint32_t mine[PER], sum = 0;
+#pragma unroll
+    for (int j = 0; j < PER; ++j) { mine[j] = tid * PER < P ? cells[tid * PER + j] : 0u; sum += mine[j]; }
+    const uint32_t upto = wave_scan32(sum, lane);
+    if (lane == 63u) wg_small[8 + hw] = upto;
+    __syncthreads();
+    uint32_t at_cell = upto - sum, n = 0;
+#pragma unroll
+    for (uint32_t h = 0; h < kBlock / 64; ++h) { const uint32_t c = wg_small[8 + h]; at_cell += h < hw ? c : 0u; n += c; }
+    const bool by_cell = wg_small[3] == 0u;
+    if (by_cell) {
+      if (tid * PER < P) {
+#pragma unroll
+        for (int j = 0; j < PER; ++j) { cells[tid * PER + j] = at_cell; at_cell += mine[j]; }
       }
-      // (the step after this one: the half-cleaner at distance half / 2, or the first step of the next size)
-      between(k <= 128u, half >= 2u ? (half >> 1) <= 64u : 2u * k <= 128u);
-      for (uint32_t j = half >> 1; j > 0; j >>= 1) {
+      __syncthreads();
+#pragma unroll
+      for (int u = 0; u < PER; ++u)
+        if (live >> u & 1u) { at[u] += cells[cell_of(end[u])]; key[at[u]] = key_of(u); }
+      __syncthreads();
+#pragma unroll
+      for (int u = 0; u < PER; ++u) {
+        if (!(live >> u & 1u)) continue;
+        const uint32_t c = cell_of(end[u]), lo = cells[c], hi = c + 1u < P ? cells[c + 1u] : n;
+        const unsigned long long k = key_of(u);
+        at[u] = lo;
+        if (hi - lo > 1u)
+          for (uint32_t m = lo; m < hi; ++m) at[u] += key[m] < k ? 1u : 0u;
+      }
+      __syncthreads();
+#pragma unroll
+      for (int u = 0; u < PER; ++u)
+        if (live >> u & 1u) key[at[u]] = key_of(u);
+      __syncthreads();
+    } else {
+      // The iterations of a region usually end one after the other, so that the keys of a region (a run of I
+      // consecutive entries) are in order as they come; that is checked (an entry that is no stage has the
+      // largest key: it must be behind the stages of its run).
+      const bool runs = I >= 2u && (I & (I - 1u)) == 0u;  // runs that the merge steps below can start from
+#pragma unroll
+      for (int u = 0; u < PER; ++u)
+        if (tid + kBlock * u < P) key[tid + kBlock * u] = live >> u & 1u ? key_of(u) : ~0ull;
+      __syncthreads();
+      bool disorder = false;
+      if (runs)
+        for (uint32_t i = tid; i < N; i += kBlock)
+          if ((i & (I - 1u)) != 0u) disorder = disorder || key[i - 1u] > key[i];
+      if (__builtin_amdgcn_ballot_w64(disorder) != 0ull && lane == 0) wg_small[4] = 1u;
+      __syncthreads();
+      // Ascending sort by merging: blocks of k/2 keys in order become blocks of k.  The first step of a merge
+      // compares key i of the lower block with key k/2 - 1 - i of the upper one (the smaller k/2 keys of the
+      // two end up below, the larger above, each a rising-then-falling sequence), the steps after it are the
+      // half-cleaners of a bitonic merge.  With every region's run in order the merging starts at blocks of I.
+      // A thread takes the pairs t = tid, tid + 256, ..., so the 64 pairs of a hardware wave lie in one block of
+      // 128 consecutive keys whenever the two keys of a pair are at most 64 apart (and, in a first step, the
+      // blocks hold at most 128 keys): such steps touch no key of another wave, and since the LDS operations
+      // of one wave take effect in order, two of them in a row need no workgroup barrier between them.
+      auto between = [&](bool local_before, bool local_after) {
+        if (local_before && local_after) { __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront"); __builtin_amdgcn_wave_barrier(); }
+        else __syncthreads();
+      };
+      for (uint32_t k = (runs && wg_small[4] == 0u) ? 2u * I : 2u; k <= P; k <<= 1) {
+        const uint32_t half = k >> 1;
         for (uint32_t t = tid; t < P / 2; t += kBlock) {
-          const uint32_t lo = ((t & ~(j - 1u)) << 1) | (t & (j - 1u));  // the element of the pair with bit j clear
-          const uint32_t hi = lo | j;
+          const uint32_t blk = (t / half) * k, i = t & (half - 1u), lo = blk + i, hi = blk + k - 1u - i;
           const unsigned long long a = key[lo], b = key[hi];
           if (a > b) { key[lo] = b; key[hi] = a; }
         }
-        between(j <= 64u, j >= 2u ? true : 2u * k <= 128u);
+        // (the step after this one: the half-cleaner at distance half / 2, or the first step of the next size)
+        between(k <= 128u, half >= 2u ? (half >> 1) <= 64u : 2u * k <= 128u);
+        for (uint32_t j = half >> 1; j > 0; j >>= 1) {
+          for (uint32_t t = tid; t < P / 2; t += kBlock) {
+            const uint32_t lo = ((t & ~(j - 1u)) << 1) | (t & (j - 1u));  // the element of the pair with bit j clear
+            const uint32_t hi = lo | j;
+            const unsigned long long a = key[lo], b = key[hi];
+            if (a > b) { key[lo] = b; key[hi] = a; }
+          }
+          between(j <= 64u, j >= 2u ? true : 2u * k <= 128u);
+        }
       }
+      __syncthreads();
     }
-    __syncthreads();
-    const uint32_t n = wg_small[0];  // the stages are the first n keys
-    // ---- 2: the stage each stage waited for -------------------------------------------------------
-    for (uint32_t r = tid; r < P; r += kBlock) {
-      uint32_t pred = kNone;
+    // ---- 2: the stage each stage waited for (the stages are the first n keys) -----------------------
+    uint32_t pred[PER];
+#pragma unroll
+    for (int u = 0; u < PER; ++u) {
+      const uint32_t r = tid + kBlock * u;
+      pred[u] = kNone;
       if (r < n) {
         const uint32_t s = start[(uint32_t)key[r]];
         uint32_t lo = 0, hi = n;  // first rank whose end exceeds s
+        if (s < first_end) hi = 0;
+        else if (s >= last_end) lo = n;
+        else if (by_cell) {
+          const uint32_t c = cell_of(s);
+          lo = cells[c];
+          hi = c + 1u < P ? cells[c + 1u] : n;
+        }
         while (lo < hi) {
           const uint32_t mid = (lo + hi) >> 1;
           if ((uint32_t)(key[mid] >> 32) <= s) lo = mid + 1; else hi = mid;
         }
         const uint32_t c = lo < r ? lo : r;
-        pred = c ? c - 1u : kNone;
+        pred[u] = c ? c - 1u : kNone;
+        jump1[r] = pred[u];
+        if (r + 1u == n) mark[r] = 1;
       }
-      jump0[r] = pred;
-      if (r + 1u == n) mark[r] = 1;
     }
     // ---- 3: mark the list that starts at the last stage --------------------------------------------
-    uint32_t* cur = jump0;
-    uint32_t* nxt = jump1;
+    uint32_t* cur = jump1;
+    uint32_t* nxt = cells;
     for (uint32_t round = 0; (1u << round) < n; ++round) {
       __syncthreads();
       for (uint32_t r = tid; r < n; r += kBlock) {
@@ -171,20 +271,15 @@ __global__ __launch_bounds__(kBlock) void kp_critical_main(CriticalParams p) {
     }
     __syncthreads();
     // ---- 4: totals ---------------------------------------------------------------------------------
-    // (the links of one step were overwritten by the doubling: they are found again, one search each)
     uint32_t my_n = 0, my_first = 0xFFFFFFFFu;
     unsigned long long my_lat = 0, my_bub = 0;
-    for (uint32_t r = tid; r < n; r += kBlock) {
-      if (!mark[r]) continue;
+#pragma unroll
+    for (int u = 0; u < PER; ++u) {
+      const uint32_t r = tid + kBlock * u;
+      if (r >= n || !mark[r]) continue;
       const uint32_t idx = (uint32_t)key[r];
       const uint32_t s = start[idx], l = lat[idx];
-      uint32_t lo = 0, hi = n;
-      while (lo < hi) {
-        const uint32_t mid = (lo + hi) >> 1;
-        if ((uint32_t)(key[mid] >> 32) <= s) lo = mid + 1; else hi = mid;
-      }
-      const uint32_t c = lo < r ? lo : r;
-      if (c) my_bub += s - (uint32_t)(key[c - 1u] >> 32);
+      if (pred[u] != kNone) my_bub += s - (uint32_t)(key[pred[u]] >> 32);
       ++my_n; my_lat += l;
       my_first = s < my_first ? s : my_first;
       const uint32_t region = idx / I;
@@ -196,7 +291,7 @@ __global__ __launch_bounds__(kBlock) void kp_critical_main(CriticalParams p) {
       atomicAdd(&wg_tot[0], (unsigned long long)my_n);
       atomicAdd(&wg_tot[1], my_lat);
       atomicAdd(&wg_tot[2], my_bub);
-      atomicMin(&wg_small[1], my_first);
+      atomicMin(&wg_small[0], my_first);
     }
     __syncthreads();
     if (tid == 0) {
@@ -204,7 +299,7 @@ __global__ __launch_bounds__(kBlock) void kp_critical_main(CriticalParams p) {
       if (n) {
         const unsigned long long last = key[n - 1u];
         const uint32_t idx = (uint32_t)last;
-        a = u32x4{(uint32_t)wg_tot[0], ((idx / I) << 16) | (idx % I), wg_small[1], (uint32_t)(last >> 32)};
+        a = u32x4{(uint32_t)wg_tot[0], ((idx / I) << 16) | (idx % I), wg_small[0], (uint32_t)(last >> 32)};
         all_tot[0] += 1ull;
       } else {
         a = u32x4{0u, 0xFFFFFFFFu, 0u, 0u};
@@ -222,6 +317,27 @@ __global__ __launch_bounds__(kBlock) void kp_critical_main(CriticalParams p) {
 }
 
 struct LaunchCache { int dev = -1; uint32_t lds = 0; uint32_t max_grid = 0; };
+
+template <int PER>
+kp_status launch(const CriticalParams& p, hipStream_t s) {
+  const uint32_t lds = 25u * p.P + 16u * p.R + 24u + 48u + 32u;
+  static thread_local LaunchCache cache;
+  int dev = 0;
+  KP_HIP_TRY(hipGetDevice(&dev));
+  if (cache.dev != dev || cache.lds != lds) {
+    KP_HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void*>(kp_critical_main<PER>),
+                                   hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
+    int per_cu = 0, cus = 0;
+    KP_HIP_TRY(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kp_critical_main<PER>, kBlock, lds));
+    if (per_cu < 1) return kp::fail(KP_ERR_UNSUPPORTED_SHAPE, "critical-path kernel does not fit one CU (LDS %u B)", lds);
+    KP_HIP_TRY(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev));
+    cache.dev = dev; cache.lds = lds; cache.max_grid = (uint32_t)per_cu * (uint32_t)cus;
+  }
+  const uint32_t grid = cache.max_grid < p.n_wg ? cache.max_grid : p.n_wg;
+  hipLaunchKernelGGL(kp_critical_main<PER>, dim3(grid), dim3(kBlock), lds, s, p);
+  KP_HIP_TRY(hipGetLastError());
+  return KP_OK;
+}
 
 }  // namespace
 
@@ -250,26 +366,14 @@ extern "C" kp_status kp_stages_critical(const void* stages, int n_wg, int n_regi
   p.region = p.hdr + 8;
   p.rows = reinterpret_cast<u32x4*>(out + 64 + 16 * (size_t)n_regions);
   p.n_wg = (uint32_t)n_wg; p.R = (uint32_t)n_regions; p.I = (uint32_t)max_iter; p.N = (uint32_t)n_ent;
-  p.P = 64; p.log2P = 6;
-  while (p.P < p.N) { p.P <<= 1; ++p.log2P; }
+  p.P = 64;
+  while (p.P < p.N) p.P <<= 1;
   hipLaunchKernelGGL(kp_critical_init, dim3(1), dim3(256), 0, s, p.hdr, p.n_wg, p.R, p.I);
   KP_HIP_TRY(hipGetLastError());
   if (n_wg == 0) return KP_OK;
-  const uint32_t lds = 25u * p.P + 16u * p.R + 24u + 16u + 32u;
-  static thread_local LaunchCache cache;
-  int dev = 0;
-  KP_HIP_TRY(hipGetDevice(&dev));
-  if (cache.dev != dev || cache.lds != lds) {
-    KP_HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void*>(kp_critical_main),
-                                   hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
-    int per_cu = 0, cus = 0;
-    KP_HIP_TRY(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kp_critical_main, kBlock, lds));
-    if (per_cu < 1) return kp::fail(KP_ERR_UNSUPPORTED_SHAPE, "critical-path kernel does not fit one CU (LDS %u B)", lds);
-    KP_HIP_TRY(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev));
-    cache.dev = dev; cache.lds = lds; cache.max_grid = (uint32_t)per_cu * (uint32_t)cus;
-  }
-  const uint32_t grid = cache.max_grid < (uint32_t)n_wg ? cache.max_grid : (uint32_t)n_wg;
-  hipLaunchKernelGGL(kp_critical_main, dim3(grid), dim3(kBlock), lds, s, p);
-  KP_HIP_TRY(hipGetLastError());
-  return KP_OK;
+  if (p.P <= 256) return launch<1>(p, s);
+  if (p.P == 512) return launch<2>(p, s);
+  if (p.P == 1024) return launch<4>(p, s);
+  if (p.P == 2048) return launch<8>(p, s);
+  return launch<16>(p, s);
 }

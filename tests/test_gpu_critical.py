@@ -149,3 +149,27 @@ def test_argument_errors(kp):
     kp.kp_stages_critical(dev, 0, 3, 4, out)               # no workgroups: header only
     torch.cuda.synchronize()
     assert out.cpu().numpy()[:64].view("<u8").tolist() == [0, 3, 4, 0, 0, 0, 0, 0]
+
+
+@pytest.mark.parametrize("R,I", [(1, 64), (5, 13), (3, 85), (1, 257), (8, 64), (19, 27), (16, 64), (41, 25), (16, 128), (11, 187), (128, 32)])
+@pytest.mark.parametrize("crowd", ["one cell", "cell limit", "past limit"])
+def test_stages_that_end_close_together(kp, oracle_mod, R, I, crowd):
+    """The counting sort's cells: one stage far behind all others, which then share a cell; 32 stages in one
+    cell (the most it ranks) and 33 (sorted by the network), with the rest spread evenly.  Sizes at and beyond
+    the powers of two at which a thread takes more stages."""
+    n = R * I
+    tab = random_table(oracle_mod, 7 * n, 5, R, I, p_empty=0.1 if crowd == "one cell" else 0.0, t_max=3 * n, ext_max=40)
+    flat = tab.reshape(5, n)
+    if crowd == "one cell":
+        flat[:, n // 2] = (9, 1 << 30, (1 << 30) + 50, 1)
+    else:
+        k = 32 if crowd == "cell limit" else 33
+        rng = np.random.default_rng(n)
+        for row in flat:
+            end = np.arange(n, dtype=np.uint32) * 64 + 32
+            first = n // 3
+            take = slice(first, min(first + k, n))
+            end[take] = end[first] + rng.integers(0, 8, size=end[take].size, dtype=np.uint32)
+            row["max_end"] = rng.permutation(end)
+            row["min_start"] = row["max_end"] - np.minimum(row["max_end"], rng.integers(0, 300, size=n).astype(np.uint32))
+    check(kp, oracle_mod, oracle_mod.stage_block(tab), 5, R, I)
