@@ -287,6 +287,105 @@ __global__ __launch_bounds__(256) void kp_gemm_small(GemmArgs g) {
   }
 }
 
+// The same tile for a short K and many workgroups: one K step at a time, 8 KiB of LDS.  A workgroup is then over
+// before a pipeline has filled, its time is latency and the C tile, and what counts is how many of them share a
+// CU: eight or more here, five of the pipelined kernel's.  Measured on 4032 x 3968 x K (3906 workgroups), this
+// kernel against the pipelined one: K = 32 9.0 / 16.0 us, 96 13.2 / 16.4, 160 18.1 / 20.7, 192 20.4 / 22.3, 320 29.4 / 25.6,
+// 640 50.1 / 42.6; with all regions recorded K = 32 12.3 / 20.5, 160 23.7 / 27.3, 192 26.5 / 29.4, 320 38.6 / 34.0.  With fewer
+// workgroups the pipeline wins at every K (2112 x 1984, 1023 of them: K = 32 7.0 / 5.8, 192 8.3 / 7.4; 1984 x 960 x 160:
+// 6.9 / 4.8 us; 1624 of them, recorded, K = 160: 13.5 / 14.9), hence the two conditions of short_k().
+//
+// LDS rows of 32 bf16: chunk c of row r at position c ^ (r / 2) % 4.
+__device__ __forceinline__ uint32_t short_off(uint32_t row, uint32_t chunk) {
+  return row * 64u + ((chunk ^ ((row >> 1) & 3u)) << 4);
+}
+
+template <int INSTR>
+__global__ __launch_bounds__(256) void kp_gemm_short(GemmArgs g) {
+  constexpr int SITE = INSTR, kMayCross = 0;
+  static_assert(SITE <= 3, "no chained sites");
+  constexpr int BM = 64, BN = 64, BK = 32;
+  __shared__ __align__(16) unsigned char sA[BM * BK * 2];
+  __shared__ __align__(16) unsigned char sB[BN * BK * 2];
+  extern __shared__ __align__(16) uint32_t ring_lds[];
+  __shared__ uint64_t t_begin[2];
+
+  const uint32_t tid = threadIdx.x, lane = tid & 63u, wave = tid >> 6;
+  const uint32_t tiles_n = g.N / BN;
+  const uint32_t wg = blockIdx.x;
+  const uint32_t m0 = (wg / tiles_n) * BM, n0 = (wg % tiles_n) * BN;
+  kp::Ring ring{};
+  if constexpr (INSTR != 0)
+    ring = kp::ring_init<true>(ring_lds, t_begin, g.cap_lds, g.region_mask, g.flush, g.cap_hbm, g.trace, g.n_wg, 4u >> g.group_log2, wg,
+                         g.group_log2);
+  ring.collab = g.collab;
+  if constexpr (INSTR == 3) kp::ring_use_realtime(ring);
+  kp::sites_begin<SITE>(ring);
+
+  // global -> register mapping
+  // A: 64 rows x 4 chunks = 256 chunks, one per thread
+  const uint32_t a_row = tid >> 2, a_chunk = tid & 3u;
+  const uint16_t* a_src = g.A + (size_t)(m0 + a_row) * g.K + a_chunk * 8;
+  // B: 4 k-groups x 32 column pairs = 128 tasks; threads 128..255 idle for B
+  const uint32_t b_kg = (tid >> 5) & 3u, b_np = tid & 31u;
+  const bool b_on = tid < 128;
+  const uint16_t* b_src = g.B + (size_t)(b_kg * 8) * g.N + n0 + b_np * 2;
+
+  const uint32_t wr = wave >> 1, wc = wave & 1u;  // wave position in the 2x2 grid
+  f32x16 acc = {0};
+
+  for (uint32_t kt = 0; kt < g.K / BK; ++kt) {
+    // ---- region 0: global load ---------------------------------------------------------------
+    if (kt == 0) KP_SITE_K(ring, 0, kp::kNoRegion, 0); else KP_SITE_K(ring, 0, 2, 0);
+    const u32x4 av = *reinterpret_cast<const u32x4*>(a_src + (size_t)kt * BK);
+    uint32_t bv[8];
+#pragma unroll
+    for (int i = 0; i < 8; ++i)
+      bv[i] = b_on ? *reinterpret_cast<const uint32_t*>(b_src + ((size_t)kt * BK + i) * g.N) : 0u;
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    KP_SITE_K(ring, 0, 0, 1);
+    // ---- region 1: LDS store -----------------------------------------------------------------
+    __syncthreads();  // previous step's MFMA reads are done
+    *reinterpret_cast<u32x4*>(sA + short_off(a_row, a_chunk)) = av;
+    if (b_on) {
+      u32x4 lo, hi;  // column 2*b_np and 2*b_np+1, eight consecutive k each
+      lo.x = __builtin_amdgcn_perm(bv[1], bv[0], 0x05040100u); hi.x = __builtin_amdgcn_perm(bv[1], bv[0], 0x07060302u);
+      lo.y = __builtin_amdgcn_perm(bv[3], bv[2], 0x05040100u); hi.y = __builtin_amdgcn_perm(bv[3], bv[2], 0x07060302u);
+      lo.z = __builtin_amdgcn_perm(bv[5], bv[4], 0x05040100u); hi.z = __builtin_amdgcn_perm(bv[5], bv[4], 0x07060302u);
+      lo.w = __builtin_amdgcn_perm(bv[7], bv[6], 0x05040100u); hi.w = __builtin_amdgcn_perm(bv[7], bv[6], 0x07060302u);
+      *reinterpret_cast<u32x4*>(sB + short_off(b_np * 2, b_kg)) = lo;
+      *reinterpret_cast<u32x4*>(sB + short_off(b_np * 2 + 1, b_kg)) = hi;
+    }
+    __syncthreads();
+    KP_SITE_K(ring, 0, 1, 2);
+    // ---- region 2: MFMA ------------------------------------------------------------------------
+#pragma unroll
+    for (int ks = 0; ks < BK / 16; ++ks) {
+      // operand layout of v_mfma_f32_32x32x16_bf16: lane l supplies row/column l%32, k = 8*(l/32)..+7
+      const uint32_t chunk = ks * 2 + (lane >> 5);
+      const bf16x8 af = *reinterpret_cast<const bf16x8*>(sA + short_off(wr * 32 + (lane & 31u), chunk));
+      const bf16x8 bf = *reinterpret_cast<const bf16x8*>(sB + short_off(wc * 32 + (lane & 31u), chunk));
+      acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(af, bf, acc, 0, 0, 0);
+    }
+    asm volatile("s_nop 0" ::: "memory");
+  }
+  KP_SITE_K(ring, 0, 2, kp::kNoRegion);
+
+  // epilogue: accumulator register v of lane l is C[row, col] with col = l%32,
+  // row = 8*(v/4) + 4*(l/32) + v%4 inside the wave's 32x32 tile
+  const uint32_t col = n0 + wc * 32 + (lane & 31u);
+#pragma unroll
+  for (int v = 0; v < 16; ++v) {
+    const uint32_t row = m0 + wr * 32 + 8 * (v / 4) + 4 * (lane >> 5) + (v % 4);
+    g.C[(size_t)row * g.N + col] = (uint16_t)bf16_pack_rne(acc[v], 0.f);
+  }
+  if constexpr (INSTR != 0) {
+    kp::TraceGeom tg{g.n_wg, 4u >> g.group_log2, 3, g.cap_hbm, g.flags};
+    kp::sites_end<SITE>(ring);
+    kp::ring_finish<INSTR == 3>(ring, g.cap_lds, g.trace, tg, wg, g.rec_cost);
+  }
+}
+
 
 // ------------------------------------------------------------------------------------------
 // 256x256x64 tile, 8 waves as 2 (M) x 4 (N); each wave owns 128x64 of C as 4x2 MFMA tiles.
@@ -716,6 +815,9 @@ bool pick_shape(int M, int N, int K, GemmShape* s) {
   return false;
 }
 
+// see kp_gemm_short
+bool short_k(int K, int n_wg) { return K <= 224 && n_wg >= 1024; }
+
 template <int INSTR, int WAVES, int SCHEDULE>
 kp_status launch_big(const GemmArgs& g, int n_wg, size_t ring_bytes, hipStream_t st) {
   static thread_local int attr_dev = -1;  // the attribute is kept per device
@@ -785,7 +887,8 @@ extern "C" kp_status kp_gemm_instrumented(const void* A, const void* B, void* C,
   if (regions == 0) {  // uninstrumented baseline: no ring, no record sites
     if (big && unfenced) return launch_big<0, kBigWaves, 2>(g, n_wg, 0, st);
     if (big) return launch_big_w<0>(phased, g, n_wg, 0, st);
-    hipLaunchKernelGGL(kp_gemm_small<0>, dim3(n_wg), dim3(256), 0, st, g);
+    if (short_k(K, n_wg)) hipLaunchKernelGGL(kp_gemm_short<0>, dim3(n_wg), dim3(256), 0, st, g);
+    else hipLaunchKernelGGL(kp_gemm_small<0>, dim3(n_wg), dim3(256), 0, st, g);
     KP_HIP_TRY(hipGetLastError());
     return KP_OK;
   }
@@ -801,7 +904,15 @@ extern "C" kp_status kp_gemm_instrumented(const void* A, const void* B, void* C,
   const size_t ring_bytes = (size_t)cap_lds * 8 * streams + (group_log2 ? 16 : 0);  // (16: see chain_begin)
   if (ring_bytes > 32 * 1024) return kp::fail(KP_ERR_UNSUPPORTED_SHAPE, "LDS ring of %zu bytes exceeds the 32 KiB budget", ring_bytes);
   g.cap_lds = cap_lds; g.cap_hbm = (uint32_t)cap_wave; g.rec_cost = kp::rec_cost();
-  // Both kernels chain their sites whenever the strategy is circular and one lane stores: the region mask,
+  if (!big && short_k(K, n_wg)) {  // every region, circular, a stream per wave: the lean sites
+    const bool lean = !flush && !group_log2 && !realtime && !collab && regions == 7u;
+    if (lean) hipLaunchKernelGGL(kp_gemm_short<2>, dim3(n_wg), dim3(256), ring_bytes, st, g);
+    else if (realtime) hipLaunchKernelGGL(kp_gemm_short<3>, dim3(n_wg), dim3(256), ring_bytes, st, g);
+    else hipLaunchKernelGGL(kp_gemm_short<1>, dim3(n_wg), dim3(256), ring_bytes, st, g);
+    KP_HIP_TRY(hipGetLastError());
+    return KP_OK;
+  }
+  // The other kernels chain their sites whenever the strategy is circular and one lane stores: the region mask,
   // wave-group records and the constant-rate clock all keep that form.
   const bool chained = !flush && !collab;
   if (big) return chained ? (realtime ? launch_big_w<5>(phased, g, n_wg, ring_bytes, st) : launch_big_w<2>(phased, g, n_wg, ring_bytes, st))

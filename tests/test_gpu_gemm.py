@@ -312,6 +312,35 @@ def test_small_tile_k_pairs_and_chained_sites(kp, K, regions, opts):
     assert (np.diff(ts, axis=2) >= 0).all() and (ts > 0).all()
 
 
+@pytest.mark.parametrize("M,N", [(64 * 32, 64 * 33), (64 * 31, 64 * 33), (64 * 41, 64 * 25)])
+@pytest.mark.parametrize("K,opts", [(32, "0"), (96, "realtime"), (160, "group"), (224, "0"), (288, "0")])
+def test_small_tile_many_workgroups_short_k(kp, M, N, K, opts):
+    """The dispatch line at K = 224 and 1024 workgroups, on either side: C against the fp64 oracle and bit-identical
+    with and without sites, record tags and counts of the circular forms against those of KP_MASK_COLLAB."""
+    cap_stream = 64
+    a, b = inputs.gemm_inputs(M, N, K, seed=M + K)
+    c0, _, (n_wg, waves, _) = run_gemm(kp, a, b, 0)
+    assert (n_wg, waves) == (M // 64 * (N // 64), 4)
+    assert_close_to_oracle(c0, a, b)
+    A, B = a.cuda(), b.cuda()
+    streams = 1 if opts == "group" else 4
+    mask = 0b111 | {"0": 0, "group": kp.KP_MASK_WAVE_GROUP, "realtime": kp.KP_MASK_REALTIME}[opts]
+    raws = []
+    for extra in (0, kp.KP_MASK_COLLAB):
+        C = torch.empty(M, N, dtype=torch.bfloat16, device="cuda")
+        trace = torch.full((kp.kp_trace_bytes(n_wg, streams, cap_stream * streams),), 0x77, dtype=torch.uint8, device="cuda")
+        kp.kp_gemm_instrumented(A, B, C, M, N, K, mask | extra, trace, cap_stream * streams)
+        torch.cuda.synchronize()
+        assert torch.equal(C.view(torch.int16), c0.view(torch.int16))
+        raws.append(trace.cpu().numpy().view(np.uint32).copy())
+    (hx, rx), (hy, ry) = (_streams_of(r, n_wg, streams, cap_stream) for r in raws)
+    total = 6 * (K // 32)
+    n = min(total, cap_stream)
+    assert (hx[:, 0] == np.arange(n_wg)).all()
+    assert (hx[:, 8:8 + streams] == total).all() and (hx[:, 8:24] == hy[:, 8:24]).all()
+    assert (rx[:, :, :n, 0] == ry[:, :, :n, 0]).all()
+
+
 def _streams_of(raw, n_wg, streams, cap):
     hdr = raw[16:16 + 32 * n_wg].reshape(n_wg, 32)
     return hdr, raw[16 + 32 * n_wg:].reshape(n_wg, streams, cap, 2)
