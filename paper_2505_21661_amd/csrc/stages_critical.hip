@@ -21,8 +21,8 @@
 //      rounds instead of a walk of up to n steps;
 //   4  marked stages add their latency to their region's totals, and the gaps to the stage before them
 //      to the workgroup's bubbles.
-// Bound by LDS round trips between barriers.  4096 workgroups of
-// 16 regions x 64 iterations, rows and stage table included: 596 us with the network, 545 us with the cells.
+// Bound by LDS round trips between barriers.  16384 workgroups of 16 regions x 64 iterations: 0.49 ms with the
+// network alone, every stage searching all ends twice, 0.20 ms with the cells.
 #include "kp_common.h"
 
 namespace {
