@@ -123,6 +123,9 @@ constexpr uint32_t kMaxCounted = 128;
 // Every thread of a counted block calls this after its last atomic on the statistics block.
 template <int BLOCK>
 __device__ __forceinline__ void finish_counted(uint64_t* out, const StatsLayout& l, uint32_t R, uint32_t* flag_lds) {
+  // Each wave waits for its own atomics: the barrier does not wait for global memory, and the count's release only
+  // for the wave that counts.
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
   __syncthreads();
   if (threadIdx.x == 0)
     *flag_lds = __hip_atomic_fetch_add(&out[H_RSVD], 1ull, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT) + 1u == gridDim.x ? 1u : 0u;
