@@ -86,55 +86,6 @@ __device__ __forceinline__ void bitonic_merge(T (&v)[N]) {
   }
 }
 
-// The derived figures from the totals: the pairs of a region are the sum of its histogram, the region-pair sums
-// stand in the upper triangle of the F area (away from the sums and extrema: atomics of many workgroups on one
-// line wait for one another) and are mirrored into O, U is the diagonal, F = O / U.
-template <int BLOCK>
-__device__ __forceinline__ void derive_figures(uint64_t* out, const StatsLayout& l, uint32_t R) {
-  for (uint32_t i = threadIdx.x; i < ((R * 16u + 63u) & ~63u); i += BLOCK) {  // 16 lanes per region
-    const uint32_t r = i >> 4, part = i & 15u;
-    uint64_t n = 0;
-    if (r < R) {
-      const uint64_t* bins = out + l.hist + (size_t)r * 64 + part;
-      n = bins[0] + bins[16] + bins[32] + bins[48];
-    }
-#pragma unroll
-    for (int d = 8; d >= 1; d >>= 1) n += __shfl_xor((unsigned long long)n, d, 64);
-    if (r < R && part == 0u) out[l.cnt + r] = n;
-  }
-  for (uint32_t i = threadIdx.x; i < R * R; i += BLOCK) {
-    const uint32_t a = i / R, b = i - a * R;
-    const uint64_t o = out[l.F + (a <= b ? i : b * R + a)];
-    out[l.O + i] = o;
-    if (a == b) out[l.U + a] = o;
-  }
-  __syncthreads();  // (a workgroup's own global stores are visible to it after the barrier)
-  for (uint32_t i = threadIdx.x; i < R * R; i += BLOCK) {
-    const uint64_t u = out[l.U + i / R], o = out[l.O + i];
-    reinterpret_cast<double*>(out)[l.F + i] = u ? (double)o / (double)u : 0.0;
-  }
-}
-
-// With few decoder workgroups the one that comes last (counted in a reserved header word, which is cleared again)
-// derives the figures; a kernel of its own for that costs 3 us of the 24 that the smallest traces take.  Counting
-// costs every workgroup a release of its L2 and an atomic that the others wait for: 64 decoder workgroups 24.4 us
-// with the kernel and 21.1 with the count, 256 of them 28.0 and 28.9, 1024 of them 44 and 52.
-constexpr uint32_t kMaxCounted = 128;
-// Every thread of a counted block calls this after its last atomic on the statistics block.
-template <int BLOCK>
-__device__ __forceinline__ void finish_counted(uint64_t* out, const StatsLayout& l, uint32_t R, uint32_t* flag_lds) {
-  // Each wave waits for its own atomics: the barrier does not wait for global memory, and the count's release only
-  // for the wave that counts.
-  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-  __syncthreads();
-  if (threadIdx.x == 0)
-    *flag_lds = __hip_atomic_fetch_add(&out[H_RSVD], 1ull, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT) + 1u == gridDim.x ? 1u : 0u;
-  __syncthreads();
-  if (*flag_lds == 0u) return;  // (uniform)
-  derive_figures<BLOCK>(out, l, R);
-  if (threadIdx.x == 0) out[H_RSVD] = 0ull;
-}
-
 // The main kernel of the decoder for geometries the LDS-resident one does not take (more than 32
 // regions, more than 16384 record slots per workgroup).  Between the init kernel and the one that derives the
 // figures, on the same stream; accumulates into the block exactly as the LDS-resident kernel does (histogram, sums,

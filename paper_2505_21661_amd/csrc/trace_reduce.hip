@@ -256,8 +256,37 @@ __global__ void kp_reduce_init(const uint32_t* trace_hdr, uint64_t* out, uint32_
   }
 }
 
+// derive (one workgroup, a kernel of its own behind the main one): the figures that follow from the totals.  The
+// pairs of a region are the sum of its histogram, the region-pair sums stand in the upper triangle of the F area (away
+// from the sums and extrema: atomics of many workgroups on one line wait for one another) and are mirrored into O,
+// U is the diagonal, F = O / U.
+// Having the last of few decoder workgroups do this instead gains nothing that would pay for the count: 64
+// workgroups of 4 x 128 records, 3 regions 20.9 us this way and 21.3 counted; 64 of 4 x 256, 16 regions 24.4 and
+// 27.2; 64 of 8 x 512, 5 regions 25.7 and 25.1; 256 of them 32.3 and 33.0.
 __global__ __launch_bounds__(1024) void kp_reduce_derive(uint64_t* out, uint32_t n_wg, uint32_t W, uint32_t R) {
-  derive_figures<1024>(out, stats_layout(n_wg, W, R), R);
+  const StatsLayout l = stats_layout(n_wg, W, R);
+  for (uint32_t i = threadIdx.x; i < ((R * 16u + 63u) & ~63u); i += blockDim.x) {  // 16 lanes per region
+    const uint32_t r = i >> 4, part = i & 15u;
+    uint64_t n = 0;
+    if (r < R) {
+      const uint64_t* bins = out + l.hist + (size_t)r * 64 + part;
+      n = bins[0] + bins[16] + bins[32] + bins[48];
+    }
+#pragma unroll
+    for (int d = 8; d >= 1; d >>= 1) n += __shfl_xor((unsigned long long)n, d, 64);
+    if (r < R && part == 0u) out[l.cnt + r] = n;
+  }
+  for (uint32_t i = threadIdx.x; i < R * R; i += blockDim.x) {
+    const uint32_t a = i / R, b = i - a * R;
+    const uint64_t o = out[l.F + (a <= b ? i : b * R + a)];
+    out[l.O + i] = o;
+    if (a == b) out[l.U + a] = o;
+  }
+  __syncthreads();  // (a workgroup's own global stores are visible to it after the barrier)
+  for (uint32_t i = threadIdx.x; i < R * R; i += blockDim.x) {
+    const uint64_t u = out[l.U + i / R], o = out[l.O + i];
+    reinterpret_cast<double*>(out)[l.F + i] = u ? (double)o / (double)u : 0.0;
+  }
 }
 
 // ------------------------------------------------------------------------------------------
@@ -1093,7 +1122,6 @@ __global__ __launch_bounds__(BLOCK) void kp_reduce_main(DecodeParams p) {
     }
   }
   if (tid_k < H_STATUS && ctr[tid_k]) atomicAdd(&out[tid_k], ctr[tid_k]);
-  if (BLOCK < 1024 && gridDim.x <= kMaxCounted) finish_counted<BLOCK>(p.out, SL, R, misc);
 }
 
 // Launch shape of one kernel instantiation for one LDS size, queried once per device.
@@ -1186,7 +1214,6 @@ kp_status reduce_impl(const void* raw, size_t n, const kp_trace_hdr& h, void* ou
     if (st != KP_OK) return st;
   }
   if (main_end) KP_HIP_TRY(hipEventRecord(main_end, s));
-  if (!wide && block < 1024 && h.n_wg <= kMaxCounted) return KP_OK;  // (at most one decoder workgroup each: derived by the last)
   hipLaunchKernelGGL(kp_reduce_derive, dim3(1), dim3(1024), 0, s, out, h.n_wg, W, R);
   KP_HIP_TRY(hipGetLastError());
   return KP_OK;

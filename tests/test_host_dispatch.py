@@ -1,0 +1,22 @@
+"""Which kernels a call launches, and which geometries it takes, on devices of several sizes (no GPU needed)."""
+from tests import fake_hip
+
+
+def kernels(launches, part):
+    return [x for x in launches if part in x[0]]
+
+
+def test_statistics_are_derived_exactly_once(tmp_path):
+    """The figures are derived behind the main kernel, once, also where a small device (a partition of the chip) holds
+    fewer decoder workgroups than the trace has."""
+    calls = []
+    for dev, (cus, per_cu) in enumerate([(256, 2), (64, 2), (32, 2), (32, 3), (20, 1), (32, 8)]):
+        for waves, regions, cap in ((4, 3, 128), (8, 5, 512), (8, 16, 2048), (8, 40, 64)):
+            for n_wg in (1, 127, 128, 129, 200, 1000):
+                calls.append({"fn": "kp_trace_reduce_hdr", "trace": (n_wg, waves, regions, cap), "device": (dev, cus, per_cu)})
+    for call, (status, launches) in zip(calls, fake_hip.run(calls, tmp_path)):
+        assert status == 0, call
+        n_wg, (_, cus, per_cu) = call["trace"][0], call["device"]
+        main, derive = launches[1:-1], launches[-1]
+        assert len(main) == 1 and main[0][1] == min(n_wg, cus * per_cu), (call, launches)
+        assert "kp_reduce_derive" in derive[0] and derive[1:3] == (1, 1024), (call, launches)
