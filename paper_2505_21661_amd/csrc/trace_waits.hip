@@ -41,14 +41,14 @@ __host__ __device__ inline WaitsLayout waits_layout(uint32_t n_wg, uint32_t W, u
 enum { H_WAITS = 0, H_UNCOVERED, H_ASYNC, H_NWG = 8, H_WAVES, H_NREG, H_CAP, H_COST };
 
 constexpr uint32_t kNoId = 0xFFFFu;     // END << 7 | region of no record
-constexpr uint32_t kHistStride = 65;  // regions that hit the same bin land in different LDS banks
+constexpr uint32_t kHistStride = 65;  // regions that hit the same bin land in different LDS banks; word 64: the region's waits, at the end
 
 // The per-(wave, region) sums exist in up to four copies, one per quarter of a hardware wave: lanes 16 apart tend
 // to hold the same region, and LDS atomics of one instruction that hit one address are done one after the other.
 constexpr uint32_t kMaxEntries = 1024;  // entries of those sums, copies included (one copy may exceed it)
 
 struct WaitsLds {
-  uint32_t hist, pw_pack, pw_max, pw_min, as_pack, unc, reg_sum, reg_cnt, reg_max, reg_min, acnt, asum, total;
+  uint32_t hist, pw_pack, pw_max, pw_min, as_pack, unc, reg_sum, reg_max, reg_min, acnt, asum, total;
   uint32_t copies;
 };
 __host__ __device__ inline WaitsLds waits_lds(uint32_t from, uint32_t W, uint32_t R, uint32_t copies) {
@@ -62,7 +62,6 @@ __host__ __device__ inline WaitsLds waits_lds(uint32_t from, uint32_t W, uint32_
   l.as_pack = o; o = align16(o + R * 8);
   l.unc = o; o = align16(o + R * 8);
   l.reg_sum = o; o = align16(o + R * 8);
-  l.reg_cnt = o; o = align16(o + R * 8);
   l.reg_max = o; o = align16(o + R * 4);
   l.reg_min = o; o = align16(o + R * 4);
   l.acnt = o; o = align16(o + R * 8);
@@ -99,11 +98,10 @@ __global__ __launch_bounds__(BLOCK, BLOCK == 1024 ? 4 : 6) void kp_waits_main(Tr
   uint32_t* pw_max = reinterpret_cast<uint32_t*>(smem + X.pw_max);
   uint32_t* pw_min = reinterpret_cast<uint32_t*>(smem + X.pw_min);
   unsigned long long* reg_sum = reinterpret_cast<unsigned long long*>(smem + X.reg_sum);
-  unsigned long long* reg_cnt = reinterpret_cast<unsigned long long*>(smem + X.reg_cnt);
   uint32_t* reg_max = reinterpret_cast<uint32_t*>(smem + X.reg_max);
   uint32_t* reg_min = reinterpret_cast<uint32_t*>(smem + X.reg_min);
   unsigned long long* as_pack = reinterpret_cast<unsigned long long*>(smem + X.as_pack);  // this workgroup's whole operations: count << 46 | sum
-  uint32_t* unc = reinterpret_cast<uint32_t*>(smem + X.unc);                              // (fewer than 2^32 per decoder workgroup)
+  uint32_t* unc = reinterpret_cast<uint32_t*>(smem + X.unc);  // two per region, one per half of a hardware wave (64-bit counts: 97 us where this takes 93)
   unsigned long long* acnt = reinterpret_cast<unsigned long long*>(smem + X.acnt);
   unsigned long long* asum = reinterpret_cast<unsigned long long*>(smem + X.asum);
 
@@ -114,8 +112,8 @@ __global__ __launch_bounds__(BLOCK, BLOCK == 1024 ? 4 : 6) void kp_waits_main(Tr
   for (uint32_t i = tid; i < R * kHistStride; i += BLOCK) hist[i] = 0;
   for (uint32_t i = tid; i < W * R * copies; i += BLOCK) { pw_pack[i] = 0; pw_max[i] = 0; pw_min[i] = 0xFFFFFFFFu; }
   for (uint32_t i = tid; i < R; i += BLOCK) {
-    reg_sum[i] = 0; reg_cnt[i] = 0; reg_max[i] = 0; reg_min[i] = 0xFFFFFFFFu;
-    unc[i] = 0; as_pack[i] = 0; acnt[i] = 0; asum[i] = 0;
+    reg_sum[i] = 0; reg_max[i] = 0; reg_min[i] = 0xFFFFFFFFu;
+    unc[2u * i] = 0; unc[2u * i + 1u] = 0; as_pack[i] = 0; acnt[i] = 0; asum[i] = 0;
   }
   // stage_workgroup's first barrier orders these stores before any use
 
@@ -165,7 +163,7 @@ __global__ __launch_bounds__(BLOCK, BLOCK == 1024 ? 4 : 6) void kp_waits_main(Tr
         atomicMax(&pw_max[e], gap);
         atomicMin(&pw_min[e], gap);
         atomicAdd(&hist[a * kHistStride + (gap ? 31 - __clz(gap) : 0)], 1u);
-        if (gap <= p.rec_cost) atomicAdd(&unc[a], 1u);
+        if (gap <= p.rec_cost) atomicAdd(&unc[2u * a + (lane >> 5)], 1u);
         if (paired) {
           const uint32_t whole = after - begin;
           atomicAdd(&as_pack[a], (1ull << 46) | (unsigned long long)(whole > p.rec_cost ? whole - p.rec_cost : 0u));
@@ -268,7 +266,6 @@ __global__ __launch_bounds__(BLOCK, BLOCK == 1024 ? 4 : 6) void kp_waits_main(Tr
       if (n) {
         const uint32_t r = e % R;
         atomicAdd(&reg_sum[r], s);
-        atomicAdd(&reg_cnt[r], (unsigned long long)n);
         atomicMax(&reg_max[r], mx);
         atomicMin(&reg_min[r], mn);
       }
@@ -284,18 +281,23 @@ __global__ __launch_bounds__(BLOCK, BLOCK == 1024 ? 4 : 6) void kp_waits_main(Tr
 
   // ---- flush this decoder workgroup's totals --------------------------------------------------------
   unsigned long long* out = reinterpret_cast<unsigned long long*>(out_words);
-  for (uint32_t i = tid; i < R * 64; i += BLOCK) {
+  for (uint32_t i = tid; i < R * 64; i += BLOCK) {  // one region per hardware wave; its waits are the sum of its bins
     const uint32_t v = hist[(i >> 6) * kHistStride + (i & 63u)];
     if (v) atomicAdd(&out[SL.hist + i], (unsigned long long)v);
+    const uint32_t n = wave_sum(v);
+    if (lane == 0) hist[(i >> 6) * kHistStride + 64u] = n;
   }
+  __syncthreads();
   for (uint32_t r = tid; r < R; r += BLOCK) {
-    if (reg_cnt[r]) {
-      atomicAdd(&out[SL.cnt + r], reg_cnt[r]);
-      atomicAdd(&out[H_WAITS], reg_cnt[r]);  // the three header counts are the sums of the regions'
+    const unsigned long long n = hist[r * kHistStride + 64u];
+    if (n) {
+      atomicAdd(&out[SL.cnt + r], n);
+      atomicAdd(&out[H_WAITS], n);  // the three header counts are the sums of the regions'
       atomicAdd(&out[SL.sum + r], reg_sum[r]);
       atomicMax(&out[SL.max + r], (unsigned long long)reg_max[r]);
       atomicMin(&out[SL.min + r], (unsigned long long)reg_min[r]);
-      if (unc[r]) { atomicAdd(&out[SL.unc + r], (unsigned long long)unc[r]); atomicAdd(&out[H_UNCOVERED], (unsigned long long)unc[r]); }
+      const unsigned long long u = (unsigned long long)unc[2u * r] + unc[2u * r + 1u];
+      if (u) { atomicAdd(&out[SL.unc + r], u); atomicAdd(&out[H_UNCOVERED], u); }
       if (acnt[r]) { atomicAdd(&out[SL.acnt + r], acnt[r]); atomicAdd(&out[H_ASYNC], acnt[r]); }
       if (asum[r]) atomicAdd(&out[SL.asum + r], asum[r]);
     }

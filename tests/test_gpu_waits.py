@@ -74,6 +74,16 @@ def test_mostly_sequential_traces(kp, oracle_mod, W, R, cap, holes):
     assert_waits_equal(oracle_mod, raw, run_waits(kp, raw, use_hdr=True))
 
 
+@pytest.mark.parametrize("W,R,cap", [(1, 100, 16384), (8, 74, 2048), (16, 57, 1024), (7, 116, 2048)])
+def test_largest_geometries(kp, oracle_mod, W, R, cap):
+    """One region more and the sums no longer fit beside the staged records."""
+    spec = inputs.TraceSpec(n_wg=5, waves=W, n_regions=R, cap_wave=cap, total_per_wave=cap + 50, total_var=cap // 2,
+                            seed=W + R, p_orphan=0.02, p_swap=1e-3)
+    raw, _ = inputs.gen_trace(spec)
+    raw[6] = 15
+    assert_waits_equal(oracle_mod, raw, run_waits(kp, raw, use_hdr=True))
+
+
 def test_many_workgroups_exercise_generation_reuse(kp, oracle_mod):
     # more recorded workgroups than resident decoder workgroups: staging area and totals are reused
     spec = inputs.TraceSpec(n_wg=3000, waves=4, n_regions=6, cap_wave=64, total_per_wave=64, total_var=40, seed=78,

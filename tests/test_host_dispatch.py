@@ -20,3 +20,17 @@ def test_statistics_are_derived_exactly_once(tmp_path):
         main, derive = launches[1:-1], launches[-1]
         assert len(main) == 1 and main[0][1] == min(n_wg, cus * per_cu), (call, launches)
         assert "kp_reduce_derive" in derive[0] and derive[1:3] == (1, 1024), (call, launches)
+
+
+# (waves, cap_wave, regions): the most regions whose sums fit the LDS beside the staged records, one copy of the sums
+WAITS_LIMITS = [(1, 16384, 100), (2, 8192, 95), (4, 4096, 87), (7, 2048, 116), (8, 2048, 74), (13, 1024, 110),
+                (14, 1024, 92), (15, 1024, 74), (16, 1024, 57)]
+
+
+def test_wait_replay_takes_every_geometry_up_to_its_limit(tmp_path):
+    shapes = [(w, r, cap) for w, cap, r0 in WAITS_LIMITS for r in (1, r0 - 1, r0, r0 + 1)]
+    calls = [{"fn": "kp_trace_waits_hdr", "trace": (3, *s)} for s in shapes]
+    limit = {(w, cap): r0 for w, cap, r0 in WAITS_LIMITS}
+    for (w, r, cap), (status, launches) in zip(shapes, fake_hip.run(calls, tmp_path)):
+        assert (status == 0) == (r <= limit[w, cap]), (w, r, cap, status)
+        assert all(lds <= 160 * 1024 for _, _, _, lds in launches), launches
