@@ -86,7 +86,7 @@ __global__ void kp_waits_init(uint64_t* out, uint32_t n_wg, uint32_t W, uint32_t
 
 // (6 hardware waves per SIMD, i.e. 80 vector registers: 97 us against 102 with 85 and 122 with 64)
 template <int BLOCK, int UNITS>
-__global__ __launch_bounds__(BLOCK, BLOCK == 1024 ? 4 : 6) void kp_waits_main(Trace p, uint64_t* out_words, uint32_t parts, uint32_t copies) {
+__global__ __launch_bounds__(BLOCK, BLOCK == 1024 ? 4 : 6) void kp_waits_main(Trace p, uint64_t* out_words, uint32_t parts, uint32_t copies, uint32_t add_head) {
   extern __shared__ __align__(16) unsigned char smem[];
   const Lds L = lds_layout(p.nrec);
   const WaitsLds X = waits_lds(L.end, p.W, p.R, copies);
@@ -292,16 +292,37 @@ __global__ __launch_bounds__(BLOCK, BLOCK == 1024 ? 4 : 6) void kp_waits_main(Tr
     const unsigned long long n = hist[r * kHistStride + 64u];
     if (n) {
       atomicAdd(&out[SL.cnt + r], n);
-      atomicAdd(&out[H_WAITS], n);  // the three header counts are the sums of the regions'
+      if (add_head) atomicAdd(&out[H_WAITS], n);
       atomicAdd(&out[SL.sum + r], reg_sum[r]);
       atomicMax(&out[SL.max + r], (unsigned long long)reg_max[r]);
       atomicMin(&out[SL.min + r], (unsigned long long)reg_min[r]);
       const unsigned long long u = (unsigned long long)unc[2u * r] + unc[2u * r + 1u];
-      if (u) { atomicAdd(&out[SL.unc + r], u); atomicAdd(&out[H_UNCOVERED], u); }
-      if (acnt[r]) { atomicAdd(&out[SL.acnt + r], acnt[r]); atomicAdd(&out[H_ASYNC], acnt[r]); }
+      if (u) { atomicAdd(&out[SL.unc + r], u); if (add_head) atomicAdd(&out[H_UNCOVERED], u); }
+      if (acnt[r]) { atomicAdd(&out[SL.acnt + r], acnt[r]); if (add_head) atomicAdd(&out[H_ASYNC], acnt[r]); }
       if (asum[r]) atomicAdd(&out[SL.asum + r], asum[r]);
     }
   }
+}
+
+// The three header counts are the sums of the regions'.  Either every decoder workgroup adds its own (add_head), or a
+// kernel behind them makes them (2 us).  The adds of all regions go to one line, which every workgroup visits, three
+// times per region: with many of either the workgroups queue up there, unless they queue up just as long at the
+// regions' own sums, which an odd number of regions, 2 and 6 leave across the lines.  Measured, added / kernel, us:
+// 64 workgroups x 16 regions 10.4 / 10.9, x 28 + 0.4 added, x 64 + 4.2; 128 x 8 11.8 / 11.6, x 12 12.3 / 13.1; 256 x 4 17.6 / 15.5,
+// x 6 17.5 / 19.0, x 7 18.4 / 19.5, x 8 17.4 / 14.4, x 16 17.8 / 15.1; 1024 x 3 45.1 / 46.9, x 4 38.6 / 29.8, x 6 38.6 / 38.8,
+// x 8 39.0 / 26.4, x 9 and 13 the same either way, x 10 + 4.4 added, x 16 39.8 / 27.8.
+inline bool add_head_counts(uint32_t grid, uint32_t R) {
+  return R <= 20u && (grid <= 128u || (R & 1u) != 0u || R == 2u || R == 6u);
+}
+__global__ void kp_waits_head(uint64_t* out, uint32_t n_wg, uint32_t W, uint32_t R) {
+  const WaitsLayout l = waits_layout(n_wg, W, R);
+  const uint32_t lane = threadIdx.x & 63u, which = threadIdx.x >> 6;  // one hardware wave per count
+  const size_t from = which == H_WAITS ? l.cnt : (which == H_UNCOVERED ? l.unc : l.acnt);
+  unsigned long long n = 0;
+  for (uint32_t r = lane; r < R; r += 64u) n += out[from + r];
+#pragma unroll
+  for (int d = 32; d >= 1; d >>= 1) n += __shfl_xor(n, d, 64);
+  if (lane == 0) out[which] = n;
 }
 
 template <int BLOCK, int UNITS>
@@ -315,8 +336,13 @@ kp_status launch_waits_units(const Trace& p, uint64_t* out, const WaitsLds& X, h
   const kp_status st = resident_grid(kern, BLOCK, X.total, &cache, &grid);
   if (st != KP_OK) return st;
   if (grid > p.n_wg) grid = p.n_wg;
-  hipLaunchKernelGGL(kern, dim3(grid), dim3(BLOCK), X.total, s, p, out, parts, X.copies);
+  const bool add_head = add_head_counts(grid, p.R);
+  hipLaunchKernelGGL(kern, dim3(grid), dim3(BLOCK), X.total, s, p, out, parts, X.copies, add_head ? 1u : 0u);
   KP_HIP_TRY(hipGetLastError());
+  if (!add_head) {
+    hipLaunchKernelGGL(kp_waits_head, dim3(1), dim3(192), 0, s, out, p.n_wg, p.W, p.R);
+    KP_HIP_TRY(hipGetLastError());
+  }
   return KP_OK;
 }
 

@@ -84,6 +84,16 @@ def test_largest_geometries(kp, oracle_mod, W, R, cap):
     assert_waits_equal(oracle_mod, raw, run_waits(kp, raw, use_hdr=True))
 
 
+@pytest.mark.parametrize("n_wg,R", [(128, 20), (129, 4), (300, 6), (300, 8), (64, 21), (200, 128)])
+def test_header_counts_on_either_side_of_their_line(kp, oracle_mod, n_wg, R):
+    """Added by the decoder workgroups or made by the kernel behind them."""
+    spec = inputs.TraceSpec(n_wg=n_wg, waves=2, n_regions=R, cap_wave=64, total_per_wave=64, total_var=30, seed=n_wg + R,
+                            p_orphan=0.05, p_swap=0.01)
+    raw, _ = inputs.gen_trace(spec)
+    raw[6] = 12
+    assert_waits_equal(oracle_mod, raw, run_waits(kp, raw, use_hdr=True))
+
+
 def test_many_workgroups_exercise_generation_reuse(kp, oracle_mod):
     # more recorded workgroups than resident decoder workgroups: staging area and totals are reused
     spec = inputs.TraceSpec(n_wg=3000, waves=4, n_regions=6, cap_wave=64, total_per_wave=64, total_var=40, seed=78,

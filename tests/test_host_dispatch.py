@@ -34,3 +34,20 @@ def test_wait_replay_takes_every_geometry_up_to_its_limit(tmp_path):
     for (w, r, cap), (status, launches) in zip(shapes, fake_hip.run(calls, tmp_path)):
         assert (status == 0) == (r <= limit[w, cap]), (w, r, cap, status)
         assert all(lds <= 160 * 1024 for _, _, _, lds in launches), launches
+
+
+def test_wait_header_counts_are_made_once(tmp_path):
+    """The three header counts are added by the decoder workgroups or made by a kernel behind them: the line goes by
+    the launched grid, also where a small device holds fewer workgroups than the trace has."""
+    calls = [{"fn": "kp_trace_waits_hdr", "trace": (n_wg, 8, regions, 64), "device": (dev, cus, 2)}
+             for dev, cus in enumerate((256, 64, 8)) for regions in (1, 4, 6, 7, 16, 21, 57) for n_wg in (1, 128, 129, 5000)]
+    for call, (status, launches) in zip(calls, fake_hip.run(calls, tmp_path)):
+        assert status == 0, call
+        n_wg, _, regions, _ = call["trace"]
+        grid = min(n_wg, 2 * call["device"][1])
+        main = kernels(launches, "kp_waits_main")
+        assert len(main) == 1 and main[0][1] == grid, (call, launches)
+        head = kernels(launches, "kp_waits_head")
+        added = regions <= 20 and (grid <= 128 or regions in (1, 6, 7))
+        assert [x[1:3] for x in head] == ([] if added else [(1, 192)]), (call, launches)
+        assert not head or launches[-1] == head[0]
