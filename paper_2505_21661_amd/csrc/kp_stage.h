@@ -52,23 +52,40 @@ __device__ __forceinline__ uint32_t wave_shr1(uint32_t v, uint32_t lane0) {
   return (uint32_t)__builtin_amdgcn_update_dpp((int)lane0, (int)v, 0x138, 0xF, 0xF, false);
 }
 
-// Inclusive prefix sum over the 64 lanes: four shifts inside each row of 16, then the last lane of
-// row 0/2 into row 1/3 and the last lane of the lower half into the upper half.
-__device__ __forceinline__ uint32_t wave_scan_add(uint32_t v) {
-  v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x111, 0xF, 0xF, false);  // row_shr:1
-  v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x112, 0xF, 0xF, false);  // row_shr:2
-  v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x114, 0xF, 0xF, false);  // row_shr:4
-  v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x118, 0xF, 0xF, false);  // row_shr:8
-  v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x142, 0xA, 0xF, false);  // row_bcast:15
-  v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x143, 0xC, 0xF, false);  // row_bcast:31
-  return v;
-}
-
 // The metadata tag of the records staged in pass `iter` of a persistent workgroup.  A staged word
 // counts only if it carries the generation of its pass, so the staging area is cleared on the
 // first pass and when the 16-bit generation wraps, not for every recorded workgroup.
 __device__ __forceinline__ uint32_t live_tag_of(uint32_t iter) { return ((1u + iter % 0xFFFFu) << 16) | kMValid; }
 __device__ __forceinline__ bool is_live(uint32_t m, uint32_t live_tag) { return (m & kLiveMask) == live_tag; }
+
+// ENDs of two neighbouring ranks k and k + 1 (k even) whose START is not the record right below them: each looks for
+// the nearest record of its region among the ranks below k, two ranks per step.  `at` is the index of ranks k, k + 1
+// in rec2, `below` = k / 2; id is END << 7 | region, and a record found settles paired and start.
+// An END inside another region looks three ranks back, so one iteration of two steps, which travel together, settles a
+// round of regions inside regions.  A round that took them one per lane and asked for the lanes of a region with one
+// ballot per bit, further back one lane at a time, against this: 1024 workgroups of 8 x 2048 records, regions three deep,
+// timeline 199 / 117 us, waits 135 / 77; one region around 20 others 556 / 318 and 329 / 163.  Steps in fours: 126 us where
+// two take 111; one END of a lane after the other: 133 us where both together take 117.
+__device__ __forceinline__ void look_back(const u32x4* rec2, uint32_t at, uint32_t below, uint32_t live_tag, bool open0, uint32_t id0,
+                                          bool& paired0, uint32_t& start0, bool open1, uint32_t id1, bool& paired1, uint32_t& start1) {
+  constexpr uint32_t kSame = kLiveMask | kMRegion;
+  if (!(open0 || open1) || below == 0u) return;
+  const uint32_t want0 = live_tag | (id0 & kMRegion), want1 = live_tag | (id1 & kMRegion);
+  for (uint32_t s = 1; s <= below && (open0 || open1); s += 2u) {
+    const u32x4 va = rec2[at - s], vb = rec2[at - (s < below ? s + 1u : s)];
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      const u32x4 v = h ? vb : va;
+      const bool odd0 = ((v.w ^ want0) & kSame) == 0u, odd1 = ((v.w ^ want1) & kSame) == 0u;
+      if (open0 && (odd0 || ((v.y ^ want0) & kSame) == 0u)) {
+        paired0 = ((odd0 ? v.w : v.y) & kMEnd) == 0u; start0 = odd0 ? v.z : v.x; open0 = false;
+      }
+      if (open1 && (odd1 || ((v.y ^ want1) & kSame) == 0u)) {
+        paired1 = ((odd1 ? v.w : v.y) & kMEnd) == 0u; start1 = odd1 ? v.z : v.x; open1 = false;
+      }
+    }
+  }
+}
 
 // The records of a recorded workgroup on their way to LDS: a thread's share in 16-byte units of two records
 // (block_threads() makes it at most 8) and the header's record count of wave `thread`.  A persistent

@@ -12,9 +12,8 @@
 // rank.  Then the hardware waves share out the recorded waves in runs of consecutive ranks and walk them
 // 128 ranks per round, two per lane (a run above rank 0 first counts the pairs below it):
 //   - an END is paired iff the nearest earlier record of its region is a START: by far the most often the
-//     record right below it, in the same lane or the one below (a DPP wave shift).  A round in which some END
-//     has another record below it is walked 64 ranks at a time: the lanes with the END's region (one ballot per bit
-//     of the region number) say which record is the nearest, or a walk back through LDS does;
+//     record right below it, in the same lane or the one below (a DPP wave shift).  An END that has another record
+//     below it looks further back in LDS, two ranks per step, those of a round together (look_back);
 //   - its row index is the running count of paired ENDs (ballot + popcount);
 //   - its iteration index is the number of pairs of its region in earlier rounds, a counter in LDS, plus those in
 //     lower lanes.
@@ -22,7 +21,7 @@
 // the next workgroup's records travel under the walk, and a lane takes two ranks: of a START and an END only one
 // makes a row.  Measured on 4096 workgroups of 8 waves x 2048 records (0.54 GB read, 0.53 GB written): 495 us with
 // the loads waited for, four ranks of look-back per record and byte-wide counters scanned over the lanes; 341 us
-// with the loads ahead and ballots in their place, one rank per lane; 281 us with two (3.8 TB/s).
+// with the loads ahead and ballots in their place, one rank per lane; 270 us with two (4.0 TB/s).
 #include "kp_stage.h"
 
 namespace {
@@ -50,9 +49,7 @@ template <int BLOCK, int UNITS>
 __global__ __launch_bounds__(BLOCK) void kp_pairs_main(Trace p, PairsOut o, uint32_t parts) {
   extern __shared__ __align__(16) unsigned char smem[];
   const Lds L = lds_layout(p.nrec);
-  const uint2* rec = reinterpret_cast<const uint2*>(smem + L.rec);
   const u32x4* rec2 = reinterpret_cast<const u32x4*>(smem + L.rec);
-  const uint32_t* recw = reinterpret_cast<const uint32_t*>(smem + L.rec);  // word 2p = clock, 2p+1 = metadata
   const uint32_t* sV = reinterpret_cast<const uint32_t*>(smem + L.v);
   uint32_t* below = reinterpret_cast<uint32_t*>(smem + L.end);  // per hardware wave: pairs per region below its run
 
@@ -87,106 +84,81 @@ __global__ __launch_bounds__(BLOCK) void kp_pairs_main(Trace p, PairsOut o, uint
       u32x4* my_rows = o.rows + ((size_t)wg * W + w) * (cap / 2);
       uint32_t n_rows = 0;
       uint32_t carry_id = kNoId, carry_t = 0u;  // the rank just below the round: metadata byte (kNoId: none) and clock
-      uint32_t end_t = 0u, start_t = 0u, region = 0u;  // of this lane's pair
-      // 64 ranks from kb, one per lane, any record: is this lane's an END that is paired?
-      auto pair_64 = [&](uint32_t kb, uint32_t k_end) __attribute__((always_inline)) -> bool {
-        const uint32_t k = kb + lane;
-        const uint2 r0 = rec[wofs + (k < k_end ? k : 0u)];
-        const bool valid = k < k_end && is_live(r0.y, live_tag);
-        const uint32_t id = valid ? r0.y & 0xFFu : kNoId;
-        end_t = r0.x;
-        region = id & kMRegion;
-        const uint32_t below_id = wave_shr1(id, carry_id);
-        start_t = wave_shr1(end_t, carry_t);
-        carry_id = (uint32_t)__builtin_amdgcn_readlane((int)id, 63);
-        carry_t = (uint32_t)__builtin_amdgcn_readlane((int)end_t, 63);
-        const bool is_end = valid && (id & kMEnd) != 0u;
-        bool paired = is_end && below_id == region;
-        if (__builtin_amdgcn_ballot_w64(is_end && !paired)) {
-          // nearest earlier record of the region: a lower lane, or further back in LDS
-          uint64_t same = __builtin_amdgcn_ballot_w64(valid);
-          for (uint32_t b = 0; b < region_bits; ++b) {
-            const uint64_t set = __builtin_amdgcn_ballot_w64(valid && ((region >> b) & 1u));
-            same &= ((region >> b) & 1u) ? set : ~set;
-          }
-          const uint64_t ends = __builtin_amdgcn_ballot_w64(is_end), lower = same & lt_mask;
-          const int src = lower ? 63 - (int)__builtin_clzll(lower) : 0;
-          const uint32_t far_t = (uint32_t)__shfl((int)end_t, src, 64);
-          if (is_end && !paired) {
-            if (lower) {
-              paired = !((ends >> src) & 1ull);
-              start_t = far_t;
-            } else {
-              for (uint32_t kk = kb; kk-- > 0;) {
-                const uint32_t mq = recw[2 * (wofs + kk) + 1];
-                if (!is_live(mq, live_tag) || (mq & kMRegion) != region) continue;
-                paired = !(mq & kMEnd);
-                start_t = recw[2 * (wofs + kk)];
-                break;
-              }
-            }
-          }
-        }
-        return paired;
-      };
-      // 128 ranks, two neighbours per lane, if every END among them has its START right below it: then a lane
-      // holds at most one pair (an END above an END is not paired).  Else `slow`, and nothing has happened.
+      // 128 ranks from kb, two neighbours per lane: which of this lane's are ENDs that are paired, and with what.
+      uint32_t id0 = kNoId, id1 = kNoId, start0 = 0u, start1 = 0u;
+      u32x4 r = {0u, 0u, 0u, 0u};  // {clock, metadata} of the even rank and of the odd one
       u32x4 next = rec2[(wofs + (2u * lane < V ? 2u * lane : 0u)) >> 1];  // one round ahead, to hide the LDS latency
-      auto pair_128 = [&](uint32_t kb, uint32_t k_end, bool& slow) __attribute__((always_inline)) -> bool {
+      auto pair_128 = [&](uint32_t kb, uint32_t k_end, bool& paired0, bool& paired1) __attribute__((always_inline)) {
         const uint32_t k = kb + 2u * lane;
-        const u32x4 r = next;  // {clock, metadata} of the even rank and of the odd one
+        r = next;
         next = rec2[(wofs + (k + 128u < V ? k + 128u : 0u)) >> 1];
-        const uint32_t id0 = k < k_end && is_live(r.y, live_tag) ? r.y & 0xFFu : kNoId;
-        const uint32_t id1 = k + 1u < k_end && is_live(r.w, live_tag) ? r.w & 0xFFu : kNoId;
-        const uint32_t below_id = wave_shr1(id1, carry_id), below_t = wave_shr1(r.z, carry_t);
-        // an END carries kMEnd above its region, no record neither: x ^ y == kMEnd says "END over its START"
-        const bool near0 = (id0 ^ below_id) == kMEnd && id0 >= kMEnd, near1 = (id1 ^ id0) == kMEnd && id1 >= kMEnd;
-        const bool end0 = (id0 & ~kMRegion) == kMEnd, end1 = (id1 & ~kMRegion) == kMEnd;
-        slow = __builtin_amdgcn_ballot_w64((end0 && !near0) || (end1 && !near1)) != 0ull;
-        if (slow) return false;
+        id0 = k < k_end && is_live(r.y, live_tag) ? r.y & 0xFFu : kNoId;
+        id1 = k + 1u < k_end && is_live(r.w, live_tag) ? r.w & 0xFFu : kNoId;
+        const uint32_t below_id = wave_shr1(id1, carry_id);
+        start0 = wave_shr1(r.z, carry_t); start1 = r.x;
         carry_id = (uint32_t)__builtin_amdgcn_readlane((int)id1, 63);
         carry_t = (uint32_t)__builtin_amdgcn_readlane((int)r.z, 63);
-        region = (near1 ? id1 : id0) & kMRegion;
-        end_t = near1 ? r.z : r.x;
-        start_t = near1 ? r.x : below_t;
-        return near0 || near1;
+        // an END carries kMEnd above its region, no record neither: x ^ y == kMEnd says "END over its START"
+        paired0 = (id0 ^ below_id) == kMEnd && id0 >= kMEnd;
+        paired1 = (id1 ^ id0) == kMEnd && id1 >= kMEnd;
+        const bool open0 = (id0 & ~kMRegion) == kMEnd && !paired0;
+        const bool open1 = (id1 & ~kMRegion) == kMEnd && !paired1 && id1 != id0;
+        if (__builtin_amdgcn_ballot_w64(open0 || open1) != 0ull)
+          look_back(rec2, (wofs + k) >> 1, k >> 1, live_tag, open0, id0, paired0, start0, open1, id1, paired1, start1);
       };
       // ---- count the pairs below this run ---------------------------------------------------------------
-      auto tally = [&](bool paired) __attribute__((always_inline)) {
-        n_rows += (uint32_t)__popcll(__builtin_amdgcn_ballot_w64(paired));
-        if (paired) atomicAdd(&seen[region], 1u);
-      };
       for (uint32_t kb = 0; kb < kc; kb += 128) {  // kc is a multiple of 128 or the end of the wave
-        bool slow;
-        const bool paired = pair_128(kb, kc, slow);
-        if (!slow) tally(paired);
-        else for (uint32_t half = 0; half < 128u; half += 64u) tally(pair_64(kb + half, kc));
+        bool paired0, paired1;
+        pair_128(kb, kc, paired0, paired1);
+        n_rows += (uint32_t)__popcll(__builtin_amdgcn_ballot_w64(paired0)) + (uint32_t)__popcll(__builtin_amdgcn_ballot_w64(paired1));
+        if (paired0) atomicAdd(&seen[id0 & kMRegion], 1u);
+        if (paired1) atomicAdd(&seen[id1 & kMRegion], 1u);
       }
       // ---- emit the rows of this run ------------------------------------------------------------------------
-      auto emit = [&](bool paired) __attribute__((always_inline)) {
-        const uint64_t pb = __builtin_amdgcn_ballot_w64(paired);
-        // iteration index: pairs of this region in earlier rounds + in lower lanes of this round
-        uint64_t same = pb;
-        for (uint32_t b = 0; b < region_bits; ++b) {
-          const uint64_t set = __builtin_amdgcn_ballot_w64((region >> b) & 1u);
-          same &= ((region >> b) & 1u) ? set : ~set;
-        }
-        if (paired) {
-          const uint32_t it = seen[region] + (uint32_t)__popcll(same & lt_mask);
-          const uint64_t here_up = same & ~lt_mask;
-          if ((here_up & (here_up - 1ull)) == 0ull) seen[region] = it + 1u;  // the region's last pair of the round
-          const uint32_t d_raw = end_t - start_t;
-          const uint32_t d = d_raw > p.rec_cost ? d_raw - p.rec_cost : 0u;
-          const uint32_t j = n_rows + (uint32_t)__popcll(pb & lt_mask);
-          my_rows[j] = u32x4{start_t, d, it, region};
-        }
-        n_rows += (uint32_t)__popcll(pb);
+      auto row = [&](uint32_t j, uint32_t start, uint32_t end, uint32_t it, uint32_t region) __attribute__((always_inline)) {
+        const uint32_t d_raw = end - start;
+        my_rows[j] = u32x4{start, d_raw > p.rec_cost ? d_raw - p.rec_cost : 0u, it, region};
       };
       for (uint32_t kb = k0; kb < k1; kb += 128) {
-        bool slow;
-        const bool paired = pair_128(kb, k1, slow);
-        if (!slow) emit(paired);
-        else for (uint32_t half = 0; half < 128u; half += 64u) emit(pair_64(kb + half, k1));
+        bool paired0, paired1;
+        pair_128(kb, k1, paired0, paired1);
+        const uint64_t pb0 = __builtin_amdgcn_ballot_w64(paired0), pb1 = __builtin_amdgcn_ballot_w64(paired1);
+        // iteration index: pairs of this region in earlier rounds + on lower ranks of this round
+        if ((pb0 & pb1) == 0ull) {  // at most one pair per lane (always so where every START is right below its END)
+          const bool paired = paired0 || paired1;
+          const uint32_t region = (paired1 ? id1 : id0) & kMRegion;
+          const uint64_t pb = pb0 | pb1;
+          uint64_t same = pb;
+          for (uint32_t b = 0; b < region_bits; ++b) {
+            const uint64_t set = __builtin_amdgcn_ballot_w64((region >> b) & 1u);
+            same &= ((region >> b) & 1u) ? set : ~set;
+          }
+          if (paired) {
+            const uint32_t it = seen[region] + (uint32_t)__popcll(same & lt_mask);
+            const uint64_t here_up = same & ~lt_mask;
+            if ((here_up & (here_up - 1ull)) == 0ull) seen[region] = it + 1u;  // the region's last pair of the round
+            row(n_rows + (uint32_t)__popcll(pb & lt_mask), paired1 ? start1 : start0, paired1 ? r.z : r.x, it, region);
+          }
+          n_rows += (uint32_t)__popcll(pb);
+        } else {
+          uint64_t even0 = pb0, odd0 = pb1, even1 = pb0, odd1 = pb1;  // the pairs of even and of odd ranks with the region of this lane's even, odd rank
+          for (uint32_t b = 0; b < region_bits; ++b) {
+            const uint64_t even = __builtin_amdgcn_ballot_w64((id0 >> b) & 1u), odd = __builtin_amdgcn_ballot_w64((id1 >> b) & 1u);
+            const uint64_t flip0 = ((id0 >> b) & 1u) ? 0ull : ~0ull, flip1 = ((id1 >> b) & 1u) ? 0ull : ~0ull;
+            even0 &= even ^ flip0; odd0 &= odd ^ flip0;
+            even1 &= even ^ flip1; odd1 &= odd ^ flip1;
+          }
+          const uint32_t j = n_rows + (uint32_t)__popcll(pb0 & lt_mask) + (uint32_t)__popcll(pb1 & lt_mask);
+          const uint64_t le_mask = 2ull * lt_mask + 1ull;
+          if (paired0)
+            row(j, start0, r.x, seen[id0 & kMRegion] + (uint32_t)__popcll(even0 & lt_mask) + (uint32_t)__popcll(odd0 & lt_mask), id0 & kMRegion);
+          if (paired1)
+            row(j + (paired0 ? 1u : 0u), start1, r.z, seen[id1 & kMRegion] + (uint32_t)__popcll(even1 & le_mask) + (uint32_t)__popcll(odd1 & lt_mask), id1 & kMRegion);
+          __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");  // (LDS operations of one wave complete in order)
+          if (paired0) atomicAdd(&seen[id0 & kMRegion], 1u);
+          if (paired1) atomicAdd(&seen[id1 & kMRegion], 1u);
+          n_rows += (uint32_t)__popcll(pb0) + (uint32_t)__popcll(pb1);
+        }
       }
       // the wave with the last run knows the total
       if (lane == 0 && part + 1u == parts) o.count[(size_t)wg * W + w] = n_rows;

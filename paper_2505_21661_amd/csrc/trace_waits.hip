@@ -13,12 +13,12 @@
 // share out the recorded waves in runs of consecutive ranks and walk them 128 ranks per round, two per
 // lane.  A START takes what it needs to know about the rank below -- metadata, clock, whether that END is
 // paired and with which clock -- from its own lane or the one below through DPP wave shifts (the last lane of
-// the previous round stands in for lane 0).  A round with an END that has not its START right below it, or with an
-// empty rank, is walked 64 ranks at a time, with ballots over the region numbers and walks back through LDS.
+// the previous round stands in for lane 0).  An END that has not its START right below it looks further back in LDS
+// (look_back); a START above an empty rank, which only damaged traces have, walks back to the record below it.
 // Sums, extrema and the log2 histogram go to LDS atomics; totals live in LDS across the recorded workgroups of
 // a persistent decoder workgroup.
 // What bounds it: instruction issue.  Measured on 9000 workgroups of 3 waves x 1024 records: 144 us with the loads
-// waited for, one rank per lane and runs cut by capacity instead of by what the wave holds; 97 us (2.3 TB/s).
+// waited for, one rank per lane and runs cut by capacity instead of by what the wave holds; 93 us (2.4 TB/s).
 #include "kp_stage.h"
 
 namespace {
@@ -117,7 +117,6 @@ __global__ __launch_bounds__(BLOCK, BLOCK == 1024 ? 4 : 6) void kp_waits_main(Tr
   }
   // stage_workgroup's first barrier orders these stores before any use
 
-  uint32_t region_bits = 0; while ((1u << region_bits) < R) ++region_bits;
   InFlight<UNITS> coming;
   request_workgroup<BLOCK, UNITS>(p, blockIdx.x, coming);
   uint32_t iter = 0;
@@ -133,7 +132,6 @@ __global__ __launch_bounds__(BLOCK, BLOCK == 1024 ? 4 : 6) void kp_waits_main(Tr
       const uint32_t wofs = w << cl2, V = sV[w];
       const uint32_t rounds = (V + 127u) >> 7, plen = ((rounds + parts - 1u) / parts) << 7;
       const uint32_t k0 = part * plen, k1 = V < k0 + plen ? V : k0 + plen;
-      const unsigned long long lt_mask = (1ull << lane) - 1ull;
       const uint32_t copy = (lane >> 4) & (copies - 1u);
       // The START of an END with region `r` at rank `at`: the nearest record of its region below `from`, if that is one.
       auto find_start = [&](uint32_t from, uint32_t r, uint32_t& clock) -> bool {
@@ -169,81 +167,48 @@ __global__ __launch_bounds__(BLOCK, BLOCK == 1024 ? 4 : 6) void kp_waits_main(Tr
           atomicAdd(&as_pack[a], (1ull << 46) | (unsigned long long)(whole > p.rec_cost ? whole - p.rec_cost : 0u));
         }
       };
-      // 64 ranks from kb, one per lane, any record.
-      auto round_64 = [&](uint32_t kb) __attribute__((always_inline)) {
-        const uint32_t k = kb + lane;
-        const uint2 r0 = rec[wofs + (k < k1 ? k : 0u)];
-        const bool valid = k < k1 && is_live(r0.y, live_tag);
-        const uint32_t id = valid ? r0.y & 0xFFu : kNoId, t0 = r0.x, region = id & kMRegion;
-        uint32_t below_id = wave_shr1(id, carry_id), below_t = wave_shr1(t0, carry_t);
-        // ---- an END is paired iff the nearest earlier record of its region is a START ------------------
-        const bool is_end = valid && (id & kMEnd) != 0u;
-        bool paired = is_end && below_id == region;
-        uint32_t start_t = below_t;
-        if (__builtin_amdgcn_ballot_w64(is_end && !paired)) {
-          unsigned long long same = __builtin_amdgcn_ballot_w64(valid);
-          for (uint32_t b = 0; b < region_bits; ++b) {
-            const unsigned long long set = __builtin_amdgcn_ballot_w64(valid && ((region >> b) & 1u));
-            same &= ((region >> b) & 1u) ? set : ~set;
-          }
-          const unsigned long long ends = __builtin_amdgcn_ballot_w64(is_end), lower = same & lt_mask;
-          const int src = lower ? 63 - (int)__builtin_clzll(lower) : 0;
-          const uint32_t far_t = (uint32_t)__shfl((int)t0, src, 64);
-          if (is_end && !paired) {
-            if (lower) { paired = !((ends >> src) & 1ull); start_t = far_t; }
-            else paired = find_start(kb, region, start_t);
-          }
-        }
-        // ---- a START looks at the record below it -------------------------------------------------------
-        uint32_t below_paired = wave_shr1(paired ? 1u : 0u, carry_paired);
-        uint32_t below_start = wave_shr1(start_t, carry_start);
-        carry_id = (uint32_t)__builtin_amdgcn_readlane((int)id, 63);
-        carry_t = (uint32_t)__builtin_amdgcn_readlane((int)t0, 63);
-        carry_paired = (uint32_t)__builtin_amdgcn_readlane((int)(paired ? 1u : 0u), 63);
-        carry_start = (uint32_t)__builtin_amdgcn_readlane((int)start_t, 63);
-        const bool is_start = valid && !is_end;
-        if (is_start && below_id == kNoId) {  // the rank below is empty
-          for (uint32_t kk = k; kk-- > 0;) {  // the record below it
-            const uint2 rq = rec[wofs + kk];
-            if (!is_live(rq.y, live_tag)) continue;
-            below_id = rq.y & 0xFFu; below_t = rq.x;
-            below_paired = (below_id & kMEnd) && find_start(kk, below_id & kMRegion, below_start) ? 1u : 0u;
-            break;
-          }
-        }
-        if (is_start && below_id != kNoId && (below_id & kMEnd)) account(below_id & kMRegion, below_t, t0, below_paired != 0u, below_start);
-      };
-      // 128 ranks per round, two neighbours per lane, as long as every END among them has its START right below it
-      // and no rank is empty: then a lane holds at most one wait (a START above a START is none).
+      // 128 ranks per round, two neighbours per lane.  A lane holds at most one wait (a START above a START is none).
       u32x4 next = rec2[(wofs + (k0 + 2u * lane < k1 ? k0 + 2u * lane : 0u)) >> 1];  // one round ahead, to hide the LDS latency
       for (uint32_t kb = k0; kb < k1; kb += 128) {
         const uint32_t k = kb + 2u * lane;
         const u32x4 r = next;  // {clock, metadata} of the even rank and of the odd one
         next = rec2[(wofs + (k + 128u < k1 ? k + 128u : 0u)) >> 1];
-        const bool in0 = k < k1, in1 = k + 1u < k1;
-        const uint32_t id0 = in0 && is_live(r.y, live_tag) ? r.y & 0xFFu : kNoId;
-        const uint32_t id1 = in1 && is_live(r.w, live_tag) ? r.w & 0xFFu : kNoId;
+        const uint32_t id0 = k < k1 && is_live(r.y, live_tag) ? r.y & 0xFFu : kNoId;
+        const uint32_t id1 = k + 1u < k1 && is_live(r.w, live_tag) ? r.w & 0xFFu : kNoId;
         const uint32_t below_id = wave_shr1(id1, carry_id), below_t = wave_shr1(r.z, carry_t);
-        // x ^ y == kMEnd with END x: an END over its START
-        const bool near0 = (id0 ^ below_id) == kMEnd && id0 >= kMEnd, near1 = (id1 ^ id0) == kMEnd && id1 >= kMEnd;
-        const bool end0 = (id0 & ~kMRegion) == kMEnd, end1 = (id1 & ~kMRegion) == kMEnd;
-        if (__builtin_amdgcn_ballot_w64((end0 && !near0) || (end1 && !near1) || (in0 && id0 == kNoId) || (in1 && id1 == kNoId) ||
-                                        (in0 && k > 0u && below_id == kNoId)) != 0ull) {
-          round_64(kb);
-          if (kb + 64u < k1) round_64(kb + 64u);
-          continue;
+        // is the END at either rank paired, and with a START at which clock (x ^ y == kMEnd with END x: an END over its START)
+        bool paired0 = (id0 ^ below_id) == kMEnd && id0 >= kMEnd, paired1 = (id1 ^ id0) == kMEnd && id1 >= kMEnd;
+        uint32_t start0 = below_t, start1 = r.x;
+        const bool end0 = (id0 & ~kMRegion) == kMEnd, open0 = end0 && !paired0;
+        const bool open1 = (id1 & ~kMRegion) == kMEnd && !paired1 && id1 != id0;
+        // a START above an empty rank
+        const bool lost0 = id0 <= kMRegion && below_id == kNoId && k > 0u, lost1 = id1 <= kMRegion && id0 == kNoId;
+        uint32_t far_id = kNoId, far_t = 0u, far_start = 0u;
+        bool far_paired = false;
+        if (__builtin_amdgcn_ballot_w64(open0 || open1 || lost0 || lost1) != 0ull) {
+          look_back(rec2, (wofs + k) >> 1, k >> 1, live_tag, open0, id0, paired0, start0, open1, id1, paired1, start1);
+          if (lost0 || lost1) {
+            for (uint32_t kk = k; kk-- > 0;) {  // the record below it
+              const uint2 rq = rec[wofs + kk];
+              if (!is_live(rq.y, live_tag)) continue;
+              far_id = rq.y & 0xFFu; far_t = rq.x;
+              far_paired = (far_id & kMEnd) != 0u && find_start(kk, far_id & kMRegion, far_start);
+              break;
+            }
+          }
         }
         // of the lane below: is its odd record a paired END, and with which START
-        const uint32_t below_paired = wave_shr1(near1 ? 1u : 0u, carry_paired), below_start = wave_shr1(r.x, carry_start);
+        const uint32_t below_paired = wave_shr1(paired1 ? 1u : 0u, carry_paired), below_start = wave_shr1(start1, carry_start);
         carry_id = (uint32_t)__builtin_amdgcn_readlane((int)id1, 63);
         carry_t = (uint32_t)__builtin_amdgcn_readlane((int)r.z, 63);
-        carry_paired = (uint32_t)__builtin_amdgcn_readlane((int)(near1 ? 1u : 0u), 63);
-        carry_start = (uint32_t)__builtin_amdgcn_readlane((int)r.x, 63);
-        const bool wait1 = id1 <= kMRegion && end0;                                        // START over END in this lane
+        carry_paired = (uint32_t)__builtin_amdgcn_readlane((int)(paired1 ? 1u : 0u), 63);
+        carry_start = (uint32_t)__builtin_amdgcn_readlane((int)start1, 63);
+        const bool wait1 = id1 <= kMRegion && end0;                                // START over END in this lane
         const bool wait0 = id0 <= kMRegion && (below_id & ~kMRegion) == kMEnd;  // START over the END of the lane below
-        if (wait0 || wait1)
-          account((wait1 ? id0 : below_id) & kMRegion, wait1 ? r.x : below_t, wait1 ? r.z : r.x, wait1 ? near0 : below_paired != 0u,
-                  wait1 ? below_t : below_start);
+        const bool far = (far_id & ~kMRegion) == kMEnd;
+        if (wait0 || wait1 || far)
+          account((wait1 ? id0 : far ? far_id : below_id) & kMRegion, wait1 ? r.x : far ? far_t : below_t, wait1 || lost1 ? r.z : r.x,
+                  wait1 ? paired0 : far ? far_paired : below_paired != 0u, wait1 ? start0 : far ? far_start : below_start);
       }
     }
     __syncthreads();
@@ -308,7 +273,7 @@ __global__ __launch_bounds__(BLOCK, BLOCK == 1024 ? 4 : 6) void kp_waits_main(Tr
 // kernel behind them makes them (2 us).  The adds of all regions go to one line, which every workgroup visits, three
 // times per region: with many of either the workgroups queue up there, unless they queue up just as long at the
 // regions' own sums, which an odd number of regions, 2 and 6 leave across the lines.  Measured, added / kernel, us:
-// 64 workgroups x 16 regions 10.4 / 10.9, x 28 + 0.4 added, x 64 + 4.2; 128 x 8 11.8 / 11.6, x 12 12.3 / 13.1; 256 x 4 17.6 / 15.5,
+// 64 decoder workgroups x 16 regions 10.4 / 10.9, x 28 + 0.4 added, x 64 + 4.2; 128 x 8 11.8 / 11.6, x 12 12.3 / 13.1; 256 x 4 17.6 / 15.5,
 // x 6 17.5 / 19.0, x 7 18.4 / 19.5, x 8 17.4 / 14.4, x 16 17.8 / 15.1; 1024 x 3 45.1 / 46.9, x 4 38.6 / 29.8, x 6 38.6 / 38.8,
 // x 8 39.0 / 26.4, x 9 and 13 the same either way, x 10 + 4.4 added, x 16 39.8 / 27.8.
 inline bool add_head_counts(uint32_t grid, uint32_t R) {

@@ -77,3 +77,37 @@ def mostly_sequential_trace(seed, W, R, cap, holes=False):
                     seg[i] = (0xFFFFFFFF, seg[i][1])
         wgs.append(wg)
     return inputs.encode_trace(wgs, W, R, cap, rec_cost=7)
+
+
+def nested_trace(seed, W, R, cap, depth, inner):
+    """Regions inside regions: blocks of `depth` STARTs and their ENDs in reverse order, now and then one region
+    around `inner` others; two workgroups, wave 0 wrapped."""
+    import inputs
+
+    rng = np.random.default_rng(seed)
+    wgs = []
+    for _ in range(2):
+        evs = []
+        for w in range(W):
+            total, wave, t = (cap + 37 if w == 0 else int(rng.integers(1, cap + 1))), [], 0
+
+            def put(phase, region):
+                nonlocal t
+                t += int(rng.integers(0, 300))
+                wave.append((phase, region, t))
+
+            while len(wave) < total:
+                order = [int(x) for x in rng.permutation(R)[:depth]]
+                around = int(rng.integers(0, R)) if rng.random() < 0.05 else -1
+                if around >= 0:
+                    put(inputs.PHASE_START, around)
+                for _i in range(inner if around >= 0 else 1):
+                    for r in order:
+                        put(inputs.PHASE_START, r)
+                    for r in reversed(order):
+                        put(inputs.PHASE_END, r)
+                if around >= 0:
+                    put(inputs.PHASE_END, around)
+            evs.append(wave[:total])
+        wgs.append(inputs.events_to_wg(evs, cap, flush=False))
+    return inputs.encode_trace(wgs, W, R, cap, rec_cost=7)

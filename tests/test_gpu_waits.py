@@ -64,6 +64,15 @@ def test_generated_traces(kp, oracle_mod, W, R, cap, total):
     assert_waits_equal(oracle_mod, raw, run_waits(kp, raw))
 
 
+@pytest.mark.parametrize("W,R,cap,depth,inner", [(1, 128, 4096, 2, 3), (4, 5, 1024, 3, 40), (8, 16, 2048, 6, 12), (3, 32, 128, 17, 2), (16, 2, 64, 2, 9)])
+def test_regions_inside_regions(kp, oracle_mod, W, R, cap, depth, inner):
+    """ENDs whose START lies up to some hundreds of records back, two of them next to each other among them."""
+    from tests.gpu_util import nested_trace
+
+    raw = nested_trace(R + depth, W, R, cap, depth, inner)
+    assert_waits_equal(oracle_mod, raw, run_waits(kp, raw, use_hdr=True))
+
+
 @pytest.mark.parametrize("holes", [False, True])
 @pytest.mark.parametrize("W,R,cap", [(1, 128, 2048), (3, 7, 1024), (16, 16, 256), (8, 33, 128), (5, 3, 64), (2, 5, 8192)])
 def test_mostly_sequential_traces(kp, oracle_mod, W, R, cap, holes):
