@@ -53,7 +53,7 @@ __global__ __launch_bounds__(BLOCK) void kp_pairs_main(Trace p, PairsOut o, uint
   const uint32_t* sV = reinterpret_cast<const uint32_t*>(smem + L.v);
   uint32_t* below = reinterpret_cast<uint32_t*>(smem + L.end);  // per hardware wave: pairs per region below its run
 
-  const uint32_t tid = threadIdx.x, lane = tid & 63u, hw = tid >> 6;
+  const uint32_t tid = threadIdx.x, lane = tid & 63u, hw = (uint32_t)__builtin_amdgcn_readfirstlane((int)(tid >> 6));
   const uint32_t W = p.W, R = p.R, cap = p.cap, cl2 = p.cap_log2;
   uint32_t region_bits = 0; while ((1u << region_bits) < R) ++region_bits;
   const unsigned long long lt_mask = (1ull << lane) - 1ull;
@@ -185,7 +185,10 @@ kp_status launch_pairs_units(const Trace& p, const PairsOut& o, uint32_t lds_byt
 
 template <int BLOCK>
 kp_status launch_pairs(const Trace& p, const PairsOut& o, uint32_t lds_bytes, hipStream_t s) {
-  return p.nrec <= 8u * BLOCK ? launch_pairs_units<BLOCK, 4>(p, o, lds_bytes, s) : launch_pairs_units<BLOCK, 8>(p, o, lds_bytes, s);
+  if constexpr (BLOCK > 256) {  // (blocks of 256 hold less than 2048 records)
+    if (p.nrec > 8u * BLOCK) return launch_pairs_units<BLOCK, 8>(p, o, lds_bytes, s);
+  }
+  return launch_pairs_units<BLOCK, 4>(p, o, lds_bytes, s);
 }
 
 size_t count_bytes(size_t n_seg) { return ((n_seg + 3) / 4) * 16; }

@@ -18,7 +18,7 @@
 // Sums, extrema and the log2 histogram go to LDS atomics; totals live in LDS across the recorded workgroups of
 // a persistent decoder workgroup.
 // What bounds it: instruction issue.  Measured on 9000 workgroups of 3 waves x 1024 records: 144 us with the loads
-// waited for, one rank per lane and runs cut by capacity instead of by what the wave holds; 93 us (2.4 TB/s).
+// waited for, one rank per lane and runs cut by capacity instead of by what the wave holds; 87 us (2.5 TB/s).
 #include "kp_stage.h"
 
 namespace {
@@ -84,9 +84,10 @@ __global__ void kp_waits_init(uint64_t* out, uint32_t n_wg, uint32_t W, uint32_t
   }
 }
 
-// (6 hardware waves per SIMD, i.e. 80 vector registers: 97 us against 102 with 85 and 122 with 64)
+// (6 hardware waves per SIMD, i.e. 80 vector registers: 97 us against 102 with 85 and 122 with 64; with 8 units per thread
+// 80 would be 16 too few: 1000 workgroups of 7 x 1024 43 us where 5 waves per SIMD take 33)
 template <int BLOCK, int UNITS>
-__global__ __launch_bounds__(BLOCK, BLOCK == 1024 ? 4 : 6) void kp_waits_main(Trace p, uint64_t* out_words, uint32_t parts, uint32_t copies, uint32_t add_head) {
+__global__ __launch_bounds__(BLOCK, BLOCK == 1024 ? 4 : (UNITS == 4 ? 6 : 5)) void kp_waits_main(Trace p, uint64_t* out_words, uint32_t parts, uint32_t copies, uint32_t add_head) {
   extern __shared__ __align__(16) unsigned char smem[];
   const Lds L = lds_layout(p.nrec);
   const WaitsLds X = waits_lds(L.end, p.W, p.R, copies);
@@ -105,7 +106,7 @@ __global__ __launch_bounds__(BLOCK, BLOCK == 1024 ? 4 : 6) void kp_waits_main(Tr
   unsigned long long* acnt = reinterpret_cast<unsigned long long*>(smem + X.acnt);
   unsigned long long* asum = reinterpret_cast<unsigned long long*>(smem + X.asum);
 
-  const uint32_t tid = threadIdx.x, lane = tid & 63u, hw = tid >> 6;
+  const uint32_t tid = threadIdx.x, lane = tid & 63u, hw = (uint32_t)__builtin_amdgcn_readfirstlane((int)(tid >> 6));
   const uint32_t W = p.W, R = p.R, cl2 = p.cap_log2;
   const WaitsLayout SL = waits_layout(p.n_wg, W, R);
 
@@ -313,7 +314,10 @@ kp_status launch_waits_units(const Trace& p, uint64_t* out, const WaitsLds& X, h
 
 template <int BLOCK>
 kp_status launch_waits(const Trace& p, uint64_t* out, const WaitsLds& X, hipStream_t s) {
-  return p.nrec <= 8u * BLOCK ? launch_waits_units<BLOCK, 4>(p, out, X, s) : launch_waits_units<BLOCK, 8>(p, out, X, s);
+  if constexpr (BLOCK > 256) {  // (blocks of 256 hold less than 2048 records)
+    if (p.nrec > 8u * BLOCK) return launch_waits_units<BLOCK, 8>(p, out, X, s);
+  }
+  return launch_waits_units<BLOCK, 4>(p, out, X, s);
 }
 
 kp_status waits_impl(const void* raw, size_t n, const kp_trace_hdr& h, void* out_waits, hipStream_t s) {
