@@ -21,6 +21,8 @@
 // waited for, one rank per lane and runs cut by capacity instead of by what the wave holds; 87 us (2.5 TB/s).
 #include "kp_stage.h"
 
+#include <math.h>
+
 namespace {
 
 using namespace kp_stage;
@@ -291,6 +293,16 @@ __global__ void kp_waits_head(uint64_t* out, uint32_t n_wg, uint32_t W, uint32_t
   if (lane == 0) out[which] = n;
 }
 
+// Every decoder workgroup adds its totals to the same few lines at its end, one after the other: 0.03 us each.  A
+// recorded workgroup takes one of them 1.9 us and as long again for some 3000 record slots.  The sum of both is least
+// where the decoder workgroups are the square root of the recorded ones times the ratio of the two, however many are
+// resident.  All that are resident / so many: 509 workgroups of 8 x 64 slots 31.1 / 17.9 us (184 of 509), 2046 of 8 x 16
+// 31.2 / 25.2 (365 of 768), 5461 of 3 x 16 68.4 / 45.5, 1024 of 4 x 1024 52.9 / 41.5; 9000 of 3 x 1024: all 768, 87.
+inline uint32_t most_workgroups(uint32_t n_wg, uint32_t nrec) {
+  const double most = sqrt((double)n_wg * (64.0 + nrec / 48.0));
+  return most < (double)n_wg ? (uint32_t)most : n_wg;
+}
+
 template <int BLOCK, int UNITS>
 kp_status launch_waits_units(const Trace& p, uint64_t* out, const WaitsLds& X, hipStream_t s) {
   // hardware waves per recorded wave: as many as the block has, while a run keeps a round of 128 ranks
@@ -301,7 +313,8 @@ kp_status launch_waits_units(const Trace& p, uint64_t* out, const WaitsLds& X, h
   uint32_t grid = 0;
   const kp_status st = resident_grid(kern, BLOCK, X.total, &cache, &grid);
   if (st != KP_OK) return st;
-  if (grid > p.n_wg) grid = p.n_wg;
+  const uint32_t most = most_workgroups(p.n_wg, p.nrec);
+  if (grid > most) grid = most;
   const bool add_head = add_head_counts(grid, p.R);
   hipLaunchKernelGGL(kern, dim3(grid), dim3(BLOCK), X.total, s, p, out, parts, X.copies, add_head ? 1u : 0u);
   KP_HIP_TRY(hipGetLastError());

@@ -93,7 +93,7 @@ def test_largest_geometries(kp, oracle_mod, W, R, cap):
     assert_waits_equal(oracle_mod, raw, run_waits(kp, raw, use_hdr=True))
 
 
-@pytest.mark.parametrize("n_wg,R", [(128, 20), (129, 4), (300, 6), (300, 8), (64, 21), (200, 128)])
+@pytest.mark.parametrize("n_wg,R", [(240, 20), (260, 4), (300, 6), (300, 8), (64, 21), (200, 128)])
 def test_header_counts_on_either_side_of_their_line(kp, oracle_mod, n_wg, R):
     """Added by the decoder workgroups or made by the kernel behind them."""
     spec = inputs.TraceSpec(n_wg=n_wg, waves=2, n_regions=R, cap_wave=64, total_per_wave=64, total_var=30, seed=n_wg + R,

@@ -40,11 +40,11 @@ def test_wait_header_counts_are_made_once(tmp_path):
     """The three header counts are added by the decoder workgroups or made by a kernel behind them: the line goes by
     the launched grid, also where a small device holds fewer workgroups than the trace has."""
     calls = [{"fn": "kp_trace_waits_hdr", "trace": (n_wg, 8, regions, 64), "device": (dev, cus, 2)}
-             for dev, cus in enumerate((256, 64, 8)) for regions in (1, 4, 6, 7, 16, 21, 57) for n_wg in (1, 128, 129, 5000)]
+             for dev, cus in enumerate((256, 64, 8)) for regions in (1, 4, 6, 7, 16, 21, 57) for n_wg in (1, 74, 75, 219, 224, 5000)]
     for call, (status, launches) in zip(calls, fake_hip.run(calls, tmp_path)):
         assert status == 0, call
         n_wg, _, regions, _ = call["trace"]
-        grid = min(n_wg, 2 * call["device"][1])
+        grid = min(n_wg, 2 * call["device"][1], int((n_wg * (64 + 8 * 64 / 48)) ** 0.5))
         main = kernels(launches, "kp_waits_main")
         assert len(main) == 1 and main[0][1] == grid, (call, launches)
         head = kernels(launches, "kp_waits_head")
