@@ -332,8 +332,9 @@ kp_status kp_stages_critical(const void* stages, int n_wg, int n_regions, int ma
  * stream's wave leaves the low 12 bits of its hardware id register in kp_wg_hdr.wave_hw_id[]
  * (KP_FLAG_HW_IDS).  The records themselves are the same either way.
  * Bit 27 and the flush strategy go through the generic record sites (a site writes the records of the
- * site before it to LDS); every other combination keeps the cheaper chained sites (the loop stores only the clocks of its sites, a fixed sequence, and the
- * records are made from them when the trace is copied out: the same records in the same slots).
+ * site before it to LDS); every other combination keeps the cheaper chained sites (the loop stores only the
+ * clocks of its sites, a fixed sequence, and the records are made from them when the trace is copied out: the same
+ * records in the same slots).
  *
  * trace_buf: device, kp_trace_bytes(n_wg, streams, trace_cap) bytes, 16-byte aligned; headers and
  * records are fully written by the kernel (no pre-zeroing needed; slots beyond total_written
@@ -378,6 +379,11 @@ kp_status kp_gemm_launch_shape(int M, int N, int K, int* n_wg, int* waves_per_wg
  *       0 global load (issued here for a K-step up to five further on), 1 LDS store (the tiles of a later K-step
  *       are stored, behind the operand reads of this one), 2 MFMA (behind every second K-step with the workgroup
  *       barrier)
+ *       With a short K on many workgroups (K <= 96 and more than 256 of them, K <= 160 and more than 768, K <=
+ *       224 and 1024 or more, K <= 288 and 3072 or more) nothing is loaded ahead, and the same three regions,
+ *       with the same record sites, are 0 global load of this K-step, waited for, 1 LDS store of its tiles
+ *       between two workgroup barriers, 2 operand reads and MFMA: durations on either side of that line do not
+ *       compare region by region.
  * Other shapes: KP_ERR_UNSUPPORTED_SHAPE.
  */
 kp_status kp_gemm_instrumented(const void* A, const void* B, void* C, int M, int N, int K,

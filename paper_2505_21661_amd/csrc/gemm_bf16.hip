@@ -288,12 +288,16 @@ __global__ __launch_bounds__(256) void kp_gemm_small(GemmArgs g) {
 }
 
 // The same tile for a short K and many workgroups: one K step at a time, 8 KiB of LDS.  A workgroup is then over
-// before a pipeline has filled, its time is latency and the C tile, and what counts is how many of them share a
-// CU: eight or more here, five of the pipelined kernel's.  Measured on 4032 x 3968 x K (3906 workgroups), this
-// kernel against the pipelined one: K = 32 9.0 / 16.0 us, 96 13.2 / 16.4, 160 18.1 / 20.7, 192 20.4 / 22.3, 320 29.4 / 25.6,
-// 640 50.1 / 42.6; with all regions recorded K = 32 12.3 / 20.5, 160 23.7 / 27.3, 192 26.5 / 29.4, 320 38.6 / 34.0.  With fewer
-// workgroups the pipeline wins at every K (2112 x 1984, 1023 of them: K = 32 7.0 / 5.8, 192 8.3 / 7.4; 1984 x 960 x 160:
-// 6.9 / 4.8 us; 1624 of them, recorded, K = 160: 13.5 / 14.9), hence the two conditions of short_k().
+// before a pipeline has filled, its time is latency and the C tile, and what counts is how many of them share a CU:
+// eight or more here, five of the pipelined kernel's, three of those with a ring of 16 KiB.  Measured, this kernel /
+// the pipelined one, us: 3906 workgroups K = 32 9.1 / 15.7, 160 16.9 / 20.3, 256 23.2 / 24.9, 320 27.6 / 28.2; 8010 K
+// = 288 51.0 / 51.3, 320 57.5 / 54.4; 2205 K = 192 13.1 / 13.8, 224 14.7 / 14.2; 1155 K = 32 4.7 / 6.5, 224 9.1 / 9.0;
+// 930 K = 32 4.7 / 5.7, 160 6.9 / 6.8, 192 7.5 / 7.4; 675 K = 128 5.2 / 5.6, 160 5.8 / 5.7; 272 K = 128 4.8 / 4.8, 192
+// 5.2 / 4.8.  With all regions recorded: 3906 K = 32 16.5 / 24.0, 288 34.9 / 35.7; 1599 K = 128 14.7 / 14.9, 224 18.6
+// / 17.3; 1023 K = 32 7.1 / 10.1, 160 10.5 / 11.5, 224 12.1 / 11.9; 812 K = 32 6.8 / 9.0, 224 11.0 / 11.9; 506 K = 64
+// 6.1 / 6.8, 128 7.2 / 7.2; 255 K = 32 5.0 / 5.2, 128 6.0 / 5.5.  Hence short_k(): a line for one, three, four and
+// twelve workgroups per CU, the same with and without sites, so that a recorded kernel and its baseline are one. Its
+// sites follow one another as the pipelined kernel's do.
 //
 // LDS rows of 32 bf16: chunk c of row r at position c ^ (r / 2) % 4.
 __device__ __forceinline__ uint32_t short_off(uint32_t row, uint32_t chunk) {
@@ -302,8 +306,9 @@ __device__ __forceinline__ uint32_t short_off(uint32_t row, uint32_t chunk) {
 
 template <int INSTR>
 __global__ __launch_bounds__(256) void kp_gemm_short(GemmArgs g) {
-  constexpr int SITE = INSTR, kMayCross = 0;
-  static_assert(SITE <= 3, "no chained sites");
+  constexpr int SITE = (INSTR == 2 || INSTR == 5) ? 6 : INSTR;
+  constexpr bool REALTIME = INSTR == 3 || INSTR == 5;
+  constexpr int kMayCross = 0;
   constexpr int BM = 64, BN = 64, BK = 32;
   __shared__ __align__(16) unsigned char sA[BM * BK * 2];
   __shared__ __align__(16) unsigned char sB[BN * BK * 2];
@@ -319,8 +324,9 @@ __global__ __launch_bounds__(256) void kp_gemm_short(GemmArgs g) {
     ring = kp::ring_init<true>(ring_lds, t_begin, g.cap_lds, g.region_mask, g.flush, g.cap_hbm, g.trace, g.n_wg, 4u >> g.group_log2, wg,
                          g.group_log2);
   ring.collab = g.collab;
-  if constexpr (INSTR == 3) kp::ring_use_realtime(ring);
-  kp::sites_begin<SITE>(ring);
+  if constexpr (REALTIME) kp::ring_use_realtime(ring);
+  if constexpr (SITE == 6) kp::chain_begin(ring, (uint32_t)(uintptr_t)ring_lds + (4u >> g.group_log2) * g.cap_lds * 8u);
+  else kp::sites_begin<SITE>(ring);
 
   // global -> register mapping
   // A: 64 rows x 4 chunks = 256 chunks, one per thread
@@ -343,7 +349,7 @@ __global__ __launch_bounds__(256) void kp_gemm_short(GemmArgs g) {
     for (int i = 0; i < 8; ++i)
       bv[i] = b_on ? *reinterpret_cast<const uint32_t*>(b_src + ((size_t)kt * BK + i) * g.N) : 0u;
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-    KP_SITE_K(ring, 0, 0, 1);
+    KP_SITE_K(ring, 1, 0, 1);
     // ---- region 1: LDS store -----------------------------------------------------------------
     __syncthreads();  // previous step's MFMA reads are done
     *reinterpret_cast<u32x4*>(sA + short_off(a_row, a_chunk)) = av;
@@ -357,7 +363,7 @@ __global__ __launch_bounds__(256) void kp_gemm_short(GemmArgs g) {
       *reinterpret_cast<u32x4*>(sB + short_off(b_np * 2 + 1, b_kg)) = hi;
     }
     __syncthreads();
-    KP_SITE_K(ring, 0, 1, 2);
+    KP_SITE_K(ring, 2, 1, 2);
     // ---- region 2: MFMA ------------------------------------------------------------------------
 #pragma unroll
     for (int ks = 0; ks < BK / 16; ++ks) {
@@ -368,6 +374,7 @@ __global__ __launch_bounds__(256) void kp_gemm_short(GemmArgs g) {
       acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(af, bf, acc, 0, 0, 0);
     }
     asm volatile("s_nop 0" ::: "memory");
+    KP_COMMIT(ring, 3);
   }
   KP_SITE_K(ring, 0, 2, kp::kNoRegion);
 
@@ -381,8 +388,13 @@ __global__ __launch_bounds__(256) void kp_gemm_short(GemmArgs g) {
   }
   if constexpr (INSTR != 0) {
     kp::TraceGeom tg{g.n_wg, 4u >> g.group_log2, 3, g.cap_hbm, g.flags};
-    kp::sites_end<SITE>(ring);
-    kp::ring_finish<INSTR == 3>(ring, g.cap_lds, g.trace, tg, wg, g.rec_cost);
+    if constexpr (SITE == 6) {
+      kp::chain_commit<1>(ring);  // the site that closed the last K step
+      kp::ring_finish<REALTIME>(ring, g.cap_lds, g.trace, tg, wg, g.rec_cost, SmallGemmChain{});
+    } else {
+      kp::sites_end<SITE>(ring);
+      kp::ring_finish<REALTIME>(ring, g.cap_lds, g.trace, tg, wg, g.rec_cost);
+    }
   }
 }
 
@@ -816,7 +828,7 @@ bool pick_shape(int M, int N, int K, GemmShape* s) {
 }
 
 // see kp_gemm_short
-bool short_k(int K, int n_wg) { return K <= 224 && n_wg >= 1024; }
+bool short_k(int K, int n_wg) { return K <= (n_wg >= 3072 ? 288 : n_wg >= 1024 ? 224 : n_wg > 768 ? 160 : n_wg > 256 ? 96 : 0); }
 
 template <int INSTR, int WAVES, int SCHEDULE>
 kp_status launch_big(const GemmArgs& g, int n_wg, size_t ring_bytes, hipStream_t st) {
@@ -904,23 +916,15 @@ extern "C" kp_status kp_gemm_instrumented(const void* A, const void* B, void* C,
   const size_t ring_bytes = (size_t)cap_lds * 8 * streams + (group_log2 ? 16 : 0);  // (16: see chain_begin)
   if (ring_bytes > 32 * 1024) return kp::fail(KP_ERR_UNSUPPORTED_SHAPE, "LDS ring of %zu bytes exceeds the 32 KiB budget", ring_bytes);
   g.cap_lds = cap_lds; g.cap_hbm = (uint32_t)cap_wave; g.rec_cost = kp::rec_cost();
-  if (!big && short_k(K, n_wg)) {  // every region, circular, a stream per wave: the lean sites
-    const bool lean = !flush && !group_log2 && !realtime && !collab && regions == 7u;
-    if (lean) hipLaunchKernelGGL(kp_gemm_short<2>, dim3(n_wg), dim3(256), ring_bytes, st, g);
-    else if (realtime) hipLaunchKernelGGL(kp_gemm_short<3>, dim3(n_wg), dim3(256), ring_bytes, st, g);
-    else hipLaunchKernelGGL(kp_gemm_short<1>, dim3(n_wg), dim3(256), ring_bytes, st, g);
-    KP_HIP_TRY(hipGetLastError());
-    return KP_OK;
-  }
-  // The other kernels chain their sites whenever the strategy is circular and one lane stores: the region mask,
-  // wave-group records and the constant-rate clock all keep that form.
+  // The sites are chained whenever the strategy is circular and one lane stores: the region mask, wave-group records
+  // and the constant-rate clock all keep that form.
   const bool chained = !flush && !collab;
   if (big) return chained ? (realtime ? launch_big_w<5>(phased, g, n_wg, ring_bytes, st) : launch_big_w<2>(phased, g, n_wg, ring_bytes, st))
                           : (realtime ? launch_big_w<3>(phased, g, n_wg, ring_bytes, st) : launch_big_w<1>(phased, g, n_wg, ring_bytes, st));
-  if (chained && realtime) hipLaunchKernelGGL(kp_gemm_small<5>, dim3(n_wg), dim3(256), ring_bytes, st, g);
-  else if (chained) hipLaunchKernelGGL(kp_gemm_small<2>, dim3(n_wg), dim3(256), ring_bytes, st, g);
-  else if (realtime) hipLaunchKernelGGL(kp_gemm_small<3>, dim3(n_wg), dim3(256), ring_bytes, st, g);
-  else hipLaunchKernelGGL(kp_gemm_small<1>, dim3(n_wg), dim3(256), ring_bytes, st, g);
+  const bool short_kernel = short_k(K, n_wg);
+  auto kern = chained ? (realtime ? (short_kernel ? kp_gemm_short<5> : kp_gemm_small<5>) : (short_kernel ? kp_gemm_short<2> : kp_gemm_small<2>))
+                      : (realtime ? (short_kernel ? kp_gemm_short<3> : kp_gemm_small<3>) : (short_kernel ? kp_gemm_short<1> : kp_gemm_small<1>));
+  hipLaunchKernelGGL(kern, dim3(n_wg), dim3(256), ring_bytes, st, g);
   KP_HIP_TRY(hipGetLastError());
   return KP_OK;
 }

@@ -341,6 +341,37 @@ def test_small_tile_many_workgroups_short_k(kp, M, N, K, opts):
     assert (rx[:, :, :n, 0] == ry[:, :, :n, 0]).all()
 
 
+@pytest.mark.parametrize("tiles,K", [((17, 15), 96), ((17, 16), 96), ((17, 16), 128), ((27, 29), 160), ((27, 29), 192), ((41, 25), 224), ((41, 25), 256), ((57, 54), 288)])
+@pytest.mark.parametrize("regions,opts", [(0b111, "0"), (0b101, "0"), (0b010, "group"), (0b110, "realtime"), (0b011, "collab")])
+def test_small_tile_record_sequence(kp, tiles, K, regions, opts):
+    """Records of the 64x64x32 tile on either side of its lines for a short K: the tags that the sequence of regions
+    gives, in a ring that wraps; C bit-identical with and without sites."""
+    M, N, cap = 64 * tiles[0], 64 * tiles[1], 16
+    a, b = inputs.gemm_inputs(M, N, K, seed=M + K)
+    c0, _, (n_wg, waves, _) = run_gemm(kp, a, b, 0)
+    assert (n_wg, waves) == (tiles[0] * tiles[1], 4)
+    A, B = a.cuda(), b.cuda()
+    streams = 1 if opts == "group" else 4
+    mask = regions | {"0": 0, "group": kp.KP_MASK_WAVE_GROUP, "realtime": kp.KP_MASK_REALTIME, "collab": kp.KP_MASK_COLLAB}[opts]
+    C = torch.empty(M, N, dtype=torch.bfloat16, device="cuda")
+    trace = torch.full((kp.kp_trace_bytes(n_wg, streams, cap * streams),), 0x77, dtype=torch.uint8, device="cuda")
+    kp.kp_gemm_instrumented(A, B, C, M, N, K, mask, trace, cap * streams)
+    torch.cuda.synchronize()
+    assert torch.equal(C.view(torch.int16), c0.view(torch.int16))
+    hdr, rec = _streams_of(trace.cpu().numpy().view(np.uint32).copy(), n_wg, streams, cap)
+    kinds = [(r, phase) for _ in range(K // 32) for r in range(3) if regions >> r & 1 for phase in (0, 1)]
+    want = np.zeros((streams, cap), dtype=np.uint32)
+    for w in range(streams):
+        for seq, (r, phase) in enumerate(kinds):
+            want[w, seq % cap] = phase << 31 | r << 24 | w << 20 | seq
+    n = min(len(kinds), cap)
+    assert (hdr[:, 8:8 + streams] == len(kinds)).all()
+    assert (rec[:, :, :n, 0] == want[None, :, :n]).all()
+    order = np.argsort(rec[:, :, :n, 0] & 0xFFFFF, axis=2)
+    ts = np.take_along_axis(rec[:, :, :n, 1], order, 2).astype(np.int64)
+    assert (np.diff(ts, axis=2) >= 0).all() and (ts > 0).all()
+
+
 def _streams_of(raw, n_wg, streams, cap):
     hdr = raw[16:16 + 32 * n_wg].reshape(n_wg, 32)
     return hdr, raw[16 + 32 * n_wg:].reshape(n_wg, streams, cap, 2)

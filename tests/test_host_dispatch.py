@@ -1,4 +1,6 @@
 """Which kernels a call launches, and which geometries it takes, on devices of several sizes (no GPU needed)."""
+import pytest
+
 from tests import fake_hip
 
 
@@ -51,3 +53,18 @@ def test_wait_header_counts_are_made_once(tmp_path):
         added = regions <= 20 and (grid <= 128 or regions in (1, 6, 7))
         assert [x[1:3] for x in head] == ([] if added else [(1, 192)]), (call, launches)
         assert not head or launches[-1] == head[0]
+
+
+@pytest.mark.parametrize("tiles,k_max", [((17, 15), 0), ((257, 1), 96), ((256, 3), 96), ((769, 1), 160), ((33, 31), 160), ((41, 25), 224), ((3071, 1), 224), ((63, 62), 288)])
+def test_short_k_gemm_has_one_line_for_every_way_of_recording(tmp_path, tiles, k_max):
+    """Which 64x64x32 kernel a shape takes does not depend on what is recorded, so that a recorded kernel and the one
+    without sites are the same; circular records of one lane keep the chained sites in both."""
+    kernel = {0: 0, 7: 2, 5: 2, 7 | 1 << 30: 2, 7 | 1 << 28: 5, 7 | 1 << 31: 1, 7 | 1 << 27: 1, 7 | 1 << 27 | 1 << 28: 3}
+    calls = [{"fn": "kp_gemm_instrumented", "args": (64 * tiles[0], 64 * tiles[1], k, mask, 256)}
+             for k in (32, 96, 128, 160, 192, 224, 256, 288, 320, 4128) for mask in kernel]
+    for call, (status, launches) in zip(calls, fake_hip.run(calls, tmp_path)):
+        assert status == 0, call
+        k, mask = call["args"][2:4]
+        name = "kp_gemm_short" if k <= k_max else "kp_gemm_small"
+        assert len(launches) == 1 and f"{name}ILi{kernel[mask]}E" in launches[0][0], (call, launches)
+        assert launches[0][1] == tiles[0] * tiles[1]
