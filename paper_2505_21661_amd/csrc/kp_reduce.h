@@ -2,6 +2,7 @@
 // layout of the statistics block and the hand-over between them.
 #pragma once
 #include "kp_common.h"
+#include "kp_wave.h"
 
 namespace kp_reduce {
 
@@ -24,28 +25,7 @@ __host__ __device__ inline StatsLayout stats_layout(uint32_t n_wg, uint32_t W, u
   return l;
 }
 
-// Lane l receives the value of lane l-1; lane 0 receives `lane0` (DPP wave shift right by one).
-__device__ __forceinline__ uint32_t wave_shr1(uint32_t v, uint32_t lane0) {
-  return (uint32_t)__builtin_amdgcn_update_dpp((int)lane0, (int)v, 0x138, 0xF, 0xF, false);
-}
-
-// The DPP steps of an inclusive scan over the 64 lanes: four shifts inside each row of 16, then the
-// last lane of row 0/2 into row 1/3 and the last lane of the lower half into the upper half.  Lanes
-// without a source read 0.
-template <int STEP> __device__ __forceinline__ uint32_t scan_src(uint32_t v) {
-  if (STEP == 0) return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x111, 0xF, 0xF, false);  // row_shr:1
-  if (STEP == 1) return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x112, 0xF, 0xF, false);  // row_shr:2
-  if (STEP == 2) return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x114, 0xF, 0xF, false);  // row_shr:4
-  if (STEP == 3) return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x118, 0xF, 0xF, false);  // row_shr:8
-  if (STEP == 4) return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x142, 0xA, 0xF, false);  // row_bcast:15
-  return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x143, 0xC, 0xF, false);                 // row_bcast:31
-}
-
-__device__ __forceinline__ uint32_t wave_scan_add(uint32_t v) {
-  v += scan_src<0>(v); v += scan_src<1>(v); v += scan_src<2>(v);
-  v += scan_src<3>(v); v += scan_src<4>(v); v += scan_src<5>(v);
-  return v;
-}
+using namespace kp_wave;
 
 // Batcher's odd-even merge sort of N registers: a fixed network (63 exchanges for 16 words, 384 for 48),
 // every index known at compile time.

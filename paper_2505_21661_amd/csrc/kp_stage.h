@@ -9,8 +9,11 @@
 // counting the occupied ranks and repaired by a serial pass.
 #pragma once
 #include "kp_common.h"
+#include "kp_wave.h"
 
 namespace kp_stage {
+
+using namespace kp_wave;
 
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
@@ -45,11 +48,6 @@ __device__ inline uint32_t wave_sum(uint32_t v) {
 #pragma unroll
   for (int d = 32; d >= 1; d >>= 1) v += __shfl_xor(v, d, 64);
   return v;
-}
-
-// Lane l receives the value of lane l-1; lane 0 receives `lane0` (DPP wave shift right by one).
-__device__ __forceinline__ uint32_t wave_shr1(uint32_t v, uint32_t lane0) {
-  return (uint32_t)__builtin_amdgcn_update_dpp((int)lane0, (int)v, 0x138, 0xF, 0xF, false);
 }
 
 // The metadata tag of the records staged in pass `iter` of a persistent workgroup.  A staged word

@@ -1,0 +1,31 @@
+// Exchanges between the 64 lanes of a wave by data-parallel primitives (no LDS round trip); every lane is active.
+#pragma once
+#include <hip/hip_runtime.h>
+#include <stdint.h>
+
+namespace kp_wave {
+
+// Lane l receives the value of lane l-1; lane 0 receives `lane0` (DPP wave shift right by one).
+__device__ __forceinline__ uint32_t wave_shr1(uint32_t v, uint32_t lane0) {
+  return (uint32_t)__builtin_amdgcn_update_dpp((int)lane0, (int)v, 0x138, 0xF, 0xF, false);
+}
+
+// The DPP steps of an inclusive scan over the 64 lanes: four shifts inside each row of 16, then the
+// last lane of row 0/2 into row 1/3 and the last lane of the lower half into the upper half.  Lanes
+// without a source read 0.
+template <int STEP> __device__ __forceinline__ uint32_t scan_src(uint32_t v) {
+  if (STEP == 0) return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x111, 0xF, 0xF, false);  // row_shr:1
+  if (STEP == 1) return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x112, 0xF, 0xF, false);  // row_shr:2
+  if (STEP == 2) return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x114, 0xF, 0xF, false);  // row_shr:4
+  if (STEP == 3) return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x118, 0xF, 0xF, false);  // row_shr:8
+  if (STEP == 4) return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x142, 0xA, 0xF, false);  // row_bcast:15
+  return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x143, 0xC, 0xF, false);                 // row_bcast:31
+}
+
+__device__ __forceinline__ uint32_t wave_scan_add(uint32_t v) {
+  v += scan_src<0>(v); v += scan_src<1>(v); v += scan_src<2>(v);
+  v += scan_src<3>(v); v += scan_src<4>(v); v += scan_src<5>(v);
+  return v;
+}
+
+}  // namespace kp_wave
