@@ -21,11 +21,17 @@
 //      rounds instead of a walk of up to n steps;
 //   4  marked stages add their latency to their region's totals, and the gaps to the stage before them
 //      to the workgroup's bubbles.
-// Bound by LDS round trips between barriers.  16384 workgroups of 16 regions x 64 iterations: 0.49 ms with the
-// network alone, every stage searching all ends twice, 0.20 ms with the cells.
+// Bound by LDS round trips between barriers.  8192 workgroups of 16 regions x 64 iterations one after the other: 223 us
+// with the network alone, every stage searching all ends twice; 154 us with the cells; 138 us with the sums over a wave
+// by data-parallel primitives instead of LDS exchanges and without them in waves that hold no stage of the path.
+#include <math.h>
+
 #include "kp_common.h"
+#include "kp_wave.h"
 
 namespace {
+
+using namespace kp_wave;
 
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
@@ -48,25 +54,9 @@ __global__ void kp_critical_init(unsigned long long* out, uint32_t n_wg, uint32_
   for (uint32_t i = threadIdx.x; i < 8 + 2 * R; i += blockDim.x) out[i] = i == 0 ? n_wg : (i == 1 ? R : (i == 2 ? I : 0ull));
 }
 
-__device__ inline unsigned long long wave_sum64(unsigned long long v) {
-#pragma unroll
-  for (int d = 32; d >= 1; d >>= 1) v += __shfl_xor(v, d, 64);
-  return v;
-}
-__device__ inline uint32_t wave_sum32(uint32_t v) {
-#pragma unroll
-  for (int d = 32; d >= 1; d >>= 1) v += __shfl_xor(v, d, 64);
-  return v;
-}
-__device__ inline uint32_t wave_min32(uint32_t v) {
-#pragma unroll
-  for (int d = 32; d >= 1; d >>= 1) { const uint32_t o = __shfl_xor(v, d, 64); v = o < v ? o : v; }
-  return v;
-}
-__device__ inline uint32_t wave_scan32(uint32_t v, uint32_t lane) {  // inclusive
-#pragma unroll
-  for (int d = 1; d < 64; d <<= 1) { const uint32_t o = __shfl_up(v, d, 64); v += lane >= (uint32_t)d ? o : 0u; }
-  return v;
+// The sum over the wave of values below 2^36.
+__device__ __forceinline__ unsigned long long wave_total36(unsigned long long v) {
+  return ((unsigned long long)wave_total((uint32_t)(v >> 16)) << 16) + wave_total((uint32_t)v & 0xFFFFu);
 }
 
 // LDS: key[P] u64 | start[P] | lat[P] | jump[2][P] (the first one: cells, until the links are known) | mark[P]
@@ -84,11 +74,11 @@ __global__ __launch_bounds__(kBlock, PER <= 4 ? 6 : 1) void kp_critical_main(Cri
   unsigned long long* reg_tot = reinterpret_cast<unsigned long long*>(smem + 25 * (size_t)P);  // [R][2], 8-byte aligned: P >= 64
   unsigned long long* wg_tot = reg_tot + 2 * R;   // stages, latency, bubbles
   // [0] min start on the path, [1] first end, [2] last end, [3] a cell is too full, [4] a region's keys are
-  // out of order, [8..11] stages in the cells of each hardware wave
+  // out of order, [8..11] stages in the cells of each hardware wave, [12..15] stages of each hardware wave
   uint32_t* wg_small = reinterpret_cast<uint32_t*>(wg_tot + 3);
-  unsigned long long* all_tot = reinterpret_cast<unsigned long long*>(wg_small + 12);  // paths, stages, latency, bubbles
+  unsigned long long* all_tot = reinterpret_cast<unsigned long long*>(wg_small + 16);  // paths, stages, latency, bubbles
 
-  const uint32_t tid = threadIdx.x, lane = tid & 63u, hw = tid >> 6;
+  const uint32_t tid = threadIdx.x, lane = tid & 63u, hw = (uint32_t)__builtin_amdgcn_readfirstlane((int)(tid >> 6));
   for (uint32_t i = tid; i < 2 * R; i += kBlock) reg_tot[i] = 0ull;
   if (tid < 4) all_tot[tid] = 0ull;
 
@@ -121,8 +111,8 @@ __global__ __launch_bounds__(kBlock, PER <= 4 ? 6 : 1) void kp_critical_main(Cri
       if (i < P) { start[i] = entry[u].y; lat[i] = entry[u].x; cells[i] = 0u; mark[i] = 0; }
     }
     if (wg + gridDim.x < p.n_wg) fetch(wg + gridDim.x);
-    first_end = wave_min32(first_end);
-    last_end = ~wave_min32(~last_end);
+    first_end = wave_least(first_end);
+    last_end = ~wave_least(~last_end);
     __syncthreads();
     if (lane == 0 && first_end <= last_end) {  // the wave has a stage
       atomicMin(&wg_small[1], first_end);
@@ -141,24 +131,37 @@ __global__ __launch_bounds__(kBlock, PER <= 4 ? 6 : 1) void kp_critical_main(Cri
     auto key_of = [&](int u) { return ((unsigned long long)end[u] << 32) | (tid + kBlock * u); };
     uint32_t at[PER];  // arrival number in the cell, then the place in the order
     bool full = false;
+    uint32_t n_wave = 0;  // stages of the hardware wave
 #pragma unroll
     for (int u = 0; u < PER; ++u) {
       at[u] = 0;
-      if (live >> u & 1u) { at[u] = atomicAdd(&cells[cell_of(end[u])], 1u); full = full || at[u] >= kMaxCell; }
+      const bool is = (live >> u & 1u) != 0u;
+      const uint64_t here = __builtin_amdgcn_ballot_w64(is);
+      if (here == 0ull) continue;  // (uniform)
+      n_wave += (uint32_t)__popcll(here);
+      const uint32_t c = cell_of(end[u]), some = (uint32_t)__builtin_amdgcn_readlane((int)c, (int)__builtin_ctzll(here));
+      // (a cell that these stages alone fill: their atomics on one word would be done one after the other)
+      full = full || __popcll(__builtin_amdgcn_ballot_w64(is && c == some)) > (int)kMaxCell;
+      if (is && !full) { at[u] = atomicAdd(&cells[c], 1u); full = at[u] >= kMaxCell; }
+      full = __builtin_amdgcn_ballot_w64(full) != 0ull;
     }
-    if (__builtin_amdgcn_ballot_w64(full) != 0ull && lane == 0) wg_small[3] = 1u;
+    if (lane == 0) {
+      wg_small[12 + hw] = n_wave;
+      if (full) wg_small[3] = 1u;
+    }
     __syncthreads();
-    uint32_t mine[PER], sum = 0;
-#pragma unroll
-    for (int j = 0; j < PER; ++j) { mine[j] = tid * PER < P ? cells[tid * PER + j] : 0u; sum += mine[j]; }
-    const uint32_t upto = wave_scan32(sum, lane);
-    if (lane == 63u) wg_small[8 + hw] = upto;
-    __syncthreads();
-    uint32_t at_cell = upto - sum, n = 0;
-#pragma unroll
-    for (uint32_t h = 0; h < kBlock / 64; ++h) { const uint32_t c = wg_small[8 + h]; at_cell += h < hw ? c : 0u; n += c; }
+    const uint32_t n = wg_small[12] + wg_small[13] + wg_small[14] + wg_small[15];
     const bool by_cell = wg_small[3] == 0u;
     if (by_cell) {
+      uint32_t mine[PER], sum = 0;
+#pragma unroll
+      for (int j = 0; j < PER; ++j) { mine[j] = tid * PER < P ? cells[tid * PER + j] : 0u; sum += mine[j]; }
+      const uint32_t upto = wave_scan_add(sum);
+      if (lane == 63u) wg_small[8 + hw] = upto;
+      __syncthreads();
+      uint32_t at_cell = upto - sum;
+#pragma unroll
+      for (uint32_t h = 0; h < kBlock / 64; ++h) at_cell += h < hw ? wg_small[8 + h] : 0u;
       if (tid * PER < P) {
 #pragma unroll
         for (int j = 0; j < PER; ++j) { cells[tid * PER + j] = at_cell; at_cell += mine[j]; }
@@ -174,8 +177,15 @@ __global__ __launch_bounds__(kBlock, PER <= 4 ? 6 : 1) void kp_critical_main(Cri
         const uint32_t c = cell_of(end[u]), lo = cells[c], hi = c + 1u < P ? cells[c + 1u] : n;
         const unsigned long long k = key_of(u);
         at[u] = lo;
-        if (hi - lo > 1u)
-          for (uint32_t m = lo; m < hi; ++m) at[u] += key[m] < k ? 1u : 0u;
+        if (hi - lo > 1u) {
+          for (uint32_t m = lo; m < hi; m += 2u) {  // (two reads in flight; four gain nothing and take the registers of a workgroup per CU)
+            unsigned long long other[2];
+#pragma unroll
+            for (uint32_t x = 0; x < 2u; ++x) other[x] = key[m + x < hi ? m + x : hi - 1u];
+#pragma unroll
+            for (uint32_t x = 0; x < 2u; ++x) at[u] += m + x < hi && other[x] < k ? 1u : 0u;
+          }
+        }
       }
       __syncthreads();
 #pragma unroll
@@ -286,7 +296,9 @@ __global__ __launch_bounds__(kBlock, PER <= 4 ? 6 : 1) void kp_critical_main(Cri
       atomicAdd(&reg_tot[2 * region], 1ull);
       atomicAdd(&reg_tot[2 * region + 1], (unsigned long long)l);
     }
-    my_n = wave_sum32(my_n); my_lat = wave_sum64(my_lat); my_bub = wave_sum64(my_bub); my_first = wave_min32(my_first);
+    if (__builtin_amdgcn_ballot_w64(my_n != 0u) != 0ull) {
+      my_n = wave_total(my_n); my_lat = wave_total36(my_lat); my_bub = wave_total36(my_bub); my_first = wave_least(my_first);
+    }
     if (lane == 0 && my_n) {
       atomicAdd(&wg_tot[0], (unsigned long long)my_n);
       atomicAdd(&wg_tot[1], my_lat);
@@ -318,9 +330,24 @@ __global__ __launch_bounds__(kBlock, PER <= 4 ? 6 : 1) void kp_critical_main(Cri
 
 struct LaunchCache { int dev = -1; uint32_t lds = 0; uint32_t max_grid = 0; };
 
+// Every decoder workgroup adds its totals to the same few lines at its end, one after the other: 0.02 us each.  A
+// recorded workgroup takes one of them 3.5 us and as long again for some 400 stages, twice that and more in the network:
+// `times` as long as such an add.  With g decoder workgroups the sum of both is g + times * (n_wg / g), least at the root
+// of n_wg * times, or next to it where every one of them has the same number.  All that are resident / so many: 2048
+// workgroups of 64 stages 32.4 / 23.3 us (1024 of 2048), of 128 52.1 / 31.9.
+inline uint32_t most_workgroups(uint32_t n_wg, uint32_t P) {
+  const double times = 450.0 + P;
+  const uint32_t turns = (uint32_t)sqrt((double)n_wg / times);
+  auto cost = [&](uint32_t t) { return (double)n_wg / t + times * t; };
+  const uint32_t t = turns < 1u ? 1u : (cost(turns + 1u) < cost(turns) ? turns + 1u : turns);
+  return (n_wg + t - 1u) / t;
+}
+// Eight per CU take all its wave slots: 32768 workgroups of 64 stages 146 us, with seven 102, with six 111.
+constexpr int kMaxPerCu = 7;
+
 template <int PER>
 kp_status launch(const CriticalParams& p, hipStream_t s) {
-  const uint32_t lds = 25u * p.P + 16u * p.R + 24u + 48u + 32u;
+  const uint32_t lds = 25u * p.P + 16u * p.R + 24u + 64u + 32u;
   static thread_local LaunchCache cache;
   int dev = 0;
   KP_HIP_TRY(hipGetDevice(&dev));
@@ -331,9 +358,10 @@ kp_status launch(const CriticalParams& p, hipStream_t s) {
     KP_HIP_TRY(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kp_critical_main<PER>, kBlock, lds));
     if (per_cu < 1) return kp::fail(KP_ERR_UNSUPPORTED_SHAPE, "critical-path kernel does not fit one CU (LDS %u B)", lds);
     KP_HIP_TRY(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev));
-    cache.dev = dev; cache.lds = lds; cache.max_grid = (uint32_t)per_cu * (uint32_t)cus;
+    cache.dev = dev; cache.lds = lds; cache.max_grid = (uint32_t)(per_cu < kMaxPerCu ? per_cu : kMaxPerCu) * (uint32_t)cus;
   }
-  const uint32_t grid = cache.max_grid < p.n_wg ? cache.max_grid : p.n_wg;
+  const uint32_t most = most_workgroups(p.n_wg, p.P);
+  const uint32_t grid = cache.max_grid < most ? cache.max_grid : most;
   hipLaunchKernelGGL(kp_critical_main<PER>, dim3(grid), dim3(kBlock), lds, s, p);
   KP_HIP_TRY(hipGetLastError());
   return KP_OK;

@@ -50,6 +50,9 @@ def _child(fake_path, lib_path):
             m, n, k, mask, cap = call["args"]
             status = lib.kp_gemm_instrumented(p(BUFFER), p(BUFFER), p(BUFFER), m, n, k, ctypes.c_uint32(mask), p(BUFFER),
                                               ctypes.c_size_t(cap), None)
+        elif call["fn"] == "kp_stages_critical":
+            n_wg, regions, iterations = call["args"]
+            status = lib.kp_stages_critical(p(BUFFER), n_wg, regions, iterations, p(BUFFER), None)
         else:
             raise ValueError(call["fn"])
         launches = []

@@ -68,3 +68,22 @@ def test_short_k_gemm_has_one_line_for_every_way_of_recording(tmp_path, tiles, k
         name = "kp_gemm_short" if k <= k_max else "kp_gemm_small"
         assert len(launches) == 1 and f"{name}ILi{kernel[mask]}E" in launches[0][0], (call, launches)
         assert launches[0][1] == tiles[0] * tiles[1]
+
+
+@pytest.mark.parametrize("device", [(0, 256, 8), (1, 256, 6), (2, 32, 8)])
+def test_critical_path_workgroups_are_bounded_by_their_totals(tmp_path, device):
+    """Never more decoder workgroups than recorded ones or than seven per CU, all of them where few are recorded, and
+    otherwise a number near the root of the recorded ones that gives each as many of them as the others."""
+    shapes = [(n_wg, r, i) for n_wg in (1, 2, 450, 513, 1024, 1025, 2048, 5000, 65536) for r, i in ((1, 1), (1, 64), (5, 13), (16, 64), (128, 32))]
+    calls = [{"fn": "kp_stages_critical", "args": s, "device": device} for s in shapes]
+    for (n_wg, r, i), (status, launches) in zip(shapes, fake_hip.run(calls, tmp_path)):
+        assert status == 0 and "kp_critical_main" in launches[-1][0], (n_wg, r, i, launches)
+        places = 64
+        while places < r * i:
+            places *= 2
+        grid, resident = launches[-1][1], min(7, device[2]) * device[1]
+        root = (n_wg * (450 + places)) ** 0.5
+        assert 1 <= grid <= min(n_wg, resident)
+        assert grid == min(n_wg, resident) or (n_wg > 450 + places and root / 2 <= grid <= 2 * root)
+        turns = -(-n_wg // grid)
+        assert grid == resident or grid == -(-n_wg // turns)
