@@ -141,21 +141,28 @@ def _ptr(t) -> int:
     return t.data_ptr()
 
 
-_current_raw_stream = None  # torch's (device index) -> hipStream_t lookup and its current-device lookup
+_current_stream = None  # () -> hipStream_t of torch's current stream
+
+
+def _stream_lookup():
+    import torch
+
+    raw = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+    if raw is None:  # (not part of torch's public interface)
+        return lambda: torch.cuda.current_stream().cuda_stream
+    torch.cuda.init()
+    device = torch.cuda.current_device
+    return lambda: raw(device())
 
 
 def _stream(stream) -> int:
-    global _current_raw_stream
+    global _current_stream
     if stream is None:
         # The handle itself: building a torch.cuda.Stream object around it took 2.8 of the 6.9 us that a call
         # spent on the host, which is what the smallest calls are bound by (0.2 us this way).
-        if _current_raw_stream is None:
-            import torch
-
-            torch.cuda.init()
-            _current_raw_stream = (torch._C._cuda_getCurrentRawStream, torch.cuda.current_device)
-        raw, device = _current_raw_stream
-        return raw(device())
+        if _current_stream is None:
+            _current_stream = _stream_lookup()
+        return _current_stream()
     if isinstance(stream, int):
         return stream
     return stream.cuda_stream

@@ -1,4 +1,4 @@
-"""Properties of the device code in libkperf.so, from the metadata that the compiler leaves in it (no GPU needed)."""
+"""Properties of the built device code, from the metadata that the compiler leaves in libkperf.so, and of the binding, both without a GPU."""
 import os
 import re
 import subprocess
@@ -36,3 +36,24 @@ def test_replay_kernels_hold_their_state_in_registers(tmp_path):
     found = {k: v for k, v in kernels(tmp_path).items() if "kp_waits_main" in k or "kp_pairs_main" in k}
     assert len(found) == 10, found
     assert not any(found.values()), found
+
+
+@pytest.mark.parametrize("raw_lookup", [True, False])
+def test_a_call_without_a_stream_takes_torchs_current_one(monkeypatch, raw_lookup):
+    """With torch's lookup of the bare handle, and by its public interface where a torch does not have that."""
+    torch = pytest.importorskip("torch")
+    from paper_2505_21661_amd import binding
+
+    class Stream:
+        cuda_stream = 0x5000
+
+    monkeypatch.setattr(torch.cuda, "init", lambda: None)
+    monkeypatch.setattr(torch.cuda, "current_device", lambda: 3)
+    monkeypatch.setattr(torch.cuda, "current_stream", lambda: Stream)
+    monkeypatch.setattr(torch._C, "_cuda_getCurrentRawStream", lambda device: 0x4000 + device, raising=False)
+    if not raw_lookup:
+        monkeypatch.delattr(torch._C, "_cuda_getCurrentRawStream")
+    monkeypatch.setattr(binding, "_current_stream", None, raising=False)
+    assert binding._stream(None) == (0x4003 if raw_lookup else 0x5000)
+    assert binding._stream(None) == (0x4003 if raw_lookup else 0x5000)
+    assert binding._stream(7) == 7 and binding._stream(Stream) == 0x5000
