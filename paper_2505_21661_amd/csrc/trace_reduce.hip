@@ -56,7 +56,7 @@ enum { kStepOrdered = 1, kStepPaired, kStepCounted, kStepCellSums, kStepPlaced, 
 
 // per-workgroup temporaries (u32 words in LDS)
 enum { T_INVALID = 0, T_FIELDVALID, T_DISORDER, T_OCCUPIED, T_NONMONO, T_PAIRS, T_STARTS, T_ENDS,
-       T_EVENTS, T_MARKS, T_WIDE, T_MAXCELL, T_HELD, T_COUNT };  // T_HELD stays last
+       T_EVENTS, T_MARKS, T_WIDE, T_MAXCELL, T_ZERO, T_HELD, T_COUNT };  // T_HELD stays last
 
 struct DecodeParams {
   const uint32_t* wg_hdrs;  // 32 words per recorded workgroup
@@ -525,7 +525,9 @@ __global__ __launch_bounds__(BLOCK) void kp_reduce_main(DecodeParams p) {
     // four copies, one per quarter of the wave: lanes 16 apart tend to hold the same region, and LDS
     // atomics of one instruction that hit one address are processed one after the other.
     const uint32_t copy = (lane >> 4) & (n_copies - 1u);
+    uint32_t shortest = 0xFFFFFFFFu;
     auto account_pair = [&](uint32_t w, uint32_t region, uint32_t d_raw) {
+      shortest = d_raw < shortest ? d_raw : shortest;
       const uint32_t d = d_raw > rec_cost ? d_raw - rec_cost : 0u;
       const uint32_t e = __umul24(__umul24(w, R) + region, n_copies) + copy;
       atomicAdd(&pw_pack[e], (1ull << 46) | (unsigned long long)d);
@@ -625,9 +627,10 @@ __global__ __launch_bounds__(BLOCK) void kp_reduce_main(DecodeParams p) {
         n_pairs += __popc(mq[x] & (mq[x] << 1) & 0x80808080u);
       }
       n_pairs = wave_scan_add(n_ends | (n_pairs << 16));  // both at most 1024 per wave
-      const bool any_marked = __builtin_amdgcn_ballot_w64(marked) != 0;
+      const bool any_marked = __builtin_amdgcn_ballot_w64(marked) != 0, any_zero = __builtin_amdgcn_ballot_w64(shortest == 0u) != 0;
       if (lane == 0u) {
         if (any_marked) tmp[T_MARKS] = 1u;
+        if (any_zero) tmp[T_ZERO] = 1u;
         if (n_nonmono) atomicAdd(&tmp[T_NONMONO], n_nonmono);
       }
       if (lane == 63u) {
@@ -685,6 +688,21 @@ __global__ __launch_bounds__(BLOCK) void kp_reduce_main(DecodeParams p) {
 #pragma unroll
         for (int j = 0; j < kNR / 2; ++j)
           mq[j >> 1] |= ((uint32_t)*reinterpret_cast<const uint16_t*>(meta + qe + 128u * j) & 0x4040u) << (16 * (j & 1));
+      }
+      // A pair of length 0 overlaps nothing, and records of one clock come out of the counting sort in any order: its END
+      // could open the region, in the general sweep, to every record of the same clock until its START.  Neither is an
+      // event.  (The record a START is paired with is the next one of its region.)
+      if (tmp[T_ZERO]) {
+#pragma unroll
+        for (int i = 0; i < kNR; ++i) {
+          const uint32_t m = meta_of(i);
+          if (m & kPaired) {
+            const uint32_t step = m & kEnd ? ~0u : 1u;
+            uint32_t q = qe + 128u * (i >> 1) + (i & 1) + step;
+            while (((meta[q] ^ m) & kRegion) != 0u) q += step;
+            if (clk[clk_word(q)] == t[i]) mq[i >> 2] ^= kPaired << (8 * (i & 3));
+          }
+        }
       }
       const uint32_t scale = misc[1];
       // Straight-line code from here to the sorted sequence: the LDS operations of a lane's 16 records

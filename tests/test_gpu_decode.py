@@ -225,3 +225,27 @@ def test_sequence_numbers_that_wrap(kp, oracle_mod):
     recs[:, 0] = (recs[:, 0] & 0xFFF00000) | ((recs[:, 0] + shift) & 0xFFFFF)
     check(raw, oracle_mod)
     check(raw, oracle_mod, use_hdr=True)
+
+
+@pytest.mark.parametrize("W,R,cap", [(12, 32, 256), (8, 16, 512), (4, 3, 128), (2, 17, 64), (16, 20, 1024), (8, 5, 2048), (8, 40, 256)])
+def test_records_of_one_clock(kp, oracle_mod, W, R, cap):
+    """Few clocks, pairs of length 0 and regions inside regions: the records of one clock come in any order out of the
+    counting sort, and the region-pair sums must not depend on it."""
+    rng = np.random.default_rng(R)
+    wgs = []
+    for _ in range(20):
+        waves = []
+        for _w in range(W):
+            wave, t = [], 0
+            while len(wave) < cap - 6:
+                t += int(rng.choice([0, 0, 0, 300]))
+                order = [int(x) for x in rng.permutation(R)[:3]]
+                for phase, regions in ((S, order), (E, order[::-1])):
+                    for r in regions:
+                        wave.append((phase, r, t))
+                        t += int(rng.choice([0, 0, 0, 0, 7]))
+            waves.append(wave)
+        wgs.append(inputs.events_to_wg(waves, cap, flush=False))
+    raw = inputs.encode_trace(wgs, W, R, cap, rec_cost=0)
+    for _ in range(3):
+        check(raw, oracle_mod, use_hdr=True)
