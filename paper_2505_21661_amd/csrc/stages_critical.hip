@@ -73,7 +73,7 @@ __global__ __launch_bounds__(kBlock, PER <= 4 ? 6 : 1) void kp_critical_main(Cri
   uint8_t* mark = reinterpret_cast<uint8_t*>(jump1 + P);
   unsigned long long* reg_tot = reinterpret_cast<unsigned long long*>(smem + 25 * (size_t)P);  // [R][2], 8-byte aligned: P >= 64
   unsigned long long* wg_tot = reg_tot + 2 * R;   // stages, latency, bubbles
-  // [0] min start on the path, [1] first end, [2] last end, [3] a cell is too full, [4] a region's keys are
+  // [0] start of the first stage of the path, [1] first end, [2] last end, [3] a cell is too full, [4] a region's keys are
   // out of order, [8..11] stages in the cells of each hardware wave, [12..15] stages of each hardware wave
   uint32_t* wg_small = reinterpret_cast<uint32_t*>(wg_tot + 3);
   unsigned long long* all_tot = reinterpret_cast<unsigned long long*>(wg_small + 16);  // paths, stages, latency, bubbles
@@ -281,7 +281,7 @@ __global__ __launch_bounds__(kBlock, PER <= 4 ? 6 : 1) void kp_critical_main(Cri
     }
     __syncthreads();
     // ---- 4: totals ---------------------------------------------------------------------------------
-    uint32_t my_n = 0, my_first = 0xFFFFFFFFu;
+    uint32_t my_n = 0;
     unsigned long long my_lat = 0, my_bub = 0;
 #pragma unroll
     for (int u = 0; u < PER; ++u) {
@@ -290,20 +290,19 @@ __global__ __launch_bounds__(kBlock, PER <= 4 ? 6 : 1) void kp_critical_main(Cri
       const uint32_t idx = (uint32_t)key[r];
       const uint32_t s = start[idx], l = lat[idx];
       if (pred[u] != kNone) my_bub += s - (uint32_t)(key[pred[u]] >> 32);
+      else wg_small[0] = s;  // the first stage of the path
       ++my_n; my_lat += l;
-      my_first = s < my_first ? s : my_first;
       const uint32_t region = idx / I;
       atomicAdd(&reg_tot[2 * region], 1ull);
       atomicAdd(&reg_tot[2 * region + 1], (unsigned long long)l);
     }
     if (__builtin_amdgcn_ballot_w64(my_n != 0u) != 0ull) {
-      my_n = wave_total(my_n); my_lat = wave_total36(my_lat); my_bub = wave_total36(my_bub); my_first = wave_least(my_first);
+      my_n = wave_total(my_n); my_lat = wave_total36(my_lat); my_bub = wave_total36(my_bub);
     }
     if (lane == 0 && my_n) {
       atomicAdd(&wg_tot[0], (unsigned long long)my_n);
       atomicAdd(&wg_tot[1], my_lat);
       atomicAdd(&wg_tot[2], my_bub);
-      atomicMin(&wg_small[0], my_first);
     }
     __syncthreads();
     if (tid == 0) {

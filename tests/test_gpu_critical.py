@@ -173,3 +173,14 @@ def test_stages_that_end_close_together(kp, oracle_mod, R, I, crowd):
             row["max_end"] = rng.permutation(end)
             row["min_start"] = row["max_end"] - np.minimum(row["max_end"], rng.integers(0, 300, size=n).astype(np.uint32))
     check(kp, oracle_mod, oracle_mod.stage_block(tab), 5, R, I)
+
+
+def test_first_stage_of_a_path_that_starts_late(kp, oracle_mod):
+    """Stages that end before they start, as clocks that go back leave them: the path's first stage is the one that
+    waited for none, not the one with the smallest start."""
+    n_wg, R, I = 30, 5, 40
+    tab = random_table(oracle_mod, 9, n_wg, R, I, t_max=6000)
+    rng = np.random.default_rng(9)
+    back = (rng.random((n_wg, R, I)) < 0.1) & (tab["n_waves"] > 0)
+    tab["max_end"] = np.where(back, tab["min_start"] // 3, tab["max_end"])
+    check(kp, oracle_mod, oracle_mod.stage_block(tab), n_wg, R, I)
