@@ -223,10 +223,10 @@ inline int block_threads(uint32_t W, uint32_t nrec) {
   return (W > 8 || nrec >= 8192) ? 1024 : ((W > 4 || nrec >= 2048) ? 512 : 256);
 }
 
-// Grid of a persistent kernel: as many workgroups as stay resident, at most one per recorded workgroup.
+// Grid of a persistent kernel: as many workgroups as stay resident, and not more than `most_per_cu` of them.
 struct LaunchCache { int dev = -1; uint32_t lds = 0; uint32_t max_grid = 0; };
 template <typename Kernel>
-kp_status resident_grid(Kernel kern, int block, uint32_t lds_bytes, LaunchCache* cache, uint32_t* grid) {
+kp_status resident_grid(Kernel kern, int block, uint32_t lds_bytes, LaunchCache* cache, uint32_t* grid, int most_per_cu = 32) {
   int dev = 0;
   KP_HIP_TRY(hipGetDevice(&dev));
   if (cache->dev != dev || cache->lds != lds_bytes) {
@@ -236,7 +236,7 @@ kp_status resident_grid(Kernel kern, int block, uint32_t lds_bytes, LaunchCache*
     KP_HIP_TRY(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kern, block, lds_bytes));
     if (per_cu < 1) return kp::fail(KP_ERR_UNSUPPORTED_SHAPE, "replay kernel does not fit one CU (LDS %u B)", lds_bytes);
     KP_HIP_TRY(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev));
-    cache->dev = dev; cache->lds = lds_bytes; cache->max_grid = (uint32_t)per_cu * (uint32_t)cus;
+    cache->dev = dev; cache->lds = lds_bytes; cache->max_grid = (uint32_t)(per_cu < most_per_cu ? per_cu : most_per_cu) * (uint32_t)cus;
   }
   *grid = cache->max_grid;
   return KP_OK;

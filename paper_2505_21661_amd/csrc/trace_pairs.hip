@@ -167,6 +167,11 @@ __global__ __launch_bounds__(BLOCK) void kp_pairs_main(Trace p, PairsOut o, uint
   }
 }
 
+// Blocks of 256: six per CU.  Seven or eight, which the registers and the LDS of small rings leave room for, are slower
+// (8, 7, 6, 5, 4 per CU): 10000 workgroups of 1 x 256 slots 22.9, 22.8, 18.9, 20.8, 22.6 us, 40000 of 2 x 32 68.8, 68.7, 56.2,
+// 60.1, 66.0, 20000 of 1 x 1024 96.2, 96.1, 87.1, 89.6, 96.2; with two or three turns each 5000 of 4 x 256 26.9 / 27.5.
+template <int BLOCK> constexpr int kMostPerCu = BLOCK == 256 ? 6 : 32;
+
 template <int BLOCK, int UNITS>
 kp_status launch_pairs_units(const Trace& p, const PairsOut& o, uint32_t lds_bytes, hipStream_t s) {
   // hardware waves per recorded wave: as many as the block has, while a run keeps a round of 128 ranks
@@ -175,7 +180,7 @@ kp_status launch_pairs_units(const Trace& p, const PairsOut& o, uint32_t lds_byt
   auto kern = kp_pairs_main<BLOCK, UNITS>;
   static thread_local LaunchCache cache;
   uint32_t grid = 0;
-  const kp_status st = resident_grid(kern, BLOCK, lds_bytes, &cache, &grid);
+  const kp_status st = resident_grid(kern, BLOCK, lds_bytes, &cache, &grid, kMostPerCu<BLOCK>);
   if (st != KP_OK) return st;
   if (grid > p.n_wg) grid = p.n_wg;
   hipLaunchKernelGGL(kern, dim3(grid), dim3(BLOCK), lds_bytes, s, p, o, parts);

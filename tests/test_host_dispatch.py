@@ -87,3 +87,14 @@ def test_critical_path_workgroups_are_bounded_by_their_totals(tmp_path, device):
         assert grid == min(n_wg, resident) or (n_wg > 450 + places and root / 2 <= grid <= 2 * root)
         turns = -(-n_wg // grid)
         assert grid == resident or grid == -(-n_wg // turns)
+
+
+@pytest.mark.parametrize("device", [(0, 256, 8), (1, 256, 4), (2, 32, 8)])
+def test_timeline_workgroups_of_small_rings(tmp_path, device):
+    """Blocks of 256 threads: at most six per CU; larger ones as many as are resident."""
+    shapes = [(n_wg, w, cap) for n_wg in (1, 191, 193, 1537, 40000) for w, cap in ((1, 256), (4, 256), (2, 32), (8, 64), (8, 2048))]
+    calls = [{"fn": "kp_trace_pairs_hdr", "trace": (n_wg, w, 4, cap), "device": device} for n_wg, w, cap in shapes]
+    for (n_wg, w, cap), (status, launches) in zip(shapes, fake_hip.run(calls, tmp_path)):
+        assert status == 0 and "kp_pairs_main" in launches[-1][0], launches
+        _, grid, block, _ = launches[-1]
+        assert grid == min(n_wg, device[1] * (min(6, device[2]) if block == 256 else device[2])), (n_wg, w, cap, launches)
