@@ -5,10 +5,10 @@
 // unpaired and aligned at replay, the constant record cost is subtracted), same statistics block, in
 // several passes over a recorded workgroup's records, which stay in HBM:
 //   0  every slot is checked once (fields, slot against seq).  Only a workgroup with a record outside
-//      the slot of its seq needs more: those records go on a list, and which slot wins each rank is
-//      then found a range of ranks at a time from the slots the ranks belong in and the list (the
-//      later slot wins: atomic max into a rank -> slot table); a workgroup with more such records
-//      than the list holds scans all its slots for every range instead;
+//      the slot of its seq needs more: those records go on a list, sorted by wave and rank, which the
+//      passes below look into beside the slot a rank belongs in (the later slot wins); a workgroup with
+//      more such records than the list holds scans all its slots into a rank -> slot table (atomic max)
+//      for every range of ranks instead;
 //   1  pairing (an END is paired iff the nearest earlier record of its wave and region is a START):
 //      the hardware waves share out the recorded waves in runs of consecutive ranks and walk them 64
 //      ranks at a time, one per lane; the lanes that hold a lane's region come from one ballot per bit
@@ -24,10 +24,10 @@
 //      has places, then lanes take consecutive records and finish the order in registers (with fuller
 //      cells: every record counts the records of its cell that come before it).  The number of waves that
 //      have each region open is kept bit-sliced (plane k = bit k of every region's count): each lane's net
-//      change, a scan over lanes and hardware waves, the state before each lane's records.  The total time two regions are both open is the sum over the ends of
-//      their common stretches minus the sum over the beginnings; a common stretch of a and b begins
-//      when one of them opens while the other is open and ends when one closes while the other is
-//      open, so every event that opens or closes a region adds its clock, signed, to the sums of that
+//      change, a scan over lanes and hardware waves, the state before each lane's records.  The total time
+//      two regions are both open is the sum over the ends of their common stretches minus the sum over
+//      the beginnings; a common stretch of a and b begins when one of them opens while the other is
+//      open and ends when one closes while the other is open, so every event that opens or closes a region adds its clock, signed, to the sums of that
 //      region with every open region (modulo 2^64: the total is exact).
 // Nothing but the inputs and the statistics block is touched in HBM.
 //
@@ -47,7 +47,7 @@ using namespace kp_reduce;
 
 constexpr int kBlock = 1024;
 constexpr uint32_t kWavesHw = kBlock / 64;
-constexpr uint32_t kTable = 2048;           // ranks whose winning slots pass 1 looks up at a time
+constexpr uint32_t kTableMin = 11, kTableMax = 14;  // ranks whose winning slots pass 1 looks up at a time: log2, what LDS has room for
 constexpr uint32_t kMinWindow = 2048, kAreaMin = 32768;  // smallest window of pass 2, and the LDS that it and pass 1 share at least
 constexpr uint32_t kListMin = 512, kListMax = 8192;  // records outside the slot of their seq that a workgroup can list: what LDS has room for
 constexpr uint32_t kMaxCell = 64;           // fullest time cell in which records are ranked by comparing each with each
@@ -66,7 +66,7 @@ struct WideLds {  // byte offsets
   uint32_t last, head, rows, row_min, table;  // pass 1
   uint32_t cells, totals;                     // pass 2, behind the keys, which start at 0
   uint32_t bitmap, otri, hist, reg_sum, reg_max, reg_min, ctr, tmp, vf, pos, adv, edge, list, total;
-  uint32_t per_lane, split_log2, rows_in_lds, list_cap;
+  uint32_t per_lane, split_log2, rows_in_lds, list_cap, table_log2;
 };
 inline uint32_t up16(uint32_t x) { return (x + 15u) & ~15u; }
 // LDS byte address of a place of the sorted sequence: 16 bytes of padding after every 256, so that lanes that
@@ -83,12 +83,14 @@ WideLds lay_out(uint32_t W, uint32_t R, uint32_t nrec, uint32_t per_lane, uint32
   l.rows = up16(l.head + (split_log2 ? runs_bytes : 0u));
   l.row_min = l.rows + (rows_in_lds ? W * R * 16u : 0u);
   l.table = up16(l.row_min + (rows_in_lds ? W * R * 4u : 0u));
-  const uint32_t pass1 = l.table + kTable * 4u;
+  const uint32_t pass1 = l.table + (4u << kTableMin);
   l.cells = key_at(kBlock * per_lane);
   l.totals = l.cells + kBlock * per_lane * 2u;
   const uint32_t pass2 = l.totals + kWavesHw * kMaxPlanes * 4u;
   uint32_t area = pass1 > pass2 ? pass1 : pass2;
   area = area > kAreaMin ? area : kAreaMin;
+  l.table_log2 = kTableMin;
+  while (l.table_log2 < kTableMax && l.table + (8u << l.table_log2) <= area) ++l.table_log2;
   l.bitmap = up16(area);
   l.otri = up16(l.bitmap + ((nrec + 31) / 32) * 4);
   l.hist = l.otri + R * (R + 1) / 2 * 8;
@@ -188,7 +190,7 @@ __global__ __launch_bounds__(kBlock) void kp_reduce_wide(WideParams p) {
   // [run][region] its last record: (rank + 1) << 33 | END << 32 | clock, 0 for none; so the latest is the largest
   unsigned long long* last_all = reinterpret_cast<unsigned long long*>(smem + p.lds.last);
   uint2* head_all = reinterpret_cast<uint2*>(smem + p.lds.head);        // {clock, 1 << 31 | rank} of its first record if that is an END (waves cut into runs)
-  uint32_t* table1 = reinterpret_cast<uint32_t*>(smem + p.lds.table);   // rank -> winning slot + 1, kTable ranks at a time (pass 1)
+  uint32_t* table1 = reinterpret_cast<uint32_t*>(smem + p.lds.table);   // rank -> winning slot + 1, 2^table_log2 ranks at a time (pass 1)
   uint32_t* table2 = reinterpret_cast<uint32_t*>(smem);                 // the same for the ranks a window looks at (before its keys are written)
   uint32_t* cells = reinterpret_cast<uint32_t*>(smem + p.lds.cells);    // cell c: half (c & 1) of word c >> 1
   // the records outside the slot of their seq: (wave << 20 | rank) << 20 | slot, sorted
@@ -217,7 +219,7 @@ __global__ __launch_bounds__(kBlock) void kp_reduce_wide(WideParams p) {
   auto fresh_tid = [&]() { tid = tid_k; asm volatile("" : "+v"(tid)); lane = tid & 63u; };
   const uint32_t W = p.W, R = p.R, cap = p.cap, capm = cap - 1u, cl2 = p.cap_log2, nrec = p.nrec;
   const uint32_t rsh = (E == 8 ? 13u : (E == 4 ? 12u : 11u)) - p.waves_log2, C = 1u << rsh;  // a window looks at C ranks of every wave
-  const uint32_t tsh = 11u - p.waves_log2, Ct = 1u << tsh;                                        // table1: Ct ranks of every wave
+  const uint32_t tsh = p.lds.table_log2 - p.waves_log2, Ct = 1u << tsh;                        // table1: Ct ranks of every wave
   uint32_t region_bits = 0; while ((1u << region_bits) < R) ++region_bits;
   const StatsLayout SL = stats_layout(p.n_wg, W, R);
   if (p.out[H_STATUS] != 0) return;  // device header did not match the launch geometry
@@ -319,7 +321,9 @@ __global__ __launch_bounds__(kBlock) void kp_reduce_wide(WideParams p) {
     const bool displaced = tmp[T_DISORDER] != 0u;
     // A workgroup with such records: which slot holds rank k (the later slot wins) comes from the sorted
     // list of those records, next to the slot the rank belongs in; a workgroup with more of them than the
-    // list holds scans all its slots into a rank -> slot table, a range of ranks at a time.
+    // list holds scans all its slots into a rank -> slot table, a range of ranks at a time: as large a range as LDS has
+    // room for, four loads in flight per thread (64 workgroups of 8 x 8192 with a tenth of the neighbours swapped: 1880 us
+    // with ranges of 2048 ranks, one load at a time and a further scan that counted the winners; 496 us).
     const bool listed = displaced && tmp[T_LISTED] <= p.lds.list_cap, tabled = displaced && !listed;
     const uint32_t n_listed = listed ? tmp[T_LISTED] : 0u;
     if (listed) {
@@ -357,36 +361,27 @@ __global__ __launch_bounds__(kBlock) void kp_reduce_wide(WideParams p) {
       __syncthreads();  // pos[] is written, the table's last readers are done
       for (uint32_t i = tid; i < places; i += kBlock) table[i] = 0;
       __syncthreads();
-      for (uint32_t i = tid; i < nrec; i += kBlock) {
-        const uint32_t w = i >> cl2, s = i & capm;
-        const uint32_t k = rank_of(recs[i], w, s);
-        if (k == 0xFFFFFFFFu) continue;
-        const uint32_t d = k - pos[w];
-        if (d < (1u << sh)) atomicMax(&table[(w << sh) + d], s + 1u);
+      const uint4* units = reinterpret_cast<const uint4*>(recs);  // two records each
+      for (uint32_t i0 = tid; i0 < nrec / 2u; i0 += 4u * kBlock) {  // (the loads of an iteration are in flight together)
+        uint4 v[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) v[u] = units[i0 + u * kBlock < nrec / 2u ? i0 + u * kBlock : i0];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+          const uint32_t i = 2u * (i0 + u * kBlock), w = i < nrec ? i >> cl2 : 0u, s = i & capm;
+          const uint32_t first = sVF[w].y, from = pos[w];
+#pragma unroll
+          for (uint32_t h = 0; h < 2u; ++h) {
+            const uint2 rec = h ? make_uint2(v[u].z, v[u].w) : make_uint2(v[u].x, v[u].y);
+            const uint32_t d = ((rec.x - first) & kSeqMask) - from;  // (most records are of another range)
+            if (i < nrec && d < (1u << sh) && rank_of(rec, w, s + h) != 0xFFFFFFFFu) atomicMax(&table[(w << sh) + d], s + h + 1u);
+          }
+        }
       }
       __syncthreads();
     };
 
     uint32_t n_occupied = 0, n_disorder = 0;
-    if (tabled) {
-      uint32_t occ = 0, dis = 0;
-      for (uint32_t k0 = 0; k0 < max_v; k0 += Ct) {
-        if (tid < 16) pos[tid] = k0;
-        build_table(table1, kTable, tsh);
-        for (uint32_t idx = tid; idx < kTable; idx += kBlock) {
-          const uint32_t t = table1[idx];
-          if (t) {
-            const uint32_t s = t - 1u;
-            ++occ;
-            dis += (s != (recs[(size_t)(idx >> tsh) * cap + s].x & capm)) ? 1u : 0u;
-          }
-        }
-      }
-      occ = wave_sum(occ);
-      dis = wave_sum(dis);
-      if (lane == 0) { atomicAdd(&tmp[T_OCCUPIED], occ); atomicAdd(&tmp[T_WINNER_DISORDER], dis); }
-    }
-
     // ---- pass 1: pairing, durations, per-(wave, region) statistics, monotonicity ---------------------
     // Hardware wave (w << split) + i takes run i of recorded wave w, 64 consecutive ranks at a time, one per
     // lane.  The nearest earlier record of a lane's (wave, region) is the highest lower lane with the same
@@ -529,11 +524,13 @@ __global__ __launch_bounds__(kBlock) void kp_reduce_wide(WideParams p) {
       } else {
         for (uint32_t k0 = 0; k0 < max_v; k0 += Ct) {
           if (tid < 16) pos[tid] = k0;
-          build_table(table1, kTable, tsh);
+          build_table(table1, 1u << p.lds.table_log2, tsh);
 #pragma unroll 1
           for (uint32_t j0 = 0; j0 < Ct && k0 + j0 < V; j0 += 64u) {
             const uint32_t t = table1[(hw << tsh) + j0 + lane];
-            group(k0 + j0, t != 0u, recs[(size_t)hw * cap + (t ? t - 1u : 0u)]);
+            const uint2 rec = recs[(size_t)hw * cap + (t ? t - 1u : 0u)];
+            moved += (uint32_t)__popcll(__builtin_amdgcn_ballot_w64(t != 0u && ((rec.x ^ (t - 1u)) & capm) != 0u));
+            group(k0 + j0, t != 0u, rec);
           }
         }
       }
@@ -541,7 +538,7 @@ __global__ __launch_bounds__(kBlock) void kp_reduce_wide(WideParams p) {
         if (n_pairs) atomicAdd(&tmp[T_PAIRS], n_pairs);
         if (n_ends) atomicAdd(&tmp[T_ENDS], n_ends);
         if (nonmono) atomicAdd(&tmp[T_NONMONO], nonmono);
-        if (occupied && !tabled) atomicAdd(&tmp[T_OCCUPIED], occupied);
+        if (occupied) atomicAdd(&tmp[T_OCCUPIED], occupied);
         if (moved) atomicAdd(&tmp[T_WINNER_DISORDER], moved);
         edge[4u * hw] = carry_has ? 1u : 0u;
         edge[4u * hw + 1u] = first_ts;

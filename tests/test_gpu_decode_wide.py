@@ -89,7 +89,7 @@ def test_generated_traces(kp, oracle_mod, W, R, cap, total):
     assert st["n_pairs"] > 0 and st["n_overlap_wgs"] > 0
 
 
-@pytest.mark.parametrize("W,R,cap,p_swap", [(16, 8, 4096, 0.2), (16, 128, 1024, 0.15), (3, 40, 16384, 0.3), (8, 16, 8192, 0.004)])
+@pytest.mark.parametrize("W,R,cap,p_swap", [(16, 8, 4096, 0.2), (16, 128, 1024, 0.15), (3, 40, 16384, 0.3), (2, 5, 65536, 0.05), (8, 16, 8192, 0.004)])
 def test_heavily_shuffled_rings(kp, oracle_mod, W, R, cap, p_swap):
     """So many records outside the slot of their sequence number that the kernel's list of them overflows
     (it then scans all slots for every range of ranks), and, in the last case, a list that is nearly full."""
