@@ -157,7 +157,7 @@ def test_empty_trace_and_limits(kp, oracle_mod):
     assert e.value.status == kp.KP_ERR_UNSUPPORTED_SHAPE
 
 
-@pytest.mark.parametrize("spacing", ["random", "lockstep", "equal", "far"])
+@pytest.mark.parametrize("spacing", ["random", "lockstep", "equal", "burst", "far"])
 @pytest.mark.parametrize("W,R,cap", [(8, 40, 1024), (3, 70, 512), (16, 33, 256), (2, 128, 2048), (1, 33, 4096)])
 def test_sort_forms_of_the_overlap_windows(kp, oracle_mod, W, R, cap, spacing):
     """Clocks that put few, many or all records of a window into one time cell, windows longer than 2^24 ticks,
@@ -168,7 +168,8 @@ def test_sort_forms_of_the_overlap_windows(kp, oracle_mod, W, R, cap, spacing):
         t, wave = 3, []
         outer = cap // 2 - 7 + w  # opens region R - 1 here, closes it a quarter of the ring later
         while len(wave) < cap - 4:
-            step = {"random": int(rng.integers(1, 900)), "lockstep": 400, "equal": 0, "far": 1 << 16}[spacing]
+            step = {"random": int(rng.integers(1, 900)), "lockstep": 400, "equal": 0, "far": 1 << 16,
+                    "burst": 60000 if len(wave) % 96 < 2 else len(wave) % 4}[spacing]
             if len(wave) == outer:
                 wave.append((S, R - 1, t))
                 continue
