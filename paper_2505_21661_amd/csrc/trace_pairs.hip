@@ -31,13 +31,12 @@ using namespace kp_stage;
 constexpr uint32_t kBelowStride = 128;  // one counter per region
 constexpr uint32_t kNoId = 0xFFFFu;     // END << 7 | region of no record
 
-// First of the rounds that part i of n emits.  A wave also counts the pairs of all rounds below its run, which
-// takes about two fifths of the time of emitting them: with c = 2/5, run i + 1 is 1 - c of run i, so that
-// all parts take the same time.
-__device__ __forceinline__ uint32_t run_start(uint32_t rounds, uint32_t i, uint32_t n) {
-  float left = 1.0f, all = 1.0f;  // (1 - c)^i, (1 - c)^n
-  for (uint32_t j = 0; j < n; ++j) { left = j < i ? left * 0.6f : left; all *= 0.6f; }
-  return i >= n ? rounds : (uint32_t)((float)rounds * (1.0f - left) / (1.0f - all) + 0.5f);
+// First of the rounds that part i of n emits.  Of two parts the second also counts the pairs of the rounds below its run,
+// which takes about two fifths of the time of emitting them where the regions follow one another: it gets three
+// fifths of what the first one gets.  Three and more are equal and count their own rounds ahead of emitting them.
+inline float share_of(uint32_t n) { return n == 2u ? 0.625f : 1.0f / (float)n; }
+__device__ __forceinline__ uint32_t run_start(uint32_t rounds, uint32_t i, uint32_t n, float share) {
+  return i >= n ? rounds : (uint32_t)((float)rounds * ((float)i * share) + 0.5f);
 }
 
 struct PairsOut {
@@ -45,8 +44,9 @@ struct PairsOut {
   u32x4* rows;      // cap/2 rows per (workgroup, wave)
 };
 
-template <int BLOCK, int UNITS>
-__global__ __launch_bounds__(BLOCK) void kp_pairs_main(Trace p, PairsOut o, uint32_t parts) {
+// SHARED: more than two parts.
+template <int BLOCK, int UNITS, bool SHARED>
+__global__ __launch_bounds__(BLOCK) void kp_pairs_main(Trace p, PairsOut o, uint32_t parts, float share) {
   extern __shared__ __align__(16) unsigned char smem[];
   const Lds L = lds_layout(p.nrec);
   const u32x4* rec2 = reinterpret_cast<const u32x4*>(smem + L.rec);
@@ -69,16 +69,22 @@ __global__ __launch_bounds__(BLOCK) void kp_pairs_main(Trace p, PairsOut o, uint
     request_workgroup<BLOCK, UNITS>(p, wg + gridDim.x < p.n_wg ? wg + gridDim.x : wg, coming);
     const uint32_t live_tag = live_tag_of(iter);
     // ---- walk: `parts` hardware waves share one recorded wave -------------------------------------------
-    // Each emits the rows of a run of consecutive ranks.  A run that does not start at rank 0 first
-    // counts the pairs below it (total and per region) with the same pairing rounds, so that its row
-    // and iteration indices continue those of the runs below; no wave waits for another.
-    if (hw < W * parts) {
-      const uint32_t w = hw / parts, part = hw - w * parts;
-      const uint32_t wofs = w << cl2, V = sV[w];
+    // Each emits the rows of a run of consecutive ranks, whose row and iteration indices continue those of the runs below.
+    // Of two, the second counts the pairs below its run (in all and per region) with the same pairing rounds, and no wave
+    // waits for another.  Of more, each counts those of its own run and adds up the runs below it: (1 + c) / n of the time
+    // that one wave would need to emit all, c / (1 - (1 - c)^n) where each counts all runs below (c: the time of
+    // counting a round over that of emitting it, 2/5 where regions follow one another, 4/5 and more where they lie inside one
+    // another).  Each counting all below / its own: 512 workgroups of 1 x 16384 slots 113 / 42 us, regions three deep 277 / 68;
+    // 2000 of 5 x 2048, three parts, 93.7 / 91.6 and 177 / 159.
+    if (SHARED || hw < W * parts) {
+      const bool walks = !SHARED || hw < W * parts;  // (a hardware wave without a run comes along to the barriers)
+      const uint32_t w = walks ? hw / parts : 0u, part = walks ? hw - w * parts : 0u;
+      const uint32_t wofs = w << cl2, V = walks ? sV[w] : 0u;
       const uint32_t rounds = (V + 127u) >> 7;
-      const uint32_t k0 = run_start(rounds, part, parts) << 7, k_next = run_start(rounds, part + 1u, parts) << 7;
+      const uint32_t k0 = run_start(rounds, part, parts, share) << 7, k_next = run_start(rounds, part + 1u, parts, share) << 7;
       const uint32_t k1 = V < k_next ? V : k_next;  // this wave emits ranks [k0, k1)
-      const uint32_t kc = V < k0 ? V : k0;           // and counts ranks [0, kc)
+      const uint32_t c0 = SHARED ? k0 : 0u;         // and counts ranks [c0, c1)
+      const uint32_t c1 = !SHARED ? (V < k0 ? V : k0) : (part + 1u < parts ? k1 : k0);
       uint32_t* seen = below + hw * kBelowStride;    // pairs of each region so far
       seen[lane] = 0u; seen[64u + lane] = 0u;        // (LDS operations of one wave complete in order)
       u32x4* my_rows = o.rows + ((size_t)wg * W + w) * (cap / 2);
@@ -87,7 +93,17 @@ __global__ __launch_bounds__(BLOCK) void kp_pairs_main(Trace p, PairsOut o, uint
       // 128 ranks from kb, two neighbours per lane: which of this lane's are ENDs that are paired, and with what.
       uint32_t id0 = kNoId, id1 = kNoId, start0 = 0u, start1 = 0u;
       u32x4 r = {0u, 0u, 0u, 0u};  // {clock, metadata} of the even rank and of the odd one
-      u32x4 next = rec2[(wofs + (2u * lane < V ? 2u * lane : 0u)) >> 1];  // one round ahead, to hide the LDS latency
+      u32x4 next;  // one round ahead, to hide the LDS latency
+      auto start_at = [&](uint32_t kb) __attribute__((always_inline)) {
+        const uint32_t k = kb + 2u * lane;
+        next = rec2[(wofs + (k < V ? k : 0u)) >> 1];
+        if (kb != 0u && kb < V) {  // (uniform)
+          const u32x4 under = rec2[(wofs + kb - 2u) >> 1];
+          carry_id = is_live(under.w, live_tag) ? under.w & 0xFFu : kNoId;
+          carry_t = under.z;
+        }
+      };
+      start_at(c0);
       auto pair_128 = [&](uint32_t kb, uint32_t k_end, bool& paired0, bool& paired1) __attribute__((always_inline)) {
         const uint32_t k = kb + 2u * lane;
         r = next;
@@ -106,13 +122,25 @@ __global__ __launch_bounds__(BLOCK) void kp_pairs_main(Trace p, PairsOut o, uint
         if (__builtin_amdgcn_ballot_w64(open0 || open1) != 0ull)
           look_back(rec2, (wofs + k) >> 1, k >> 1, live_tag, open0, id0, paired0, start0, open1, id1, paired1, start1);
       };
-      // ---- count the pairs below this run ---------------------------------------------------------------
-      for (uint32_t kb = 0; kb < kc; kb += 128) {  // kc is a multiple of 128 or the end of the wave
+      // ---- count ------------------------------------------------------------------------------------------
+      for (uint32_t kb = c0; kb < c1; kb += 128) {  // c1 is a multiple of 128 or the end of the wave
         bool paired0, paired1;
-        pair_128(kb, kc, paired0, paired1);
+        pair_128(kb, c1, paired0, paired1);
         n_rows += (uint32_t)__popcll(__builtin_amdgcn_ballot_w64(paired0)) + (uint32_t)__popcll(__builtin_amdgcn_ballot_w64(paired1));
         if (paired0) atomicAdd(&seen[id0 & kMRegion], 1u);
         if (paired1) atomicAdd(&seen[id1 & kMRegion], 1u);
+      }
+      if constexpr (SHARED) {
+        __syncthreads();  // all runs are counted
+        uint32_t lo = 0u, hi = 0u;
+        for (uint32_t i = 0; i < part; ++i) {
+          const uint32_t* of = seen - (part - i) * kBelowStride;
+          lo += of[lane]; hi += of[64u + lane];
+        }
+        __syncthreads();  // and read by all that need them
+        seen[lane] = lo; seen[64u + lane] = hi;
+        n_rows = wave_total(lo + hi);
+        start_at(k0);
       }
       // ---- emit the rows of this run ------------------------------------------------------------------------
       auto row = [&](uint32_t j, uint32_t start, uint32_t end, uint32_t it, uint32_t region) __attribute__((always_inline)) {
@@ -161,7 +189,7 @@ __global__ __launch_bounds__(BLOCK) void kp_pairs_main(Trace p, PairsOut o, uint
         }
       }
       // the wave with the last run knows the total
-      if (lane == 0 && part + 1u == parts) o.count[(size_t)wg * W + w] = n_rows;
+      if (lane == 0 && walks && part + 1u == parts) o.count[(size_t)wg * W + w] = n_rows;
     }
     __syncthreads();
   }
@@ -172,20 +200,28 @@ __global__ __launch_bounds__(BLOCK) void kp_pairs_main(Trace p, PairsOut o, uint
 // 60.1, 66.0, 20000 of 1 x 1024 96.2, 96.1, 87.1, 89.6, 96.2; with two or three turns each 5000 of 4 x 256 26.9 / 27.5.
 template <int BLOCK> constexpr int kMostPerCu = BLOCK == 256 ? 6 : 32;
 
-template <int BLOCK, int UNITS>
-kp_status launch_pairs_units(const Trace& p, const PairsOut& o, uint32_t lds_bytes, hipStream_t s) {
-  // hardware waves per recorded wave: as many as the block has, while a run keeps a round of 128 ranks
-  uint32_t parts = (uint32_t)BLOCK / 64u / p.W;
-  if (parts > (p.cap + 127u) / 128u) parts = (p.cap + 127u) / 128u;
-  auto kern = kp_pairs_main<BLOCK, UNITS>;
+template <int BLOCK, int UNITS, bool SHARED>
+kp_status launch_pairs_parts(const Trace& p, const PairsOut& o, uint32_t lds_bytes, uint32_t parts, hipStream_t s) {
+  auto kern = kp_pairs_main<BLOCK, UNITS, SHARED>;
   static thread_local LaunchCache cache;
   uint32_t grid = 0;
   const kp_status st = resident_grid(kern, BLOCK, lds_bytes, &cache, &grid, kMostPerCu<BLOCK>);
   if (st != KP_OK) return st;
   if (grid > p.n_wg) grid = p.n_wg;
-  hipLaunchKernelGGL(kern, dim3(grid), dim3(BLOCK), lds_bytes, s, p, o, parts);
+  hipLaunchKernelGGL(kern, dim3(grid), dim3(BLOCK), lds_bytes, s, p, o, parts, share_of(parts));
   KP_HIP_TRY(hipGetLastError());
   return KP_OK;
+}
+
+template <int BLOCK, int UNITS>
+kp_status launch_pairs_units(const Trace& p, const PairsOut& o, uint32_t lds_bytes, hipStream_t s) {
+  // hardware waves per recorded wave: as many as the block has, while a run keeps a round of 128 ranks
+  uint32_t parts = (uint32_t)BLOCK / 64u / p.W;
+  if (parts > (p.cap + 127u) / 128u) parts = (p.cap + 127u) / 128u;
+  if constexpr (BLOCK != 512 || UNITS != 8) {  // (blocks of 512 cut one or two waves into more than two: 4096 records at most)
+    if (parts > 2u) return launch_pairs_parts<BLOCK, UNITS, true>(p, o, lds_bytes, parts, s);
+  }
+  return launch_pairs_parts<BLOCK, UNITS, false>(p, o, lds_bytes, parts, s);
 }
 
 template <int BLOCK>

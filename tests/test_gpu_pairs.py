@@ -85,6 +85,34 @@ def test_mostly_sequential_traces(kp, oracle_mod, W, R, cap, holes):
     assert_pairs_equal(oracle_mod, raw, run_pairs(kp, raw, use_hdr=True))
 
 
+@pytest.mark.parametrize("W,cap", [(1, 512), (1, 1024), (1, 2048), (3, 2048), (5, 512), (2, 8192), (1, 16384)])
+def test_runs_of_a_wave_that_is_cut_up(kp, oracle_mod, W, cap):
+    """Three and more parts per recorded wave (two for 5 waves of 512): record counts around the rounds of 128 that the
+    parts are made of, a region that is open across the cuts, pairs whose records lie on either side of one, and
+    records that fail their checks right below a cut."""
+    rng = np.random.default_rng(W + cap)
+    wgs = []
+    for total in (0, 1, 2, 127, 128, 129, 255, 257, cap // 2 - 1, cap - 128, cap - 1, cap, cap + 1, cap + 129):
+        evs = []
+        for w in range(W):
+            n = max(0, total - 3 * w)
+            wave = [(inputs.PHASE_START, 6, 1)] if w != 1 else []
+            while len(wave) < n - 1:
+                t = 10 * len(wave)
+                r = int(rng.integers(0, 6))
+                wave += [(inputs.PHASE_START, r, t), (inputs.PHASE_END, r, t + int(rng.integers(0, 12)))]
+            wave = wave[:max(0, n - 1)] + [(inputs.PHASE_END, 6, 10 * n + 20)] * (n > 0)
+            evs.append(wave)
+        wg = inputs.events_to_wg(evs, cap, flush=False)
+        if total % 2:
+            for seg in wg["slots"]:
+                for i in range(127, len(seg), 256):
+                    seg[i] = (0xFFFFFFFF, seg[i][1])
+        wgs.append(wg)
+    raw = inputs.encode_trace(wgs, W, 7, cap, rec_cost=3)
+    assert_pairs_equal(oracle_mod, raw, run_pairs(kp, raw, use_hdr=True))
+
+
 def test_many_workgroups_exercise_generation_reuse(kp, oracle_mod):
     # more recorded workgroups than resident decoder workgroups: the staging area is reused
     spec = inputs.TraceSpec(n_wg=3000, waves=4, n_regions=6, cap_wave=64, total_per_wave=64, total_var=40, seed=77,
