@@ -140,6 +140,7 @@ __global__ __launch_bounds__(BLOCK) void kp_pairs_main(Trace p, PairsOut o, uint
         __syncthreads();  // and read by all that need them
         seen[lane] = lo; seen[64u + lane] = hi;
         n_rows = wave_total(lo + hi);
+        carry_id = kNoId;  // (rank 0 has nothing below it)
         start_at(k0);
       }
       // ---- emit the rows of this run ------------------------------------------------------------------------

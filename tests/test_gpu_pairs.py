@@ -113,6 +113,18 @@ def test_runs_of_a_wave_that_is_cut_up(kp, oracle_mod, W, cap):
     assert_pairs_equal(oracle_mod, raw, run_pairs(kp, raw, use_hdr=True))
 
 
+@pytest.mark.parametrize("W,cap", [(1, 512), (1, 1024), (3, 2048), (2, 8192), (1, 16384)])
+def test_first_record_of_a_wave_that_is_cut_up(kp, oracle_mod, W, cap):
+    """A wave that begins with an END has nothing below that record, whatever its runs end in: here each ends in a
+    START of the same region."""
+    wgs = []
+    for total in (1, 127, 128, 129, 256, 384, cap // 2, cap - 2, cap, cap + 2):
+        wave = [(inputs.PHASE_START if k % 2 else inputs.PHASE_END, 0, 10 * k) for k in range(total)]
+        wgs.append(inputs.events_to_wg([wave] * W, cap, flush=False))
+    raw = inputs.encode_trace(wgs, W, 1, cap, rec_cost=3)
+    assert_pairs_equal(oracle_mod, raw, run_pairs(kp, raw, use_hdr=True))
+
+
 def test_many_workgroups_exercise_generation_reuse(kp, oracle_mod):
     # more recorded workgroups than resident decoder workgroups: the staging area is reused
     spec = inputs.TraceSpec(n_wg=3000, waves=4, n_regions=6, cap_wave=64, total_per_wave=64, total_var=40, seed=77,
