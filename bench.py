@@ -141,7 +141,7 @@ def decode_steps(args) -> int:
         rows.append({"step": i, "what": what, "ms_up_to_here": round(t, 4), "ms_of_step": round(t - prev, 4)})
         prev = t
     full = timed(lambda: kp.kp_trace_reduce_hdr(dev_raw, n, hdr, out))
-    rows.append({"step": 9, "what": "per-(workgroup, wave, region) output, totals, init and finalize kernels",
+    rows.append({"step": 9, "what": "per-(workgroup, wave, region) output, totals, the kernels that clear the block and derive figures",
                  "ms_up_to_here": round(full, 4), "ms_of_step": round(full - prev, 4)})
     del dev_raw, out
     # the multi-pass kernel for geometries outside the LDS-resident one's: same recipe, 2^26 record slots
@@ -199,6 +199,16 @@ def probe(args) -> int:
         for _ in range(2):
             kp.kp_gemm_instrumented(A, B, C, M, N, K, mask, trace if mask & 31 else None, 4096 if mask & 31 else 0)
     torch.cuda.synchronize()
+    for M, N, K in ((2112, 1984, 2080), (4032, 3968, 160)):  # the 64x64x32 tile: pipelined, short K
+        a, b = inputs.gemm_inputs(M, N, K, seed=4)
+        A, B = a.to(dev), b.to(dev)
+        C = torch.empty(M, N, dtype=torch.bfloat16, device=dev)
+        n_wg, waves, R = kp.kp_gemm_launch_shape(M, N, K)
+        trace = torch.zeros(kp.kp_trace_bytes(n_wg, waves, 512), dtype=torch.uint8, device=dev)
+        for mask in (0, 0b111):
+            for _ in range(2):
+                kp.kp_gemm_instrumented(A, B, C, M, N, K, mask, trace if mask else None, 512 if mask else 0)
+    torch.cuda.synchronize()
     Bt, H, S, D = 4, 32, 4096, 128
     q, k, v = inputs.attn_inputs(Bt, H, S, D, seed=3)
     Q, Kt, V = q.to(dev), k.to(dev), v.to(dev)
@@ -228,12 +238,13 @@ def probe(args) -> int:
         kp.kp_stages_critical(stages, spec.n_wg, spec.n_regions, 64, paths)
     torch.cuda.synchronize()
     del d_raw, stats, pairs, waits, stages, paths
-    ws = wide_spec(8, 16, 8192, min(args.log2_records, 26))  # the decoder's multi-pass kernel
-    wraw, _ = inputs.gen_trace(ws)
-    wdev = torch.from_numpy(wraw.view(np.int32)).to(dev)
-    wstats = torch.zeros(kp.kp_stats_bytes(ws.n_wg, ws.waves, ws.n_regions), dtype=torch.uint8, device=dev)
-    for _ in range(2):
-        kp.kp_trace_reduce_hdr(wdev, ws.n_slots, kp.make_hdr(ws.n_wg, ws.waves, ws.n_regions, ws.cap_wave), wstats)
+    for W, R, cap in ((8, 16, 8192), (8, 48, 4096)):  # the decoder's multi-pass kernel
+        ws = wide_spec(W, R, cap, min(args.log2_records, 26))
+        wraw, _ = inputs.gen_trace(ws)
+        wdev = torch.from_numpy(wraw.view(np.int32)).to(dev)
+        wstats = torch.zeros(kp.kp_stats_bytes(ws.n_wg, ws.waves, ws.n_regions), dtype=torch.uint8, device=dev)
+        for _ in range(2):
+            kp.kp_trace_reduce_hdr(wdev, ws.n_slots, kp.make_hdr(ws.n_wg, ws.waves, ws.n_regions, ws.cap_wave), wstats)
     torch.cuda.synchronize()
     return 0
 
@@ -391,7 +402,7 @@ def main() -> int:
     attn_tf_ins = attn_flop / ms["attn_instr"] / 1e9
     attn_overhead = (ms["attn_instr"] - ms["attn_vanilla"]) / ms["attn_vanilla"] * 100.0
     ms["decode_main_kernel"] = float(np.mean([b.elapsed_time(e) for b, e in main_events]))
-    dec_rps = d_n / (ms["decode"] * 1e-3)  # the whole call: clearing, replay and finalize kernels
+    dec_rps = d_n / (ms["decode"] * 1e-3)  # the whole call: clearing, replay and deriving kernels
     dec_gbs = DECODE_BYTES_PER_RECORD * d_n / (ms["decode_main_kernel"] * 1e-3) / 1e9  # the replay kernel alone
 
     st = kp.parse_stats(d_stats)
