@@ -989,9 +989,21 @@ __global__ __launch_bounds__(BLOCK) void kp_reduce_main(DecodeParams p) {
             own[1] = u32x4{mk[4], mk[5], mk[6], mk[7]};
             products = (tid & ~63u) * kNR < n_events ? n_limbs : 0u;  // this wave holds records
           } else {
+            // Its neighbours may add up their own stretches only: what is open where this wave's begin counts as
+            // switched on there, what is open where they end as switched off.
+            auto add_open = [&](uint32_t val) {
+              uint32_t act = pl[0];
+#pragma unroll
+              for (int k = 1; k < PLANES; ++k) act |= pl[k];
+              for (uint32_t rows = act & region_bits; rows; rows &= rows - 1)
+                for (uint32_t set = rows; set; set &= set - 1)  // (from the diagonal on)
+                  atomicAdd(&oacc32[(__ffs(rows) - 1u) * (R | 1u) + __ffs(set) - 1u], val);
+            };
+            if (lane == 0) add_open(0u - key_clock(key[0]));
 #pragma unroll
             for (int i = 0; i < kNR; ++i)
               switch_record(key_region_bit(key[i]) & region_bits, key_end_mask(key[i]), key_clock(key[i]));
+            if (lane == 63) add_open(t_next);
           }
         } else {
           // ---- the general way: the sequence is already in order, clocks up to 32 bits, up to 32 regions --

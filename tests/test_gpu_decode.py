@@ -249,3 +249,24 @@ def test_records_of_one_clock(kp, oracle_mod, W, R, cap):
     raw = inputs.encode_trace(wgs, W, R, cap, rec_cost=0)
     for _ in range(3):
         check(raw, oracle_mod, use_hdr=True)
+
+
+@pytest.mark.parametrize("W,R,cap", [(4, 3, 1024), (2, 7, 1024), (8, 16, 2048), (16, 5, 1024), (1, 2, 16384)])
+def test_a_long_gap_between_short_stretches(kp, oracle_mod, W, R, cap):
+    """Records every few hundred ticks and one stretch of 2^21 ticks or more, which only the hardware wave that holds it
+    adds up record by record: at every place of the sequence, and behind the last record, with regions open around it."""
+    rng = np.random.default_rng(W * R)
+    wgs = []
+    for place in (0.0, 0.1, 0.35, 0.5, 0.77, 0.95, 1.0):
+        waves = []
+        for w in range(W):
+            k = np.arange(cap - 4)
+            t = k * 600 + rng.integers(0, 600, cap - 4) + np.where(k >= place * cap, (1 << 21) + 5000, 0)
+            region = rng.integers(0, R - 1, cap) if w else np.zeros(cap, int)
+            inner = [(E if i % 2 else S, int(region[i // 2]), int(t[i])) for i in k]
+            waves.append([(S, R - 1, 0)] + inner + [(E, R - 1, int(t[-1]) + 7 * w)])
+        wg = inputs.events_to_wg(waves, cap, flush=False)
+        wg["t_end"] += (1 << 21) if place == 1.0 else 0
+        wgs.append(wg)
+    raw = inputs.encode_trace(wgs, W, R, cap, rec_cost=2)
+    check(raw, oracle_mod, use_hdr=True)
