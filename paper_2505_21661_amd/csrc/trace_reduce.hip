@@ -691,7 +691,9 @@ __global__ __launch_bounds__(BLOCK) void kp_reduce_main(DecodeParams p) {
       }
       // A pair of length 0 overlaps nothing, and records of one clock come out of the counting sort in any order: its END
       // could open the region, in the general sweep, to every record of the same clock until its START.  Neither is an
-      // event.  (The record a START is paired with is the next one of its region.)
+      // event.  (The record a START is paired with is the next one of its region; the clocks of a wave do not fall here,
+      // so that every record between the two has their clock: another one ends the search.  256 workgroups of 2 x 2048
+      // records of 17 regions, half of them in any order: 295 us going to the partner every time, 244 this way.)
       if (tmp[T_ZERO]) {
 #pragma unroll
         for (int i = 0; i < kNR; ++i) {
@@ -699,7 +701,7 @@ __global__ __launch_bounds__(BLOCK) void kp_reduce_main(DecodeParams p) {
           if (m & kPaired) {
             const uint32_t step = m & kEnd ? ~0u : 1u;
             uint32_t q = qe + 128u * (i >> 1) + (i & 1) + step;
-            while (((meta[q] ^ m) & kRegion) != 0u) q += step;
+            while (clk[clk_word(q)] == t[i] && ((meta[q] ^ m) & kRegion) != 0u) q += step;
             if (clk[clk_word(q)] == t[i]) mq[i >> 2] ^= kPaired << (8 * (i & 3));
           }
         }
