@@ -298,9 +298,11 @@ __global__ void kp_waits_head(uint64_t* out, uint32_t n_wg, uint32_t W, uint32_t
 // where the decoder workgroups are the square root of the recorded ones times the ratio of the two, however many are
 // resident.  All that are resident / so many: 509 workgroups of 8 x 64 slots 31.1 / 17.9 us (184 of 509), 2046 of 8 x 16
 // 31.2 / 25.2 (365 of 768), 5461 of 3 x 16 68.4 / 45.5, 1024 of 4 x 1024 52.9 / 41.5; 9000 of 3 x 1024: all 768, 87.
+// (To the nearest whole number of recorded workgroups for each: of 256, where some 240 are the least sum, a few would take
+// a second one: 16 x 256 slots 29.2 us, 22.7 with all 256.)
 inline uint32_t most_workgroups(uint32_t n_wg, uint32_t nrec) {
-  const double most = sqrt((double)n_wg * (64.0 + nrec / 48.0));
-  return most < (double)n_wg ? (uint32_t)most : n_wg;
+  const uint32_t each = (uint32_t)(sqrt((double)n_wg / (64.0 + nrec / 48.0)) + 0.5);
+  return each > 1u ? (n_wg + each - 1u) / each : n_wg;
 }
 
 template <int BLOCK, int UNITS>
