@@ -4,15 +4,24 @@
 // The paper's case study profiles a flash-attention kernel whose regions are the two GEMMs and
 // the softmax of every KV iteration (Sec. 5.2, Table 3: GEMM0 = Q K^T, softmax, GEMM1 = P V).
 // This is the library's own MFMA kernel with the same three regions per KV tile of 64:
-//   region 0  S^T = K Q^T     (MFMA); closes behind the barrier that follows it
-//   region 1  online softmax   (VALU, fp32); opens with the four loads that send this wave's share of the
-//             next K tile from global memory straight to LDS
-//   region 2  O^T += V^T P^T   (MFMA; V is transposed by the LDS read); closes behind the barrier that
-//             follows it, and the next V tile is requested there
+//   region 0  S^T = K Q^T     (MFMA), with the eight loads that send this wave's share of the next V and the next K
+//             tile from global memory straight to LDS threaded in
+//   region 1  online softmax   (VALU, fp32)
+//   region 2  O^T += V^T P^T   (MFMA; V is transposed by the LDS read); closes behind the barrier that follows it
 // One workgroup = 4 waves = 128 query rows of one (batch, head); each wave owns 32 rows.  The
 // products are formed transposed so that a lane holds all scores of ONE query row: the row
 // maximum and sum are then in-lane reductions plus one exchange with the lane 32 away, and the
 // rescaling of the output accumulators is a per-lane multiply.
+//
+// What bounds it: with two workgroups per CU the chip's power (0.97-1.03 PFLOP/s at some 1.5 GHz; the matrix pipes want
+// 1056 cycles per wave and KV tile, the vector ALU about 800, and the two overlap only in part: a probe with an MFMA, four
+// FMAs and two exponentials per step and two waves per SIMD takes 43 cycles a step where either kind alone takes 33 and
+// 31).  With one, the rate at which a single wave issues: 6 cycles per vector instruction, 14 per exponential, some 330
+// instructions per KV tile.  So every instruction counts, and every operand is requested eight (K) or four (V) MFMAs ahead
+// in an order that the scheduling fences hold: left to itself the compiler reads the operands of one step, waits for them,
+// multiplies.  4 x 32 x 4096, causal, all regions recorded 639 -> 550 us; 1 x 12 x 1152, 108 workgroups 27.4 -> 24.3 us;
+// 2 x 9 x 1920, causal 52 -> 38 us (half of which is the order of the workgroups).  Exponentials threaded between the
+// MFMAs of either product, all or a part of them: within 1 % of this form, and region 1 no longer the softmax.
 #include <type_traits>
 
 #include "kp_common.h"
@@ -46,6 +55,7 @@ constexpr int kD = 128, kBq = 128, kBkv = 64, kAttnThreads = 256;
 constexpr uint32_t kRow = kD * 2;             // a row of either tile: one kv, 128 d, 256 bytes in 16 chunks of 16
 constexpr uint32_t kKBytes = kBkv * kRow;     // K tile [64 kv][128 d]
 constexpr uint32_t kVBytes = kBkv * kRow;     // V tile [64 kv][128 d], as it lies in memory
+constexpr int kNoLoads = 0x0F70;              // s_waitcnt vmcnt(0), the other counters as they are
 constexpr float kSlack = 8.0f;                // log2 of how far a score may exceed the softmax reference
 
 // two fp32 -> packed bf16 pair (lo in bits 15:0), round to nearest even: one v_cvt_pk_bf16_f32
@@ -54,6 +64,12 @@ typedef float f32x2 __attribute__((ext_vector_type(2)));
 __device__ __forceinline__ uint32_t bf16_pack_rne(float lo, float hi) {
   const f32x2 v = {lo, hi};
   return __builtin_bit_cast(uint32_t, __builtin_convertvector(v, bf16x2));
+}
+
+// The larger of a lane's value and that of the lane 32 away.
+__device__ __forceinline__ float either_half_max(float x) {
+  const auto r = __builtin_amdgcn_permlane32_swap(__builtin_bit_cast(uint32_t, x), __builtin_bit_cast(uint32_t, x), false, false);
+  return fmaxf(__builtin_bit_cast(float, (uint32_t)r[0]), __builtin_bit_cast(float, (uint32_t)r[1]));
 }
 
 // Both tiles go from global memory straight to LDS (global_load_lds_dwordx4: lane l of a wave lands at byte
@@ -90,23 +106,34 @@ struct AttnChain {
 
 template <int INSTR>
 __global__ __launch_bounds__(kAttnThreads, 2) void kp_attn_fwd(AttnArgs g) {
-  extern __shared__ __align__(16) unsigned char smem[];  // [K tile][V^T tile][ring]
-  unsigned char* sK = smem;
-  unsigned char* sV = smem + kKBytes;
-  uint32_t* ring_lds = reinterpret_cast<uint32_t*>(smem + kKBytes + kVBytes);
+  extern __shared__ __align__(16) unsigned char smem[];  // [K tile][V tile, two buffers][ring]
+  uint32_t* ring_lds = reinterpret_cast<uint32_t*>(smem + kKBytes + 2 * kVBytes);
 
   const uint32_t tid = threadIdx.x, lane = tid & 63u, wave = tid >> 6;
   const uint32_t h32 = lane >> 5, l32 = lane & 31u;
   const uint32_t q_blocks = g.S / kBq;
-  // Workgroups are dealt round-robin to the 8 XCDs, each with its own L2.  All query blocks of a
-  // (batch, head) go to one XCD, one head after the other, so that its K and V (2 MiB) are fetched
-  // into one L2 once instead of into all eight.  `wg` is the recorded workgroup: head-major.
+  // Workgroups are dealt round-robin to the 8 XCDs, each with its own L2.  `wg` is the recorded workgroup:
+  // head-major, the last query block of a head first.
   uint32_t wg = blockIdx.x;
-  if (((g.n_wg / q_blocks) & 7u) == 0u) {
-    const uint32_t xcd = blockIdx.x & 7u, j = blockIdx.x >> 3;
-    wg = ((j / q_blocks) * 8u + xcd) * q_blocks + j % q_blocks;
+  if (g.causal == 0u) {
+    // every XCD takes a run of consecutive workgroups, so that it reads the K and V of few heads
+    const uint32_t xcd = blockIdx.x & 7u, rest = g.n_wg & 7u;
+    wg = xcd * (g.n_wg >> 3) + (xcd < rest ? xcd : rest) + (blockIdx.x >> 3);
+  } else {
+    // Causal work per block grows with its index.  All blocks of a (batch, head) go to one XCD where the heads can be
+    // dealt out evenly, so that its K and V (2 MiB at 4096 keys) are fetched into one L2 once instead of into all
+    // eight; as many heads as the XCD (the chip) has places for at a time are taken together, the longest blocks of
+    // all of them first.  One head after the other, its long blocks start late and the last ones run on alone: 32
+    // blocks and 16 heads per XCD take 292 times as long as one KV tile on 64 places, 264 with two heads together.
+    const uint32_t heads = g.n_wg / q_blocks, per_xcd = (heads & 7u) == 0u ? 1u : 0u;
+    const uint32_t xcd = per_xcd ? blockIdx.x & 7u : 0u, j = per_xcd ? blockIdx.x >> 3 : blockIdx.x;
+    const uint32_t mine = per_xcd ? heads >> 3 : heads, places = per_xcd ? 64u : 512u;
+    const uint32_t together = places > q_blocks ? places / q_blocks : 1u;
+    const uint32_t group = j / (together * q_blocks), in = j - group * (together * q_blocks);
+    const uint32_t left = mine - group * together, n = left < together ? left : together;
+    const uint32_t block = in / n, h = group * together + in - block * n;
+    wg = (per_xcd ? h * 8u + xcd : h) * q_blocks + block;
   }
-  // long (late) query blocks first: causal work per block grows with its index
   const uint32_t qb = q_blocks - 1u - (wg % q_blocks);
   const uint32_t bh = wg / q_blocks;
   const size_t head = (size_t)bh * g.S * kD;
@@ -128,53 +155,59 @@ __global__ __launch_bounds__(kAttnThreads, 2) void kp_attn_fwd(AttnArgs g) {
   for (int s = 0; s < 8; ++s)
     qf[s] = *reinterpret_cast<const bf16x8*>(g.Q + head + (size_t)qrow * kD + 16 * s + 8 * h32);
 
-  // global -> LDS: either tile is 16 blocks of 1 KiB (four rows); wave w loads blocks 4 w .. 4 w + 3 of it.
-  // Lane i of block j is row 4 j + i / 16, chunk position i % 16.
-  const uint32_t lds0 = kp::wave_uniform((uint32_t)(uintptr_t)smem + 4096u * wave);
-  const uint16_t* k_src[4];
-  const uint16_t* v_src[4];
-#pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    const uint32_t row = 16u * wave + 4u * (uint32_t)i + (lane >> 4), pos = lane & 15u;
-    k_src[i] = g.K + head + (size_t)row * kD + ((pos ^ (row & 15u)) << 3);
-    v_src[i] = g.V + head + (size_t)row * kD + ((pos ^ (4u * (row & 3u))) << 3);
+  // global -> LDS: either tile is 16 blocks of 1 KiB (four rows); wave w loads blocks w, w + 4, w + 8 and w + 12 of it.
+  // Lane i of block j is row 4 j + i / 16, chunk position i % 16: rows 16 apart have the same swizzle, so that the
+  // four loads of a tile share one lane offset and their scalar bases are 16 rows apart.
+  const uint32_t lds0 = kp::wave_uniform((uint32_t)(uintptr_t)smem + 1024u * wave);
+  uint32_t k_ofs, v_ofs;  // bytes
+  {
+    const uint32_t row = 4u * wave + (lane >> 4), pos = lane & 15u;
+    k_ofs = row * kRow + ((pos ^ row) << 4);
+    v_ofs = row * kRow + ((pos ^ (4u * (row & 3u))) << 4);
   }
   // One load: M0 (the LDS base) is put back afterwards, the compiler does not expect inline assembly to change
   // it.  From inline assembly because the compiler would make the next LDS access of any kind wait for such a
   // load; hidden from its count of outstanding vector-memory operations the loads still complete in order, and
   // the kernel waits for them itself in front of the barrier that precedes the tile's use.
-  auto direct_load = [&](const uint16_t* src, uint32_t dst) {
+  auto load_block = [&](const uint16_t* base, uint32_t ofs, uint32_t dst) __attribute__((always_inline)) {
     uint32_t saved_m0;
-    asm volatile("s_mov_b32 %0, m0\n\ts_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off\n\ts_mov_b32 m0, %0"
-                 : "=&s"(saved_m0) : "v"(src), "s"(dst) : "memory");
+    asm volatile("s_mov_b32 %0, m0\n\ts_mov_b32 m0, %3\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2\n\ts_mov_b32 m0, %0"
+                 : "=&s"(saved_m0) : "v"(ofs), "s"(base), "s"(dst) : "memory");
   };
-  auto load_k = [&](uint32_t kv0) {
-#pragma unroll
-    for (int i = 0; i < 4; ++i) direct_load(k_src[i] + (size_t)kv0 * kD, lds0 + (uint32_t)i * 1024u);
-  };
-  auto load_v = [&](uint32_t kv0) {
-#pragma unroll
-    for (int i = 0; i < 4; ++i) direct_load(v_src[i] + (size_t)kv0 * kD, lds0 + kKBytes + (uint32_t)i * 1024u);
+  const uint16_t* k_next = g.K + head;  // the K and V tile requested next
+  const uint16_t* v_next = g.V + head;
+  uint32_t v_into = kKBytes;   // LDS offset of the V buffer that the next tile goes to
+  uint32_t v_other = kVBytes;  // from the V buffer in use to the other one
+  auto load_k = [&](int i) __attribute__((always_inline)) { load_block(k_next + i * 16 * kD, k_ofs, lds0 + 4096u * (uint32_t)i); };
+  auto load_v = [&](int i) __attribute__((always_inline)) { load_block(v_next + i * 16 * kD, v_ofs, lds0 + v_into + 4096u * (uint32_t)i); };
+  auto tiles_requested = [&]() __attribute__((always_inline)) {
+    k_next += kBkv * kD;
+    v_next += kBkv * kD;
+    v_into ^= kKBytes ^ (kKBytes + kVBytes);
   };
   // operand reads: K row 32 tk + l32, chunk 2 s + h32; V for the kv of MFMA step (tk, s) and the d of tile dt
   uint32_t k_rd[8], v_rd[4];
 #pragma unroll
-  for (int sx = 0; sx < 8; ++sx) k_rd[sx] = l32 * kRow + (((2u * (uint32_t)sx + h32) ^ (l32 & 15u)) << 4);
+  for (int sx = 0; sx < 8; ++sx) k_rd[sx] = (uint32_t)(uintptr_t)smem + l32 * kRow + (((2u * (uint32_t)sx + h32) ^ (l32 & 15u)) << 4);
   {
     const uint32_t i = lane & 15u, grp = lane >> 4;  // groups 0, 1: d 0-15, 16-31 of the tile; 2, 3 the same for h = 1
 #pragma unroll
     for (int dt = 0; dt < 4; ++dt) {
       const uint32_t d = 32u * (uint32_t)dt + 16u * (grp & 1u) + 4u * (i & 3u);
-      v_rd[dt] = (4u * (grp >> 1) + (i >> 2)) * kRow + (((d >> 3) ^ (4u * (i >> 2))) << 4) + 8u * ((d >> 2) & 1u);
+      v_rd[dt] = (uint32_t)(uintptr_t)smem + kKBytes + (4u * (grp >> 1) + (i >> 2)) * kRow + (((d >> 3) ^ (4u * (i >> 2))) << 4) + 8u * ((d >> 2) & 1u);
     }
   }
+  auto read_k = [&](int s, int tk) -> bf16x8 {
+    typedef const __attribute__((address_space(3))) bf16x8* lds_bf16x8;
+    return *(lds_bf16x8)(uintptr_t)(k_rd[s] + (uint32_t)tk * 32u * kRow);
+  };
   auto read_v = [&](uint32_t kv_step, int dt) -> bf16x8 {  // kv_step: first kv of the MFMA step (a multiple of 16)
     typedef short s16x4 __attribute__((ext_vector_type(4)));
     typedef short s16x8 __attribute__((ext_vector_type(8)));
     typedef __attribute__((address_space(3))) s16x4* lds_s16x4;
-    const unsigned char* at = sV + v_rd[dt] + kv_step * kRow;
-    const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4)(at));
-    const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4)(at + 8u * kRow));
+    const uint32_t at = v_rd[dt] + kv_step * kRow;
+    const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4)(uintptr_t)(at));
+    const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4)(uintptr_t)(at + 8u * kRow));
     const s16x8 v = {lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
     return __builtin_bit_cast(bf16x8, v);
   };
@@ -185,64 +218,87 @@ __global__ __launch_bounds__(kAttnThreads, 2) void kp_attn_fwd(AttnArgs g) {
   float m_run = -INFINITY, l_run = 0.f;
 
   const uint32_t n_tiles = g.causal ? (q0 + kBq) / kBkv : g.S / kBkv;
-  // Staging overlaps arithmetic: the K tile is only read by region 0 and the V tile only by region 2, so K tile
-  // t+1 is requested behind the barrier that follows region 0 of tile t (and travels while softmax and P V run)
-  // and V tile t+1 behind the barrier that follows region 2 of tile t; each is waited for in front of the
-  // barrier that precedes its use.
-  load_k(0);
-  load_v(0);
+  // Staging overlaps arithmetic.  V tile t+1 goes to the other V buffer and is requested under the first MFMAs of region
+  // 0 of tile t; every wave was done with that buffer before the barrier that ends tile t-1.  K has one buffer, whose
+  // operands are all in registers half-way through region 0: behind a barrier there K tile t+1 is requested, under the
+  // MFMAs that are left.  One wait covers both tiles, in front of the barrier that ends tile t.  The loads are spread over
+  // the MFMAs because all loads of a CU queue up in one unit.
+#pragma unroll
+  for (int i = 0; i < 4; ++i) load_k(i);
+#pragma unroll
+  for (int i = 0; i < 4; ++i) load_v(i);
+  tiles_requested();
+  __builtin_amdgcn_s_waitcnt(kNoLoads);  // (the compiler's own count of outstanding loads: without it the loop would wait for the Q fragments)
   asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
   // One KV tile.  MORE (tile t+1 exists) and MASK (the tile may reach past the diagonal) are compile-time: the
-  // steady-state body has no branch.  Each barrier waits for this wave's LDS traffic and for the tile it
-  // requested one barrier earlier.
-  auto tile = [&](uint32_t t, auto more_c, auto mask_c) {
+  // steady-state body has no branch but the one that moves the softmax reference.
+  bf16x8 kf[8];  // operands of K Q^T, eight MFMAs ahead
+  auto request_k_operands = [&]() __attribute__((always_inline)) {
+#pragma unroll
+    for (int n = 0; n < 8; ++n) kf[n] = read_k(n, 0);
+  };
+  auto tile = [&](uint32_t t, auto more_c, auto mask_c) __attribute__((always_inline)) {
     constexpr bool MORE = decltype(more_c)::value, MASK = decltype(mask_c)::value;
     const uint32_t kv0 = t * kBkv;
+    const bool diag = MASK && g.causal && (kv0 + kBkv > q0 + wave * 32);  // tile reaches past this wave's first row
+    f32x16 sacc[2];  // raw scores of kv0 .. kv0 + 31 and of the 32 behind them
+    sacc[0] = f32x16{0}; sacc[1] = f32x16{0};
+    float mx = -INFINITY;  // maximum of the raw scores; the positive scale is applied afterwards
+    float psum = 0.f;
+    u32x4 pw[4];  // P as packed bf16 pairs, in accumulator order: one entry per MFMA step of V^T P^T (16 kv)
+    auto mask = [&](int tk) __attribute__((always_inline)) {
+      if (!diag) return;
+#pragma unroll
+      for (int v = 0; v < 16; ++v) {
+        const uint32_t kv = kv0 + 32 * tk + 8 * (v >> 2) + 4 * h32 + (v & 3);
+        if (kv > qrow) sacc[tk][v] = -INFINITY;
+      }
+    };
+    auto exps = [&](int pair) __attribute__((always_inline)) {  // probabilities 2 pair and 2 pair + 1 of this lane's 32
+      const int tk = pair >> 3, v = 2 * (pair & 7);
+      const float p0 = __builtin_amdgcn_exp2f(__builtin_fmaf(sacc[tk][v], g.scale_log2, -m_run));
+      const float p1 = __builtin_amdgcn_exp2f(__builtin_fmaf(sacc[tk][v + 1], g.scale_log2, -m_run));
+      psum += p0 + p1;  // fp32 sum of the unrounded probabilities
+      pw[pair >> 2][pair & 3] = bf16_pack_rne(p0, p1);
+    };
 
-    // ---- region 0: S^T = K Q^T, with the staging of V^T tile t threaded in ------------------------
+    // ---- region 0: S^T = K Q^T --------------------------------------------------------------------
     // (opened by the site that closed region 2 of the tile before, or by the one ahead of the loop)
     // The two workgroups of a CU drift apart, so a SIMD usually holds one wave in a matrix region and
     // one in the softmax.  The matrix regions run at a higher wave priority: when both want to issue,
-    // the MFMA goes first and the matrix pipe stays fed, while the softmax fills the gaps (measured:
-    // 3 % faster than equal priorities, the opposite order 3 % slower).
-    __builtin_amdgcn_s_setprio(1);
-    f32x16 sacc[2];
-    sacc[0] = f32x16{0}; sacc[1] = f32x16{0};
+    // the MFMA goes first and the matrix pipe stays fed, while the softmax fills the gaps (equal priorities are
+    // 3-6 % slower; this order of the two products or the other: 1 % apart).
+    __builtin_amdgcn_s_setprio(2);
 #pragma unroll
-    for (int s = 0; s < 8; ++s) {
-#pragma unroll
-      for (int tk = 0; tk < 2; ++tk) {
-        const bf16x8 kf = *reinterpret_cast<const bf16x8*>(sK + k_rd[s] + (uint32_t)tk * 32u * kRow);
-        sacc[tk] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf, qf[s], sacc[tk], 0, 0, 0);
+    for (int n = 0; n < 16; ++n) {  // the lower 32 kv, then the upper ones, whose operands are requested meanwhile
+      const int s = n & 7, tk = n >> 3;
+      sacc[tk] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[s], qf[s], sacc[tk], 0, 0, 0);
+      if (tk == 0) kf[s] = read_k(s, 1);
+      if (MORE && tk == 0 && (s & 1)) load_v(s >> 1);
+      if (MORE && n >= 11 && n < 15) load_k(n - 11);
+      if (tk == 1) {  // the maximum of the lower half
+        if (s == 0) mask(0);
+        mx = fmaxf(fmaxf(mx, sacc[0][2 * s]), sacc[0][2 * s + 1]);
       }
+      __builtin_amdgcn_sched_barrier(0);
       // the three sites of the tile before (ahead of the first tile: the one that opened region 0)
-      if constexpr (INSTR >= 4) if (s == 3) kp::chain_commit<3>(ring);
+      if constexpr (INSTR >= 4) if (n == 10) kp::chain_commit<3>(ring);
+      // every wave has read K tile t
+      if (MORE && n == 9) asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
     }
     __builtin_amdgcn_s_setprio(0);
-
-    // every wave is done with K tile t and V tile t has landed; K tile t+1 travels while softmax and P V run
-    asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
-    // The site sits behind the barrier, not in front of it: in front, the barrier's wait for LDS traffic
-    // would also wait for the two record stores the site has just issued, every tile (measured: 1.5
-    // points of overhead).  The wait at the barrier thereby belongs to the region that ends here.
+    if constexpr (MORE) tiles_requested();
     KP_BOUNDARY(ring, 0, 1);
     KP_CHAIN(0, ring);
-    if constexpr (MORE) load_k(kv0 + kBkv);
 
     // ---- region 1: online softmax (this lane: query row qrow, 32 of the tile's 64 kv) -------------
-    const bool diag = MASK && g.causal && (kv0 + kBkv > q0 + wave * 32);  // tile reaches past this wave's first row
-    float mx = -INFINITY;  // maximum of the raw scores; the positive scale is applied afterwards
+    bf16x8 vf[4];  // operands of one step of V^T P^T
 #pragma unroll
-    for (int tk = 0; tk < 2; ++tk)
+    for (int dt = 0; dt < 4; ++dt) vf[dt] = read_v(0, dt);
+    mask(1);
 #pragma unroll
-      for (int v = 0; v < 16; ++v) {
-        if (diag) {
-          const uint32_t kv = kv0 + 32 * tk + 8 * (v >> 2) + 4 * h32 + (v & 3);
-          if (kv > qrow) sacc[tk][v] = -INFINITY;
-        }
-        mx = fmaxf(mx, sacc[tk][v]);
-      }
-    mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
+    for (int v = 0; v < 16; v += 2) mx = fmaxf(fmaxf(mx, sacc[1][v]), sacc[1][v + 1]);
+    mx = either_half_max(mx);
     // The value the exponentials are taken against only has to keep them in range; it need not be the
     // running maximum.  It moves (and O and l are rescaled) only when some row of the wave exceeds it
     // by more than 2^kSlack, which after the first few tiles practically never happens; until then a
@@ -258,46 +314,41 @@ __global__ __launch_bounds__(kAttnThreads, 2) void kp_attn_fwd(AttnArgs g) {
         for (int v = 0; v < 16; ++v) oacc[dt][v] *= alpha;
       m_run = m_new;
     }
-    float psum = 0.f;
-    uint32_t pk[2][8];  // P as packed bf16 pairs, in accumulator order
 #pragma unroll
-    for (int tk = 0; tk < 2; ++tk)
-#pragma unroll
-      for (int v = 0; v < 16; v += 2) {
-        const float p0 = __builtin_amdgcn_exp2f(__builtin_fmaf(sacc[tk][v], g.scale_log2, -m_run));
-        const float p1 = __builtin_amdgcn_exp2f(__builtin_fmaf(sacc[tk][v + 1], g.scale_log2, -m_run));
-        psum += p0 + p1;  // fp32 sum of the unrounded probabilities
-        pk[tk][v >> 1] = bf16_pack_rne(p0, p1);
-      }
+    for (int i = 0; i < 16; ++i) exps(i);
     l_run += psum;
     KP_BOUNDARY(ring, 1, 2);
     KP_CHAIN(1, ring);
-    __builtin_amdgcn_s_setprio(2);
+    __builtin_amdgcn_s_setprio(1);
 
     // ---- region 2: O^T += V^T P^T ---------------------------------------------------------------------
     // The kv order inside an MFMA step follows the accumulator layout of S^T (kv = 16s + 4h + e for
     // e < 4, 16s + 8 + 4h + e - 4 otherwise), so P needs no cross-lane movement; V^T is read to match.
+    auto pv = [&](int step, int dt) __attribute__((always_inline)) {
+      oacc[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf[dt], __builtin_bit_cast(bf16x8, pw[step]), oacc[dt], 0, 0, 0);
+    };
 #pragma unroll
-    for (int tk = 0; tk < 2; ++tk)
-#pragma unroll
-      for (int s = 0; s < 2; ++s) {
-        u32x4 pw;
-        pw.x = pk[tk][4 * s + 0]; pw.y = pk[tk][4 * s + 1]; pw.z = pk[tk][4 * s + 2]; pw.w = pk[tk][4 * s + 3];
-        const bf16x8 pf = __builtin_bit_cast(bf16x8, pw);
-#pragma unroll
-        for (int dt = 0; dt < 4; ++dt) {
-          oacc[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(read_v(32u * (uint32_t)tk + 16u * (uint32_t)s, dt), pf, oacc[dt], 0, 0, 0);
-        }
-      }
-    __builtin_amdgcn_s_setprio(0);
+    for (int n = 0; n < 12; ++n) {
+      pv(n >> 2, n & 3);
+      vf[n & 3] = read_v(16u * (uint32_t)((n >> 2) + 1), n & 3);
+      __builtin_amdgcn_sched_barrier(0);
+    }
 
-    // every wave is done with V tile t, and K tile t+1 has landed
+    // Every wave has read V tile t, and K and V tile t+1 have landed.  The last four MFMAs come behind the barrier, under
+    // the first operand reads of the next tile.
     asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
-    // One site closes region 2 and opens region 0 of the next tile: a tile costs three sites, not four.
-    // Behind the barrier for the same reason as above.
+    if constexpr (MORE) request_k_operands();
+#pragma unroll
+    for (int dt = 0; dt < 4; ++dt) pv(3, dt);
+#pragma unroll
+    for (int dt = 0; dt < 4; ++dt) v_rd[dt] += v_other;
+    v_other = 0u - v_other;
+    __builtin_amdgcn_s_setprio(0);
+    // One site closes region 2 and opens region 0 of the next tile: a tile costs three sites, not four.  It sits behind
+    // the barrier: in front, the barrier's wait for LDS traffic would also wait for the two record stores that a generic
+    // site has just issued, every tile (1.5 points of overhead).
     if constexpr (MORE) KP_BOUNDARY(ring, 2, 0); else KP_BOUNDARY(ring, 2, kp::kNoRegion);
     KP_CHAIN(2, ring);
-    if constexpr (MORE) load_v(kv0 + kBkv);
   };
   constexpr std::true_type yes{};
   constexpr std::false_type no{};
@@ -305,6 +356,7 @@ __global__ __launch_bounds__(kAttnThreads, 2) void kp_attn_fwd(AttnArgs g) {
   KP_CHAIN(0, ring);  // (the first two fill the first batch and write no record)
   KP_CHAIN(1, ring);
   KP_CHAIN(2, ring);
+  request_k_operands();
   // only the last two tiles of a causal block can reach past the diagonal
   for (uint32_t t = 0; t + 2 < n_tiles; ++t) tile(t, yes, no);
   tile(n_tiles - 2, yes, yes);
@@ -376,7 +428,7 @@ extern "C" kp_status kp_attn_instrumented(const void* Q, const void* K, const vo
   g.group_log2 = group_log2;
   g.collab = collab ? 1u : 0u;
   g.flags = (flush ? KP_FLAG_FLUSH : 0u) | (realtime ? KP_FLAG_REALTIME : 0u) | (collab ? KP_FLAG_HW_IDS : 0u);
-  const uint32_t tile_bytes = kKBytes + kVBytes;
+  const uint32_t tile_bytes = kKBytes + 2 * kVBytes;
   if (regions == 0) {
     hipLaunchKernelGGL(kp_attn_fwd<0>, dim3(n_wg), dim3(kAttnThreads), tile_bytes, st, g);
     KP_HIP_TRY(hipGetLastError());

@@ -83,6 +83,28 @@ def test_heads_in_multiples_of_eight_take_the_xcd_mapping(kp):
     assert (hdr[:, 8] == want).all()
 
 
+@pytest.mark.parametrize("causal", [True, False])
+@pytest.mark.parametrize("B,H,S", [(1, 7, 384), (2, 20, 256), (1, 24, 4224), (1, 16, 4096), (1, 3, 128 * 65), (1, 8, 128 * 65)])
+def test_every_workgroup_order(kp, B, H, S, causal):
+    """How workgroups are dealt out depends on the mask, on whether the heads divide among the 8 XCDs and on how many
+    heads are taken together (all of them, a last group that is not full, one): every query block must come out, under
+    its own workgroup id.  A causal row q of V = key index + 1 averages to (q + 2) / 2 when Q is zero."""
+    D, blocks = 128, S // 128
+    Q = torch.zeros(B, H, S, D, dtype=torch.bfloat16, device="cuda")
+    K = torch.randn(B, H, S, D, device="cuda", generator=torch.Generator("cuda").manual_seed(S)).to(torch.bfloat16)
+    V = torch.arange(1, S + 1, device="cuda", dtype=torch.float32).view(1, 1, S, 1) / S + torch.arange(B * H, device="cuda").view(B, H, 1, 1)
+    V = V.expand(B, H, S, D).to(torch.bfloat16).contiguous()
+    O, trace, (n_wg, waves, _) = run_attn(kp, Q, K, V, causal, 0b010, trace_cap=8, dev=(Q, K, V))
+    v = V[..., 0].double()
+    want = v.cumsum(2) / torch.arange(1, S + 1, device="cuda", dtype=torch.float64) if causal else v.mean(2, keepdim=True).expand(B, H, S)
+    # (equal probabilities, exact in bf16; the sums are fp32, the result is rounded once to bf16: 2^-9)
+    assert ((O.double() - want.unsqueeze(3)).abs() <= 2.0 ** -8 * want.unsqueeze(3)).all()
+    hdr = trace.cpu().numpy().view(np.uint32)[16:16 + 32 * n_wg].reshape(n_wg, 32)
+    assert (hdr[:, 0] == np.arange(n_wg)).all()
+    tiles = 2 * (blocks - np.arange(n_wg) % blocks) if causal else np.full(n_wg, 2 * blocks)
+    assert (hdr[:, 8:8 + waves] == 2 * tiles[:, None]).all()
+
+
 def test_attention_special_cases(kp):
     q, k, v = inputs.attn_inputs(1, 1, 256, 128, seed=8)
     vc = torch.full_like(v, 0.75)
