@@ -107,14 +107,18 @@ struct GemmChain {
 // ------------------------------------------------------------------------------------------
 // 64x64x32 tile, 4 waves as 2x2, each wave one 32x32 accumulator tile.
 //
-// What bounds it: with few workgroups the latency of a K step, with many the L1 and LDS traffic of so small a tile
-// (8 KiB through either per workgroup and K step against 64 cycles of MFMAs).  So the global loads run two pairs
-// of K steps ahead in registers, the two LDS stages hold a pair each (one barrier per pair), B is stored as it
-// comes and transposed by the operand read, and up to five workgroups share a CU.  Measured (median of passes in
-// a row), against one stage, loads waited for where they are issued, two barriers per K step: 2112x1984x2080
-// 57 -> 34 us (512 TFLOP/s), 4032x3968x4000 318 -> 233 us, 128x128x3776 (4 workgroups) 53 -> 18 us; with all
-// regions recorded 429 -> 266 us and 73 -> 29 us.  Three pairs ahead: 3 % slower where many workgroups share a CU
-// (registers), nothing gained with few.  Plain order of the tiles instead of bands per XCD: 39 us.
+// What bounds it: with few workgroups the latency of a K step, with many the L2 -> L1 traffic of so small a tile (16 KiB
+// per workgroup and pair of K steps: 545 MB of 128-byte lines, none of which hits in L1, at 16-18 TB/s; with the loads
+// left out 2112x1984x2080 takes 28 of 36 us, with the LDS stores left out too 19, with half the operand reads left out
+// 35).  So the global loads run two pairs of K steps ahead in registers, the two LDS stages hold a pair each (one barrier
+// per pair), B is stored as it comes and transposed by the operand read, and up to five workgroups share a CU.  The
+// loop is one block without exits, in which the loads stand where they are written (with an exit behind every K step the
+// compiler put them behind it, and waited for all of them once in two pairs), a lane's addresses move by one 64-bit
+// addition per pair, and what needs to look at the end of K comes behind the loop.  Against the form with exits (median of
+// passes in a row): 2112x1984x2080 32.8 -> 31.1 us (560 TFLOP/s), all regions recorded 42.5 -> 36.5; 4032x3968x4000 223
+// -> 217, recorded 249 -> 228; 128x128x3776 (4 workgroups) 18.3 -> 16.3, recorded 29.3 -> 21.2.  Three pairs ahead: 3 %
+// slower where many workgroups share a CU (registers), nothing gained with few.  Plain order of the tiles instead of bands
+// per XCD: 39 us; four neighbouring tiles on one CU, to share panels in L1: no hits, 3 % slower.
 //
 // The sequence of its record sites (n in all): the first opens region 0, then three per K step close regions
 // 0, 1 and 2 and open the next, the last only closes.
@@ -162,19 +166,32 @@ __global__ __launch_bounds__(256) void kp_gemm_small(GemmArgs g) {
   const uint32_t row = tid >> 3, chunk = tid & 7u;
   const uint32_t a_dst = row * 128u + ((chunk ^ ((row >> 1) & 7u)) << 4);              // (row + 32: + 4096)
   const uint32_t b_dst = A_BYTES + row * 128u + ((chunk ^ (((row >> 1) & 1u) << 2)) << 4);
-  const uint16_t* a_src = g.A + (size_t)(m0 + row) * g.K;
-  const uint16_t* b_src = g.B + n0 + chunk * 8u;
+  const uint32_t PAIRS = (KT + 1u) / 2u;
   u32x4 ra[AHEAD][2], rb[AHEAD][2];
-  // (what lies past the last K step is asked for as the last chunk or row of the matrix and never used)
-  auto request_a = [&](uint32_t pair, int set) __attribute__((always_inline)) {
-    const uint32_t k = pair * (2 * BK) + chunk * 8u, kc = k < g.K ? k : g.K - 8u;
-    ra[set][0] = *reinterpret_cast<const u32x4*>(a_src + kc);
-    ra[set][1] = *reinterpret_cast<const u32x4*>(a_src + (size_t)32u * g.K + kc);
+  // This lane's addresses in the pair requested last; every request moves them on (behind the site that opens its region:
+  // the distance is opaque), up to the last pair, which is then asked for again (nobody uses it: a K step without loads
+  // would have an empty region 0).  LAST: the pair may be the first or the last one, and of one K step only; what would
+  // lie behind it is asked for as the same of the first step.
+  const uint16_t* a_src = g.A + (size_t)(m0 + row) * g.K + chunk * 8u;
+  const uint16_t* b_src = g.B + (size_t)row * g.N + n0 + chunk * 8u;
+  const size_t a_down = (size_t)32u * g.K, b_down = (size_t)32u * g.N;
+  auto request_a = [&](uint32_t pair, int set, auto last_c) __attribute__((always_inline)) {
+    constexpr bool LAST = decltype(last_c)::value;
+    size_t on = !LAST || (pair > 0u && pair < PAIRS) ? 2u * BK : 0u;
+    asm volatile("" : "+s"(on) : : "memory");
+    a_src += on;
+    const uint16_t* at = a_src;
+    if (LAST && pair + 1u >= PAIRS && (KT & 1u) && chunk >= 4u) at -= BK;
+    ra[set][0] = *reinterpret_cast<const u32x4*>(at);
+    ra[set][1] = *reinterpret_cast<const u32x4*>(at + a_down);
   };
-  auto request_b = [&](uint32_t pair, int set) __attribute__((always_inline)) {
-    const uint32_t k0 = pair * (2 * BK) + row, k1 = k0 + 32u;
-    rb[set][0] = *reinterpret_cast<const u32x4*>(b_src + (size_t)(k0 < g.K ? k0 : g.K - 1u) * g.N);
-    rb[set][1] = *reinterpret_cast<const u32x4*>(b_src + (size_t)(k1 < g.K ? k1 : g.K - 1u) * g.N);
+  auto request_b = [&](uint32_t pair, int set, auto last_c) __attribute__((always_inline)) {
+    constexpr bool LAST = decltype(last_c)::value;
+    size_t on = !LAST || (pair > 0u && pair < PAIRS) ? 2u * b_down : 0u;
+    asm volatile("" : "+s"(on) : : "memory");
+    b_src += on;
+    rb[set][0] = *reinterpret_cast<const u32x4*>(b_src);
+    rb[set][1] = *reinterpret_cast<const u32x4*>(b_src + (LAST && pair + 1u >= PAIRS && (KT & 1u) ? 0u : b_down));
   };
   auto store_a = [&](uint32_t stage, int set) __attribute__((always_inline)) {
     *reinterpret_cast<u32x4*>(tiles + stage * STAGE + a_dst) = ra[set][0];
@@ -184,8 +201,10 @@ __global__ __launch_bounds__(256) void kp_gemm_small(GemmArgs g) {
     *reinterpret_cast<u32x4*>(tiles + stage * STAGE + b_dst) = rb[set][0];
     *reinterpret_cast<u32x4*>(tiles + stage * STAGE + b_dst + 4096u) = rb[set][1];
   };
+  constexpr std::true_type yes{};
+  constexpr std::false_type no{};
 #pragma unroll
-  for (int i = 0; i < AHEAD; ++i) { request_a((uint32_t)i, i); request_b((uint32_t)i, i); }
+  for (int i = 0; i < AHEAD; ++i) { request_a((uint32_t)i, i, yes); request_b((uint32_t)i, i, yes); }
 
   kp::Ring ring{};
   if constexpr (INSTR != 0)
@@ -225,45 +244,67 @@ __global__ __launch_bounds__(256) void kp_gemm_small(GemmArgs g) {
   store_b(0, 0);
   asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
   KP_SITE_K(ring, 0, kp::kNoRegion, 0);
-  // K step 2 pair + HALF; the registers of pair p are set p % AHEAD
-  auto step = [&](uint32_t pair, auto half_c, int set, int next) __attribute__((always_inline)) {
-    constexpr int HALF = decltype(half_c)::value;
-    const uint32_t s = pair & 1u;
+  // One pair of K steps; the registers of pair p are set p % AHEAD.  TAIL: the pair or one requested here may be the last.
+  auto pair_of_steps = [&](uint32_t pair, int set, auto tail_c) __attribute__((always_inline)) {
+    constexpr bool TAIL = decltype(tail_c)::value;
+    const uint32_t s = (uint32_t)set;  // LDS stage
+    const unsigned char* stage = tiles + s * STAGE;
+    bf16x8 af[4], bf[4];
+    auto operands = [&](int first) __attribute__((always_inline)) {
+#pragma unroll
+      for (int i = first; i < first + 2; ++i) {
+        af[i] = *reinterpret_cast<const bf16x8*>(stage + a_rd[i]);
+        bf[i] = read_b(stage, i);
+      }
+      __builtin_amdgcn_sched_barrier(0);
+    };
     // ---- region 0: the global loads of pair + AHEAD are issued -----------------------------------
-    if (HALF == 0) request_a(pair + AHEAD, set); else request_b(pair + AHEAD, set);
+    request_a(pair + AHEAD, set, tail_c);
+    __builtin_amdgcn_sched_barrier(0);
     KP_SITE_K(ring, 1, 0, 1);
     // ---- region 1: the operands of this K step are requested from LDS, pair + 1 goes to the other stage
-    // (behind the last pair: nobody reads it).  The requests come first and stay on this side of the site: behind
+    // (if there is one).  The requests come first and stay on this side of the site: behind
     // it they would be waited for together with its clock (29 against 33 us with four workgroups, recorded).
-    const unsigned char* stage = tiles + s * STAGE;
-    bf16x8 af[2], bf[2];
-#pragma unroll
-    for (int i = 0; i < 2; ++i) {
-      af[i] = *reinterpret_cast<const bf16x8*>(stage + a_rd[2 * HALF + i]);
-      bf[i] = read_b(stage, 2 * HALF + i);
-    }
-    if (HALF == 0) store_a(s ^ 1u, next); else store_b(s ^ 1u, next);
+    operands(0);
+    if (!TAIL || pair + 1u < PAIRS) store_a(s ^ 1u, set ^ 1);
     KP_SITE_K(ring, 2, 1, 2);
-    // ---- region 2: MFMA, and behind a pair the barrier after which the other stage may be read and this one
-    // written
+    // ---- region 2: MFMA
 #pragma unroll
     for (int i = 0; i < 2; ++i) acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(bf[i], af[i], acc, 0, 0, 0);
     KP_COMMIT(ring, 3);
-    if (HALF == 1) asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
-    if (2u * pair + HALF + 1u < KT) KP_SITE_K(ring, 0, 2, 0); else KP_SITE_K(ring, 0, 2, kp::kNoRegion);
+    if (TAIL && 2u * pair + 1u >= KT) {
+      KP_SITE_K(ring, 0, 2, kp::kNoRegion);
+      return;
+    }
+    KP_SITE_K(ring, 0, 2, 0);
+    __builtin_amdgcn_sched_barrier(0);
+    // ---- the same for the second K step; behind it the barrier after which the other stage may be read and this one
+    // written
+    request_b(pair + AHEAD, set, tail_c);
+    __builtin_amdgcn_sched_barrier(0);
+    KP_SITE_K(ring, 1, 0, 1);
+    operands(2);
+    if (!TAIL || pair + 1u < PAIRS) store_b(s ^ 1u, set ^ 1);
+    KP_SITE_K(ring, 2, 1, 2);
+#pragma unroll
+    for (int i = 2; i < 4; ++i) acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(bf[i], af[i], acc, 0, 0, 0);
+    KP_COMMIT(ring, 3);
+    asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+    if (!TAIL || 2u * pair + 2u < KT) KP_SITE_K(ring, 0, 2, 0); else KP_SITE_K(ring, 0, 2, kp::kNoRegion);
   };
-  constexpr std::integral_constant<int, 0> even{};
-  constexpr std::integral_constant<int, 1> odd{};
   static_assert(AHEAD == 2, "the K loop is unrolled by two pairs");
-  for (uint32_t pair = 0;; pair += 2u) {
-    step(pair, even, 0, 1);
-    if (2u * pair + 1u >= KT) break;
-    step(pair, odd, 0, 1);
-    if (2u * pair + 2u >= KT) break;
-    step(pair + 1u, even, 1, 0);
-    if (2u * pair + 3u >= KT) break;
-    step(pair + 1u, odd, 1, 0);
-    if (2u * pair + 4u >= KT) break;
+  uint32_t pair = 0;
+  for (; 2u * (pair + 5u) <= KT; pair += 2u) {  // (both pairs requested in an iteration have two K steps, and eight steps are not worth one)
+    pair_of_steps(pair, 0, no);
+    pair_of_steps(pair + 1u, 1, no);
+  }
+#pragma unroll
+  for (int i = 0; i < 3; ++i) {  // at most five pairs are left; written out, so that the compiler waits for the loads it has to
+    if (pair >= PAIRS) break;
+    pair_of_steps(pair, 0, yes);
+    if (pair + 1u >= PAIRS) break;
+    pair_of_steps(pair + 1u, 1, yes);
+    pair += 2u;
   }
 
   // epilogue, transposed tile: register v of lane l is C[m, n] with m = l%32 and n = 8*(v/4) + 4*(l/32) + v%4

@@ -312,6 +312,20 @@ def test_small_tile_k_pairs_and_chained_sites(kp, K, regions, opts):
     assert (np.diff(ts, axis=2) >= 0).all() and (ts > 0).all()
 
 
+@pytest.mark.parametrize("steps", list(range(1, 24)) + [40, 65])
+def test_small_tile_every_number_of_k_steps(kp, steps):
+    """The K loop takes two pairs of K steps at a time and leaves up to ten steps to what follows it, the last pair of which
+    may hold one step: every remainder, C against the fp64 oracle and bit-identical with sites, and the operands at the end
+    of their allocations."""
+    M, N, K = 128, 192, 32 * steps
+    a, b = inputs.gemm_inputs(M, N, K, seed=steps)
+    c0, _, _ = run_gemm(kp, a, b, 0)
+    assert_close_to_oracle(c0, a, b)
+    c1, _, _ = run_gemm(kp, a, b, 0b111, trace_cap=64)
+    c2, _, _ = run_gemm(kp, a, b, 0b011 | kp.KP_MASK_COLLAB, trace_cap=64)
+    assert torch.equal(c1.view(torch.int16), c0.view(torch.int16)) and torch.equal(c2.view(torch.int16), c0.view(torch.int16))
+
+
 @pytest.mark.parametrize("M,N", [(64 * 32, 64 * 33), (64 * 31, 64 * 33), (64 * 41, 64 * 25)])
 @pytest.mark.parametrize("K,opts", [(32, "0"), (96, "realtime"), (160, "group"), (224, "0"), (288, "0")])
 def test_small_tile_many_workgroups_short_k(kp, M, N, K, opts):
