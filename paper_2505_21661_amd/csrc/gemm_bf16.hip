@@ -58,12 +58,6 @@ __device__ __forceinline__ uint32_t tile_off(uint32_t row, uint32_t chunk) {
   return row * 128u + ((chunk ^ ((row >> 1) & 7u)) << 4);  // byte offset
 }
 
-// Same, for the transposed B tile of the large kernel (BK = 64): its 16-byte writes come from lanes
-// whose rows are 8 apart, so the swizzle also folds in the next three row bits.
-__device__ __forceinline__ uint32_t tile_off_bt(uint32_t row, uint32_t chunk) {
-  return row * 128u + ((chunk ^ ((row ^ (row >> 3)) & 7u)) << 4);
-}
-
 // END of one region and START of the next with a single clock sample.  INSTR: 0 no record sites,
 // 1 generic sites (region mask, either buffer strategy, either store), 3 the same on the constant-rate
 // clock, 2 chained sites (circular, one lane stores; the region mask and wave-group records included), 5 chained
@@ -445,8 +439,8 @@ __global__ __launch_bounds__(256) void kp_gemm_short(GemmArgs g) {
 // LDS holds two stages of the A tile [256][64] and of the B tile (128 KiB); the K loop is software-pipelined
 // over the two stages.  Default schedule: while the MFMAs consume stage s, the tiles of K step +1 travel from
 // global memory straight to stage s^1 (no staging registers; B stays row-major and is transposed by the LDS
-// read).  Stage-by-stage schedule: K step +1 moves from staging registers to stage s^1 (B transposed in
-// registers into a [256 n][64 k] tile) and the global loads of K step +2 are in flight.
+// read).  Stage-by-stage schedule: K step +1 moves from staging registers to the same places of stage s^1 and the global
+// loads of K step +2 are in flight.
 // MFMA operands are swapped (B^T rows as the first operand) so that a lane ends up with four
 // consecutive columns of one C row per accumulator quad and can store them as 8 bytes.
 constexpr int kBigBM = 256, kBigBN = 256, kBigBK = 64;
@@ -507,8 +501,9 @@ __global__ __launch_bounds__(WAVES * 64) void kp_gemm_big(GemmArgs g) {
   // Every thread stages the same share of a K step, so all waves reach the barrier together:
   //   A: 256 rows x 8 chunks of 16 bytes; thread t takes chunk (t & 7) of rows (t >> 3) + (T/8)*i;
   //   B: blocks of 4 k x 8 n, 16 x 32 of them; thread t takes blocks t + T*j (k quad id >> 5, n block
-  //      id & 31), loads the four rows of each (16 bytes each) and transposes them in registers into
-  //      eight 8-byte k-runs, one per column of the transposed tile.
+  //      id & 31) and stores the four rows of each (16 bytes) as they come; the operand reads transpose.
+  //      (Transposed in registers, 16 v_perm_b32 and eight 8-byte stores of which every pass took two cycles,
+  //      the LDS write stage took 911 ticks per K step of a 2048x4096x4096 launch instead of 775, and the launch 4 us more.)
   // 2048/T + 4*(512/T) 16-byte global loads per thread and K step: vector-memory instructions are
   // issued at a fixed rate per CU whatever their width, so wide loads keep the issue time short.
   const uint32_t a_row = tid >> 3, a_chunk = tid & 7u;
@@ -516,8 +511,10 @@ __global__ __launch_bounds__(WAVES * 64) void kp_gemm_big(GemmArgs g) {
   uint32_t a_dst[NA];  // LDS byte offsets inside a stage
 #pragma unroll
   for (int i = 0; i < NA; ++i) a_dst[i] = tile_off<BK>(a_row + (T / 8) * i, a_chunk);
-  // column c of a block goes to row 8*nb + c of the transposed tile, chunk kq / 2, half kq % 2
   const uint32_t b_nb = tid & 31u;
+  uint32_t b_dst[4];  // row i of the block: k = 4 (k quad) + i, chunk nb at position nb ^ 4 (k % 4)
+#pragma unroll
+  for (int i = 0; i < 4; ++i) b_dst[i] = A_BYTES + (4u * (tid >> 5) + (uint32_t)i) * 512u + ((b_nb ^ (4u * (uint32_t)i)) << 4);
   const uint16_t* src_b = g.B + (size_t)((tid >> 5) * 4) * g.N + n0 + b_nb * 8;
 
   u32x4 la[NA], lb[NB][4];  // staging registers: A chunks, B rows
@@ -530,19 +527,8 @@ __global__ __launch_bounds__(WAVES * 64) void kp_gemm_big(GemmArgs g) {
   auto store_a = [&](uint32_t stage, int i) {
     *reinterpret_cast<u32x4*>(smem + stage * STAGE + a_dst[i]) = la[i];
   };
-  // word w of the four rows holds columns 2w (low halves) and 2w+1 (high halves)
-  auto store_b = [&](uint32_t stage, int j, int w) {
-    unsigned char* sB = smem + stage * STAGE + A_BYTES;
-    const uint32_t kq = (tid >> 5) + (T / 32) * (uint32_t)j;
-    const uint32_t w0 = lb[j][0][w], w1 = lb[j][1][w], w2 = lb[j][2][w], w3 = lb[j][3][w];
-    u32x2 ev, od;
-    // low halves / high halves of two words side by side: one v_perm_b32 each (bytes 0-3 of the
-    // selector's space are the second operand, 4-7 the first)
-    ev.x = __builtin_amdgcn_perm(w1, w0, 0x05040100u); ev.y = __builtin_amdgcn_perm(w3, w2, 0x05040100u);
-    od.x = __builtin_amdgcn_perm(w1, w0, 0x07060302u); od.y = __builtin_amdgcn_perm(w3, w2, 0x07060302u);
-    const uint32_t n = b_nb * 8u + 2u * (uint32_t)w;
-    *reinterpret_cast<u32x2*>(sB + tile_off_bt(n, kq >> 1) + (kq & 1u) * 8u) = ev;
-    *reinterpret_cast<u32x2*>(sB + tile_off_bt(n + 1u, kq >> 1) + (kq & 1u) * 8u) = od;
+  auto store_b = [&](uint32_t stage, int j, int i) {
+    *reinterpret_cast<u32x4*>(smem + stage * STAGE + b_dst[i] + (uint32_t)j * (T / 32) * 2048u) = lb[j][i];
   };
 
   // ---- global -> LDS (default schedule) ------------------------------------------------------
@@ -772,21 +758,29 @@ __global__ __launch_bounds__(WAVES * 64) void kp_gemm_big(GemmArgs g) {
     }
     KP_SITE_K(ring, 2, 0, 3);
     stage_fence();
+    // The operands of MFMA step ks + 1 are requested between the MFMAs of step ks, in the order of their use: the stage
+    // takes 1227 ticks of a wave (32 MFMAs alone: 1056).  All of a step's ahead of the step before's MFMAs 1456, ahead of
+    // its own MFMAs 1313; 2048x4096x4096 recorded 106, 117.5 and 117 us.
+    bf16x8 af[2][4], bfr[2][TN];
+    auto read_operand = [&](int ks, int which) __attribute__((always_inline)) {
+      if (which < TN) bfr[ks & 1][which] = read_b(sB, ks, which);
+      else if (which < TN + 4)
+        af[ks & 1][which - TN] = *reinterpret_cast<const bf16x8*>(
+            sA + tile_off<BK>(wm * 128 + (which - TN) * 32 + (lane & 31u), (uint32_t)ks * 2u + (lane >> 5)));
+    };
+#pragma unroll
+    for (int which = 0; which < TN + 4; ++which) read_operand(0, which);
+    if constexpr (SCHEDULE == 1) __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
     for (int ks = 0; ks < BK / 16; ++ks) {
-      const uint32_t chunk = ks * 2 + (lane >> 5);
-      bf16x8 af[4], bfr[TN];
 #pragma unroll
       for (int tm = 0; tm < 4; ++tm)
-        af[tm] = *reinterpret_cast<const bf16x8*>(sA + tile_off<BK>(wm * 128 + tm * 32 + (lane & 31u), chunk));
 #pragma unroll
-      for (int tn = 0; tn < TN; ++tn)
-        bfr[tn] = *reinterpret_cast<const bf16x8*>(sB + tile_off_bt(wn * (32 * TN) + tn * 32 + (lane & 31u), chunk));
-#pragma unroll
-      for (int tn = 0; tn < TN; ++tn)
-#pragma unroll
-        for (int tm = 0; tm < 4; ++tm)
-          acc[tn][tm] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(bfr[tn], af[tm], acc[tn][tm], 0, 0, 0);
+        for (int tn = 0; tn < TN; ++tn) {
+          acc[tn][tm] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(bfr[ks & 1][tn], af[ks & 1][tm], acc[tn][tm], 0, 0, 0);
+          if (ks + 1 < BK / 16) read_operand(ks + 1, TN * tm + tn);
+          if constexpr (SCHEDULE == 1) __builtin_amdgcn_sched_barrier(0);
+        }
     }
     asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");  // (nothing of this wave's is in flight any more: see above)
     KP_SITE_K(ring, 3, 3, 1);
