@@ -124,6 +124,30 @@ struct SmallGemmChain {
   __device__ uint32_t start_region(uint32_t site, uint32_t n) const { return site + 1u == n ? kp::kNoRegion : site % 3u; }
 };
 
+// A wave's 32x32 of C, transposed (register v of lane l is C[m, n] with m = l%32 and n = 8*(v/4) + 4*(l/32) + v%4), through
+// 2 KiB of LDS of its own to memory: a lane holds four columns of a row, 32 rows with 16 bytes each per store instruction;
+// this way there are two instead of four, with 64 bytes of 16 rows.  A row is four chunks of 16 bytes; chunk c of row r at
+// position c ^ (r / 2) % 4, its halves swapped where r / 8 is odd: 16 lanes of an 8-byte write hit all banks once.
+__device__ __forceinline__ void c_tile_to_lds(const f32x16& acc, unsigned char* lds) {
+  const uint32_t lane = threadIdx.x & 63u, r = lane & 31u, half = (lane >> 5) ^ ((r >> 3) & 1u);
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    u32x2 pk;
+    pk.x = bf16_pack_rne(acc[4 * q + 0], acc[4 * q + 1]);
+    pk.y = bf16_pack_rne(acc[4 * q + 2], acc[4 * q + 3]);
+    *reinterpret_cast<u32x2*>(lds + r * 64u + (((uint32_t)q ^ ((r >> 1) & 3u)) << 4) + 8u * half) = pk;
+  }
+}
+__device__ __forceinline__ void c_tile_to_memory(const unsigned char* lds, uint16_t* c, uint32_t ldc) {
+  const uint32_t lane = threadIdx.x & 63u, r = lane >> 2, chunk = (lane & 3u) ^ ((r >> 1) & 3u);  // (the same chunk in row r + 16)
+  uint16_t* at = c + (size_t)r * ldc + 8u * chunk;
+#pragma unroll
+  for (int i = 0; i < 2; ++i) {
+    const u32x4 v = *reinterpret_cast<const u32x4*>(lds + 1024u * (uint32_t)i + 16u * lane);
+    *reinterpret_cast<u32x4*>(at + (size_t)(16 * i) * ldc) = (r & 8u) ? u32x4{v.z, v.w, v.x, v.y} : v;
+  }
+}
+
 template <int INSTR>
 __global__ __launch_bounds__(256) void kp_gemm_small(GemmArgs g) {
   constexpr int SITE = (INSTR == 2 || INSTR == 5) ? 6 : INSTR;
@@ -238,6 +262,12 @@ __global__ __launch_bounds__(256) void kp_gemm_small(GemmArgs g) {
   store_b(0, 0);
   asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
   KP_SITE_K(ring, 0, kp::kNoRegion, 0);
+  // The site that closes a K step and opens the next one, if there is one.  (A chained site keeps its clock either way.)
+  auto close = [&](bool last) __attribute__((always_inline)) {
+    if constexpr (SITE == 6) KP_SITE_K(ring, 0, 2, 0);
+    else if (last) KP_SITE_K(ring, 0, 2, kp::kNoRegion);
+    else KP_SITE_K(ring, 0, 2, 0);
+  };
   // One pair of K steps; the registers of pair p are set p % AHEAD.  TAIL: the pair or one requested here may be the last.
   auto pair_of_steps = [&](uint32_t pair, int set, auto tail_c) __attribute__((always_inline)) {
     constexpr bool TAIL = decltype(tail_c)::value;
@@ -266,11 +296,8 @@ __global__ __launch_bounds__(256) void kp_gemm_small(GemmArgs g) {
 #pragma unroll
     for (int i = 0; i < 2; ++i) acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(bf[i], af[i], acc, 0, 0, 0);
     KP_COMMIT(ring, 3);
-    if (TAIL && 2u * pair + 1u >= KT) {
-      KP_SITE_K(ring, 0, 2, kp::kNoRegion);
-      return;
-    }
-    KP_SITE_K(ring, 0, 2, 0);
+    close(TAIL && 2u * pair + 1u >= KT);
+    if (TAIL && 2u * pair + 1u >= KT) return;
     __builtin_amdgcn_sched_barrier(0);
     // ---- the same for the second K step; behind it the barrier after which the other stage may be read and this one
     // written
@@ -284,7 +311,7 @@ __global__ __launch_bounds__(256) void kp_gemm_small(GemmArgs g) {
     for (int i = 2; i < 4; ++i) acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(bf[i], af[i], acc, 0, 0, 0);
     KP_COMMIT(ring, 3);
     asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
-    if (!TAIL || 2u * pair + 2u < KT) KP_SITE_K(ring, 0, 2, 0); else KP_SITE_K(ring, 0, 2, kp::kNoRegion);
+    close(TAIL && 2u * pair + 2u >= KT);
   };
   static_assert(AHEAD == 2, "the K loop is unrolled by two pairs");
   uint32_t pair = 0;
@@ -301,19 +328,14 @@ __global__ __launch_bounds__(256) void kp_gemm_small(GemmArgs g) {
     pair += 2u;
   }
 
-  // epilogue, transposed tile: register v of lane l is C[m, n] with m = l%32 and n = 8*(v/4) + 4*(l/32) + v%4
-  uint16_t* c_row = g.C + (size_t)(m0 + wr * 32u + (lane & 31u)) * g.N + n0 + wc * 32u + 4u * (lane >> 5);
-#pragma unroll
-  for (int q = 0; q < 4; ++q) {
-    u32x2 pk;
-    pk.x = bf16_pack_rne(acc[4 * q + 0], acc[4 * q + 1]);
-    pk.y = bf16_pack_rne(acc[4 * q + 2], acc[4 * q + 3]);
-    *reinterpret_cast<u32x2*>(c_row + 8 * q) = pk;
-  }
+  // (through the stage that the last pair does not read: with an odd number of K steps there is no barrier behind it)
+  unsigned char* c_lds = tiles + (PAIRS & 1u) * STAGE + 2048u * wave;
+  c_tile_to_lds(acc, c_lds);
+  KP_COMMIT(ring, 1);  // the site that closed the last K step
+  c_tile_to_memory(c_lds, g.C + (size_t)(m0 + wr * 32u) * g.N + n0 + wc * 32u, g.N);
   if constexpr (INSTR != 0) {
     kp::TraceGeom tg{g.n_wg, 4u >> g.group_log2, 3, g.cap_hbm, g.flags};
     if constexpr (SITE == 6) {
-      kp::chain_commit<1>(ring);  // the site that closed the last K step
       kp::ring_finish<REALTIME>(ring, g.cap_lds, g.trace, tg, wg, g.rec_cost, SmallGemmChain{});
     } else {
       kp::sites_end<SITE>(ring);
@@ -325,12 +347,13 @@ __global__ __launch_bounds__(256) void kp_gemm_small(GemmArgs g) {
 // The same tile for a short K and many workgroups: one K step at a time, 8 KiB of LDS.  A workgroup is then over
 // before a pipeline has filled, its time is latency and the C tile, and what counts is how many of them share a CU:
 // eight or more here, five of the pipelined kernel's, three of those with a ring of 16 KiB.  Measured, this kernel /
-// the pipelined one, us: 3906 workgroups K = 32 9.1 / 15.7, 160 16.9 / 20.3, 256 23.2 / 24.9, 320 27.6 / 28.2; 8010 K
-// = 288 51.0 / 51.3, 320 57.5 / 54.4; 2205 K = 192 13.1 / 13.8, 224 14.7 / 14.2; 1155 K = 32 4.7 / 6.5, 224 9.1 / 9.0;
-// 930 K = 32 4.7 / 5.7, 160 6.9 / 6.8, 192 7.5 / 7.4; 675 K = 128 5.2 / 5.6, 160 5.8 / 5.7; 272 K = 128 4.8 / 4.8, 192
-// 5.2 / 4.8.  With all regions recorded: 3906 K = 32 16.5 / 24.0, 288 34.9 / 35.7; 1599 K = 128 14.7 / 14.9, 224 18.6
-// / 17.3; 1023 K = 32 7.1 / 10.1, 160 10.5 / 11.5, 224 12.1 / 11.9; 812 K = 32 6.8 / 9.0, 224 11.0 / 11.9; 506 K = 64
-// 6.1 / 6.8, 128 7.2 / 7.2; 255 K = 32 5.0 / 5.2, 128 6.0 / 5.5.  Hence short_k(): a line for one, three, four and
+// the pipelined one, us: 3906 workgroups K = 32 8.0 / 12.3, 160 16.7 / 18.6, 256 22.0 / 22.3, 288 23.3 / 24.1, 320 24.6 /
+// 24.3; 8010 K = 288 46.6 / 45.6, 320 50.9 / 46.5; 2205 K = 192 12.0 / 11.7, 224 13.0 / 12.5; 1155 K = 32 4.9 / 5.5, 224
+// 7.7 / 7.7; 1023 K = 160 5.9 / 5.9; 930 K = 160 6.0 / 6.0, 192 6.4 / 6.1; 675 K = 96 4.8 / 4.9, 128 5.1 / 4.9; 272 K = 96
+// 4.8 / 4.8.  With all regions recorded: 3906 K = 32 11.8 / 17.5, 288 28.2 / 31.7, 320 29.4 / 31.2; 1155 K = 224 10.5 /
+// 11.3; 1023 K = 32 5.7 / 6.7, 160 8.0 / 8.3, 224 9.1 / 9.2; 812 K = 32 5.3 / 6.3, 160 7.5 / 7.8; 506 K = 64 5.2 / 5.3, 128
+// 5.6 / 5.7; 255 K = 32 4.9 / 4.9.  (B in four-byte loads by half of the threads, transposed on its way to LDS, and C in
+// two-byte stores: 3906 K = 32 9.2, 288 27.3.)  Hence short_k(): a line for one, three, four and
 // twelve workgroups per CU, the same with and without sites, so that a recorded kernel and its baseline are one. Its
 // sites follow one another as the pipelined kernel's do.
 //
@@ -364,67 +387,63 @@ __global__ __launch_bounds__(256) void kp_gemm_short(GemmArgs g) {
   else kp::sites_begin<SITE>(ring);
 
   // global -> register mapping
-  // A: 64 rows x 4 chunks = 256 chunks, one per thread
-  const uint32_t a_row = tid >> 2, a_chunk = tid & 3u;
+  // A: 64 rows x 4 chunks of 16 bytes, B: 32 rows x 8 chunks as they lie in memory, one of each per thread
+  const uint32_t a_row = tid >> 2, a_chunk = tid & 3u, b_row = tid >> 3, b_chunk = tid & 7u;
   const uint16_t* a_src = g.A + (size_t)(m0 + a_row) * g.K + a_chunk * 8;
-  // B: 4 k-groups x 32 column pairs = 128 tasks; threads 128..255 idle for B
-  const uint32_t b_kg = (tid >> 5) & 3u, b_np = tid & 31u;
-  const bool b_on = tid < 128;
-  const uint16_t* b_src = g.B + (size_t)(b_kg * 8) * g.N + n0 + b_np * 2;
+  const uint16_t* b_src = g.B + (size_t)b_row * g.N + n0 + b_chunk * 8;
 
   const uint32_t wr = wave >> 1, wc = wave & 1u;  // wave position in the 2x2 grid
+  // B is transposed by the operand read, as in the pipelined kernel; chunk c of row k at position c ^ 4 (k / 2 % 2)
+  const unsigned char* b_rd;
+  {
+    const uint32_t bi = lane & 15u, bg = lane >> 4;
+    const uint32_t k = 8u * (bg >> 1) + (bi >> 2), n = wc * 32u + 16u * (bg & 1u) + 4u * (bi & 3u);
+    b_rd = sB + k * 128u + (((n >> 3) ^ (((k >> 1) & 1u) << 2)) << 4) + 8u * ((n >> 2) & 1u);
+  }
   f32x16 acc = {0};
 
   for (uint32_t kt = 0; kt < g.K / BK; ++kt) {
     // ---- region 0: global load ---------------------------------------------------------------
     if (kt == 0) KP_SITE_K(ring, 0, kp::kNoRegion, 0); else KP_SITE_K(ring, 0, 2, 0);
     const u32x4 av = *reinterpret_cast<const u32x4*>(a_src + (size_t)kt * BK);
-    uint32_t bv[8];
-#pragma unroll
-    for (int i = 0; i < 8; ++i)
-      bv[i] = b_on ? *reinterpret_cast<const uint32_t*>(b_src + ((size_t)kt * BK + i) * g.N) : 0u;
+    const u32x4 bv = *reinterpret_cast<const u32x4*>(b_src + (size_t)kt * BK * g.N);
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     KP_SITE_K(ring, 1, 0, 1);
     // ---- region 1: LDS store -----------------------------------------------------------------
     __syncthreads();  // previous step's MFMA reads are done
     *reinterpret_cast<u32x4*>(sA + short_off(a_row, a_chunk)) = av;
-    if (b_on) {
-      u32x4 lo, hi;  // column 2*b_np and 2*b_np+1, eight consecutive k each
-      lo.x = __builtin_amdgcn_perm(bv[1], bv[0], 0x05040100u); hi.x = __builtin_amdgcn_perm(bv[1], bv[0], 0x07060302u);
-      lo.y = __builtin_amdgcn_perm(bv[3], bv[2], 0x05040100u); hi.y = __builtin_amdgcn_perm(bv[3], bv[2], 0x07060302u);
-      lo.z = __builtin_amdgcn_perm(bv[5], bv[4], 0x05040100u); hi.z = __builtin_amdgcn_perm(bv[5], bv[4], 0x07060302u);
-      lo.w = __builtin_amdgcn_perm(bv[7], bv[6], 0x05040100u); hi.w = __builtin_amdgcn_perm(bv[7], bv[6], 0x07060302u);
-      *reinterpret_cast<u32x4*>(sB + short_off(b_np * 2, b_kg)) = lo;
-      *reinterpret_cast<u32x4*>(sB + short_off(b_np * 2 + 1, b_kg)) = hi;
-    }
+    *reinterpret_cast<u32x4*>(sB + b_row * 128u + ((b_chunk ^ (((b_row >> 1) & 1u) << 2)) << 4)) = bv;
     __syncthreads();
     KP_SITE_K(ring, 2, 1, 2);
     // ---- region 2: MFMA ------------------------------------------------------------------------
+    bf16x8 af[BK / 16], bf[BK / 16];
 #pragma unroll
     for (int ks = 0; ks < BK / 16; ++ks) {
       // operand layout of v_mfma_f32_32x32x16_bf16: lane l supplies row/column l%32, k = 8*(l/32)..+7
-      const uint32_t chunk = ks * 2 + (lane >> 5);
-      const bf16x8 af = *reinterpret_cast<const bf16x8*>(sA + short_off(wr * 32 + (lane & 31u), chunk));
-      const bf16x8 bf = *reinterpret_cast<const bf16x8*>(sB + short_off(wc * 32 + (lane & 31u), chunk));
-      acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(af, bf, acc, 0, 0, 0);
+      typedef short s16x4 __attribute__((ext_vector_type(4)));
+      typedef short s16x8 __attribute__((ext_vector_type(8)));
+      typedef __attribute__((address_space(3))) s16x4* lds_s16x4;
+      af[ks] = *reinterpret_cast<const bf16x8*>(sA + short_off(wr * 32 + (lane & 31u), (uint32_t)ks * 2u + (lane >> 5)));
+      const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4)(b_rd + 16 * ks * 128));
+      const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4)(b_rd + (16 * ks + 4) * 128));
+      const s16x8 v = {lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
+      bf[ks] = __builtin_bit_cast(bf16x8, v);
     }
+#pragma unroll
+    for (int ks = 0; ks < BK / 16; ++ks) acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(bf[ks], af[ks], acc, 0, 0, 0);  // (transposed)
     asm volatile("s_nop 0" ::: "memory");
     KP_COMMIT(ring, 3);
   }
   KP_SITE_K(ring, 0, 2, kp::kNoRegion);
 
-  // epilogue: accumulator register v of lane l is C[row, col] with col = l%32,
-  // row = 8*(v/4) + 4*(l/32) + v%4 inside the wave's 32x32 tile
-  const uint32_t col = n0 + wc * 32 + (lane & 31u);
-#pragma unroll
-  for (int v = 0; v < 16; ++v) {
-    const uint32_t row = m0 + wr * 32 + 8 * (v / 4) + 4 * (lane >> 5) + (v % 4);
-    g.C[(size_t)row * g.N + col] = (uint16_t)bf16_pack_rne(acc[v], 0.f);
-  }
+  __syncthreads();  // every wave is past its last operand read
+  unsigned char* c_lds = (wave & 2u ? sB : sA) + 2048u * (wave & 1u);
+  c_tile_to_lds(acc, c_lds);
+  KP_COMMIT(ring, 1);  // the site that closed the last K step
+  c_tile_to_memory(c_lds, g.C + (size_t)(m0 + wr * 32u) * g.N + n0 + wc * 32u, g.N);
   if constexpr (INSTR != 0) {
     kp::TraceGeom tg{g.n_wg, 4u >> g.group_log2, 3, g.cap_hbm, g.flags};
     if constexpr (SITE == 6) {
-      kp::chain_commit<1>(ring);  // the site that closed the last K step
       kp::ring_finish<REALTIME>(ring, g.cap_lds, g.trace, tg, wg, g.rec_cost, SmallGemmChain{});
     } else {
       kp::sites_end<SITE>(ring);
