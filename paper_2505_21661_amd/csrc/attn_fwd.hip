@@ -21,7 +21,8 @@
 // in an order that the scheduling fences hold: left to itself the compiler reads the operands of one step, waits for them,
 // multiplies.  4 x 32 x 4096, causal, all regions recorded 639 -> 550 us; 1 x 12 x 1152, 108 workgroups 27.4 -> 24.3 us;
 // 2 x 9 x 1920, causal 52 -> 38 us (half of which is the order of the workgroups).  Exponentials threaded between the
-// MFMAs of either product, all or a part of them: within 1 % of this form, and region 1 no longer the softmax.
+// MFMAs of either product, all or a part of them: within 1 % of this form, and region 1 no longer the softmax.  O goes
+// through LDS and leaves as whole rows: 4 x 32 x 384 16.6 -> 14.6 us, 1 x 12 x 1152 24.2 -> 23.1, 4 x 32 x 4096 1-2 %.
 #include <type_traits>
 
 #include "kp_common.h"
@@ -362,19 +363,30 @@ __global__ __launch_bounds__(kAttnThreads, 2) void kp_attn_fwd(AttnArgs g) {
   tile(n_tiles - 2, yes, yes);
   tile(n_tiles - 1, no, yes);
 
-  // epilogue: O[q][d] = O^T[d][q] / l
+  // epilogue: O[q][d] = O^T[d][q] / l.  A lane holds four d of a row at a time; through LDS (8 KiB per wave: every wave is
+  // past its last operand read) they leave as whole rows.  A row is 16 chunks of 16 bytes; chunk c of row r at position
+  // c ^ r % 8, its halves swapped where r / 8 is odd: 16 lanes of an 8-byte write hit all banks once.
   const float l_tot = l_run + __shfl_xor(l_run, 32, 64);
   const float inv = 1.0f / l_tot;
-  uint16_t* orow = g.O + head + (size_t)qrow * kD;
+  unsigned char* sO = smem + 8192u * wave;
+  {
+    const uint32_t half = h32 ^ ((l32 >> 3) & 1u);
 #pragma unroll
-  for (int dt = 0; dt < 4; ++dt)
+    for (int dt = 0; dt < 4; ++dt)
 #pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      u32x2 pk2;
-      pk2.x = bf16_pack_rne(oacc[dt][4 * q + 0] * inv, oacc[dt][4 * q + 1] * inv);
-      pk2.y = bf16_pack_rne(oacc[dt][4 * q + 2] * inv, oacc[dt][4 * q + 3] * inv);
-      *reinterpret_cast<u32x2*>(orow + 32 * dt + 8 * q + 4 * h32) = pk2;
-    }
+      for (int q = 0; q < 4; ++q) {
+        u32x2 pk2;
+        pk2.x = bf16_pack_rne(oacc[dt][4 * q + 0] * inv, oacc[dt][4 * q + 1] * inv);
+        pk2.y = bf16_pack_rne(oacc[dt][4 * q + 2] * inv, oacc[dt][4 * q + 3] * inv);
+        *reinterpret_cast<u32x2*>(sO + l32 * 256u + (((uint32_t)(4 * dt + q) ^ (l32 & 7u)) << 4) + 8u * half) = pk2;
+      }
+  }
+#pragma unroll
+  for (int i = 0; i < 8; ++i) {  // four rows: lane l takes row 4 i + l / 16, position l % 16
+    const uint32_t r = 4u * (uint32_t)i + (lane >> 4), chunk = (lane & 15u) ^ (r & 7u);
+    const u32x4 v = *reinterpret_cast<const u32x4*>(sO + 1024u * (uint32_t)i + 16u * lane);
+    *reinterpret_cast<u32x4*>(g.O + head + (size_t)(q0 + wave * 32u + r) * kD + 8u * chunk) = (i & 2) ? u32x4{v.z, v.w, v.x, v.y} : v;
+  }
   if constexpr (INSTR != 0) {
     kp::TraceGeom tg{g.n_wg, 4u >> g.group_log2, 3, g.cap_hbm, g.flags};
     if constexpr (INSTR >= 4) {
