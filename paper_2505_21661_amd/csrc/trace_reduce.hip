@@ -8,7 +8,7 @@
 //   A  every record is scattered to its rank (seq - first surviving seq), which undoes ring
 //      rotation and out-of-order flushes in O(1) per record; the records of the next workgroup
 //      are requested before the results of the current one are written;
-//   B  a lane takes the records of 8 rounds of 128 consecutive ranks, two neighbours per round;
+//   B  a lane takes the records of NR / 2 rounds of 128 consecutive ranks, two neighbours per round;
 //      an END is paired iff the nearest earlier record of its (wave, region) is a START --
 //      usually the rank just below, in the same lane or the lane below (DPP);
 //      d = (u32)(ts_end - ts_start) minus the constant record cost (Sec. 4.3) goes to the
@@ -16,7 +16,7 @@
 //   C  the paired records of all waves are sorted by clock: counting sort into time cells (one
 //      LDS atomic per record gives cell and arrival slot) and a prefix sum over the cells put
 //      them in cell order;
-//   D  every lane takes 16 consecutive records of that sequence and finishes the order in
+//   D  every lane takes NR (4 or 16) consecutive records of that sequence and finishes the order in
 //      registers (a sorting network over its own records, then a merge of its outer halves with
 //      the neighbouring lanes').  The number of waves that have each region open is kept
 //      bit-sliced (plane k = bit k of every region's count); a first pass gives each lane's net
@@ -27,7 +27,7 @@
 //   E  the per-(workgroup, wave, region) results go to HBM and into running totals, which live in
 //      LDS and reach HBM once per decoder workgroup.
 // Traces outside what the register sort covers (more than 16 regions, a span of 2^26 ticks or
-// more, a time cell with more than 17 records) rank the records inside their cell by comparing
+// more, a time cell with more than NR + 1 records) rank the records inside their cell by comparing
 // clocks and add every switch of a region to the region-pair sums with LDS atomics.
 // A workgroup with a corrupt record (bad field, duplicated seq) has holes in its ranks; it is rare,
 // takes no part in the overlap statistics and is paired by a plain serial walk per (wave, region).
@@ -44,9 +44,6 @@ typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 constexpr uint32_t kSeqMask = 0xFFFFFu;
 // staged metadata byte: bits 5:0 region (63 = no record), 6 paired, 7 END
 constexpr uint32_t kRegion = 0x3Fu, kEmpty = 0x3Fu, kPaired = 0x40u, kEnd = 0x80u;
-constexpr int kNR = 16;                       // positions per lane
-constexpr uint32_t kWaveSpan = 64 * kNR;      // positions per hardware wave
-constexpr uint32_t kMaxCellWindow = 17;       // fullest time cell the sweep's register sort covers
 constexpr uint32_t kMaxRecPerWg = 16384;
 constexpr uint32_t kMaxLds = 160 * 1024;
 constexpr uint32_t kHistStride = 65;  // histogram rows 65 words apart: equal bins of different regions, different banks
@@ -71,32 +68,51 @@ struct DecodeParams {
 __host__ __device__ constexpr uint32_t align16(uint32_t x) { return (x + 15u) & ~15u; }
 constexpr uint32_t kMaxPerWave = 1024;  // entries of the per-(wave, region) sums, copies included
 
-// LDS of a decoder workgroup of BLOCK threads, byte offsets.  Every array is sized for the largest
-// geometry the kernel takes, so that all addresses are compile-time constants.
-template <int BLOCK>
+// LDS of a decoder workgroup, byte offsets.  Every array is sized for the largest geometry the kernel takes (RMAX regions,
+// PERWAVE entries of the per-(wave, region) sums), so that all addresses are compile-time constants.  A team of BLOCK
+// threads decodes one recorded workgroup at a time in arrays of its own; the TEAMS teams of a decoder workgroup share the
+// running totals.
+template <int BLOCK, int NR, int TEAMS, int RMAX, int PERWAVE>
 struct Lds {
-  static constexpr uint32_t npos = BLOCK * kNR;
+  static constexpr uint32_t npos = BLOCK * NR, ncell = BLOCK * 16;
+  // of every team
   static constexpr uint32_t clk = 0;                                       // 4 words of padding after every 64
   static constexpr uint32_t meta = align16(clk + (npos + npos / 16) * 4);
-  static constexpr uint32_t cells = align16(meta + npos + 16);             // one 16-bit counter per time cell, npos cells, + the total
-  static constexpr uint32_t ctr = align16(cells + (npos / 2 + 4) * 4);
-  static constexpr uint32_t tmp = ctr + 16 * 8;
+  static constexpr uint32_t cells = align16(meta + npos + 16);             // one 16-bit counter per time cell + the total
+  static constexpr uint32_t tmp = align16(cells + (ncell / 2 + 4) * 4);
   static constexpr uint32_t misc = align16(tmp + T_COUNT * 4);
   static constexpr uint32_t vf = misc + 4 * 4;
   static constexpr uint32_t wtot = vf + 32 * 8;
   static constexpr uint32_t ptot = wtot + 16 * 4;
-  static constexpr uint32_t hist = ptot + 16 * 8 * 4;
-  static constexpr uint32_t oacc = align16(hist + KP_MAX_REGIONS * kHistStride * 4);
-  static constexpr uint32_t oacc32 = oacc + KP_MAX_REGIONS * KP_MAX_REGIONS * 8;
-  static constexpr uint32_t reg_sum = align16(oacc32 + KP_MAX_REGIONS * (KP_MAX_REGIONS + 1) * 4);
-  static constexpr uint32_t reg_max = reg_sum + KP_MAX_REGIONS * 8;
-  static constexpr uint32_t reg_min = reg_max + KP_MAX_REGIONS * 4;
-  static constexpr uint32_t pw_pack = reg_min + KP_MAX_REGIONS * 4;
-  static constexpr uint32_t pw_max = pw_pack + kMaxPerWave * 8;
-  static constexpr uint32_t pw_min = pw_max + kMaxPerWave * 4;
-  static constexpr uint32_t total = pw_min + kMaxPerWave * 4;
+  static constexpr uint32_t oacc32 = align16(ptot + (BLOCK / 64) * 8 * 4);
+  static constexpr uint32_t pw_pack = align16(oacc32 + RMAX * (RMAX + 1) * 4);
+  static constexpr uint32_t pw_max = pw_pack + PERWAVE * 8;
+  static constexpr uint32_t pw_min = pw_max + PERWAVE * 4;
+  static constexpr uint32_t team = align16(pw_min + PERWAVE * 4);
+  // of all teams
+  static constexpr uint32_t ctr = TEAMS * team;
+  static constexpr uint32_t hist = ctr + 16 * 8;
+  static constexpr uint32_t oacc = align16(hist + RMAX * kHistStride * 4);
+  static constexpr uint32_t reg_sum = oacc + RMAX * RMAX * 8;
+  static constexpr uint32_t reg_max = reg_sum + RMAX * 8;
+  static constexpr uint32_t reg_min = reg_max + RMAX * 4;
+  static constexpr uint32_t total = align16(reg_min + RMAX * 4);
   static_assert(total <= kMaxLds, "decoder LDS exceeds one CU");
+  // waves per SIMD that this leaves room for, at most the four for which 128 registers do
+  static constexpr int waves = (int)(kMaxLds / total) * (BLOCK * TEAMS / 64) / 4;
+  static constexpr int waves_per_simd = waves < 1 ? 1 : waves > 4 ? 4 : waves;
 };
+
+// All threads of a team.  Where that is one wave its LDS operations are done in order, and only the compiler has to be held.
+template <int BLOCK>
+__device__ __forceinline__ void team_sync() {
+  if constexpr (BLOCK == 64) {
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+  } else {
+    __syncthreads();
+  }
+}
 
 // Word of the clock array that holds position i: 4 words of padding after every 64, so that the
 // 64 lanes of a wave reading 16 consecutive words each (64 bytes apart) spread over all banks.
@@ -138,103 +154,93 @@ __device__ __forceinline__ uint32_t key_clock(uint32_t k) { return k >> 6; }
 __device__ __forceinline__ uint32_t key_region_bit(uint32_t k) { return 1u << ((k >> 1) & 31u); }  // bit 31 for a place past the end: above every region
 __device__ __forceinline__ uint32_t key_end_mask(uint32_t k) { return (uint32_t)__builtin_amdgcn_sbfe((int)k, 0, 1); }  // all ones for an END
 
-// The 16 records of the clock-sorted sequence that lane `tid` of the sweep owns, from a sequence that
+// The NR records of the clock-sorted sequence that lane `tid` of the sweep owns, from a sequence that
 // is only ordered cell by cell (inside a cell the records stand in arrival order).  Cells follow one
 // another in clock order, so sorting the words sorts every cell and moves no record out of its cell.
-//
-// Form for cells of at most 9 records: the lane sorts its own 16 places and puts them back; a cell that
-// lies across the boundary to the next lane then has at most 8 records on either side, all of them in
-// the upper half here and in the lower half there, so merging these two halves (both sorted) and
-// handing the lower 8 back to this lane, the upper 8 to the next one finishes the job.  Each lane does
-// that for its lower half with the lane below and for its upper half with the lane above: the larger
-// (smaller) of element i of one run and element 7 - i of the other are the upper (lower) 8 of the two
-// runs, in rising-then-falling order.  Contains one workgroup barrier.
-template <uint32_t NPOS>
-__device__ __forceinline__ void sorted_own(uint32_t* clk, uint32_t tid, uint32_t n_events, uint32_t fake, uint32_t (&key)[kNR]) {
-  const uint32_t g0 = tid * kNR;
-  u32x4* own = reinterpret_cast<u32x4*>(clk + clk_word(g0));
+template <int NR>
+__device__ __forceinline__ void load_run(const uint32_t* clk, uint32_t lane_of_sweep, uint32_t (&key)[NR]) {
+  const u32x4* at = reinterpret_cast<const u32x4*>(clk + clk_word(lane_of_sweep * NR));
 #pragma unroll
-  for (int x = 0; x < kNR / 4; ++x) {
-    const u32x4 v = own[x];
+  for (int x = 0; x < NR / 4; ++x) {
+    const u32x4 v = at[x];
     key[4 * x] = v.x; key[4 * x + 1] = v.y; key[4 * x + 2] = v.z; key[4 * x + 3] = v.w;
-  }
-  if (__builtin_amdgcn_ballot_w64(g0 + kNR > n_events)) {
-#pragma unroll
-    for (int y = 0; y < kNR; ++y) key[y] = g0 + y < n_events ? key[y] : fake;
-  }
-  network_sort<kNR>(key);
-  own[0] = u32x4{key[0], key[1], key[2], key[3]};
-  own[1] = u32x4{key[4], key[5], key[6], key[7]};
-  own[2] = u32x4{key[8], key[9], key[10], key[11]};
-  own[3] = u32x4{key[12], key[13], key[14], key[15]};
-  __syncthreads();
-  {
-    const u32x4* below = reinterpret_cast<const u32x4*>(clk + clk_word((tid > 0 ? tid - 1 : 0) * kNR));
-    const u32x4* above = reinterpret_cast<const u32x4*>(clk + clk_word((tid + 1 < NPOS / kNR ? tid + 1 : tid) * kNR));
-    const u32x4 b0 = below[2], b1 = below[3], a0 = above[0], a1 = above[1];
-    const uint32_t lo_gate = tid > 0 ? 0xFFFFFFFFu : 0u;               // no lane below: nothing comes up
-    const uint32_t hi_fill = tid + 1 < NPOS / kNR ? 0u : 0xFFFFFFFFu;  // no lane above: nothing comes down
-    const uint32_t bw[8] = {b0.x & lo_gate, b0.y & lo_gate, b0.z & lo_gate, b0.w & lo_gate,
-                            b1.x & lo_gate, b1.y & lo_gate, b1.z & lo_gate, b1.w & lo_gate};
-    const uint32_t aw[8] = {a0.x | hi_fill, a0.y | hi_fill, a0.z | hi_fill, a0.w | hi_fill,
-                            a1.x | hi_fill, a1.y | hi_fill, a1.z | hi_fill, a1.w | hi_fill};
-    uint32_t lo[8], hi[8];
-#pragma unroll
-    for (int i = 0; i < 8; ++i) {
-      lo[i] = key[7 - i] > bw[i] ? key[7 - i] : bw[i];         // upper 8 of (upper half below, own lower half)
-      hi[i] = key[8 + i] < aw[7 - i] ? key[8 + i] : aw[7 - i];  // lower 8 of (own upper half, lower half above)
-    }
-    bitonic_merge<8>(lo);
-    bitonic_merge<8>(hi);
-#pragma unroll
-    for (int i = 0; i < 8; ++i) { key[i] = lo[i]; key[8 + i] = hi[i]; }
   }
 }
+template <int NR>
+__device__ __forceinline__ void store_run(uint32_t* clk, uint32_t lane_of_sweep, const uint32_t (&key)[NR]) {
+  u32x4* at = reinterpret_cast<u32x4*>(clk + clk_word(lane_of_sweep * NR));
+#pragma unroll
+  for (int x = 0; x < NR / 4; ++x) at[x] = u32x4{key[4 * x], key[4 * x + 1], key[4 * x + 2], key[4 * x + 3]};
+}
+template <int NR>
+__device__ __forceinline__ void load_and_sort_own(const uint32_t* clk, uint32_t tid, uint32_t n_events, uint32_t fake, uint32_t (&key)[NR]) {
+  load_run<NR>(clk, tid, key);
+  if (__builtin_amdgcn_ballot_w64(tid * NR + NR > n_events)) {
+#pragma unroll
+    for (int y = 0; y < NR; ++y) key[y] = tid * NR + y < n_events ? key[y] : fake;
+  }
+  network_sort<NR>(key);
+}
 
-// Form for cells of up to 17 records: a cell then lies in at most two neighbouring lanes, with up to 16
-// records in either.  The lane sorts its own 16 places; then lanes 2m and 2m + 1 merge their runs (the
-// lower lane keeps the lower 16 of the 32, the upper lane the upper 16), and after that lanes 2m + 1 and
+// Form for cells of at most NR / 2 + 1 records: the lane sorts its own NR places and puts them back; a cell that
+// lies across the boundary to the next lane then has at most NR / 2 records on either side, all of them in
+// the upper half here and in the lower half there, so merging these two halves (both sorted) and
+// handing the lower ones back to this lane, the upper ones to the next one finishes the job.  Each lane does
+// that for its lower half with the lane below and for its upper half with the lane above: the larger
+// (smaller) of element i of one run and element NR / 2 - 1 - i of the other are the upper (lower) ones of the two
+// runs, in rising-then-falling order.  Contains one barrier of the team.
+template <int BLOCK, int NR>
+__device__ __forceinline__ void sorted_own(uint32_t* clk, uint32_t tid, uint32_t n_events, uint32_t fake, uint32_t (&key)[NR]) {
+  constexpr int H = NR / 2;
+  load_and_sort_own<NR>(clk, tid, n_events, fake, key);
+  store_run<NR>(clk, tid, key);
+  team_sync<BLOCK>();
+  uint32_t below[NR], above[NR];  // (the halves that are not used are not loaded)
+  load_run<NR>(clk, tid > 0 ? tid - 1 : 0, below);
+  load_run<NR>(clk, tid + 1 < BLOCK ? tid + 1 : tid, above);
+  const uint32_t lo_gate = tid > 0 ? 0xFFFFFFFFu : 0u;           // no lane below: nothing comes up
+  const uint32_t hi_fill = tid + 1 < BLOCK ? 0u : 0xFFFFFFFFu;  // no lane above: nothing comes down
+  uint32_t lo[H], hi[H];
+#pragma unroll
+  for (int i = 0; i < H; ++i) {
+    const uint32_t bw = below[H + i] & lo_gate, aw = above[H - 1 - i] | hi_fill;
+    lo[i] = key[H - 1 - i] > bw ? key[H - 1 - i] : bw;  // the upper ones of (upper half below, own lower half)
+    hi[i] = key[H + i] < aw ? key[H + i] : aw;          // the lower ones of (own upper half, lower half above)
+  }
+  bitonic_merge<H>(lo);
+  bitonic_merge<H>(hi);
+#pragma unroll
+  for (int i = 0; i < H; ++i) { key[i] = lo[i]; key[H + i] = hi[i]; }
+}
+
+// Form for cells of up to NR + 1 records: a cell then lies in at most two neighbouring lanes, with up to NR
+// records in either.  The lane sorts its own places; then lanes 2m and 2m + 1 merge their runs (the
+// lower lane keeps the lower NR, the upper lane the upper NR), and after that lanes 2m + 1 and
 // 2m + 2 do the same.  The second merge moves no record across the boundary the first one settled: what
 // it hands down to lane 2m + 1 belongs to the cell that lies across the boundary above, and that cell
-// has no record in lane 2m (it would hold 18).  Contains three workgroup barriers.
-template <uint32_t NPOS>
-__device__ __forceinline__ void sorted_pairs(uint32_t* clk, uint32_t tid, uint32_t n_events, uint32_t fake, uint32_t (&key)[kNR]) {
-  const uint32_t g0 = tid * kNR;
-  u32x4* own = reinterpret_cast<u32x4*>(clk + clk_word(g0));
-#pragma unroll
-  for (int x = 0; x < kNR / 4; ++x) {
-    const u32x4 v = own[x];
-    key[4 * x] = v.x; key[4 * x + 1] = v.y; key[4 * x + 2] = v.z; key[4 * x + 3] = v.w;
-  }
-  if (__builtin_amdgcn_ballot_w64(g0 + kNR > n_events)) {
-#pragma unroll
-    for (int y = 0; y < kNR; ++y) key[y] = g0 + y < n_events ? key[y] : fake;
-  }
-  network_sort<kNR>(key);
+// has no record in lane 2m (it would hold NR + 2).  Contains three barriers of the team.
+template <int BLOCK, int NR>
+__device__ __forceinline__ void sorted_pairs(uint32_t* clk, uint32_t tid, uint32_t n_events, uint32_t fake, uint32_t (&key)[NR]) {
+  load_and_sort_own<NR>(clk, tid, n_events, fake, key);
 #pragma unroll
   for (int round = 0; round < 2; ++round) {
-    own[0] = u32x4{key[0], key[1], key[2], key[3]};
-    own[1] = u32x4{key[4], key[5], key[6], key[7]};
-    own[2] = u32x4{key[8], key[9], key[10], key[11]};
-    own[3] = u32x4{key[12], key[13], key[14], key[15]};
-    __syncthreads();
+    store_run<NR>(clk, tid, key);
+    team_sync<BLOCK>();
     // round 0: partner of lane t is t ^ 1; round 1: the other neighbour (the first and the last lane have none)
-    const bool upper = ((tid ^ (uint32_t)round) & 1u) != 0u;  // this lane keeps the upper 16 of the merge
-    const bool alone = round == 1 && (tid == 0u || tid + 1u == NPOS / kNR);
-    const uint32_t partner = upper ? tid - 1u : tid + 1u;
-    const u32x4* other = reinterpret_cast<const u32x4*>(clk + clk_word((alone ? tid : partner) * kNR));
-    const u32x4 p0 = other[0], p1 = other[1], p2 = other[2], p3 = other[3];
-    const uint32_t pw[kNR] = {p0.x, p0.y, p0.z, p0.w, p1.x, p1.y, p1.z, p1.w, p2.x, p2.y, p2.z, p2.w, p3.x, p3.y, p3.z, p3.w};
-    // the larger (smaller) of element i of one run and element 15 - i of the other: the upper (lower) 16
+    const bool upper = ((tid ^ (uint32_t)round) & 1u) != 0u;  // this lane keeps the upper ones of the merge
+    const bool alone = round == 1 && (tid == 0u || tid + 1u == BLOCK);
+    uint32_t pw[NR];
+    load_run<NR>(clk, alone ? tid : upper ? tid - 1u : tid + 1u, pw);
+    // the larger (smaller) of element i of one run and element NR - 1 - i of the other: the upper (lower) ones
     const uint32_t neutral = upper ? 0u : 0xFFFFFFFFu;
 #pragma unroll
-    for (int i = 0; i < kNR; ++i) {
-      const uint32_t x = key[i], y = alone ? neutral : pw[kNR - 1 - i];
+    for (int i = 0; i < NR; ++i) {
+      const uint32_t x = key[i], y = alone ? neutral : pw[NR - 1 - i];
       const uint32_t lo = x < y ? x : y, hi = x < y ? y : x;
       key[i] = upper ? hi : lo;
     }
-    bitonic_merge<kNR>(key);
-    if (round == 0) __syncthreads();  // every lane has read its partner's run before it is overwritten
+    bitonic_merge<NR>(key);
+    if (round == 0) team_sync<BLOCK>();  // every lane has read its partner's run before it is overwritten
   }
 }
 
@@ -276,6 +282,21 @@ __global__ __launch_bounds__(1024) void kp_reduce_derive(uint64_t* out, uint32_t
     for (int d = 8; d >= 1; d >>= 1) n += __shfl_xor((unsigned long long)n, d, 64);
     if (r < R && part == 0u) out[l.cnt + r] = n;
   }
+  if (R <= 32u) {  // one element per thread, read before any is written: no second way to memory and back
+    const uint32_t i = threadIdx.x, a = i / R, b = i - a * R;
+    uint64_t o = 0, u = 0;
+    if (i < R * R) {
+      o = out[l.F + (a <= b ? i : b * R + a)];
+      u = out[l.F + a * R + a];
+    }
+    __syncthreads();
+    if (i < R * R) {
+      out[l.O + i] = o;
+      if (a == b) out[l.U + a] = o;
+      reinterpret_cast<double*>(out)[l.F + i] = u ? (double)o / (double)u : 0.0;
+    }
+    return;
+  }
   for (uint32_t i = threadIdx.x; i < R * R; i += blockDim.x) {
     const uint32_t a = i / R, b = i - a * R;
     const uint64_t o = out[l.F + (a <= b ? i : b * R + a)];
@@ -293,34 +314,40 @@ __global__ __launch_bounds__(1024) void kp_reduce_derive(uint64_t* out, uint32_t
 // Position p = wave*cap_wave + rank indexes the staged records.  Hardware wave h of the decoder
 // owns positions [h*1024, h*1024 + 1024) and lane l takes position h*1024 + 64*j + l in round j,
 // so that neighbouring lanes hold neighbouring ranks.
-template <int BLOCK, int PLANES>
-__global__ __launch_bounds__(BLOCK) void kp_reduce_main(DecodeParams p) {
-  using L = Lds<BLOCK>;
-  __shared__ __align__(16) unsigned char smem[L::total];
+template <int BLOCK, int NR, int TEAMS, int PLANES, int RMAX, int PERWAVE>
+__global__ __launch_bounds__(BLOCK * TEAMS, (Lds<BLOCK, NR, TEAMS, RMAX, PERWAVE>::waves_per_simd)) void kp_reduce_main(DecodeParams p) {
+  using L = Lds<BLOCK, NR, TEAMS, RMAX, PERWAVE>;
+  constexpr uint32_t kWaveSpan = 64 * NR;      // positions per hardware wave
+  constexpr uint32_t kMaxCellWindow = NR + 1;  // fullest time cell the sweep's register sort covers
+  static_assert(TEAMS == 1 || BLOCK == 64, "teams of more than one wave have no barrier of their own");
+  __shared__ __align__(16) unsigned char shared[L::total];
+  const uint32_t team = TEAMS == 1 ? 0u : (uint32_t)__builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+  const uint32_t n_teams = TEAMS == 1 ? 1u : blockDim.x >> 6;  // (as many as the launch asked for)
+  unsigned char* smem = shared + team * L::team;
   uint32_t* clk = reinterpret_cast<uint32_t*>(smem + L::clk);
   uint8_t* meta = smem + L::meta;
   uint32_t* cells = reinterpret_cast<uint32_t*>(smem + L::cells);  // cell c: half (c & 1) of word c >> 1
-  uint32_t* hist = reinterpret_cast<uint32_t*>(smem + L::hist);
-  unsigned long long* oacc = reinterpret_cast<unsigned long long*>(smem + L::oacc);
+  uint32_t* hist = reinterpret_cast<uint32_t*>(shared + L::hist);
+  unsigned long long* oacc = reinterpret_cast<unsigned long long*>(shared + L::oacc);
   uint32_t* oacc32 = reinterpret_cast<uint32_t*>(smem + L::oacc32);  // this workgroup's sums modulo 2^32
-  unsigned long long* reg_sum = reinterpret_cast<unsigned long long*>(smem + L::reg_sum);
-  uint32_t* reg_max = reinterpret_cast<uint32_t*>(smem + L::reg_max);
-  uint32_t* reg_min = reinterpret_cast<uint32_t*>(smem + L::reg_min);
+  unsigned long long* reg_sum = reinterpret_cast<unsigned long long*>(shared + L::reg_sum);
+  uint32_t* reg_max = reinterpret_cast<uint32_t*>(shared + L::reg_max);
+  uint32_t* reg_min = reinterpret_cast<uint32_t*>(shared + L::reg_min);
   unsigned long long* pw_pack = reinterpret_cast<unsigned long long*>(smem + L::pw_pack);
   uint32_t* pw_max = reinterpret_cast<uint32_t*>(smem + L::pw_max);
   uint32_t* pw_min = reinterpret_cast<uint32_t*>(smem + L::pw_min);
-  unsigned long long* ctr = reinterpret_cast<unsigned long long*>(smem + L::ctr);
+  unsigned long long* ctr = reinterpret_cast<unsigned long long*>(shared + L::ctr);
   uint32_t* tmp = reinterpret_cast<uint32_t*>(smem + L::tmp);
   uint32_t* misc = reinterpret_cast<uint32_t*>(smem + L::misc);  // [0] span overflow, [1] cell scale, [2] span
   uint2* sVF = reinterpret_cast<uint2*>(smem + L::vf);           // per wave: records held, first surviving seq
   uint32_t* wtot = reinterpret_cast<uint32_t*>(smem + L::wtot);
   uint32_t* ptot = reinterpret_cast<uint32_t*>(smem + L::ptot);
 
-  constexpr uint32_t NPOS = BLOCK * kNR, NCELL = NPOS;
+  constexpr uint32_t NPOS = L::npos, NCELL = L::ncell;
   // The last four words of the clock array are padding that no position maps to, and the metadata
   // array has 16 spare bytes: stores of lanes that have nothing to store go there instead of branching.
   constexpr uint32_t kSpareWord = NPOS + NPOS / 16 - 1;
-  const uint32_t tid_k = threadIdx.x;
+  const uint32_t tid_k = TEAMS == 1 ? threadIdx.x : threadIdx.x & 63u;  // in the team
   // The kernel arguments arrive as one block of scalar registers.  Each one used in the loop gets a
   // register of its own through an opaque move: when scalar registers run short the compiler then parks
   // and fetches single values instead of the whole block.
@@ -330,23 +357,37 @@ __global__ __launch_bounds__(BLOCK) void kp_reduce_main(DecodeParams p) {
   const uint32_t n_wg = own_reg(p.n_wg), n_copies = own_reg(p.ncopy), stop_after = own_reg(p.stop_after);
   const uint32_t rec_cost = own_reg(p.rec_cost), flush = own_reg(p.flush);
   const StatsLayout SL = stats_layout(n_wg, W, R);
-  if (p.out[H_STATUS] != 0) return;  // device header did not match the launch geometry
+  const uint64_t status = p.out[H_STATUS];  // (needed behind the first requests only)
 
-  for (uint32_t i = tid_k; i < R * kHistStride; i += BLOCK) hist[i] = 0;
-  for (uint32_t i = tid_k; i < R * R; i += BLOCK) oacc[i] = 0;
+  const uint32_t n_threads = TEAMS == 1 ? (uint32_t)BLOCK : blockDim.x;
+  for (uint32_t i = threadIdx.x; i < R * kHistStride; i += n_threads) hist[i] = 0;
+  for (uint32_t i = threadIdx.x; i < R * R; i += n_threads) oacc[i] = 0;
   for (uint32_t i = tid_k; i < R * (R | 1u); i += BLOCK) oacc32[i] = 0;
-  for (uint32_t i = tid_k; i < R; i += BLOCK) { reg_sum[i] = 0; reg_max[i] = 0; reg_min[i] = 0xFFFFFFFFu; }
+  for (uint32_t i = threadIdx.x; i < R; i += n_threads) { reg_sum[i] = 0; reg_max[i] = 0; reg_min[i] = 0xFFFFFFFFu; }
   for (uint32_t i = tid_k; i < n_copies * W * R; i += BLOCK) { pw_pack[i] = 0; pw_max[i] = 0; pw_min[i] = 0xFFFFFFFFu; }
-  if (tid_k < 16) ctr[tid_k] = 0;
+  if (threadIdx.x < 16) ctr[threadIdx.x] = 0;
   __syncthreads();
 
-  // The records of a workgroup (eight 16-byte units, two records each, per thread) and the words of its
+  auto clear_meta = [&](uint32_t t) __attribute__((always_inline)) {  // no record: the NR metadata bytes of thread t
+    if constexpr (NR == 16) reinterpret_cast<u32x4*>(meta)[t] = u32x4{0x3F3F3F3Fu, 0x3F3F3F3Fu, 0x3F3F3F3Fu, 0x3F3F3F3Fu};
+    else reinterpret_cast<uint32_t*>(meta)[t] = 0x3F3F3F3Fu;
+  };
+  auto load_meta = [&](uint32_t t, uint32_t (&w)[NR / 4]) __attribute__((always_inline)) {
+    if constexpr (NR == 16) {
+      const u32x4 v = reinterpret_cast<const u32x4*>(meta)[t];
+      w[0] = v.x; w[1] = v.y; w[2] = v.z; w[3] = v.w;
+    } else {
+      w[0] = reinterpret_cast<const uint32_t*>(meta)[t];
+    }
+  };
+
+  // The records of a workgroup (NR / 2 16-byte units, two records each, per thread) and the words of its
   // header are requested one workgroup ahead, before the previous workgroup's results are written, so
   // that the memory latency runs under that tail and under the clearing of the staging state.
-  u32x4 v[8];
+  u32x4 v[NR / 2];
   uint32_t h_total;  // lane & 15 -> records written by that wave
   uint2 h_begin, h_end;
-  constexpr int kEarly = 6;  // units requested before the matrix products of the sweep of the workgroup before
+  constexpr int kEarly = NR / 2 * 3 / 4 > 1 ? NR / 2 * 3 / 4 : NR / 2;  // units requested before the matrix products of the sweep of the workgroup before
   auto request_units = [&](uint32_t g, uint32_t t, auto first, auto last) {
     const u32x4* recs = p.records + (size_t)g * (nrec / 2);
 #pragma unroll
@@ -361,10 +402,15 @@ __global__ __launch_bounds__(BLOCK) void kp_reduce_main(DecodeParams p) {
     h_begin = *reinterpret_cast<const uint2*>(whn + 2);
     h_end = *reinterpret_cast<const uint2*>(whn + 4);
   };
-  request_units(blockIdx.x, tid_k, std::integral_constant<int, 0>{}, std::integral_constant<int, kEarly>{});
-  request_header(blockIdx.x, tid_k);
+  const uint32_t first_wg = blockIdx.x + team * gridDim.x, stride = gridDim.x * n_teams;
+  {
+    const uint32_t at = TEAMS == 1 || first_wg < n_wg ? first_wg : n_wg - 1u;  // (a team without a workgroup asks all the same)
+    request_units(at, tid_k, std::integral_constant<int, 0>{}, std::integral_constant<int, kEarly>{});
+    request_header(at, tid_k);
+  }
+  if (status != 0) return;  // device header did not match the launch geometry
 
-  for (uint32_t wg = blockIdx.x; wg < n_wg; wg += gridDim.x) {
+  for (uint32_t wg = first_wg; wg < n_wg; wg += stride) {
     // A fresh copy of the thread index per workgroup that the optimiser cannot see through: without it
     // the address arithmetic of all 16 rounds is computed once before the loop and held in registers
     // for the whole kernel.
@@ -376,7 +422,7 @@ __global__ __launch_bounds__(BLOCK) void kp_reduce_main(DecodeParams p) {
     // its clock word; round j: cwe + 136 j (pbase is a multiple of 1024, lanes 32.. are past one padding)
     const uint32_t cwe = qe + (pbase >> 4) + ((lane >> 5) << 2);
     // the last units of this workgroup's records: they travel while the staging state is cleared
-    request_units(wg, tid, std::integral_constant<int, kEarly>{}, std::integral_constant<int, 8>{});
+    request_units(wg, tid, std::integral_constant<int, kEarly>{}, std::integral_constant<int, NR / 2>{});
     // ---- workgroup header, clear the staging state -----------------------------------------------
     if (tid <= KP_MAX_WAVES) {  // (entries from W up: no records)
       const uint32_t T = tid < W ? h_total : 0u;
@@ -401,21 +447,22 @@ __global__ __launch_bounds__(BLOCK) void kp_reduce_main(DecodeParams p) {
       misc[1] = scale >= 4294967295.0 ? 0xFFFFFFFFu : (uint32_t)scale;
       misc[2] = (uint32_t)sp;
     }
-    reinterpret_cast<u32x4*>(meta)[tid] = u32x4{0x3F3F3F3Fu, 0x3F3F3F3Fu, 0x3F3F3F3Fu, 0x3F3F3F3Fu};
+    clear_meta(tid);
     {  // a position without a record reads as the largest clock: it never counts as a step back in time
-      u32x4* own = reinterpret_cast<u32x4*>(clk + clk_word(tid * kNR));
-      const u32x4 ones{0xFFFFFFFFu, 0xFFFFFFFFu, 0xFFFFFFFFu, 0xFFFFFFFFu};
-      own[0] = ones; own[1] = ones; own[2] = ones; own[3] = ones;
+      uint32_t ones[NR];
+#pragma unroll
+      for (int i = 0; i < NR; ++i) ones[i] = 0xFFFFFFFFu;
+      store_run<NR>(clk, tid, ones);
     }
     reinterpret_cast<u32x4*>(cells)[2 * tid] = u32x4{0u, 0u, 0u, 0u};
     reinterpret_cast<u32x4*>(cells)[2 * tid + 1] = u32x4{0u, 0u, 0u, 0u};
     if (tid == 0) reinterpret_cast<u32x4*>(cells)[2 * BLOCK] = u32x4{0u, 0u, 0u, 0u};
-    __syncthreads();
+    team_sync<BLOCK>();
 
     uint32_t wg_invalid = 0;
     bool eligible = false;
     uint32_t products = 0;  // limbs of the stretch lengths when the sweep hands its sets to the matrix cores, else 0
-    const uint32_t wg_ahead = wg + gridDim.x < n_wg ? wg + gridDim.x : wg;  // (the last one asks for its own again)
+    const uint32_t wg_ahead = wg + stride < n_wg ? wg + stride : wg;  // (the last one asks for its own again)
     do {  // (left early only when single steps are timed)
     // ---- A: scatter by rank ------------------------------------------------------------------
     // Eight 16-byte units (two records each) per thread cover the workgroup.  Two records that go to an
@@ -425,7 +472,7 @@ __global__ __launch_bounds__(BLOCK) void kp_reduce_main(DecodeParams p) {
     {
       uint32_t c_field = 0, c_dis = 0;
 #pragma unroll
-      for (int u = 0; u < 8; ++u) {
+      for (int u = 0; u < NR / 2; ++u) {
         const uint32_t f0 = 2u * (tid + u * BLOCK);
         // a unit past the last record slot falls into a wave past the last one, which holds no records
         const uint32_t wv = f0 >> cl2, w = wv < KP_MAX_WAVES ? wv : KP_MAX_WAVES, s0 = f0 & capm;
@@ -454,7 +501,7 @@ __global__ __launch_bounds__(BLOCK) void kp_reduce_main(DecodeParams p) {
       add_tmp(tmp, T_FIELDVALID, c_field);
       add_tmp(tmp, T_DISORDER, c_dis);
     }
-    __syncthreads();
+    team_sync<BLOCK>();
     if (stop_after == kStepOrdered) break;
 
     // ---- a duplicated seq leaves fewer occupied ranks than valid records ---------------------------
@@ -462,22 +509,22 @@ __global__ __launch_bounds__(BLOCK) void kp_reduce_main(DecodeParams p) {
     // distinct ranks: only a workgroup with a record elsewhere needs the count.
     uint32_t n_occupied = tmp[T_FIELDVALID];
     if (tmp[T_DISORDER] != 0u) {
-      const u32x4 mv = reinterpret_cast<const u32x4*>(meta)[tid];
-      const uint32_t mw[4] = {mv.x, mv.y, mv.z, mv.w};
+      uint32_t mw[NR / 4];
+      load_meta(tid, mw);
       uint32_t occ = 0;
 #pragma unroll
-      for (int i = 0; i < 4; ++i)  // bytes whose region field is not the "no record" code
+      for (int i = 0; i < NR / 4; ++i)  // bytes whose region field is not the "no record" code
         occ += __popc((((mw[i] & 0x3F3F3F3Fu) ^ 0x3F3F3F3Fu) + 0x7F7F7F7Fu) & 0x80808080u);
       add_tmp(tmp, T_OCCUPIED, occ);
-      __syncthreads();
+      team_sync<BLOCK>();
       n_occupied = tmp[T_OCCUPIED];
       if (n_occupied != tmp[T_FIELDVALID]) {
         // Rare: some seq occurs twice.  The later slot must win, so redo this workgroup's
         // scatter in slot order, one thread per wave.
-        __syncthreads();
-        reinterpret_cast<u32x4*>(meta)[tid] = u32x4{0x3F3F3F3Fu, 0x3F3F3F3Fu, 0x3F3F3F3Fu, 0x3F3F3F3Fu};
+        team_sync<BLOCK>();
+        clear_meta(tid);
         if (tid == 0) { tmp[T_DISORDER] = 0; tmp[T_OCCUPIED] = 0; }
-        __syncthreads();
+        team_sync<BLOCK>();
         if (tid < W) {
           const uint32_t w = tid, V = sVF[w].x, first = sVF[w].y;
           const uint32_t* seg = reinterpret_cast<const uint32_t*>(p.records) + ((size_t)wg * nrec + (size_t)w * cap) * 2;
@@ -500,18 +547,18 @@ __global__ __launch_bounds__(BLOCK) void kp_reduce_main(DecodeParams p) {
           atomicAdd(&tmp[T_DISORDER], dis);
           atomicAdd(&tmp[T_OCCUPIED], occ2);
         }
-        __syncthreads();
+        team_sync<BLOCK>();
         n_occupied = tmp[T_OCCUPIED];
       }
     }
     // ---- this lane's 16 positions: in round j the even position qe + 128 j and the one above it ---------
     // (The arrays below are only ever assigned outside of branches: a conditional assignment makes the
     // compiler carry each array through the branch as one 16-register value, copied at every merge.)
-    uint32_t t[kNR], mq[kNR / 4];  // clocks; metadata bytes, record i in byte i & 3 of word i >> 2
+    uint32_t t[NR], mq[NR / 4];  // clocks; metadata bytes, record i in byte i & 3 of word i >> 2
 #pragma unroll
-    for (int j = 0; j < kNR / 4; ++j) mq[j] = 0u;
+    for (int j = 0; j < NR / 4; ++j) mq[j] = 0u;
 #pragma unroll
-    for (int j = 0; j < kNR / 2; ++j) {
+    for (int j = 0; j < NR / 2; ++j) {
       const uint2 tt = *reinterpret_cast<const uint2*>(clk + cwe + 136u * j);
       t[2 * j] = tt.x; t[2 * j + 1] = tt.y;
       // positions past the last record slot stay cleared
@@ -562,7 +609,7 @@ __global__ __launch_bounds__(BLOCK) void kp_reduce_main(DecodeParams p) {
         }
       };
 #pragma unroll
-      for (int j = 0; j < kNR / 2; ++j) {
+      for (int j = 0; j < NR / 2; ++j) {
         const uint32_t q = qe + 128u * j;  // even position; the odd one is q + 1
         const uint32_t m2 = (mq[j >> 1] >> (16 * (j & 1))) & 0xFFFFu;  // byte 0: even position, byte 1: odd
         const uint32_t t0 = t[2 * j], t1 = t[2 * j + 1];
@@ -613,8 +660,8 @@ __global__ __launch_bounds__(BLOCK) void kp_reduce_main(DecodeParams p) {
       // the START claimed by the even position of the lane above (lane 63: of lane 0 in the next round)
       const uint32_t claims0 = (uint32_t)__builtin_amdgcn_readlane((int)claims, 0);
 #pragma unroll
-      for (int j = 0; j < kNR / 2; ++j) {
-        const uint32_t next_round = j + 1 < kNR / 2 ? (claims0 >> (j + 1)) & 1u : 0u;
+      for (int j = 0; j < NR / 2; ++j) {
+        const uint32_t next_round = j + 1 < NR / 2 ? (claims0 >> (j + 1)) & 1u : 0u;
         const uint32_t got = (uint32_t)__builtin_amdgcn_update_dpp((int)next_round, (int)((claims >> j) & 1u), 0x130, 0xF, 0xF,
                                                                    false);  // wave_shl:1
         set_paired(2 * j + 1, got);
@@ -622,7 +669,7 @@ __global__ __launch_bounds__(BLOCK) void kp_reduce_main(DecodeParams p) {
       // ENDs, and ENDs that are paired (the flag sits one bit below): counted on the packed bytes
       uint32_t n_ends = 0, n_pairs = 0;
 #pragma unroll
-      for (int x = 0; x < kNR / 4; ++x) {
+      for (int x = 0; x < NR / 4; ++x) {
         n_ends += __popc(mq[x] & 0x80808080u);
         n_pairs += __popc(mq[x] & (mq[x] << 1) & 0x80808080u);
       }
@@ -673,20 +720,20 @@ __global__ __launch_bounds__(BLOCK) void kp_reduce_main(DecodeParams p) {
         if (n) atomicAdd(&tmp[T_NONMONO], n);
       }
     }
-    __syncthreads();
+    team_sync<BLOCK>();
 #pragma unroll
-    for (int i = 0; i < kNR; ++i) asm volatile("" : "+v"(t[i]));  // (opaque across the barrier, see below)
+    for (int i = 0; i < NR; ++i) asm volatile("" : "+v"(t[i]));  // (opaque across the barrier, see below)
 #pragma unroll
-    for (int i = 0; i < kNR / 4; ++i) asm volatile("" : "+v"(mq[i]));
+    for (int i = 0; i < NR / 4; ++i) asm volatile("" : "+v"(mq[i]));
     eligible = !misc[0] && wg_invalid == 0u && tmp[T_NONMONO] == 0u;
 
     if (eligible && stop_after != kStepPaired) {
       // ---- C: order the paired records of all waves by clock ---------------------------------------
       // marks left by ENDs of other hardware waves (only the last position can have one) and by walks
-      set_paired(kNR - 1, ((uint32_t)meta[qe + 128u * (kNR / 2 - 1) + 1u] >> 6) & 1u);
+      set_paired(NR - 1, ((uint32_t)meta[qe + 128u * (NR / 2 - 1) + 1u] >> 6) & 1u);
       if (tmp[T_MARKS]) {
 #pragma unroll
-        for (int j = 0; j < kNR / 2; ++j)
+        for (int j = 0; j < NR / 2; ++j)
           mq[j >> 1] |= ((uint32_t)*reinterpret_cast<const uint16_t*>(meta + qe + 128u * j) & 0x4040u) << (16 * (j & 1));
       }
       // A pair of length 0 overlaps nothing, and records of one clock come out of the counting sort in any order: its END
@@ -696,7 +743,7 @@ __global__ __launch_bounds__(BLOCK) void kp_reduce_main(DecodeParams p) {
       // records of 17 regions, half of them in any order: 295 us going to the partner every time, 244 this way.)
       if (tmp[T_ZERO]) {
 #pragma unroll
-        for (int i = 0; i < kNR; ++i) {
+        for (int i = 0; i < NR; ++i) {
           const uint32_t m = meta_of(i);
           if (m & kPaired) {
             const uint32_t step = m & kEnd ? ~0u : 1u;
@@ -709,10 +756,10 @@ __global__ __launch_bounds__(BLOCK) void kp_reduce_main(DecodeParams p) {
       const uint32_t scale = misc[1];
       // Straight-line code from here to the sorted sequence: the LDS operations of a lane's 16 records
       // are issued together and no array is assigned inside a branch.
-      uint32_t ca[kNR];  // cell | arrival slot << 16; then: first place of the cell; then: place in the sorted sequence
+      uint32_t ca[NR];  // cell | arrival slot << 16; then: first place of the cell; then: place in the sorted sequence
       uint32_t t_max = 0;
 #pragma unroll
-      for (int i = 0; i < kNR; ++i) {
+      for (int i = 0; i < NR; ++i) {
         const bool ev = (meta_of(i) & kPaired) != 0u;
         t_max = ev && t[i] > t_max ? t[i] : t_max;
         uint32_t c = __umulhi(t[i], scale);
@@ -723,14 +770,14 @@ __global__ __launch_bounds__(BLOCK) void kp_reduce_main(DecodeParams p) {
         ca[i] = c | (((old >> sh) & 0xFFFFu) << 16);
       }
       if (__builtin_amdgcn_ballot_w64(t_max > misc[2]) && lane == 0u) tmp[T_WIDE] = 1u;  // a clock past the span
-      __syncthreads();
+      team_sync<BLOCK>();
       if (stop_after == kStepCounted) break;
       // (the registers that cross this barrier are made opaque: values derived from them for the next
       // phase would otherwise be computed before it and held in registers across it)
 #pragma unroll
-      for (int i = 0; i < kNR; ++i) asm volatile("" : "+v"(t[i]), "+v"(ca[i]));
+      for (int i = 0; i < NR; ++i) asm volatile("" : "+v"(t[i]), "+v"(ca[i]));
 #pragma unroll
-      for (int i = 0; i < kNR / 4; ++i) asm volatile("" : "+v"(mq[i]));
+      for (int i = 0; i < NR / 4; ++i) asm volatile("" : "+v"(mq[i]));
       {  // exclusive prefix sum over the cell counters, 16 cells (8 words) per thread
         u32x4 a = reinterpret_cast<u32x4*>(cells)[2 * tid], b = reinterpret_cast<u32x4*>(cells)[2 * tid + 1];
         uint32_t wv[8] = {a.x, a.y, a.z, a.w, b.x, b.y, b.z, b.w};
@@ -752,7 +799,7 @@ __global__ __launch_bounds__(BLOCK) void kp_reduce_main(DecodeParams p) {
           o = scan_src<4>(f); f = o > f ? o : f; o = scan_src<5>(f); f = o > f ? o : f;
           if (lane == 63) atomicMax(&tmp[T_MAXCELL], f);
         }
-        __syncthreads();
+        team_sync<BLOCK>();
         uint32_t base = incl - run;
         {  // + the totals of the waves below: lane h of the first row takes wave h's
           uint32_t below = (lane & 15u) < hw ? wtot[lane & 15u] : 0u;
@@ -766,14 +813,14 @@ __global__ __launch_bounds__(BLOCK) void kp_reduce_main(DecodeParams p) {
         reinterpret_cast<u32x4*>(cells)[2 * tid + 1] = b;
         if (tid == BLOCK - 1) { cells[NCELL / 2] = base + run; tmp[T_EVENTS] = base + run; }
       }
-      __syncthreads();
+      team_sync<BLOCK>();
       if (stop_after == kStepCellSums) break;
       // (the registers that cross this barrier are made opaque: values derived from them for the next
       // phase would otherwise be computed before it and held in registers across it)
 #pragma unroll
-      for (int i = 0; i < kNR; ++i) asm volatile("" : "+v"(t[i]), "+v"(ca[i]));
+      for (int i = 0; i < NR; ++i) asm volatile("" : "+v"(t[i]), "+v"(ca[i]));
 #pragma unroll
-      for (int i = 0; i < kNR / 4; ++i) asm volatile("" : "+v"(mq[i]));
+      for (int i = 0; i < NR / 4; ++i) asm volatile("" : "+v"(mq[i]));
       auto cell_start = [&](uint32_t c) -> uint32_t { return (cells[c >> 1] >> ((c & 1u) << 4)) & 0xFFFFu; };
       // sorted sequence entry besides the clock: region << 1 | END
       auto info_of = [&](int i) -> uint32_t { return ((meta_of(i) & 0x1Fu) << 1) | (meta_of(i) >> 7); };
@@ -783,20 +830,20 @@ __global__ __launch_bounds__(BLOCK) void kp_reduce_main(DecodeParams p) {
       const bool window_sort = R <= 16u && misc[2] < (1u << 26) && !tmp[T_WIDE] && tmp[T_MAXCELL] <= kMaxCellWindow;
       if (window_sort) {
 #pragma unroll
-        for (int i = 0; i < kNR; ++i) {
+        for (int i = 0; i < NR; ++i) {
           const bool ev = (meta_of(i) & kPaired) != 0u;
           const uint32_t g = cell_start(ca[i] & 0xFFFFu) + (ca[i] >> 16);
           // the word the sweep sorts: clock << 6 | region << 1 | END (no branch: the others all write one unused word)
           clk[ev ? clk_word(g) : kSpareWord] = (t[i] << 6) | info_of(i);
         }
-        __syncthreads();
+        team_sync<BLOCK>();
         if (stop_after >= kStepPlaced && stop_after <= kStepSorted) break;
       } else {
       // provisional place: cell start + arrival slot (plain index here, the padded layout comes with the
       // final places)
-      uint32_t nm[kNR];  // records in the cell (0: this record is no event) | arrival slot << 16
+      uint32_t nm[NR];  // records in the cell (0: this record is no event) | arrival slot << 16
 #pragma unroll
-      for (int i = 0; i < kNR; ++i) {
+      for (int i = 0; i < NR; ++i) {
         const uint32_t ev = 0u - ((meta_of(i) >> 6) & 1u);  // all ones for an event
         const uint32_t c = ca[i] & 0xFFFFu, mine = ca[i] >> 16;
         const uint32_t s0 = cell_start(c), s1 = cell_start(c + 1);
@@ -804,11 +851,11 @@ __global__ __launch_bounds__(BLOCK) void kp_reduce_main(DecodeParams p) {
         ca[i] = s0;
         nm[i] = ((s1 - s0) | (mine << 16)) & ev;
       }
-      __syncthreads();
+      team_sync<BLOCK>();
       if (stop_after == kStepPlaced) break;
       // rank among the records of the same cell: by clock, then by arrival slot
 #pragma unroll
-      for (int i = 0; i < kNR; ++i) {
+      for (int i = 0; i < NR; ++i) {
         const uint32_t n = nm[i] & 0xFFFFu, s0 = ca[i], mine = nm[i] >> 16, t0 = t[i];
         uint32_t before = 0;
         for (uint32_t it = 0; __builtin_amdgcn_ballot_w64(it < n); ++it) {
@@ -819,22 +866,22 @@ __global__ __launch_bounds__(BLOCK) void kp_reduce_main(DecodeParams p) {
         }
         ca[i] = s0 + before;
       }
-      __syncthreads();
+      team_sync<BLOCK>();
       if (stop_after == kStepRanked) break;
 #pragma unroll
-      for (int i = 0; i < kNR; ++i) {
+      for (int i = 0; i < NR; ++i) {
         const bool ev = (meta_of(i) & kPaired) != 0u;
         clk[ev ? clk_word(ca[i]) : kSpareWord] = t[i];
         meta[ev ? ca[i] : NPOS] = (uint8_t)info_of(i);
       }
-      __syncthreads();
+      team_sync<BLOCK>();
       if (stop_after == kStepSorted) break;
       }
 
       // ---- D: region-pair overlap, 16 consecutive records of the sorted sequence per lane ----------
       {
         const uint32_t n_events = tmp[T_EVENTS];
-        const uint32_t g0 = tid * kNR;
+        const uint32_t g0 = tid * NR;
         const uint32_t region_bits = 0xFFFFFFFFu >> (32u - R);  // places past the end carry a bit above the regions
         uint32_t pl[PLANES], inc[PLANES];
 #pragma unroll
@@ -871,7 +918,7 @@ __global__ __launch_bounds__(BLOCK) void kp_reduce_main(DecodeParams p) {
             for (int k = 0; k < PLANES; ++k) ptot[hw * 8 + k] = inc[k];
           }
           if (lane == 0) wtot[hw] = first_clock;
-          __syncthreads();
+          team_sync<BLOCK>();
 #pragma unroll
           for (int k = 0; k < PLANES; ++k) pl[k] = wave_shr1(inc[k], 0u);
           if (hw > 0) {  // lane h of a row takes wave h's net change; a scan over the row, then the entry of wave hw - 1
@@ -922,15 +969,15 @@ __global__ __launch_bounds__(BLOCK) void kp_reduce_main(DecodeParams p) {
         };
         if (window_sort) {
           // ---- the order is finished in registers; one word per record from here on ------------------
-          uint32_t key[kNR];
+          uint32_t key[NR];
           const uint32_t fake = (misc[2] << 6) | 0x3Fu;
-          if (tmp[T_MAXCELL] <= 9u) sorted_own<NPOS>(clk, tid, n_events, fake, key);
-          else sorted_pairs<NPOS>(clk, tid, n_events, fake, key);
+          if (tmp[T_MAXCELL] <= NR / 2 + 1u) sorted_own<BLOCK, NR>(clk, tid, n_events, fake, key);
+          else sorted_pairs<BLOCK, NR>(clk, tid, n_events, fake, key);
 #pragma unroll
-          for (int i = 0; i < kNR; ++i) planes_step<PLANES>(pl, key_region_bit(key[i]), key_end_mask(key[i]));
+          for (int i = 0; i < NR; ++i) planes_step<PLANES>(pl, key_region_bit(key[i]), key_end_mask(key[i]));
           state_before(key_clock(key[0]));
 #pragma unroll
-          for (int i = 0; i < kNR; ++i) asm volatile("" : "+v"(key[i]));  // (opaque across the barrier, as above)
+          for (int i = 0; i < NR; ++i) asm volatile("" : "+v"(key[i]));  // (opaque across the barrier, as above)
           // ---- the sorted sequence as segments: the set of active regions after record k and the ticks
           // until record k + 1.  O[a][b] = sum over segments of ticks * active(a) * active(b) is a 16 x K by
           // K x 16 matrix product: the matrix cores take it 64 segments at a time (i8 operands: the ticks in
@@ -940,11 +987,11 @@ __global__ __launch_bounds__(BLOCK) void kp_reduce_main(DecodeParams p) {
           const uint32_t t_next = (uint32_t)__builtin_amdgcn_update_dpp((int)t_above, (int)key_clock(key[0]), 0x130, 0xF, 0xF, false);  // wave_shl:1
           // (places past the end of the sequence carry the workgroup's last clock: stretches of length 0
           // behind a last one in which no region is open)
-          uint32_t len[kNR];
+          uint32_t len[NR];
           uint32_t any_len = 0;
 #pragma unroll
-          for (int i = 0; i < kNR; ++i) {
-            len[i] = (i + 1 < kNR ? key_clock(key[i + 1]) : t_next) - key_clock(key[i]);
+          for (int i = 0; i < NR; ++i) {
+            len[i] = (i + 1 < NR ? key_clock(key[i + 1]) : t_next) - key_clock(key[i]);
             any_len |= len[i];
           }
           {  // OR over the wave
@@ -955,31 +1002,36 @@ __global__ __launch_bounds__(BLOCK) void kp_reduce_main(DecodeParams p) {
           }
           if (any_len < (1u << 21)) {  // else: a gap of more than three limbs, the general way takes this wave
             const uint32_t n_limbs = any_len < (1u << 7) ? 1u : (any_len < (1u << 14) ? 2u : 3u);
-            // The lane's own 16 places of the sequence are free now (every neighbour read them before the last
-            // barrier): they take the active sets and two limbs, the 16 metadata bytes the third limb.
-            u32x4* own = reinterpret_cast<u32x4*>(clk + clk_word(g0));
-            {
-              uint32_t l0[4] = {0u, 0u, 0u, 0u};
+            // The lane's own places of the sequence are free now (every neighbour read them before the last
+            // barrier): they take the active sets (16 bits each) and two limbs, its metadata bytes the third limb.
+            uint32_t* own = clk + clk_word(g0);
+            auto limb_words = [&](int shift, uint32_t (&l)[NR / 4]) __attribute__((always_inline)) {
 #pragma unroll
-              for (int i = 0; i < kNR; ++i) l0[i >> 2] |= (len[i] & 0x7Fu) << (8 * (i & 3));
-              own[2] = u32x4{l0[0], l0[1], l0[2], l0[3]};
-            }
-            if (n_limbs > 1u) {
-              uint32_t l1[4] = {0u, 0u, 0u, 0u};
+              for (int i = 0; i < NR / 4; ++i) l[i] = 0u;
 #pragma unroll
-              for (int i = 0; i < kNR; ++i) l1[i >> 2] |= ((len[i] >> 7) & 0x7Fu) << (8 * (i & 3));
-              own[3] = u32x4{l1[0], l1[1], l1[2], l1[3]};
+              for (int i = 0; i < NR; ++i) l[i >> 2] |= ((len[i] >> shift) & 0x7Fu) << (8 * (i & 3));
+            };
+            uint32_t l0[NR / 4], l1[NR / 4];
+            limb_words(0, l0);
+            if constexpr (NR == 16) {
+              reinterpret_cast<u32x4*>(own)[2] = u32x4{l0[0], l0[1], l0[2], l0[3]};
+              if (n_limbs > 1u) {
+                limb_words(7, l1);
+                reinterpret_cast<u32x4*>(own)[3] = u32x4{l1[0], l1[1], l1[2], l1[3]};
+              }
+            } else {
+              limb_words(7, l1);
             }
             if (n_limbs > 2u) {
-              uint32_t l2[4] = {0u, 0u, 0u, 0u};
+              uint32_t l2[NR / 4];
+              limb_words(14, l2);
 #pragma unroll
-              for (int i = 0; i < kNR; ++i) l2[i >> 2] |= ((len[i] >> 14) & 0x7Fu) << (8 * (i & 3));
-              reinterpret_cast<u32x4*>(meta)[tid] = u32x4{l2[0], l2[1], l2[2], l2[3]};
+              for (int i = 0; i < NR / 4; ++i) reinterpret_cast<uint32_t*>(meta)[tid * (NR / 4) + i] = l2[i];
             }
-            uint32_t mk[kNR / 2];  // active sets after records 2x and 2x + 1, 16 bits each
+            uint32_t mk[NR / 2];  // active sets after records 2x and 2x + 1, 16 bits each
             uint32_t act_even = 0u;
 #pragma unroll
-            for (int i = 0; i < kNR; ++i) {
+            for (int i = 0; i < NR; ++i) {
               planes_step<PLANES>(pl, key_region_bit(key[i]), key_end_mask(key[i]));
               uint32_t act = pl[0];
 #pragma unroll
@@ -987,9 +1039,13 @@ __global__ __launch_bounds__(BLOCK) void kp_reduce_main(DecodeParams p) {
               if (i & 1) mk[i >> 1] = __builtin_amdgcn_perm(act, act_even, 0x05040100u);  // the low halves of the two
               else act_even = act;
             }
-            own[0] = u32x4{mk[0], mk[1], mk[2], mk[3]};
-            own[1] = u32x4{mk[4], mk[5], mk[6], mk[7]};
-            products = (tid & ~63u) * kNR < n_events ? n_limbs : 0u;  // this wave holds records
+            if constexpr (NR == 16) {
+              reinterpret_cast<u32x4*>(own)[0] = u32x4{mk[0], mk[1], mk[2], mk[3]};
+              reinterpret_cast<u32x4*>(own)[1] = u32x4{mk[4], mk[5], mk[6], mk[7]};
+            } else {
+              *reinterpret_cast<u32x4*>(own) = u32x4{mk[0], mk[1], l0[0], l1[0]};
+            }
+            products = (tid & ~63u) * NR < n_events ? n_limbs : 0u;  // this wave holds records
           } else {
             // Its neighbours may add up their own stretches only: what is open where this wave's begin counts as
             // switched on there, what is open where they end as switched off.
@@ -1003,42 +1059,39 @@ __global__ __launch_bounds__(BLOCK) void kp_reduce_main(DecodeParams p) {
             };
             if (lane == 0) add_open(0u - key_clock(key[0]));
 #pragma unroll
-            for (int i = 0; i < kNR; ++i)
+            for (int i = 0; i < NR; ++i)
               switch_record(key_region_bit(key[i]) & region_bits, key_end_mask(key[i]), key_clock(key[i]));
             if (lane == 63) add_open(t_next);
           }
         } else {
           // ---- the general way: the sequence is already in order, clocks up to 32 bits, up to 32 regions --
-          uint32_t st[kNR], sx[kNR];  // clock, region bit (0: no record)
+          uint32_t st[NR], sx[NR];  // clock, region bit (0: no record)
           uint32_t ends = 0;           // bit i: record i is an END
-          const u32x4 mv = reinterpret_cast<const u32x4*>(meta)[tid];
-          const uint32_t mw[4] = {mv.x, mv.y, mv.z, mv.w};
-          const u32x4* tv = reinterpret_cast<const u32x4*>(clk + clk_word(g0));
+          uint32_t mw[NR / 4];
+          load_meta(tid, mw);
+          load_run<NR>(clk, tid, st);
 #pragma unroll
-          for (int i = 0; i < 4; ++i) {
-            const u32x4 v = tv[i];
-            st[4 * i] = v.x; st[4 * i + 1] = v.y; st[4 * i + 2] = v.z; st[4 * i + 3] = v.w;
-          }
-#pragma unroll
-          for (int i = 0; i < kNR; ++i) {
+          for (int i = 0; i < NR; ++i) {
             const uint32_t info = (mw[i >> 2] >> (8 * (i & 3))) & 0xFFu;
             sx[i] = g0 + i < n_events ? 1u << (info >> 1) : 0u;
             ends |= (info & 1u) << i;
           }
           auto end_mask = [&](int i) -> uint32_t { return (uint32_t)((int32_t)(ends << (31 - i)) >> 31); };  // all ones for an END
 #pragma unroll
-          for (int i = 0; i < kNR; ++i) planes_step<PLANES>(pl, sx[i], end_mask(i));
+          for (int i = 0; i < NR; ++i) planes_step<PLANES>(pl, sx[i], end_mask(i));
           state_before(st[0]);
 #pragma unroll
-          for (int i = 0; i < kNR; ++i) switch_record(sx[i], end_mask(i), st[i]);
+          for (int i = 0; i < NR; ++i) switch_record(sx[i], end_mask(i), st[i]);
         }
       }
     }
     } while (0);
     // The first records of the next workgroup travel while the matrix cores work.
     request_units(wg_ahead, tid, std::integral_constant<int, 0>{}, std::integral_constant<int, kEarly>{});
-    if (products) {  // wave-uniform
-      const uint32_t n_limbs = products;
+    // (Wave-uniform, and in a scalar register: matrix instructions do not heed the execution mask, and a short branch on a
+    // vector register is taken by masking alone.)
+    const uint32_t n_limbs = (uint32_t)__builtin_amdgcn_readfirstlane((int)products);
+    if (n_limbs) {
       __builtin_amdgcn_wave_barrier();
       typedef int i32x4 __attribute__((ext_vector_type(4)));
       i32x4 acc[3];
@@ -1047,12 +1100,23 @@ __global__ __launch_bounds__(BLOCK) void kp_reduce_main(DecodeParams p) {
       const uint32_t j = lane & 15u;  // operand row / column: region j
       const uint32_t up = 15u - j;      // shift that takes bit j of a 16-bit set to its top
       // (a wave that is not full has no segments past its share of the records; with 16 waves one register is too many)
-      const uint32_t sets = BLOCK == 1024 ? 16u : (tmp[T_EVENTS] - (tid & ~63u) * kNR + 63u) >> 6;
-      for (uint32_t n = 0; n < 16 && n < sets; ++n) {  // 64 segments: those of lanes 4n .. 4n + 3
-        const uint32_t src = (tid & ~63u) + 4u * n + (lane >> 4);
-        const u32x4* from = reinterpret_cast<const u32x4*>(clk + clk_word(src * kNR));
-        const u32x4 s0 = from[0], s1 = from[1];
-        const uint32_t w8[8] = {s0.x, s0.y, s0.z, s0.w, s1.x, s1.y, s1.z, s1.w};
+      const uint32_t sets = BLOCK == 1024 && NR == 16 ? 16u : (uint32_t)__builtin_amdgcn_readfirstlane((int)(tmp[T_EVENTS] - (tid & ~63u) * NR + 63u)) >> 6;
+      for (uint32_t n = 0; n < NR && n < sets; ++n) {  // 64 segments: those of 64 / NR lanes
+        const uint32_t src = (tid & ~63u) + (64u / NR) * n + (16u / NR) * (lane >> 4);  // the first that this lane reads of
+        const u32x4* from = reinterpret_cast<const u32x4*>(clk + clk_word(src * NR));
+        uint32_t w8[8];  // sets of 16 segments
+        u32x4 l0, l1{0u, 0u, 0u, 0u};
+        if constexpr (NR == 16) {
+          const u32x4 s0 = from[0], s1 = from[1];
+          w8[0] = s0.x; w8[1] = s0.y; w8[2] = s0.z; w8[3] = s0.w; w8[4] = s1.x; w8[5] = s1.y; w8[6] = s1.z; w8[7] = s1.w;
+          l0 = from[2];
+          if (n_limbs > 1u) l1 = from[3];
+        } else {  // four lanes' places side by side
+          const u32x4 a = from[0], b = from[1], c = from[2], d = from[3];
+          w8[0] = a.x; w8[1] = a.y; w8[2] = b.x; w8[3] = b.y; w8[4] = c.x; w8[5] = c.y; w8[6] = d.x; w8[7] = d.y;
+          l0 = u32x4{a.z, b.z, c.z, d.z};
+          l1 = u32x4{a.w, b.w, c.w, d.w};
+        }
         // One byte per segment, all ones if region j is open in it: the byte permute's selectors 8..11
         // replicate the top bits of the four halves of its two operands.  As an i8 operand such a byte
         // is -1, so the products below come out negated.
@@ -1061,16 +1125,14 @@ __global__ __launch_bounds__(BLOCK) void kp_reduce_main(DecodeParams p) {
         for (int y = 0; y < 4; ++y)
           ones[y] = (int)__builtin_amdgcn_perm(w8[2 * y + 1] << up, w8[2 * y] << up, 0x0B0A0908u);
         const i32x4 bits = ones;
-        const u32x4 l0 = from[2];
         acc[0] = __builtin_amdgcn_mfma_i32_16x16x64_i8(ones & i32x4{(int)l0.x, (int)l0.y, (int)l0.z, (int)l0.w}, bits,
                                                        acc[0], 0, 0, 0);
         if (n_limbs > 1u) {
-          const u32x4 l1 = from[3];
           acc[1] = __builtin_amdgcn_mfma_i32_16x16x64_i8(ones & i32x4{(int)l1.x, (int)l1.y, (int)l1.z, (int)l1.w}, bits,
                                                          acc[1], 0, 0, 0);
         }
         if (n_limbs > 2u) {
-          const u32x4 l2 = reinterpret_cast<const u32x4*>(meta)[src];
+          const u32x4 l2 = *reinterpret_cast<const u32x4*>(meta + src * NR);
           acc[2] = __builtin_amdgcn_mfma_i32_16x16x64_i8(ones & i32x4{(int)l2.x, (int)l2.y, (int)l2.z, (int)l2.w}, bits,
                                                          acc[2], 0, 0, 0);
         }
@@ -1084,7 +1146,7 @@ __global__ __launch_bounds__(BLOCK) void kp_reduce_main(DecodeParams p) {
         if (a <= b && b < R && total) atomicAdd(&oacc32[a * (R | 1u) + b], total);
       }
     }
-    __syncthreads();
+    team_sync<BLOCK>();
     request_header(wg_ahead, tid);
     if (stop_after) continue;
 
@@ -1120,17 +1182,22 @@ __global__ __launch_bounds__(BLOCK) void kp_reduce_main(DecodeParams p) {
       uint32_t* ba = oacc32 + b * (R | 1u) + a;
       const uint32_t v = a == b ? *ab : *ab + *ba;
       *ab = 0u; *ba = 0u;
-      oacc[i] += v;
+      if constexpr (TEAMS == 1) oacc[i] += v;
+      else if (v) atomicAdd(&oacc[i], (unsigned long long)v);
     }
     if (tid == 0) {
-      ctr[H_INVALID] += wg_invalid;
-      ctr[H_DISORDER] += tmp[T_DISORDER];
-      ctr[H_NONMONO] += tmp[T_NONMONO];
-      ctr[H_PAIRS] += tmp[T_PAIRS];
-      ctr[H_ORPHAN_START] += tmp[T_STARTS] - tmp[T_ENDS] - tmp[T_PAIRS];  // T_STARTS counts the records
-      ctr[H_ORPHAN_END] += tmp[T_ENDS] - tmp[T_PAIRS];
-      ctr[H_SPAN_OVF] += misc[0];
-      ctr[H_OVERLAP_WGS] += eligible ? 1u : 0u;
+      auto count = [&](int which, uint32_t n) {
+        if constexpr (TEAMS == 1) ctr[which] += n;
+        else if (n) atomicAdd(&ctr[which], (unsigned long long)n);
+      };
+      count(H_INVALID, wg_invalid);
+      count(H_DISORDER, tmp[T_DISORDER]);
+      count(H_NONMONO, tmp[T_NONMONO]);
+      count(H_PAIRS, tmp[T_PAIRS]);
+      count(H_ORPHAN_START, tmp[T_STARTS] - tmp[T_ENDS] - tmp[T_PAIRS]);  // T_STARTS counts the records
+      count(H_ORPHAN_END, tmp[T_ENDS] - tmp[T_PAIRS]);
+      count(H_SPAN_OVF, misc[0]);
+      count(H_OVERLAP_WGS, eligible ? 1u : 0u);
     }
     // No barrier here: the arrays this tail reads and resets are next written in B, two barriers on, and
     // what the head of the next workgroup writes first (temporaries, header words) is touched here only by
@@ -1140,49 +1207,57 @@ __global__ __launch_bounds__(BLOCK) void kp_reduce_main(DecodeParams p) {
 
   // ---- flush this decoder workgroup's totals --------------------------------------------------
   unsigned long long* out = reinterpret_cast<unsigned long long*>(p.out);
-  for (uint32_t i = tid_k; i < R * 64; i += BLOCK) {
+  for (uint32_t i = threadIdx.x; i < R * 64; i += n_threads) {
     const uint32_t h = hist[(i >> 6) * kHistStride + (i & 63u)];
     if (h) atomicAdd(&out[SL.hist + i], (unsigned long long)h);
   }
-  for (uint32_t i = tid_k; i < R * R; i += BLOCK)
+  for (uint32_t i = threadIdx.x; i < R * R; i += n_threads)
     if (oacc[i]) atomicAdd(&out[SL.F + i], oacc[i]);  // (the upper triangle)
-  for (uint32_t r = tid_k; r < R; r += BLOCK) {
+  for (uint32_t r = threadIdx.x; r < R; r += n_threads) {
     if (reg_min[r] != 0xFFFFFFFFu || reg_max[r] || reg_sum[r]) {
       atomicAdd(&out[SL.sum + r], reg_sum[r]);
       atomicMax(&out[SL.max + r], (unsigned long long)reg_max[r]);
       atomicMin(&out[SL.min + r], (unsigned long long)reg_min[r]);
     }
   }
-  if (tid_k < H_STATUS && ctr[tid_k]) atomicAdd(&out[tid_k], ctr[tid_k]);
+  if (threadIdx.x < H_STATUS && ctr[threadIdx.x]) atomicAdd(&out[threadIdx.x], ctr[threadIdx.x]);
 }
 
 // Launch shape of one kernel instantiation for one LDS size, queried once per device.
 struct LaunchCache { int dev = -1; uint32_t max_grid = 0; };
 
-template <int BLOCK, int PLANES>
+template <int BLOCK, int NR, int TEAMS, int PLANES, int RMAX, int PERWAVE>
 kp_status launch_main(const DecodeParams& p, hipStream_t s) {
-  auto kern = kp_reduce_main<BLOCK, PLANES>;
+  auto kern = kp_reduce_main<BLOCK, NR, TEAMS, PLANES, RMAX, PERWAVE>;
   static thread_local LaunchCache cache;
   int dev = 0;
   KP_HIP_TRY(hipGetDevice(&dev));
   if (cache.dev != dev) {
     int per_cu = 0, cus = 0;
-    KP_HIP_TRY(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kern, BLOCK, 0));
-    if (per_cu < 1) return kp::fail(KP_ERR_UNSUPPORTED_SHAPE, "decoder kernel does not fit one CU (LDS %u B)", Lds<BLOCK>::total);
+    KP_HIP_TRY(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kern, BLOCK * TEAMS, 0));
+    if (per_cu < 1) return kp::fail(KP_ERR_UNSUPPORTED_SHAPE, "decoder kernel does not fit one CU (LDS %u B)", Lds<BLOCK, NR, TEAMS, RMAX, PERWAVE>::total);
     KP_HIP_TRY(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev));
     cache.dev = dev; cache.max_grid = (uint32_t)per_cu * (uint32_t)cus;
   }
+  uint32_t teams = 1;
+  if (TEAMS > 1) {  // one decoder workgroup per CU first, then more waves in it
+    teams = (p.n_wg + 255u) / 256u;
+    if (teams > (uint32_t)TEAMS) teams = TEAMS;
+  }
   uint32_t grid = cache.max_grid;
-  if (grid > p.n_wg) grid = p.n_wg;
-  hipLaunchKernelGGL(kern, dim3(grid), dim3(BLOCK), 0, s, p);
+  if (grid > (p.n_wg + teams - 1u) / teams) grid = (p.n_wg + teams - 1u) / teams;
+  hipLaunchKernelGGL(kern, dim3(grid), dim3(BLOCK * teams), 0, s, p);
   KP_HIP_TRY(hipGetLastError());
   return KP_OK;
 }
 
-template <int BLOCK>
-kp_status launch_planes(const DecodeParams& p, hipStream_t s) {
+template <int BLOCK, int NR, int TEAMS, int RMAX, int PERWAVE>
+kp_status launch_planes(DecodeParams& p, hipStream_t s) {
+  p.ncopy = 4;  // as many copies of the per-(wave, region) sums as their LDS array has room for
+  while (p.ncopy > 1 && p.ncopy * p.W * p.R > (uint32_t)PERWAVE) p.ncopy >>= 1;
   // counters of open waves per region run up to the number of waves
-  return p.W < 16 ? launch_main<BLOCK, 4>(p, s) : launch_main<BLOCK, 5>(p, s);
+  if constexpr (NR == 16) if (p.W < 16) return launch_main<BLOCK, NR, TEAMS, 4, RMAX, PERWAVE>(p, s);
+  return launch_main<BLOCK, NR, TEAMS, 5, RMAX, PERWAVE>(p, s);
 }
 
 kp_status reduce_impl(const void* raw, size_t n, const kp_trace_hdr& h, void* out_stats, uint32_t stop_after,
@@ -1213,9 +1288,6 @@ kp_status reduce_impl(const void* raw, size_t n, const kp_trace_hdr& h, void* ou
     return kp::fail(KP_ERR_INVALID_ARG, "raw and out_stats must be 16-byte aligned");
 
   const uint32_t W = h.waves_per_wg, R = h.n_regions, cap = h.cap_wave;
-  const int block = nrec > 4096 ? 1024 : (nrec > 1024 ? 256 : 64);  // 16 positions per lane
-  uint32_t ncopy = 4;  // as many copies of the per-(wave, region) sums as their LDS array has room for
-  while (ncopy > 1 && ncopy * W * R > kMaxPerWave) ncopy >>= 1;
 
   uint64_t* out = static_cast<uint64_t*>(out_stats);
   const uint8_t* base = static_cast<const uint8_t*>(raw);
@@ -1239,10 +1311,35 @@ kp_status reduce_impl(const void* raw, size_t n, const kp_trace_hdr& h, void* ou
     p.n_wg = h.n_wg; p.W = W; p.R = R; p.cap = cap;
     p.cap_log2 = 0; while ((1u << p.cap_log2) < cap) ++p.cap_log2;
     p.rec_cost = h.rec_cost; p.flush = h.flags & KP_FLAG_FLUSH;
-    p.nrec = nrec; p.ncopy = ncopy; p.stop_after = stop_after;
-    const kp_status st = block == 1024 ? launch_planes<1024>(p, s)
-                       : block == 256  ? launch_planes<256>(p, s)
-                                       : launch_planes<64>(p, s);
+    p.nrec = nrec; p.ncopy = 1; p.stop_after = stop_after;
+    // How many threads take a recorded workgroup, with how many records each.  Up to 16384 records: 1024 threads, 16
+    // each, which is all that fits one CU.  Fewer records leave a choice.  With no more recorded workgroups than CUs the
+    // time is one workgroup's chain of steps, and four records per lane make it shorter: 64 workgroups of 4 x 128 records
+    // 20.6 us with 16 each (one wave), 16.7 with four (four waves); 256 of 8 x 512 32.3 and 30.1; 100 of 1 x 4096 26.7 and
+    // 24.0.  With more of them it is the work, most of which a wave does for all its places whether they hold records or
+    // not: as few places as the records need, and as many waves on a CU as LDS allows, whose arrays are sized for at most
+    // 8, 16 or 32 regions.  Up to 1024 records one wave decodes a workgroup, and the waves of a decoder workgroup share
+    // the running totals, which reach HBM once: every address of them takes about 20 ns per decoder workgroup.  Against
+    // one wave per decoder workgroup, 16 records per lane, arrays for 32 regions: 20000 workgroups of 1 x 16 records 361 ->
+    // 76 us (16 records per lane in teams 168), 60000 of 1 x 64, 16 regions 1084 -> 219 (490), 8192 of 4 x 128 172 -> 73, 3000
+    // of 16 x 64 90 -> 42; 256 threads, arrays for 8 regions: 16000 of 2 x 1024 693 -> 487.
+    kp_status st;
+    if (h.n_wg <= 256 && nrec <= 4096) {
+      st = nrec > 1024 ? launch_planes<1024, 4, 1, KP_MAX_REGIONS, kMaxPerWave>(p, s)
+         : nrec > 256  ? launch_planes<256, 4, 1, KP_MAX_REGIONS, 512>(p, s)
+                       : launch_planes<64, 4, 1, KP_MAX_REGIONS, 512>(p, s);
+    } else if (nrec > 4096) {
+      st = launch_planes<1024, 16, 1, KP_MAX_REGIONS, kMaxPerWave>(p, s);
+    } else if (nrec > 1024) {
+      st = R <= 8 ? launch_planes<256, 16, 1, 8, 128>(p, s) : R <= 16 ? launch_planes<256, 16, 1, 16, 256>(p, s)
+                                                           : launch_planes<256, 16, 1, KP_MAX_REGIONS, 512>(p, s);
+    } else if (nrec > 256) {
+      st = R <= 8 ? launch_planes<64, 16, 12, 8, 128>(p, s) : R <= 16 ? launch_planes<64, 16, 12, 16, 256>(p, s)
+                                                           : launch_planes<64, 16, 6, KP_MAX_REGIONS, 512>(p, s);
+    } else {
+      st = R <= 8 ? launch_planes<64, 4, 16, 8, 128>(p, s) : R <= 16 ? launch_planes<64, 4, 12, 16, 256>(p, s)
+                                                           : launch_planes<64, 4, 8, KP_MAX_REGIONS, 512>(p, s);
+    }
     if (st != KP_OK) return st;
   }
   if (main_end) KP_HIP_TRY(hipEventRecord(main_end, s));

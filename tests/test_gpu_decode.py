@@ -100,6 +100,24 @@ def test_spans_from_a_few_ticks_to_many_million(kp, oracle_mod, p0):
         check(raw, oracle_mod)
 
 
+@pytest.mark.parametrize("n_wg,W,R,cap", [
+    (256, 1, 8, 256), (257, 1, 8, 256), (257, 1, 9, 256), (257, 2, 17, 128), (256, 2, 17, 128),      # 256 records
+    (256, 4, 3, 256), (300, 4, 8, 256), (300, 4, 16, 256), (300, 4, 17, 256), (300, 16, 32, 32),    # up to 1024
+    (256, 8, 32, 512), (260, 8, 8, 512), (260, 8, 16, 512), (260, 8, 17, 512), (260, 16, 8, 256),  # up to 4096
+    (3300, 16, 8, 16), (1500, 16, 32, 16), (4100, 1, 1, 2), (513, 3, 5, 64), (5000, 5, 7, 32)])
+def test_every_split_of_the_decoder(kp, oracle_mod, n_wg, W, R, cap):
+    """The number of recorded workgroups, of record slots and of regions decide how many threads decode a workgroup, how
+    many records a lane takes and how many workgroups share one set of totals: both sides of every line, clean and damaged
+    traces, crowded and sparse clocks."""
+    for p0, seed in ((1.0, 1), (5.0, 2), (11.0, 3)):
+        spec = inputs.TraceSpec(n_wg=n_wg, waves=W, n_regions=R, cap_wave=cap, total_per_wave=cap, total_var=cap // 2, seed=seed,
+                                dist="lognormal", p0=p0, p1=1.0, gap_max=1 if p0 < 3 else 32, p_orphan=0.02, p_swap=0.01 if cap >= 16 else 0.0)
+        raw, _ = inputs.gen_trace(spec)
+        check(raw, oracle_mod, use_hdr=True)
+    raw = inputs.messy_trace(n_wg + W, n_wg=min(n_wg, 600), waves=W, n_regions=R, cap_wave=min(cap, 64), p_bad=0.01, allow_nonmono=False)
+    check(raw, oracle_mod, use_hdr=True)
+
+
 def test_empty_trace(kp, oracle_mod):
     check(inputs.encode_trace([], 4, 3, 8), oracle_mod)
 
