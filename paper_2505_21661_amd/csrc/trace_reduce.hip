@@ -1239,13 +1239,10 @@ kp_status launch_main(const DecodeParams& p, hipStream_t s) {
     KP_HIP_TRY(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev));
     cache.dev = dev; cache.max_grid = (uint32_t)per_cu * (uint32_t)cus;
   }
-  uint32_t teams = 1;
-  if (TEAMS > 1) {  // one decoder workgroup per CU first, then more waves in it
-    teams = (p.n_wg + 255u) / 256u;
-    if (teams > (uint32_t)TEAMS) teams = TEAMS;
-  }
   uint32_t grid = cache.max_grid;
-  if (grid > (p.n_wg + teams - 1u) / teams) grid = (p.n_wg + teams - 1u) / teams;
+  if (grid > p.n_wg) grid = p.n_wg;
+  uint32_t teams = (p.n_wg + grid - 1u) / grid;  // (every CU has a decoder workgroup before one gets a second team)
+  if (teams > (uint32_t)TEAMS) teams = TEAMS;
   hipLaunchKernelGGL(kern, dim3(grid), dim3(BLOCK * teams), 0, s, p);
   KP_HIP_TRY(hipGetLastError());
   return KP_OK;
