@@ -6,12 +6,14 @@
 // iter, region} that kp_trace_pairs wrote for the waves of a workgroup are folded into one entry
 // per (workgroup, region, iteration): {max dur, min start, max (start + dur), rows folded}.
 //
-// A streaming kernel: one decoder workgroup per recorded workgroup at a time (persistent, grid
-// stride), its table in LDS.  Hardware wave h reads the rows of recorded waves h, h + 8, ... with
-// 16-byte loads, four per lane and step and four steps in flight, and folds them with LDS atomics; the
-// table then goes to
-// HBM with 16-byte stores and is reset in the same pass.  The rows of a region are kept
-// max_iter + 1 entries apart in LDS so that equal iterations of different regions use different banks.
+// A streaming kernel: persistent decoder workgroups, one recorded workgroup at a time, its table in LDS.  The rows
+// come with 16-byte loads, four per lane and step, two steps in flight, which do not end with a recorded workgroup: the
+// first rows of the next are on their way while the table is written (16-byte stores) and reset.
+// What bounds it: HBM.  2^25 rows of 4096 workgroups of 8 waves, 16 regions x 64 iterations (0.53 GB, and 67 MB of
+// table): 189 us with every wait a wait for all loads (branches around the folds, buffers handed on) and every
+// recorded workgroup starting with nothing on its way, 158 us without; 118 us with one decoder workgroup per CU instead of
+// two and a turn's rows read in the order they lie in memory, 105 us (5.6 TB/s) with two steps in flight instead of
+// three and runs of recorded workgroups per XCD.
 #include "kp_common.h"
 
 namespace {
@@ -19,6 +21,8 @@ namespace {
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
 constexpr int kBlock = 512;
+constexpr uint32_t kWavesHw = kBlock / 64;
+constexpr int kDepth = 2;  // steps of 256 rows that a hardware wave has on their way
 constexpr uint32_t kMaxTableBytes = 64 * 1024;
 
 struct StagesParams {
@@ -26,7 +30,7 @@ struct StagesParams {
   const u32x4* rows;      // cap_wave / 2 row slots per (workgroup, wave)
   unsigned long long* hdr;  // n_rows, n_clipped, n_bad_region, 0
   u32x4* table;           // [n_wg][R][max_iter]
-  uint32_t n_wg, W, R, half, max_iter;
+  uint32_t n_wg, W, R, half, max_iter, stride;
 };
 
 __global__ void kp_stages_init(unsigned long long* hdr) {
@@ -41,73 +45,101 @@ __device__ inline uint32_t wave_sum(uint32_t v) {
 
 __global__ __launch_bounds__(kBlock) void kp_stages_main(StagesParams p) {
   extern __shared__ __align__(16) unsigned char smem[];
-  uint32_t* tab = reinterpret_cast<uint32_t*>(smem);  // entry (r, it) at word 4 * (r * (max_iter + 1) + it)
-  u32x4* tab4 = reinterpret_cast<u32x4*>(smem);
-  const uint32_t tid = threadIdx.x, lane = tid & 63u, hw = tid >> 6;
-  const uint32_t W = p.W, R = p.R, MI = p.max_iter, stride = MI + 1;
-  const u32x4 empty = u32x4{0u, 0xFFFFFFFFu, 0u, 0u};
+  // entry (r, it) at word r * stride + it of four arrays
+  const uint32_t stride = p.stride, words = p.R * stride, array = words + 64u;  // (64: a place for every lane without a row)
+  uint32_t* longest = reinterpret_cast<uint32_t*>(smem);
+  uint32_t* first = longest + array;
+  uint32_t* last = first + array;
+  uint32_t* folded = last + array;
+  const uint32_t tid = threadIdx.x, lane = tid & 63u, hw = (uint32_t)__builtin_amdgcn_readfirstlane((int)(tid >> 6));
+  const uint32_t W = p.W, R = p.R, MI = p.max_iter;
 
-  for (uint32_t i = tid; i < R * stride; i += kBlock) tab4[i] = empty;
+  auto reset = [&](uint32_t at) { longest[at] = 0u; first[at] = 0xFFFFFFFFu; last[at] = 0u; folded[at] = 0u; };
+  for (uint32_t i = tid; i < words; i += kBlock) reset(i);
   __syncthreads();
 
   uint32_t n_rows = 0, n_clipped = 0, n_bad = 0;
-  auto fold = [&](const u32x4& row) {
+  // Folds a row if it is one.  Without branches: loads that a branch lies behind would all be waited for at its end.
+  auto fold = [&](const u32x4& row, bool is_row) __attribute__((always_inline)) {
     const uint32_t start = row.x, dur = row.y, it = row.z, region = row.w;
-    if (region >= R) { ++n_bad; return; }
-    if (it >= MI) { ++n_clipped; return; }
-    uint32_t* e = tab + 4 * (region * stride + it);
-    atomicMax(e + 0, dur);
-    atomicMin(e + 1, start);
-    atomicMax(e + 2, start + dur);
-    atomicAdd(e + 3, 1u);
-    ++n_rows;
+    const bool known = is_row && region < R, kept = known && it < MI;
+    n_bad += is_row && !known ? 1u : 0u;
+    n_clipped += known && !kept ? 1u : 0u;
+    n_rows += kept ? 1u : 0u;
+    const uint32_t at = kept ? region * stride + it : words + lane;
+    atomicMax(&longest[at], dur);
+    atomicMin(&first[at], start);
+    atomicMax(&last[at], start + dur);
+    atomicAdd(&folded[at], 1u);
   };
 
-  for (uint32_t wg = blockIdx.x; wg < p.n_wg; wg += gridDim.x) {
-    for (uint32_t w = hw; w < W; w += kBlock / 64) {
-      const size_t seg = (size_t)wg * W + w;
-      uint32_t cnt = p.count[seg];
-      cnt = cnt < p.half ? cnt : p.half;  // a count beyond the wave's slots cannot be honoured
-      const u32x4* rows = p.rows + seg * p.half;
-      // Four rows per lane and step, and the rows of the next three steps are requested before this
-      // step's are folded, so that the folds (LDS atomics) run under the loads and a wave keeps 16 KiB
-      // in flight (measured for 1.3e8 rows: 0.595 ms with one step in flight, 0.548 with two, 0.510
-      // with three, 0.500 with four).  A row past the count is read from the wave's last valid row (or
-      // not at all for an empty wave) and not folded.
-      if (cnt == 0) continue;
-      auto fetch = [&](uint32_t j0, u32x4 (&r)[4]) {
+  // Turn i of this decoder workgroup takes recorded workgroup wg_of(i).  Decoder workgroups are dealt round-robin to the
+  // eight XCDs; each XCD takes a run of consecutive recorded workgroups (all of them in turn: 114 us where this takes 105).
+  const uint32_t xcd = blockIdx.x & 7u, many = p.n_wg & 7u, rest = gridDim.x & 7u;
+  const uint32_t mine = (p.n_wg >> 3) + (xcd < many ? 1u : 0u), apart = (gridDim.x >> 3) + (xcd < rest ? 1u : 0u);
+  const uint32_t from = xcd * (p.n_wg >> 3) + (xcd < many ? xcd : many) + (blockIdx.x >> 3);
+  const uint32_t turns = (mine - (blockIdx.x >> 3) + apart - 1u) / apart;
+  auto wg_of = [&](uint32_t i) { return from + i * apart; };
+  // A turn's steps: unit q is block q % blocks of 256 rows of recorded wave q / blocks; hardware wave h takes units h, h + 8, ...
+  // Every hardware wave makes the same number of steps, some of them without rows.  (Wave after wave of 256 rows each instead,
+  // which starts eight streams 16 KiB apart: 131 us, consecutive blocks 117.)
+  const uint32_t blocks = (p.half + 255u) / 256u, steps = (W * blocks + kWavesHw - 1u) / kWavesHw;
+  const uint32_t w_step = kWavesHw / blocks, block_step = kWavesHw % blocks;
+
+  // The step requested next: turn, step, recorded wave and block of 256 rows; cnt: rows of that recorded wave, by a scalar
+  // load (a vector load among those of the rows would be waited for together with them).
+  uint32_t at_turn = 0, at_step = 0, at_w = hw / blocks, at_block = hw % blocks;
+  // Requests it; gives the number of its rows.  Always four loads, or the waits for the steps behind it would be for all of
+  // its own as well: a lane without a row reads the step's last one, a step without rows the first one there is.
+  typedef const __attribute__((address_space(4))) uint32_t* scalar_ptr;
+  auto count_at = [&]() __attribute__((always_inline)) -> uint32_t {
+    return ((scalar_ptr)(uintptr_t)p.count)[(size_t)wg_of(at_turn < turns ? at_turn : turns - 1u) * W + (at_w < W ? at_w : 0u)];
+  };
+  uint32_t cnt = count_at();
+  auto request = [&](u32x4 (&r)[4]) __attribute__((always_inline)) -> uint32_t {
+    cnt = cnt < p.half ? cnt : p.half;  // a count beyond the wave's slots cannot be honoured
+    const uint32_t begin = at_block * 256u;
+    uint32_t n = cnt > begin ? cnt - begin : 0u;
+    n = at_turn < turns && at_w < W ? (n < 256u ? n : 256u) : 0u;
+    const u32x4* rows = p.rows + (n ? ((size_t)wg_of(at_turn) * W + at_w) * p.half + begin : (size_t)0);
+    const uint32_t top = n ? n - 1u : 0u;
 #pragma unroll
-        for (int u = 0; u < 4; ++u) {
-          const uint32_t j = j0 + 64u * u;
-          r[u] = __builtin_nontemporal_load(rows + (j < cnt ? j : cnt - 1u));
+    for (uint32_t u = 0; u < 4; ++u) {
+      const uint32_t j = lane + 64u * u;
+      r[u] = __builtin_nontemporal_load(rows + (j < top ? j : top));
+    }
+    at_w += w_step; at_block += block_step;
+    if (at_block >= blocks) { at_block -= blocks; ++at_w; }
+    if (++at_step == steps) { at_step = 0; ++at_turn; at_w = hw / blocks; at_block = hw % blocks; }
+    cnt = count_at();
+    return n;
+  };
+  u32x4 buf[kDepth][4];
+  uint32_t n_of[kDepth];
+#pragma unroll
+  for (int d = 0; d < kDepth; ++d) n_of[d] = request(buf[d]);
+  uint32_t turn = 0, step = 0;
+  while (turn < turns) {  // (no exit inside: the steps behind the last turn's have no rows)
+#pragma unroll
+    for (int d = 0; d < kDepth; ++d) {
+#pragma unroll
+      for (uint32_t u = 0; u < 4; ++u)
+        fold(buf[d][u], lane + 64u * u < n_of[d]);
+      n_of[d] = request(buf[d]);
+      if (++step == steps && turn < turns) {
+        __syncthreads();
+        // table to HBM, and reset for the next workgroup
+        u32x4* dst = p.table + (size_t)wg_of(turn) * R * MI;
+        for (uint32_t i = tid; i < R * MI; i += kBlock) {
+          const uint32_t r = i / MI, it = i - r * MI;
+          const uint32_t at = r * stride + it;
+          dst[i] = u32x4{longest[at], first[at], last[at], folded[at]};
+          reset(at);
         }
-      };
-      constexpr int kDepth = 4;
-      u32x4 buf[kDepth][4];
-#pragma unroll
-      for (int d = 0; d < kDepth - 1; ++d)
-        if (256u * d < cnt) fetch(lane + 256u * d, buf[d]);
-      for (uint32_t j0 = lane; j0 - lane < cnt; j0 += 256) {
-        if (j0 - lane + 256u * (kDepth - 1) < cnt) fetch(j0 + 256u * (kDepth - 1), buf[kDepth - 1]);
-#pragma unroll
-        for (int u = 0; u < 4; ++u)
-          if (j0 + 64u * u < cnt) fold(buf[0][u]);
-#pragma unroll
-        for (int d = 0; d + 1 < kDepth; ++d)
-#pragma unroll
-          for (int u = 0; u < 4; ++u) buf[d][u] = buf[d + 1][u];
+        __syncthreads();
+        step = 0; ++turn;
       }
     }
-    __syncthreads();
-    // ---- table to HBM, and reset for the next workgroup ----------------------------------------------
-    u32x4* dst = p.table + (size_t)wg * R * MI;
-    for (uint32_t i = tid; i < R * MI; i += kBlock) {
-      const uint32_t r = i / MI, it = i - r * MI;
-      const uint32_t at = r * stride + it;
-      dst[i] = tab4[at];
-      tab4[at] = empty;
-    }
-    __syncthreads();
   }
 
   n_rows = wave_sum(n_rows); n_clipped = wave_sum(n_clipped); n_bad = wave_sum(n_bad);
@@ -118,7 +150,17 @@ __global__ __launch_bounds__(kBlock) void kp_stages_main(StagesParams p) {
   }
 }
 
-struct LaunchCache { int dev = -1; uint32_t lds = 0; uint32_t max_grid = 0; };
+// Entries that the regions' rows of the table lie apart.  Regions that follow one another put an iteration of each of
+// them into neighbouring lanes: 64 lanes hold 64 / R iterations of R regions, which this many words apart fall into
+// different banks.  Where that would take more than 72 KiB, an odd number does.
+constexpr uint32_t kBanks = 64;
+inline uint32_t region_stride(uint32_t R, uint32_t max_iter) {
+  const uint32_t apart = R < kBanks ? (kBanks + R - 1u) / R : 1u;
+  const uint32_t stride = max_iter + ((apart - max_iter) & (kBanks - 1u));
+  return 16u * R * stride <= 72u * 1024u ? stride : max_iter | 1u;
+}
+
+struct LaunchCache { int dev = -1; uint32_t lds = 0; uint32_t per_cu = 0, cus = 0; };
 
 }  // namespace
 
@@ -137,7 +179,6 @@ extern "C" kp_status kp_pairs_stages(const void* pairs, int n_wg, int waves_per_
                     cap_per_wg, n_regions, max_iter);
   if (((uintptr_t)pairs & 15u) || ((uintptr_t)out_stages & 15u))
     return kp::fail(KP_ERR_INVALID_ARG, "pairs and out_stages must be 16-byte aligned");
-  const uint32_t lds = 16u * (uint32_t)n_regions * ((uint32_t)max_iter + 1u);
   if ((uint64_t)n_regions * ((uint64_t)max_iter + 1u) * 16u > kMaxTableBytes)
     return kp::fail(KP_ERR_UNSUPPORTED_SHAPE, "a table of %d regions x %d iterations exceeds %u bytes of LDS",
                     n_regions, max_iter, kMaxTableBytes);
@@ -152,6 +193,8 @@ extern "C" kp_status kp_pairs_stages(const void* pairs, int n_wg, int waves_per_
   p.table = reinterpret_cast<u32x4*>(out + 32);
   p.n_wg = (uint32_t)n_wg; p.W = (uint32_t)waves_per_wg; p.R = (uint32_t)n_regions;
   p.half = (uint32_t)(cap_per_wg / waves_per_wg) / 2u; p.max_iter = (uint32_t)max_iter;
+  p.stride = region_stride(p.R, p.max_iter);
+  const uint32_t lds = 16u * (p.R * p.stride + 64u);
 
   hipLaunchKernelGGL(kp_stages_init, dim3(1), dim3(64), 0, s, p.hdr);
   KP_HIP_TRY(hipGetLastError());
@@ -167,9 +210,17 @@ extern "C" kp_status kp_pairs_stages(const void* pairs, int n_wg, int waves_per_
     KP_HIP_TRY(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kp_stages_main, kBlock, lds));
     if (per_cu < 1) return kp::fail(KP_ERR_UNSUPPORTED_SHAPE, "stage kernel does not fit one CU (LDS %u B)", lds);
     KP_HIP_TRY(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev));
-    cache.dev = dev; cache.lds = lds; cache.max_grid = (uint32_t)per_cu * (uint32_t)cus;
+    cache.dev = dev; cache.lds = lds; cache.per_cu = (uint32_t)per_cu; cache.cus = (uint32_t)cus;
   }
-  uint32_t grid = cache.max_grid < (uint32_t)n_wg ? cache.max_grid : (uint32_t)n_wg;
+  // Decoder workgroups per CU: one streams as fast as the memory gives rows, and every further one is another place that
+  // they come from; but the turns of small workgroups are steps between barriers, which several take side by side.  One / two
+  // / three, us: 4096 workgroups of 8 x 1024 rows 105 / 123 / 144, 2000 of 4096 54 / 84 / 117, 1500 of 5 x 256 25 / 38 / 52,
+  // 9000 of 16 x 64 84 / 85 / 99, 8000 of 2 x 128 39 / 32 / 35, 60000 of 4 x 32 225 / 158 / 138, 16000 of 2 x 16 65 / 48 / 43.
+  const uint32_t rows_wg = p.W * p.half;
+  uint32_t per_cu = rows_wg >= 1024u ? 1u : rows_wg >= 192u ? 2u : 3u;
+  per_cu = per_cu < cache.per_cu ? per_cu : cache.per_cu;
+  uint32_t grid = per_cu * cache.cus;
+  grid = grid < (uint32_t)n_wg ? grid : (uint32_t)n_wg;
   hipLaunchKernelGGL(kp_stages_main, dim3(grid), dim3(kBlock), lds, s, p);
   KP_HIP_TRY(hipGetLastError());
   return KP_OK;
