@@ -5,8 +5,15 @@
 // them at trace replay (Sec. 4.2 "SM-level Data Layout", "Shared Memory Circular Buffer"; Sec. 4.3).
 // Here every record goes to position wave * cap_wave + rank, rank = seq - first surviving seq, as a
 // (clock, metadata) pair, which undoes ring rotation and out-of-order flushes in O(1) per record.
-// A sequence number that occurs twice must leave the later slot in place; that is detected by
-// counting the occupied ranks and repaired by a serial pass.
+// A sequence number that occurs twice must leave the later slot in place: only a record outside the
+// slot of its seq can share it with another, so those are placed behind the others, by an exchange
+// that says whether the rank was taken, and a workgroup with such a pair is scattered again.
+// What bounds the scatter is instruction issue: where 128 records cannot belong to more than one
+// recorded wave, everything about it is uniform and read from the lanes that hold the header's
+// counts, and units without records are left out.
+// Against every record placed as it came and the occupied ranks counted where one was displaced, wave, capacity and
+// first seq read from LDS by every unit: 4096 workgroups of 8 x 2048 records, 0.1 % displaced, timeline 289 / 282 us, waits
+// 224 / 211; waits of 9000 of 3 x 1024, partly filled, 90 / 88, 3000 of 16 x 512 88 / 84, 1000 of 12 x 512 31.6 / 31.0.
 #pragma once
 #include "kp_common.h"
 #include "kp_wave.h"
@@ -37,7 +44,7 @@ __host__ __device__ inline Lds lds_layout(uint32_t nrec) {
   Lds l;
   uint32_t o = 0;
   l.rec = o; o = align16(o + nrec * 8);
-  l.tmp = o; o = align16(o + 4 * 4);     // [0] records accepted, [1] ranks occupied, [2] accepted outside their seq's slot
+  l.tmp = o; o = align16(o + 4 * 4);     // by parity of the pass: [0, 1] some seq occurs twice, [2, 3] a record outside the slot of its seq
   l.v = o; o = align16(o + 16 * 4);      // records held per wave
   l.first = o; o = align16(o + 16 * 4);  // first surviving seq per wave
   l.end = o;
@@ -99,13 +106,13 @@ template <int BLOCK, int UNITS>
 __device__ __forceinline__ void request_workgroup(const Trace& p, uint32_t wg, InFlight<UNITS>& f) {
   const u32x4* recs = p.records + (size_t)wg * (p.nrec / 2);
   const uint32_t tid = fresh_tid(), n16 = p.nrec / 2;
+  f.total = p.wg_hdrs[(size_t)32 * wg + 8 + (tid & 15u)];  // (first: staging begins with it)
 #pragma unroll
   for (int u = 0; u < UNITS; ++u) {
     if (u * BLOCK >= n16) break;  // (uniform)
     const uint32_t i = tid + u * BLOCK;
     f.v[u] = __builtin_nontemporal_load(recs + (i < n16 ? i : n16 - 1u));
   }
-  f.total = p.wg_hdrs[(size_t)32 * wg + 8 + (tid & 15u)];
 }
 
 // Stages the requested workgroup `wg`.  Every thread of the block calls it; it ends with a barrier, after
@@ -123,57 +130,81 @@ __device__ __forceinline__ void stage_workgroup(const Trace& p, unsigned char* s
   const uint32_t tid = fresh_tid(), lane = tid & 63u;
   const uint32_t W = p.W, R = p.R, cap = p.cap, nrec = p.nrec, capm = cap - 1, cl2 = p.cap_log2;
   const uint32_t live_tag = live_tag_of(iter);
+  uint32_t* const twice = tmp + (iter & 1u);         // some seq occurs twice
+  uint32_t* const displaced = tmp + 2u + (iter & 1u);  // a record is not in the slot of its seq
 
+  if ((live_tag >> 16) == 1u) {
+    u32x4* z = reinterpret_cast<u32x4*>(rec);
+    for (uint32_t i = tid; i < nrec / 2; i += BLOCK) z[i] = u32x4{0u, 0u, 0u, 0u};
+    if (tid < 4u) tmp[tid] = 0u;
+    __syncthreads();
+  }
   if (tid < 16u) {
     const uint32_t T = tid < W ? f.total : 0u;
     const uint32_t V = T < cap ? T : cap;
     sV[tid] = V;
     sFirst[tid] = p.flush ? 0u : T - V;
   }
-  if (tid >= 64 && tid < 67) tmp[tid - 64] = 0;
-  if ((live_tag >> 16) == 1u) {
-    u32x4* z = reinterpret_cast<u32x4*>(rec);
-    for (uint32_t i = tid; i < nrec / 2; i += BLOCK) z[i] = u32x4{0u, 0u, 0u, 0u};
-  }
-  __syncthreads();
+  if (tid == 64u) { tmp[(iter + 1u) & 1u] = 0u; tmp[2u + ((iter + 1u) & 1u)] = 0u; }  // the flags of the next pass
   // ---- scatter by rank --------------------------------------------------------------------------
-  uint32_t c_field = 0;  // records of this thread accepted
-  {
-    const uint32_t n16 = nrec / 2;
-    uint32_t c_dis = 0;
+  // Records in the slot of their own seq have distinct seq modulo the ring size, hence distinct ranks.  The others
+  // (bit 2u + h of `moved`: record h of unit u) wait until those are in place.
+  uint32_t moved = 0;
+  // Two neighbouring records from slot s0 of recorded wave w, which holds V records, from seq `first` on.
+  auto accept = [&](int u, uint32_t w, uint32_t V, uint32_t first, uint32_t s0) __attribute__((always_inline)) {
+#pragma unroll
+    for (uint32_t h = 0; h < 2u; ++h) {
+      const uint32_t tag = h ? f.v[u].z : f.v[u].x, pay = h ? f.v[u].w : f.v[u].y;
+      const uint32_t k = (tag - first) & kSeqMask;  // the low 20 bits of tag - first are those of seq - first
+      const bool good = s0 + h < V && k < V && ((tag >> 20) & 0xFu) == w && ((tag >> 24) & 0x7Fu) < R;
+      const bool home = ((tag ^ (s0 + h)) & capm) == 0u;
+      if (good && home) rec[(w << cl2) + k] = make_uint2(pay, (tag >> 24) | live_tag);  // region and END flag sit in the tag as in the metadata
+      moved |= good && !home ? 1u << (2u * (uint32_t)u + h) : 0u;
+    }
+  };
+  const uint32_t n16 = nrec / 2;
+  if (cap >= 128u) {  // the 128 records of a hardware wave's unit are one recorded wave's: all about it is uniform
+    const uint32_t hw = (uint32_t)__builtin_amdgcn_readfirstlane((int)(tid >> 6));
 #pragma unroll
     for (int u = 0; u < UNITS; ++u) {
       if (u * BLOCK >= n16) break;  // (uniform)
-      const uint32_t f0 = 2u * (tid + u * BLOCK), s0 = f0 & capm;
-      const bool live = f0 < nrec;
-      const uint32_t w = live ? f0 >> cl2 : 0u;
-      const uint32_t V = live ? sV[w] : 0u, first = sFirst[w];
+      const uint32_t f0 = 128u * (hw + u * (BLOCK / 64)), w = f0 >> cl2;
+      if (f0 >= nrec) break;
+      const uint32_t T = (uint32_t)__builtin_amdgcn_readlane((int)f.total, (int)w);
+      const uint32_t V = T < cap ? T : cap;
+      if ((f0 & capm) < V) accept(u, w, V, p.flush ? 0u : T - V, (f0 & capm) + 2u * lane);
+    }
+  } else {
+#pragma unroll
+    for (int u = 0; u < UNITS; ++u) {
+      if (u * BLOCK >= n16) break;  // (uniform)
+      const uint32_t f0 = 2u * (tid + u * BLOCK), w = f0 < nrec ? f0 >> cl2 : 0u;
+      const uint32_t T = (uint32_t)__shfl((int)f.total, (int)w, 64);
+      const uint32_t V = f0 < nrec ? (T < cap ? T : cap) : 0u;
+      accept(u, w, V, p.flush || T < cap ? 0u : T - cap, f0 & capm);
+    }
+  }
+  if (__builtin_amdgcn_ballot_w64(moved != 0u) && lane == 0) *displaced = 1u;
+  __syncthreads();
+  if (*displaced == 0u) return;
+  // ---- the others: one whose rank is taken shares its seq with another record --------------------------
+  {
+    bool taken = false;
+#pragma unroll
+    for (int u = 0; u < UNITS; ++u) {
 #pragma unroll
       for (uint32_t h = 0; h < 2u; ++h) {
-        const uint32_t tag = h ? f.v[u].z : f.v[u].x, pay = h ? f.v[u].w : f.v[u].y;
-        const uint32_t k = (tag - first) & kSeqMask;  // the low 20 bits of tag - first are those of seq - first
-        const bool good = s0 + h < V && k < V && ((tag >> 20) & 0xFu) == w && ((tag >> 24) & 0x7Fu) < R;
-        c_field += good ? 1u : 0u;
-        c_dis |= good ? (tag ^ (s0 + h)) & capm : 0u;
-        if (good) rec[(w << cl2) + k] = make_uint2(pay, (tag >> 24) | live_tag);  // region and END flag sit in the tag as in the metadata
+        if (!((moved >> (2u * (uint32_t)u + h)) & 1u)) continue;
+        const uint32_t tag = h ? f.v[u].z : f.v[u].x, w = 2u * (tid + u * BLOCK) >> cl2;
+        const uint32_t at = (w << cl2) + ((tag - sFirst[w]) & kSeqMask);
+        taken = is_live(atomicExch(&recw[2u * at + 1u], (tag >> 24) | live_tag), live_tag) || taken;
+        recw[2u * at] = h ? f.v[u].w : f.v[u].y;
       }
     }
-    if (__builtin_amdgcn_ballot_w64(c_dis != 0u) && lane == 0) tmp[2] = 1u;
+    if (taken) *twice = 1u;
   }
   __syncthreads();
-  // ---- a duplicated seq leaves fewer occupied ranks than accepted records ------------------------
-  // Records that all sit in the slot of their own seq have distinct seq modulo the ring size, hence
-  // distinct ranks: only a workgroup with a record elsewhere needs the count.
-  if (tmp[2] == 0u) return;
-  {
-    uint32_t occ = 0;
-    for (uint32_t q = tid; q < nrec; q += BLOCK) occ += is_live(recw[2 * q + 1], live_tag) ? 1u : 0u;
-    occ = wave_sum(occ);
-    c_field = wave_sum(c_field);
-    if (lane == 0) { atomicAdd(&tmp[0], c_field); atomicAdd(&tmp[1], occ); }
-  }
-  __syncthreads();
-  if (tmp[1] != tmp[0]) {
+  if (*twice != 0u) {
     // Rare: some seq occurs twice.  The later slot must win, so redo this workgroup's scatter: the metadata words take the
     // largest slot of their rank first (a slot's number stays below every live tag), and the records of those slots follow.
     // 512 workgroups of 1 x 2048 slots, two such records each: timeline 301 and

@@ -111,3 +111,26 @@ def nested_trace(seed, W, R, cap, depth, inner):
             evs.append(wave[:total])
         wgs.append(inputs.events_to_wg(evs, cap, flush=False))
     return inputs.encode_trace(wgs, W, R, cap, rec_cost=7)
+
+
+def shared_seq_trace(seed, n_wg, W, R, cap):
+    """Workgroups of four kinds in turn: all records in the slots of their seq; some slots swapped; some records that repeat
+    the seq of the slot below (one of the two is in its own slot); pairs of records that share a seq outside its slot."""
+    import inputs
+
+    spec = inputs.TraceSpec(n_wg=n_wg, waves=W, n_regions=R, cap_wave=cap, total_per_wave=cap, total_var=cap // 2, seed=seed, p_orphan=0.05)
+    raw, _ = inputs.gen_trace(spec)
+    raw = raw.copy()
+    slots = raw[16 + 32 * n_wg:].reshape(n_wg, W, cap, 2)
+    rng = np.random.default_rng(seed)
+    for wg in range(n_wg):
+        w = int(rng.integers(0, W))
+        a = int(rng.integers(0, cap // 4 - 2))
+        seg = slots[wg, w]
+        if wg % 4 == 1:
+            seg[[a, a + 1]] = seg[[a + 1, a]]
+        elif wg % 4 == 2:
+            seg[a + 1, 0] = (seg[a + 1, 0] & ~np.uint32(0xFFFFF)) | (seg[a, 0] & np.uint32(0xFFFFF))
+        elif wg % 4 == 3:
+            seg[[a, a + 1], 0] = (seg[[a, a + 1], 0] & ~np.uint32(0xFFFFF)) | (seg[a + 2, 0] & np.uint32(0xFFFFF))
+    return raw

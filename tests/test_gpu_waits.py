@@ -103,6 +103,15 @@ def test_header_counts_on_either_side_of_their_line(kp, oracle_mod, n_wg, R):
     assert_waits_equal(oracle_mod, raw, run_waits(kp, raw, use_hdr=True))
 
 
+# rings of 64 (a hardware wave's 128 records are several recorded waves') and of 128 and more; several turns each
+@pytest.mark.parametrize("n_wg,W,R,cap", [(3001, 3, 5, 64), (3002, 3, 5, 128), (1205, 5, 16, 512), (603, 8, 7, 1024)])
+def test_shared_seq_in_every_other_turn(kp, oracle_mod, n_wg, W, R, cap):
+    from tests.gpu_util import shared_seq_trace
+
+    raw = shared_seq_trace(n_wg, n_wg, W, R, cap)
+    assert_waits_equal(oracle_mod, raw, run_waits(kp, raw, use_hdr=True))
+
+
 def test_many_workgroups_exercise_generation_reuse(kp, oracle_mod):
     # more recorded workgroups than resident decoder workgroups: staging area and totals are reused
     spec = inputs.TraceSpec(n_wg=3000, waves=4, n_regions=6, cap_wave=64, total_per_wave=64, total_var=40, seed=78,
