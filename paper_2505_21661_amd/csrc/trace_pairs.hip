@@ -22,7 +22,9 @@
 // makes a row.  Measured on 4096 workgroups of 8 waves x 2048 records (0.54 GB read, 0.53 GB written): 495 us with
 // the loads waited for, four ranks of look-back per record and byte-wide counters scanned over the lanes; 341 us
 // with the loads ahead and ballots in their place, one rank per lane; 270 us with two; 245 us (4.4 TB/s) with what
-// follows from the hardware wave's index in scalar registers and no code for more than two parts.
+// follows from the hardware wave's index in scalar registers and no code for more than two parts.  With 0.1 % of the records
+// displaced 272 us, 260 with staging in fewer instructions, 250 with the lanes below counted by mbcnt and the region's bits
+// matched three operands at a time.  (Non-temporal stores of the rows: 252 us, and whoever reads them next takes 15 % longer.)
 #include "kp_stage.h"
 
 namespace {
@@ -158,16 +160,18 @@ __global__ __launch_bounds__(BLOCK) void kp_pairs_main(Trace p, PairsOut o, uint
           const bool paired = paired0 || paired1;
           const uint32_t region = (paired1 ? id1 : id0) & kMRegion;
           const uint64_t pb = pb0 | pb1;
-          uint64_t same = pb;
+          uint32_t same_lo = (uint32_t)pb, same_hi = (uint32_t)(pb >> 32);  // the lanes whose pair has this lane's region
           for (uint32_t b = 0; b < region_bits; ++b) {
-            const uint64_t set = __builtin_amdgcn_ballot_w64((region >> b) & 1u);
-            same &= ((region >> b) & 1u) ? set : ~set;
+            const uint32_t bit = (uint32_t)__builtin_amdgcn_sbfe((int)region, b, 1u);  // 0 or all ones
+            const uint64_t set = __builtin_amdgcn_ballot_w64(bit != 0u);
+            same_lo &= ~((uint32_t)set ^ bit); same_hi &= ~((uint32_t)(set >> 32) ^ bit);
           }
           if (paired) {
-            const uint32_t it = seen[region] + (uint32_t)__popcll(same & lt_mask);
-            const uint64_t here_up = same & ~lt_mask;
-            if ((here_up & (here_up - 1ull)) == 0ull) seen[region] = it + 1u;  // the region's last pair of the round
-            row(n_rows + (uint32_t)__popcll(pb & lt_mask), paired1 ? start1 : start0, paired1 ? r.z : r.x, it, region);
+            const uint32_t lower = __builtin_amdgcn_mbcnt_hi(same_hi, __builtin_amdgcn_mbcnt_lo(same_lo, 0u));
+            const uint32_t it = seen[region] + lower;
+            if ((uint32_t)(__popc(same_lo) + __popc(same_hi)) == lower + 1u) seen[region] = it + 1u;  // the region's last pair of the round
+            row(__builtin_amdgcn_mbcnt_hi((uint32_t)(pb >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)pb, n_rows)),
+                paired1 ? start1 : start0, paired1 ? r.z : r.x, it, region);
           }
           n_rows += (uint32_t)__popcll(pb);
         } else {
