@@ -12,6 +12,7 @@ namespace kp {
 char* last_error_buf();
 uint32_t rec_cost();  // the value of kp_set_rec_cost: goes into the header of every trace recorded from now on
 constexpr int kLastErrorLen = 512;
+kp_status read_header(const void* raw, kp_trace_hdr* hdr, hipStream_t s);  // the header of a trace in device memory; waits for it
 
 inline kp_status fail(kp_status code, const char* fmt, ...) {
   va_list ap;

@@ -279,7 +279,7 @@ extern "C" kp_status kp_trace_pairs(const void* raw, size_t n, void* out_pairs, 
   if (!raw || !out_pairs) return kp::fail(KP_ERR_INVALID_ARG, "NULL argument");
   kp_trace_hdr h;
   hipStream_t s = static_cast<hipStream_t>(stream);
-  KP_HIP_TRY(hipMemcpyAsync(&h, raw, sizeof h, hipMemcpyDeviceToHost, s));
-  KP_HIP_TRY(hipStreamSynchronize(s));
+  const kp_status st = kp::read_header(raw, &h, s);
+  if (st != KP_OK) return st;
   return pairs_impl(raw, n, h, out_pairs, s);
 }

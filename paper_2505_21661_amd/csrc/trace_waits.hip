@@ -382,7 +382,7 @@ extern "C" kp_status kp_trace_waits(const void* raw, size_t n, void* out_waits, 
   if (!raw || !out_waits) return kp::fail(KP_ERR_INVALID_ARG, "NULL argument");
   kp_trace_hdr h;
   hipStream_t s = static_cast<hipStream_t>(stream);
-  KP_HIP_TRY(hipMemcpyAsync(&h, raw, sizeof h, hipMemcpyDeviceToHost, s));
-  KP_HIP_TRY(hipStreamSynchronize(s));
+  const kp_status st = kp::read_header(raw, &h, s);
+  if (st != KP_OK) return st;
   return waits_impl(raw, n, h, out_waits, s);
 }

@@ -288,3 +288,38 @@ def test_a_long_gap_between_short_stretches(kp, oracle_mod, W, R, cap):
         wgs.append(wg)
     raw = inputs.encode_trace(wgs, W, R, cap, rec_cost=2)
     check(raw, oracle_mod, use_hdr=True)
+
+
+def test_headers_read_back_by_several_threads(kp, oracle_mod):
+    """Every thread reads the headers of its own traces back, on a stream of its own with other work ahead (one read longer
+    than the host looks for it) or without."""
+    import threading
+
+    failures = []
+
+    def replay(i):
+        try:
+            stream = torch.cuda.Stream()
+            busy = torch.randn(4096, 4096, device="cuda")
+            for turn in range(6):
+                raw = inputs.messy_trace(900 + 10 * i + turn, n_wg=3 + turn, waves=1 + i, n_regions=2 + i, cap_wave=32)
+                n_wg, W, R, cap = (int(x) for x in raw[2:6])
+                dev = torch.from_numpy(raw.view(np.int32)).cuda()
+                out = torch.zeros(kp.kp_stats_bytes(n_wg, W, R), dtype=torch.uint8, device="cuda")
+                torch.cuda.synchronize()
+                with torch.cuda.stream(stream):
+                    for _ in range(4 if turn % 2 else 0):
+                        busy = busy @ busy * 1e-4
+                    kp.kp_trace_reduce(dev, n_wg * W * cap, out)
+                stream.synchronize()
+                if not np.array_equal(oracle_mod.decode_bytes(raw), out.cpu().numpy()):
+                    failures.append((i, turn))
+        except Exception as e:  # noqa: BLE001
+            failures.append((i, repr(e)))
+
+    threads = [threading.Thread(target=replay, args=(i,)) for i in range(3)]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    assert not failures, failures
