@@ -10,10 +10,11 @@
 // come with 16-byte loads, four per lane and step, two steps in flight, which do not end with a recorded workgroup: the
 // first rows of the next are on their way while the table is written (16-byte stores) and reset.
 // What bounds it: HBM.  2^25 rows of 4096 workgroups of 8 waves, 16 regions x 64 iterations (0.53 GB, and 67 MB of
-// table): 189 us with every wait a wait for all loads (branches around the folds, buffers handed on) and every
-// recorded workgroup starting with nothing on its way, 158 us without; 118 us with one decoder workgroup per CU instead of
-// two and a turn's rows read in the order they lie in memory, 105 us (5.6 TB/s) with two steps in flight instead of
-// three and runs of recorded workgroups per XCD.
+// table): 189 us with every wait a wait for all loads (branches around the folds, buffers handed on), every recorded
+// workgroup starting with nothing on its way and 4096 adds to one word of the header at the end, 12 ns each; 93 us
+// (6.4 TB/s of rows and table) now.
+#include <math.h>
+
 #include "kp_common.h"
 
 namespace {
@@ -22,7 +23,7 @@ typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
 constexpr int kBlock = 512;
 constexpr uint32_t kWavesHw = kBlock / 64;
-constexpr int kDepth = 2;  // steps of 256 rows that a hardware wave has on their way
+constexpr int kDepth = 2;  // steps that a hardware wave has on their way
 constexpr uint32_t kMaxTableBytes = 64 * 1024;
 
 struct StagesParams {
@@ -43,7 +44,10 @@ __device__ inline uint32_t wave_sum(uint32_t v) {
   return v;
 }
 
+// A step is PER rows per lane.
+template <int PER>
 __global__ __launch_bounds__(kBlock) void kp_stages_main(StagesParams p) {
+  constexpr uint32_t kRows = 64u * PER;
   extern __shared__ __align__(16) unsigned char smem[];
   // entry (r, it) at word r * stride + it of four arrays
   const uint32_t stride = p.stride, words = p.R * stride, array = words + 64u;  // (64: a place for every lane without a row)
@@ -51,13 +55,11 @@ __global__ __launch_bounds__(kBlock) void kp_stages_main(StagesParams p) {
   uint32_t* first = longest + array;
   uint32_t* last = first + array;
   uint32_t* folded = last + array;
+  uint32_t* counts = folded + array;  // rows, clipped, of no region
   const uint32_t tid = threadIdx.x, lane = tid & 63u, hw = (uint32_t)__builtin_amdgcn_readfirstlane((int)(tid >> 6));
   const uint32_t W = p.W, R = p.R, MI = p.max_iter;
 
   auto reset = [&](uint32_t at) { longest[at] = 0u; first[at] = 0xFFFFFFFFu; last[at] = 0u; folded[at] = 0u; };
-  for (uint32_t i = tid; i < words; i += kBlock) reset(i);
-  __syncthreads();
-
   uint32_t n_rows = 0, n_clipped = 0, n_bad = 0;
   // Folds a row if it is one.  Without branches: loads that a branch lies behind would all be waited for at its end.
   auto fold = [&](const u32x4& row, bool is_row) __attribute__((always_inline)) {
@@ -74,37 +76,37 @@ __global__ __launch_bounds__(kBlock) void kp_stages_main(StagesParams p) {
   };
 
   // Turn i of this decoder workgroup takes recorded workgroup wg_of(i).  Decoder workgroups are dealt round-robin to the
-  // eight XCDs; each XCD takes a run of consecutive recorded workgroups (all of them in turn: 114 us where this takes 105).
+  // eight XCDs; each XCD takes a run of consecutive recorded workgroups (all of them in turn: 8 % slower at 4096 workgroups of 8 x 1024 rows).
   const uint32_t xcd = blockIdx.x & 7u, many = p.n_wg & 7u, rest = gridDim.x & 7u;
   const uint32_t mine = (p.n_wg >> 3) + (xcd < many ? 1u : 0u), apart = (gridDim.x >> 3) + (xcd < rest ? 1u : 0u);
   const uint32_t from = xcd * (p.n_wg >> 3) + (xcd < many ? xcd : many) + (blockIdx.x >> 3);
   const uint32_t turns = (mine - (blockIdx.x >> 3) + apart - 1u) / apart;
   auto wg_of = [&](uint32_t i) { return from + i * apart; };
-  // A turn's steps: unit q is block q % blocks of 256 rows of recorded wave q / blocks; hardware wave h takes units h, h + 8, ...
-  // Every hardware wave makes the same number of steps, some of them without rows.  (Wave after wave of 256 rows each instead,
-  // which starts eight streams 16 KiB apart: 131 us, consecutive blocks 117.)
-  const uint32_t blocks = (p.half + 255u) / 256u, steps = (W * blocks + kWavesHw - 1u) / kWavesHw;
+  // A turn's steps: unit q is block q % blocks of kRows rows of recorded wave q / blocks; hardware wave h takes units h, h + 8, ...
+  // Every hardware wave makes the same number of steps, some of them without rows.  (Wave after wave instead,
+  // eight streams 16 KiB apart: 12 % slower.)
+  const uint32_t blocks = (p.half + kRows - 1u) / kRows, steps = (W * blocks + kWavesHw - 1u) / kWavesHw;
   const uint32_t w_step = kWavesHw / blocks, block_step = kWavesHw % blocks;
 
-  // The step requested next: turn, step, recorded wave and block of 256 rows; cnt: rows of that recorded wave, by a scalar
+  // The step requested next: turn, step, recorded wave and block; cnt: rows of that recorded wave, by a scalar
   // load (a vector load among those of the rows would be waited for together with them).
   uint32_t at_turn = 0, at_step = 0, at_w = hw / blocks, at_block = hw % blocks;
-  // Requests it; gives the number of its rows.  Always four loads, or the waits for the steps behind it would be for all of
+  // Requests it; gives the number of its rows.  Always PER loads, or the waits for the steps behind it would be for all of
   // its own as well: a lane without a row reads the step's last one, a step without rows the first one there is.
   typedef const __attribute__((address_space(4))) uint32_t* scalar_ptr;
   auto count_at = [&]() __attribute__((always_inline)) -> uint32_t {
     return ((scalar_ptr)(uintptr_t)p.count)[(size_t)wg_of(at_turn < turns ? at_turn : turns - 1u) * W + (at_w < W ? at_w : 0u)];
   };
   uint32_t cnt = count_at();
-  auto request = [&](u32x4 (&r)[4]) __attribute__((always_inline)) -> uint32_t {
+  auto request = [&](u32x4 (&r)[PER]) __attribute__((always_inline)) -> uint32_t {
     cnt = cnt < p.half ? cnt : p.half;  // a count beyond the wave's slots cannot be honoured
-    const uint32_t begin = at_block * 256u;
+    const uint32_t begin = at_block * kRows;
     uint32_t n = cnt > begin ? cnt - begin : 0u;
-    n = at_turn < turns && at_w < W ? (n < 256u ? n : 256u) : 0u;
+    n = at_turn < turns && at_w < W ? (n < kRows ? n : kRows) : 0u;
     const u32x4* rows = p.rows + (n ? ((size_t)wg_of(at_turn) * W + at_w) * p.half + begin : (size_t)0);
     const uint32_t top = n ? n - 1u : 0u;
 #pragma unroll
-    for (uint32_t u = 0; u < 4; ++u) {
+    for (uint32_t u = 0; u < PER; ++u) {
       const uint32_t j = lane + 64u * u;
       r[u] = __builtin_nontemporal_load(rows + (j < top ? j : top));
     }
@@ -114,16 +116,20 @@ __global__ __launch_bounds__(kBlock) void kp_stages_main(StagesParams p) {
     cnt = count_at();
     return n;
   };
-  u32x4 buf[kDepth][4];
+  u32x4 buf[kDepth][PER];
   uint32_t n_of[kDepth];
 #pragma unroll
   for (int d = 0; d < kDepth; ++d) n_of[d] = request(buf[d]);
+  // (behind the first requests: a short call is the latencies of its start)
+  for (uint32_t i = tid; i < words; i += kBlock) reset(i);
+  if (tid < 3u) counts[tid] = 0u;
+  __syncthreads();
   uint32_t turn = 0, step = 0;
   while (turn < turns) {  // (no exit inside: the steps behind the last turn's have no rows)
 #pragma unroll
     for (int d = 0; d < kDepth; ++d) {
 #pragma unroll
-      for (uint32_t u = 0; u < 4; ++u)
+      for (uint32_t u = 0; u < PER; ++u)
         fold(buf[d][u], lane + 64u * u < n_of[d]);
       n_of[d] = request(buf[d]);
       if (++step == steps && turn < turns) {
@@ -143,11 +149,11 @@ __global__ __launch_bounds__(kBlock) void kp_stages_main(StagesParams p) {
   }
 
   n_rows = wave_sum(n_rows); n_clipped = wave_sum(n_clipped); n_bad = wave_sum(n_bad);
-  if (lane == 0) {
-    if (n_rows) atomicAdd(&p.hdr[0], (unsigned long long)n_rows);
-    if (n_clipped) atomicAdd(&p.hdr[1], (unsigned long long)n_clipped);
-    if (n_bad) atomicAdd(&p.hdr[2], (unsigned long long)n_bad);
-  }
+  // One add per count and decoder workgroup: they queue up at the header, 12 ns each (one per hardware wave, with
+  // two decoder workgroups per CU: 1000 recorded ones of 4 x 512 rows 57 us where this takes 13).
+  if (lane == 0) { atomicAdd(&counts[0], n_rows); atomicAdd(&counts[1], n_clipped); atomicAdd(&counts[2], n_bad); }
+  __syncthreads();
+  if (tid < 3u && counts[tid]) atomicAdd(&p.hdr[tid], (unsigned long long)counts[tid]);
 }
 
 // Entries that the regions' rows of the table lie apart.  Regions that follow one another put an iteration of each of
@@ -161,6 +167,37 @@ inline uint32_t region_stride(uint32_t R, uint32_t max_iter) {
 }
 
 struct LaunchCache { int dev = -1; uint32_t lds = 0; uint32_t per_cu = 0, cus = 0; };
+
+template <int PER>
+kp_status launch(const StagesParams& p, hipStream_t s) {
+  const uint32_t lds = 16u * (p.R * p.stride + 64u + 1u);
+  static thread_local LaunchCache cache;
+  int dev = 0;
+  KP_HIP_TRY(hipGetDevice(&dev));
+  if (cache.dev != dev || cache.lds != lds) {
+    KP_HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void*>(kp_stages_main<PER>),
+                                   hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
+    int per_cu = 0, cus = 0;
+    KP_HIP_TRY(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kp_stages_main<PER>, kBlock, lds));
+    if (per_cu < 1) return kp::fail(KP_ERR_UNSUPPORTED_SHAPE, "stage kernel does not fit one CU (LDS %u B)", lds);
+    KP_HIP_TRY(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev));
+    cache.dev = dev; cache.lds = lds; cache.per_cu = (uint32_t)per_cu; cache.cus = (uint32_t)cus;
+  }
+  // Decoder workgroups: one per CU streams as fast as the memory gives rows (one / two / three per CU, us: 4096 workgroups of
+  // 8 x 1024 rows 93 / 94 / 96, 1500 of 5 x 256 13.0 / 15.2 / 16.3).  The turns of small workgroups are steps between
+  // barriers, 0.6 us each, which several take side by side, and each of them queues up at the header for 12 ns: the sum
+  // is least at the root of 50 times their number.  (1 / 2 / 3 / 4 per CU, us: 60000 of 4 x 32 141 / 90 / 81 / 77, 8000 of 2 x 128
+  // 27.1 / 20.8 / 21.2 / 22.3, 3276 of 5 x 32 13.1 / 14.1 / 16.0 / 18.2.)
+  uint32_t per_cu = PER == 1 ? 4u : 1u;
+  per_cu = per_cu < cache.per_cu ? per_cu : cache.per_cu;
+  uint32_t grid = per_cu * cache.cus;
+  const uint32_t least = (uint32_t)sqrt(50.0 * p.n_wg), few = least > cache.cus ? least : cache.cus;
+  grid = grid < few ? grid : few;
+  grid = grid < p.n_wg ? grid : p.n_wg;
+  hipLaunchKernelGGL(kp_stages_main<PER>, dim3(grid), dim3(kBlock), lds, s, p);
+  KP_HIP_TRY(hipGetLastError());
+  return KP_OK;
+}
 
 }  // namespace
 
@@ -194,34 +231,13 @@ extern "C" kp_status kp_pairs_stages(const void* pairs, int n_wg, int waves_per_
   p.n_wg = (uint32_t)n_wg; p.W = (uint32_t)waves_per_wg; p.R = (uint32_t)n_regions;
   p.half = (uint32_t)(cap_per_wg / waves_per_wg) / 2u; p.max_iter = (uint32_t)max_iter;
   p.stride = region_stride(p.R, p.max_iter);
-  const uint32_t lds = 16u * (p.R * p.stride + 64u);
 
   hipLaunchKernelGGL(kp_stages_init, dim3(1), dim3(64), 0, s, p.hdr);
   KP_HIP_TRY(hipGetLastError());
   if (n_wg == 0) return KP_OK;
 
-  static thread_local LaunchCache cache;
-  int dev = 0;
-  KP_HIP_TRY(hipGetDevice(&dev));
-  if (cache.dev != dev || cache.lds != lds) {
-    KP_HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void*>(kp_stages_main),
-                                   hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
-    int per_cu = 0, cus = 0;
-    KP_HIP_TRY(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kp_stages_main, kBlock, lds));
-    if (per_cu < 1) return kp::fail(KP_ERR_UNSUPPORTED_SHAPE, "stage kernel does not fit one CU (LDS %u B)", lds);
-    KP_HIP_TRY(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev));
-    cache.dev = dev; cache.lds = lds; cache.per_cu = (uint32_t)per_cu; cache.cus = (uint32_t)cus;
-  }
-  // Decoder workgroups per CU: one streams as fast as the memory gives rows, and every further one is another place that
-  // they come from; but the turns of small workgroups are steps between barriers, which several take side by side.  One / two
-  // / three, us: 4096 workgroups of 8 x 1024 rows 105 / 123 / 144, 2000 of 4096 54 / 84 / 117, 1500 of 5 x 256 25 / 38 / 52,
-  // 9000 of 16 x 64 84 / 85 / 99, 8000 of 2 x 128 39 / 32 / 35, 60000 of 4 x 32 225 / 158 / 138, 16000 of 2 x 16 65 / 48 / 43.
-  const uint32_t rows_wg = p.W * p.half;
-  uint32_t per_cu = rows_wg >= 1024u ? 1u : rows_wg >= 192u ? 2u : 3u;
-  per_cu = per_cu < cache.per_cu ? per_cu : cache.per_cu;
-  uint32_t grid = per_cu * cache.cus;
-  grid = grid < (uint32_t)n_wg ? grid : (uint32_t)n_wg;
-  hipLaunchKernelGGL(kp_stages_main, dim3(grid), dim3(kBlock), lds, s, p);
-  KP_HIP_TRY(hipGetLastError());
-  return KP_OK;
+  // Waves of up to 128 rows: one row per lane and step.  1 / 2 / 4 rows, us, each with its best number of decoder workgroups:
+  // 16000 workgroups of 2 x 16 rows 27 / 31 / 40, 9000 of 16 x 64 30 / 34 / 44, 8000 of 2 x 128 20.8 / 22.3 / 26.5, 2000 of
+  // 8 x 128 13.7 / 13.8 / 13.9; 1500 of 5 x 256 14.9 / 14.2 / 13.0, 4096 of 8 x 1024 99 / 95 / 93.
+  return p.half <= 128u ? launch<1>(p, s) : launch<4>(p, s);
 }
