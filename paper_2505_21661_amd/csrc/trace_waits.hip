@@ -256,19 +256,23 @@ __global__ __launch_bounds__(BLOCK, BLOCK == 1024 ? 4 : (UNITS == 4 ? 6 : 5)) vo
     if (lane == 0) hist[(i >> 6) * kHistStride + 64u] = n;
   }
   __syncthreads();
-  for (uint32_t r = tid; r < R; r += BLOCK) {
+  // The seven arrays of the regions lie one behind the other: one thread per word, so that the adds of a workgroup to a
+  // line are one request (an array after the other: 20000 workgroups of 4 x 32 slots 95 us where this takes 82, 9000 of
+  // 3 x 1024 89 / 85).
+  for (uint32_t i = tid; i < 7u * R; i += BLOCK) {
+    const uint32_t array = i / R, r = i - array * R;
     const unsigned long long n = hist[r * kHistStride + 64u];
-    if (n) {
-      atomicAdd(&out[SL.cnt + r], n);
-      if (add_head) atomicAdd(&out[H_WAITS], n);
-      atomicAdd(&out[SL.sum + r], reg_sum[r]);
-      atomicMax(&out[SL.max + r], (unsigned long long)reg_max[r]);
-      atomicMin(&out[SL.min + r], (unsigned long long)reg_min[r]);
-      const unsigned long long u = (unsigned long long)unc[2u * r] + unc[2u * r + 1u];
-      if (u) { atomicAdd(&out[SL.unc + r], u); if (add_head) atomicAdd(&out[H_UNCOVERED], u); }
-      if (acnt[r]) { atomicAdd(&out[SL.acnt + r], acnt[r]); if (add_head) atomicAdd(&out[H_ASYNC], acnt[r]); }
-      if (asum[r]) atomicAdd(&out[SL.asum + r], asum[r]);
-    }
+    if (!n) continue;
+    unsigned long long* to = &out[SL.cnt + i];
+    if (array == 2u) { atomicMin(to, (unsigned long long)reg_min[r]); continue; }
+    if (array == 3u) { atomicMax(to, (unsigned long long)reg_max[r]); continue; }
+    const unsigned long long v = array == 0u ? n : array == 1u ? reg_sum[r] : array == 4u ? (unsigned long long)unc[2u * r] + unc[2u * r + 1u]
+                                                        : array == 5u ? acnt[r] : asum[r];
+    if (v) atomicAdd(to, v);
+    if (!add_head) continue;
+    if (array == 0u) atomicAdd(&out[H_WAITS], v);
+    if (array == 4u && v) atomicAdd(&out[H_UNCOVERED], v);
+    if (array == 5u && v) atomicAdd(&out[H_ASYNC], v);
   }
 }
 
