@@ -18,7 +18,7 @@
 // Sums, extrema and the log2 histogram go to LDS atomics; totals live in LDS across the recorded workgroups of
 // a persistent decoder workgroup.
 // What bounds it: instruction issue.  Measured on 9000 workgroups of 3 waves x 1024 records: 144 us with the loads
-// waited for, one rank per lane and runs cut by capacity instead of by what the wave holds; 87 us (2.5 TB/s).
+// waited for, one rank per lane and runs cut by capacity instead of by what the wave holds; 82 us (2.7 TB/s).
 #include "kp_stage.h"
 
 #include <math.h>
