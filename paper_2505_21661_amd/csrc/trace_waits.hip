@@ -282,9 +282,11 @@ __global__ __launch_bounds__(BLOCK, BLOCK == 1024 ? 4 : (UNITS == 4 ? 6 : 5)) vo
 // regions' own sums, which an odd number of regions, 2 and 6 leave across the lines.  Measured, added / kernel, us:
 // 64 decoder workgroups x 16 regions 10.4 / 10.9, x 28 + 0.4 added, x 64 + 4.2; 128 x 8 11.8 / 11.6, x 12 12.3 / 13.1; 256 x 4 17.6 / 15.5,
 // x 6 17.5 / 19.0, x 7 18.4 / 19.5, x 8 17.4 / 14.4, x 16 17.8 / 15.1; 1024 x 3 45.1 / 46.9, x 4 38.6 / 29.8, x 6 38.6 / 38.8,
-// x 8 39.0 / 26.4, x 9 and 13 the same either way, x 10 + 4.4 added, x 16 39.8 / 27.8.
+// x 8 39.0 / 26.4, x 9 the same either way, x 10 + 4.4 added, x 16 39.8 / 27.8.  With more than nine regions the words of all
+// arrays take two hardware waves, both of which add: 3000 recorded workgroups of 4 x 256 slots x 9 regions 40.9 / 41.2, x 11
+// 46.5 / 40.7, x 13 46.3 / 38.2, x 15 46.8 / 38.2.
 inline bool add_head_counts(uint32_t grid, uint32_t R) {
-  return R <= 20u && (grid <= 128u || (R & 1u) != 0u || R == 2u || R == 6u);
+  return R <= 20u && (grid <= 128u || (R <= 9u && ((R & 1u) != 0u || R == 2u || R == 6u)));
 }
 __global__ void kp_waits_head(uint64_t* out, uint32_t n_wg, uint32_t W, uint32_t R) {
   const WaitsLayout l = waits_layout(n_wg, W, R);

@@ -103,6 +103,15 @@ def test_header_counts_on_either_side_of_their_line(kp, oracle_mod, n_wg, R):
     assert_waits_equal(oracle_mod, raw, run_waits(kp, raw, use_hdr=True))
 
 
+# the words of all regions' totals just fit one hardware wave, or do not; four waves; the largest count
+@pytest.mark.parametrize("R", [9, 10, 37, 128])
+def test_totals_of_one_and_of_several_waves(kp, oracle_mod, R):
+    spec = inputs.TraceSpec(n_wg=700, waves=2, n_regions=R, cap_wave=64, total_per_wave=64, total_var=30, seed=R, p_orphan=0.05, p_swap=0.01)
+    raw, _ = inputs.gen_trace(spec)
+    raw[6] = 12
+    assert_waits_equal(oracle_mod, raw, run_waits(kp, raw, use_hdr=True))
+
+
 # rings of 64 (a hardware wave's 128 records are several recorded waves') and of 128 and more; several turns each
 @pytest.mark.parametrize("n_wg,W,R,cap", [(3001, 3, 5, 64), (3002, 3, 5, 128), (1205, 5, 16, 512), (603, 8, 7, 1024)])
 def test_shared_seq_in_every_other_turn(kp, oracle_mod, n_wg, W, R, cap):

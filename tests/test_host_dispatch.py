@@ -56,6 +56,15 @@ def test_wait_header_counts_are_made_once(tmp_path):
         assert not head or launches[-1] == head[0]
 
 
+def test_wait_header_counts_of_odd_region_counts(tmp_path):
+    """With more than nine regions the totals of a decoder workgroup take two hardware waves: many workgroups leave the header
+    counts to the kernel behind them, few add them all the same."""
+    calls = [{"fn": "kp_trace_waits_hdr", "trace": (n_wg, 4, regions, 256), "device": (0, 256, 2)} for regions in (9, 11, 19) for n_wg in (100, 3000)]
+    for call, (status, launches) in zip(calls, fake_hip.run(calls, tmp_path)):
+        n_wg, _, regions, _ = call["trace"]
+        assert status == 0 and (len(kernels(launches, "kp_waits_head")) == 0) == (n_wg == 100 or regions == 9), (call, launches)
+
+
 @pytest.mark.parametrize("tiles,k_max", [((17, 15), 0), ((257, 1), 96), ((256, 3), 96), ((769, 1), 160), ((33, 31), 160), ((41, 25), 224), ((3071, 1), 224), ((63, 62), 288)])
 def test_short_k_gemm_has_one_line_for_every_way_of_recording(tmp_path, tiles, k_max):
     """Which 64x64x32 kernel a shape takes does not depend on what is recorded, so that a recorded kernel and the one
