@@ -3,6 +3,7 @@
 
 #include <atomic>
 #include <chrono>
+#include <mutex>
 
 #include "kp_common.h"
 
@@ -27,28 +28,62 @@ static __global__ void kp_header_to_host(const uint32_t* hdr, uint32_t* slot, ui
   if (threadIdx.x == 0) __hip_atomic_store(slot + kHdrWords, call, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
 }
 
-// Host memory that a kernel can write: one small allocation per thread that reads headers back, given back when the thread
-// ends.  A thread has one read under way at a time, whatever the stream.
-struct HeaderSlot {
-  uint32_t* words = nullptr;
-  uint32_t calls = 0;
-  bool usable = true;
+// Host memory that a kernel can write: 32 places of 128 bytes, one for each header on its way, whatever its thread and
+// stream.  One allocation for the process, made by the first call that needs it; it lasts as long as the library does (no
+// call of the runtime stands at the end of a thread or of the process, where it could wait for kernels or break another
+// thread's capture).  A device reset takes the allocation back under the library: its number, which the runtime gives to no
+// other one, says whether it is still there.  With all places taken the header is copied.
+class HeaderPlaces {
+ public:
+  static constexpr uint32_t kPlaces = 32, kWords = 32;
+  // A place and the number of the call that it is for, or nullptr.
+  uint32_t* take(uint32_t* call) {
+    std::lock_guard<std::mutex> hold(lock_);
+    if (!ready()) return nullptr;
+    for (uint32_t i = 0; i < kPlaces; ++i) {
+      if ((taken_ >> i) & 1u) continue;
+      taken_ |= 1u << i;
+      *call = ++calls_;
+      words_[kWords * i + kHdrWords] = ~*call;
+      return words_ + kWords * i;
+    }
+    return nullptr;
+  }
+  void give_back(const uint32_t* place) {
+    std::lock_guard<std::mutex> hold(lock_);
+    if (place >= words_ && place < words_ + kPlaces * kWords) taken_ &= ~(1u << ((uint32_t)(place - words_) / kWords));
+  }
+
+ private:
+  static bool number_of(void* p, uint64_t* id) {
+    const bool known = hipPointerGetAttribute(id, HIP_POINTER_ATTRIBUTE_BUFFER_ID, reinterpret_cast<hipDeviceptr_t>(p)) == hipSuccess;
+    if (!known) (void)hipGetLastError();
+    return known;
+  }
   bool ready() {
-    if (words || !usable) return usable;
+    uint64_t id = 0;
+    if (words_ && number_of(words_, &id) && id == id_) return true;
+    words_ = nullptr; taken_ = 0u;
     // (an allocation is allowed here also while another thread captures a graph)
     hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
-    if (hipThreadExchangeStreamCaptureMode(&mode) == hipSuccess) {
-      usable = hipHostMalloc(reinterpret_cast<void**>(&words), 4 * (kHdrWords + 1), hipHostMallocPortable | hipHostMallocMapped) == hipSuccess;
-      (void)hipThreadExchangeStreamCaptureMode(&mode);
-      if (usable) words[kHdrWords] = 0u;
+    if (hipThreadExchangeStreamCaptureMode(&mode) != hipSuccess) { (void)hipGetLastError(); return false; }
+    void* p = nullptr;
+    if (hipHostMalloc(&p, 4 * kPlaces * kWords, hipHostMallocPortable | hipHostMallocMapped | hipHostMallocCoherent) != hipSuccess) {
+      (void)hipGetLastError();
+    } else if (!number_of(p, &id_)) {
+      (void)hipHostFree(p);
     } else {
-      usable = false;
+      words_ = static_cast<uint32_t*>(p);
     }
-    if (!usable) { words = nullptr; (void)hipGetLastError(); }
-    return usable;
+    (void)hipThreadExchangeStreamCaptureMode(&mode);
+    return words_ != nullptr;
   }
-  ~HeaderSlot() { if (words) (void)hipHostFree(words); }
+  std::mutex lock_;
+  uint32_t* words_ = nullptr;
+  uint64_t id_ = 0;
+  uint32_t taken_ = 0, calls_ = 0;
 };
+static HeaderPlaces g_places;
 
 // The copying engine's way into pageable memory takes 20 us, into pinned memory 12; a kernel that writes the header to
 // where the host looks for it 7.  That way is for device memory of the current device and streams that run: a pointer of
@@ -70,27 +105,29 @@ static bool goes_by_kernel(const void* raw, hipStream_t s) {
 }
 
 kp_status read_header(const void* raw, kp_trace_hdr* hdr, hipStream_t s) {
-  static thread_local HeaderSlot slot;
-  if (!goes_by_kernel(raw, s) || !slot.ready()) {
+  uint32_t call = 0;
+  uint32_t* const place = goes_by_kernel(raw, s) ? g_places.take(&call) : nullptr;
+  if (!place) {
     KP_HIP_TRY(hipMemcpyAsync(hdr, raw, sizeof *hdr, hipMemcpyDeviceToHost, s));
     KP_HIP_TRY(hipStreamSynchronize(s));
     return KP_OK;
   }
-  const uint32_t call = ++slot.calls;
-  hipLaunchKernelGGL(kp_header_to_host, dim3(1), dim3(64), 0, s, static_cast<const uint32_t*>(raw), slot.words, call);
-  KP_HIP_TRY(hipGetLastError());
-  auto arrived = [&]() { return __atomic_load_n(slot.words + kHdrWords, __ATOMIC_ACQUIRE) == call; };
+  hipLaunchKernelGGL(kp_header_to_host, dim3(1), dim3(64), 0, s, static_cast<const uint32_t*>(raw), place, call);
+  const hipError_t launched = hipGetLastError();
+  if (launched != hipSuccess) {  // (nobody writes to the place)
+    g_places.give_back(place);
+    return fail(KP_ERR_HIP, "launching the read of the trace header failed: %s", hipGetErrorString(launched));
+  }
+  auto arrived = [&]() { return __atomic_load_n(place + kHdrWords, __ATOMIC_ACQUIRE) == call; };
   const auto until = std::chrono::steady_clock::now() + std::chrono::microseconds(200);
   while (!arrived() && std::chrono::steady_clock::now() < until) {}
   if (!arrived()) {  // there is other work ahead of it, or something went wrong
     const hipError_t e = hipStreamSynchronize(s);
-    if (e != hipSuccess || !arrived()) {
-      slot.words = nullptr;  // (the kernel may still write to it: never given back)
-      slot.usable = false;
-      return fail(KP_ERR_HIP, "reading the trace header back failed: %s", hipGetErrorString(e));
-    }
+    // (a place that the kernel may still write to is not given back)
+    if (e != hipSuccess || !arrived()) return fail(KP_ERR_HIP, "reading the trace header back failed: %s", hipGetErrorString(e));
   }
-  memcpy(hdr, slot.words, sizeof *hdr);
+  memcpy(hdr, place, sizeof *hdr);
+  g_places.give_back(place);
   return KP_OK;
 }
 }  // namespace kp

@@ -10,9 +10,8 @@ ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 BUFFER = 0x10000000  # stands for any device buffer; never read or written
 
 
-def run(calls, tmp_path, lib=None):
-    """calls: dicts with "fn", and "trace" (n_wg, waves, regions, cap) or "args"; "device" (index, CUs, resident
-    workgroups per CU).  Returns [(status, [(kernel, grid, block, dynamic LDS)])]."""
+def libraries(tmp_path, lib=None):
+    """Paths of the stand-in for the HIP runtime and of libkperf.so, both built if need be."""
     if lib is None:
         lib = os.path.join(ROOT, "paper_2505_21661_amd", "libkperf.so")
         if not os.path.exists(lib):
@@ -22,6 +21,13 @@ def run(calls, tmp_path, lib=None):
     fake = os.path.join(str(tmp_path), "libfake_hip.so")
     if not os.path.exists(fake):
         subprocess.check_call(["gcc", "-O1", "-shared", "-fPIC", "-o", fake, os.path.join(ROOT, "tests", "fake_hip.c")])
+    return fake, lib
+
+
+def run(calls, tmp_path, lib=None):
+    """calls: dicts with "fn", and "trace" (n_wg, waves, regions, cap) or "args"; "device" (index, CUs, resident
+    workgroups per CU).  Returns [(status, [(kernel, grid, block, dynamic LDS)])]."""
+    fake, lib = libraries(tmp_path, lib)
     done = subprocess.run([sys.executable, os.path.abspath(__file__), fake, lib], input=json.dumps(calls), text=True,
                           capture_output=True, timeout=120)
     assert done.returncode == 0, (done.returncode, done.stderr[-2000:])

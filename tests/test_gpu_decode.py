@@ -323,3 +323,53 @@ def test_headers_read_back_by_several_threads(kp, oracle_mod):
     for t in threads:
         t.join()
     assert not failures, failures
+
+
+def test_a_trace_in_pinned_host_memory(kp, oracle_mod):
+    """Memory of another kind than the device's, which the C ABI takes: its header comes by the runtime's copy."""
+    raw = inputs.messy_trace(950, n_wg=5, waves=3, n_regions=4, cap_wave=32)
+    n_wg, W, R, cap = (int(x) for x in raw[2:6])
+    pinned = torch.empty(raw.size, dtype=torch.int32, pin_memory=True)
+    pinned.copy_(torch.from_numpy(raw.view(np.int32)))
+    out = torch.zeros(kp.kp_stats_bytes(n_wg, W, R), dtype=torch.uint8, device="cuda")
+    torch.cuda.synchronize()
+    assert kp.lib().kp_trace_reduce(pinned.data_ptr(), n_wg * W * cap, out.data_ptr(), torch.cuda.current_stream().cuda_stream) == 0
+    torch.cuda.synchronize()
+    assert np.array_equal(oracle_mod.decode_bytes(raw), out.cpu().numpy())
+
+
+def test_a_thread_that_read_a_header_ends_during_a_capture(kp, oracle_mod):
+    """The end of such a thread is no concern of another thread's capture."""
+    import threading
+
+    raw = inputs.messy_trace(960, n_wg=5, waves=3, n_regions=4, cap_wave=32)
+    n_wg, W, R, cap = (int(x) for x in raw[2:6])
+    n, dev = n_wg * W * cap, torch.from_numpy(raw.view(np.int32)).cuda()
+    outs = [torch.zeros(kp.kp_stats_bytes(n_wg, W, R), dtype=torch.uint8, device="cuda") for _ in range(2)]
+    hdr = kp.make_hdr(n_wg, W, R, cap, int(raw[6]), int(raw[7]))
+    kp.kp_trace_reduce_hdr(dev, n, hdr, outs[0])
+    torch.cuda.synchronize()
+    read, end = threading.Event(), threading.Event()
+
+    def reader():
+        kp.kp_trace_reduce(dev, n, outs[1])
+        torch.cuda.synchronize()
+        read.set()
+        end.wait(30)
+
+    thread = threading.Thread(target=reader)
+    thread.start()
+    assert read.wait(30)
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        kp.kp_trace_reduce_hdr(dev, n, hdr, outs[0])
+        end.set()
+        thread.join()
+        kp.kp_trace_reduce_hdr(dev, n, hdr, outs[0])
+    want = oracle_mod.decode_bytes(raw)
+    assert np.array_equal(want, outs[1].cpu().numpy())
+    for _ in range(3):
+        outs[0].fill_(0x77)
+        graph.replay()
+        torch.cuda.synchronize()
+        assert np.array_equal(want, outs[0].cpu().numpy())
