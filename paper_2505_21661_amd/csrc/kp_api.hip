@@ -124,7 +124,8 @@ kp_status read_header(const void* raw, kp_trace_hdr* hdr, hipStream_t s) {
   if (!arrived()) {  // there is other work ahead of it, or something went wrong
     const hipError_t e = hipStreamSynchronize(s);
     // (a place that the kernel may still write to is not given back)
-    if (e != hipSuccess || !arrived()) return fail(KP_ERR_HIP, "reading the trace header back failed: %s", hipGetErrorString(e));
+    if (e != hipSuccess) return fail(KP_ERR_HIP, "reading the trace header back failed: %s", hipGetErrorString(e));
+    if (!arrived()) return fail(KP_ERR_HIP, "reading the trace header back failed: its kernel did not run");
   }
   memcpy(hdr, place, sizeof *hdr);
   g_places.give_back(place);

@@ -36,9 +36,9 @@ def test_after_a_device_reset_the_memory_is_allocated_anew(tmp_path):
     assert got["stray_writes"] == 0 and got["allocations"] == 1
 
 
-def test_a_place_without_an_answer_is_not_used_again(tmp_path):
+def test_a_kernel_that_did_not_run_is_named(tmp_path):
     got = run("silent", tmp_path)
-    assert all(s != 0 for s in got["status"][:3])
+    assert all(s != 0 for s in got["status"][:3]) and "no error" not in got["error"] and "did not run" in got["error"]
     assert got["status"][3:] == [0, 0] and got["kernels"] == 5  # other places serve the calls behind
 
 
