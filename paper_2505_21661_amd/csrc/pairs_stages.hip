@@ -16,8 +16,11 @@
 #include <math.h>
 
 #include "kp_common.h"
+#include "kp_wave.h"
 
 namespace {
+
+using kp_wave::scan_src;
 
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
@@ -82,71 +85,98 @@ __global__ __launch_bounds__(kBlock) void kp_stages_main(StagesParams p) {
   const uint32_t from = xcd * (p.n_wg >> 3) + (xcd < many ? xcd : many) + (blockIdx.x >> 3);
   const uint32_t turns = (mine - (blockIdx.x >> 3) + apart - 1u) / apart;
   auto wg_of = [&](uint32_t i) { return from + i * apart; };
-  // A turn's steps: unit q is block q % blocks of kRows rows of recorded wave q / blocks; hardware wave h takes units h, h + 8, ...
-  // Every hardware wave makes the same number of steps, some of them without rows.  (Wave after wave instead,
-  // eight streams 16 KiB apart: 12 % slower.)
-  const uint32_t blocks = (p.half + kRows - 1u) / kRows, steps = (W * blocks + kWavesHw - 1u) / kWavesHw;
-  const uint32_t w_step = kWavesHw / blocks, block_step = kWavesHw % blocks;
-
-  // The step requested next: turn, step, recorded wave and block; cnt: rows of that recorded wave, by a scalar
-  // load (a vector load among those of the rows would be waited for together with them).
-  uint32_t at_turn = 0, at_step = 0, at_w = hw / blocks, at_block = hw % blocks;
+  // A turn's steps: the blocks of kRows rows that hold any are its units, numbered as they lie in memory; hardware wave h
+  // takes units h, h + 8, ...  Every hardware wave makes the same number of steps, some of the last ones without rows.
+  // (Wave after wave instead, eight streams 16 KiB apart: 12 % slower.  Units by the rings' capacity, whatever they hold:
+  // 4096 workgroups of 8 x 1024 row slots, all of them empty, 55 us where this takes 21, 51 rows in each 59 / 31, one full
+  // wave of eight 58 / 29, all of them full the same.)
+  //
+  // The step requested next: turn and step; lane w: rows of recorded wave w in that turn, units of the waves below it, and of
+  // those and itself.  `ahead`: rows in the turn behind it, on their way since this one was opened.
+  uint32_t at_turn = 0, at_step = 0, at_steps, held, below, upto;
+  const uint32_t* ahead_at = p.count + (size_t)wg_of(0) * W + (lane < W ? lane : W - 1u);
+  auto counts_behind = [&](uint32_t t) __attribute__((always_inline)) -> uint32_t {  // of turn t + 1, behind those of turn t (the last turn's again)
+    ahead_at += t + 1u < turns ? (size_t)apart * W : (size_t)0;
+    return *ahead_at;
+  };
+  auto open_turn = [&](uint32_t rows) __attribute__((always_inline)) {
+    held = at_turn < turns && lane < W ? (rows < p.half ? rows : p.half) : 0u;  // a count beyond the wave's slots cannot be honoured
+    const uint32_t units = (held + kRows - 1u) / kRows;
+    upto = units;
+    upto += scan_src<0>(upto); upto += scan_src<1>(upto); upto += scan_src<2>(upto); upto += scan_src<3>(upto);  // (16 waves at most)
+    below = upto - units;
+    at_steps = ((uint32_t)__builtin_amdgcn_readlane((int)upto, 15) + kWavesHw - 1u) / kWavesHw;
+    at_step = 0;
+  };
+  const uint32_t rows_of_first = *ahead_at;
+  uint32_t ahead = counts_behind(0);
+  open_turn(rows_of_first);
   // Requests it; gives the number of its rows.  Always PER loads, or the waits for the steps behind it would be for all of
   // its own as well: a lane without a row reads the step's last one, a step without rows the first one there is.
-  typedef const __attribute__((address_space(4))) uint32_t* scalar_ptr;
-  auto count_at = [&]() __attribute__((always_inline)) -> uint32_t {
-    return ((scalar_ptr)(uintptr_t)p.count)[(size_t)wg_of(at_turn < turns ? at_turn : turns - 1u) * W + (at_w < W ? at_w : 0u)];
-  };
-  uint32_t cnt = count_at();
-  auto request = [&](u32x4 (&r)[PER]) __attribute__((always_inline)) -> uint32_t {
-    cnt = cnt < p.half ? cnt : p.half;  // a count beyond the wave's slots cannot be honoured
-    const uint32_t begin = at_block * kRows;
-    uint32_t n = cnt > begin ? cnt - begin : 0u;
-    n = at_turn < turns && at_w < W ? (n < kRows ? n : kRows) : 0u;
-    const u32x4* rows = p.rows + (n ? ((size_t)wg_of(at_turn) * W + at_w) * p.half + begin : (size_t)0);
+  auto request = [&](u32x4 (&r)[PER], uint32_t& turn_of) __attribute__((always_inline)) -> uint32_t {
+    auto next_turn = [&]() __attribute__((always_inline)) {
+      ++at_turn;
+      open_turn(ahead);
+      ahead = counts_behind(at_turn);
+    };
+    if (__builtin_expect(at_step == at_steps && at_turn < turns, 0)) {
+      next_turn();
+      // (a loop of its own: in the turn opened first the counts are waited for alone, not with the rows behind them)
+      while (__builtin_expect(at_steps == 0u && at_turn < turns, 0)) next_turn();
+    }
+    const uint32_t q = hw + kWavesHw * at_step;
+    const uint32_t w = (uint32_t)__builtin_popcountll(__builtin_amdgcn_ballot_w64(upto <= q) & 0xFFFFull);  // (16 past the last unit)
+    const uint32_t begin = (q - (uint32_t)__builtin_amdgcn_readlane((int)below, (int)w)) * kRows;
+    const uint32_t rows_of_w = (uint32_t)__builtin_amdgcn_readlane((int)held, (int)w);
+    uint32_t n = rows_of_w > begin ? rows_of_w - begin : 0u;
+    n = n < kRows ? n : kRows;
+    const u32x4* rows = p.rows + (n ? ((size_t)wg_of(at_turn) * W + w) * p.half + begin : (size_t)0);
     const uint32_t top = n ? n - 1u : 0u;
 #pragma unroll
     for (uint32_t u = 0; u < PER; ++u) {
       const uint32_t j = lane + 64u * u;
       r[u] = __builtin_nontemporal_load(rows + (j < top ? j : top));
     }
-    at_w += w_step; at_block += block_step;
-    if (at_block >= blocks) { at_block -= blocks; ++at_w; }
-    if (++at_step == steps) { at_step = 0; ++at_turn; at_w = hw / blocks; at_block = hw % blocks; }
-    cnt = count_at();
+    turn_of = at_turn;
+    ++at_step;
     return n;
   };
   u32x4 buf[kDepth][PER];
-  uint32_t n_of[kDepth];
+  uint32_t n_of[kDepth], turn_of[kDepth];
 #pragma unroll
-  for (int d = 0; d < kDepth; ++d) n_of[d] = request(buf[d]);
+  for (int d = 0; d < kDepth; ++d) n_of[d] = request(buf[d], turn_of[d]);
   // (behind the first requests: a short call is the latencies of its start)
   for (uint32_t i = tid; i < words; i += kBlock) reset(i);
   if (tid < 3u) counts[tid] = 0u;
   __syncthreads();
-  uint32_t turn = 0, step = 0;
-  while (turn < turns) {  // (no exit inside: the steps behind the last turn's have no rows)
+  uint32_t turn = 0;
+  // Tables of the turns up to `end` to HBM, and reset for the next one.
+  auto write_tables = [&](uint32_t end) __attribute__((always_inline)) {
+    for (; turn < end; ++turn) {
+      __syncthreads();
+      u32x4* dst = p.table + (size_t)wg_of(turn) * R * MI;
+      for (uint32_t i = tid; i < R * MI; i += kBlock) {
+        const uint32_t r = i / MI, it = i - r * MI;
+        const uint32_t at = r * stride + it;
+        dst[i] = u32x4{longest[at], first[at], last[at], folded[at]};
+        reset(at);
+      }
+      __syncthreads();
+    }
+  };
+  while (turn_of[0] < turns) {  // (no exit inside: loads that one lies behind would all be waited for)
 #pragma unroll
     for (int d = 0; d < kDepth; ++d) {
+      write_tables(turn_of[d]);
+      if (n_of[d] != 0u) {  // (of the last steps: 3000 workgroups of 1 x 256 rows 20.3 / 18.4 us)
 #pragma unroll
-      for (uint32_t u = 0; u < PER; ++u)
-        fold(buf[d][u], lane + 64u * u < n_of[d]);
-      n_of[d] = request(buf[d]);
-      if (++step == steps && turn < turns) {
-        __syncthreads();
-        // table to HBM, and reset for the next workgroup
-        u32x4* dst = p.table + (size_t)wg_of(turn) * R * MI;
-        for (uint32_t i = tid; i < R * MI; i += kBlock) {
-          const uint32_t r = i / MI, it = i - r * MI;
-          const uint32_t at = r * stride + it;
-          dst[i] = u32x4{longest[at], first[at], last[at], folded[at]};
-          reset(at);
-        }
-        __syncthreads();
-        step = 0; ++turn;
+        for (uint32_t u = 0; u < PER; ++u)
+          fold(buf[d][u], lane + 64u * u < n_of[d]);
       }
+      n_of[d] = request(buf[d], turn_of[d]);
     }
   }
+  write_tables(turns);
 
   n_rows = wave_sum(n_rows); n_clipped = wave_sum(n_clipped); n_bad = wave_sum(n_bad);
   // One add per count and decoder workgroup: they queue up at the header, 12 ns each (one per hardware wave, with

@@ -80,6 +80,64 @@ def test_turns_and_blocks(kp, oracle_mod, n_wg, W, cap, R, max_iter):
     check(kp, oracle_mod, raw, max_iter)
 
 
+@pytest.mark.parametrize("fill", ["none", "first", "last", "few", "ragged", "one wave"])
+@pytest.mark.parametrize("n_wg,W,half", [(1, 1, 1), (3, 5, 64), (261, 16, 40), (1300, 2, 65), (2100, 4, 128), (300, 3, 129), (521, 1, 700), (17, 16, 520)])
+def test_rows_that_fill_little_of_their_places(kp, oracle_mod, n_wg, W, half, fill):
+    """Recorded workgroups and waves without rows, at the beginning, at the end and in a row, next to full ones; a count
+    beyond the wave's places stands for all of them."""
+    rng = np.random.default_rng(n_wg + W + half)
+    R, max_iter = 7, 9
+    counts = np.zeros((n_wg, W), dtype=np.uint32)
+    if fill == "first":
+        counts[0] = rng.integers(0, half + 1, W)
+    elif fill == "last":
+        counts[-1, -1] = half
+    elif fill == "few":
+        counts[:] = np.where(rng.random((n_wg, W)) < 0.05, rng.integers(1, half + 1, (n_wg, W)), 0)
+    elif fill == "ragged":
+        counts[:] = rng.integers(0, half + 1, (n_wg, W))
+        counts[rng.random(n_wg) < 0.3] = 0
+        counts[rng.random((n_wg, W)) < 0.1] = 0xFFFFFFFF
+    elif fill == "one wave":
+        counts[:, W // 2] = half
+    n_seg = n_wg * W
+    block = np.zeros(oracle_mod.pairs_bytes(n_wg, W, 2 * half), dtype=np.uint8)
+    rows = block[(n_seg + 3) // 4 * 16:].view(np.uint32).reshape(n_seg * half, 4)
+    rows[:] = rng.integers(0, 1 << 32, rows.shape, dtype=np.uint32)
+    rows[:, 2] = rng.integers(0, max_iter + 1, len(rows))
+    rows[:, 3] = rng.integers(0, R + 1, len(rows))
+    held = block.copy()
+    held[:4 * n_seg].view(np.uint32)[:] = np.minimum(counts, half).reshape(-1)
+    block[:4 * n_seg].view(np.uint32)[:] = counts.reshape(-1)
+    want = oracle_mod.stages_raw(held, n_wg, W, 2 * half, R, max_iter)
+    assert np.array_equal(want, run_stages(kp, block, n_wg, W, 2 * half, R, max_iter))
+
+
+def test_time_goes_by_the_rows(kp):
+    """A table of places without rows takes a fraction of the time of a full one (a fifth; half of it while every
+    place was stepped over)."""
+    n_wg, W, half, R, max_iter = 2048, 8, 1024, 16, 64
+    block = torch.zeros(kp.kp_pairs_bytes(n_wg, W, 2 * W * half), dtype=torch.uint8, device="cuda")
+    out = torch.zeros(kp.kp_stages_bytes(n_wg, R, max_iter), dtype=torch.uint8, device="cuda")
+    rows = block[4 * n_wg * W:].view(torch.int32).view(n_wg * W, half, 4)
+    i = torch.arange(half, device="cuda", dtype=torch.int32)
+    rows[:, :, 2], rows[:, :, 3] = i // R, i % R
+    best = []
+    for count in (0, half):
+        block[:4 * n_wg * W].view(torch.int32).fill_(count)
+        times = []
+        for _ in range(12):
+            begin, end = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            begin.record()
+            for _ in range(5):
+                kp.kp_pairs_stages(block, n_wg, W, 2 * W * half, R, max_iter, out)
+            end.record()
+            torch.cuda.synchronize()
+            times.append(begin.elapsed_time(end))
+        best.append(min(times))
+    assert best[0] < 0.4 * best[1], best
+
+
 def test_fewer_regions_than_the_rows_use(kp, oracle_mod):
     spec = inputs.TraceSpec(n_wg=11, waves=4, n_regions=6, cap_wave=64, total_per_wave=60, total_var=10, seed=80)
     raw, _ = inputs.gen_trace(spec)
