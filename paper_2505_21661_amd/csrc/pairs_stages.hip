@@ -58,7 +58,7 @@ __global__ __launch_bounds__(kBlock) void kp_stages_main(StagesParams p) {
   uint32_t* first = longest + array;
   uint32_t* last = first + array;
   uint32_t* folded = last + array;
-  uint32_t* counts = folded + array;  // rows, clipped, of no region
+  unsigned long long* counts = reinterpret_cast<unsigned long long*>(folded + array);  // rows, clipped, of no region
   const uint32_t tid = threadIdx.x, lane = tid & 63u, hw = (uint32_t)__builtin_amdgcn_readfirstlane((int)(tid >> 6));
   const uint32_t W = p.W, R = p.R, MI = p.max_iter;
 
@@ -147,7 +147,7 @@ __global__ __launch_bounds__(kBlock) void kp_stages_main(StagesParams p) {
   for (int d = 0; d < kDepth; ++d) n_of[d] = request(buf[d], turn_of[d]);
   // (behind the first requests: a short call is the latencies of its start)
   for (uint32_t i = tid; i < words; i += kBlock) reset(i);
-  if (tid < 3u) counts[tid] = 0u;
+  if (tid < 3u) counts[tid] = 0ull;
   __syncthreads();
   uint32_t turn = 0;
   // Tables of the turns up to `end` to HBM, and reset for the next one.
@@ -181,9 +181,13 @@ __global__ __launch_bounds__(kBlock) void kp_stages_main(StagesParams p) {
   n_rows = wave_sum(n_rows); n_clipped = wave_sum(n_clipped); n_bad = wave_sum(n_bad);
   // One add per count and decoder workgroup: they queue up at the header, 12 ns each (one per hardware wave, with
   // two decoder workgroups per CU: 1000 recorded ones of 4 x 512 rows 57 us where this takes 13).
-  if (lane == 0) { atomicAdd(&counts[0], n_rows); atomicAdd(&counts[1], n_clipped); atomicAdd(&counts[2], n_bad); }
+  if (lane == 0) {
+    atomicAdd(&counts[0], (unsigned long long)n_rows);
+    atomicAdd(&counts[1], (unsigned long long)n_clipped);
+    atomicAdd(&counts[2], (unsigned long long)n_bad);
+  }
   __syncthreads();
-  if (tid < 3u && counts[tid]) atomicAdd(&p.hdr[tid], (unsigned long long)counts[tid]);
+  if (tid < 3u && counts[tid]) atomicAdd(&p.hdr[tid], counts[tid]);
 }
 
 // Entries that the regions' rows of the table lie apart.  Regions that follow one another put an iteration of each of
@@ -200,7 +204,7 @@ struct LaunchCache { int dev = -1; uint32_t lds = 0; uint32_t per_cu = 0, cus = 
 
 template <int PER>
 kp_status launch(const StagesParams& p, hipStream_t s) {
-  const uint32_t lds = 16u * (p.R * p.stride + 64u + 1u);
+  const uint32_t lds = 16u * (p.R * p.stride + 64u + 2u);  // (table, places for lanes without a row, counts)
   static thread_local LaunchCache cache;
   int dev = 0;
   KP_HIP_TRY(hipGetDevice(&dev));
