@@ -163,8 +163,10 @@ __device__ __forceinline__ void stage_workgroup(const Trace& p, unsigned char* s
     }
   };
   const uint32_t n16 = nrec / 2;
-  if (cap >= 128u) {  // the 128 records of a hardware wave's unit are one recorded wave's: all about it is uniform
-    const uint32_t hw = (uint32_t)__builtin_amdgcn_readfirstlane((int)(tid >> 6));
+  const uint32_t hw = (uint32_t)__builtin_amdgcn_readfirstlane((int)(tid >> 6));
+  // Hardware waves without a record leave at once: of 64 slots only one wave has any (waits of 65535 workgroups of 2 x 32
+  // slots 124 / 118 us, 60000 of 4 x 16 126 / 118; timeline of the former 88 / 79).
+  if (cap >= 128u && nrec > 256u) {  // the 128 records of a hardware wave's unit are one recorded wave's: all about it is uniform (65535 workgroups of 2 x 128: 129.6 / 128.1 the other way)
 #pragma unroll
     for (int u = 0; u < UNITS; ++u) {
       if (u * BLOCK >= n16) break;  // (uniform)
@@ -177,14 +179,14 @@ __device__ __forceinline__ void stage_workgroup(const Trace& p, unsigned char* s
   } else {
 #pragma unroll
     for (int u = 0; u < UNITS; ++u) {
-      if (u * BLOCK >= n16) break;  // (uniform)
+      if (128u * (hw + u * (BLOCK / 64)) >= nrec) break;
       const uint32_t f0 = 2u * (tid + u * BLOCK), w = f0 < nrec ? f0 >> cl2 : 0u;
       const uint32_t T = (uint32_t)__shfl((int)f.total, (int)w, 64);
       const uint32_t V = f0 < nrec ? (T < cap ? T : cap) : 0u;
       accept(u, w, V, p.flush || T < cap ? 0u : T - cap, f0 & capm);
     }
   }
-  if (__builtin_amdgcn_ballot_w64(moved != 0u) && lane == 0) *displaced = 1u;
+  if (moved != 0u) *displaced = 1u;  // (asked of the wave by a ballot: 1 % slower)
   __syncthreads();
   if (*displaced == 0u) return;
   // ---- the others: one whose rank is taken shares its seq with another record --------------------------
