@@ -115,7 +115,8 @@ def nested_trace(seed, W, R, cap, depth, inner):
 
 def shared_seq_trace(seed, n_wg, W, R, cap):
     """Workgroups of four kinds in turn: all records in the slots of their seq; some slots swapped; some records that repeat
-    the seq of the slot below (one of the two is in its own slot); pairs of records that share a seq outside its slot."""
+    the seq of the slot below (one of the two is in its own slot); pairs of records that share a seq outside its slot, which
+    holds another one, next to each other and far apart."""
     import inputs
 
     spec = inputs.TraceSpec(n_wg=n_wg, waves=W, n_regions=R, cap_wave=cap, total_per_wave=cap, total_var=cap // 2, seed=seed, p_orphan=0.05)
@@ -132,5 +133,35 @@ def shared_seq_trace(seed, n_wg, W, R, cap):
         elif wg % 4 == 2:
             seg[a + 1, 0] = (seg[a + 1, 0] & ~np.uint32(0xFFFFF)) | (seg[a, 0] & np.uint32(0xFFFFF))
         elif wg % 4 == 3:
-            seg[[a, a + 1], 0] = (seg[[a, a + 1], 0] & ~np.uint32(0xFFFFF)) | (seg[a + 2, 0] & np.uint32(0xFFFFF))
+            b = a + (1 if wg % 8 == 3 else cap // 4)
+            other, shared = seg[a, 0] & np.uint32(0xFFFFF), seg[b + 1, 0] & np.uint32(0xFFFFF)
+            seg[[a, b], 0] = (seg[[a, b], 0] & ~np.uint32(0xFFFFF)) | shared
+            seg[b + 1, 0] = (seg[b + 1, 0] & ~np.uint32(0xFFFFF)) | other
+    return raw
+
+
+def damaged_between_clean_trace(seed, n_wg, W, R, cap):
+    """Clean and displaced records, and between their workgroups ones with a record that fails its checks, a seq that occurs
+    twice, a clock that goes back, a span beyond 32 bits, and without any record."""
+    import inputs
+
+    spec = inputs.TraceSpec(n_wg=n_wg, waves=W, n_regions=R, cap_wave=cap, total_per_wave=cap, total_var=cap // 4, seed=seed, dist="lognormal",
+                            p0=4.0, p1=1.0, p_orphan=0.02, p_swap=0.002)
+    raw, _ = inputs.gen_trace(spec)
+    raw = raw.copy()
+    heads = raw[16:16 + 32 * n_wg].reshape(n_wg, 32)
+    slots = raw[16 + 32 * n_wg:].reshape(n_wg, W, cap, 2)
+    rng = np.random.default_rng(seed)
+    for wg in range(n_wg):
+        seg, a = slots[wg, int(rng.integers(0, W))], int(rng.integers(0, cap // 2))
+        if wg % 5 == 1:
+            seg[a, 0] |= np.uint32(0x7F000000)
+        elif wg % 7 == 2:
+            seg[a + 1, 0] = (seg[a + 1, 0] & ~np.uint32(0xFFFFF)) | (seg[a, 0] & np.uint32(0xFFFFF))
+        elif wg % 11 == 3:
+            heads[wg, 5] += 2
+        elif wg % 13 == 4:
+            seg[[a, a + 1], 1] = seg[[a + 1, a], 1]
+        elif wg % 17 == 5:
+            heads[wg, 8:24] = 0
     return raw

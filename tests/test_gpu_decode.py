@@ -108,7 +108,7 @@ def test_spans_from_a_few_ticks_to_many_million(kp, oracle_mod, p0):
 def test_every_split_of_the_decoder(kp, oracle_mod, n_wg, W, R, cap):
     """The number of recorded workgroups, of record slots and of regions decide how many threads decode a workgroup, how
     many records a lane takes and how many workgroups share one set of totals: both sides of every line, clean and damaged
-    traces, crowded and sparse clocks."""
+    traces, crowded and sparse clocks.  (Most of these are over after one turn.)"""
     for p0, seed in ((1.0, 1), (5.0, 2), (11.0, 3)):
         spec = inputs.TraceSpec(n_wg=n_wg, waves=W, n_regions=R, cap_wave=cap, total_per_wave=cap, total_var=cap // 2, seed=seed,
                                 dist="lognormal", p0=p0, p1=1.0, gap_max=1 if p0 < 3 else 32, p_orphan=0.02, p_swap=0.01 if cap >= 16 else 0.0)
@@ -116,6 +116,21 @@ def test_every_split_of_the_decoder(kp, oracle_mod, n_wg, W, R, cap):
         check(raw, oracle_mod, use_hdr=True)
     raw = inputs.messy_trace(n_wg + W, n_wg=min(n_wg, 600), waves=W, n_regions=R, cap_wave=min(cap, 64), p_bad=0.01, allow_nonmono=False)
     check(raw, oracle_mod, use_hdr=True)
+
+
+# one or two geometries (up to 15 waves and 16) of every form that can be given more recorded workgroups than its decoder
+# workgroups and their teams take at a time, with 256 CUs; the forms for at most as many as CUs are the ones that cannot
+@pytest.mark.parametrize("n_wg,W,R,cap", [
+    (300, 8, 16, 1024), (301, 16, 20, 512),                                                      # 1024 threads, 256 at a time
+    (1100, 8, 8, 256), (1050, 16, 8, 128), (801, 8, 16, 256), (790, 16, 9, 128), (601, 8, 17, 256), (555, 16, 32, 128),  # 256 threads
+    (3301, 4, 3, 128), (3109, 16, 8, 32), (3302, 4, 16, 128), (3111, 16, 11, 32), (1701, 4, 17, 128), (1600, 16, 32, 32),  # a wave, 16 records per lane
+    (4501, 2, 8, 64), (3300, 4, 16, 64), (3333, 16, 9, 16), (2201, 2, 17, 64), (2100, 16, 32, 16)])                  # a wave, four records per lane
+def test_every_form_of_the_decoder_over_several_turns(kp, oracle_mod, n_wg, W, R, cap):
+    """What a decoder workgroup carries from one recorded workgroup into the next: requests, sums that are reset behind
+    their last use, totals; with damaged workgroups between clean ones."""
+    from tests.gpu_util import damaged_between_clean_trace
+
+    check(damaged_between_clean_trace(n_wg, n_wg, W, R, cap), oracle_mod, use_hdr=True)
 
 
 def test_empty_trace(kp, oracle_mod):

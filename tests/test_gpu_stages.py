@@ -69,10 +69,12 @@ def test_many_workgroups_reuse_the_table(kp, oracle_mod):
     check(kp, oracle_mod, raw, 5)
 
 
-# several turns per decoder workgroup with one, two and three of them per CU; recorded workgroups that eight does not
-# divide; blocks of 256 rows that are not full and do not divide evenly among eight waves; an odd stride of the table
+# several turns per decoder workgroup, with one of them per CU and (the last three: 547, 774 and 1024 of them on 256 CUs) up
+# to four; recorded workgroups that eight does not divide; blocks of 256 rows that are not full and do not divide evenly
+# among eight waves; an odd stride of the table
 @pytest.mark.parametrize("n_wg,W,cap,R,max_iter", [(517, 3, 1024, 16, 64), (1043, 2, 256, 7, 9), (263, 1, 2048, 33, 20),
-                                                   (2309, 1, 2, 1, 1), (801, 4, 64, 40, 101), (5, 8, 2048, 3, 300)])
+                                                   (2309, 1, 2, 1, 1), (801, 4, 64, 40, 101), (5, 8, 2048, 3, 300),
+                                                   (6001, 1, 16, 3, 4), (12003, 2, 8, 2, 2), (21005, 1, 32, 2, 5)])
 def test_turns_and_blocks(kp, oracle_mod, n_wg, W, cap, R, max_iter):
     spec = inputs.TraceSpec(n_wg=n_wg, waves=W, n_regions=R, cap_wave=cap, total_per_wave=cap - cap // 4, total_var=cap // 4,
                             seed=n_wg, p_orphan=0.02, p_swap=1e-3)
