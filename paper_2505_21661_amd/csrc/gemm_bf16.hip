@@ -101,10 +101,10 @@ struct GemmChain {
 // ------------------------------------------------------------------------------------------
 // 64x64x32 tile, 4 waves as 2x2, each wave one 32x32 accumulator tile.
 //
-// What bounds it: with few workgroups the latency of a K step, with many the L2 -> L1 traffic of so small a tile (16 KiB
-// per workgroup and pair of K steps: 545 MB of 128-byte lines, none of which hits in L1, at 16-18 TB/s; with the loads
-// left out 2112x1984x2080 takes 28 of 36 us, with the LDS stores left out too 19, with half the operand reads left out
-// 35).  So the global loads run two pairs of K steps ahead in registers, the two LDS stages hold a pair each (one barrier
+// What bounds it: with few workgroups the latency of a K step, with many the way of the tiles through registers into LDS:
+// of the 36 us that 2112x1984x2080 took when this was looked at the loads were 8 (16 KiB per workgroup and pair of K steps: 545
+// MB of 128-byte lines, none of which hits in L1), the LDS stores 9 more, half of the operand reads 1; what was left, 19 us, are
+// the MFMAs (14 at the rate of a large product) and the barriers.  So the global loads run two pairs of K steps ahead in registers, the two LDS stages hold a pair each (one barrier
 // per pair), B is stored as it comes and transposed by the operand read, and up to five workgroups share a CU.  The
 // loop is one block without exits, in which the loads stand where they are written (with an exit behind every K step the
 // compiler put them behind it, and waited for all of them once in two pairs), a lane's addresses move by one 64-bit
@@ -352,7 +352,9 @@ __global__ __launch_bounds__(256) void kp_gemm_small(GemmArgs g) {
 // 7.7 / 7.7; 1023 K = 160 5.9 / 5.9; 930 K = 160 6.0 / 6.0, 192 6.4 / 6.1; 675 K = 96 4.8 / 4.9, 128 5.1 / 4.9; 272 K = 96
 // 4.8 / 4.8.  With all regions recorded: 3906 K = 32 11.8 / 17.5, 288 28.2 / 31.7, 320 29.4 / 31.2; 1155 K = 224 10.5 /
 // 11.3; 1023 K = 32 5.7 / 6.7, 160 8.0 / 8.3, 224 9.1 / 9.2; 812 K = 32 5.3 / 6.3, 160 7.5 / 7.8; 506 K = 64 5.2 / 5.3, 128
-// 5.6 / 5.7; 255 K = 32 4.9 / 4.9.  (B in four-byte loads by half of the threads, transposed on its way to LDS, and C in
+// 5.6 / 5.7; 255 K = 32 4.9 / 4.9.  Where the pipelined kernel has come to be the faster one without sites it is not with them
+// (without / all regions / 64-lane store): 2205 K = 192 11.7, 15.0, 19.6 against 11.0, 15.1, 22.9, K = 224 12.8, 16.2, 21.8 against 12.0,
+// 16.2, 25.4; 8010 K = 256 38.9, 47.7, 69.1 against 37.8, 48.3, 80.7, K = 288 44.4, 53.3, 75.2 against 41.7, 55.8, 89.2.  (B in four-byte loads by half of the threads, transposed on its way to LDS, and C in
 // two-byte stores: 3906 K = 32 9.2, 288 27.3.)  Hence short_k(): a line for one, three, four and
 // twelve workgroups per CU, the same with and without sites, so that a recorded kernel and its baseline are one. Its
 // sites follow one another as the pipelined kernel's do.
@@ -461,17 +463,19 @@ __global__ __launch_bounds__(256) void kp_gemm_short(GemmArgs g) {
 // read).  Stage-by-stage schedule: K step +1 moves from staging registers to the same places of stage s^1 and the global
 // loads of K step +2 are in flight.
 // MFMA operands are swapped (B^T rows as the first operand) so that a lane ends up with four
-// consecutive columns of one C row per accumulator quad and can store them as 8 bytes.
-constexpr int kBigBM = 256, kBigBN = 256, kBigBK = 64;
+// consecutive columns of one C row per accumulator quad and puts them into LDS as 8 bytes, on their way to memory.
+// (With 4 waves as 2 x 2, 128x128 of C each, accumulators in AGPRs and one wave per SIMD, an earlier form was no faster: a third
+// less LDS read traffic and a short barrier, but a single wave per SIMD hides less.)
+constexpr int kBigBM = 256, kBigBN = 256, kBigBK = 64, kBigWaves = 8;
 constexpr uint32_t kBigTileBytes = 2u * (kBigBM + kBigBN) * kBigBK * 2u;  // both stages
 
-template <int INSTR, int WAVES, int SCHEDULE>
-__global__ __launch_bounds__(WAVES * 64) void kp_gemm_big(GemmArgs g) {
+template <int INSTR, int SCHEDULE>
+__global__ __launch_bounds__(kBigWaves * 64) void kp_gemm_big(GemmArgs g) {
   // default schedule: vector, scalar and LDS-read instructions may be scheduled across a chained site; the
   // regions are halves of the K step's MFMAs, which stay on their side (stages apart: nothing crosses)
   constexpr int kMayCross = SCHEDULE == 0 ? 0x106 : 0;
   // SCHEDULE 0: staging threaded through the MFMAs; 1: the stages of a K step one after the other; 2: the
-  // same source without the scheduling fences between the stages (uninstrumented only)
+  // same source without the scheduling fences between the stages and behind the MFMAs (uninstrumented only)
   constexpr bool PHASED = SCHEDULE != 0;
   static_assert(SCHEDULE != 2 || INSTR == 0, "the unfenced stage-by-stage form has no record sites");
   // INSTR 2 and 5 (constant-rate clock): chained sites; 1 and 3 are the generic sites, which the flush
@@ -480,11 +484,9 @@ __global__ __launch_bounds__(WAVES * 64) void kp_gemm_big(GemmArgs g) {
   constexpr int SITE = (INSTR == 2 || INSTR == 5) ? 6 : INSTR;
   constexpr bool REALTIME = INSTR == 3 || INSTR == 5;
   constexpr int BM = kBigBM, BN = kBigBN, BK = kBigBK;
-  constexpr int TN = WAVES == 8 ? 2 : 4;   // 32-column MFMA tiles per wave (wave tile 128 x 32*TN)
-  static_assert(WAVES == 8 || WAVES == 4, "2 x 4 or 2 x 2 waves");
-  constexpr int T = WAVES * 64;             // threads
+  constexpr int TN = 2;                    // 32-column MFMA tiles per wave (wave tile 128 x 64)
+  constexpr int T = kBigWaves * 64;         // threads
   constexpr int NA = 2048 / T;              // A chunks per thread and K step
-  constexpr int NB = 512 / T;               // B blocks (4 k x 8 n) per thread and K step
   constexpr uint32_t A_BYTES = BM * BK * 2, B_BYTES = BN * BK * 2, STAGE = A_BYTES + B_BYTES;
   extern __shared__ __align__(16) unsigned char smem[];  // [stage0 A|B][stage1 A|B][ring]
   uint32_t* ring_lds = reinterpret_cast<uint32_t*>(smem + 2 * STAGE);
@@ -509,21 +511,21 @@ __global__ __launch_bounds__(WAVES * 64) void kp_gemm_big(GemmArgs g) {
   kp::Ring ring{};
   if constexpr (INSTR != 0)
     ring = kp::ring_init<true>(ring_lds, reinterpret_cast<uint64_t*>(smem), g.cap_lds, g.region_mask, g.flush,
-                         g.cap_hbm, g.trace, g.n_wg, (uint32_t)WAVES >> g.group_log2, wg, g.group_log2);
+                         g.cap_hbm, g.trace, g.n_wg, (uint32_t)kBigWaves >> g.group_log2, wg, g.group_log2);
   ring.collab = g.collab;
   if constexpr (REALTIME) kp::ring_use_realtime(ring);
   // (with wave groups the host adds 16 bytes behind the ring for the waves that do not record)
-  if constexpr (SITE == 6) kp::chain_begin(ring, (uint32_t)(uintptr_t)ring_lds + ((uint32_t)WAVES >> g.group_log2) * g.cap_lds * 8u);
+  if constexpr (SITE == 6) kp::chain_begin(ring, (uint32_t)(uintptr_t)ring_lds + ((uint32_t)kBigWaves >> g.group_log2) * g.cap_lds * 8u);
   else kp::sites_begin<SITE>(ring);
 
   // ---- global -> register -> LDS mapping (stage-by-stage schedule) ---------------------------
   // Every thread stages the same share of a K step, so all waves reach the barrier together:
   //   A: 256 rows x 8 chunks of 16 bytes; thread t takes chunk (t & 7) of rows (t >> 3) + (T/8)*i;
-  //   B: blocks of 4 k x 8 n, 16 x 32 of them; thread t takes blocks t + T*j (k quad id >> 5, n block
-  //      id & 31) and stores the four rows of each (16 bytes) as they come; the operand reads transpose.
+  //   B: blocks of 4 k x 8 n, 16 x 32 of them; thread t takes block t (k quad t >> 5, n block
+  //      t & 31) and stores its four rows (16 bytes) as they come; the operand reads transpose.
   //      (Transposed in registers, 16 v_perm_b32 and eight 8-byte stores of which every pass took two cycles,
   //      the LDS write stage took 911 ticks per K step of a 2048x4096x4096 launch instead of 775, and the launch 4 us more.)
-  // 2048/T + 4*(512/T) 16-byte global loads per thread and K step: vector-memory instructions are
+  // Eight 16-byte global loads per thread and K step: vector-memory instructions are
   // issued at a fixed rate per CU whatever their width, so wide loads keep the issue time short.
   const uint32_t a_row = tid >> 3, a_chunk = tid & 7u;
   const uint16_t* src_a = g.A + (size_t)(m0 + a_row) * g.K + a_chunk * 8;
@@ -536,18 +538,18 @@ __global__ __launch_bounds__(WAVES * 64) void kp_gemm_big(GemmArgs g) {
   for (int i = 0; i < 4; ++i) b_dst[i] = A_BYTES + (4u * (tid >> 5) + (uint32_t)i) * 512u + ((b_nb ^ (4u * (uint32_t)i)) << 4);
   const uint16_t* src_b = g.B + (size_t)((tid >> 5) * 4) * g.N + n0 + b_nb * 8;
 
-  u32x4 la[NA], lb[NB][4];  // staging registers: A chunks, B rows
+  u32x4 la[NA], lb[4];  // staging registers: A chunks, B rows
   auto load_a = [&](uint32_t kt, int i) {
     la[i] = *reinterpret_cast<const u32x4*>(src_a + (size_t)kt * BK + (size_t)((T / 8) * i) * g.K);
   };
-  auto load_b = [&](uint32_t kt, int j, int i) {  // block j of this thread starts T/32 k quads further down
-    lb[j][i] = *reinterpret_cast<const u32x4*>(src_b + ((size_t)kt * BK + (size_t)((T / 32) * 4 * j + i)) * g.N);
+  auto load_b = [&](uint32_t kt, int i) {
+    lb[i] = *reinterpret_cast<const u32x4*>(src_b + ((size_t)kt * BK + (size_t)i) * g.N);
   };
   auto store_a = [&](uint32_t stage, int i) {
     *reinterpret_cast<u32x4*>(smem + stage * STAGE + a_dst[i]) = la[i];
   };
-  auto store_b = [&](uint32_t stage, int j, int i) {
-    *reinterpret_cast<u32x4*>(smem + stage * STAGE + b_dst[i] + (uint32_t)j * (T / 32) * 2048u) = lb[j][i];
+  auto store_b = [&](uint32_t stage, int i) {
+    *reinterpret_cast<u32x4*>(smem + stage * STAGE + b_dst[i]) = lb[i];
   };
 
   // ---- global -> LDS (default schedule) ------------------------------------------------------
@@ -603,8 +605,7 @@ __global__ __launch_bounds__(WAVES * 64) void kp_gemm_big(GemmArgs g) {
     for (int i = 0; i < 4; ++i) direct_load(b_base + (size_t)kt * BK * g.N, db_off[i], dst + A_BYTES + (uint32_t)i * 1024u);
   };
 
-  const uint32_t wm = WAVES == 8 ? wave >> 2 : wave >> 1;  // wave position: 2 x 4 or 2 x 2
-  const uint32_t wn = WAVES == 8 ? wave & 3u : wave & 1u;
+  const uint32_t wm = wave >> 2, wn = wave & 3u;  // wave position: 2 x 4
   // Operand reads of the row-major B tile: ds_read_b64_tr_b16 hands lane j of a group of 16 lanes the elements
   // j, 16 + j, 32 + j, 48 + j of the 64 that the group's lanes address (4 each, lane after lane).  With lane i
   // of a group addressing B[k0 + i / 4][n0 + 4 (i % 4) ..+3], lane j receives B[k0 .. k0 + 3][n0 + j]: four
@@ -640,23 +641,23 @@ __global__ __launch_bounds__(WAVES * 64) void kp_gemm_big(GemmArgs g) {
   // prologue: K step 0 into stage 0 (and, stage by stage, K step 1 into the staging registers)
   const uint32_t KT = g.K / BK;
   if constexpr (DIRECT) {
-    static_assert(WAVES == 8 && BK == 64, "four 1 KiB blocks of either tile per wave");
+    static_assert(kBigWaves == 8 && BK == 64, "four 1 KiB blocks of either tile per wave");
     direct_tiles(0, 0);
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // the tiles of K step 0 have landed
   } else {
 #pragma unroll
     for (int i = 0; i < NA; ++i) load_a(0, i);
 #pragma unroll
-    for (int i = 0; i < 4 * NB; ++i) load_b(0, i >> 2, i & 3);
+    for (int i = 0; i < 4; ++i) load_b(0, i);
 #pragma unroll
     for (int i = 0; i < NA; ++i) store_a(0, i);
 #pragma unroll
-    for (int i = 0; i < 4 * NB; ++i) store_b(0, i >> 2, i & 3);
+    for (int i = 0; i < 4; ++i) store_b(0, i);
     if (KT > 1) {
 #pragma unroll
       for (int i = 0; i < NA; ++i) load_a(1, i);
 #pragma unroll
-      for (int i = 0; i < 4 * NB; ++i) load_b(1, i >> 2, i & 3);
+      for (int i = 0; i < 4; ++i) load_b(1, i);
     }
   }
   asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
@@ -752,9 +753,10 @@ __global__ __launch_bounds__(WAVES * 64) void kp_gemm_big(GemmArgs g) {
   // wait for this wave's LDS traffic and for the other waves.  Four sites and eight records per K step.
   // A record site pins its place in the instruction stream (it is a scheduling fence: nothing moves across
   // the clock read).  Without sites the compiler would be free to thread the stages through one another
-  // again, and "the same schedule without record sites" would be another, faster schedule (measured: 135.5
-  // against 140 us): so the uninstrumented form has a bare scheduling fence wherever the instrumented one
-  // has a site.  SCHEDULE 2 leaves them out, for that comparison.
+  // again, and "the same schedule without record sites" would be another schedule: so the uninstrumented form has
+  // a bare scheduling fence wherever the instrumented one has a site, and both have one behind every MFMA, which keeps
+  // the operand requests where they are written.  SCHEDULE 2 leaves all of them out, for that comparison: at
+  // 4096x4096x4096 128 us, 123 with the fences, 130 with the sites.
   auto stage_fence = [] { if constexpr (INSTR == 0 && SCHEDULE == 1) __builtin_amdgcn_sched_barrier(0); };
   auto iteration_phased = [&](uint32_t kt, auto more_c, auto more2_c) {
     constexpr bool MORE = decltype(more_c)::value, MORE2 = decltype(more2_c)::value;
@@ -765,7 +767,7 @@ __global__ __launch_bounds__(WAVES * 64) void kp_gemm_big(GemmArgs g) {
 #pragma unroll
       for (int i = 0; i < NA; ++i) store_a(stage ^ 1u, i);
 #pragma unroll
-      for (int i = 0; i < 4 * NB; ++i) store_b(stage ^ 1u, i >> 2, i & 3);
+      for (int i = 0; i < 4; ++i) store_b(stage ^ 1u, i);
     }
     KP_SITE_K(ring, 1, 2, 0);
     stage_fence();
@@ -773,7 +775,7 @@ __global__ __launch_bounds__(WAVES * 64) void kp_gemm_big(GemmArgs g) {
 #pragma unroll
       for (int i = 0; i < NA; ++i) load_a(kt + 2, i);
 #pragma unroll
-      for (int i = 0; i < 4 * NB; ++i) load_b(kt + 2, i >> 2, i & 3);
+      for (int i = 0; i < 4; ++i) load_b(kt + 2, i);
     }
     KP_SITE_K(ring, 2, 0, 3);
     stage_fence();
@@ -835,7 +837,6 @@ __global__ __launch_bounds__(WAVES * 64) void kp_gemm_big(GemmArgs g) {
   // its last operand read) and leave as whole 128-byte lines.  A row is eight chunks of 16 bytes; chunk c of row r at
   // position c ^ r % 8, its halves swapped where r / 8 is odd: 16 lanes of an 8-byte write hit all banks once.  Stored from the registers, the
   // epilogue took 13500 ticks of a 4096x4096x4096 launch, all regions recorded (118 us); it takes 3900 (111 us).
-  static_assert(TN == 2, "128 bytes per row and wave");
   {
     unsigned char* sC = smem + 16384u * wave;
     const uint32_t r = lane & 31u, half = (lane >> 5) ^ ((r >> 3) & 1u);
@@ -861,7 +862,7 @@ __global__ __launch_bounds__(WAVES * 64) void kp_gemm_big(GemmArgs g) {
   }
   KP_SITE_K(ring, PHASED ? 1 : 0, PHASED ? 4 : 3, kp::kNoRegion);
   if constexpr (INSTR != 0) {
-    kp::TraceGeom tg{g.n_wg, (uint32_t)WAVES >> g.group_log2, PHASED ? 5u : 4u, g.cap_hbm, g.flags};
+    kp::TraceGeom tg{g.n_wg, (uint32_t)kBigWaves >> g.group_log2, PHASED ? 5u : 4u, g.cap_hbm, g.flags};
     if constexpr (SITE == 6) {
       // the site that closed the epilogue and, with the stages apart, the one that opened it
       kp::chain_commit<PHASED ? 2 : 1>(ring);
@@ -880,12 +881,6 @@ namespace {
 
 struct GemmShape { int bm, bn, bk, waves, regions; };
 
-// Waves per workgroup of the 256x256x64 kernel.  The kernel template also builds with 4 waves
-// (128x128 of C per wave, accumulators in AGPRs, one wave per SIMD); on MI355X that variant measured
-// about the same speed (146 vs 137-142 us at 4096^3: a third less LDS read traffic and a short
-// barrier, but a single wave per SIMD hides less), so only the 8-wave form is instantiated.
-constexpr int kBigWaves = 8;
-
 bool pick_shape(int M, int N, int K, GemmShape* s) {
   if (M <= 0 || N <= 0 || K <= 0) return false;
   // the large tile only pays off once there are enough tiles to spread over the chip
@@ -897,25 +892,25 @@ bool pick_shape(int M, int N, int K, GemmShape* s) {
 // see kp_gemm_short
 bool short_k(int K, int n_wg) { return K <= (n_wg >= 3072 ? 288 : n_wg >= 1024 ? 224 : n_wg > 768 ? 160 : n_wg > 256 ? 96 : 0); }
 
-template <int INSTR, int WAVES, int SCHEDULE>
+template <int INSTR, int SCHEDULE>
 kp_status launch_big(const GemmArgs& g, int n_wg, size_t ring_bytes, hipStream_t st) {
   static thread_local int attr_dev = -1;  // the attribute is kept per device
   int dev = 0;
   KP_HIP_TRY(hipGetDevice(&dev));
   if (attr_dev != dev) {
-    KP_HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void*>(kp_gemm_big<INSTR, WAVES, SCHEDULE>),
+    KP_HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void*>(kp_gemm_big<INSTR, SCHEDULE>),
                                    hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024));
     attr_dev = dev;
   }
-  hipLaunchKernelGGL((kp_gemm_big<INSTR, WAVES, SCHEDULE>), dim3(n_wg), dim3(WAVES * 64), kBigTileBytes + ring_bytes, st, g);
+  hipLaunchKernelGGL((kp_gemm_big<INSTR, SCHEDULE>), dim3(n_wg), dim3(kBigWaves * 64), kBigTileBytes + ring_bytes, st, g);
   KP_HIP_TRY(hipGetLastError());
   return KP_OK;
 }
 
 template <int INSTR>
 kp_status launch_big_w(bool phased, const GemmArgs& g, int n_wg, size_t ring_bytes, hipStream_t st) {
-  return phased ? launch_big<INSTR, kBigWaves, 1>(g, n_wg, ring_bytes, st)
-                : launch_big<INSTR, kBigWaves, 0>(g, n_wg, ring_bytes, st);
+  return phased ? launch_big<INSTR, 1>(g, n_wg, ring_bytes, st)
+                : launch_big<INSTR, 0>(g, n_wg, ring_bytes, st);
 }
 
 }  // namespace
@@ -964,7 +959,7 @@ extern "C" kp_status kp_gemm_instrumented(const void* A, const void* B, void* C,
   g.flags = (flush ? KP_FLAG_FLUSH : 0u) | (realtime ? KP_FLAG_REALTIME : 0u) | (collab ? KP_FLAG_HW_IDS : 0u);
   const bool big = s.bm == 256;
   if (regions == 0) {  // uninstrumented baseline: no ring, no record sites
-    if (big && unfenced) return launch_big<0, kBigWaves, 2>(g, n_wg, 0, st);
+    if (big && unfenced) return launch_big<0, 2>(g, n_wg, 0, st);
     if (big) return launch_big_w<0>(phased, g, n_wg, 0, st);
     if (short_k(K, n_wg)) hipLaunchKernelGGL(kp_gemm_short<0>, dim3(n_wg), dim3(256), 0, st, g);
     else hipLaunchKernelGGL(kp_gemm_small<0>, dim3(n_wg), dim3(256), 0, st, g);
