@@ -40,19 +40,19 @@ PEAK_HBM_GBS = 8000.0       # MI355X HBM3E
 # HBM bytes per launch from hardware counters (FETCH_SIZE x 2.000 + WRITE_SIZE x 1.000 KiB, the factors
 # read off a plain 1 GiB copy); procedure and readings are in profiles/pmc_hbm_traffic.md.
 TRAFFIC_BYTES = {
-    "decode_2^28": (1079450.8 * 2.0 + 37816.8) * 1024,
-    "gemm_vanilla": (98365.0 * 2.0 + 32796.2) * 1024,
-    "attn_vanilla": (196729.4 * 2.0 + 131100.3) * 1024,
-    "timeline_2^28": (1057962.5 * 2.0 + 2085926.4) * 1024,
-    "waits_2^28": (1056935.8 * 2.0 + 33216.0) * 1024,
-    "stages_2^28": (1043570.7 * 2.0 + 274535.0) * 1024,
-    "critical_2^28": (132139.5 * 2.0 + 992.0) * 1024,
+    "decode_2^28": (1080693.9 * 2.0 + 38840.8) * 1024,
+    "gemm_vanilla": (98356.5 * 2.0 + 32768.0) * 1024,
+    "attn_vanilla": (235271.0 * 2.0 + 131072.0) * 1024,
+    "timeline_2^28": (1094926.1 * 2.0 + 2077725.8) * 1024,
+    "waits_2^28": (1081431.6 * 2.0 + 33216.0) * 1024,
+    "stages_2^28": (1041258.1 * 2.0 + 262167.4) * 1024,
+    "critical_2^28": (132182.8 * 2.0 + 992.0) * 1024,
 }
 DECODE_BYTES_PER_RECORD = 8.0 + 16.0 * 16 / 2048 + 128.0 / 16384  # record + per-(wg,wave,region) out + wg header
 
 
 def cpu_baseline(args, inputs, a, b, q, k, v) -> dict:
-    """The CPU oracle as it stands, timed on the host cores of the GPU machine on bounded samples of the
+    """The CPU oracle as it stands, timed on the host cores beside the GPU on bounded samples of the
     benchmark's own workloads (about 10 s for the decoder, a few seconds for the others)."""
     import numpy as np
 

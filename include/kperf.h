@@ -372,9 +372,10 @@ kp_status kp_gemm_launch_shape(int M, int N, int K, int* n_wg, int* waves_per_wg
  *       issue (for the K-step after that), 3 MFMA, 1 wait (LDS traffic landed + barrier); 4 epilogue,
  *       once.  KP_MASK_PHASES with bits 0..4 all zero runs that schedule without record sites: a record
  *       site keeps its place in the instruction stream, so where the instrumented kernel has a site
- *       this one has a bare scheduling fence and the stages stay apart; with bit 26 (KP_MASK_UNFENCED)
- *       as well the fences are left out and the compiler threads the stages as it likes (for the
- *       comparison of the two; KP_ERR_INVALID_ARG with any region bit or without KP_MASK_PHASES).
+ *       this one has a bare scheduling fence and the stages stay apart (behind every MFMA both have one: the
+ *       operand requests stay where they are written); with bit 26 (KP_MASK_UNFENCED) as well all of these
+ *       fences are left out and the compiler threads the stages as it likes, which has come to be the slower
+ *       kernel (for the comparison of the two; KP_ERR_INVALID_ARG with any region bit or without KP_MASK_PHASES).
  *   otherwise M, N multiples of 64 and K of 32: tile 64x64x32, 4 waves, each once per K-step:
  *       0 global load (issued here for a K-step up to five further on), 1 LDS store (the tiles of a later K-step
  *       are stored, behind the operand reads of this one), 2 MFMA (behind every second K-step with the workgroup
@@ -399,7 +400,10 @@ kp_status kp_attn_launch_shape(int B, int H, int S, int D, int* n_wg, int* waves
  * (KP_ERR_UNSUPPORTED_SHAPE otherwise); scale must be positive and finite.
  * The paper's flash-attention study times the two GEMMs and the softmax of every KV iteration
  * (Sec. 5.2, Table 3); the regions here, once per KV tile of 64 keys, are
- *   0 Q K^T (MFMA), 1 online softmax, 2 P V (MFMA);
+ *   0 Q K^T (MFMA), 1 online softmax, 2 P V (MFMA).
+ * Region 0 takes in what hides between its MFMAs: while the scores of the tile's upper 32 keys are computed, those of the
+ * lower 32 are masked and their row maximum is taken; region 1 is the rest of the softmax (mask and maximum of the
+ * upper 32, the exponentials, the sums and, where the reference moves, the rescaling).
  * END of region 2 and START of region 0 of the next tile share one clock sample.  It is taken behind the workgroup
  * barrier that follows the tile, so the wait at that barrier belongs to region 2 (it also waits for the tiles that the
  * next one reads), and behind the last four MFMAs of P V, which are issued there.  The K and V tiles go from global

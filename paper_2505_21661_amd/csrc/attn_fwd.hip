@@ -5,8 +5,8 @@
 // the softmax of every KV iteration (Sec. 5.2, Table 3: GEMM0 = Q K^T, softmax, GEMM1 = P V).
 // This is the library's own MFMA kernel with the same three regions per KV tile of 64:
 //   region 0  S^T = K Q^T     (MFMA), with the eight loads that send this wave's share of the next V and the next K
-//             tile from global memory straight to LDS threaded in
-//   region 1  online softmax   (VALU, fp32)
+//             tile from global memory straight to LDS threaded in, and mask and maximum of the tile's lower 32 keys
+//   region 1  online softmax   (VALU, fp32): what is left of it
 //   region 2  O^T += V^T P^T   (MFMA; V is transposed by the LDS read); closes behind the barrier that follows it
 // One workgroup = 4 waves = 128 query rows of one (batch, head); each wave owns 32 rows.  The
 // products are formed transposed so that a lane holds all scores of ONE query row: the row
@@ -19,7 +19,7 @@
 // 31).  With one, the rate at which a single wave issues: 6 cycles per vector instruction, 14 per exponential, some 330
 // instructions per KV tile.  So every instruction counts, and every operand is requested eight (K) or four (V) MFMAs ahead
 // in an order that the scheduling fences hold: left to itself the compiler reads the operands of one step, waits for them,
-// multiplies.  4 x 32 x 4096, causal, all regions recorded 639 -> 550 us; 1 x 12 x 1152, 108 workgroups 27.4 -> 24.3 us;
+// multiplies.  4 x 32 x 4096, causal, all regions recorded 639 -> 550 us (541 with O as below); 1 x 12 x 1152, 108 workgroups 27.4 -> 24.3 us (21.8);
 // 2 x 9 x 1920, causal 52 -> 38 us (half of which is the order of the workgroups).  Exponentials threaded between the
 // MFMAs of either product, all or a part of them: within 1 % of this form, and region 1 no longer the softmax.  O goes
 // through LDS and leaves as whole rows: 4 x 32 x 384 16.6 -> 14.6 us, 1 x 12 x 1152 24.2 -> 23.1, 4 x 32 x 4096 1-2 %.
@@ -122,8 +122,8 @@ __global__ __launch_bounds__(kAttnThreads, 2) void kp_attn_fwd(AttnArgs g) {
     wg = xcd * (g.n_wg >> 3) + (xcd < rest ? xcd : rest) + (blockIdx.x >> 3);
   } else {
     // Causal work per block grows with its index.  All blocks of a (batch, head) go to one XCD where the heads can be
-    // dealt out evenly, so that its K and V (2 MiB at 4096 keys) are fetched into one L2 once instead of into all
-    // eight; as many heads as the XCD (the chip) has places for at a time are taken together, the longest blocks of
+    // dealt out evenly, so that its K and V (2 MiB at 4096 keys) are fetched into one L2 (1.3 times, as those of two heads
+    // fill it) instead of into all eight; as many heads as the XCD (the chip) has places for at a time (two per CU of the whole chip) are taken together, the longest blocks of
     // all of them first.  One head after the other, its long blocks start late and the last ones run on alone: 32
     // blocks and 16 heads per XCD take 292 times as long as one KV tile on 64 places, 264 with two heads together.
     const uint32_t heads = g.n_wg / q_blocks, per_xcd = (heads & 7u) == 0u ? 1u : 0u;

@@ -312,7 +312,7 @@ __global__ __launch_bounds__(1024) void kp_reduce_derive(uint64_t* out, uint32_t
 
 // ------------------------------------------------------------------------------------------
 // Position p = wave*cap_wave + rank indexes the staged records.  Hardware wave h of the decoder
-// owns positions [h*1024, h*1024 + 1024) and lane l takes position h*1024 + 64*j + l in round j,
+// owns the 64 * NR positions from 64 * NR * h on, and lane l takes 128 j + 2 l of them and the one above it in round j,
 // so that neighbouring lanes hold neighbouring ranks.
 template <int BLOCK, int NR, int TEAMS, int PLANES, int RMAX, int PERWAVE>
 __global__ __launch_bounds__(BLOCK * TEAMS, (Lds<BLOCK, NR, TEAMS, RMAX, PERWAVE>::waves_per_simd)) void kp_reduce_main(DecodeParams p) {
@@ -412,14 +412,14 @@ __global__ __launch_bounds__(BLOCK * TEAMS, (Lds<BLOCK, NR, TEAMS, RMAX, PERWAVE
 
   for (uint32_t wg = first_wg; wg < n_wg; wg += stride) {
     // A fresh copy of the thread index per workgroup that the optimiser cannot see through: without it
-    // the address arithmetic of all 16 rounds is computed once before the loop and held in registers
+    // the address arithmetic of all rounds is computed once before the loop and held in registers
     // for the whole kernel.
     uint32_t tid = tid_k;
     asm volatile("" : "+v"(tid));
     const uint32_t lane = tid & 63u, hw = (uint32_t)__builtin_amdgcn_readfirstlane((int)(tid >> 6));
     const uint32_t pbase = hw * kWaveSpan;
     const uint32_t qe = pbase + 2u * lane;     // even position of round 0; round j: qe + 128 j
-    // its clock word; round j: cwe + 136 j (pbase is a multiple of 1024, lanes 32.. are past one padding)
+    // its clock word; round j: cwe + 136 j (pbase is a multiple of 64, lanes 32.. are past one padding)
     const uint32_t cwe = qe + (pbase >> 4) + ((lane >> 5) << 2);
     // the last units of this workgroup's records: they travel while the staging state is cleared
     request_units(wg, tid, std::integral_constant<int, kEarly>{}, std::integral_constant<int, NR / 2>{});
@@ -465,7 +465,7 @@ __global__ __launch_bounds__(BLOCK * TEAMS, (Lds<BLOCK, NR, TEAMS, RMAX, PERWAVE
     const uint32_t wg_ahead = wg + stride < n_wg ? wg + stride : wg;  // (the last one asks for its own again)
     do {  // (left early only when single steps are timed)
     // ---- A: scatter by rank ------------------------------------------------------------------
-    // Eight 16-byte units (two records each) per thread cover the workgroup.  Two records that go to an
+    // NR / 2 16-byte units (two records each) per thread cover the workgroup.  Two records that go to an
     // even rank and the rank above it (the usual case: both sit in the slot of their seq) leave with one
     // 8-byte and one 2-byte store.
     // (Slots that hold a record and fail a check are what is left of the header's record count.)
@@ -551,9 +551,9 @@ __global__ __launch_bounds__(BLOCK * TEAMS, (Lds<BLOCK, NR, TEAMS, RMAX, PERWAVE
         n_occupied = tmp[T_OCCUPIED];
       }
     }
-    // ---- this lane's 16 positions: in round j the even position qe + 128 j and the one above it ---------
+    // ---- this lane's NR positions: in round j the even position qe + 128 j and the one above it ---------
     // (The arrays below are only ever assigned outside of branches: a conditional assignment makes the
-    // compiler carry each array through the branch as one 16-register value, copied at every merge.)
+    // compiler carry each array through the branch as one value of NR registers, copied at every merge.)
     uint32_t t[NR], mq[NR / 4];  // clocks; metadata bytes, record i in byte i & 3 of word i >> 2
 #pragma unroll
     for (int j = 0; j < NR / 4; ++j) mq[j] = 0u;
@@ -1310,7 +1310,7 @@ kp_status reduce_impl(const void* raw, size_t n, const kp_trace_hdr& h, void* ou
     p.rec_cost = h.rec_cost; p.flush = h.flags & KP_FLAG_FLUSH;
     p.nrec = nrec; p.ncopy = 1; p.stop_after = stop_after;
     // How many threads take a recorded workgroup, with how many records each.  Up to 16384 records: 1024 threads, 16
-    // each, which is all that fits one CU.  Fewer records leave a choice.  With no more recorded workgroups than CUs the
+    // each, which is all that fits one CU.  Fewer records leave a choice.  With no more recorded workgroups than CUs (256 of the whole chip) the
     // time is one workgroup's chain of steps, and four records per lane make it shorter: 64 workgroups of 4 x 128 records
     // 20.6 us with 16 each (one wave), 16.7 with four (four waves); 256 of 8 x 512 32.3 and 30.1; 100 of 1 x 4096 26.7 and
     // 24.0.  With more of them it is the work, most of which a wave does for all its places whether they hold records or
