@@ -139,7 +139,7 @@ size_t kp_stats_bytes(int n_wg, int waves_per_wg, int n_regions);
  *   out_stats  device, kp_stats_bytes(...) bytes, 16-byte aligned; fully overwritten
  *
  * kp_trace_reduce reads the 64-byte trace header back from the device to learn the geometry:
- * it synchronises `stream` once before it enqueues the kernels.  kp_trace_reduce_hdr takes
+ * it waits for it, and with it for the work ahead on `stream`, before it enqueues the kernels.  kp_trace_reduce_hdr takes
  * the geometry from a HOST copy of the header instead and never synchronises; if the device
  * header disagrees, no statistics are produced and kp_stats_hdr.status is set to 1.
  *
