@@ -593,6 +593,26 @@ def test_stage_by_stage_regions(kp, oracle_mod, shape):
     assert kp.parse_stats(out_m)["cnt"].tolist() == [0, steps * per, 0, steps * per, 0]
 
 
+@pytest.mark.parametrize("steps", [1, 2, 3, 4, 7])
+@pytest.mark.parametrize("extra", ["0", "group", "flush", "collab"])
+def test_stage_by_stage_few_k_steps(kp, steps, extra):
+    """Waves 4 to 7 are one barrier behind waves 0 to 3: the K steps in which only one half still writes or loads tiles, and
+    fewer of them than the pipeline is deep.  C bit-identical to the default schedule's (same sums in the same order),
+    with and without sites, and the closed-form record counts."""
+    M, N, K = 1024, 1280, 64 * steps
+    a, b = inputs.gemm_inputs(M, N, K, seed=40 + steps)
+    c_ref, _, _ = run_gemm(kp, a, b, 0)
+    assert_close_to_oracle(c_ref, a, b)
+    mask = {"0": 0, "group": kp.KP_MASK_WAVE_GROUP, "flush": kp.KP_MASK_FLUSH, "collab": kp.KP_MASK_COLLAB}[extra]
+    streams = 2 if extra == "group" else 8
+    c_off, _, _ = run_gemm_phased(kp, a, b, 0)
+    c_ins, trace, (n_wg, _, _) = run_gemm_phased(kp, a, b, 0b11111, trace_cap=64 * streams, extra=mask)
+    for c in (c_off, c_ins):
+        assert torch.equal(c.view(torch.int16), c_ref.view(torch.int16))
+    raw = trace.cpu().numpy().view(np.uint32)
+    assert (raw[16:16 + 32 * n_wg].reshape(n_wg, 32)[:, 8:8 + streams] == (4 * steps + 1) * 2).all()
+
+
 def test_stage_by_stage_needs_the_large_tile(kp):
     a, b = inputs.gemm_inputs(256, 256, 256, seed=0)
     with pytest.raises(kp.KperfError) as e:
