@@ -10,6 +10,11 @@ __device__ __forceinline__ uint32_t wave_shr1(uint32_t v, uint32_t lane0) {
   return (uint32_t)__builtin_amdgcn_update_dpp((int)lane0, (int)v, 0x138, 0xF, 0xF, false);
 }
 
+// Lane l receives the value of lane l-1; lane 0 that of lane 63 (DPP wave rotate right by one).
+__device__ __forceinline__ uint32_t wave_ror1(uint32_t v) {
+  return (uint32_t)__builtin_amdgcn_mov_dpp((int)v, 0x13C, 0xF, 0xF, true);
+}
+
 // The DPP steps of an inclusive scan over the 64 lanes: four shifts inside each row of 16, then the
 // last lane of row 0/2 into row 1/3 and the last lane of the lower half into the upper half.  Lanes
 // without a source read `none`.
@@ -20,6 +25,10 @@ template <int STEP> __device__ __forceinline__ uint32_t scan_src(uint32_t v, uin
   if (STEP == 3) return (uint32_t)__builtin_amdgcn_update_dpp((int)none, (int)v, 0x118, 0xF, 0xF, false);  // row_shr:8
   if (STEP == 4) return (uint32_t)__builtin_amdgcn_update_dpp((int)none, (int)v, 0x142, 0xA, 0xF, false);  // row_bcast:15
   return (uint32_t)__builtin_amdgcn_update_dpp((int)none, (int)v, 0x143, 0xC, 0xF, false);                 // row_bcast:31
+}
+
+template <int STEP> __device__ __forceinline__ uint64_t scan_src64(uint64_t v) {
+  return (uint64_t)scan_src<STEP>((uint32_t)v) | ((uint64_t)scan_src<STEP>((uint32_t)(v >> 32)) << 32);
 }
 
 __device__ __forceinline__ uint32_t wave_scan_add(uint32_t v) {

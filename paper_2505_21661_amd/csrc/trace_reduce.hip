@@ -3,14 +3,14 @@
 // The paper stores START/END records unpaired, per warp, in a ring whose tail survives, and
 // aligns them at "trace replay" on the host (Sec. 4.2 "SM-level Data Layout", "Shared Memory
 // Circular Buffer"; Sec. 4.3).  Here replay runs on the GPU: one persistent decoder workgroup
-// takes one recorded workgroup at a time and keeps it in LDS as a clock word and a metadata byte
-// per record.
-//   A  every record is scattered to its rank (seq - first surviving seq), which undoes ring
-//      rotation and out-of-order flushes in O(1) per record; the records of the next workgroup
-//      are requested before the results of the current one are written;
-//   B  a lane takes the records of NR / 2 rounds of 128 consecutive ranks, two neighbours per round;
-//      an END is paired iff the nearest earlier record of its (wave, region) is a START --
-//      usually the rank just below, in the same lane or the lane below (DPP);
+// takes one recorded workgroup at a time.
+//   A  every lane holds the records of NR / 2 rounds of 128 consecutive slots, two neighbours per round, and checks that
+//      they are the ones that belong there (seq against slot).  One that is not goes to its slot through LDS, in O(1), which
+//      undoes out-of-order flushes; ring rotation is a question of which slot is the oldest.  The records of the next
+//      workgroup are requested before the results of the current one are written;
+//   B  an END is paired iff the nearest earlier record of its (wave, region) is a START --
+//      usually the slot just below, in the same lane or the lane below (DPP), four records at a time on their packed
+//      metadata bytes; the others look through the records in LDS, where they are put only if some END has to;
 //      d = (u32)(ts_end - ts_start) minus the constant record cost (Sec. 4.3) goes to the
 //      per-(wave, region) sums and the log2 histogram with LDS atomics;
 //   C  the paired records of all waves are sorted by clock: counting sort into time cells (one
@@ -18,14 +18,17 @@
 //      them in cell order;
 //   D  every lane takes NR (4 or 16) consecutive records of that sequence and finishes the order in
 //      registers (a sorting network over its own records, then a merge of its outer halves with
-//      the neighbouring lanes').  The number of waves that have each region open is kept
-//      bit-sliced (plane k = bit k of every region's count); a first pass gives each lane's net
-//      change, a prefix sum over lanes and waves the state at the start of each lane's stretch,
-//      and the second pass the set of open regions after every record.  The time two regions
+//      the neighbouring lanes').  A first pass gives each lane's net change in the number of waves that have each region
+//      open, a prefix sum over lanes and waves (one 64-bit number with four bits per region, up to 15 waves) the state at
+//      the start of each lane's stretch, and a second pass, on bit-sliced counts (plane k = bit k of every region's count),
+//      the set of open regions after every record.  The time two regions
 //      are both open is the sum over the stretches between records of length * open(a) * open(b):
 //      a matrix product, taken by the matrix cores 64 stretches at a time;
 //   E  the per-(workgroup, wave, region) results go to HBM and into running totals, which live in
 //      LDS and reach HBM once per decoder workgroup.
+// What bounds it is instruction issue: 2.6 vector instructions per record (3.2 with every record scattered to LDS by its
+// rank and read back, one round at a time in B, planes in the prefix sum): 16384 workgroups of 8 x 2048 records 1775 -> 1550
+// us; 4000 of 4 x 1024, wrapped 125 -> 114; 256 of 8 x 512 28.7 -> 27.1; 512 of 8 x 2048, regions three deep 389 -> 219.
 // Traces outside what the register sort covers (more than 16 regions, a span of 2^26 ticks or
 // more, a time cell with more than NR + 1 records) rank the records inside their cell by comparing
 // clocks and add every switch of a region to the region-pair sums with LDS atomics.
@@ -51,9 +54,13 @@ constexpr uint32_t kHistStride = 65;  // histogram rows 65 words apart: equal bi
 // steps after which kp_trace_reduce_steps can leave a workgroup
 enum { kStepOrdered = 1, kStepPaired, kStepCounted, kStepCellSums, kStepPlaced, kStepRanked, kStepSorted, kStepSwept };
 
+// A condition that seldom holds: what hangs on it is kept out of the straight line of instructions, which a launch of few
+// workgroups has to fetch before it can run.
+__device__ __forceinline__ bool rare(bool x) { return __builtin_expect(x, false); }
+
 // per-workgroup temporaries (u32 words in LDS)
-enum { T_INVALID = 0, T_FIELDVALID, T_DISORDER, T_OCCUPIED, T_NONMONO, T_PAIRS, T_STARTS, T_ENDS,
-       T_EVENTS, T_MARKS, T_WIDE, T_MAXCELL, T_ZERO, T_HELD, T_COUNT };  // T_HELD stays last
+enum { T_BAD = 0, T_DISORDER, T_UNFILLED, T_NONMONO, T_PAIRS, T_STARTS, T_ENDS,
+       T_EVENTS, T_MARKS, T_DEEP, T_WIDE, T_MAXCELL, T_ZERO, T_HELD, T_COUNT };  // T_HELD stays last
 
 struct DecodeParams {
   const uint32_t* wg_hdrs;  // 32 words per recorded workgroup
@@ -75,24 +82,29 @@ constexpr uint32_t kMaxPerWave = 1024;  // entries of the per-(wave, region) sum
 template <int BLOCK, int NR, int TEAMS, int RMAX, int PERWAVE>
 struct Lds {
   static constexpr uint32_t npos = BLOCK * NR, ncell = BLOCK * 16;
-  // of every team
-  static constexpr uint32_t clk = 0;                                       // 4 words of padding after every 64
-  static constexpr uint32_t meta = align16(clk + (npos + npos / 16) * 4);
-  static constexpr uint32_t cells = align16(meta + npos + 16);             // one 16-bit counter per time cell + the total
-  static constexpr uint32_t tmp = align16(cells + (ncell / 2 + 4) * 4);
-  static constexpr uint32_t misc = align16(tmp + T_COUNT * 4);
-  static constexpr uint32_t vf = misc + 4 * 4;
-  static constexpr uint32_t wtot = vf + 32 * 8;
-  static constexpr uint32_t ptot = wtot + 16 * 4;
-  static constexpr uint32_t oacc32 = align16(ptot + (BLOCK / 64) * 8 * 4);
-  static constexpr uint32_t pw_pack = align16(oacc32 + RMAX * (RMAX + 1) * 4);
+  // (What is addressed by a computed index stands in the first 64 KiB: its base then fits the instruction.)
+  // of all teams
+  static constexpr uint32_t hist = 0;
+  static constexpr uint32_t teams = align16(hist + RMAX * kHistStride * 4);
+  // of every team, from the start of its block on
+  static constexpr uint32_t pw_pack = 0;
   static constexpr uint32_t pw_max = pw_pack + PERWAVE * 8;
   static constexpr uint32_t pw_min = pw_max + PERWAVE * 4;
-  static constexpr uint32_t team = align16(pw_min + PERWAVE * 4);
+  static constexpr uint32_t cells = pw_min + PERWAVE * 4;                  // one 16-bit counter per time cell + the total
+  static constexpr uint32_t clk = align16(cells + (ncell / 2 + 4) * 4);    // 4 words of padding after every 64
+  static constexpr uint32_t meta = align16(clk + (npos + npos / 16) * 4);
+  static constexpr uint32_t tmp = align16(meta + npos + 16);
+  static constexpr uint32_t misc = align16(tmp + T_COUNT * 4);
+  static constexpr uint32_t vf = misc + 4 * 4;
+  static constexpr uint32_t ring_end = vf + (KP_MAX_WAVES + 1) * 8;
+  static constexpr uint32_t wtot = ring_end + KP_MAX_WAVES * 8;
+  static constexpr uint32_t ptot = wtot + 16 * 4;
+  static constexpr uint32_t wave_end = ptot;                               // (done with before ptot is written)
+  static constexpr uint32_t oacc32 = align16(ptot + (BLOCK / 64) * 8 * 4);
+  static constexpr uint32_t team = align16(oacc32 + RMAX * (RMAX + 1) * 4);
   // of all teams
-  static constexpr uint32_t ctr = TEAMS * team;
-  static constexpr uint32_t hist = ctr + 16 * 8;
-  static constexpr uint32_t oacc = align16(hist + RMAX * kHistStride * 4);
+  static constexpr uint32_t ctr = teams + TEAMS * team;
+  static constexpr uint32_t oacc = ctr + 16 * 8;
   static constexpr uint32_t reg_sum = oacc + RMAX * RMAX * 8;
   static constexpr uint32_t reg_max = reg_sum + RMAX * 8;
   static constexpr uint32_t reg_min = reg_max + RMAX * 4;
@@ -118,12 +130,6 @@ __device__ __forceinline__ void team_sync() {
 // 64 lanes of a wave reading 16 consecutive words each (64 bytes apart) spread over all banks.
 __device__ __forceinline__ uint32_t clk_word(uint32_t i) { return i + ((i >> 6) << 2); }
 
-// Sum over the wave, added to tmp[which] by the last lane.
-__device__ __forceinline__ void add_tmp(uint32_t* tmp, int which, uint32_t v) {
-  v = wave_scan_add(v);
-  if ((threadIdx.x & 63u) == 63u && v) atomicAdd(&tmp[which], v);
-}
-
 // a += b for bit-sliced numbers: plane k holds bit k of 32 independent counters, modulo 2^PLANES.
 template <int PLANES>
 __device__ __forceinline__ void planes_add(uint32_t (&a)[PLANES], const uint32_t (&b)[PLANES]) {
@@ -145,14 +151,25 @@ __device__ __forceinline__ void planes_step(uint32_t (&pl)[PLANES], uint32_t x, 
   for (int k = 0; k < PLANES; ++k) { const uint32_t o = pl[k]; pl[k] = o ^ carry; carry &= o ^ dm; }
 }
 
-// The sweep works on one word per record of the sequence: clock << 6 | region << 1 | END; records with
+// The sweep works on one word per record of the sequence: clock << 6 | END << 5 | region; records with
 // equal words are interchangeable.  A place past the end of the sequence holds `fake`: the largest
 // clock of the workgroup with a region number that no record has, so that it sorts last, opens no
 // region and the stretch in front of it has an honest length.
 // Fields of such a word.
 __device__ __forceinline__ uint32_t key_clock(uint32_t k) { return k >> 6; }
-__device__ __forceinline__ uint32_t key_region_bit(uint32_t k) { return 1u << ((k >> 1) & 31u); }  // bit 31 for a place past the end: above every region
-__device__ __forceinline__ uint32_t key_end_mask(uint32_t k) { return (uint32_t)__builtin_amdgcn_sbfe((int)k, 0, 1); }  // all ones for an END
+__device__ __forceinline__ uint32_t key_region_bit(uint32_t k) { return 1u << (k & 31u); }  // bit 31 for a place past the end: above every region
+__device__ __forceinline__ uint32_t key_end_mask(uint32_t k) { return (uint32_t)__builtin_amdgcn_sbfe((int)k, 5, 1); }  // all ones for an END
+
+// Eight 4-bit numbers as planes: byte k of the result holds bit k of each.  Bit 4 r + k goes to 8 k + r: the five index
+// bits r2 r1 r0 k1 k0 become k1 k0 r2 r1 r0, by four exchanges of two of them.
+__device__ __forceinline__ uint32_t planes_of_nibbles(uint32_t x) {
+  auto exchange = [&](int d, uint32_t m) { const uint32_t t = ((x >> d) ^ x) & m; x ^= t ^ (t << d); };
+  exchange(14, 0x0000CCCCu);
+  exchange(7, 0x00AA00AAu);
+  exchange(2, 0x0C0C0C0Cu);
+  exchange(1, 0x22222222u);
+  return x;
+}
 
 // The NR records of the clock-sorted sequence that lane `tid` of the sweep owns, from a sequence that
 // is only ordered cell by cell (inside a cell the records stand in arrival order).  Cells follow one
@@ -271,6 +288,14 @@ __global__ void kp_reduce_init(const uint32_t* trace_hdr, uint64_t* out, uint32_
 // 27.2; 64 of 8 x 512, 5 regions 25.7 and 25.1; 256 of them 32.3 and 33.0.
 __global__ __launch_bounds__(1024) void kp_reduce_derive(uint64_t* out, uint32_t n_wg, uint32_t W, uint32_t R) {
   const StatsLayout l = stats_layout(n_wg, W, R);
+  // Up to 32 regions: one element per thread, requested ahead of the histograms and read before any is written, so that
+  // there is one way to memory and back.
+  uint64_t o = 0, u = 0;
+  const uint32_t at = threadIdx.x, at_a = at / R, at_b = at - at_a * R;
+  if (R <= 32u && at < R * R) {
+    o = out[l.F + (at_a <= at_b ? at : at_b * R + at_a)];
+    u = out[l.F + at_a * R + at_a];
+  }
   for (uint32_t i = threadIdx.x; i < ((R * 16u + 63u) & ~63u); i += blockDim.x) {  // 16 lanes per region
     const uint32_t r = i >> 4, part = i & 15u;
     uint64_t n = 0;
@@ -282,18 +307,12 @@ __global__ __launch_bounds__(1024) void kp_reduce_derive(uint64_t* out, uint32_t
     for (int d = 8; d >= 1; d >>= 1) n += __shfl_xor((unsigned long long)n, d, 64);
     if (r < R && part == 0u) out[l.cnt + r] = n;
   }
-  if (R <= 32u) {  // one element per thread, read before any is written: no second way to memory and back
-    const uint32_t i = threadIdx.x, a = i / R, b = i - a * R;
-    uint64_t o = 0, u = 0;
-    if (i < R * R) {
-      o = out[l.F + (a <= b ? i : b * R + a)];
-      u = out[l.F + a * R + a];
-    }
+  if (R <= 32u) {
     __syncthreads();
-    if (i < R * R) {
-      out[l.O + i] = o;
-      if (a == b) out[l.U + a] = o;
-      reinterpret_cast<double*>(out)[l.F + i] = u ? (double)o / (double)u : 0.0;
+    if (at < R * R) {
+      out[l.O + at] = o;
+      if (at_a == at_b) out[l.U + at_a] = o;
+      reinterpret_cast<double*>(out)[l.F + at] = u ? (double)o / (double)u : 0.0;
     }
     return;
   }
@@ -323,7 +342,7 @@ __global__ __launch_bounds__(BLOCK * TEAMS, (Lds<BLOCK, NR, TEAMS, RMAX, PERWAVE
   __shared__ __align__(16) unsigned char shared[L::total];
   const uint32_t team = TEAMS == 1 ? 0u : (uint32_t)__builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
   const uint32_t n_teams = TEAMS == 1 ? 1u : blockDim.x >> 6;  // (as many as the launch asked for)
-  unsigned char* smem = shared + team * L::team;
+  unsigned char* smem = shared + L::teams + team * L::team;
   uint32_t* clk = reinterpret_cast<uint32_t*>(smem + L::clk);
   uint8_t* meta = smem + L::meta;
   uint32_t* cells = reinterpret_cast<uint32_t*>(smem + L::cells);  // cell c: half (c & 1) of word c >> 1
@@ -340,10 +359,14 @@ __global__ __launch_bounds__(BLOCK * TEAMS, (Lds<BLOCK, NR, TEAMS, RMAX, PERWAVE
   uint32_t* tmp = reinterpret_cast<uint32_t*>(smem + L::tmp);
   uint32_t* misc = reinterpret_cast<uint32_t*>(smem + L::misc);  // [0] span overflow, [1] cell scale, [2] span
   uint2* sVF = reinterpret_cast<uint2*>(smem + L::vf);           // per wave: records held, first surviving seq
+  uint2* ring_end = reinterpret_cast<uint2*>(smem + L::ring_end);  // per wave: clock and metadata in the last slot of its ring
+  uint2* wave_end = reinterpret_cast<uint2*>(smem + L::wave_end);  // the same of the last position of each hardware wave
   uint32_t* wtot = reinterpret_cast<uint32_t*>(smem + L::wtot);
   uint32_t* ptot = reinterpret_cast<uint32_t*>(smem + L::ptot);
 
+  auto seldom = [](bool x) -> bool { return NR == 4 ? x : rare(x); };  // (where a ring begins or ends: in most rounds of small workgroups)
   constexpr uint32_t NPOS = L::npos, NCELL = L::ncell;
+  constexpr uint32_t kSlotShift = (BLOCK == 1024 ? 14 : BLOCK == 256 ? 12 : 10) + 4;
   // The last four words of the clock array are padding that no position maps to, and the metadata
   // array has 16 spare bytes: stores of lanes that have nothing to store go there instead of branching.
   constexpr uint32_t kSpareWord = NPOS + NPOS / 16 - 1;
@@ -390,9 +413,10 @@ __global__ __launch_bounds__(BLOCK * TEAMS, (Lds<BLOCK, NR, TEAMS, RMAX, PERWAVE
   constexpr int kEarly = NR / 2 * 3 / 4 > 1 ? NR / 2 * 3 / 4 : NR / 2;  // units requested before the matrix products of the sweep of the workgroup before
   auto request_units = [&](uint32_t g, uint32_t t, auto first, auto last) {
     const u32x4* recs = p.records + (size_t)g * (nrec / 2);
+    const uint32_t t_first = (t >> 6) * (kWaveSpan / 2u) + (t & 63u);
 #pragma unroll
     for (int u = decltype(first)::value; u < decltype(last)::value; ++u) {
-      const uint32_t i = t + u * BLOCK;
+      const uint32_t i = t_first + 64u * u;
       v[u] = __builtin_nontemporal_load(recs + (i < nrec / 2 ? i : nrec / 2 - 1));
     }
   };
@@ -439,21 +463,14 @@ __global__ __launch_bounds__(BLOCK * TEAMS, (Lds<BLOCK, NR, TEAMS, RMAX, PERWAVE
       const uint64_t tb = (uint64_t)h_begin.x | ((uint64_t)h_begin.y << 32);
       const uint64_t te = (uint64_t)h_end.x | ((uint64_t)h_end.y << 32);
       const uint64_t sp = te - tb;
-      // cell of clock t: (t * scale) >> 32, i.e. the span divided into NCELL cells (clamped below).  Any
-      // scale near NCELL * 2^32 / (span + 1) orders the cells by time, so a floating-point quotient does:
-      // a 64-bit integer division is some 150 instructions that every wave of the workgroup waits for.
-      const double scale = (double)NCELL * 4294967296.0 / ((double)(uint32_t)sp + 1.0);
+      // 16 times the cell of clock t: t * scale, i.e. the span divided into NCELL cells (clamped below).  Any
+      // scale near 16 * NCELL / (span + 1) orders the cells by time.
+      const float scale = (float)(16u * NCELL) / ((float)(uint32_t)sp + 1.0f);
       misc[0] = (sp >> 32) ? 1u : 0u;
-      misc[1] = scale >= 4294967295.0 ? 0xFFFFFFFFu : (uint32_t)scale;
+      misc[1] = __builtin_bit_cast(uint32_t, scale);
       misc[2] = (uint32_t)sp;
     }
     clear_meta(tid);
-    {  // a position without a record reads as the largest clock: it never counts as a step back in time
-      uint32_t ones[NR];
-#pragma unroll
-      for (int i = 0; i < NR; ++i) ones[i] = 0xFFFFFFFFu;
-      store_run<NR>(clk, tid, ones);
-    }
     reinterpret_cast<u32x4*>(cells)[2 * tid] = u32x4{0u, 0u, 0u, 0u};
     reinterpret_cast<u32x4*>(cells)[2 * tid + 1] = u32x4{0u, 0u, 0u, 0u};
     if (tid == 0) reinterpret_cast<u32x4*>(cells)[2 * BLOCK] = u32x4{0u, 0u, 0u, 0u};
@@ -461,210 +478,329 @@ __global__ __launch_bounds__(BLOCK * TEAMS, (Lds<BLOCK, NR, TEAMS, RMAX, PERWAVE
 
     uint32_t wg_invalid = 0;
     bool eligible = false;
-    uint32_t products = 0;  // limbs of the stretch lengths when the sweep hands its sets to the matrix cores, else 0
+    uint32_t products = 0;  // digits of the stretch lengths when the sweep hands its sets to the matrix cores, else 0
     const uint32_t wg_ahead = wg + stride < n_wg ? wg + stride : wg;  // (the last one asks for its own again)
     do {  // (left early only when single steps are timed)
-    // ---- A: scatter by rank ------------------------------------------------------------------
-    // NR / 2 16-byte units (two records each) per thread cover the workgroup.  Two records that go to an
-    // even rank and the rank above it (the usual case: both sit in the slot of their seq) leave with one
-    // 8-byte and one 2-byte store.
-    // (Slots that hold a record and fail a check are what is left of the header's record count.)
-    {
-      uint32_t c_field = 0, c_dis = 0;
+    // ---- A: every record to its place --------------------------------------------------------------
+    // Places are slots: rank k of a wave belongs in slot (first + k) mod capacity, and a record is nearly always there.
+    // So the records stay in the registers they were loaded into, and a lane checks that its two of a round are the ones
+    // expected.  A round in which some record is not looks at every one of them: a record that belongs elsewhere is left
+    // in LDS at its place, and a place whose own record is missing looks there behind the barrier.
+    // Round j: the even position qe + 128 j and the one above it.  A place without a record holds the largest clock: it
+    // never counts as a step back in time.
+    uint32_t t[NR], mq[NR / 4];  // clocks; metadata bytes, record i in byte i & 3 of word i >> 2
+    uint32_t holes = 0;          // bit i: place i has a slot that holds a record, but not its own
+    // Rings of at least 128 slots: a round is one recorded wave's, and what there is to know of that is uniform; of at least
+    // a hardware wave's share: so are all its rounds.
+    const bool whole_rings = cap >= kWaveSpan, small_rings = cap < 128u;
+    const uint32_t wave_here = pbase >> cl2;
+    uint32_t held_here = 0, first_here = 0;  // records held by that wave, its first surviving seq
+    if (whole_rings && wave_here < W) {
+      const uint32_t T = (uint32_t)__builtin_amdgcn_readlane((int)h_total, (int)wave_here);
+      held_here = T < cap ? T : cap;
+      first_here = flush ? 0u : T - held_here;
+    }
+    const uint32_t slot_here = pbase & capm;
+    const uint32_t to_oldest = (first_here - slot_here) & capm;  // slots from the hardware wave's first place to the oldest record
+    auto set_round = [&](int j, uint32_t t0, uint32_t t1, uint32_t m2) __attribute__((always_inline)) {
+      t[2 * j] = t0; t[2 * j + 1] = t1;
+      if (j & 1) mq[j >> 1] |= m2 << 16; else mq[j >> 1] = m2;
+    };
+    // What others need to know of the records here: the last one of the hardware wave and those at the ends of rings.
+    auto publish_ends = [&]() __attribute__((always_inline)) {
+      const uint2 e = make_uint2(t[NR - 1], mq[NR / 4 - 1] >> 24);
+      if (lane == 63u) wave_end[hw] = e;
+      if (whole_rings) {
+        if (((pbase + kWaveSpan) & capm) == 0u && wave_here < W && lane == 63u) ring_end[wave_here] = e;
+      } else {
 #pragma unroll
-      for (int u = 0; u < NR / 2; ++u) {
-        const uint32_t f0 = 2u * (tid + u * BLOCK);
-        // a unit past the last record slot falls into a wave past the last one, which holds no records
-        const uint32_t wv = f0 >> cl2, w = wv < KP_MAX_WAVES ? wv : KP_MAX_WAVES, s0 = f0 & capm;
-        const uint2 vf = sVF[w];
-        const uint32_t V = vf.x, first = vf.y;
-        const uint32_t tag0 = v[u].x, pay0 = v[u].y, tag1 = v[u].z, pay1 = v[u].w;
-        // rank: the low 20 bits of tag - first are those of seq - first
-        const uint32_t k0 = (tag0 - first) & kSeqMask, k1 = (tag1 - first) & kSeqMask;
-        const bool good0 = s0 < V && k0 < V && ((tag0 >> 20) & 0xFu) == w && ((tag0 >> 24) & 0x7Fu) < R;
-        const bool good1 = s0 + 1u < V && k1 < V && ((tag1 >> 20) & 0xFu) == w && ((tag1 >> 24) & 0x7Fu) < R;
-        c_field += (good0 ? 1u : 0u) + (good1 ? 1u : 0u);
-        c_dis += ((good0 && ((tag0 ^ s0) & capm) != 0u) ? 1u : 0u) + ((good1 && ((tag1 ^ (s0 + 1u)) & capm) != 0u) ? 1u : 0u);
-        const uint32_t base = f0 - s0;  // first position of the recorded wave
-        const uint32_t pos0 = base + k0, pos1 = base + k1;
-        // an even rank and the one above it: k1 - k0 == 1 and k0 even
-        const bool twin = good0 && good1 && (((k1 - k0) ^ 1u) | (k0 & 1u)) == 0u;
-        if (twin) {
-          uint32_t* dst = clk + clk_word(pos0);
-          dst[0] = pay0; dst[1] = pay1;
-          *reinterpret_cast<uint16_t*>(meta + pos0) = (uint16_t)__builtin_amdgcn_perm(tag1, tag0, 0x0C0C0703u);  // END flag and region of both
-        } else {
-          if (good0) { clk[clk_word(pos0)] = pay0; meta[pos0] = (uint8_t)(tag0 >> 24); }
-          if (good1) { clk[clk_word(pos1)] = pay1; meta[pos1] = (uint8_t)(tag1 >> 24); }
+        for (int j = 0; j < NR / 2; ++j) {
+          const uint32_t q = qe + 128u * j;
+          if (((q + 2u) & capm) == 0u && q < nrec) ring_end[q >> cl2] = make_uint2(t[2 * j + 1], (mq[j >> 1] >> (16 * (j & 1) + 8)) & 0xFFu);
         }
       }
-      add_tmp(tmp, T_FIELDVALID, c_field);
-      add_tmp(tmp, T_DISORDER, c_dis);
+    };
+    {
+      uint32_t c_bad = 0, c_dis = 0;
+      // e0, e1: the low 24 bits of the tags if both records are in place.  (Where that does not take a ring that begins
+      // in the round or a seq that wraps into account, the records are looked at like any other.)
+      auto check = [&](int j, uint32_t w, uint32_t V, uint32_t first, uint32_t s0, bool whole, uint32_t e0, uint32_t e1) __attribute__((always_inline)) {
+        const uint32_t tag0 = v[j].x, tag1 = v[j].z;
+        const uint32_t wrong = ((tag0 ^ e0) | (tag1 ^ e1)) & 0xFFFFFFu;
+        const uint32_t r0 = tag0 & 0x7F000000u, r1 = tag1 & 0x7F000000u;
+        uint32_t t0 = v[j].y, t1 = v[j].w, m2 = __builtin_amdgcn_perm(tag1, tag0, 0x0C0C0703u);  // END flag and region of both
+        if (seldom(!whole || (__builtin_amdgcn_ballot_w64(wrong != 0u) | __builtin_amdgcn_ballot_w64((r0 > r1 ? r0 : r1) >= (R << 24))) != 0ull)) {
+          bool home0 = s0 < V, home1 = s0 + 1u < V;
+          const bool odd0 = ((tag0 ^ e0) & 0xFFFFFFu) != 0u || r0 >= (R << 24), odd1 = ((tag1 ^ e1) & 0xFFFFFFu) != 0u || r1 >= (R << 24);
+          if (rare(__builtin_amdgcn_ballot_w64((home0 && odd0) || (home1 && odd1)) != 0ull)) {
+            // rank: the low 20 bits of tag - first are those of seq - first
+            const uint32_t n0 = (tag0 - first) & kSeqMask, n1 = (tag1 - first) & kSeqMask;
+            const bool good0 = s0 < V && n0 < V && ((tag0 >> 20) & 0xFu) == w && r0 < (R << 24);
+            const bool good1 = s0 + 1u < V && n1 < V && ((tag1 >> 20) & 0xFu) == w && r1 < (R << 24);
+            home0 = good0 && ((tag0 ^ s0) & capm) == 0u;
+            home1 = good1 && ((tag1 ^ (s0 + 1u)) & capm) == 0u;
+            const uint32_t q = qe + 128u * j - s0;  // first position of the recorded wave
+            if (good0 && !home0) { const uint32_t to = q + (tag0 & capm); clk[clk_word(to)] = t0; meta[to] = (uint8_t)(tag0 >> 24); ++c_dis; }
+            if (good1 && !home1) { const uint32_t to = q + (tag1 & capm); clk[clk_word(to)] = t1; meta[to] = (uint8_t)(tag1 >> 24); ++c_dis; }
+            c_bad += (s0 < V && !good0 ? 1u : 0u) + (s0 + 1u < V && !good1 ? 1u : 0u);
+            holes |= (s0 < V && !home0 ? 1u << (2 * j) : 0u) | (s0 + 1u < V && !home1 ? 2u << (2 * j) : 0u);
+          }
+          t0 = home0 ? t0 : 0xFFFFFFFFu;
+          t1 = home1 ? t1 : 0xFFFFFFFFu;
+          m2 = (home0 ? m2 & 0xFFu : kEmpty) | (home1 ? m2 & 0xFF00u : kEmpty << 8);
+        }
+        set_round(j, t0, t1, m2);
+      };
+      if (whole_rings) {
+        const uint32_t tag_here = (wave_here << 20) + first_here + ((slot_here - first_here) & capm) + 2u * lane;
+#pragma unroll
+        for (int j = 0; j < NR / 2; ++j) {
+          if (rare(slot_here + 128u * j >= held_here)) {
+            set_round(j, 0xFFFFFFFFu, 0xFFFFFFFFu, kEmpty | (kEmpty << 8));
+          } else {
+            const uint32_t e0 = tag_here + (128u * j - (to_oldest != 0u && 128u * j >= to_oldest ? cap : 0u));
+            check(j, wave_here, held_here, first_here, slot_here + 128u * j + 2u * lane, slot_here + 128u * j + 128u <= held_here, e0, e0 + 1u);
+          }
+        }
+      } else if (!small_rings) {
+#pragma unroll
+        for (int j = 0; j < NR / 2; ++j) {
+          const uint32_t p0 = pbase + 128u * j, w = p0 >> cl2, slot = p0 & capm;
+          const uint32_t T = (uint32_t)__builtin_amdgcn_readlane((int)h_total, (int)(w & 15u));
+          const uint32_t V = w >= W ? 0u : T < cap ? T : cap, first = flush ? 0u : T - V;
+          if (rare(slot >= V)) {
+            set_round(j, 0xFFFFFFFFu, 0xFFFFFFFFu, kEmpty | (kEmpty << 8));
+          } else {
+            const uint32_t k0 = (slot - first + 2u * lane) & capm, base = (w << 20) + first;
+            check(j, w, V, first, slot + 2u * lane, slot + 128u <= V, base + k0, base + ((k0 + 1u) & capm));
+          }
+        }
+      } else {
+#pragma unroll
+        for (int j = 0; j < NR / 2; ++j) {
+          const uint32_t q = qe + 128u * j, s0 = q & capm, wv = q >> cl2, w = wv < KP_MAX_WAVES ? wv : KP_MAX_WAVES;  // (entry KP_MAX_WAVES: no records)
+          const uint2 vf = sVF[w];
+          const uint32_t k0 = (s0 - vf.y) & capm, base = vf.y + (w << 20);
+          check(j, w, vf.x, vf.y, s0, __builtin_amdgcn_ballot_w64(s0 + 1u >= vf.x) == 0ull, base + k0, base + ((k0 + 1u) & capm));
+        }
+      }
+      publish_ends();
+      if (__builtin_amdgcn_ballot_w64((c_bad | c_dis) != 0u)) {
+        if (c_bad) atomicAdd(&tmp[T_BAD], c_bad);
+        if (c_dis) atomicAdd(&tmp[T_DISORDER], c_dis);
+      }
     }
     team_sync<BLOCK>();
     if (stop_after == kStepOrdered) break;
 
-    // ---- a duplicated seq leaves fewer occupied ranks than valid records ---------------------------
-    // Records that all sit in the slot of their own seq have distinct seq modulo the ring size, hence
-    // distinct ranks: only a workgroup with a record elsewhere needs the count.
-    uint32_t n_occupied = tmp[T_FIELDVALID];
-    if (tmp[T_DISORDER] != 0u) {
-      uint32_t mw[NR / 4];
-      load_meta(tid, mw);
-      uint32_t occ = 0;
+    // ---- records outside the slot of their seq -----------------------------------------------------
+    wg_invalid = tmp[T_BAD];  // slots that hold a record and did not make it into the ordered sequence
+    if (rare(tmp[T_DISORDER] != 0u)) {
+      uint32_t left = 0;
 #pragma unroll
-      for (int i = 0; i < NR / 4; ++i)  // bytes whose region field is not the "no record" code
-        occ += __popc((((mw[i] & 0x3F3F3F3Fu) ^ 0x3F3F3F3Fu) + 0x7F7F7F7Fu) & 0x80808080u);
-      add_tmp(tmp, T_OCCUPIED, occ);
+      for (int j = 0; j < NR / 2; ++j) {
+        const uint32_t mine = (holes >> (2 * j)) & 3u;
+        if (__builtin_amdgcn_ballot_w64(mine != 0u) == 0ull) continue;
+        const uint32_t there = *reinterpret_cast<const uint16_t*>(meta + qe + 128u * j);
+        const uint2 tt = *reinterpret_cast<const uint2*>(clk + cwe + 136u * j);
+        const bool take0 = (mine & 1u) && (there & 0x3Fu) != kEmpty, take1 = (mine & 2u) && ((there >> 8) & 0x3Fu) != kEmpty;
+        left += __popc(mine) - (take0 ? 1u : 0u) - (take1 ? 1u : 0u);
+        if (take0) t[2 * j] = tt.x;
+        if (take1) t[2 * j + 1] = tt.y;
+        const uint32_t bytes = (take0 ? 0xFFu : 0u) | (take1 ? 0xFF00u : 0u);
+        mq[j >> 1] = (mq[j >> 1] & ~(bytes << (16 * (j & 1)))) | ((there & bytes) << (16 * (j & 1)));
+      }
+      publish_ends();
+      if (left) atomicAdd(&tmp[T_UNFILLED], left);
       team_sync<BLOCK>();
-      n_occupied = tmp[T_OCCUPIED];
-      if (n_occupied != tmp[T_FIELDVALID]) {
-        // Rare: some seq occurs twice.  The later slot must win, so redo this workgroup's
-        // scatter in slot order, one thread per wave.
+      wg_invalid = tmp[T_UNFILLED];
+      // Every slot without its own record holds a bad one or one that belongs elsewhere: as many places are left without a
+      // record as there are bad ones, unless some record found its place taken.
+      if (rare(wg_invalid != tmp[T_BAD])) {
+        // Rare: some seq occurs twice.  The later slot must win, so this workgroup's records are placed again in slot
+        // order, one thread per wave.
         team_sync<BLOCK>();
         clear_meta(tid);
-        if (tid == 0) { tmp[T_DISORDER] = 0; tmp[T_OCCUPIED] = 0; }
+        {
+          uint32_t ones[NR];
+#pragma unroll
+          for (int i = 0; i < NR; ++i) ones[i] = 0xFFFFFFFFu;
+          store_run<NR>(clk, tid, ones);
+        }
+        if (tid == 0) { tmp[T_DISORDER] = 0; tmp[T_UNFILLED] = tmp[T_HELD]; }
         team_sync<BLOCK>();
         if (tid < W) {
           const uint32_t w = tid, V = sVF[w].x, first = sVF[w].y;
           const uint32_t* seg = reinterpret_cast<const uint32_t*>(p.records) + ((size_t)wg * nrec + (size_t)w * cap) * 2;
           for (uint32_t s = 0; s < V; ++s) {
             const uint32_t tag = seg[2 * s];
-            const uint32_t seq = tag & kSeqMask, k = (seq - first) & kSeqMask, region = (tag >> 24) & 0x7Fu;
+            const uint32_t k = (tag - first) & kSeqMask, region = (tag >> 24) & 0x7Fu, at = w * cap + (tag & capm);
             if (k >= V || ((tag >> 20) & 0xFu) != w || region >= R) continue;
             // the clock word remembers the winning slot for now
-            clk[clk_word(w * cap + k)] = s;
-            meta[w * cap + k] = (uint8_t)(tag >> 24);
+            clk[clk_word(at)] = s;
+            meta[at] = (uint8_t)(tag >> 24);
           }
-          uint32_t dis = 0, occ2 = 0;
+          uint32_t dis = 0, occ = 0;
           for (uint32_t k = 0; k < V; ++k) {
-            if ((meta[w * cap + k] & kRegion) == kEmpty) continue;
-            const uint32_t s = clk[clk_word(w * cap + k)];
-            dis += (s != ((seg[2 * s] & kSeqMask) & capm));
-            clk[clk_word(w * cap + k)] = seg[2 * s + 1];
-            ++occ2;
+            const uint32_t at = w * cap + k;
+            if ((meta[at] & kRegion) == kEmpty) continue;
+            const uint32_t s = clk[clk_word(at)];
+            dis += s != k;
+            clk[clk_word(at)] = seg[2 * s + 1];
+            ++occ;
           }
           atomicAdd(&tmp[T_DISORDER], dis);
-          atomicAdd(&tmp[T_OCCUPIED], occ2);
+          atomicSub(&tmp[T_UNFILLED], occ);
         }
         team_sync<BLOCK>();
-        n_occupied = tmp[T_OCCUPIED];
+        wg_invalid = tmp[T_UNFILLED];
+#pragma unroll
+        for (int j = 0; j < NR / 2; ++j) {
+          const uint2 tt = *reinterpret_cast<const uint2*>(clk + cwe + 136u * j);
+          const uint32_t m2 = *reinterpret_cast<const uint16_t*>(meta + qe + 128u * j);
+          t[2 * j] = tt.x; t[2 * j + 1] = tt.y;
+          mq[j >> 1] = j & 1 ? (mq[j >> 1] & 0xFFFFu) | (m2 << 16) : m2;
+        }
+        publish_ends();
+        team_sync<BLOCK>();
       }
     }
-    // ---- this lane's NR positions: in round j the even position qe + 128 j and the one above it ---------
-    // (The arrays below are only ever assigned outside of branches: a conditional assignment makes the
-    // compiler carry each array through the branch as one value of NR registers, copied at every merge.)
-    uint32_t t[NR], mq[NR / 4];  // clocks; metadata bytes, record i in byte i & 3 of word i >> 2
-#pragma unroll
-    for (int j = 0; j < NR / 4; ++j) mq[j] = 0u;
-#pragma unroll
-    for (int j = 0; j < NR / 2; ++j) {
-      const uint2 tt = *reinterpret_cast<const uint2*>(clk + cwe + 136u * j);
-      t[2 * j] = tt.x; t[2 * j + 1] = tt.y;
-      // positions past the last record slot stay cleared
-      mq[j >> 1] |= (uint32_t)*reinterpret_cast<const uint16_t*>(meta + qe + 128u * j) << (16 * (j & 1));
-    }
+    const uint32_t n_occupied = tmp[T_HELD] - wg_invalid;
     auto meta_of = [&](int i) -> uint32_t { return (mq[i >> 2] >> (8 * (i & 3))) & 0xFFu; };
     auto set_paired = [&](int i, uint32_t yes) { mq[i >> 2] |= (yes << 6) << (8 * (i & 3)); };  // yes: 0 or 1
-    wg_invalid = tmp[T_HELD] - n_occupied;  // slots that hold a record and did not make it into the ordered sequence
 
     // One pair: duration into the per-(wave, region) sums and the histogram.  The sums exist in up to
     // four copies, one per quarter of the wave: lanes 16 apart tend to hold the same region, and LDS
     // atomics of one instruction that hit one address are processed one after the other.
     const uint32_t copy = (lane >> 4) & (n_copies - 1u);
     uint32_t shortest = 0xFFFFFFFFu;
-    auto account_pair = [&](uint32_t w, uint32_t region, uint32_t d_raw) {
+    auto account_row = [&](uint32_t row, uint32_t region, uint32_t d_raw) __attribute__((always_inline)) {  // row: wave * R
       shortest = d_raw < shortest ? d_raw : shortest;
       const uint32_t d = d_raw > rec_cost ? d_raw - rec_cost : 0u;
-      const uint32_t e = __umul24(__umul24(w, R) + region, n_copies) + copy;
+      const uint32_t e = __umul24(row + region, n_copies) + copy;
       atomicAdd(&pw_pack[e], (1ull << 46) | (unsigned long long)d);
       atomicMax(&pw_max[e], d);
       atomicMin(&pw_min[e], d);
       atomicAdd(&hist[__umul24(region, kHistStride) + (31 - __clz(d | 1u))], 1u);
     };
+    auto account_pair = [&](uint32_t w, uint32_t region, uint32_t d_raw) { account_row(__umul24(w, R), region, d_raw); };
 
-    if (wg_invalid == 0u) {
+    uint32_t deep = 0;  // bit i: place i holds an END that has to look further down than one rank
+    if (!rare(wg_invalid != 0u)) {
       // ---- B: pairing, durations, per-(wave,region) statistics, monotonicity ------------------------
-      // Every rank below a wave's record count holds a record here.  An END is paired iff the nearest
+      // Every slot that a wave's record count covers holds a record here.  An END is paired iff the nearest
       // earlier record of its (wave, region) is a START; every START that is not claimed this way is an
       // orphan, so only ENDs search.  In traces of kernels whose regions follow one another the START
       // sits one rank below: in the lane's own even position, or, for an END in the even position, in
-      // the odd position of the lane below (DPP; the last lane of the previous round stands in for lane
-      // 0).  Both positions of a round are tested at once on the two metadata bytes side by side.  An
-      // END whose lower neighbour belongs to another region walks back through LDS.
+      // the odd position of the lane below (DPP; lane 0 takes the last lane of the round before, or what the
+      // hardware wave or the end of the ring before it left in LDS).  Both positions of a round are tested at once on
+      // the two metadata bytes side by side.  An END whose lower neighbour belongs to another region looks further
+      // behind the barrier, where all records are in LDS.
       // A START learns that it is paired from its END: in the same lane directly, one lane up through a
-      // DPP shift of the claims, and when the END is in another hardware wave or found the START by
-      // walking, through a mark in the START's metadata byte that is read back after the barrier.
+      // DPP shift of the claims, and otherwise through a mark at its place in LDS that is read back after the barrier.
       uint32_t n_nonmono = 0;  // wave-uniform count
-      uint32_t claims = 0;
       bool marked = false;
-      uint32_t cm = kEmpty, ct = 0;
-      if (pbase > 0 && pbase < nrec) { cm = meta[pbase - 1]; ct = clk[clk_word(pbase - 1)]; }
       auto count = [](bool b) -> uint32_t { return (uint32_t)__popcll(__builtin_amdgcn_ballot_w64(b)); };
-      auto walk_back = [&](uint32_t qq, uint32_t mine, bool& have, uint32_t& sm, uint32_t& sq, uint32_t& sts) {
-        const uint32_t k = qq & capm, wofs = qq - k;
-        for (uint32_t kk = k - 1; kk-- > 0;) {
-          const uint32_t mm = meta[wofs + kk];
-          if (((mm ^ mine) & kRegion) == 0u) { have = true; sm = mm; sq = wofs + kk; sts = clk[clk_word(sq)]; break; }
-        }
-      };
+      uint2 below = wave_end[hw ? hw - 1u : 0u];
+      if (slot_here == 0u) below = ring_end[wave_here & 15u];
+      // Masks of rounds: those in which a ring begins (but for the first, whose record below is known), and those that may
+      // hold the oldest record of a ring.
+      uint32_t begins_in = 0u, oldest_in = 0u;
+      if (whole_rings) {
+        oldest_in = to_oldest < kWaveSpan ? 1u << (to_oldest >> 7) : 0u;
+      } else if (small_rings) {
+        begins_in = oldest_in = 0xFFFFFFFFu;
+      } else {
 #pragma unroll
-      for (int j = 0; j < NR / 2; ++j) {
-        const uint32_t q = qe + 128u * j;  // even position; the odd one is q + 1
-        const uint32_t m2 = (mq[j >> 1] >> (16 * (j & 1))) & 0xFFFFu;  // byte 0: even position, byte 1: odd
-        const uint32_t t0 = t[2 * j], t1 = t[2 * j + 1];
-        uint32_t pm = wave_shr1(m2 >> 8, cm);
-        const uint32_t pt = wave_shr1(t1, ct);
-        cm = (uint32_t)__builtin_amdgcn_readlane((int)m2, 63) >> 8;
-        ct = (uint32_t)__builtin_amdgcn_readlane((int)t1, 63);
-        const uint32_t k0 = q & capm;
-        const bool lowest = k0 == 0u;  // first rank of a recorded wave: no record below
-        pm = lowest ? kEmpty : pm;
-        const uint32_t p2 = ((m2 << 8) | pm) & 0xFFFFu;  // the record one rank below each of the two
-        const uint32_t x2 = m2 ^ p2;
-        // bit 7 of each of the two bytes: that byte of the argument is not zero
-        auto nonzero7 = [](uint32_t v) -> uint32_t { return ((v & 0x7F7Fu) + 0x7F7Fu) | v; };
-        const uint32_t end2 = m2 & 0x8080u;                                   // is an END (no record: 0)
-        const uint32_t differ2 = nonzero7(x2 & 0x3F3Fu) & end2;               // END, other region one rank below
-        const uint32_t near2 = ~nonzero7((x2 & 0xBFBFu) ^ 0x8080u) & end2;    // END, START of its region one rank below
-        bool p0 = (near2 & 0x80u) != 0u, p1 = (near2 & 0x8000u) != 0u;
-        uint32_t st0 = pt, st1 = t0;  // clock of the START
-        // (a position without a record holds the largest clock, and so do all above it in its wave)
-        n_nonmono += count(!lowest && t0 < pt) + count(t1 < t0);
-        // as END, or as the START of the odd position; the mark of an END sits one bit above its flag
-        uint32_t flags = (near2 >> 1) | ((near2 >> 9) & kPaired);
-        claims |= (p0 ? 1u : 0u) << j;
-        if (j == 0 && p0 && lane == 0u && pbase > 0) meta[pbase - 1] = (uint8_t)(pm | kPaired);
-        if (__builtin_amdgcn_ballot_w64(differ2 != 0u)) {
-          const uint32_t m0 = m2 & 0xFFu, m1 = m2 >> 8;
-          const bool deep0 = (differ2 & 0x80u) && k0 > 1, deep1 = (differ2 & 0x8000u) && k0 > 0;
-          bool have0 = false, have1 = false;
-          uint32_t sm0 = 0, sm1 = 0, sq0 = 0, sq1 = 0;
-          if (deep0) walk_back(q, m0, have0, sm0, sq0, st0);
-          if (deep1) walk_back(q + 1, m1, have1, sm1, sq1, st1);
-          const bool far0 = have0 && !(sm0 & kEnd), far1 = have1 && !(sm1 & kEnd);
-          if (far0) meta[sq0] = (uint8_t)(sm0 | kPaired);
-          if (far1) meta[sq1] = (uint8_t)(sm1 | kPaired);
-          flags |= (far0 ? kPaired : 0u) | (far1 ? kPaired << 8 : 0u);
-          marked = marked || far0 || far1;
-          p0 = p0 || far0; p1 = p1 || far1;
-        }
-        mq[j >> 1] |= flags << (16 * (j & 1));
-        const uint32_t w = q >> cl2;
-        if (p0 || p1) account_pair(w, (p1 ? m2 >> 8 : m2) & kRegion, p1 ? t1 - st1 : t0 - st0);
-        const bool both = p0 && p1;
-        if (__builtin_amdgcn_ballot_w64(both)) {
-          if (both) account_pair(w, m2 & kRegion, t0 - st0);
+        for (int j = 0; j < NR / 2; ++j) {
+          const uint32_t p0 = pbase + 128u * j, T = (uint32_t)__builtin_amdgcn_readlane((int)h_total, (int)((p0 >> cl2) & 15u));
+          const uint32_t rot = flush || T < cap ? 0u : T & capm;  // (first surviving seq modulo capacity: T - capacity)
+          begins_in |= j != 0 && (p0 & capm) == 0u ? 1u << j : 0u;
+          oldest_in |= rot - (p0 & capm) < 128u ? 1u << j : 0u;
         }
       }
-      // the START claimed by the even position of the lane above (lane 63: of lane 0 in the next round)
-      const uint32_t claims0 = (uint32_t)__builtin_amdgcn_readlane((int)claims, 0);
+      uint32_t odd_before = below.y << 16;  // the odd positions' metadata of the two rounds before: lane 63's are the ones below lane 0
 #pragma unroll
-      for (int j = 0; j < NR / 2; ++j) {
-        const uint32_t next_round = j + 1 < NR / 2 ? (claims0 >> (j + 1)) & 1u : 0u;
-        const uint32_t got = (uint32_t)__builtin_amdgcn_update_dpp((int)next_round, (int)((claims >> j) & 1u), 0x130, 0xF, 0xF,
-                                                                   false);  // wave_shl:1
-        set_paired(2 * j + 1, got);
+      for (int x = 0; x < NR / 4; ++x) {
+        // Rounds 2 x and 2 x + 1 side by side: bytes 0 and 1 the even and the odd position of the first, 2 and 3 of the second.
+        const uint32_t m4 = mq[x], odd = (m4 >> 8) & 0x00FF00FFu;
+        const uint32_t edge = __builtin_amdgcn_alignbit(odd, odd_before, 16);
+        const uint32_t pm = wave_shr1(odd, x == 0 ? (odd_before >> 16) | (wave_ror1(odd) << 16) : wave_ror1(edge));
+        odd_before = odd;
+        uint32_t p4 = ((m4 << 8) & 0xFF00FF00u) | pm;  // the record one rank below each of the four
+        uint32_t pt[2], own_t[2];                      // the clock one rank below the even position, the odd position
+        uint32_t search = 0x80808080u;                 // bits of the positions that may have to look further down
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+          const int j = 2 * x + h;
+          pt[h] = wave_shr1(t[2 * j + 1], j == 0 ? below.x : wave_ror1(t[j == 0 ? 0 : 2 * j - 1]));
+          own_t[h] = t[2 * j];
+          if (seldom((begins_in >> j) & 1u)) {  // the record below the first slot of a ring is the one in its last
+            const uint32_t q = qe + 128u * j, w = q >> cl2;
+            const uint2 e = ring_end[w & 15u];
+            if ((q & capm) == 0u) {
+              pt[h] = e.x;
+              p4 = (p4 & ~(0xFFu << (16 * h))) | (e.y << (16 * h));
+            }
+          }
+          if (seldom((oldest_in >> j) & 1u)) {  // nothing below rank 0, nothing to look for below rank 1
+            const uint32_t q = qe + 128u * j, s0 = q & capm, wv = q >> cl2, w = wv < KP_MAX_WAVES ? wv : KP_MAX_WAVES;
+            const uint32_t rot = sVF[w].y & capm;
+            const bool lowest0 = s0 == rot, lowest1 = s0 + 1u == rot;
+            p4 |= (lowest0 ? kEmpty << (16 * h) : 0u) | (lowest1 ? kEmpty << (16 * h + 8) : 0u);  // (region 63)
+            pt[h] = lowest0 ? 0u : pt[h];
+            own_t[h] = lowest1 ? 0u : own_t[h];
+            search &= ~((lowest0 || s0 == ((rot + 1u) & capm) ? 0x80u << (16 * h) : 0u) | (lowest1 || lowest0 ? 0x8000u << (16 * h) : 0u));
+          }
+          // (a position without a record holds the largest clock, and so do all above it in its wave)
+          n_nonmono += count(t[2 * j] < pt[h]) + count(t[2 * j + 1] < own_t[h]);
+          asm volatile("" : "+s"(n_nonmono));  // (counted here: kept for later the two masks would be parked in vector registers)
+        }
+        const uint32_t x4 = m4 ^ p4;
+        // bit 7 of each byte: that byte of the argument is not zero
+        auto nonzero7 = [](uint32_t v) -> uint32_t { return ((v & 0x7F7F7F7Fu) + 0x7F7F7F7Fu) | v; };
+        const uint32_t end4 = m4 & 0x80808080u;                                   // is an END (no record: 0)
+        const uint32_t differ4 = nonzero7(x4 & 0x3F3F3F3Fu) & end4 & search;      // END, other region one rank below
+        const uint32_t near4 = ~nonzero7((x4 & 0xBFBFBFBFu) ^ 0x80808080u) & end4;  // END, START of its region one rank below
+        // as END, or as the START of the odd position; the mark of an END sits one bit above its flag
+        mq[x] = m4 | (near4 >> 1) | ((near4 >> 9) & 0x00400040u);
+        if (rare(__builtin_amdgcn_ballot_w64(differ4 != 0u) != 0ull))
+          deep |= (((differ4 >> 7) & 1u) | ((differ4 >> 14) & 2u) | ((differ4 >> 21) & 4u) | ((differ4 >> 28) & 8u)) << (4 * x);
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+          const int j = 2 * x + h;
+          const uint32_t q = qe + 128u * j;  // even position; the odd one is q + 1
+          const bool e0 = (near4 & (0x80u << (16 * h))) != 0u, e1 = (near4 & (0x8000u << (16 * h))) != 0u;
+          // a START that is not in the lane below: in the last place of a hardware wave, or of a ring
+          if (j == 0 && !small_rings) {
+            if (e0 && lane == 0u) { meta[slot_here == 0u ? q + capm : q - 1u] = (uint8_t)kPaired; marked = !whole_rings; }
+          } else if (seldom((begins_in >> j) & 1u)) {
+            if (e0 && (q & capm) == 0u) { meta[q + capm] = (uint8_t)kPaired; marked = true; }
+          }
+          uint32_t row = ((pbase + 128u * j) >> cl2) * R;
+          if (rare(small_rings)) row = (uint32_t)__builtin_amdgcn_ds_bpermute((int)(lane << 2), (int)(__umul24(q >> cl2, R)));  // (its own: kept out of the straight line)
+          const uint32_t m0 = (m4 >> (16 * h)) & kRegion, m1 = (m4 >> (16 * h + 8)) & kRegion;
+          const uint32_t d0 = t[2 * j] - pt[h], d1 = t[2 * j + 1] - t[2 * j];
+          if (e0 || e1) account_row(row, e1 ? m1 : m0, e1 ? d1 : d0);
+          if (rare(e0 && e1)) account_row(row, m0, d0);
+        }
+      }
+      // A START in an odd position that the even position of the lane above claimed (lane 63: that of lane 0 in the next
+      // round): the END there carries both flags.  Two rounds at a time.
+      uint32_t claim[NR / 4 + 1];  // bits 7 and 23: the even position's END is paired
+#pragma unroll
+      for (int x = 0; x < NR / 4; ++x) {
+        claim[x] = mq[x] & (mq[x] << 1) & 0x00800080u;
+        if (seldom(begins_in != 0u))  // (where a ring begins the START is elsewhere)
+          claim[x] &= (((qe + 256u * x) & capm) ? 0x80u : 0u) | (((qe + 256u * x + 128u) & capm) ? 0x800000u : 0u);
+      }
+      claim[NR / 4] = 0u;
+#pragma unroll
+      for (int x = 0; x < NR / 4; ++x) {
+        const uint32_t now = (uint32_t)__builtin_amdgcn_readlane((int)claim[x], 0), next = (uint32_t)__builtin_amdgcn_readlane((int)claim[x + 1], 0);
+        const uint32_t above = (uint32_t)__builtin_amdgcn_update_dpp((int)((now >> 16) | (next << 16)), (int)claim[x], 0x130, 0xF, 0xF,
+                                                                     false);  // wave_shl:1
+        mq[x] |= above << 7;
       }
       // ENDs, and ENDs that are paired (the flag sits one bit below): counted on the packed bytes
       uint32_t n_ends = 0, n_pairs = 0;
@@ -675,8 +811,10 @@ __global__ __launch_bounds__(BLOCK * TEAMS, (Lds<BLOCK, NR, TEAMS, RMAX, PERWAVE
       }
       n_pairs = wave_scan_add(n_ends | (n_pairs << 16));  // both at most 1024 per wave
       const bool any_marked = __builtin_amdgcn_ballot_w64(marked) != 0, any_zero = __builtin_amdgcn_ballot_w64(shortest == 0u) != 0;
+      const bool any_deep = __builtin_amdgcn_ballot_w64(deep != 0u) != 0;
       if (lane == 0u) {
         if (any_marked) tmp[T_MARKS] = 1u;
+        if (any_deep) tmp[T_DEEP] = 1u;
         if (any_zero) tmp[T_ZERO] = 1u;
         if (n_nonmono) atomicAdd(&tmp[T_NONMONO], n_nonmono);
       }
@@ -685,42 +823,101 @@ __global__ __launch_bounds__(BLOCK * TEAMS, (Lds<BLOCK, NR, TEAMS, RMAX, PERWAVE
         atomicAdd(&tmp[T_ENDS], n_pairs & 0xFFFFu);
       }
       if (tid == 0) tmp[T_STARTS] = n_occupied;  // records; orphans = records - ENDs - pairs, ENDs - pairs
-    } else {
-      // ---- B, workgroup with holes: the definition, one thread per (wave, region) -----------------
-      for (uint32_t e = tid; e < W * R; e += BLOCK) {
-        const uint32_t w = e / R, r = e - w * R, V = sVF[w].x;
-        bool have_prev = false;
-        uint32_t prev_m = 0, prev_t = 0, n_pairs = 0, n_starts = 0, n_ends = 0;
-        for (uint32_t k = 0; k < V; ++k) {
-          const uint32_t mm = meta[w * cap + k];
-          if ((mm & kRegion) != r) continue;
-          const uint32_t ts = clk[clk_word(w * cap + k)];
-          if (mm & kEnd) {
-            ++n_ends;
-            if (have_prev && !(prev_m & kEnd)) { ++n_pairs; account_pair(w, r, ts - prev_t); }
-          } else {
-            ++n_starts;
-          }
-          have_prev = true; prev_m = mm; prev_t = ts;
-        }
-        if (n_pairs) atomicAdd(&tmp[T_PAIRS], n_pairs);
-        if (n_starts + n_ends) atomicAdd(&tmp[T_STARTS], n_starts + n_ends);
-        if (n_ends) atomicAdd(&tmp[T_ENDS], n_ends);
-      }
-      for (uint32_t w = tid; w < W; w += BLOCK) {
-        const uint32_t V = sVF[w].x;
-        bool have_prev = false;
-        uint32_t prev_t = 0, n = 0;
-        for (uint32_t k = 0; k < V; ++k) {
-          if ((meta[w * cap + k] & kRegion) == kEmpty) continue;
-          const uint32_t ts = clk[clk_word(w * cap + k)];
-          n += (have_prev && ts < prev_t) ? 1u : 0u;
-          have_prev = true; prev_t = ts;
-        }
-        if (n) atomicAdd(&tmp[T_NONMONO], n);
-      }
     }
     team_sync<BLOCK>();
+    // marks left by ENDs of other hardware waves (only the last position can have one) and at the ends of short rings
+    auto read_marks = [&]() __attribute__((always_inline)) {
+#pragma unroll
+      for (int j = 0; j < NR / 2; ++j)
+        mq[j >> 1] |= ((uint32_t)*reinterpret_cast<const uint16_t*>(meta + qe + 128u * j) & 0x4040u) << (16 * (j & 1));
+    };
+    if (wg_invalid == 0u) {
+      set_paired(NR - 1, ((uint32_t)meta[qe + 128u * (NR / 2 - 1) + 1u] >> 6) & 1u);
+      if (rare(tmp[T_MARKS] != 0u)) read_marks();
+    }
+    if (rare(wg_invalid != 0u || tmp[T_DEEP] != 0u || tmp[T_ZERO] != 0u)) {
+      // Whoever looks further than one rank needs the other lanes' records: all of them to LDS, each at its position.
+#pragma unroll
+      for (int j = 0; j < NR / 2; ++j) {
+        *reinterpret_cast<uint2*>(clk + cwe + 136u * j) = make_uint2(t[2 * j], t[2 * j + 1]);
+        *reinterpret_cast<uint16_t*>(meta + qe + 128u * j) = (uint16_t)(mq[j >> 1] >> (16 * (j & 1)));
+      }
+      team_sync<BLOCK>();
+      if (wg_invalid != 0u) {
+        // ---- B, workgroup with holes: the definition, one thread per (wave, region) -----------------
+        for (uint32_t e = tid; e < W * R; e += BLOCK) {
+          const uint32_t w = e / R, r = e - w * R, V = sVF[w].x, first = sVF[w].y;
+          bool have_prev = false;
+          uint32_t prev_m = 0, prev_t = 0, n_pairs = 0, n_starts = 0, n_ends = 0;
+          for (uint32_t k = 0; k < V; ++k) {
+            const uint32_t at = w * cap + ((first + k) & capm), mm = meta[at];
+            if ((mm & kRegion) != r) continue;
+            const uint32_t ts = clk[clk_word(at)];
+            if (mm & kEnd) {
+              ++n_ends;
+              if (have_prev && !(prev_m & kEnd)) { ++n_pairs; account_pair(w, r, ts - prev_t); }
+            } else {
+              ++n_starts;
+            }
+            have_prev = true; prev_m = mm; prev_t = ts;
+          }
+          if (n_pairs) atomicAdd(&tmp[T_PAIRS], n_pairs);
+          if (n_starts + n_ends) atomicAdd(&tmp[T_STARTS], n_starts + n_ends);
+          if (n_ends) atomicAdd(&tmp[T_ENDS], n_ends);
+        }
+        for (uint32_t w = tid; w < W; w += BLOCK) {
+          const uint32_t V = sVF[w].x, first = sVF[w].y;
+          bool have_prev = false;
+          uint32_t prev_t = 0, n = 0;
+          for (uint32_t k = 0; k < V; ++k) {
+            const uint32_t at = w * cap + ((first + k) & capm);
+            if ((meta[at] & kRegion) == kEmpty) continue;
+            const uint32_t ts = clk[clk_word(at)];
+            n += (have_prev && ts < prev_t) ? 1u : 0u;
+            have_prev = true; prev_t = ts;
+          }
+          if (n) atomicAdd(&tmp[T_NONMONO], n);
+        }
+        team_sync<BLOCK>();
+      } else if (tmp[T_DEEP] != 0u) {
+        // ---- B, regions inside regions: down the ranks to the nearest record of the END's region -----
+        // (each lane takes its ENDs one after the other, four ranks at a step.  All lanes' END of one place at a time, rank by
+        // rank: 512 turns of nested regions, three deep, 8 x 2048 records 409 us, 500 of 8 x 512 78.0.)
+        shortest = 0xFFFFFFFFu;
+        uint32_t found = 0;
+        while (deep != 0u) {
+          const uint32_t i = (uint32_t)__builtin_ctz(deep);
+          deep &= deep - 1u;
+          const uint32_t q = qe + 128u * (i >> 1) + (i & 1u), base = q & ~capm, mine = meta[q], row = __umul24(q >> cl2, R);
+          uint32_t s = q & capm;  // the slots looked at next lie below this one (a ring of two has none)
+          for (uint32_t left = (s - sVF[(q >> cl2) & 15u].y) & capm; left != 0u;) {
+            s = s ? s : cap;
+            const uint32_t lo = (s - 1u) & ~3u, n = s - lo, four = *reinterpret_cast<const uint32_t*>(meta + base + lo);
+            // bit 7 of each byte that names the region; bytes from the n-th on and those older than the oldest record do not count
+            const uint32_t other = (four ^ (mine * 0x01010101u)) & 0x3F3F3F3Fu;
+            uint32_t same = ~(other + 0x7F7F7F7Fu) & (0x80808080u >> (32u - 8u * n));
+            if (left < n) same &= 0xFFFFFFFFu << (8u * (n - left));
+            if (same != 0u) {
+              const uint32_t b = (31u - (uint32_t)__builtin_clz(same)) >> 3, at = base + lo + b, mm = (four >> (8u * b)) & 0xFFu;
+              if (!(mm & kEnd)) {
+                meta[at] = (uint8_t)(mm | kPaired);
+                account_row(row, mine & kRegion, clk[clk_word(q)] - clk[clk_word(at)]);
+                found |= 1u << i;
+              }
+              break;
+            }
+            left = left > n ? left - n : 0u;
+            s = lo;
+          }
+        }
+#pragma unroll
+        for (int i = 0; i < NR; ++i) set_paired(i, (found >> i) & 1u);
+        if (found) atomicAdd(&tmp[T_PAIRS], (uint32_t)__popc(found));
+        if (shortest == 0u) tmp[T_ZERO] = 1u;
+        team_sync<BLOCK>();
+        read_marks();
+      }
+    }
 #pragma unroll
     for (int i = 0; i < NR; ++i) asm volatile("" : "+v"(t[i]));  // (opaque across the barrier, see below)
 #pragma unroll
@@ -729,45 +926,39 @@ __global__ __launch_bounds__(BLOCK * TEAMS, (Lds<BLOCK, NR, TEAMS, RMAX, PERWAVE
 
     if (eligible && stop_after != kStepPaired) {
       // ---- C: order the paired records of all waves by clock ---------------------------------------
-      // marks left by ENDs of other hardware waves (only the last position can have one) and by walks
-      set_paired(NR - 1, ((uint32_t)meta[qe + 128u * (NR / 2 - 1) + 1u] >> 6) & 1u);
-      if (tmp[T_MARKS]) {
-#pragma unroll
-        for (int j = 0; j < NR / 2; ++j)
-          mq[j >> 1] |= ((uint32_t)*reinterpret_cast<const uint16_t*>(meta + qe + 128u * j) & 0x4040u) << (16 * (j & 1));
-      }
       // A pair of length 0 overlaps nothing, and records of one clock come out of the counting sort in any order: its END
       // could open the region, in the general sweep, to every record of the same clock until its START.  Neither is an
       // event.  (The record a START is paired with is the next one of its region; the clocks of a wave do not fall here,
       // so that every record between the two has their clock: another one ends the search.  256 workgroups of 2 x 2048
       // records of 17 regions, half of them in any order: 295 us going to the partner every time, 244 this way.)
-      if (tmp[T_ZERO]) {
+      if (rare(tmp[T_ZERO] != 0u)) {
 #pragma unroll
         for (int i = 0; i < NR; ++i) {
           const uint32_t m = meta_of(i);
           if (m & kPaired) {
-            const uint32_t step = m & kEnd ? ~0u : 1u;
-            uint32_t q = qe + 128u * (i >> 1) + (i & 1) + step;
-            while (clk[clk_word(q)] == t[i] && ((meta[q] ^ m) & kRegion) != 0u) q += step;
+            const uint32_t step = m & kEnd ? ~0u : 1u, q0 = qe + 128u * (i >> 1) + (i & 1), base = q0 & ~capm;
+            uint32_t q = base + ((q0 + step) & capm);
+            while (clk[clk_word(q)] == t[i] && ((meta[q] ^ m) & kRegion) != 0u) q = base + ((q + step) & capm);
             if (clk[clk_word(q)] == t[i]) mq[i >> 2] ^= kPaired << (8 * (i & 3));
           }
         }
       }
-      const uint32_t scale = misc[1];
+      const float scale = __builtin_bit_cast(float, misc[1]);
       // Straight-line code from here to the sorted sequence: the LDS operations of a lane's 16 records
       // are issued together and no array is assigned inside a branch.
-      uint32_t ca[NR];  // cell | arrival slot << 16; then: first place of the cell; then: place in the sorted sequence
+      uint32_t ca[NR];  // 16 * cell + a fraction, below 16 * NCELL | arrival slot << kSlotShift
+      static_assert(NCELL * 16u == 1u << kSlotShift && L::npos <= 1u << (32u - kSlotShift), "cell and slot in one word");
       uint32_t t_max = 0;
 #pragma unroll
       for (int i = 0; i < NR; ++i) {
-        const bool ev = (meta_of(i) & kPaired) != 0u;
-        t_max = ev && t[i] > t_max ? t[i] : t_max;
-        uint32_t c = __umulhi(t[i], scale);
-        c = c < NCELL - 1 ? c : NCELL - 1;
-        const uint32_t sh = (c & 1u) << 4;
-        // a record that is no event adds nothing, so that all 16 atomics are in flight together
-        const uint32_t old = atomicAdd(&cells[c >> 1], ev ? 1u << sh : 0u);
-        ca[i] = c | (((old >> sh) & 0xFFFFu) << 16);
+        const uint32_t te = meta_of(i) & kPaired ? t[i] : 0u;  // (a record that is no event adds nothing, so that all atomics are in flight together)
+        t_max = te > t_max ? te : t_max;
+        // (a conversion, a product and a conversion that never fall: the cells follow one another in time)
+        const float at = (float)te * scale;
+        const uint32_t y = (uint32_t)(at < (float)(NCELL * 16u - 1u) ? at : (float)(NCELL * 16u - 1u));
+        const uint32_t sh = y & 16u;  // cell c: half (c & 1) of word c >> 1
+        const uint32_t old = atomicAdd(&cells[y >> 5], ((mq[i >> 2] >> (8 * (i & 3) + 6)) & 1u) << sh);
+        ca[i] = y | (((old >> sh) & 0xFFFFu) << kSlotShift);
       }
       if (__builtin_amdgcn_ballot_w64(t_max > misc[2]) && lane == 0u) tmp[T_WIDE] = 1u;  // a clock past the span
       team_sync<BLOCK>();
@@ -822,19 +1013,36 @@ __global__ __launch_bounds__(BLOCK * TEAMS, (Lds<BLOCK, NR, TEAMS, RMAX, PERWAVE
 #pragma unroll
       for (int i = 0; i < NR / 4; ++i) asm volatile("" : "+v"(mq[i]));
       auto cell_start = [&](uint32_t c) -> uint32_t { return (cells[c >> 1] >> ((c & 1u) << 4)) & 0xFFFFu; };
-      // sorted sequence entry besides the clock: region << 1 | END
-      auto info_of = [&](int i) -> uint32_t { return ((meta_of(i) & 0x1Fu) << 1) | (meta_of(i) >> 7); };
+      // sorted sequence entry besides the clock: END << 5 | region (four at a time)
+      uint32_t info[NR / 4];
+#pragma unroll
+      for (int x = 0; x < NR / 4; ++x) info[x] = (mq[x] & 0x1F1F1F1Fu) | ((mq[x] >> 2) & 0x20202020u);
+      auto info_of = [&](int i) -> uint32_t { return (info[i >> 2] >> (8 * (i & 3))) & 0x3Fu; };
       // When clock and region fit one word and no cell holds more than kMaxCellWindow records, the records stay
       // in arrival order inside their cell here and every lane of the sweep sorts a window of the sequence
       // in registers; otherwise the records are ranked inside their cell first.
       const bool window_sort = R <= 16u && misc[2] < (1u << 26) && !tmp[T_WIDE] && tmp[T_MAXCELL] <= kMaxCellWindow;
-      if (window_sort) {
+      if (!rare(!window_sort)) {
+        // the word the sweep sorts: clock << 6 | END << 5 | region (no branch: what is no event writes one unused word)
+        // (opaque here: what both ways compute from these would otherwise be computed ahead of the choice between them)
 #pragma unroll
-        for (int i = 0; i < NR; ++i) {
-          const bool ev = (meta_of(i) & kPaired) != 0u;
-          const uint32_t g = cell_start(ca[i] & 0xFFFFu) + (ca[i] >> 16);
-          // the word the sweep sorts: clock << 6 | region << 1 | END (no branch: the others all write one unused word)
-          clk[ev ? clk_word(g) : kSpareWord] = (t[i] << 6) | info_of(i);
+        for (int i = 0; i < NR; ++i) asm volatile("" : "+v"(ca[i]));
+#pragma unroll
+        for (int i = 0; i < NR / 4; ++i) asm volatile("" : "+v"(mq[i]), "+v"(info[i]));
+        constexpr int kTogether = NR < 16 ? NR : 16;
+#pragma unroll
+        for (int i0 = 0; i0 < NR; i0 += kTogether) {
+          uint32_t to[kTogether];
+#pragma unroll
+          for (int i = 0; i < kTogether; ++i) {
+            const uint32_t y = ca[i0 + i] & ((1u << kSlotShift) - 1u);
+            to[i] = clk_word(((cells[y >> 5] >> (y & 16u)) & 0xFFFFu) + (ca[i0 + i] >> kSlotShift));
+          }
+#pragma unroll
+          for (int i = 0; i < kTogether; ++i) {
+            asm volatile("" : "+v"(to[i]));  // (ahead of the choice: the compiler would make a branch of it)
+            clk[meta_of(i0 + i) & kPaired ? to[i] : kSpareWord] = (t[i0 + i] << 6) | info_of(i0 + i);
+          }
         }
         team_sync<BLOCK>();
         if (stop_after >= kStepPlaced && stop_after <= kStepSorted) break;
@@ -845,7 +1053,7 @@ __global__ __launch_bounds__(BLOCK * TEAMS, (Lds<BLOCK, NR, TEAMS, RMAX, PERWAVE
 #pragma unroll
       for (int i = 0; i < NR; ++i) {
         const uint32_t ev = 0u - ((meta_of(i) >> 6) & 1u);  // all ones for an event
-        const uint32_t c = ca[i] & 0xFFFFu, mine = ca[i] >> 16;
+        const uint32_t c = (ca[i] & ((1u << kSlotShift) - 1u)) >> 4, mine = ca[i] >> kSlotShift;
         const uint32_t s0 = cell_start(c), s1 = cell_start(c + 1);
         clk[ev ? s0 + mine : kSpareWord] = t[i];  // no branch: the others all write one unused word
         ca[i] = s0;
@@ -967,21 +1175,51 @@ __global__ __launch_bounds__(BLOCK * TEAMS, (Lds<BLOCK, NR, TEAMS, RMAX, PERWAVE
             }
           }
         };
-        if (window_sort) {
+        if (!rare(!window_sort)) {
           // ---- the order is finished in registers; one word per record from here on ------------------
           uint32_t key[NR];
           const uint32_t fake = (misc[2] << 6) | 0x3Fu;
-          if (tmp[T_MAXCELL] <= NR / 2 + 1u) sorted_own<BLOCK, NR>(clk, tid, n_events, fake, key);
+          if (!rare(tmp[T_MAXCELL] > NR / 2 + 1u)) sorted_own<BLOCK, NR>(clk, tid, n_events, fake, key);
           else sorted_pairs<BLOCK, NR>(clk, tid, n_events, fake, key);
+          if constexpr (PLANES == 4) {
+            // Counts up to 15 of 16 regions are one number of 64 bits, four to each.  A sum of such numbers is right in every
+            // digit as long as the counts it stands for are, whatever it took and gave on the way: so the state before a
+            // lane's stretch is a prefix sum of integers, and becomes planes at the end.
+            uint64_t net = 0;
 #pragma unroll
-          for (int i = 0; i < NR; ++i) planes_step<PLANES>(pl, key_region_bit(key[i]), key_end_mask(key[i]));
-          state_before(key_clock(key[0]));
+            for (int i = 0; i < NR; ++i) net += (uint64_t)((int64_t)(int32_t)(key_end_mask(key[i]) | 1u) << ((4u * key[i]) & 63u));
+            if (__builtin_amdgcn_ballot_w64(g0 + NR > n_events)) {  // a place past the end counted as an END of region 15
+              const uint32_t past = g0 + NR > n_events ? (g0 > n_events ? (uint32_t)NR : g0 + NR - n_events) : 0u;
+              net += (uint64_t)past << 60;
+            }
+            uint64_t incl = net;
+            incl += scan_src64<0>(incl); incl += scan_src64<1>(incl); incl += scan_src64<2>(incl);
+            incl += scan_src64<3>(incl); incl += scan_src64<4>(incl); incl += scan_src64<5>(incl);
+            uint64_t* wave_net = reinterpret_cast<uint64_t*>(ptot);
+            if (lane == 63u) wave_net[hw] = incl;
+            if (lane == 0u) wtot[hw] = key_clock(key[0]);
+            team_sync<BLOCK>();
+            uint64_t state = incl - net;
+            if (hw > 0u) {  // lane h of a row takes wave h's net change; a scan over the row, then the entry of wave hw - 1
+              uint64_t sum = wave_net[lane & 15u];
+              sum += scan_src64<0>(sum); sum += scan_src64<1>(sum); sum += scan_src64<2>(sum); sum += scan_src64<3>(sum);
+              state += (uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)sum, (int)(hw - 1u)) |
+                       ((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(sum >> 32), (int)(hw - 1u)) << 32);
+            }
+            const uint32_t lo = planes_of_nibbles((uint32_t)state), hi = planes_of_nibbles((uint32_t)(state >> 32));
+#pragma unroll
+            for (int k = 0; k < 4; ++k) pl[k] = __builtin_amdgcn_perm(hi, lo, 0x0C0C0400u + 0x0101u * k);
+          } else {
+#pragma unroll
+            for (int i = 0; i < NR; ++i) planes_step<PLANES>(pl, key_region_bit(key[i]), key_end_mask(key[i]));
+            state_before(key_clock(key[0]));
+          }
 #pragma unroll
           for (int i = 0; i < NR; ++i) asm volatile("" : "+v"(key[i]));  // (opaque across the barrier, as above)
           // ---- the sorted sequence as segments: the set of active regions after record k and the ticks
           // until record k + 1.  O[a][b] = sum over segments of ticks * active(a) * active(b) is a 16 x K by
           // K x 16 matrix product: the matrix cores take it 64 segments at a time (i8 operands: the ticks in
-          // 7-bit limbs, one product per limb), and no accumulator atomics are left in the sweep.
+          // signed digits of base 256, one product per digit), and no accumulator atomics are left in the sweep.
           // clock of the record after the lane's 16: the first one of the lane above
           const uint32_t t_above = hw + 1 < BLOCK / 64 ? wtot[hw + 1 < BLOCK / 64 ? hw + 1 : hw] : misc[2];
           const uint32_t t_next = (uint32_t)__builtin_amdgcn_update_dpp((int)t_above, (int)key_clock(key[0]), 0x130, 0xF, 0xF, false);  // wave_shl:1
@@ -1000,31 +1238,36 @@ __global__ __launch_bounds__(BLOCK * TEAMS, (Lds<BLOCK, NR, TEAMS, RMAX, PERWAVE
             f |= scan_src<3>(f); f |= scan_src<4>(f); f |= scan_src<5>(f);
             any_len = (uint32_t)__builtin_amdgcn_readlane((int)f, 63);
           }
-          if (any_len < (1u << 21)) {  // else: a gap of more than three limbs, the general way takes this wave
-            const uint32_t n_limbs = any_len < (1u << 7) ? 1u : (any_len < (1u << 14) ? 2u : 3u);
+          if (!rare(any_len >= 0x7F7F80u)) {  // else: a gap of more than three digits, the general way takes this wave
+            const uint32_t n_digits = any_len < 0x80u ? 1u : (any_len < 0x7F80u ? 2u : 3u);
             // The lane's own places of the sequence are free now (every neighbour read them before the last
-            // barrier): they take the active sets (16 bits each) and two limbs, its metadata bytes the third limb.
+            // barrier): they take the active sets (16 bits each) and two digits, its metadata bytes the third one.
             uint32_t* own = clk + clk_word(g0);
-            auto limb_words = [&](int shift, uint32_t (&l)[NR / 4]) __attribute__((always_inline)) {
+            // (digit k of a length, from -128 to 127: byte k of length + 0x808080, less 0x80)
 #pragma unroll
-              for (int i = 0; i < NR / 4; ++i) l[i] = 0u;
+            for (int i = 0; i < NR; ++i) len[i] += 0x808080u;
+            auto digit_words = [&](uint32_t k, uint32_t (&l)[NR / 4]) __attribute__((always_inline)) {
 #pragma unroll
-              for (int i = 0; i < NR; ++i) l[i >> 2] |= ((len[i] >> shift) & 0x7Fu) << (8 * (i & 3));
+              for (int i = 0; i < NR / 4; ++i) {
+                const uint32_t a = __builtin_amdgcn_perm(len[4 * i + 1], len[4 * i], 0x0C0C0400u + 0x0101u * k);
+                const uint32_t b = __builtin_amdgcn_perm(len[4 * i + 3], len[4 * i + 2], 0x0C0C0400u + 0x0101u * k);
+                l[i] = __builtin_amdgcn_perm(b, a, 0x05040100u) ^ 0x80808080u;
+              }
             };
             uint32_t l0[NR / 4], l1[NR / 4];
-            limb_words(0, l0);
+            digit_words(0, l0);
             if constexpr (NR == 16) {
               reinterpret_cast<u32x4*>(own)[2] = u32x4{l0[0], l0[1], l0[2], l0[3]};
-              if (n_limbs > 1u) {
-                limb_words(7, l1);
+              if (n_digits > 1u) {
+                digit_words(1, l1);
                 reinterpret_cast<u32x4*>(own)[3] = u32x4{l1[0], l1[1], l1[2], l1[3]};
               }
             } else {
-              limb_words(7, l1);
+              digit_words(1, l1);
             }
-            if (n_limbs > 2u) {
+            if (n_digits > 2u) {
               uint32_t l2[NR / 4];
-              limb_words(14, l2);
+              digit_words(2, l2);
 #pragma unroll
               for (int i = 0; i < NR / 4; ++i) reinterpret_cast<uint32_t*>(meta)[tid * (NR / 4) + i] = l2[i];
             }
@@ -1045,7 +1288,7 @@ __global__ __launch_bounds__(BLOCK * TEAMS, (Lds<BLOCK, NR, TEAMS, RMAX, PERWAVE
             } else {
               *reinterpret_cast<u32x4*>(own) = u32x4{mk[0], mk[1], l0[0], l1[0]};
             }
-            products = (tid & ~63u) * NR < n_events ? n_limbs : 0u;  // this wave holds records
+            products = (tid & ~63u) * NR < n_events ? n_digits : 0u;  // this wave holds records
           } else {
             // Its neighbours may add up their own stretches only: what is open where this wave's begin counts as
             // switched on there, what is open where they end as switched off.
@@ -1073,8 +1316,8 @@ __global__ __launch_bounds__(BLOCK * TEAMS, (Lds<BLOCK, NR, TEAMS, RMAX, PERWAVE
 #pragma unroll
           for (int i = 0; i < NR; ++i) {
             const uint32_t info = (mw[i >> 2] >> (8 * (i & 3))) & 0xFFu;
-            sx[i] = g0 + i < n_events ? 1u << (info >> 1) : 0u;
-            ends |= (info & 1u) << i;
+            sx[i] = g0 + i < n_events ? 1u << (info & 31u) : 0u;
+            ends |= (info >> 5) << i;
           }
           auto end_mask = [&](int i) -> uint32_t { return (uint32_t)((int32_t)(ends << (31 - i)) >> 31); };  // all ones for an END
 #pragma unroll
@@ -1090,8 +1333,8 @@ __global__ __launch_bounds__(BLOCK * TEAMS, (Lds<BLOCK, NR, TEAMS, RMAX, PERWAVE
     request_units(wg_ahead, tid, std::integral_constant<int, 0>{}, std::integral_constant<int, kEarly>{});
     // (Wave-uniform, and in a scalar register: matrix instructions do not heed the execution mask, and a short branch on a
     // vector register is taken by masking alone.)
-    const uint32_t n_limbs = (uint32_t)__builtin_amdgcn_readfirstlane((int)products);
-    if (n_limbs) {
+    const uint32_t n_digits = (uint32_t)__builtin_amdgcn_readfirstlane((int)products);
+    if (n_digits) {
       __builtin_amdgcn_wave_barrier();
       typedef int i32x4 __attribute__((ext_vector_type(4)));
       i32x4 acc[3];
@@ -1101,16 +1344,18 @@ __global__ __launch_bounds__(BLOCK * TEAMS, (Lds<BLOCK, NR, TEAMS, RMAX, PERWAVE
       const uint32_t up = 15u - j;      // shift that takes bit j of a 16-bit set to its top
       // (a wave that is not full has no segments past its share of the records; with 16 waves one register is too many)
       const uint32_t sets = BLOCK == 1024 && NR == 16 ? 16u : (uint32_t)__builtin_amdgcn_readfirstlane((int)(tmp[T_EVENTS] - (tid & ~63u) * NR + 63u)) >> 6;
+      // this lane reads the places from 64 n + 16 (lane / 16) of the wave's on
+      const uint32_t place0 = (tid & ~63u) * NR + 16u * (lane >> 4);
+      const u32x4* from0 = reinterpret_cast<const u32x4*>(clk + clk_word(place0));
       for (uint32_t n = 0; n < NR && n < sets; ++n) {  // 64 segments: those of 64 / NR lanes
-        const uint32_t src = (tid & ~63u) + (64u / NR) * n + (16u / NR) * (lane >> 4);  // the first that this lane reads of
-        const u32x4* from = reinterpret_cast<const u32x4*>(clk + clk_word(src * NR));
+        const u32x4* from = from0 + 17u * n;  // (68 words: 64 and their padding)
         uint32_t w8[8];  // sets of 16 segments
         u32x4 l0, l1{0u, 0u, 0u, 0u};
         if constexpr (NR == 16) {
           const u32x4 s0 = from[0], s1 = from[1];
           w8[0] = s0.x; w8[1] = s0.y; w8[2] = s0.z; w8[3] = s0.w; w8[4] = s1.x; w8[5] = s1.y; w8[6] = s1.z; w8[7] = s1.w;
           l0 = from[2];
-          if (n_limbs > 1u) l1 = from[3];
+          if (n_digits > 1u) l1 = from[3];
         } else {  // four lanes' places side by side
           const u32x4 a = from[0], b = from[1], c = from[2], d = from[3];
           w8[0] = a.x; w8[1] = a.y; w8[2] = b.x; w8[3] = b.y; w8[4] = c.x; w8[5] = c.y; w8[6] = d.x; w8[7] = d.y;
@@ -1127,12 +1372,12 @@ __global__ __launch_bounds__(BLOCK * TEAMS, (Lds<BLOCK, NR, TEAMS, RMAX, PERWAVE
         const i32x4 bits = ones;
         acc[0] = __builtin_amdgcn_mfma_i32_16x16x64_i8(ones & i32x4{(int)l0.x, (int)l0.y, (int)l0.z, (int)l0.w}, bits,
                                                        acc[0], 0, 0, 0);
-        if (n_limbs > 1u) {
+        if (n_digits > 1u) {
           acc[1] = __builtin_amdgcn_mfma_i32_16x16x64_i8(ones & i32x4{(int)l1.x, (int)l1.y, (int)l1.z, (int)l1.w}, bits,
                                                          acc[1], 0, 0, 0);
         }
-        if (n_limbs > 2u) {
-          const u32x4 l2 = *reinterpret_cast<const u32x4*>(meta + src * NR);
+        if (n_digits > 2u) {
+          const u32x4 l2 = *reinterpret_cast<const u32x4*>(meta + place0 + 64u * n);
           acc[2] = __builtin_amdgcn_mfma_i32_16x16x64_i8(ones & i32x4{(int)l2.x, (int)l2.y, (int)l2.z, (int)l2.w}, bits,
                                                          acc[2], 0, 0, 0);
         }
@@ -1142,7 +1387,7 @@ __global__ __launch_bounds__(BLOCK * TEAMS, (Lds<BLOCK, NR, TEAMS, RMAX, PERWAVE
 #pragma unroll
       for (int v = 0; v < 4; ++v) {
         const uint32_t a = 4u * (lane >> 4) + v, b = j;
-        const uint32_t total = 0u - ((uint32_t)acc[0][v] + ((uint32_t)acc[1][v] << 7) + ((uint32_t)acc[2][v] << 14));
+        const uint32_t total = 0u - ((uint32_t)acc[0][v] + ((uint32_t)acc[1][v] << 8) + ((uint32_t)acc[2][v] << 16));
         if (a <= b && b < R && total) atomicAdd(&oacc32[a * (R | 1u) + b], total);
       }
     }
@@ -1253,7 +1498,7 @@ kp_status launch_planes(DecodeParams& p, hipStream_t s) {
   p.ncopy = 4;  // as many copies of the per-(wave, region) sums as their LDS array has room for
   while (p.ncopy > 1 && p.ncopy * p.W * p.R > (uint32_t)PERWAVE) p.ncopy >>= 1;
   // counters of open waves per region run up to the number of waves
-  if constexpr (NR == 16) if (p.W < 16) return launch_main<BLOCK, NR, TEAMS, 4, RMAX, PERWAVE>(p, s);
+  if (p.W < 16) return launch_main<BLOCK, NR, TEAMS, 4, RMAX, PERWAVE>(p, s);
   return launch_main<BLOCK, NR, TEAMS, 5, RMAX, PERWAVE>(p, s);
 }
 

@@ -133,6 +133,38 @@ def test_every_form_of_the_decoder_over_several_turns(kp, oracle_mod, n_wg, W, R
     check(damaged_between_clean_trace(n_wg, n_wg, W, R, cap), oracle_mod, use_hdr=True)
 
 
+# rings of at least the 1024 (256 with four records per lane) slots that a hardware wave takes, of at least the 128 of one of
+# its rounds, and smaller ones, for the kernels with 1024 threads, 256, and one wave
+@pytest.mark.parametrize("n_wg,W,R,cap", [
+    (300, 8, 16, 2048), (260, 16, 20, 512), (260, 2, 5, 1024), (260, 8, 16, 512), (260, 16, 9, 64),       # 16 records per lane
+    (300, 1, 5, 1024), (300, 4, 16, 128), (300, 16, 20, 32),
+    (40, 8, 5, 512), (40, 4, 5, 256), (40, 4, 5, 128), (40, 8, 5, 64), (40, 1, 3, 256), (40, 2, 3, 64), (300, 2, 8, 128)])  # four
+def test_the_oldest_record_anywhere_in_the_ring(kp, oracle_mod, n_wg, W, R, cap):
+    """Records are paired where they lie, in the order of a ring that begins with its oldest one: rings that wrapped by any
+    number of records or not at all, oldest records that are ENDs, STARTs and ENDs of a pair at the two ends of a ring and of
+    a hardware wave's share; with records outside the slot of their seq, seqs that occur twice and bad records, and with
+    regions inside regions."""
+    from tests.gpu_util import nested_trace
+
+    spec = inputs.TraceSpec(n_wg=n_wg, waves=W, n_regions=R, cap_wave=cap, total_per_wave=3 * cap, total_var=2 * cap + cap // 2, seed=cap + W,
+                            dist="exp", p0=40.0, gap_max=4, p_orphan=0.1, p_swap=0.002)
+    raw, _ = inputs.gen_trace(spec)
+    check(raw, oracle_mod, use_hdr=True)
+    raw = raw.copy()
+    slots = raw[16 + 32 * n_wg:].reshape(n_wg, W, cap, 2)
+    rng = np.random.default_rng(cap)
+    for wg in range(n_wg):
+        seg, a = slots[wg, int(rng.integers(0, W))], int(rng.integers(0, cap - 1))
+        if wg % 5 == 1:    # a seq that occurs twice
+            seg[a + 1, 0] = (seg[a + 1, 0] & ~np.uint32(0xFFFFF)) | (seg[a, 0] & np.uint32(0xFFFFF))
+        elif wg % 5 == 2:  # a bad record
+            seg[a, 0] |= np.uint32(0x7F000000)
+        elif wg % 5 == 3:  # the records at the two ends of the ring, each in the other's slot
+            seg[[0, cap - 1]] = seg[[cap - 1, 0]]
+    check(raw, oracle_mod, use_hdr=True)
+    check(nested_trace(cap, W, R, cap, depth=min(3, R), inner=4), oracle_mod, use_hdr=True)
+
+
 def test_empty_trace(kp, oracle_mod):
     check(inputs.encode_trace([], 4, 3, 8), oracle_mod)
 
