@@ -31,9 +31,12 @@
 //      region with every open region (modulo 2^64: the total is exact).
 // Nothing but the inputs and the statistics block is touched in HBM.
 //
-// What bounds it: the latency of its steps (16 hardware waves in lockstep between some ten barriers per window),
-// then LDS and instruction issue in about equal parts.  So a window is as large as LDS allows (8192 records: a
-// third of a workgroup's usual ring), the order is finished in registers, and nothing is done per region.  Measured
+// What bounds it: the latency of its steps (the hardware waves are in lockstep between some ten barriers per window),
+// then LDS and instruction issue in about equal parts.  So two decoder workgroups share a CU where there is work for them
+// (launch_wide), a window is as large as LDS then allows, the order is finished in registers, and nothing is done per region.  Of
+// the 675 us that 1024 workgroups of 8 x 4096 records with 48 regions take one workgroup to a CU, pass 0 is 57 (what reading them
+// once takes), pass 1 122, looking at the windows and counting cells 134, sorting 111, the sweep 135, the sums of the region
+// pairs 114; two to a CU 627.  Before: measured
 // on 1024 workgroups of 8 waves x 4096 records with 48 regions (268 MB), merging 2048 records at a time in LDS and
 // walking the regions one by one in the sweep before: 2594 -> 685 us (passes 0 and 1: 640 -> 187 us, of which 220 us
 // were a device-wide fence per workgroup; the sweep: 220 us, half of it the sums of the region pairs).  Keys of 64
@@ -45,18 +48,18 @@ namespace {
 
 using namespace kp_reduce;
 
-constexpr int kBlock = 1024;
-constexpr uint32_t kWavesHw = kBlock / 64;
+constexpr uint32_t kWavesMost = 16;         // hardware waves of a decoder workgroup, at most
 constexpr uint32_t kTableMin = 11, kTableMax = 14;  // ranks whose winning slots pass 1 looks up at a time: log2, what LDS has room for
 constexpr uint32_t kAreaMin = 32768;        // LDS that the passes share at least
 constexpr uint32_t kListMin = 512, kListMax = 8192;  // records outside the slot of their seq that a workgroup can list: what LDS has room for
 constexpr uint32_t kMaxCell = 64;           // fullest time cell in which records are ranked by comparing each with each
 constexpr uint32_t kSeqMask = 0xFFFFFu;
-constexpr uint32_t kHistStride = 65;        // histogram rows 65 words apart: equal bins of different regions, different banks
+constexpr uint32_t kBins = 32;              // a duration has 32 bits: bins from there on stay empty
+constexpr uint32_t kHistStride = kBins + 1; // an odd number of words apart: equal bins of different regions, different banks
 constexpr uint32_t kMaxPlanes = 4 * 5;      // words of a bit-sliced count of every region the tag can name
 constexpr uint64_t kNoKey = ~0ull;
 constexpr uint32_t kNoId = 0xFFFFu;          // END << 7 | region of no record
-constexpr uint32_t kMaxLds = 160 * 1024;
+constexpr uint32_t kMaxLds = 160 * 1024;    // of a CU
 
 // per-workgroup temporaries (u32 words in LDS)
 enum { T_FIELDVALID = 0, T_DISORDER, T_OCCUPIED, T_WINNER_DISORDER, T_NONMONO, T_PAIRS, T_ENDS, T_WINDOW_BEGIN,
@@ -73,8 +76,10 @@ inline uint32_t up16(uint32_t x) { return (x + 15u) & ~15u; }
 // read 8 consecutive places each, 64 bytes apart, spread over all banks.
 __host__ __device__ constexpr uint32_t key_at(uint32_t place) { return place * 8u + ((place >> 5) << 4); }
 
-// per_lane: records of a window per lane; split_log2: runs per recorded wave in pass 1
-WideLds lay_out(uint32_t W, uint32_t R, uint32_t nrec, uint32_t per_lane, uint32_t split_log2, bool rows_in_lds) {
+// block: threads of a decoder workgroup; per_cu: decoder workgroups that share the LDS of a CU; per_lane: records of a window
+// per lane; split_log2: runs per recorded wave in pass 1
+WideLds lay_out(uint32_t block, uint32_t per_cu, uint32_t W, uint32_t R, uint32_t nrec, uint32_t per_lane, uint32_t split_log2, bool rows_in_lds) {
+  const uint32_t max_lds = kMaxLds / per_cu;
   WideLds l;
   l.per_lane = per_lane; l.split_log2 = split_log2; l.rows_in_lds = rows_in_lds ? 1u : 0u;
   const uint32_t runs_bytes = (W << split_log2) * R * 8u;
@@ -84,11 +89,11 @@ WideLds lay_out(uint32_t W, uint32_t R, uint32_t nrec, uint32_t per_lane, uint32
   l.row_min = l.rows + (rows_in_lds ? W * R * 16u : 0u);
   l.table = up16(l.row_min + (rows_in_lds ? W * R * 4u : 0u));
   const uint32_t pass1 = l.table + (4u << kTableMin);
-  l.cells = key_at(kBlock * per_lane);
-  l.totals = l.cells + kBlock * per_lane * 2u;
-  const uint32_t pass2 = l.totals + kWavesHw * kMaxPlanes * 4u;
+  l.cells = key_at(block * per_lane);
+  l.totals = l.cells + block * per_lane * 2u;
+  const uint32_t pass2 = l.totals + kWavesMost * kMaxPlanes * 4u;
   uint32_t area = pass1 > pass2 ? pass1 : pass2;
-  area = area > kAreaMin ? area : kAreaMin;
+  area = area > kAreaMin / per_cu ? area : kAreaMin / per_cu;
   l.table_log2 = kTableMin;
   while (l.table_log2 < kTableMax && l.table + (8u << l.table_log2) <= area) ++l.table_log2;
   l.bitmap = up16(area);
@@ -104,25 +109,30 @@ WideLds lay_out(uint32_t W, uint32_t R, uint32_t nrec, uint32_t per_lane, uint32
   l.pos = l.vf + 32 * 8;
   l.adv = l.pos + 16 * 4;
   l.edge = l.adv + 16 * 4;
-  l.list = l.edge + kWavesHw * 16;
+  l.list = l.edge + kWavesMost * 16;
   l.list_cap = kListMin;
-  while (l.list_cap < kListMax && l.list + l.list_cap * 2 * 8 <= kMaxLds) l.list_cap *= 2;  // what is left
+  while (l.list_cap < kListMax && l.list + l.list_cap * 2 * 8 <= max_lds) l.list_cap *= 2;  // what is left
   l.total = l.list + l.list_cap * 8;
   return l;
+}
+// Runs that a recorded wave is cut into in pass 1 (log2): as many as there are hardware waves for, while a run keeps 256 ranks.
+inline uint32_t split_log2(uint32_t block, uint32_t W, uint32_t cap) {
+  uint32_t most = 0;
+  while ((W << (most + 1)) <= block / 64u && (cap >> (most + 1)) >= 256u) ++most;
+  return most;
 }
 // The largest window that LDS has room for (beside a list of twice the smallest size), with the rows of the
 // (wave, region) sums in LDS and the recorded waves cut into as many runs as there are hardware waves for;
 // failing that with fewer runs; the smallest window also with the rows in HBM.
-WideLds wide_lds(uint32_t W, uint32_t R, uint32_t cap) {
-  uint32_t most = 0;
-  while ((W << (most + 1)) <= kWavesHw && (cap >> (most + 1)) >= 256u) ++most;
+WideLds wide_lds(uint32_t block, uint32_t per_cu, uint32_t W, uint32_t R, uint32_t cap) {
+  const uint32_t max_lds = kMaxLds / per_cu, most = split_log2(block, W, cap);
   for (uint32_t per_lane = 8; per_lane >= 2; per_lane >>= 1) {
     for (uint32_t split = most + 1; split-- > 0;) {
-      const WideLds l = lay_out(W, R, W * cap, per_lane, split, true);
-      if (l.total <= kMaxLds && (per_lane == 2 || l.list_cap > kListMin)) return l;
+      const WideLds l = lay_out(block, per_cu, W, R, W * cap, per_lane, split, true);
+      if (l.total <= max_lds && (per_lane == 2 || l.list_cap > kListMin)) return l;
     }
   }
-  return lay_out(W, R, W * cap, 2, 0, false);
+  return lay_out(block, per_cu, W, R, W * cap, 2, 0, false);
 }
 
 struct WideParams {
@@ -182,9 +192,10 @@ __device__ __forceinline__ void planes_scan_step(Planes<NW, P>& p) {
   planes_add<NW, P>(p, o);
 }
 
-// E: records of a window per lane; NW: 32-bit words that hold one bit per region; P: bits of a count of waves.
-template <int E, int NW, int P>
-__global__ __launch_bounds__(kBlock) void kp_reduce_wide(WideParams p) {
+// kBlock: threads; E: records of a window per lane; NW: 32-bit words that hold one bit per region; P: bits of a count of waves.
+template <int kBlock, int E, int NW, int P>
+__global__ __launch_bounds__(kBlock, 4) void kp_reduce_wide(WideParams p) {
+  constexpr uint32_t kWavesHw = kBlock / 64;
   extern __shared__ __align__(16) unsigned char smem[];
   constexpr uint32_t K = kBlock * E;  // places of a window
   // [run][region] its last record: (rank + 1) << 33 | END << 32 | clock, 0 for none; so the latest is the largest
@@ -218,7 +229,9 @@ __global__ __launch_bounds__(kBlock) void kp_reduce_wide(WideParams p) {
   // passes is done ahead of the loops and held in registers through them.
   auto fresh_tid = [&]() { tid = tid_k; asm volatile("" : "+v"(tid)); lane = tid & 63u; };
   const uint32_t W = p.W, R = p.R, cap = p.cap, capm = cap - 1u, cl2 = p.cap_log2, nrec = p.nrec;
-  const uint32_t rsh = (E == 8 ? 13u : (E == 4 ? 12u : 11u)) - p.waves_log2, C = 1u << rsh;  // a window looks at C ranks of every wave
+  constexpr uint32_t kPlacesLog2 = (E == 8 ? 3u : E == 4 ? 2u : 1u) + (kBlock == 1024 ? 10u : kBlock == 512 ? 9u : 8u);
+  static_assert(K == 1u << kPlacesLog2, "places of a window");
+  const uint32_t rsh = kPlacesLog2 - p.waves_log2, C = 1u << rsh;  // a window looks at C ranks of every wave
   const uint32_t tsh = p.lds.table_log2 - p.waves_log2, Ct = 1u << tsh;                        // table1: Ct ranks of every wave
   uint32_t region_bits = 0; while ((1u << region_bits) < R) ++region_bits;
   const StatsLayout SL = stats_layout(p.n_wg, W, R);
@@ -263,7 +276,7 @@ __global__ __launch_bounds__(kBlock) void kp_reduce_wide(WideParams p) {
         __hip_atomic_store(&row[1], 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
       }
     }
-    if (tid < kWavesHw) edge[4u * tid] = 0u;
+    if (tid < kWavesMost) edge[4u * tid] = 0u;
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // the rows are cleared before any wave adds to them
     __syncthreads();
     uint32_t held = 0, max_v = 0;
@@ -390,10 +403,10 @@ __global__ __launch_bounds__(kBlock) void kp_reduce_wide(WideParams p) {
     // (a workgroup that looks its winning slots up in a table does not cut its waves into runs)
     {
       const uint32_t split = tabled ? 0u : p.lds.split_log2;
-      const uint32_t w_here = hw >> split, run = hw & ((1u << split) - 1u);
-      unsigned long long* last = last_all + hw * R;
-      uint2* head = head_all + hw * R;
       uint32_t n_pairs = 0, n_ends = 0, nonmono = 0, occupied = 0, moved = 0;  // (the same in all lanes)
+      uint32_t w_here = 0, run = 0;
+      unsigned long long* last = last_all;
+      uint2* head = head_all;
       bool carry_has = false;
       uint32_t carry_ts = 0, first_ts = 0, carry_id = kNoId;  // the run's last record so far: clock, END << 7 | region; clock of its first
       const uint64_t below = (1ull << lane) - 1ull;
@@ -483,6 +496,14 @@ __global__ __launch_bounds__(kBlock) void kp_reduce_wide(WideParams p) {
           if ((near >> lane) & 1ull) mark(b0 + lane - 1u);
         }
       };
+      // (runs may outnumber the hardware waves where these are fewer than the recorded ones)
+      const uint32_t n_runs = kWavesHw == kWavesMost ? 1u : W << split;
+      for (uint32_t run0 = 0; run0 < n_runs; run0 += kWavesHw) {
+      const uint32_t id = run0 + hw;
+      w_here = id >> split; run = id & ((1u << split) - 1u);
+      last = last_all + id * R;
+      head = head_all + id * R;
+      carry_has = false; carry_ts = 0u; first_ts = 0u; carry_id = kNoId;
       const uint32_t V = w_here < W ? sVF[w_here].x : 0u;
       if (!tabled) {
         // rank k belongs in slot (first + k) mod cap; nothing is shared with the other runs
@@ -527,22 +548,25 @@ __global__ __launch_bounds__(kBlock) void kp_reduce_wide(WideParams p) {
           build_table(table1, 1u << p.lds.table_log2, tsh);
 #pragma unroll 1
           for (uint32_t j0 = 0; j0 < Ct && k0 + j0 < V; j0 += 64u) {
-            const uint32_t t = table1[(hw << tsh) + j0 + lane];
-            const uint2 rec = recs[(size_t)hw * cap + (t ? t - 1u : 0u)];
+            const uint32_t t = table1[(id << tsh) + j0 + lane];
+            const uint2 rec = recs[(size_t)id * cap + (t ? t - 1u : 0u)];
             moved += (uint32_t)__popcll(__builtin_amdgcn_ballot_w64(t != 0u && ((rec.x ^ (t - 1u)) & capm) != 0u));
             group(k0 + j0, t != 0u, rec);
           }
         }
       }
       if (lane == 0 && w_here < W) {
+        edge[4u * id] = carry_has ? 1u : 0u;
+        edge[4u * id + 1u] = first_ts;
+        edge[4u * id + 2u] = carry_ts;
+      }
+      }
+      if (lane == 0) {
         if (n_pairs) atomicAdd(&tmp[T_PAIRS], n_pairs);
         if (n_ends) atomicAdd(&tmp[T_ENDS], n_ends);
         if (nonmono) atomicAdd(&tmp[T_NONMONO], nonmono);
         if (occupied) atomicAdd(&tmp[T_OCCUPIED], occupied);
         if (moved) atomicAdd(&tmp[T_WINNER_DISORDER], moved);
-        edge[4u * hw] = carry_has ? 1u : 0u;
-        edge[4u * hw + 1u] = first_ts;
-        edge[4u * hw + 2u] = carry_ts;
       }
       __syncthreads();
       // Join the runs of a wave, region by region.
@@ -875,7 +899,7 @@ __global__ __launch_bounds__(kBlock) void kp_reduce_wide(WideParams p) {
 #pragma unroll
         for (int w = 0; w < NW; ++w)
 #pragma unroll
-          for (int k = 0; k < P; ++k) sum.at[w][k] = totals[(lane & 15u) * kMaxPlanes + w * P + k];
+          for (int k = 0; k < P; ++k) sum.at[w][k] = kWavesHw == 16u || (lane & 15u) < kWavesHw ? totals[(lane & 15u) * kMaxPlanes + w * P + k] : 0u;
         planes_scan_step<0, NW, P>(sum); planes_scan_step<1, NW, P>(sum); planes_scan_step<2, NW, P>(sum); planes_scan_step<3, NW, P>(sum);
 #pragma unroll
         for (int w = 0; w < NW; ++w)
@@ -931,9 +955,9 @@ __global__ __launch_bounds__(kBlock) void kp_reduce_wide(WideParams p) {
 
   // ---- flush this decoder workgroup's totals ----------------------------------------------------
   unsigned long long* out = reinterpret_cast<unsigned long long*>(p.out);
-  for (uint32_t i = tid; i < R * 64; i += kBlock) {
-    const uint32_t h = hist[(i >> 6) * kHistStride + (i & 63u)];
-    if (h) atomicAdd(&out[SL.hist + i], (unsigned long long)h);
+  for (uint32_t i = tid; i < R * kBins; i += kBlock) {
+    const uint32_t r = i / kBins, bin = i % kBins, h = hist[r * kHistStride + bin];
+    if (h) atomicAdd(&out[SL.hist + r * 64u + bin], (unsigned long long)h);
   }
   for (uint32_t i = tid; i < R * R; i += kBlock) {
     const uint32_t a = i / R, b = i - a * R;
@@ -955,7 +979,8 @@ namespace kp_reduce {
 
 kp_status wide_supported(const kp_trace_hdr& h) {
   const uint32_t nrec = h.waves_per_wg * h.cap_wave;
-  const uint32_t need = wide_lds(h.waves_per_wg, h.n_regions, h.cap_wave).total;
+  // What the smallest form needs with 64 bins per histogram row: the limits are those from before the rows had 32.
+  const uint32_t need = lay_out(1024u, 1u, h.waves_per_wg, h.n_regions, nrec, 2u, 0u, false).list + kListMin * 8u + h.n_regions * (64u - kBins) * 4u;
   if (need > kMaxLds)
     return kp::fail(KP_ERR_UNSUPPORTED_SHAPE,
                     "%u record slots per workgroup with %u regions: the decoder needs %u B of LDS (limit %u)", nrec,
@@ -965,23 +990,23 @@ kp_status wide_supported(const kp_trace_hdr& h) {
 
 namespace {
 
-template <int E, int NW, int P>
+template <int BLOCK, int E, int NW, int P>
 kp_status launch(const WideParams& p, hipStream_t s) {
-  auto kern = kp_reduce_wide<E, NW, P>;
+  auto kern = kp_reduce_wide<BLOCK, E, NW, P>;
   static thread_local kp_stage::LaunchCache cache;
   uint32_t grid = 0;
-  const kp_status st = kp_stage::resident_grid(kern, kBlock, p.lds.total, &cache, &grid);
+  const kp_status st = kp_stage::resident_grid(kern, BLOCK, p.lds.total, &cache, &grid);
   if (st != KP_OK) return st;
   if (grid > p.n_wg) grid = p.n_wg;
-  hipLaunchKernelGGL(kern, dim3(grid), dim3(kBlock), p.lds.total, s, p);
+  hipLaunchKernelGGL(kern, dim3(grid), dim3(BLOCK), p.lds.total, s, p);
   KP_HIP_TRY(hipGetLastError());
   return KP_OK;
 }
-template <int E>
+template <int BLOCK, int E>
 kp_status launch_words(const WideParams& p, hipStream_t s) {
   if (p.W == 16)  // counts up to 16
-    return p.R <= 32 ? launch<E, 1, 5>(p, s) : (p.R <= 64 ? launch<E, 2, 5>(p, s) : launch<E, 4, 5>(p, s));
-  return p.R <= 32 ? launch<E, 1, 4>(p, s) : (p.R <= 64 ? launch<E, 2, 4>(p, s) : launch<E, 4, 4>(p, s));
+    return p.R <= 32 ? launch<BLOCK, E, 1, 5>(p, s) : (p.R <= 64 ? launch<BLOCK, E, 2, 5>(p, s) : launch<BLOCK, E, 4, 5>(p, s));
+  return p.R <= 32 ? launch<BLOCK, E, 1, 4>(p, s) : (p.R <= 64 ? launch<BLOCK, E, 2, 4>(p, s) : launch<BLOCK, E, 4, 4>(p, s));
 }
 
 }  // namespace
@@ -999,8 +1024,36 @@ kp_status launch_wide(const uint32_t* wg_hdrs, const void* records, uint64_t* ou
   p.rec_cost = h.rec_cost; p.flush = h.flags & KP_FLAG_FLUSH;
   p.nrec = p.W * p.cap;
   p.waves_log2 = 0; while ((1u << p.waves_log2) < p.W) ++p.waves_log2;
-  p.lds = wide_lds(p.W, p.R, p.cap);
-  return p.lds.per_lane == 8 ? launch_words<8>(p, s) : (p.lds.per_lane == 4 ? launch_words<4>(p, s) : launch_words<2>(p, s));
+  // How many threads take a recorded workgroup.  1024, and windows of 8192 places, are all that fits one CU.  With more
+  // recorded workgroups than CUs (256 of the whole chip) two of 512 threads, with 4096 places each, hide each other's barriers and
+  // LDS round trips: 1024 workgroups of 8 x 4096 slots, 48 regions 675 -> 627 us, 1000 of 16 x 2048, 16 regions 772 -> 743, 2000 of
+  // 8 x 2048, 64 regions 829 -> 699, 3000 of 4 x 1024, 64 regions 428 -> 285, 257 of 8 x 4096 359 -> 332, 512 of 3 x 8192 the same;
+  // with no more of them than CUs it is one workgroup's chain of steps: 100 of 8 x 4096 172 against 235 us, 200 of 16 x 512 82 / 118.
+  // Up to 2048 slots one window of 2048 places holds all there are: three workgroups of 256 threads where LDS has room
+  // (1024 threads / 512 / 256, us: 4000 of 8 x 256, 40 regions 394 / 226 / 185, 4000 of 1 x 256 300 / 160 / 123), else, and with few
+  // workgroups, 512 threads with four records each (100 of 2 x 256 27.0 -> 24.2, 256 of 2 x 512, 64 regions 38.8 -> 36.5, 1021 of
+  // 8 x 256, 64 regions 146 -> 92).
+  if (p.nrec <= 2048u && p.n_wg > 256u) {
+    p.lds = lay_out(256u, 3u, p.W, p.R, p.nrec, 8u, 0u, true);
+    if (p.lds.total <= kMaxLds / 3u) return launch_words<256, 8>(p, s);
+  }
+  if (p.nrec <= 2048u) {
+    const uint32_t per_cu = p.n_wg > 256u ? 2u : 1u;
+    p.lds = lay_out(512u, per_cu, p.W, p.R, p.nrec, 4u, split_log2(512u, p.W, p.cap), true);
+    if (p.lds.total <= kMaxLds / per_cu) return launch_words<512, 4>(p, s);
+  }
+  if (p.n_wg > 256u) {
+    p.lds = wide_lds(512u, 2u, p.W, p.R, p.cap);
+    if (p.lds.total <= kMaxLds / 2u && p.lds.per_lane == 8u) return launch_words<512, 8>(p, s);
+  }
+  // (one window of 4096 places, four records a lane, where three quarters of it hold all: 170 of 12 x 256 slots, 100 regions 65.0 ->
+  // 61.6 us, 600 of 5 x 512, 100 regions 140 -> 132; of 8192 with full ones: 100 of 16 x 256 80.8 -> 80.1)
+  if (p.nrec <= 3072u) {
+    p.lds = lay_out(1024u, 1u, p.W, p.R, p.nrec, 4u, split_log2(1024u, p.W, p.cap), true);
+    if (p.lds.total <= kMaxLds) return launch_words<1024, 4>(p, s);
+  }
+  p.lds = wide_lds(1024u, 1u, p.W, p.R, p.cap);
+  return p.lds.per_lane == 8 ? launch_words<1024, 8>(p, s) : (p.lds.per_lane == 4 ? launch_words<1024, 4>(p, s) : launch_words<1024, 2>(p, s));
 }
 
 }  // namespace kp_reduce

@@ -188,3 +188,25 @@ def test_sort_forms_of_the_overlap_windows(kp, oracle_mod, W, R, cap, spacing):
     raw = inputs.encode_trace(wgs, W, R, cap, rec_cost=1)
     stats = check(raw, oracle_mod, use_hdr=True)
     assert stats["n_overlap_wgs"] == 2
+
+
+# 256 threads (rings of up to 2048 slots in all, more than 256 workgroups; up to 16 runs on four hardware waves), 512 with four
+# records each, 512 with eight (more than 256 workgroups), 1024 with eight and with four; the last case of each on the far side of the line
+@pytest.mark.parametrize("n_wg,W,R,cap", [
+    (300, 16, 33, 128), (257, 8, 40, 256), (300, 1, 40, 2048), (300, 5, 36, 256), (300, 16, 48, 128),
+    (256, 16, 33, 128), (5, 1, 128, 2048), (300, 16, 64, 128), (9, 12, 100, 64), (300, 7, 128, 256),
+    (300, 16, 40, 256), (257, 8, 17, 4096), (300, 3, 64, 2048), (300, 1, 5, 32768), (256, 8, 40, 512), (300, 16, 128, 256), (20, 12, 100, 256), (9, 3, 33, 1024)])
+@pytest.mark.parametrize("p_swap", [0.0, 0.02, 0.6])
+def test_every_number_of_threads(kp, oracle_mod, n_wg, W, R, cap, p_swap):
+    """Records in the slot of their seq, some that are not (listed), so many that they do not fit the list (looked up in a
+    table), with a corrupt workgroup between clean ones."""
+    spec = inputs.TraceSpec(n_wg=n_wg, waves=W, n_regions=R, cap_wave=cap, total_per_wave=cap + cap // 4, total_var=cap // 2,
+                            seed=W * R + cap, dist="lognormal", p0=4.0, p1=1.0, p_orphan=0.05, p_swap=p_swap)
+    raw, _ = inputs.gen_trace(spec)
+    raw = raw.copy()
+    slots = raw[16 + 32 * n_wg:].reshape(n_wg, W, cap, 2)
+    slots[n_wg // 2, W - 1, 3, 0] |= np.uint32(0x7F000000) if R < 128 else np.uint32(0x00F00000)
+    if R == 128 and W == 16:
+        slots[n_wg // 2, W - 1, 3, 0] ^= np.uint32(0x00100000)
+    st = check(raw, oracle_mod, use_hdr=True)
+    assert st["n_overlap_wgs"] == n_wg - 1 and (p_swap == 0.0) == (st["n_disorder"] == 0)
