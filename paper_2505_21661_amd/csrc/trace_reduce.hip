@@ -29,6 +29,9 @@
 // What bounds it is instruction issue: 2.6 vector instructions per record (3.2 with every record scattered to LDS by its
 // rank and read back, one round at a time in B, planes in the prefix sum): 16384 workgroups of 8 x 2048 records 1775 -> 1550
 // us; 4000 of 4 x 1024, wrapped 125 -> 114; 256 of 8 x 512 28.7 -> 27.1; 512 of 8 x 2048, regions three deep 389 -> 219.
+// A kernel of its own per class of ring sizes (RINGS), and for more than 16 regions (MANY), instead of one that chooses:
+// 16384 of 8 x 2048 1562 -> 1495, 8191 of 2 x 4096 889 -> 856, 8192 of 16 x 32 74.0 -> 70.1, 64 of 4 x 128 16.4 -> 15.5, 65534 of 7 x 128,
+// 32 regions 1325 -> 1289.
 // Traces outside what the register sort covers (more than 16 regions, a span of 2^26 ticks or
 // more, a time cell with more than NR + 1 records) rank the records inside their cell by comparing
 // clocks and add every switch of a region to the region-pair sums with LDS atomics.
@@ -51,6 +54,9 @@ constexpr uint32_t kMaxRecPerWg = 16384;
 constexpr uint32_t kMaxLds = 160 * 1024;
 constexpr uint32_t kHistStride = 65;  // histogram rows 65 words apart: equal bins of different regions, different banks
 
+// rings of less than 128 slots; of 128 and more, so that a round is one recorded wave's, but less than a hardware wave's share; of at
+// least that share; either of the last two
+enum { kSmall, kPart, kWhole, kAny };
 // steps after which kp_trace_reduce_steps can leave a workgroup
 enum { kStepOrdered = 1, kStepPaired, kStepCounted, kStepCellSums, kStepPlaced, kStepRanked, kStepSorted, kStepSwept };
 
@@ -333,9 +339,12 @@ __global__ __launch_bounds__(1024) void kp_reduce_derive(uint64_t* out, uint32_t
 // Position p = wave*cap_wave + rank indexes the staged records.  Hardware wave h of the decoder
 // owns the 64 * NR positions from 64 * NR * h on, and lane l takes 128 j + 2 l of them and the one above it in round j,
 // so that neighbouring lanes hold neighbouring ranks.
-template <int BLOCK, int NR, int TEAMS, int PLANES, int RMAX, int PERWAVE>
+// RINGS: slots of a ring.  MANY: more than 16 regions, which
+// the register sort does not take.
+template <int BLOCK, int NR, int TEAMS, int PLANES, int RMAX, int PERWAVE, int RINGS, bool MANY>
 __global__ __launch_bounds__(BLOCK * TEAMS, (Lds<BLOCK, NR, TEAMS, RMAX, PERWAVE>::waves_per_simd)) void kp_reduce_main(DecodeParams p) {
   using L = Lds<BLOCK, NR, TEAMS, RMAX, PERWAVE>;
+  constexpr bool SMALL = RINGS == kSmall;
   constexpr uint32_t kWaveSpan = 64 * NR;      // positions per hardware wave
   constexpr uint32_t kMaxCellWindow = NR + 1;  // fullest time cell the sweep's register sort covers
   static_assert(TEAMS == 1 || BLOCK == 64, "teams of more than one wave have no barrier of their own");
@@ -364,7 +373,7 @@ __global__ __launch_bounds__(BLOCK * TEAMS, (Lds<BLOCK, NR, TEAMS, RMAX, PERWAVE
   uint32_t* wtot = reinterpret_cast<uint32_t*>(smem + L::wtot);
   uint32_t* ptot = reinterpret_cast<uint32_t*>(smem + L::ptot);
 
-  auto seldom = [](bool x) -> bool { return NR == 4 ? x : rare(x); };  // (where a ring begins or ends: in most rounds of small workgroups)
+  auto seldom = [](bool x) -> bool { return NR == 4 || SMALL ? x : rare(x); };  // (where a ring begins or ends: in most rounds of small workgroups)
   constexpr uint32_t NPOS = L::npos, NCELL = L::ncell;
   constexpr uint32_t kSlotShift = (BLOCK == 1024 ? 14 : BLOCK == 256 ? 12 : 10) + 4;
   // The last four words of the clock array are padding that no position maps to, and the metadata
@@ -490,9 +499,10 @@ __global__ __launch_bounds__(BLOCK * TEAMS, (Lds<BLOCK, NR, TEAMS, RMAX, PERWAVE
     // never counts as a step back in time.
     uint32_t t[NR], mq[NR / 4];  // clocks; metadata bytes, record i in byte i & 3 of word i >> 2
     uint32_t holes = 0;          // bit i: place i has a slot that holds a record, but not its own
+    uint32_t oldest = 0;         // (small rings) bits j, 8 + j, 16 + j: the even place of round j is rank 0, rank 1, the last one
     // Rings of at least 128 slots: a round is one recorded wave's, and what there is to know of that is uniform; of at least
     // a hardware wave's share: so are all its rounds.
-    const bool whole_rings = cap >= kWaveSpan, small_rings = cap < 128u;
+    const bool whole_rings = RINGS == kWhole || (RINGS == kAny && cap >= kWaveSpan);
     const uint32_t wave_here = pbase >> cl2;
     uint32_t held_here = 0, first_here = 0;  // records held by that wave, its first surviving seq
     if (whole_rings && wave_here < W) {
@@ -562,7 +572,7 @@ __global__ __launch_bounds__(BLOCK * TEAMS, (Lds<BLOCK, NR, TEAMS, RMAX, PERWAVE
             check(j, wave_here, held_here, first_here, slot_here + 128u * j + 2u * lane, slot_here + 128u * j + 128u <= held_here, e0, e0 + 1u);
           }
         }
-      } else if (!small_rings) {
+      } else if (!SMALL) {
 #pragma unroll
         for (int j = 0; j < NR / 2; ++j) {
           const uint32_t p0 = pbase + 128u * j, w = p0 >> cl2, slot = p0 & capm;
@@ -581,6 +591,7 @@ __global__ __launch_bounds__(BLOCK * TEAMS, (Lds<BLOCK, NR, TEAMS, RMAX, PERWAVE
           const uint32_t q = qe + 128u * j, s0 = q & capm, wv = q >> cl2, w = wv < KP_MAX_WAVES ? wv : KP_MAX_WAVES;  // (entry KP_MAX_WAVES: no records)
           const uint2 vf = sVF[w];
           const uint32_t k0 = (s0 - vf.y) & capm, base = vf.y + (w << 20);
+          oldest |= (k0 == 0u ? 1u << j : 0u) | (k0 == 1u ? 0x100u << j : 0u) | (k0 == capm ? 0x10000u << j : 0u);
           check(j, w, vf.x, vf.y, s0, __builtin_amdgcn_ballot_w64(s0 + 1u >= vf.x) == 0ull, base + k0, base + ((k0 + 1u) & capm));
         }
       }
@@ -706,11 +717,13 @@ __global__ __launch_bounds__(BLOCK * TEAMS, (Lds<BLOCK, NR, TEAMS, RMAX, PERWAVE
       // Masks of rounds: those in which a ring begins (but for the first, whose record below is known), and those that may
       // hold the oldest record of a ring.
       uint32_t begins_in = 0u, oldest_in = 0u;
+      uint2 last_of = make_uint2(0u, 0u);  // lane w & 15: the record in the last slot of wave w's ring
       if (whole_rings) {
         oldest_in = to_oldest < kWaveSpan ? 1u << (to_oldest >> 7) : 0u;
-      } else if (small_rings) {
+      } else if (SMALL) {
         begins_in = oldest_in = 0xFFFFFFFFu;
       } else {
+        last_of = ring_end[lane & 15u];
 #pragma unroll
         for (int j = 0; j < NR / 2; ++j) {
           const uint32_t p0 = pbase + 128u * j, T = (uint32_t)__builtin_amdgcn_readlane((int)h_total, (int)((p0 >> cl2) & 15u));
@@ -736,21 +749,27 @@ __global__ __launch_bounds__(BLOCK * TEAMS, (Lds<BLOCK, NR, TEAMS, RMAX, PERWAVE
           pt[h] = wave_shr1(t[2 * j + 1], j == 0 ? below.x : wave_ror1(t[j == 0 ? 0 : 2 * j - 1]));
           own_t[h] = t[2 * j];
           if (seldom((begins_in >> j) & 1u)) {  // the record below the first slot of a ring is the one in its last
-            const uint32_t q = qe + 128u * j, w = q >> cl2;
-            const uint2 e = ring_end[w & 15u];
+            const uint32_t q = qe + 128u * j, w = SMALL ? q >> cl2 : (pbase + 128u * j) >> cl2;
+            const uint2 e = SMALL ? ring_end[w & 15u] : make_uint2((uint32_t)__builtin_amdgcn_readlane((int)last_of.x, (int)(w & 15u)),
+                                                                    (uint32_t)__builtin_amdgcn_readlane((int)last_of.y, (int)(w & 15u)));
             if ((q & capm) == 0u) {
               pt[h] = e.x;
               p4 = (p4 & ~(0xFFu << (16 * h))) | (e.y << (16 * h));
             }
           }
           if (seldom((oldest_in >> j) & 1u)) {  // nothing below rank 0, nothing to look for below rank 1
-            const uint32_t q = qe + 128u * j, s0 = q & capm, wv = q >> cl2, w = wv < KP_MAX_WAVES ? wv : KP_MAX_WAVES;
-            const uint32_t rot = sVF[w].y & capm;
-            const bool lowest0 = s0 == rot, lowest1 = s0 + 1u == rot;
+            bool lowest0, lowest1, second0;
+            if constexpr (SMALL) {
+              lowest0 = (oldest >> j) & 1u; second0 = (oldest >> (8 + j)) & 1u; lowest1 = (oldest >> (16 + j)) & 1u;
+            } else {
+              const uint32_t p0 = pbase + 128u * j, s0 = (p0 & capm) + 2u * lane, T = (uint32_t)__builtin_amdgcn_readlane((int)h_total, (int)((p0 >> cl2) & 15u));
+              const uint32_t rot = flush || T < cap ? 0u : T & capm;
+              lowest0 = s0 == rot; lowest1 = s0 + 1u == rot; second0 = s0 == ((rot + 1u) & capm);
+            }
             p4 |= (lowest0 ? kEmpty << (16 * h) : 0u) | (lowest1 ? kEmpty << (16 * h + 8) : 0u);  // (region 63)
             pt[h] = lowest0 ? 0u : pt[h];
             own_t[h] = lowest1 ? 0u : own_t[h];
-            search &= ~((lowest0 || s0 == ((rot + 1u) & capm) ? 0x80u << (16 * h) : 0u) | (lowest1 || lowest0 ? 0x8000u << (16 * h) : 0u));
+            search &= ~((lowest0 || second0 ? 0x80u << (16 * h) : 0u) | (lowest1 || lowest0 ? 0x8000u << (16 * h) : 0u));
           }
           // (a position without a record holds the largest clock, and so do all above it in its wave)
           n_nonmono += count(t[2 * j] < pt[h]) + count(t[2 * j + 1] < own_t[h]);
@@ -772,13 +791,13 @@ __global__ __launch_bounds__(BLOCK * TEAMS, (Lds<BLOCK, NR, TEAMS, RMAX, PERWAVE
           const uint32_t q = qe + 128u * j;  // even position; the odd one is q + 1
           const bool e0 = (near4 & (0x80u << (16 * h))) != 0u, e1 = (near4 & (0x8000u << (16 * h))) != 0u;
           // a START that is not in the lane below: in the last place of a hardware wave, or of a ring
-          if (j == 0 && !small_rings) {
+          if (j == 0 && !SMALL) {
             if (e0 && lane == 0u) { meta[slot_here == 0u ? q + capm : q - 1u] = (uint8_t)kPaired; marked = !whole_rings; }
           } else if (seldom((begins_in >> j) & 1u)) {
             if (e0 && (q & capm) == 0u) { meta[q + capm] = (uint8_t)kPaired; marked = true; }
           }
           uint32_t row = ((pbase + 128u * j) >> cl2) * R;
-          if (rare(small_rings)) row = (uint32_t)__builtin_amdgcn_ds_bpermute((int)(lane << 2), (int)(__umul24(q >> cl2, R)));  // (its own: kept out of the straight line)
+          if constexpr (SMALL) row = __umul24(q >> cl2, R);
           const uint32_t m0 = (m4 >> (16 * h)) & kRegion, m1 = (m4 >> (16 * h + 8)) & kRegion;
           const uint32_t d0 = t[2 * j] - pt[h], d1 = t[2 * j + 1] - t[2 * j];
           if (e0 || e1) account_row(row, e1 ? m1 : m0, e1 ? d1 : d0);
@@ -1021,8 +1040,8 @@ __global__ __launch_bounds__(BLOCK * TEAMS, (Lds<BLOCK, NR, TEAMS, RMAX, PERWAVE
       // When clock and region fit one word and no cell holds more than kMaxCellWindow records, the records stay
       // in arrival order inside their cell here and every lane of the sweep sorts a window of the sequence
       // in registers; otherwise the records are ranked inside their cell first.
-      const bool window_sort = R <= 16u && misc[2] < (1u << 26) && !tmp[T_WIDE] && tmp[T_MAXCELL] <= kMaxCellWindow;
-      if (!rare(!window_sort)) {
+      const bool window_sort = !MANY && R <= 16u && misc[2] < (1u << 26) && !tmp[T_WIDE] && tmp[T_MAXCELL] <= kMaxCellWindow;
+      if (MANY ? false : !rare(!window_sort)) {
         // the word the sweep sorts: clock << 6 | END << 5 | region (no branch: what is no event writes one unused word)
         // (opaque here: what both ways compute from these would otherwise be computed ahead of the choice between them)
 #pragma unroll
@@ -1175,7 +1194,7 @@ __global__ __launch_bounds__(BLOCK * TEAMS, (Lds<BLOCK, NR, TEAMS, RMAX, PERWAVE
             }
           }
         };
-        if (!rare(!window_sort)) {
+        if (MANY ? false : !rare(!window_sort)) {
           // ---- the order is finished in registers; one word per record from here on ------------------
           uint32_t key[NR];
           const uint32_t fake = (misc[2] << 6) | 0x3Fu;
@@ -1471,9 +1490,9 @@ __global__ __launch_bounds__(BLOCK * TEAMS, (Lds<BLOCK, NR, TEAMS, RMAX, PERWAVE
 // Launch shape of one kernel instantiation for one LDS size, queried once per device.
 struct LaunchCache { int dev = -1; uint32_t max_grid = 0; };
 
-template <int BLOCK, int NR, int TEAMS, int PLANES, int RMAX, int PERWAVE>
+template <int BLOCK, int NR, int TEAMS, int PLANES, int RMAX, int PERWAVE, int RINGS, bool MANY>
 kp_status launch_main(const DecodeParams& p, hipStream_t s) {
-  auto kern = kp_reduce_main<BLOCK, NR, TEAMS, PLANES, RMAX, PERWAVE>;
+  auto kern = kp_reduce_main<BLOCK, NR, TEAMS, PLANES, RMAX, PERWAVE, RINGS, MANY>;
   static thread_local LaunchCache cache;
   int dev = 0;
   KP_HIP_TRY(hipGetDevice(&dev));
@@ -1493,13 +1512,24 @@ kp_status launch_main(const DecodeParams& p, hipStream_t s) {
   return KP_OK;
 }
 
-template <int BLOCK, int NR, int TEAMS, int RMAX, int PERWAVE>
+template <int BLOCK, int NR, int TEAMS, int RMAX, int PERWAVE, int RINGS, bool MANY>
+kp_status launch_rings(const DecodeParams& p, hipStream_t s) {
+  // counters of open waves per region run up to the number of waves
+  if (p.W < 16) return launch_main<BLOCK, NR, TEAMS, 4, RMAX, PERWAVE, RINGS, MANY>(p, s);
+  return launch_main<BLOCK, NR, TEAMS, 5, RMAX, PERWAVE, RINGS, MANY>(p, s);
+}
+
+template <int BLOCK, int NR, int TEAMS, int RMAX, int PERWAVE, bool MANY = false>
 kp_status launch_planes(DecodeParams& p, hipStream_t s) {
   p.ncopy = 4;  // as many copies of the per-(wave, region) sums as their LDS array has room for
   while (p.ncopy > 1 && p.ncopy * p.W * p.R > (uint32_t)PERWAVE) p.ncopy >>= 1;
-  // counters of open waves per region run up to the number of waves
-  if (p.W < 16) return launch_main<BLOCK, NR, TEAMS, 4, RMAX, PERWAVE>(p, s);
-  return launch_main<BLOCK, NR, TEAMS, 5, RMAX, PERWAVE>(p, s);
+  if constexpr (BLOCK * NR <= 1024) {  // (16 waves with rings of 64 slots have 1024 in all)
+    if (p.cap < 128u) return launch_rings<BLOCK, NR, TEAMS, RMAX, PERWAVE, kSmall, MANY>(p, s);
+  }
+  if constexpr (TEAMS == 1 && BLOCK > 64) {
+    return p.cap < 64u * NR ? launch_rings<BLOCK, NR, TEAMS, RMAX, PERWAVE, kPart, MANY>(p, s) : launch_rings<BLOCK, NR, TEAMS, RMAX, PERWAVE, kWhole, MANY>(p, s);
+  }
+  return launch_rings<BLOCK, NR, TEAMS, RMAX, PERWAVE, kAny, MANY>(p, s);
 }
 
 kp_status reduce_impl(const void* raw, size_t n, const kp_trace_hdr& h, void* out_stats, uint32_t stop_after,
@@ -1567,25 +1597,32 @@ kp_status reduce_impl(const void* raw, size_t n, const kp_trace_hdr& h, void* ou
     // of 16 x 64 90 -> 42; 256 threads, arrays for 8 regions: 16000 of 2 x 1024 693 -> 487.
     kp_status st;
     if (h.n_wg <= 256 && nrec <= 4096) {
-      st = nrec > 1024 ? launch_planes<1024, 4, 1, KP_MAX_REGIONS, kMaxPerWave>(p, s)
-         : nrec > 256  ? launch_planes<256, 4, 1, KP_MAX_REGIONS, 512>(p, s)
-                       : launch_planes<64, 4, 1, KP_MAX_REGIONS, 512>(p, s);
+      if (R <= 16)
+        st = nrec > 1024 ? launch_planes<1024, 4, 1, KP_MAX_REGIONS, kMaxPerWave>(p, s)
+           : nrec > 256  ? launch_planes<256, 4, 1, KP_MAX_REGIONS, 512>(p, s)
+                         : launch_planes<64, 4, 1, KP_MAX_REGIONS, 512>(p, s);
+      else
+        st = nrec > 1024 ? launch_planes<1024, 4, 1, KP_MAX_REGIONS, kMaxPerWave, true>(p, s)
+           : nrec > 256  ? launch_planes<256, 4, 1, KP_MAX_REGIONS, 512, true>(p, s)
+                         : launch_planes<64, 4, 1, KP_MAX_REGIONS, 512, true>(p, s);
     } else if (nrec > 4096) {
       st = launch_planes<1024, 16, 1, KP_MAX_REGIONS, kMaxPerWave>(p, s);
     } else if (nrec > 1024) {
       st = R <= 8 ? launch_planes<256, 16, 1, 8, 128>(p, s) : R <= 16 ? launch_planes<256, 16, 1, 16, 256>(p, s)
-                                                           : launch_planes<256, 16, 1, KP_MAX_REGIONS, 512>(p, s);
+                                                           : launch_planes<256, 16, 1, KP_MAX_REGIONS, 512, true>(p, s);
     } else if (nrec > 256) {
       st = R <= 8 ? launch_planes<64, 16, 12, 8, 128>(p, s) : R <= 16 ? launch_planes<64, 16, 12, 16, 256>(p, s)
-                                                           : launch_planes<64, 16, 6, KP_MAX_REGIONS, 512>(p, s);
+                                                           : launch_planes<64, 16, 6, KP_MAX_REGIONS, 512, true>(p, s);
     } else {
       st = R <= 8 ? launch_planes<64, 4, 16, 8, 128>(p, s) : R <= 16 ? launch_planes<64, 4, 12, 16, 256>(p, s)
-                                                           : launch_planes<64, 4, 8, KP_MAX_REGIONS, 512>(p, s);
+                                                           : launch_planes<64, 4, 8, KP_MAX_REGIONS, 512, true>(p, s);
     }
     if (st != KP_OK) return st;
   }
   if (main_end) KP_HIP_TRY(hipEventRecord(main_end, s));
-  hipLaunchKernelGGL(kp_reduce_derive, dim3(1), dim3(1024), 0, s, out, h.n_wg, W, R);
+  // 16 threads per histogram row, one per region pair
+  const uint32_t derive = R > 32u ? 1024u : ((R < 16u ? 16u : R) * R + 63u) & ~63u;
+  hipLaunchKernelGGL(kp_reduce_derive, dim3(1), dim3(derive), 0, s, out, h.n_wg, W, R);
   KP_HIP_TRY(hipGetLastError());
   return KP_OK;
 }
