@@ -1081,17 +1081,37 @@ __global__ __launch_bounds__(BLOCK * TEAMS, (Lds<BLOCK, NR, TEAMS, RMAX, PERWAVE
       team_sync<BLOCK>();
       if (stop_after == kStepPlaced) break;
       // rank among the records of the same cell: by clock, then by arrival slot
+      // (the reads of all of a lane's records together: 4094 workgroups of 8 x 512, 32 regions 252.6 -> 246.0 us, 31 of 8 x 128, 24 regions
+      // 19.0 -> 18.2; one-wave teams, whose cells are emptier, are better off record by record: 65534 of 1 x 512 926 / 987)
+      if constexpr (MANY && TEAMS == 1) {
+        uint32_t most = 0, before[NR];
 #pragma unroll
-      for (int i = 0; i < NR; ++i) {
-        const uint32_t n = nm[i] & 0xFFFFu, s0 = ca[i], mine = nm[i] >> 16, t0 = t[i];
-        uint32_t before = 0;
-        for (uint32_t it = 0; __builtin_amdgcn_ballot_w64(it < n); ++it) {
-          if (it < n) {
-            const uint32_t tm = clk[s0 + it];
-            before += (uint32_t)(tm < t0) | ((uint32_t)(tm == t0) & (uint32_t)(it < mine));  // the record's own entry gives 0
+        for (int i = 0; i < NR; ++i) { const uint32_t n = nm[i] & 0xFFFFu; most = n > most ? n : most; before[i] = 0u; }
+        for (uint32_t it = 0; __builtin_amdgcn_ballot_w64(it < most); ++it) {
+          uint32_t tm[NR];
+#pragma unroll
+          for (int i = 0; i < NR; ++i) tm[i] = clk[it < (nm[i] & 0xFFFFu) ? ca[i] + it : kSpareWord];
+#pragma unroll
+          for (int i = 0; i < NR; ++i) {
+            const bool lower = tm[i] < t[i] || (tm[i] == t[i] && it < (nm[i] >> 16));  // the record's own entry gives none
+            before[i] += it < (nm[i] & 0xFFFFu) && lower ? 1u : 0u;
           }
         }
-        ca[i] = s0 + before;
+#pragma unroll
+        for (int i = 0; i < NR; ++i) ca[i] += before[i];
+      } else {
+#pragma unroll
+        for (int i = 0; i < NR; ++i) {
+          const uint32_t n = nm[i] & 0xFFFFu, s0 = ca[i], mine = nm[i] >> 16, t0 = t[i];
+          uint32_t before = 0;
+          for (uint32_t it = 0; __builtin_amdgcn_ballot_w64(it < n); ++it) {
+            if (it < n) {
+              const uint32_t tm = clk[s0 + it];
+              before += (uint32_t)(tm < t0) | ((uint32_t)(tm == t0) & (uint32_t)(it < mine));  // the record's own entry gives 0
+            }
+          }
+          ca[i] = s0 + before;
+        }
       }
       team_sync<BLOCK>();
       if (stop_after == kStepRanked) break;
@@ -1515,8 +1535,11 @@ kp_status launch_main(const DecodeParams& p, hipStream_t s) {
 template <int BLOCK, int NR, int TEAMS, int RMAX, int PERWAVE, int RINGS, bool MANY>
 kp_status launch_rings(const DecodeParams& p, hipStream_t s) {
   // counters of open waves per region run up to the number of waves
-  if (p.W < 16) return launch_main<BLOCK, NR, TEAMS, 4, RMAX, PERWAVE, RINGS, MANY>(p, s);
-  return launch_main<BLOCK, NR, TEAMS, 5, RMAX, PERWAVE, RINGS, MANY>(p, s);
+  constexpr int kShortest = RINGS == kSmall ? 2 : RINGS == kWhole ? 64 * NR : 128;
+  if constexpr (16 * kShortest <= BLOCK * NR) {  // (else 16 waves have more records than this form takes)
+    if (p.W == 16) return launch_main<BLOCK, NR, TEAMS, 5, RMAX, PERWAVE, RINGS, MANY>(p, s);
+  }
+  return launch_main<BLOCK, NR, TEAMS, 4, RMAX, PERWAVE, RINGS, MANY>(p, s);
 }
 
 template <int BLOCK, int NR, int TEAMS, int RMAX, int PERWAVE, bool MANY = false>
@@ -1526,10 +1549,11 @@ kp_status launch_planes(DecodeParams& p, hipStream_t s) {
   if constexpr (BLOCK * NR <= 1024) {  // (16 waves with rings of 64 slots have 1024 in all)
     if (p.cap < 128u) return launch_rings<BLOCK, NR, TEAMS, RMAX, PERWAVE, kSmall, MANY>(p, s);
   }
-  if constexpr (TEAMS == 1 && BLOCK > 64) {
+  if constexpr ((TEAMS == 1 && BLOCK > 64) || (NR == 16 && !MANY)) {
     return p.cap < 64u * NR ? launch_rings<BLOCK, NR, TEAMS, RMAX, PERWAVE, kPart, MANY>(p, s) : launch_rings<BLOCK, NR, TEAMS, RMAX, PERWAVE, kWhole, MANY>(p, s);
+  } else {
+    return launch_rings<BLOCK, NR, TEAMS, RMAX, PERWAVE, kAny, MANY>(p, s);
   }
-  return launch_rings<BLOCK, NR, TEAMS, RMAX, PERWAVE, kAny, MANY>(p, s);
 }
 
 kp_status reduce_impl(const void* raw, size_t n, const kp_trace_hdr& h, void* out_stats, uint32_t stop_after,
@@ -1596,7 +1620,13 @@ kp_status reduce_impl(const void* raw, size_t n, const kp_trace_hdr& h, void* ou
     // 76 us (16 records per lane in teams 168), 60000 of 1 x 64, 16 regions 1084 -> 219 (490), 8192 of 4 x 128 172 -> 73, 3000
     // of 16 x 64 90 -> 42; 256 threads, arrays for 8 regions: 16000 of 2 x 1024 693 -> 487.
     kp_status st;
-    if (h.n_wg <= 256 && nrec <= 4096) {
+    // Of 257 to 1024 records some more of them are few in that sense: three decoder workgroups of 256 threads fit a CU, and until
+    // their totals queue up on the way to HBM they beat waves that take 16 records a lane (257 to 1024 records: with four records
+    // a lane / 16, us): 300 of 2 x 256, 5 regions 24.2 / 27.9, 600 35.9 / 29.2; 300 of 8 x 128, 16 regions 20.5 / 27.2, 600 27.5 /
+    // 27.4, 768 31.2 / 27.7; with 24 regions, of which 16 records a lane leave room for six waves on a CU, 300 of 16 x 32 24.4 / 38.9,
+    // 1200 38.0 / 42.5, 1536 45.7 / 44.7.
+    const uint32_t few = nrec <= 256 || nrec > 1024 ? 256u : R <= 16 ? 400u : 1400u;
+    if (h.n_wg <= few && nrec <= 4096) {
       if (R <= 16)
         st = nrec > 1024 ? launch_planes<1024, 4, 1, KP_MAX_REGIONS, kMaxPerWave>(p, s)
            : nrec > 256  ? launch_planes<256, 4, 1, KP_MAX_REGIONS, 512>(p, s)
