@@ -1650,9 +1650,7 @@ kp_status reduce_impl(const void* raw, size_t n, const kp_trace_hdr& h, void* ou
     if (st != KP_OK) return st;
   }
   if (main_end) KP_HIP_TRY(hipEventRecord(main_end, s));
-  // 16 threads per histogram row, one per region pair
-  const uint32_t derive = R > 32u ? 1024u : ((R < 16u ? 16u : R) * R + 63u) & ~63u;
-  hipLaunchKernelGGL(kp_reduce_derive, dim3(1), dim3(derive), 0, s, out, h.n_wg, W, R);
+  hipLaunchKernelGGL(kp_reduce_derive, dim3(1), dim3(1024), 0, s, out, h.n_wg, W, R);
   KP_HIP_TRY(hipGetLastError());
   return KP_OK;
 }
