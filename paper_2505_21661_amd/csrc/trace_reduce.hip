@@ -52,7 +52,7 @@ constexpr uint32_t kSeqMask = 0xFFFFFu;
 constexpr uint32_t kRegion = 0x3Fu, kEmpty = 0x3Fu, kPaired = 0x40u, kEnd = 0x80u;
 constexpr uint32_t kMaxRecPerWg = 16384;
 constexpr uint32_t kMaxLds = 160 * 1024;
-constexpr uint32_t kHistStride = 65;  // histogram rows 65 words apart: equal bins of different regions, different banks
+constexpr uint32_t kBins = 32, kHistStride = 33;  // (durations have 32 bits) histogram rows an odd number of words apart: equal bins of different regions, different banks
 
 // rings of less than 128 slots; of 128 and more, so that a round is one recorded wave's, but less than a hardware wave's share; of at
 // least that share; either of the last two
@@ -375,7 +375,7 @@ __global__ __launch_bounds__(BLOCK * TEAMS, (Lds<BLOCK, NR, TEAMS, RMAX, PERWAVE
 
   auto seldom = [](bool x) -> bool { return NR == 4 || SMALL ? x : rare(x); };  // (where a ring begins or ends: in most rounds of small workgroups)
   constexpr uint32_t NPOS = L::npos, NCELL = L::ncell;
-  constexpr uint32_t kSlotShift = (BLOCK == 1024 ? 14 : BLOCK == 256 ? 12 : 10) + 4;
+  constexpr uint32_t kSlotShift = (BLOCK == 1024 ? 14 : BLOCK == 512 ? 13 : BLOCK == 256 ? 12 : BLOCK == 128 ? 11 : 10) + 4;
   // The last four words of the clock array are padding that no position maps to, and the metadata
   // array has 16 spare bytes: stores of lanes that have nothing to store go there instead of branching.
   constexpr uint32_t kSpareWord = NPOS + NPOS / 16 - 1;
@@ -1491,9 +1491,9 @@ __global__ __launch_bounds__(BLOCK * TEAMS, (Lds<BLOCK, NR, TEAMS, RMAX, PERWAVE
 
   // ---- flush this decoder workgroup's totals --------------------------------------------------
   unsigned long long* out = reinterpret_cast<unsigned long long*>(p.out);
-  for (uint32_t i = threadIdx.x; i < R * 64; i += n_threads) {
-    const uint32_t h = hist[(i >> 6) * kHistStride + (i & 63u)];
-    if (h) atomicAdd(&out[SL.hist + i], (unsigned long long)h);
+  for (uint32_t i = threadIdx.x; i < R * kBins; i += n_threads) {
+    const uint32_t r = i / kBins, bin = i % kBins, h = hist[r * kHistStride + bin];
+    if (h) atomicAdd(&out[SL.hist + r * 64u + bin], (unsigned long long)h);
   }
   for (uint32_t i = threadIdx.x; i < R * R; i += n_threads)
     if (oacc[i]) atomicAdd(&out[SL.F + i], oacc[i]);  // (the upper triangle)
@@ -1625,6 +1625,12 @@ kp_status reduce_impl(const void* raw, size_t n, const kp_trace_hdr& h, void* ou
     // a lane / 16, us): 300 of 2 x 256, 5 regions 24.2 / 27.9, 600 35.9 / 29.2; 300 of 8 x 128, 16 regions 20.5 / 27.2, 600 27.5 /
     // 27.4, 768 31.2 / 27.7; with 24 regions, of which 16 records a lane leave room for six waves on a CU, 300 of 16 x 32 24.4 / 38.9,
     // 1200 38.0 / 42.5, 1536 45.7 / 44.7.
+    // From 1024 records up the threads are as many as the records need, to the next power of two: with half of the places empty the
+    // other half's waves come along to every barrier and every step, and two workgroups fit where one did.  512 threads against 1024:
+    // 16384 of 8 x 1024, 16 regions 1622 -> 757 us, 510 of 16 x 512 72.4 -> 41.9, 100 of 8 x 1024 35.9 -> 27.1, 4000 of 8 x 1024, 24
+    // regions 593 -> 324 (with more than 256 sums per workgroup one to a CU: 510 of 16 x 512, 32 regions 102.5 -> 80.5); 128 against
+    // 256: 16000 of 2 x 1024 418 -> 215, 2000 of 8 x 256, 24 regions 127 -> 85, 300 of 2 x 1024 31.6 -> 30.2; but twice as many totals queue
+    // up: 2000 of 3 x 512, 5 regions 80 against 96, of 2 x 1024, 4 regions 64.6 / 67.7, 1500 55.8 / 55.6, 2500 79.7 / 71.1.
     const uint32_t few = nrec <= 256 || nrec > 1024 ? 256u : R <= 16 ? 400u : 1400u;
     if (h.n_wg <= few && nrec <= 4096) {
       if (R <= 16)
@@ -1635,6 +1641,12 @@ kp_status reduce_impl(const void* raw, size_t n, const kp_trace_hdr& h, void* ou
         st = nrec > 1024 ? launch_planes<1024, 4, 1, KP_MAX_REGIONS, kMaxPerWave, true>(p, s)
            : nrec > 256  ? launch_planes<256, 4, 1, KP_MAX_REGIONS, 512, true>(p, s)
                          : launch_planes<64, 4, 1, KP_MAX_REGIONS, 512, true>(p, s);
+    } else if (nrec > 4096 && nrec <= 8192) {
+      st = R <= 16 ? launch_planes<512, 16, 1, 16, 512>(p, s) : W * R <= 256 ? launch_planes<512, 16, 1, KP_MAX_REGIONS, 256, true>(p, s)
+                                                              : launch_planes<512, 16, 1, KP_MAX_REGIONS, 512, true>(p, s);
+    } else if (nrec > 1024 && nrec <= 2048 && (R > 8 || h.n_wg < 1500 || h.n_wg >= 2500)) {
+      st = R <= 8 ? launch_planes<128, 16, 1, 8, 128>(p, s) : R <= 16 ? launch_planes<128, 16, 1, 16, 256>(p, s)
+                                                           : launch_planes<128, 16, 1, KP_MAX_REGIONS, 512, true>(p, s);
     } else if (nrec > 4096) {
       st = launch_planes<1024, 16, 1, KP_MAX_REGIONS, kMaxPerWave>(p, s);
     } else if (nrec > 1024) {

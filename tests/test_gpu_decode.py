@@ -140,7 +140,9 @@ def test_every_form_of_the_decoder_over_several_turns(kp, oracle_mod, n_wg, W, R
     (300, 1, 5, 1024), (300, 4, 16, 128), (300, 16, 20, 32),
     (40, 8, 5, 512), (40, 4, 5, 256), (40, 4, 5, 128), (40, 8, 5, 64), (40, 1, 3, 256), (40, 2, 3, 64), (300, 2, 8, 128),  # four
     (40, 1, 20, 4096), (40, 8, 20, 512), (40, 4, 20, 256), (40, 4, 32, 128), (40, 16, 20, 64), (40, 1, 20, 256), (40, 2, 20, 64),  # more than 16 regions
-    (400, 8, 16, 64), (401, 8, 16, 64), (1400, 3, 17, 128), (1401, 3, 17, 128), (300, 1, 3, 1024)])  # either side of the line between 256 threads and one wave
+    (400, 8, 16, 64), (401, 8, 16, 64), (1400, 3, 17, 128), (1401, 3, 17, 128), (300, 1, 3, 1024),  # either side of the line between 256 threads and one wave
+    (260, 8, 16, 1024), (260, 4, 24, 2048), (260, 16, 32, 512), (20, 1, 3, 8192), (260, 3, 16, 2048),  # 512 threads
+    (300, 16, 16, 128), (300, 2, 20, 1024), (300, 1, 3, 2048), (1500, 2, 8, 1024)])  # 128, the last one not
 def test_the_oldest_record_anywhere_in_the_ring(kp, oracle_mod, n_wg, W, R, cap):
     """Records are paired where they lie, in the order of a ring that begins with its oldest one: rings that wrapped by any
     number of records or not at all, oldest records that are ENDs, STARTs and ENDs of a pair at the two ends of a ring and of
