@@ -26,7 +26,7 @@
 //      a matrix product, taken by the matrix cores 64 stretches at a time;
 //   E  the per-(workgroup, wave, region) results go to HBM and into running totals, which live in
 //      LDS and reach HBM once per decoder workgroup.
-// What bounds it is instruction issue: 2.6 vector instructions per record (3.2 with every record scattered to LDS by its
+// What bounds it is instruction issue: 2.5 vector instructions per record (3.2 with every record scattered to LDS by its
 // rank and read back, one round at a time in B, planes in the prefix sum): 16384 workgroups of 8 x 2048 records 1775 -> 1550
 // us; 4000 of 4 x 1024, wrapped 125 -> 114; 256 of 8 x 512 28.7 -> 27.1; 512 of 8 x 2048, regions three deep 389 -> 219.
 // A kernel of its own per class of ring sizes (RINGS), and for more than 16 regions (MANY), instead of one that chooses:
@@ -1083,7 +1083,8 @@ __global__ __launch_bounds__(BLOCK * TEAMS, (Lds<BLOCK, NR, TEAMS, RMAX, PERWAVE
       // rank among the records of the same cell: by clock, then by arrival slot
       // (the reads of all of a lane's records together: 4094 workgroups of 8 x 512, 32 regions 252.6 -> 246.0 us, 31 of 8 x 128, 24 regions
       // 19.0 -> 18.2; one-wave teams, whose cells are emptier, are better off record by record: 65534 of 1 x 512 926 / 987)
-      if constexpr (MANY && TEAMS == 1) {
+      // (so are two workgroups of 512 threads per CU, which have 128 registers for it: 4000 of 8 x 1024, 24 regions 304 / 326)
+      if constexpr (MANY && TEAMS == 1 && (BLOCK != 512 || PERWAVE > 256)) {
         uint32_t most = 0, before[NR];
 #pragma unroll
         for (int i = 0; i < NR; ++i) { const uint32_t n = nm[i] & 0xFFFFu; most = n > most ? n : most; before[i] = 0u; }
