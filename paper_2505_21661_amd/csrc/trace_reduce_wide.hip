@@ -1054,7 +1054,9 @@ kp_status launch_wide(const uint32_t* wg_hdrs, const void* records, uint64_t* ou
   // (With more than one window each, two of them take 1.9 times as long as one of 1024 threads alone and one that is left over
   // 1.4 times: a last turn of at most one to a CU pays only behind three full ones.  582 of 7 x 1024, 64 regions 110 us, 126 this way.)
   const bool full_turns = p.nrec <= 4096u || p.n_wg >= 1536u || (p.n_wg - 1u) % 512u >= 256u;
-  if (p.n_wg > 256u && full_turns) {
+  // (One window of 8192 places is better than two or three of 4096: 1362 of 12 x 512, 40 regions 210 us against 231.)
+  const bool one_large = p.cap <= (8192u >> p.waves_log2) && p.cap > (4096u >> p.waves_log2);
+  if (p.n_wg > 256u && full_turns && !one_large) {
     p.lds = wide_lds(512u, 2u, p.W, p.R, p.cap);
     if (p.lds.total <= kMaxLds / 2u && p.lds.per_lane == 8u) return launch_words<512, 8>(p, s);
   }
