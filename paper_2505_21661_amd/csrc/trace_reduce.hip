@@ -1191,7 +1191,10 @@ __global__ __launch_bounds__(BLOCK * TEAMS, (Lds<BLOCK, NR, TEAMS, RMAX, PERWAVE
           }
         };
         // One record of the sequence for the general way of adding up: a region that switches on or off
-        // adds -t / +t to its sums with every region open at that instant (LDS atomics).
+        // adds -t / +t to its sums with every region open at that instant (LDS atomics).  Here the records of one clock come in
+        // any order: where waves end a region and start it again, its count may run past the last one that the planes hold
+        // and the region is off for a moment.  It counts as switched whenever it changes, on whichever record, so that what
+        // is added on one clock for such a moment cancels.
         auto switch_record = [&](uint32_t x, uint32_t dm, uint32_t tt) {
           uint32_t act_before = pl[0];
 #pragma unroll
@@ -1200,14 +1203,13 @@ __global__ __launch_bounds__(BLOCK * TEAMS, (Lds<BLOCK, NR, TEAMS, RMAX, PERWAVE
           uint32_t act_after = pl[0];
 #pragma unroll
           for (int k = 1; k < PLANES; ++k) act_after |= pl[k];
-          const uint32_t act = dm ? act_after : act_before;  // active regions other than this one
-          if (x & ~act) {  // the region was off before this START / is off after this END
+          if (act_before != act_after) {  // (in the bit of this region)
             // modulo 2^32: the totals of one workgroup lie below its span, which is below 2^32
             const uint32_t a = __ffs(x) - 1;
             uint32_t* row = oacc32 + a * (R | 1u);
-            const uint32_t val = dm ? tt : 0u - tt;
+            const uint32_t val = act_after & x ? 0u - tt : tt;
             atomicAdd(&row[a], val);
-            uint32_t set = act & region_bits;
+            uint32_t set = act_before & act_after & region_bits;  // the others
             while (set) {
               const uint32_t bb = __ffs(set) - 1;
               set &= set - 1;

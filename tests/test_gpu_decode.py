@@ -424,3 +424,48 @@ def test_a_thread_that_read_a_header_ends_during_a_capture(kp, oracle_mod):
         graph.replay()
         torch.cuda.synchronize()
         assert np.array_equal(want, outs[0].cpu().numpy())
+
+
+def restart_trace(seed, n_wg, W, R, cap, most):
+    """All waves are in region 0 and restart it now and then: up to `most` of them end it and start it again on one tick, on
+    which another wave may open or close a further region.  Two dozen workgroups, over and over: where in the clock-sorted
+    sequence a tick lies differs from one to the next."""
+    rng = np.random.default_rng(seed)
+    distinct = []
+    for i in range(min(n_wg, 24)):
+        waves = [[(S, 0, 40 * w)] for w in range(W)]
+        inner = [0] * W  # the further region a wave has open
+        t = 40 * W
+        for _ in range(i):
+            t += 400
+            if R > 1 and len(waves[i % W]) + 4 < cap:
+                waves[i % W] += [(S, 1 + i % (R - 1), t), (E, 1 + i % (R - 1), t + 200)]
+        for _ in range(200):
+            t += 400
+            able = [w for w in range(W) if inner[w] == 0 and len(waves[w]) + 5 <= cap]
+            again = [int(w) for w in rng.permutation(able)[:int(rng.integers(1, most + 1))]]
+            for w in again:
+                waves[w] += [(E, 0, t), (S, 0, t)]
+            other = int(rng.integers(0, W))
+            if R > 1 and other not in again and rng.random() < 0.7 and (inner[other] or len(waves[other]) + 5 <= cap):
+                r = inner[other] or int(rng.integers(1, R))
+                waves[other].append((E if inner[other] else S, r, t))
+                inner[other] = 0 if inner[other] else r
+            if not able and not any(inner):
+                break
+        for w in range(W):
+            t += 40
+            waves[w] += ([(E, inner[w], t)] if inner[w] else []) + [(E, 0, t)]
+            assert len(waves[w]) <= cap
+        distinct.append(inputs.events_to_wg(waves, cap, flush=False))
+    return inputs.encode_trace([distinct[i % len(distinct)] for i in range(n_wg)], W, R, cap, rec_cost=1)
+
+
+@pytest.mark.parametrize("n_wg,W,R,cap", [
+    (40, 15, 32, 64), (450, 15, 17, 64), (30, 12, 24, 256), (30, 16, 32, 256),                                   # more than 16 regions
+    (30, 15, 40, 256), (300, 15, 40, 128), (30, 16, 100, 128)])                                                   # more than 32
+def test_regions_that_restart_on_a_tick(kp, oracle_mod, n_wg, W, R, cap):
+    """An END and the START of the same region in one wave on one clock, in whichever order they come out of the sort: between the
+    two of them the region may seem to be open in more waves than the workgroup has."""
+    for most in (1, 2, 8, W):
+        check(restart_trace(most, n_wg, W, R, cap, most), oracle_mod, use_hdr=True)
