@@ -149,22 +149,24 @@ __device__ __forceinline__ void planes_add(uint32_t (&a)[PLANES], const uint32_t
   }
 }
 
-// counter[bit of x] += 1 (dm = 0) or -= 1 (dm = all ones); x is zero or one-hot.
+// counter[bit of x] += 1 (up = all ones) or -= 1 (up = 0); x is zero or one-hot.
 template <int PLANES>
-__device__ __forceinline__ void planes_step(uint32_t (&pl)[PLANES], uint32_t x, uint32_t dm) {
+__device__ __forceinline__ void planes_step(uint32_t (&pl)[PLANES], uint32_t x, uint32_t up) {
   uint32_t carry = x;
 #pragma unroll
-  for (int k = 0; k < PLANES; ++k) { const uint32_t o = pl[k]; pl[k] = o ^ carry; carry &= o ^ dm; }
+  for (int k = 0; k < PLANES; ++k) { const uint32_t o = pl[k]; pl[k] = o ^ carry; carry = __builtin_amdgcn_bitop3_b32(carry, o, up, 0x90); }  // carry & ~(o ^ up), which the compiler would make two instructions of
 }
 
-// The sweep works on one word per record of the sequence: clock << 6 | END << 5 | region; records with
-// equal words are interchangeable.  A place past the end of the sequence holds `fake`: the largest
+// The sweep works on one word per record of the sequence: clock << 6 | START << 5 | region; records with
+// equal words are interchangeable.  Of the records of one clock the ENDs come first: pairs of length 0 are not in the
+// sequence, so every END meets a count that has its START in it, and no count ever exceeds the number of waves, whichever
+// waves end a region and start it again on that clock.  A place past the end of the sequence holds `fake`: the largest
 // clock of the workgroup with a region number that no record has, so that it sorts last, opens no
 // region and the stretch in front of it has an honest length.
 // Fields of such a word.
 __device__ __forceinline__ uint32_t key_clock(uint32_t k) { return k >> 6; }
 __device__ __forceinline__ uint32_t key_region_bit(uint32_t k) { return 1u << (k & 31u); }  // bit 31 for a place past the end: above every region
-__device__ __forceinline__ uint32_t key_end_mask(uint32_t k) { return (uint32_t)__builtin_amdgcn_sbfe((int)k, 5, 1); }  // all ones for an END
+__device__ __forceinline__ uint32_t key_start_mask(uint32_t k) { return (uint32_t)__builtin_amdgcn_sbfe((int)k, 5, 1); }  // all ones for a START
 
 // Eight 4-bit numbers as planes: byte k of the result holds bit k of each.  Bit 4 r + k goes to 8 k + r: the five index
 // bits r2 r1 r0 k1 k0 become k1 k0 r2 r1 r0, by four exchanges of two of them.
@@ -1032,17 +1034,17 @@ __global__ __launch_bounds__(BLOCK * TEAMS, (Lds<BLOCK, NR, TEAMS, RMAX, PERWAVE
 #pragma unroll
       for (int i = 0; i < NR / 4; ++i) asm volatile("" : "+v"(mq[i]));
       auto cell_start = [&](uint32_t c) -> uint32_t { return (cells[c >> 1] >> ((c & 1u) << 4)) & 0xFFFFu; };
-      // sorted sequence entry besides the clock: END << 5 | region (four at a time)
+      // sorted sequence entry besides the clock: START << 5 | region (four at a time)
       uint32_t info[NR / 4];
 #pragma unroll
-      for (int x = 0; x < NR / 4; ++x) info[x] = (mq[x] & 0x1F1F1F1Fu) | ((mq[x] >> 2) & 0x20202020u);
+      for (int x = 0; x < NR / 4; ++x) info[x] = (mq[x] & 0x1F1F1F1Fu) | ((~mq[x] >> 2) & 0x20202020u);
       auto info_of = [&](int i) -> uint32_t { return (info[i >> 2] >> (8 * (i & 3))) & 0x3Fu; };
       // When clock and region fit one word and no cell holds more than kMaxCellWindow records, the records stay
       // in arrival order inside their cell here and every lane of the sweep sorts a window of the sequence
       // in registers; otherwise the records are ranked inside their cell first.
       const bool window_sort = !MANY && R <= 16u && misc[2] < (1u << 26) && !tmp[T_WIDE] && tmp[T_MAXCELL] <= kMaxCellWindow;
       if (MANY ? false : !rare(!window_sort)) {
-        // the word the sweep sorts: clock << 6 | END << 5 | region (no branch: what is no event writes one unused word)
+        // the word the sweep sorts: clock << 6 | START << 5 | region (no branch: what is no event writes one unused word)
         // (opaque here: what both ways compute from these would otherwise be computed ahead of the choice between them)
 #pragma unroll
         for (int i = 0; i < NR; ++i) asm volatile("" : "+v"(ca[i]));
@@ -1195,11 +1197,11 @@ __global__ __launch_bounds__(BLOCK * TEAMS, (Lds<BLOCK, NR, TEAMS, RMAX, PERWAVE
         // any order: where waves end a region and start it again, its count may run past the last one that the planes hold
         // and the region is off for a moment.  It counts as switched whenever it changes, on whichever record, so that what
         // is added on one clock for such a moment cancels.
-        auto switch_record = [&](uint32_t x, uint32_t dm, uint32_t tt) {
+        auto switch_record = [&](uint32_t x, uint32_t up, uint32_t tt) {
           uint32_t act_before = pl[0];
 #pragma unroll
           for (int k = 1; k < PLANES; ++k) act_before |= pl[k];
-          planes_step<PLANES>(pl, x, dm);
+          planes_step<PLANES>(pl, x, up);
           uint32_t act_after = pl[0];
 #pragma unroll
           for (int k = 1; k < PLANES; ++k) act_after |= pl[k];
@@ -1225,15 +1227,17 @@ __global__ __launch_bounds__(BLOCK * TEAMS, (Lds<BLOCK, NR, TEAMS, RMAX, PERWAVE
           else sorted_pairs<BLOCK, NR>(clk, tid, n_events, fake, key);
           if constexpr (PLANES == 4) {
             // Counts up to 15 of 16 regions are one number of 64 bits, four to each.  A sum of such numbers is right in every
-            // digit as long as the counts it stands for are, whatever it took and gave on the way: so the state before a
+            // digit as long as the counts it stands for are (from 0 to the number of waves behind every record: see the
+            // words' order), whatever it took and gave on the way: so the state before a
             // lane's stretch is a prefix sum of integers, and becomes planes at the end.
-            uint64_t net = 0;
+            uint64_t ended = 0;  // ENDs less STARTs
 #pragma unroll
-            for (int i = 0; i < NR; ++i) net += (uint64_t)((int64_t)(int32_t)(key_end_mask(key[i]) | 1u) << ((4u * key[i]) & 63u));
-            if (__builtin_amdgcn_ballot_w64(g0 + NR > n_events)) {  // a place past the end counted as an END of region 15
+            for (int i = 0; i < NR; ++i) ended += (uint64_t)((int64_t)(int32_t)(key_start_mask(key[i]) | 1u) << ((4u * key[i]) & 63u));
+            if (__builtin_amdgcn_ballot_w64(g0 + NR > n_events)) {  // a place past the end counted as a START of region 15
               const uint32_t past = g0 + NR > n_events ? (g0 > n_events ? (uint32_t)NR : g0 + NR - n_events) : 0u;
-              net += (uint64_t)past << 60;
+              ended += (uint64_t)past << 60;
             }
+            const uint64_t net = 0ull - ended;
             uint64_t incl = net;
             incl += scan_src64<0>(incl); incl += scan_src64<1>(incl); incl += scan_src64<2>(incl);
             incl += scan_src64<3>(incl); incl += scan_src64<4>(incl); incl += scan_src64<5>(incl);
@@ -1253,7 +1257,7 @@ __global__ __launch_bounds__(BLOCK * TEAMS, (Lds<BLOCK, NR, TEAMS, RMAX, PERWAVE
             for (int k = 0; k < 4; ++k) pl[k] = __builtin_amdgcn_perm(hi, lo, 0x0C0C0400u + 0x0101u * k);
           } else {
 #pragma unroll
-            for (int i = 0; i < NR; ++i) planes_step<PLANES>(pl, key_region_bit(key[i]), key_end_mask(key[i]));
+            for (int i = 0; i < NR; ++i) planes_step<PLANES>(pl, key_region_bit(key[i]), key_start_mask(key[i]));
             state_before(key_clock(key[0]));
           }
 #pragma unroll
@@ -1317,7 +1321,7 @@ __global__ __launch_bounds__(BLOCK * TEAMS, (Lds<BLOCK, NR, TEAMS, RMAX, PERWAVE
             uint32_t act_even = 0u;
 #pragma unroll
             for (int i = 0; i < NR; ++i) {
-              planes_step<PLANES>(pl, key_region_bit(key[i]), key_end_mask(key[i]));
+              planes_step<PLANES>(pl, key_region_bit(key[i]), key_start_mask(key[i]));
               uint32_t act = pl[0];
 #pragma unroll
               for (int k = 1; k < PLANES; ++k) act |= pl[k];
@@ -1345,13 +1349,13 @@ __global__ __launch_bounds__(BLOCK * TEAMS, (Lds<BLOCK, NR, TEAMS, RMAX, PERWAVE
             if (lane == 0) add_open(0u - key_clock(key[0]));
 #pragma unroll
             for (int i = 0; i < NR; ++i)
-              switch_record(key_region_bit(key[i]) & region_bits, key_end_mask(key[i]), key_clock(key[i]));
+              switch_record(key_region_bit(key[i]) & region_bits, key_start_mask(key[i]), key_clock(key[i]));
             if (lane == 63) add_open(t_next);
           }
         } else {
           // ---- the general way: the sequence is already in order, clocks up to 32 bits, up to 32 regions --
           uint32_t st[NR], sx[NR];  // clock, region bit (0: no record)
-          uint32_t ends = 0;           // bit i: record i is an END
+          uint32_t starts = 0;         // bit i: record i is a START
           uint32_t mw[NR / 4];
           load_meta(tid, mw);
           load_run<NR>(clk, tid, st);
@@ -1359,14 +1363,14 @@ __global__ __launch_bounds__(BLOCK * TEAMS, (Lds<BLOCK, NR, TEAMS, RMAX, PERWAVE
           for (int i = 0; i < NR; ++i) {
             const uint32_t info = (mw[i >> 2] >> (8 * (i & 3))) & 0xFFu;
             sx[i] = g0 + i < n_events ? 1u << (info & 31u) : 0u;
-            ends |= (info >> 5) << i;
+            starts |= ((info >> 5) & 1u) << i;
           }
-          auto end_mask = [&](int i) -> uint32_t { return (uint32_t)((int32_t)(ends << (31 - i)) >> 31); };  // all ones for an END
+          auto start_mask = [&](int i) -> uint32_t { return (uint32_t)((int32_t)(starts << (31 - i)) >> 31); };  // all ones for a START
 #pragma unroll
-          for (int i = 0; i < NR; ++i) planes_step<PLANES>(pl, sx[i], end_mask(i));
+          for (int i = 0; i < NR; ++i) planes_step<PLANES>(pl, sx[i], start_mask(i));
           state_before(st[0]);
 #pragma unroll
-          for (int i = 0; i < NR; ++i) switch_record(sx[i], end_mask(i), st[i]);
+          for (int i = 0; i < NR; ++i) switch_record(sx[i], start_mask(i), st[i]);
         }
       }
     }

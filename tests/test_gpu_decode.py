@@ -461,11 +461,16 @@ def restart_trace(seed, n_wg, W, R, cap, most):
     return inputs.encode_trace([distinct[i % len(distinct)] for i in range(n_wg)], W, R, cap, rec_cost=1)
 
 
+# with up to 15 waves the counts of open waves have four bits per region; every number of threads and of records per lane
 @pytest.mark.parametrize("n_wg,W,R,cap", [
+    (40, 15, 2, 16), (40, 15, 16, 64), (40, 15, 2, 64), (40, 14, 3, 256), (40, 15, 16, 256),                    # four records per lane
+    (260, 15, 2, 16), (450, 15, 2, 64), (450, 8, 3, 64), (450, 12, 16, 64), (260, 15, 3, 128), (260, 9, 16, 128),  # one wave, 128 threads
+    (260, 12, 2, 256), (260, 15, 16, 256), (30, 15, 3, 512), (30, 8, 16, 1024), (30, 9, 2, 1024),               # 256, 512, 1024 threads
+    (40, 16, 3, 64), (30, 16, 16, 1024), (30, 7, 3, 256),                                                        # five bits; counts that always fit
     (40, 15, 32, 64), (450, 15, 17, 64), (30, 12, 24, 256), (30, 16, 32, 256),                                   # more than 16 regions
     (30, 15, 40, 256), (300, 15, 40, 128), (30, 16, 100, 128)])                                                   # more than 32
 def test_regions_that_restart_on_a_tick(kp, oracle_mod, n_wg, W, R, cap):
-    """An END and the START of the same region in one wave on one clock, in whichever order they come out of the sort: between the
-    two of them the region may seem to be open in more waves than the workgroup has."""
+    """An END and the START of the same region in one wave on one clock: between the two of them a region is open in one wave more
+    or fewer than the workgroup has, and neither the region nor its neighbours in the counts may be taken for open or closed."""
     for most in (1, 2, 8, W):
         check(restart_trace(most, n_wg, W, R, cap, most), oracle_mod, use_hdr=True)
