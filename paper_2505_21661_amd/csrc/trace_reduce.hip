@@ -462,7 +462,7 @@ __global__ __launch_bounds__(BLOCK * TEAMS, (Lds<BLOCK, NR, TEAMS, RMAX, PERWAVE
     if (tid <= KP_MAX_WAVES) {  // (entries from W up: no records)
       const uint32_t T = tid < W ? h_total : 0u;
       const uint32_t V = T < cap ? T : cap;
-      sVF[tid] = make_uint2(V, flush ? 0u : T - V);
+      sVF[tid] = make_uint2(V, flush ? 0u : (T - V) & kSeqMask);
       atomicAdd(&ctr[H_DROPPED], (unsigned long long)(T - V));
       atomicAdd(&ctr[H_SLOTS_VALID], (unsigned long long)V);
     }
@@ -506,11 +506,11 @@ __global__ __launch_bounds__(BLOCK * TEAMS, (Lds<BLOCK, NR, TEAMS, RMAX, PERWAVE
     // a hardware wave's share: so are all its rounds.
     const bool whole_rings = RINGS == kWhole || (RINGS == kAny && cap >= kWaveSpan);
     const uint32_t wave_here = pbase >> cl2;
-    uint32_t held_here = 0, first_here = 0;  // records held by that wave, its first surviving seq
+    uint32_t held_here = 0, first_here = 0;  // records held by that wave, its first surviving seq (of 20 bits)
     if (whole_rings && wave_here < W) {
       const uint32_t T = (uint32_t)__builtin_amdgcn_readlane((int)h_total, (int)wave_here);
       held_here = T < cap ? T : cap;
-      first_here = flush ? 0u : T - held_here;
+      first_here = flush ? 0u : (T - held_here) & kSeqMask;
     }
     const uint32_t slot_here = pbase & capm;
     const uint32_t to_oldest = (first_here - slot_here) & capm;  // slots from the hardware wave's first place to the oldest record
@@ -535,15 +535,17 @@ __global__ __launch_bounds__(BLOCK * TEAMS, (Lds<BLOCK, NR, TEAMS, RMAX, PERWAVE
     {
       uint32_t c_bad = 0, c_dis = 0;
       // e0, e1: the low 24 bits of the tags if both records are in place.  (Where that does not take a ring that begins
-      // in the round or a seq that wraps into account, the records are looked at like any other.)
-      auto check = [&](int j, uint32_t w, uint32_t V, uint32_t first, uint32_t s0, bool whole, uint32_t e0, uint32_t e1) __attribute__((always_inline)) {
+      // in the round into account, the records are looked at like any other.)  above: the region's bits of a tag from which on
+      // a record is looked at: the first that does not exist, or all where seq wraps inside the ring.
+      auto above_of = [&](uint32_t first) -> uint32_t { return first + capm <= kSeqMask ? R << 24 : 0u; };
+      auto check = [&](int j, uint32_t w, uint32_t V, uint32_t first, uint32_t s0, bool whole, uint32_t above, uint32_t e0, uint32_t e1) __attribute__((always_inline)) {
         const uint32_t tag0 = v[j].x, tag1 = v[j].z;
         const uint32_t wrong = ((tag0 ^ e0) | (tag1 ^ e1)) & 0xFFFFFFu;
         const uint32_t r0 = tag0 & 0x7F000000u, r1 = tag1 & 0x7F000000u;
         uint32_t t0 = v[j].y, t1 = v[j].w, m2 = __builtin_amdgcn_perm(tag1, tag0, 0x0C0C0703u);  // END flag and region of both
-        if (seldom(!whole || (__builtin_amdgcn_ballot_w64(wrong != 0u) | __builtin_amdgcn_ballot_w64((r0 > r1 ? r0 : r1) >= (R << 24))) != 0ull)) {
+        if (seldom(!whole || (__builtin_amdgcn_ballot_w64(wrong != 0u) | __builtin_amdgcn_ballot_w64((r0 > r1 ? r0 : r1) >= above)) != 0ull)) {
           bool home0 = s0 < V, home1 = s0 + 1u < V;
-          const bool odd0 = ((tag0 ^ e0) & 0xFFFFFFu) != 0u || r0 >= (R << 24), odd1 = ((tag1 ^ e1) & 0xFFFFFFu) != 0u || r1 >= (R << 24);
+          const bool odd0 = ((tag0 ^ e0) & 0xFFFFFFu) != 0u || r0 >= above, odd1 = ((tag1 ^ e1) & 0xFFFFFFu) != 0u || r1 >= above;
           if (rare(__builtin_amdgcn_ballot_w64((home0 && odd0) || (home1 && odd1)) != 0ull)) {
             // rank: the low 20 bits of tag - first are those of seq - first
             const uint32_t n0 = (tag0 - first) & kSeqMask, n1 = (tag1 - first) & kSeqMask;
@@ -564,14 +566,14 @@ __global__ __launch_bounds__(BLOCK * TEAMS, (Lds<BLOCK, NR, TEAMS, RMAX, PERWAVE
         set_round(j, t0, t1, m2);
       };
       if (whole_rings) {
-        const uint32_t tag_here = (wave_here << 20) + first_here + ((slot_here - first_here) & capm) + 2u * lane;
+        const uint32_t tag_here = (wave_here << 20) + first_here + ((slot_here - first_here) & capm) + 2u * lane, above = above_of(first_here);
 #pragma unroll
         for (int j = 0; j < NR / 2; ++j) {
           if (rare(slot_here + 128u * j >= held_here)) {
             set_round(j, 0xFFFFFFFFu, 0xFFFFFFFFu, kEmpty | (kEmpty << 8));
           } else {
             const uint32_t e0 = tag_here + (128u * j - (to_oldest != 0u && 128u * j >= to_oldest ? cap : 0u));
-            check(j, wave_here, held_here, first_here, slot_here + 128u * j + 2u * lane, slot_here + 128u * j + 128u <= held_here, e0, e0 + 1u);
+            check(j, wave_here, held_here, first_here, slot_here + 128u * j + 2u * lane, slot_here + 128u * j + 128u <= held_here, above, e0, e0 + 1u);
           }
         }
       } else if (!SMALL) {
@@ -579,12 +581,12 @@ __global__ __launch_bounds__(BLOCK * TEAMS, (Lds<BLOCK, NR, TEAMS, RMAX, PERWAVE
         for (int j = 0; j < NR / 2; ++j) {
           const uint32_t p0 = pbase + 128u * j, w = p0 >> cl2, slot = p0 & capm;
           const uint32_t T = (uint32_t)__builtin_amdgcn_readlane((int)h_total, (int)(w & 15u));
-          const uint32_t V = w >= W ? 0u : T < cap ? T : cap, first = flush ? 0u : T - V;
+          const uint32_t V = w >= W ? 0u : T < cap ? T : cap, first = flush ? 0u : (T - V) & kSeqMask;
           if (rare(slot >= V)) {
             set_round(j, 0xFFFFFFFFu, 0xFFFFFFFFu, kEmpty | (kEmpty << 8));
           } else {
             const uint32_t k0 = (slot - first + 2u * lane) & capm, base = (w << 20) + first;
-            check(j, w, V, first, slot + 2u * lane, slot + 128u <= V, base + k0, base + ((k0 + 1u) & capm));
+            check(j, w, V, first, slot + 2u * lane, slot + 128u <= V, above_of(first), base + k0, base + ((k0 + 1u) & capm));
           }
         }
       } else {
@@ -592,9 +594,10 @@ __global__ __launch_bounds__(BLOCK * TEAMS, (Lds<BLOCK, NR, TEAMS, RMAX, PERWAVE
         for (int j = 0; j < NR / 2; ++j) {
           const uint32_t q = qe + 128u * j, s0 = q & capm, wv = q >> cl2, w = wv < KP_MAX_WAVES ? wv : KP_MAX_WAVES;  // (entry KP_MAX_WAVES: no records)
           const uint2 vf = sVF[w];
-          const uint32_t k0 = (s0 - vf.y) & capm, base = vf.y + (w << 20);
+          const uint32_t k0 = (s0 - vf.y) & capm;
+          const uint32_t e0 = (w << 20) | ((vf.y + k0) & kSeqMask), e1 = (w << 20) | ((vf.y + ((k0 + 1u) & capm)) & kSeqMask);
           oldest |= (k0 == 0u ? 1u << j : 0u) | (k0 == 1u ? 0x100u << j : 0u) | (k0 == capm ? 0x10000u << j : 0u);
-          check(j, w, vf.x, vf.y, s0, __builtin_amdgcn_ballot_w64(s0 + 1u >= vf.x) == 0ull, base + k0, base + ((k0 + 1u) & capm));
+          check(j, w, vf.x, vf.y, s0, __builtin_amdgcn_ballot_w64(s0 + 1u >= vf.x) == 0ull, R << 24, e0, e1);
         }
       }
       publish_ends();

@@ -474,3 +474,31 @@ def test_regions_that_restart_on_a_tick(kp, oracle_mod, n_wg, W, R, cap):
     or fewer than the workgroup has, and neither the region nor its neighbours in the counts may be taken for open or closed."""
     for most in (1, 2, 8, W):
         check(restart_trace(most, n_wg, W, R, cap, most), oracle_mod, use_hdr=True)
+
+
+@pytest.mark.parametrize("n_wg,W,R,cap", [
+    (40, 4, 3, 16), (40, 8, 5, 64), (40, 4, 5, 128), (40, 2, 5, 512), (300, 2, 8, 32), (450, 8, 16, 64), (450, 2, 5, 128),
+    (300, 8, 16, 128), (300, 4, 5, 1024), (30, 8, 16, 1024), (30, 16, 5, 1024), (30, 16, 20, 512), (30, 3, 40, 512)])
+@pytest.mark.parametrize("dropped", [(1 << 20) - 7, 1 << 20, 3 << 20, (16 << 20) + 37, (5 << 20) - 200])
+def test_long_captures(kp, oracle_mod, n_wg, W, R, cap, dropped):
+    """Waves that dropped 2^20 records or more, or nearly so that seq wraps inside the ring: clean, and with records that name another
+    wave: the one that a sum of the wave's place in the tag and the full record number would give, in whole rings and from the
+    place on where seq wraps."""
+    spec = inputs.TraceSpec(n_wg=n_wg, waves=W, n_regions=R, cap_wave=cap, total_per_wave=2 * cap, total_var=cap // 2, seed=cap + W, dist="exp",
+                            p0=30.0, gap_max=4, p_orphan=0.02, p_swap=0.002 if cap >= 128 else 0.0)
+    raw, _ = inputs.gen_trace(spec)
+    raw = raw.copy()
+    heads = raw[16:16 + 32 * n_wg].reshape(n_wg, 32)
+    slots = raw[16 + 32 * n_wg:].reshape(n_wg, W, cap, 2)
+    number = slots[..., 0] & np.uint32(0xFFFFF)
+    shift = dropped - dropped % cap  # (a record stays in its slot)
+    assert (heads[:, 8:8 + W] > cap).all() and int(number.max()) + shift < 1 << 32
+    heads[:, 8:8 + W] += np.uint32(shift)
+    number = number + np.uint32(shift)
+    slots[..., 0] = (slots[..., 0] & np.uint32(0xFFF00000)) | (number & np.uint32(0xFFFFF))
+    check(raw, oracle_mod, use_hdr=True)
+    for wg in range(0, n_wg, 2):
+        for w in range(W) if wg % 6 == 0 else [wg // 2 % W]:
+            other = np.uint32(w) + (number[wg, w] >> np.uint32(20)) & np.uint32(0xF)
+            slots[wg, w, :, 0] = (slots[wg, w, :, 0] & np.uint32(0xFF0FFFFF)) | (other << np.uint32(20))
+    check(raw, oracle_mod, use_hdr=True)
