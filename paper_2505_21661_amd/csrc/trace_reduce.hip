@@ -534,17 +534,17 @@ __global__ __launch_bounds__(BLOCK * TEAMS, (Lds<BLOCK, NR, TEAMS, RMAX, PERWAVE
     };
     {
       uint32_t c_bad = 0, c_dis = 0;
-      // e0, e1: the low 24 bits of the tags if both records are in place.  (Where that does not take a ring that begins
-      // in the round into account, the records are looked at like any other.)  above: the region's bits of a tag from which on
-      // a record is looked at: the first that does not exist, or all where seq wraps inside the ring.
-      auto above_of = [&](uint32_t first) -> uint32_t { return first + capm <= kSeqMask ? R << 24 : 0u; };
-      auto check = [&](int j, uint32_t w, uint32_t V, uint32_t first, uint32_t s0, bool whole, uint32_t above, uint32_t e0, uint32_t e1) __attribute__((always_inline)) {
+      // e0, e1: the low 24 bits of the tags if both records are in place; not exact in every lane where seq wraps inside the
+      // ring or the ring begins inside the round, which the caller says.  The records are looked at in any case if not `whole` (some
+      // place has no record) or `look` is not 0, and if one names a region from `above` on.
+      auto check = [&](int j, uint32_t w, uint32_t V, uint32_t first, uint32_t s0, bool whole, uint32_t look, bool exact, uint32_t above, uint32_t e0, uint32_t e1) __attribute__((always_inline)) {
         const uint32_t tag0 = v[j].x, tag1 = v[j].z;
         const uint32_t wrong = ((tag0 ^ e0) | (tag1 ^ e1)) & 0xFFFFFFu;
         const uint32_t r0 = tag0 & 0x7F000000u, r1 = tag1 & 0x7F000000u;
         uint32_t t0 = v[j].y, t1 = v[j].w, m2 = __builtin_amdgcn_perm(tag1, tag0, 0x0C0C0703u);  // END flag and region of both
-        if (seldom(!whole || (__builtin_amdgcn_ballot_w64(wrong != 0u) | __builtin_amdgcn_ballot_w64((r0 > r1 ? r0 : r1) >= above)) != 0ull)) {
+        if (seldom(!whole || (look | __builtin_amdgcn_ballot_w64(wrong != 0u) | __builtin_amdgcn_ballot_w64((r0 > r1 ? r0 : r1) >= above)) != 0ull)) {
           bool home0 = s0 < V, home1 = s0 + 1u < V;
+          if (!exact) above = 0u;
           const bool odd0 = ((tag0 ^ e0) & 0xFFFFFFu) != 0u || r0 >= above, odd1 = ((tag1 ^ e1) & 0xFFFFFFu) != 0u || r1 >= above;
           if (rare(__builtin_amdgcn_ballot_w64((home0 && odd0) || (home1 && odd1)) != 0ull)) {
             // rank: the low 20 bits of tag - first are those of seq - first
@@ -566,15 +566,15 @@ __global__ __launch_bounds__(BLOCK * TEAMS, (Lds<BLOCK, NR, TEAMS, RMAX, PERWAVE
         set_round(j, t0, t1, m2);
       };
       if (whole_rings) {
-        const uint32_t tag_here = (wave_here << 20) + first_here + ((slot_here - first_here) & capm) + 2u * lane, above = above_of(first_here);
+        const uint32_t tag_here = (wave_here << 20) + first_here + ((slot_here - first_here) & capm) + 2u * lane;
+        // rounds in which the expected tags are not exact, and with those that have a place without a record
+        const uint32_t inexact = first_here + capm > kSeqMask ? 0xFFFFFFFFu : (to_oldest & 127u) != 0u && to_oldest < kWaveSpan ? 1u << (to_oldest >> 7) : 0u;
+        const uint32_t full = held_here > slot_here ? (held_here - slot_here) >> 7 : 0u;
+        const uint32_t look = inexact | (full < NR / 2 ? 0xFFFFFFFFu << full : 0u);
 #pragma unroll
         for (int j = 0; j < NR / 2; ++j) {
-          if (rare(slot_here + 128u * j >= held_here)) {
-            set_round(j, 0xFFFFFFFFu, 0xFFFFFFFFu, kEmpty | (kEmpty << 8));
-          } else {
-            const uint32_t e0 = tag_here + (128u * j - (to_oldest != 0u && 128u * j >= to_oldest ? cap : 0u));
-            check(j, wave_here, held_here, first_here, slot_here + 128u * j + 2u * lane, slot_here + 128u * j + 128u <= held_here, above, e0, e0 + 1u);
-          }
+          const uint32_t e0 = tag_here + (128u * j - (to_oldest != 0u && 128u * j >= to_oldest ? cap : 0u));
+          check(j, wave_here, held_here, first_here, slot_here + 128u * j + 2u * lane, true, look & (1u << j), (inexact & (1u << j)) == 0u, R << 24, e0, e0 + 1u);
         }
       } else if (!SMALL) {
 #pragma unroll
@@ -586,7 +586,7 @@ __global__ __launch_bounds__(BLOCK * TEAMS, (Lds<BLOCK, NR, TEAMS, RMAX, PERWAVE
             set_round(j, 0xFFFFFFFFu, 0xFFFFFFFFu, kEmpty | (kEmpty << 8));
           } else {
             const uint32_t k0 = (slot - first + 2u * lane) & capm, base = (w << 20) + first;
-            check(j, w, V, first, slot + 2u * lane, slot + 128u <= V, above_of(first), base + k0, base + ((k0 + 1u) & capm));
+            check(j, w, V, first, slot + 2u * lane, slot + 128u <= V, 0u, true, first + capm <= kSeqMask ? R << 24 : 0u, base + k0, base + ((k0 + 1u) & capm));
           }
         }
       } else {
@@ -597,7 +597,7 @@ __global__ __launch_bounds__(BLOCK * TEAMS, (Lds<BLOCK, NR, TEAMS, RMAX, PERWAVE
           const uint32_t k0 = (s0 - vf.y) & capm;
           const uint32_t e0 = (w << 20) | ((vf.y + k0) & kSeqMask), e1 = (w << 20) | ((vf.y + ((k0 + 1u) & capm)) & kSeqMask);
           oldest |= (k0 == 0u ? 1u << j : 0u) | (k0 == 1u ? 0x100u << j : 0u) | (k0 == capm ? 0x10000u << j : 0u);
-          check(j, w, vf.x, vf.y, s0, __builtin_amdgcn_ballot_w64(s0 + 1u >= vf.x) == 0ull, R << 24, e0, e1);
+          check(j, w, vf.x, vf.y, s0, __builtin_amdgcn_ballot_w64(s0 + 1u >= vf.x) == 0ull, 0u, true, R << 24, e0, e1);
         }
       }
       publish_ends();

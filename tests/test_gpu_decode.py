@@ -502,3 +502,21 @@ def test_long_captures(kp, oracle_mod, n_wg, W, R, cap, dropped):
             other = np.uint32(w) + (number[wg, w] >> np.uint32(20)) & np.uint32(0xF)
             slots[wg, w, :, 0] = (slots[wg, w, :, 0] & np.uint32(0xFF0FFFFF)) | (other << np.uint32(20))
     check(raw, oracle_mod, use_hdr=True)
+
+
+@pytest.mark.parametrize("n_wg,W,R,cap", [(40, 2, 3, 256), (40, 4, 5, 1024), (40, 8, 20, 512), (300, 2, 5, 1024), (300, 1, 16, 2048), (300, 4, 24, 1024),
+                                          (130, 4, 16, 2048), (130, 8, 5, 2048), (130, 1, 20, 16384), (40, 8, 5, 64), (450, 2, 16, 512), (40, 3, 40, 512)])
+@pytest.mark.parametrize("ends_round", [True, False])
+def test_rings_written_further_than_the_header_says(kp, oracle_mod, n_wg, W, R, cap, ends_round):
+    """A wave's count is 1 to 127 records short: as many slots of its ring hold records newer than the count covers, which are
+    invalid, in the place of the oldest that it does.  The overrun ends at a multiple of 128 slots, or anywhere."""
+    spec = inputs.TraceSpec(n_wg=n_wg, waves=W, n_regions=R, cap_wave=cap, total_per_wave=3 * cap if ends_round else 3 * cap + cap // 3,
+                            total_var=0 if ends_round else cap // 2, seed=cap + W, dist="exp", p0=30.0, gap_max=4, p_orphan=0.02)
+    raw, _ = inputs.gen_trace(spec)
+    raw = raw.copy()
+    heads = raw[16:16 + 32 * n_wg].reshape(n_wg, 32)
+    assert not ends_round or (heads[:, 8:8 + W] == 3 * cap).all()
+    for wg in range(n_wg):
+        if wg % 10 != 9:
+            heads[wg, 8 + wg % W] -= np.uint32([1, 2, 3, 31, 64, 65, 100, 126, 127][wg % 10])
+    check(raw, oracle_mod, use_hdr=True)
