@@ -805,8 +805,7 @@ __global__ __launch_bounds__(BLOCK * TEAMS, (Lds<BLOCK, NR, TEAMS, RMAX, PERWAVE
           if constexpr (SMALL) row = __umul24(q >> cl2, R);
           const uint32_t m0 = (m4 >> (16 * h)) & kRegion, m1 = (m4 >> (16 * h + 8)) & kRegion;
           const uint32_t d0 = t[2 * j] - pt[h], d1 = t[2 * j + 1] - t[2 * j];
-          if (e0 || e1) account_row(row, e1 ? m1 : m0, e1 ? d1 : d0);
-          if (rare(e0 && e1)) account_row(row, m0, d0);
+          if (e0 || e1) account_row(row, e1 ? m1 : m0, e1 ? d1 : d0);  // (never both: what the odd one is paired with is a START)
         }
       }
       // A START in an odd position that the even position of the lane above claimed (lane 63: that of lane 0 in the next
@@ -1546,7 +1545,7 @@ template <int BLOCK, int NR, int TEAMS, int RMAX, int PERWAVE, int RINGS, bool M
 kp_status launch_rings(const DecodeParams& p, hipStream_t s) {
   // counters of open waves per region run up to the number of waves
   constexpr int kShortest = RINGS == kSmall ? 2 : RINGS == kWhole ? 64 * NR : 128;
-  if constexpr (16 * kShortest <= BLOCK * NR) {  // (else 16 waves have more records than this form takes)
+  if constexpr (16 * kShortest <= BLOCK * NR && (!MANY || 16 * 17 <= PERWAVE)) {  // (else 16 waves have more records or sums than this form takes)
     if (p.W == 16) return launch_main<BLOCK, NR, TEAMS, 5, RMAX, PERWAVE, RINGS, MANY>(p, s);
   }
   return launch_main<BLOCK, NR, TEAMS, 4, RMAX, PERWAVE, RINGS, MANY>(p, s);
@@ -1559,7 +1558,11 @@ kp_status launch_planes(DecodeParams& p, hipStream_t s) {
   if constexpr (BLOCK * NR <= 1024) {  // (16 waves with rings of 64 slots have 1024 in all)
     if (p.cap < 128u) return launch_rings<BLOCK, NR, TEAMS, RMAX, PERWAVE, kSmall, MANY>(p, s);
   }
-  if constexpr ((TEAMS == 1 && BLOCK > 64) || (NR == 16 && !MANY)) {
+  if constexpr (BLOCK == 1024 && NR == 16) {  // (more than 8192 slots in at most 16 rings)
+    return launch_rings<BLOCK, NR, TEAMS, RMAX, PERWAVE, kWhole, MANY>(p, s);
+  } else if constexpr (BLOCK == 512 && MANY && PERWAVE == 512) {  // (more than 256 sums: nine rings or more in 8192 slots)
+    return launch_rings<BLOCK, NR, TEAMS, RMAX, PERWAVE, kPart, MANY>(p, s);
+  } else if constexpr ((TEAMS == 1 && BLOCK > 64) || (NR == 16 && !MANY)) {
     return p.cap < 64u * NR ? launch_rings<BLOCK, NR, TEAMS, RMAX, PERWAVE, kPart, MANY>(p, s) : launch_rings<BLOCK, NR, TEAMS, RMAX, PERWAVE, kWhole, MANY>(p, s);
   } else {
     return launch_rings<BLOCK, NR, TEAMS, RMAX, PERWAVE, kAny, MANY>(p, s);

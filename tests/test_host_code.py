@@ -57,3 +57,15 @@ def test_a_call_without_a_stream_takes_torchs_current_one(monkeypatch, raw_looku
     assert binding._stream(None) == (0x4003 if raw_lookup else 0x5000)
     assert binding._stream(None) == (0x4003 if raw_lookup else 0x5000)
     assert binding._stream(7) == 7 and binding._stream(Stream) == 0x5000
+
+
+@pytest.mark.skipif(not os.path.exists(READELF), reason="no llvm-readelf")
+def test_every_kernel_of_the_statistics_is_taken_by_some_geometry(tmp_path):
+    """Either side of the lines in the numbers of workgroups and regions, all waves and ring sizes."""
+    from tests import fake_hip
+
+    calls = [{"fn": "kp_trace_reduce_hdr", "trace": (n_wg, waves, regions, 1 << log2)} for n_wg in (1, 257, 401, 1401, 2600)
+             for waves in range(1, 17) for regions in (1, 8, 9, 16, 17, 32, 33, 64, 65, 128) for log2 in range(1, 20)]
+    taken = {x[0] for _, launches in fake_hip.run(calls, tmp_path) for x in launches}
+    built = {k for k in kernels(tmp_path) if "kp_reduce" in k}
+    assert built and built == taken, built ^ taken
