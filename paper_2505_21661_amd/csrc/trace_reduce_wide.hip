@@ -1015,14 +1015,14 @@ template <int BLOCK, int E>
 kp_status launch_words(const WideParams& p, hipStream_t s) {
   // (What no geometry comes with is not built: with up to 32 regions it is more than 16384 slots; with 16 waves and two records per
   // lane more than 64 regions; with 16 waves and more than 64 regions three workgroups do not share a CU's LDS.)
-  if constexpr (BLOCK * E > 2048) {
-    if (p.R <= 32) return p.W == 16 ? launch<BLOCK, E, 1, 5>(p, s) : launch<BLOCK, E, 1, 4>(p, s);
-  }
+  constexpr bool small = BLOCK < 1024 && BLOCK * E <= 2048;
   if (p.W == 16) {  // counts up to 16
+    if constexpr (!small && E != 2) { if (p.R <= 32) return launch<BLOCK, E, 1, 5>(p, s); }
     if constexpr (E != 2) { if (p.R <= 64) return launch<BLOCK, E, 2, 5>(p, s); }
     if constexpr (BLOCK != 256) { if (p.R > 64) return launch<BLOCK, E, 4, 5>(p, s); }
     return kp::fail(KP_ERR_UNSUPPORTED_SHAPE, "no decoder for 16 waves, %u regions and %u record slots per workgroup", p.R, p.nrec);
   }
+  if constexpr (!small) { if (p.R <= 32) return launch<BLOCK, E, 1, 4>(p, s); }
   return p.R <= 64 ? launch<BLOCK, E, 2, 4>(p, s) : launch<BLOCK, E, 4, 4>(p, s);
 }
 
