@@ -370,10 +370,7 @@ kp_status kp_gemm_launch_shape(int M, int N, int K, int* n_wg, int* waves_per_wg
  *       region (5 regions, kp_trace_hdr.n_regions = 5; 4 sites and 8 records per K-step and wave):
  *       2 LDS write (the staging registers of the next K-step go to the other LDS stage), 0 global load
  *       issue (for the K-step after that), 3 MFMA, 1 wait (LDS traffic landed + barrier); 4 epilogue,
- *       once.  Waves 4 to 7 run half a K-step behind waves 0 to 3, so that the two waves of a SIMD are in
- *       different stages: they write this K-step's tiles and load the next one's, their barrier stands between
- *       the loads and the MFMAs (what they wait there counts to region 0), and their region 1 is the wait for
- *       LDS traffic.  KP_MASK_PHASES with bits 0..4 all zero runs that schedule without record sites: a record
+ *       once.  KP_MASK_PHASES with bits 0..4 all zero runs that schedule without record sites: a record
  *       site keeps its place in the instruction stream, so where the instrumented kernel has a site
  *       this one has a bare scheduling fence and the stages stay apart (behind every MFMA both have one: the
  *       operand requests stay where they are written); with bit 26 (KP_MASK_UNFENCED) as well all of these

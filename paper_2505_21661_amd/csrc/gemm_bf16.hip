@@ -640,7 +640,6 @@ __global__ __launch_bounds__(kBigWaves * 64) void kp_gemm_big(GemmArgs g) {
 
   // prologue: K step 0 into stage 0 (and, stage by stage, K step 1 into the staging registers)
   const uint32_t KT = g.K / BK;
-  const uint32_t late = kp::wave_uniform(wave >> 2);  // stage by stage: waves 4 to 7, whose barrier comes ahead of the MFMAs
   if constexpr (DIRECT) {
     static_assert(kBigWaves == 8 && BK == 64, "four 1 KiB blocks of either tile per wave");
     direct_tiles(0, 0);
@@ -650,20 +649,18 @@ __global__ __launch_bounds__(kBigWaves * 64) void kp_gemm_big(GemmArgs g) {
     for (int i = 0; i < NA; ++i) load_a(0, i);
 #pragma unroll
     for (int i = 0; i < 4; ++i) load_b(0, i);
-    if (late == 0u) {
 #pragma unroll
-      for (int i = 0; i < NA; ++i) store_a(0, i);
+    for (int i = 0; i < NA; ++i) store_a(0, i);
 #pragma unroll
-      for (int i = 0; i < 4; ++i) store_b(0, i);
-      if (KT > 1) {
+    for (int i = 0; i < 4; ++i) store_b(0, i);
+    if (KT > 1) {
 #pragma unroll
-        for (int i = 0; i < NA; ++i) load_a(1, i);
+      for (int i = 0; i < NA; ++i) load_a(1, i);
 #pragma unroll
-        for (int i = 0; i < 4; ++i) load_b(1, i);
-      }
+      for (int i = 0; i < 4; ++i) load_b(1, i);
     }
   }
-  if (!PHASED || late == 0u) asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+  asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
 
   // Default schedule.  Iteration kt runs the MFMAs of K step kt on LDS stage kt & 1.  It starts by sending
   // both tiles of K step kt+1 from global memory to the other stage, eight loads per wave that have the whole
@@ -754,15 +751,10 @@ __global__ __launch_bounds__(kBigWaves * 64) void kp_gemm_big(GemmArgs g) {
   // instrumentation of a software-pipelined GEMM, Sec. 5.3): 2 the staging registers (K step kt+1) go to
   // the other LDS stage, 0 the global loads of K step kt+2 are issued, 3 the MFMAs of K step kt, 1 the
   // wait for this wave's LDS traffic and for the other waves.  Four sites and eight records per K step.
-  // The two waves of a SIMD (w and w + 4) must not be in the same stage: writing a K step's tiles keeps the LDS busy for 800
-  // cycles (80 bytes each), its loads the CU's one unit for 1024, its MFMAs the matrix pipe for 2112, and with all waves
-  // behind one barrier in one order these add up.  So waves 4 to 7 are one barrier late: between two barriers they run the
-  // MFMAs of K step kt first and then write K step kt+1 and load kt+2 (in their own order of stages: write kt, load kt+1,
-  // barrier, MFMAs of kt, wait), while waves 0 to 3 write and load first.  Every stage of the LDS is written and read between
-  // the same two barriers as before.  Their MFMAs go first where both want to issue, or those of waves 0 to 3 would keep them
-  // from their writes until the pipe is free (108 us).  All waves in one order and this, 2048x4096x4096 recorded 101.4 / 94.8
-  // us, 4096x4096x4096 122.3 / 119.1, without sites 117.8 / 116.8.  What is left: a wave's stages, one after the other, take
-  // 2760 of the 3150 ticks between two barriers (write 650, load 800, MFMAs 1310).
+  // With all waves behind one barrier in one order the LDS writes (800 cycles of the CU), the loads (1024 of its one unit) and
+  // the MFMAs (2112 of a SIMD) of a K step add up to 3380 ticks.  Waves 4 to 7 half a K step behind (write, load, barrier, MFMAs)
+  // take 2048x4096x4096 recorded from 101.4 to 94.8 us, without sites 117.8 -> 116.8 at 4096x4096x4096; but their barrier then
+  // stands where region 0 meets region 3, and a wave's wait would count to its loads.
   // A record site pins its place in the instruction stream (it is a scheduling fence: nothing moves across
   // the clock read).  Without sites the compiler would be free to thread the stages through one another
   // again, and "the same schedule without record sites" would be another schedule: so the uninstrumented form has
@@ -775,22 +767,20 @@ __global__ __launch_bounds__(kBigWaves * 64) void kp_gemm_big(GemmArgs g) {
     const uint32_t stage = kt & 1u;
     const unsigned char* sA = smem + stage * STAGE;
     const unsigned char* sB = sA + A_BYTES;
-    const uint32_t kw = kt + 1u - late;  // the K step whose tiles this wave writes
-    if (MORE || late) {
+    if constexpr (MORE) {
 #pragma unroll
-      for (int i = 0; i < NA; ++i) store_a(kw & 1u, i);
+      for (int i = 0; i < NA; ++i) store_a(stage ^ 1u, i);
 #pragma unroll
-      for (int i = 0; i < 4; ++i) store_b(kw & 1u, i);
+      for (int i = 0; i < 4; ++i) store_b(stage ^ 1u, i);
     }
     KP_SITE_K(ring, 1, 2, 0);
     stage_fence();
-    if (MORE2 || (MORE && late)) {
+    if constexpr (MORE2) {
 #pragma unroll
-      for (int i = 0; i < NA; ++i) load_a(kw + 1u, i);
+      for (int i = 0; i < NA; ++i) load_a(kt + 2, i);
 #pragma unroll
-      for (int i = 0; i < 4; ++i) load_b(kw + 1u, i);
+      for (int i = 0; i < 4; ++i) load_b(kt + 2, i);
     }
-    if (late) asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier\n\ts_setprio 2" ::: "memory");
     KP_SITE_K(ring, 2, 0, 3);
     stage_fence();
     // The operands of MFMA step ks + 1 are requested between the MFMAs of step ks, in the order of their use: the stage
@@ -817,11 +807,10 @@ __global__ __launch_bounds__(kBigWaves * 64) void kp_gemm_big(GemmArgs g) {
           if constexpr (SCHEDULE == 1) __builtin_amdgcn_sched_barrier(0);
         }
     }
-    asm volatile("s_waitcnt lgkmcnt(0)\n\ts_setprio 0" ::: "memory");  // (nothing of this wave's is in flight any more: see above)
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");  // (nothing of this wave's is in flight any more: see above)
     KP_SITE_K(ring, 3, 3, 1);
     stage_fence();
-    if (!MORE || !late) asm volatile("s_barrier" ::: "memory");
-    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+    asm volatile("s_barrier\n\ts_waitcnt lgkmcnt(0)" ::: "memory");
     KP_COMMIT(ring, 4);
     if constexpr (MORE) KP_SITE_K(ring, 0, 1, 2); else KP_SITE_K(ring, 0, 1, 4);
     stage_fence();

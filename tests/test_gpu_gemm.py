@@ -596,8 +596,7 @@ def test_stage_by_stage_regions(kp, oracle_mod, shape):
 @pytest.mark.parametrize("steps", [1, 2, 3, 4, 7])
 @pytest.mark.parametrize("extra", ["0", "group", "flush", "collab"])
 def test_stage_by_stage_few_k_steps(kp, steps, extra):
-    """Waves 4 to 7 are one barrier behind waves 0 to 3: the K steps in which only one half still writes or loads tiles, and
-    fewer of them than the pipeline is deep.  C bit-identical to the default schedule's (same sums in the same order),
+    """Fewer K steps than the pipeline is deep, and the last ones, in which no tiles are written or loaded any more.  C bit-identical to the default schedule's (same sums in the same order),
     with and without sites, and the closed-form record counts."""
     M, N, K = 1024, 1280, 64 * steps
     a, b = inputs.gemm_inputs(M, N, K, seed=40 + steps)
@@ -611,6 +610,25 @@ def test_stage_by_stage_few_k_steps(kp, steps, extra):
         assert torch.equal(c.view(torch.int16), c_ref.view(torch.int16))
     raw = trace.cpu().numpy().view(np.uint32)
     assert (raw[16:16 + 32 * n_wg].reshape(n_wg, 32)[:, 8:8 + streams] == (4 * steps + 1) * 2).all()
+
+
+@pytest.mark.parametrize("clock", ["0", "collab"])
+def test_stage_by_stage_every_wave_waits_in_region_1(kp, clock):
+    """The barrier of a K step stands in region 1 in every wave, so that the regions can be compared from wave to wave: nobody's wait
+    of a K step ends before everybody's has begun, and each of the eight lies inside the workgroup's K step."""
+    M, N, steps = 1024, 1280, 7
+    a, b = inputs.gemm_inputs(M, N, 64 * steps, seed=50)
+    mask = kp.KP_MASK_COLLAB if clock == "collab" else 0
+    _, trace, (n_wg, waves, _) = run_gemm_phased(kp, a, b, 0b11111, trace_cap=64 * 8, extra=mask)
+    raw = trace.cpu().numpy().view(np.uint32)
+    rec = raw[16 + 32 * n_wg:].reshape(n_wg, waves, 64, 2)[:, :, :2 * (4 * steps + 1)]
+    region, end, clk = (rec[..., 0] >> 24) & 0x7F, rec[..., 0] >> 31, rec[..., 1].astype(np.int64)
+    for phase in (0, 1):  # regions in the same order in every wave: 2, 0, 3, 1 per K step, then 4
+        assert (region[end == phase].reshape(n_wg, waves, -1) == np.array([2, 0, 3, 1] * steps + [4])).all()
+    starts, ends = (clk[(region == 1) & (end == phase)].reshape(n_wg, waves, steps) for phase in (0, 1))
+    # a clock is read while the wave goes on to the barrier or comes from it: some ten ticks either way, against a stage's 500 to 1300
+    assert (starts.max(axis=1) <= ends.min(axis=1) + 100).all()
+    assert (ends.max(axis=1)[:, :-1] <= starts.min(axis=1)[:, 1:] + 100).all()
 
 
 def test_stage_by_stage_needs_the_large_tile(kp):
