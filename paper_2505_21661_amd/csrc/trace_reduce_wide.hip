@@ -222,7 +222,7 @@ __global__ __launch_bounds__(kBlock, 4) void kp_reduce_wide(WideParams p) {
   uint2* sVF = reinterpret_cast<uint2*>(smem + p.lds.vf);               // per wave: records held, first surviving seq
   uint32_t* pos = reinterpret_cast<uint32_t*>(smem + p.lds.pos);        // per wave: first rank of the range in LDS
   uint32_t* adv = reinterpret_cast<uint32_t*>(smem + p.lds.adv);        // per wave: ranks the window took
-  uint32_t* edge = reinterpret_cast<uint32_t*>(smem + p.lds.edge);      // pass 1, per run: 1 if it holds a record, first clock, last clock; pass 2: records in the cells of each hardware wave
+  uint32_t* edge = reinterpret_cast<uint32_t*>(smem + p.lds.edge);      // pass 1, per run: 1 if it holds a record, first clock, last clock and id; pass 2: records in the cells of each hardware wave
   // hi (hi + 1), which is even: the bytes of hi (hi + 1) / 2 places are four times as many.  (A 32-bit product, which the compiler
   // makes of it, takes four times as long as this instruction:
   // 1024 workgroups of 8 x 4096 slots, 48 regions 632 -> 621 us, 300 of 16 x 2048, 128 regions 780 -> 768.)
@@ -506,13 +506,20 @@ __global__ __launch_bounds__(kBlock, 4) void kp_reduce_wide(WideParams p) {
           if ((near >> lane) & 1ull) mark(b0 + lane - 1u);
         }
       };
+      auto take_run = [&](uint32_t id) {
+        w_here = id >> split; run = id & ((1u << split) - 1u);
+        last = last_all + id * R;
+        head = head_all + id * R;
+      };
+      auto keep_edge = [&](uint32_t id) {
+        if (lane == 0 && w_here < W) *reinterpret_cast<uint4*>(edge + 4u * id) = make_uint4(carry_has ? 1u : 0u, first_ts, carry_ts, carry_id);
+      };
       // (runs may outnumber the hardware waves where these are fewer than the recorded ones)
-      const uint32_t n_runs = kWavesHw == kWavesMost ? 1u : W << split;
+      const bool several = kWavesHw != kWavesMost && tabled && W > kWavesHw;
+      const uint32_t n_runs = kWavesHw == kWavesMost || several ? 1u : W << split;
       for (uint32_t run0 = 0; run0 < n_runs; run0 += kWavesHw) {
       const uint32_t id = run0 + hw;
-      w_here = id >> split; run = id & ((1u << split) - 1u);
-      last = last_all + id * R;
-      head = head_all + id * R;
+      take_run(id);
       carry_has = false; carry_ts = 0u; first_ts = 0u; carry_id = kNoId;
       const uint32_t V = w_here < W ? sVF[w_here].x : 0u;
       if (!tabled) {
@@ -556,20 +563,33 @@ __global__ __launch_bounds__(kBlock, 4) void kp_reduce_wide(WideParams p) {
         for (uint32_t k0 = 0; k0 < max_v; k0 += Ct) {
           if (tid < 16) pos[tid] = k0;
           build_table(table1, 1u << p.lds.table_log2, tsh);
+          // A table holds a range of ranks of all waves, and takes a look at every slot.  So it is made once, and a hardware wave that
+          // has several waves walks the range in one after the other, with each one's last record kept beside its edges.  (Each through
+          // all ranges, the tables made anew for it: 1000 workgroups of 16 x 1024 slots, 40 regions, a third of the neighbours swapped
+          // 613 us, 558 this way; 500 of 16 x 2048, 24 regions 594 / 536.  Where each has one wave nothing is reloaded: 563 / 566
+          // for 1000 of 8 x 1024, 585 if it is.)
+          for (uint32_t id_t = hw;;) {
+            const uint32_t V_t = id_t < W ? sVF[id_t].x : 0u;
 #pragma unroll 1
-          for (uint32_t j0 = 0; j0 < Ct && k0 + j0 < V; j0 += 64u) {
-            const uint32_t t = table1[(id << tsh) + j0 + lane];
-            const uint2 rec = recs[(size_t)id * cap + (t ? t - 1u : 0u)];
-            moved += (uint32_t)__popcll(__builtin_amdgcn_ballot_w64(t != 0u && ((rec.x ^ (t - 1u)) & capm) != 0u));
-            group(k0 + j0, t != 0u, rec);
+            for (uint32_t j0 = 0; j0 < Ct && k0 + j0 < V_t; j0 += 64u) {
+              const uint32_t t = table1[(id_t << tsh) + j0 + lane];
+              const uint2 rec = recs[(size_t)id_t * cap + (t ? t - 1u : 0u)];
+              moved += (uint32_t)__popcll(__builtin_amdgcn_ballot_w64(t != 0u && ((rec.x ^ (t - 1u)) & capm) != 0u));
+              group(k0 + j0, t != 0u, rec);
+            }
+            if (!several) break;
+            keep_edge(id_t);
+            id_t += kWavesHw;
+            const bool back = id_t >= W;  // to the first, for the next range
+            if (back) id_t = hw;
+            take_run(id_t);
+            auto kept = [&](uint32_t i) { return (uint32_t)__builtin_amdgcn_readfirstlane((int)edge[4u * id_t + i]); };
+            carry_has = kept(0u) != 0u; first_ts = kept(1u); carry_ts = carry_has ? kept(2u) : 0u; carry_id = carry_has ? kept(3u) : kNoId;
+            if (back) break;
           }
         }
       }
-      if (lane == 0 && w_here < W) {
-        edge[4u * id] = carry_has ? 1u : 0u;
-        edge[4u * id + 1u] = first_ts;
-        edge[4u * id + 2u] = carry_ts;
-      }
+      keep_edge(id);
       }
       if (lane == 0) {
         if (n_pairs) atomicAdd(&tmp[T_PAIRS], n_pairs);

@@ -210,3 +210,19 @@ def test_every_number_of_threads(kp, oracle_mod, n_wg, W, R, cap, p_swap):
         slots[n_wg // 2, W - 1, 3, 0] ^= np.uint32(0x00100000)
     st = check(raw, oracle_mod, use_hdr=True)
     assert st["n_overlap_wgs"] == n_wg - 1 and (p_swap == 0.0) == (st["n_disorder"] == 0)
+
+
+@pytest.mark.parametrize("n_wg,W,R,cap", [(300, 16, 40, 1024), (300, 9, 64, 2048), (300, 13, 17, 2048), (1600, 12, 33, 128), (300, 3, 40, 8192)])
+def test_tables_of_waves_that_share_a_hardware_wave(kp, oracle_mod, n_wg, W, R, cap):
+    """So many records out of place that their slots are looked up in tables, a range of ranks at a time, by fewer hardware waves than
+    the workgroup has: rings that end in any range, and waves without a record beside full ones."""
+    spec = inputs.TraceSpec(n_wg=n_wg, waves=W, n_regions=R, cap_wave=cap, total_per_wave=cap // 2, total_var=cap // 2,
+                            seed=W + cap, dist="lognormal", p0=4.0, p1=1.0, p_orphan=0.05, p_swap=0.4, swap_max=30)
+    raw, _ = inputs.gen_trace(spec)
+    raw = raw.copy()
+    heads = raw[16:16 + 32 * n_wg].reshape(n_wg, 32)
+    for wg in range(n_wg):
+        if wg % 3:
+            heads[wg, 8 + wg % W] = 0
+    st = check(raw, oracle_mod, use_hdr=True)
+    assert st["n_disorder"] > 0.1 * st["n_slots_valid"] and st["n_overlap_wgs"] > 0
