@@ -25,6 +25,22 @@ __host__ __device__ inline StatsLayout stats_layout(uint32_t n_wg, uint32_t W, u
   return l;
 }
 
+// Recorded workgroups as they would be on a device of 256 CUs, the one that the choice of a decoder was measured on: with how many
+// of them a form pays is a question of how many there are per CU.
+inline kp_status wgs_of_256_cus(uint32_t n_wg, uint32_t* n) {
+  static thread_local int known = -1, cus = 0;
+  int dev = 0;
+  KP_HIP_TRY(hipGetDevice(&dev));
+  if (known != dev) {
+    KP_HIP_TRY(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev));
+    if (cus < 1) return kp::fail(KP_ERR_UNSUPPORTED_SHAPE, "device %d reports %d compute units", dev, cus);
+    known = dev;
+  }
+  const uint64_t scaled = ((uint64_t)n_wg * 256u + (uint32_t)cus - 1u) / (uint32_t)cus;
+  *n = scaled < 0xFFFFFFFFull ? (uint32_t)scaled : 0xFFFFFFFFu;
+  return KP_OK;
+}
+
 using namespace kp_wave;
 
 // Batcher's odd-even merge sort of N registers: a fixed network (63 exchanges for 16 words, 384 for 48),

@@ -1621,8 +1621,11 @@ kp_status reduce_impl(const void* raw, size_t n, const kp_trace_hdr& h, void* ou
     p.cap_log2 = 0; while ((1u << p.cap_log2) < cap) ++p.cap_log2;
     p.rec_cost = h.rec_cost; p.flush = h.flags & KP_FLAG_FLUSH;
     p.nrec = nrec; p.ncopy = 1; p.stop_after = stop_after;
-    // How many threads take a recorded workgroup, with how many records each.  Up to 16384 records: 1024 threads, 16
-    // each, which is all that fits one CU.  Fewer records leave a choice.  With no more recorded workgroups than CUs (256 of the whole chip) the
+    uint32_t wgs = 0;
+    kp_status st = wgs_of_256_cus(h.n_wg, &wgs);
+    if (st != KP_OK) return st;
+    // How many threads take a recorded workgroup, with how many records each (numbers of workgroups are those on 256 CUs).  Up to 16384 records: 1024
+    // threads, 16 each, which is all that fits one CU.  Fewer records leave a choice.  With no more recorded workgroups than CUs the
     // time is one workgroup's chain of steps, and four records per lane make it shorter: 64 workgroups of 4 x 128 records
     // 20.6 us with 16 each (one wave), 16.7 with four (four waves); 256 of 8 x 512 32.3 and 30.1; 100 of 1 x 4096 26.7 and
     // 24.0.  With more of them it is the work, most of which a wave does for all its places whether they hold records or
@@ -1632,7 +1635,6 @@ kp_status reduce_impl(const void* raw, size_t n, const kp_trace_hdr& h, void* ou
     // one wave per decoder workgroup, 16 records per lane, arrays for 32 regions: 20000 workgroups of 1 x 16 records 361 ->
     // 76 us (16 records per lane in teams 168), 60000 of 1 x 64, 16 regions 1084 -> 219 (490), 8192 of 4 x 128 172 -> 73, 3000
     // of 16 x 64 90 -> 42; 256 threads, arrays for 8 regions: 16000 of 2 x 1024 693 -> 487.
-    kp_status st;
     // Of 257 to 1024 records some more of them are few in that sense: three decoder workgroups of 256 threads fit a CU, and until
     // their totals queue up on the way to HBM they beat waves that take 16 records a lane (257 to 1024 records: with four records
     // a lane / 16, us): 300 of 2 x 256, 5 regions 24.2 / 27.9, 600 35.9 / 29.2; 300 of 8 x 128, 16 regions 20.5 / 27.2, 600 27.5 /
@@ -1642,10 +1644,15 @@ kp_status reduce_impl(const void* raw, size_t n, const kp_trace_hdr& h, void* ou
     // other half's waves come along to every barrier and every step, and two workgroups fit where one did.  512 threads against 1024:
     // 16384 of 8 x 1024, 16 regions 1622 -> 757 us, 510 of 16 x 512 72.4 -> 41.9, 100 of 8 x 1024 35.9 -> 27.1, 4000 of 8 x 1024, 24
     // regions 593 -> 324 (with more than 256 sums per workgroup one to a CU: 510 of 16 x 512, 32 regions 102.5 -> 80.5); 128 against
-    // 256: 16000 of 2 x 1024 418 -> 215, 2000 of 8 x 256, 24 regions 127 -> 85, 300 of 2 x 1024 31.6 -> 30.2; but twice as many totals queue
-    // up: 2000 of 3 x 512, 5 regions 80 against 96, of 2 x 1024, 4 regions 64.6 / 67.7, 1500 55.8 / 55.6, 2500 79.7 / 71.1.
+    // 256: 16000 of 2 x 1024 418 -> 215, 2000 of 8 x 256, 24 regions 127 -> 85, 300 of 2 x 1024 31.6 -> 30.2.  Four workgroups of 256
+    // threads or eight of 128 fit a CU, so that with more than 1024 recorded ones the smaller form hands over more totals, one decoder workgroup after
+    // the other at each address, until from 2048 on the larger one has to take several turns more.  What that comes to depends on how often the lanes
+    // of a wave name the same region (128 / 256 threads, us): 1000, 1600, 2000, 2600 and 4000 of 2 x 1024, 5 regions 56 / 61, 78 / 72, 94 / 80, 98 / 99,
+    // 108 / 120; of 8 x 256, 5 regions 58 / 62, 79 / 72, 95 / 79, 99 / 95, 110 / 122; of 3 x 512, 8 regions 44 / 49, 58 / 61, 67 / 67, 71 / 84, 82 / 121;
+    // of 16 x 128, 3 regions 47 / 50, 63 / 64, 73 / 71, 76 / 88, 90 / 132; with more than 8 regions within 4 % up to 1600 (12 regions, 8 x 256 67 / 65), then
+    // the smaller one.
     const uint32_t few = nrec <= 256 || nrec > 1024 ? 256u : R <= 16 ? 400u : 1400u;
-    if (h.n_wg <= few && nrec <= 4096) {
+    if (wgs <= few && nrec <= 4096) {
       if (R <= 16)
         st = nrec > 1024 ? launch_planes<1024, 4, 1, KP_MAX_REGIONS, kMaxPerWave>(p, s)
            : nrec > 256  ? launch_planes<256, 4, 1, KP_MAX_REGIONS, 512>(p, s)
@@ -1657,7 +1664,7 @@ kp_status reduce_impl(const void* raw, size_t n, const kp_trace_hdr& h, void* ou
     } else if (nrec > 4096 && nrec <= 8192) {
       st = R <= 16 ? launch_planes<512, 16, 1, 16, 512>(p, s) : W * R <= 256 ? launch_planes<512, 16, 1, KP_MAX_REGIONS, 256, true>(p, s)
                                                               : launch_planes<512, 16, 1, KP_MAX_REGIONS, 512, true>(p, s);
-    } else if (nrec > 1024 && nrec <= 2048 && (R > 8 || h.n_wg < 1500 || h.n_wg >= 2500)) {
+    } else if (nrec > 1024 && nrec <= 2048 && (R > 8 || wgs < 1500 || wgs >= 2500)) {
       st = R <= 8 ? launch_planes<128, 16, 1, 8, 128>(p, s) : R <= 16 ? launch_planes<128, 16, 1, 16, 256>(p, s)
                                                            : launch_planes<128, 16, 1, KP_MAX_REGIONS, 512, true>(p, s);
     } else if (nrec > 4096) {

@@ -1061,8 +1061,11 @@ kp_status launch_wide(const uint32_t* wg_hdrs, const void* records, uint64_t* ou
   p.rec_cost = h.rec_cost; p.flush = h.flags & KP_FLAG_FLUSH;
   p.nrec = p.W * p.cap;
   p.waves_log2 = 0; while ((1u << p.waves_log2) < p.W) ++p.waves_log2;
-  // How many threads take a recorded workgroup.  1024, and windows of 8192 places, are all that fits one CU.  With more
-  // recorded workgroups than CUs (256 of the whole chip) two of 512 threads, with 4096 places each, hide each other's barriers and
+  uint32_t wgs = 0;
+  const kp_status known = wgs_of_256_cus(p.n_wg, &wgs);
+  if (known != KP_OK) return known;
+  // How many threads take a recorded workgroup (numbers of workgroups are those on 256 CUs).  1024, and windows of 8192 places, are
+  // all that fits one CU.  With more recorded workgroups than CUs two of 512 threads, with 4096 places each, hide each other's barriers and
   // LDS round trips: 1024 workgroups of 8 x 4096 slots, 48 regions 675 -> 627 us, 1000 of 16 x 2048, 16 regions 772 -> 743, 2000 of
   // 8 x 2048, 64 regions 829 -> 699, 3000 of 4 x 1024, 64 regions 428 -> 285, 257 of 8 x 4096 359 -> 332, 512 of 3 x 8192 the same;
   // with no more of them than CUs it is one workgroup's chain of steps: 100 of 8 x 4096 172 against 235 us, 200 of 16 x 512 82 / 118.
@@ -1070,21 +1073,21 @@ kp_status launch_wide(const uint32_t* wg_hdrs, const void* records, uint64_t* ou
   // (1024 threads / 512 / 256, us: 4000 of 8 x 256, 40 regions 394 / 226 / 185, 4000 of 1 x 256 300 / 160 / 123), else, and with few
   // workgroups, 512 threads with four records each (100 of 2 x 256 27.0 -> 24.2, 256 of 2 x 512, 64 regions 38.8 -> 36.5, 1021 of
   // 8 x 256, 64 regions 146 -> 92).
-  if (p.nrec <= 2048u && p.n_wg > 256u) {
+  if (p.nrec <= 2048u && wgs > 256u) {
     p.lds = lay_out(256u, 3u, p.W, p.R, p.nrec, 8u, 0u, true);
     if (p.lds.total <= kMaxLds / 3u) return launch_words<256, 8>(p, s);
   }
   if (p.nrec <= 2048u) {
-    const uint32_t per_cu = p.n_wg > 256u ? 2u : 1u;
+    const uint32_t per_cu = wgs > 256u ? 2u : 1u;
     p.lds = lay_out(512u, per_cu, p.W, p.R, p.nrec, 4u, split_log2(512u, p.W, p.cap), true);
     if (p.lds.total <= kMaxLds / per_cu) return launch_words<512, 4>(p, s);
   }
   // (With more than one window each, two of them take 1.9 times as long as one of 1024 threads alone and one that is left over
   // 1.4 times: a last turn of at most one to a CU pays only behind three full ones.  582 of 7 x 1024, 64 regions 110 us, 126 this way.)
-  const bool full_turns = p.nrec <= 4096u || p.n_wg >= 1536u || (p.n_wg - 1u) % 512u >= 256u;
+  const bool full_turns = p.nrec <= 4096u || wgs >= 1536u || (wgs - 1u) % 512u >= 256u;
   // (One window of 8192 places is better than two or three of 4096: 1362 of 12 x 512, 40 regions 210 us against 231.)
   const bool one_large = p.cap <= (8192u >> p.waves_log2) && p.cap > (4096u >> p.waves_log2);
-  if (p.n_wg > 256u && full_turns && !one_large) {
+  if (wgs > 256u && full_turns && !one_large) {
     p.lds = wide_lds(512u, 2u, p.W, p.R, p.cap);
     if (p.lds.total <= kMaxLds / 2u && p.lds.per_lane == 8u) return launch_words<512, 8>(p, s);
   }

@@ -108,3 +108,17 @@ def test_timeline_workgroups_of_small_rings(tmp_path, device):
         assert status == 0 and "kp_pairs_main" in launches[-1][0], launches
         _, grid, block, _ = launches[-1]
         assert grid == min(n_wg, device[1] * (min(6, device[2]) if block == 256 else device[2])), (n_wg, w, cap, launches)
+
+
+@pytest.mark.parametrize("cus", [128, 32])
+def test_the_choice_of_a_statistics_kernel_goes_by_workgroups_per_cu(tmp_path, cus):
+    """A device with fewer CUs takes as many workgroups per CU with the same kernel, on either side of every line."""
+    counts = (8, 256, 264, 400, 408, 512, 520, 768, 776, 1400, 1408, 1496, 1504, 1528, 1536, 2496, 2504, 4000)
+    shapes = [(2, 3, 64), (8, 5, 64), (8, 24, 128), (2, 5, 1024), (16, 12, 128), (8, 5, 512), (8, 16, 1024), (8, 5, 2048),
+              (8, 40, 128), (8, 64, 256), (7, 64, 1024), (12, 40, 512), (16, 8, 4096)]
+    calls = [{"fn": "kp_trace_reduce_hdr", "trace": (n * of // 256, waves, regions, cap), "device": (of, of, 4)}
+             for waves, regions, cap in shapes for n in counts for of in (256, cus)]
+    done = fake_hip.run(calls, tmp_path)
+    for call, (status, launches), (other_status, others) in zip(calls[::2], done[::2], done[1::2]):
+        assert status == other_status == 0
+        assert [x[0] for x in launches] == [x[0] for x in others], (call, launches, others)
