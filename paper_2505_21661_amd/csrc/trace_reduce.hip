@@ -1638,8 +1638,11 @@ kp_status reduce_impl(const void* raw, size_t n, const kp_trace_hdr& h, void* ou
     // Of 257 to 1024 records some more of them are few in that sense: three decoder workgroups of 256 threads fit a CU, and until
     // their totals queue up on the way to HBM they beat waves that take 16 records a lane (257 to 1024 records: with four records
     // a lane / 16, us): 300 of 2 x 256, 5 regions 24.2 / 27.9, 600 35.9 / 29.2; 300 of 8 x 128, 16 regions 20.5 / 27.2, 600 27.5 /
-    // 27.4, 768 31.2 / 27.7; with 24 regions, of which 16 records a lane leave room for six waves on a CU, 300 of 16 x 32 24.4 / 38.9,
-    // 1200 38.0 / 42.5, 1536 45.7 / 44.7.
+    // 27.4, 768 31.2 / 27.7.  With more than 16 regions those waves take longer and are six to a CU, so that the line is where a fourth
+    // decoder workgroup of 256 threads would have to wait for its CU: 400, 768 and 1100 of 2 x 256, 24 regions 25 / 31, 35 / 31, 39 / 33, of 4 x 256, 17
+    // regions 28 / 40, 38 / 40, 46 / 41, of 7 x 64, 32 regions 28 / 37, 38 / 39, 45 / 40; and where nearly all lanes of such a wave have records of many
+    // rings it is as late as their last turn begins: 700, 1100 and 1400 of 16 x 64, 20 regions 38 / 47, 48 / 48, 49 / 53, of 8 x 128, 24 regions 33 / 42,
+    // 40 / 44, 41 / 44.
     // From 1024 records up the threads are as many as the records need, to the next power of two: with half of the places empty the
     // other half's waves come along to every barrier and every step, and two workgroups fit where one did.  512 threads against 1024:
     // 16384 of 8 x 1024, 16 regions 1622 -> 757 us, 510 of 16 x 512 72.4 -> 41.9, 100 of 8 x 1024 35.9 -> 27.1, 4000 of 8 x 1024, 24
@@ -1651,7 +1654,7 @@ kp_status reduce_impl(const void* raw, size_t n, const kp_trace_hdr& h, void* ou
     // 108 / 120; of 8 x 256, 5 regions 58 / 62, 79 / 72, 95 / 79, 99 / 95, 110 / 122; of 3 x 512, 8 regions 44 / 49, 58 / 61, 67 / 67, 71 / 84, 82 / 121;
     // of 16 x 128, 3 regions 47 / 50, 63 / 64, 73 / 71, 76 / 88, 90 / 132; with more than 8 regions within 4 % up to 1600 (12 regions, 8 x 256 67 / 65), then
     // the smaller one.
-    const uint32_t few = nrec <= 256 || nrec > 1024 ? 256u : R <= 16 ? 400u : 1400u;
+    const uint32_t few = nrec <= 256 || nrec > 1024 ? 256u : R <= 16 ? 400u : W >= 8 && nrec > 768 ? 1400u : 768u;
     if (wgs <= few && nrec <= 4096) {
       if (R <= 16)
         st = nrec > 1024 ? launch_planes<1024, 4, 1, KP_MAX_REGIONS, kMaxPerWave>(p, s)

@@ -114,7 +114,7 @@ def test_timeline_workgroups_of_small_rings(tmp_path, device):
 def test_the_choice_of_a_statistics_kernel_goes_by_workgroups_per_cu(tmp_path, cus):
     """A device with fewer CUs takes as many workgroups per CU with the same kernel, on either side of every line."""
     counts = (8, 256, 264, 400, 408, 512, 520, 768, 776, 1400, 1408, 1496, 1504, 1528, 1536, 2496, 2504, 4000)
-    shapes = [(2, 3, 64), (8, 5, 64), (8, 24, 128), (2, 5, 1024), (16, 12, 128), (8, 5, 512), (8, 16, 1024), (8, 5, 2048),
+    shapes = [(2, 3, 64), (8, 5, 64), (8, 24, 128), (2, 24, 256), (2, 5, 1024), (16, 12, 128), (8, 5, 512), (8, 16, 1024), (8, 5, 2048),
               (8, 40, 128), (8, 64, 256), (7, 64, 1024), (12, 40, 512), (16, 8, 4096)]
     calls = [{"fn": "kp_trace_reduce_hdr", "trace": (n * of // 256, waves, regions, cap), "device": (of, of, 4)}
              for waves, regions, cap in shapes for n in counts for of in (256, cus)]
@@ -122,3 +122,12 @@ def test_the_choice_of_a_statistics_kernel_goes_by_workgroups_per_cu(tmp_path, c
     for call, (status, launches), (other_status, others) in zip(calls[::2], done[::2], done[1::2]):
         assert status == other_status == 0
         assert [x[0] for x in launches] == [x[0] for x in others], (call, launches, others)
+
+
+@pytest.mark.parametrize("waves,regions,cap,last", [(2, 16, 256, 400), (2, 17, 256, 768), (7, 32, 64, 768), (12, 24, 64, 768),
+                                                    (8, 24, 128, 1400), (16, 17, 64, 1400), (4, 20, 256, 768), (4, 17, 64, 256)])
+def test_up_to_how_many_workgroups_four_records_go_to_a_lane(tmp_path, waves, regions, cap, last):
+    """Each decoder workgroup holds one recorded workgroup then, whatever the grid."""
+    calls = [{"fn": "kp_trace_reduce_hdr", "trace": (n, waves, regions, cap), "device": (0, 256, 3)} for n in (1, last, last + 1)]
+    names = [kernels(launches, "kp_reduce_main")[0][0] for _, launches in fake_hip.run(calls, tmp_path)]
+    assert names[0] == names[1] != names[2] and "ELi4ELi1E" in names[1], names
