@@ -131,7 +131,7 @@ def decode_steps(args) -> int:
         torch.cuda.synchronize()
         return e0.elapsed_time(e1) / reps
 
-    steps = ["records ordered by sequence number (load, scatter by rank)", "paired, durations and histogram",
+    steps = ["records checked against the tags of their slots, those elsewhere put in place", "paired, durations and histogram",
              "paired records counted into time cells", "prefix sum over the cells", "records placed cell by cell",
              "ranked inside their cell (only without the register sort)", "sorted sequence written (likewise)",
              "register sort of the windows, region-pair overlap"]

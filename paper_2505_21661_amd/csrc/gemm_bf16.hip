@@ -753,7 +753,7 @@ __global__ __launch_bounds__(kBigWaves * 64) void kp_gemm_big(GemmArgs g) {
   // wait for this wave's LDS traffic and for the other waves.  Four sites and eight records per K step.
   // With all waves behind one barrier in one order the LDS writes (800 cycles of the CU), the loads (1024 of its one unit) and
   // the MFMAs (2112 of a SIMD) of a K step add up to 3380 ticks.  Waves 4 to 7 half a K step behind (write, load, barrier, MFMAs)
-  // take 2048x4096x4096 recorded from 101.4 to 94.8 us, without sites 117.8 -> 116.8 at 4096x4096x4096; but their barrier then
+  // take 2048x4096x4096 recorded from 101.4 to 93.3 us, without sites 117.8 -> 116.8 at 4096x4096x4096; but their barrier then
   // stands where region 0 meets region 3, and a wave's wait would count to its loads.
   // A record site pins its place in the instruction stream (it is a scheduling fence: nothing moves across
   // the clock read).  Without sites the compiler would be free to thread the stages through one another

@@ -338,9 +338,9 @@ __global__ __launch_bounds__(1024) void kp_reduce_derive(uint64_t* out, uint32_t
 }
 
 // ------------------------------------------------------------------------------------------
-// Position p = wave*cap_wave + rank indexes the staged records.  Hardware wave h of the decoder
+// Position p = wave*cap_wave + slot.  Hardware wave h of the decoder
 // owns the 64 * NR positions from 64 * NR * h on, and lane l takes 128 j + 2 l of them and the one above it in round j,
-// so that neighbouring lanes hold neighbouring ranks.
+// so that neighbouring lanes hold neighbouring slots.
 // RINGS: slots of a ring.  MANY: more than 16 regions, which
 // the register sort does not take.
 template <int BLOCK, int NR, int TEAMS, int PLANES, int RMAX, int PERWAVE, int RINGS, bool MANY>
